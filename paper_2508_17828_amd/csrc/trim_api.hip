@@ -288,6 +288,24 @@ int fill_u32(uint32_t *p, size_t count, uint32_t v, hipStream_t st) {
     return TRIM_OK;
 }
 
+// Clusters per workgroup of the k-means update: as many as 32 (every workgroup reads all the
+// assignments), fewer until there are two workgroups per CU or one cluster is left, and never
+// more than 48 KB of float64 sums.
+template <int ABYTES>
+int launch_kmeans_update(const float *x, int64_t ns, int d, int dim, const void *assign, int64_t astride, int K, int ny,
+                         float *cent, hipStream_t st) {
+    const int cols = dim < kUpdCols ? dim : kUpdCols, nz = (dim + kUpdCols - 1) / kUpdCols;
+    int lg = kUpdMaxLog2;
+    while (lg > 0 && ((int64_t)((K + (1 << lg) - 1) >> lg) * ny * nz < 512 || ((size_t)cols << lg) * 8 > 48 * 1024)) --lg;
+    const size_t lds = kmeans_update_lds(lg, cols);
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kmeans_update_kernel<ABYTES>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(kmeans_update_kernel<ABYTES>, dim3((unsigned)((K + (1 << lg) - 1) >> lg), (unsigned)ny, (unsigned)nz),
+                       dim3(kUpdThreads), lds, st, x, ns, (int64_t)d, dim, assign, astride, K, lg, cent);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+
 constexpr int kRangeRound = 2048;   // survivor-list capacity per round in range mode
 constexpr int kRangeSplitTarget = 2048;  // aim for at least this many workgroups
 
@@ -561,18 +579,13 @@ int trim_train_pq(const float *train, int64_t ns, int32_t d, int32_t M, int32_t 
     const int dsub = d / M;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int per = kC * dsub;  // centroid coordinates per subspace
-    for (int j = 0; j < M; ++j) {
-        hipLaunchKernelGGL(kmeans_init_kernel, dim3((per + 255) / 256), dim3(256), 0, st, train, ns,
-                           (int64_t)d, j * dsub, dsub, init_rows, kC, codebooks_out + (size_t)j * per);
-    }
+    hipLaunchKernelGGL(kmeans_init_kernel, dim3((per + 255) / 256, M), dim3(256), 0, st, train, ns, (int64_t)d, dsub,
+                       init_rows, kC, codebooks_out);
     HIP_TRY(hipGetLastError());
     for (int it = 0; it < iters; ++it) {
-        const int rc = trim_encode(train, ns, d, codebooks_out, M, codes_ws, dlx_ws, stream);
+        int rc = trim_encode(train, ns, d, codebooks_out, M, codes_ws, dlx_ws, stream);
         if (rc) return rc;
-        hipLaunchKernelGGL(kmeans_update_kernel<1>, dim3((per + 255) / 256, M), dim3(256), 0, st, train,
-                           ns, (int64_t)d, 0, dsub, static_cast<const void *>(codes_ws), (int64_t)M, kC,
-                           codebooks_out);
-        HIP_TRY(hipGetLastError());
+        if ((rc = launch_kmeans_update<1>(train, ns, d, dsub, codes_ws, M, kC, M, codebooks_out, st))) return rc;
     }
     return TRIM_OK;
 }
@@ -585,16 +598,13 @@ int trim_train_ivf(const float *train, int64_t ns, int32_t d, int32_t nlist, int
     if ((int64_t)nlist * d > 0x7fffffff) return TRIM_UNSUPPORTED_SHAPE;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int per = nlist * d;
-    hipLaunchKernelGGL(kmeans_init_kernel, dim3((per + 255) / 256), dim3(256), 0, st, train, ns,
-                       (int64_t)d, 0, d, init_rows, nlist, centroids_out);
+    hipLaunchKernelGGL(kmeans_init_kernel, dim3((per + 255) / 256), dim3(256), 0, st, train, ns, (int64_t)d, d, init_rows,
+                       nlist, centroids_out);
     HIP_TRY(hipGetLastError());
     for (int it = 0; it < iters; ++it) {
-        const int rc = trim_ivf_probe(train, ns, d, centroids_out, nlist, 1, assign_ws, stream);
+        int rc = trim_ivf_probe(train, ns, d, centroids_out, nlist, 1, assign_ws, stream);
         if (rc) return rc;
-        hipLaunchKernelGGL(kmeans_update_kernel<4>, dim3((per + 255) / 256), dim3(256), 0, st, train, ns,
-                           (int64_t)d, 0, d, static_cast<const void *>(assign_ws), (int64_t)1, nlist,
-                           centroids_out);
-        HIP_TRY(hipGetLastError());
+        if ((rc = launch_kmeans_update<4>(train, ns, d, d, assign_ws, 1, nlist, 1, centroids_out, st))) return rc;
     }
     return TRIM_OK;
 }
@@ -610,9 +620,8 @@ int trim_estimate_gamma(const trim_index_view *index, const int32_t *sample_rows
     if (!index->base || !index->codes || !index->codebooks || !sample_rows || !sample_queries || !gamma_out)
         return TRIM_INVALID_ARG;
     if (!aligned16(sample_queries)) return TRIM_INVALID_ARG;
-    int npow2 = 1;
-    while (npow2 < Q) npow2 <<= 1;
-    const size_t lds = ((size_t)2 * index->d + npow2) * 4;
+    const int per = S > 1 && gamma_lds(2, index->d, Q) + 1024 <= kLdsBytes ? 2 : 1;
+    const size_t lds = gamma_lds(per, index->d, Q);
     if (lds + 1024 > kLdsBytes) return TRIM_UNSUPPORTED_SHAPE;
     hipStream_t st = static_cast<hipStream_t>(stream);
     int rc = fill_u32(reinterpret_cast<uint32_t *>(gamma_out), 1, 0x7f800000u, st);  // +inf
@@ -620,15 +629,15 @@ int trim_estimate_gamma(const trim_index_view *index, const int32_t *sample_rows
     GammaArgs a{};
     a.base = index->base; a.codes = index->codes; a.codebooks = index->codebooks;
     a.rows = sample_rows; a.queries = sample_queries; a.n = index->n; a.d = index->d; a.M = index->M;
-    a.Q = Q; a.npow2 = npow2;
+    a.S = S; a.Q = Q;
     long m = (long)std::ceil((double)p * (double)Q);
     if (m < 1) m = 1;
     if (m > Q) m = Q;
     a.rank = (int32_t)(Q - m);
     a.gamma_x = gamma_x_out; a.gamma_bits = reinterpret_cast<uint32_t *>(gamma_out);
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(gamma_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL(gamma_kernel, dim3((unsigned)S), dim3(256), lds, st, a);
+    void (*fn)(GammaArgs) = per == 2 ? gamma_kernel<2> : gamma_kernel<1>;
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(fn, dim3((unsigned)((S + per - 1) / per)), dim3(kGammaThreads), lds, st, a);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
 }
@@ -708,20 +717,15 @@ int trim_fs_train_pq(const float *train, int64_t ns, int32_t d, int32_t M, int32
     if ((size_t)2 * kC4 * dsub * 4 > 64 * 1024) return TRIM_UNSUPPORTED_SHAPE;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int per = kC4 * dsub;  // centroid coordinates per subspace
-    for (int j = 0; j < M; ++j) {
-        hipLaunchKernelGGL(kmeans_init_kernel, dim3((per + 255) / 256), dim3(256), 0, st, train, ns,
-                           (int64_t)d, j * dsub, dsub, init_rows, kC4, codebooks_out + (size_t)j * per);
-    }
+    hipLaunchKernelGGL(kmeans_init_kernel, dim3((per + 255) / 256, M), dim3(256), 0, st, train, ns, (int64_t)d, dsub,
+                       init_rows, kC4, codebooks_out);
     HIP_TRY(hipGetLastError());
     for (int it = 0; it < iters; ++it) {
         hipLaunchKernelGGL(encode_fs_kernel<false>, dim3((unsigned)((ns + 255) / 256)), dim3(256),
                            (size_t)2 * kC4 * dsub * 4, st, train, ns, d, codebooks_out, M, dsub, assign_ws,
                            static_cast<float *>(nullptr));
         HIP_TRY(hipGetLastError());
-        hipLaunchKernelGGL(kmeans_update_kernel<1>, dim3((per + 255) / 256, M), dim3(256), 0, st, train,
-                           ns, (int64_t)d, 0, dsub, static_cast<const void *>(assign_ws), (int64_t)M, kC4,
-                           codebooks_out);
-        HIP_TRY(hipGetLastError());
+        if (const int rc = launch_kmeans_update<1>(train, ns, d, dsub, assign_ws, M, kC4, M, codebooks_out, st)) return rc;
     }
     return TRIM_OK;
 }

@@ -1,0 +1,69 @@
+"""Index construction and calibration kernels at the edges of their tiles, against the oracle."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def T():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2508_17828_amd import trim
+    trim.lib()
+    return trim
+
+
+# rows around the 8192-row chunks of the update; clusters that leave a last group partly empty; a row
+# longer than one 1024-column slice; one cluster that takes nearly everything
+@pytest.mark.parametrize("ns,d,nlist", [(8191, 8, 7), (8193, 12, 33), (16385, 4, 130), (9000, 1028, 5)])
+def test_update_of_coarse_centroids(T, oracle, ns, d, nlist):
+    import torch
+    from oracle import index_build
+    rng = np.random.default_rng(ns)
+    x = rng.standard_normal((ns, d)).astype(np.float32)
+    x[ns // 4:] *= np.float32(0.01)
+    init = rng.choice(ns, nlist, replace=False).astype(np.int32)
+    want = index_build.train_ivf_fixed(x, nlist, 2, init)
+    got = T.trim_train_ivf(torch.from_numpy(x).cuda(), nlist, 2, torch.from_numpy(init).cuda()).cpu().numpy()
+    np.testing.assert_array_equal(got.view(np.uint32), want.view(np.uint32))
+
+
+@pytest.mark.parametrize("ns,d,M,bits", [(8192, 16, 4, 8), (8200, 20, 4, 8), (300, 64, 4, 8), (8300, 8, 4, 4)])
+def test_update_of_codebooks(T, oracle, ns, d, M, bits):
+    import torch
+    from oracle import index_build
+    rng = np.random.default_rng(d)
+    x = rng.standard_normal((ns, d)).astype(np.float32)
+    x[: ns // 2] = x[0]                     # one cluster per subspace takes half of the rows
+    K = 256 if bits == 8 else 16
+    init = rng.choice(ns, K, replace=False).astype(np.int32)
+    fn = T.trim_train_pq if bits == 8 else T.trim_fs_train_pq
+    ref = index_build.train_pq_fixed if bits == 8 else index_build.train_pq_fs_fixed
+    want = ref(x, M, 2, init)
+    got = fn(torch.from_numpy(x).cuda(), M, 2, torch.from_numpy(init).cuda()).cpu().numpy()
+    np.testing.assert_array_equal(got.view(np.uint32), want.view(np.uint32))
+
+
+# one and many queries, an odd vector left over, vectors longer than a half wave's step, values too
+# many for two vectors' worth of LDS, and a rank at either end
+@pytest.mark.parametrize("S,Q,d,M,p", [(1, 1, 8, 4, 0.5), (3, 7, 128, 32, 1.0), (5, 1000, 260, 20, 0.0),
+                                       (2, 16384, 1536, 192, 0.9), (3, 9, 4, 4, 0.6)])
+def test_gamma_rank(T, S, Q, d, M, p):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(S * 1000 + Q)
+    base = torch.randn((50, d), device="cuda", generator=g)
+    cb = torch.randn((M, 256, d // M), device="cuda", generator=g)
+    q = torch.randn((Q, d), device="cuda", generator=g)
+    if S == 3 and Q == 9:
+        q[:] = q[0]                          # every value the same
+    codes, dlx = T.trim_encode(base, cb)
+    rows = torch.arange(S, device="cuda", dtype=torch.int32)
+    gamma, each = T.trim_estimate_gamma(T.Index(base, codes, dlx, cb), rows, q, p)
+    land = torch.stack([cb[j][codes[:S, j].long()] for j in range(M)], 1).reshape(S, d).double()
+    u, w = base[:S].double() - land, q.double()[None] - land[:, None]
+    cos = (w * u[:, None]).sum(-1) / (w.norm(dim=-1) * u.norm(dim=-1)[:, None])
+    m = min(Q, max(1, int(np.ceil(p * Q))))
+    want = (1.0 - cos).sort(dim=1).values[:, Q - m]
+    np.testing.assert_allclose(each.cpu().numpy(), want.cpu().numpy(), atol=2e-5)
+    assert gamma.item() == max(0.0, each.min().item())
