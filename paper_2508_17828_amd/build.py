@@ -16,6 +16,9 @@ FLAGS = [
     # no packed-fp32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wextra", "-Wno-unused-parameter",
+    # matrix-core results stay in vector registers (the kernels that use them have room, and every
+    # result is read by the vector ALU right away)
+    "-mllvm", "-amdgpu-mfma-vgpr-form=1",
     # per-kernel registers, spills and static LDS, checked below
     "-Rpass-analysis=kernel-resource-usage",
 ]

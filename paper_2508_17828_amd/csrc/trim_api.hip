@@ -306,6 +306,35 @@ int launch_kmeans_update(const float *x, int64_t ns, int d, int dim, const void 
     return TRIM_OK;
 }
 
+// Encoding with the matrix-core filter: 256 vectors per workgroup, 128 where 256 would leave fewer
+// than two workgroups per CU (a workgroup splits the centroids for its own vectors, so fewer of
+// them cost more).
+template <int D>
+int launch_encode(const float *base, int64_t n, int d, const float *codebooks, int M, uint8_t *codes, float *dlx, hipStream_t st) {
+    const bool wide = n >= 512 * kEncThreads;
+    const int per = wide ? kEncThreads : kEncThreads / 2;
+    void (*fn)(const float *, int64_t, int, const float *, int, uint8_t *, float *) =
+        wide ? encode_mfma_kernel<D, 2> : encode_mfma_kernel<D, 1>;
+    const size_t lds = wide ? encode_lds<D, 2>() : encode_lds<D, 1>();
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(fn, dim3((unsigned)((n + per - 1) / per)), dim3(kEncThreads), lds, st, base, n, d, codebooks, M, codes, dlx);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+
+template <bool PACKED>
+int launch_encode_fs(const float *base, int64_t n, int d, const float *codebooks, int m, uint8_t *codes, float *dlx, hipStream_t st) {
+    const int dsub = d / m;
+    if (dsub == 2)
+        hipLaunchKernelGGL(encode_fs2_kernel<PACKED>, dim3((unsigned)((n + kFsRows - 1) / kFsRows)), dim3(kFsRows), 0, st, base,
+                           n, d, codebooks, m, codes, dlx);
+    else
+        hipLaunchKernelGGL(encode_fs_kernel<PACKED>, dim3((unsigned)((n + 255) / 256)), dim3(256), (size_t)2 * kC4 * dsub * 4,
+                           st, base, n, d, codebooks, m, dsub, codes, dlx);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+
 constexpr int kRangeRound = 2048;   // survivor-list capacity per round in range mode
 constexpr int kRangeSplitTarget = 2048;  // aim for at least this many workgroups
 
@@ -487,14 +516,15 @@ int trim_encode(const float *base, int64_t n, int32_t d, const float *codebooks,
     if (!base || !codebooks || !codes_out || !dlx_out) return TRIM_INVALID_ARG;
     if (reinterpret_cast<uintptr_t>(codes_out) & 3u) return TRIM_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const dim3 grid((unsigned)((n + 255) / 256)), block(256);
-    const size_t lds = (size_t)kC * dsub * 4;
-    if (dsub == 4)
-        hipLaunchKernelGGL(encode_kernel<4>, grid, block, lds, st, base, n, d, codebooks, M, dsub, codes_out, dlx_out);
-    else if (dsub == 8)
-        hipLaunchKernelGGL(encode_kernel<8>, grid, block, lds, st, base, n, d, codebooks, M, dsub, codes_out, dlx_out);
-    else
-        hipLaunchKernelGGL(encode_kernel<0>, grid, block, lds, st, base, n, d, codebooks, M, dsub, codes_out, dlx_out);
+    switch (dsub) {
+        case 4: return launch_encode<4>(base, n, d, codebooks, M, codes_out, dlx_out, st);
+        case 5: return launch_encode<5>(base, n, d, codebooks, M, codes_out, dlx_out, st);
+        case 6: return launch_encode<6>(base, n, d, codebooks, M, codes_out, dlx_out, st);
+        case 8: return launch_encode<8>(base, n, d, codebooks, M, codes_out, dlx_out, st);
+        default: break;
+    }
+    hipLaunchKernelGGL(encode_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), (size_t)kC * dsub * 4, st, base, n, d,
+                       codebooks, M, dsub, codes_out, dlx_out);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
 }
@@ -701,11 +731,7 @@ int trim_fs_encode(const float *base, int64_t n, int32_t d, const float *codeboo
     if ((size_t)2 * kC4 * dsub * 4 > 64 * 1024) return TRIM_UNSUPPORTED_SHAPE;
     if (n == 0) return TRIM_OK;
     if (!base || !codebooks || !codes_out || !dlx_out) return TRIM_INVALID_ARG;
-    hipLaunchKernelGGL(encode_fs_kernel<true>, dim3((unsigned)((n + 255) / 256)), dim3(256),
-                       (size_t)2 * kC4 * dsub * 4, static_cast<hipStream_t>(stream), base, n, d, codebooks,
-                       M, dsub, codes_out, dlx_out);
-    HIP_TRY(hipGetLastError());
-    return TRIM_OK;
+    return launch_encode_fs<true>(base, n, d, codebooks, M, codes_out, dlx_out, static_cast<hipStream_t>(stream));
 }
 
 int trim_fs_train_pq(const float *train, int64_t ns, int32_t d, int32_t M, int32_t iters,
@@ -721,10 +747,7 @@ int trim_fs_train_pq(const float *train, int64_t ns, int32_t d, int32_t M, int32
                        init_rows, kC4, codebooks_out);
     HIP_TRY(hipGetLastError());
     for (int it = 0; it < iters; ++it) {
-        hipLaunchKernelGGL(encode_fs_kernel<false>, dim3((unsigned)((ns + 255) / 256)), dim3(256),
-                           (size_t)2 * kC4 * dsub * 4, st, train, ns, d, codebooks_out, M, dsub, assign_ws,
-                           static_cast<float *>(nullptr));
-        HIP_TRY(hipGetLastError());
+        if (const int rc = launch_encode_fs<false>(train, ns, d, codebooks_out, M, assign_ws, nullptr, st)) return rc;
         if (const int rc = launch_kmeans_update<1>(train, ns, d, dsub, assign_ws, M, kC4, M, codebooks_out, st)) return rc;
     }
     return TRIM_OK;

@@ -708,17 +708,259 @@ __global__ __launch_bounds__(256) void gamma_normal_kernel(const GammaNormalArgs
 }
 
 // ---- PQ encode (Section 3.3, preprocessing step 1) ----
-// One thread per vector; the block stages one subspace's 256 centroids in LDS at a time.
-// DSUB > 0: sub-vector length known at compile time (kept in registers); DSUB == 0: generic.
-template <int DSUB>
+// The nearest centroid by the fixed binary32 rule (encode distance, smallest index on ties).
+// Evaluating the rule for all 256 centroids is bound by the vector ALU (2 d/M operations and the
+// comparison each).  For the usual sub-vector lengths the matrix cores leave 16 centroids to it:
+//
+//   filter   S(c) = |x|^2 + m + |c|^2 - 2 x.c for all 256 centroids, 32 vectors x 32 centroids per
+//            v_mfma_f32_32x32x16_f16.  x and c are taken relative to the mean of a few centroids
+//            (their difference is what counts, and the margin below grows with their lengths), scaled by a power of two and split into a
+//            binary16 value and a binary16 remainder (22 bits); the depth of the instruction
+//            holds the three products x_hi c_hi, x_lo c_hi, x_hi c_lo of every coordinate and |c|^2 in three pieces
+//            (3 d/M + 3 slots), so the split costs no extra instruction up to d/M = 4, one more
+//            up to 9.  |x|^2 + m (m: the margin below) makes every score positive, so that
+//            scores order like their bits (integer minimum of three: half an instruction a score).
+//   groups   a lane holds the scores of 16 consecutive centroids per instruction; only the group
+//            minima are kept.  Groups whose minimum is within the margin of the best are evaluated
+//            by the exact rule, 8 centroids by each of the two lanes that share a vector; usually one group.
+//
+// The margin is twice a bound of |S - exact distance|: dropped products and remainders 3 * 2^-22 of 2 |x||c|, the
+// 16 or 32 binary32 additions of an element (2^-23 each of the sum of magnitudes, at most
+// (|x| + |c|)^2), the exact rule's own roundings (d/M + 2) * 2^-24: below 2^-18 (2^-17 with
+// two instructions) of (|x| + |c|max)^2, with what binary16 subnormals lose (both sides are
+// scaled so that |c|max is 2^12 .. 2^13) inside the same bound.  Vectors or centroids out of the scaled range get an infinite
+// margin: every group is then evaluated exactly.
+//
+// 1,000,000 x 128, d/M = 4: 0.65 ms (1.75 ms on the vector ALU alone); 83,333 x 1536, d/M = 8: 0.84 ms.
+// BLK: blocks of 32 vectors per wave (2; 1 where that leaves fewer than two workgroups per CU).
+template <int D> constexpr int kEncSteps = (3 * D + 3 + 15) / 16;
+constexpr int kEncThreads = 256;
+template <int D, int BLK>
+constexpr size_t encode_lds() {
+    return (size_t)kEncSteps<D> * 2 * kC * 16 + (size_t)(kC / 8) * (8 * D + 4) * 4 + (size_t)(kEncThreads / 2) * BLK * (4 * D + 4) * 4 + 16;
+}
+template <int D, int BLK>
+__global__ __launch_bounds__(kEncThreads) void encode_mfma_kernel(const float *__restrict__ base, int64_t n, int d,
+                                                                  const float *__restrict__ codebooks, int M,
+                                                                  uint8_t *__restrict__ codes, float *__restrict__ dlx) {
+    typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+    typedef float v16f __attribute__((ext_vector_type(16)));
+    constexpr int KS = kEncSteps<D>, NX = kEncThreads / 2 * BLK, XS = 4 * D + 4;
+    static_assert(3 * D + 3 <= 16 * KS, "slots");
+    extern __shared__ __align__(16) unsigned char smem[];
+    h8 *frag = reinterpret_cast<h8 *>(smem);                           // [KS][2][256]: 8 slots of one centroid
+    // the centroids themselves, eight to a run of 8 D + 4 values: the runs that lanes with different
+    // groups read begin in different banks
+    float *cf = reinterpret_cast<float *>(frag + KS * 2 * kC);         // [32][8 D + 4]
+    float *xt = cf + (kC / 8) * (8 * D + 4);                                           // [NX][XS] four sub-vectors of every vector
+    float *wmax = xt + NX * XS;                                        // [4]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int col = lane & 31, half = lane >> 5;
+    const int64_t x0 = (int64_t)blockIdx.x * NX;
+    const bool vec_rows = (d & 3) == 0 && (reinterpret_cast<uintptr_t>(base) & 15u) == 0;
+    // where this thread's centroid sits in its 32-row tile: a lane of the result holds rows
+    // 8 q + 4 half + s, which are made the consecutive centroids 16 half + 4 q + s
+    const int my_row = (tid & ~31) | (((tid >> 2) & 3) << 3) | (((tid >> 4) & 1) << 2) | (tid & 3);
+    float c[D];
+#pragma unroll
+    for (int t = 0; t < D; ++t) c[t] = codebooks[(size_t)tid * D + t];
+    float tot[BLK];
+    uint32_t packed[BLK];
+#pragma unroll
+    for (int b = 0; b < BLK; ++b) { tot[b] = 0.0f; packed[b] = 0; }
+    for (int j = 0; j < M; ++j) {
+        // (the same values in every lane: scalar loads)
+        float mu[D];
+#pragma unroll
+        for (int t = 0; t < D; ++t) {
+            float sum = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sum = sum + codebooks[((size_t)j * kC + 32 * i) * D + t];
+            mu[t] = sum * 0.125f;
+        }
+        float n2 = 0.0f, cc[D];
+#pragma unroll
+        for (int t = 0; t < D; ++t) { cc[t] = c[t] - mu[t]; n2 = __builtin_fmaf(cc[t], cc[t], n2); }
+        float m = n2;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, off));
+        if (lane == 0) wmax[wave] = m;
+        __syncthreads();    // the previous subspace is done with; wmax is there
+        const float max2 = __builtin_fmaxf(__builtin_fmaxf(wmax[0], wmax[1]), __builtin_fmaxf(wmax[2], wmax[3]));
+        const bool usable = max2 > 1e-30f && max2 < 1e30f;
+        // 2^k with 2^24 <= 2^2k max2 < 2^26
+        const int k = usable ? (25 - (int)((__float_as_uint(max2) >> 23) - 127)) >> 1 : 0;
+        const float sc = __uint_as_float((uint32_t)(k + 127) << 23);
+        {
+            _Float16 slot[KS * 16];
+#pragma unroll
+            for (int i = 0; i < KS * 16; ++i) slot[i] = (_Float16)0.0f;
+#pragma unroll
+            for (int t = 0; t < D; ++t) {
+                const float v = -2.0f * (cc[t] * sc);
+                const _Float16 hi = (_Float16)v;
+                const _Float16 lo = (_Float16)(v - (float)hi);
+                slot[t] = hi;
+                slot[D + t] = hi;
+                slot[2 * D + t] = lo;
+            }
+            const float q2 = (n2 * sc) * sc * (1.0f / 4096.0f);       // (the vector's side of these slots is 4096)
+            const _Float16 p1 = (_Float16)q2;
+            const _Float16 p2 = (_Float16)(q2 - (float)p1);
+            const _Float16 p3 = (_Float16)((q2 - (float)p1) - (float)p2);
+            slot[3 * D] = p1;
+            slot[3 * D + 1] = p2;
+            slot[3 * D + 2] = p3;
+#pragma unroll
+            for (int i = 0; i < KS * 2; ++i) {
+                h8 f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) f[e] = slot[8 * i + e];
+                frag[i * kC + my_row] = f;
+            }
+#pragma unroll
+            for (int t = 0; t < D; ++t) cf[(tid >> 3) * (8 * D + 4) + (tid & 7) * D + t] = c[t];
+        }
+        if ((j & 3) == 0) {     // the next four sub-vectors of the workgroup's vectors
+            if (vec_rows) {
+                for (int e = tid; e < NX * D; e += kEncThreads) {
+                    const int r = e / D, g = e - r * D;
+                    const int64_t x = x0 + r < n ? x0 + r : n - 1;
+                    *reinterpret_cast<float4 *>(xt + r * XS + 4 * g) =
+                        *reinterpret_cast<const float4 *>(base + (size_t)x * d + (size_t)j * D + 4 * g);
+                }
+            } else {
+                for (int e = tid; e < NX * 4 * D; e += kEncThreads) {
+                    const int r = e / (4 * D), g = e - r * (4 * D);
+                    const int64_t x = x0 + r < n ? x0 + r : n - 1;
+                    xt[r * XS + g] = base[(size_t)x * d + (size_t)j * D + g];
+                }
+            }
+        }
+        __syncthreads();
+        if (j + 1 < M) {
+#pragma unroll
+            for (int t = 0; t < D; ++t) c[t] = codebooks[((size_t)(j + 1) * kC + tid) * D + t];
+        }
+        const float cmax = trim::sqrt_rn(max2) * sc;
+#pragma unroll
+        for (int b = 0; b < BLK; ++b) {
+            const float *xr = xt + ((wave * BLK + b) * 32 + col) * XS + (j & 3) * D;
+            float x[D];
+#pragma unroll
+            for (int t = 0; t < D; ++t) x[t] = xr[t];
+            float xn2 = 0.0f, xmax = 0.0f;
+            _Float16 slot[KS * 16];
+#pragma unroll
+            for (int i = 0; i < KS * 16; ++i) slot[i] = (_Float16)0.0f;
+#pragma unroll
+            for (int t = 0; t < D; ++t) {
+                const float v = (x[t] - mu[t]) * sc;
+                const _Float16 hi = (_Float16)v;
+                slot[t] = hi;
+                slot[D + t] = (_Float16)(v - (float)hi);
+                slot[2 * D + t] = hi;
+                xn2 = __builtin_fmaf(v, v, xn2);
+                xmax = __builtin_fmaxf(xmax, __builtin_fabsf(v));
+            }
+            slot[3 * D] = slot[3 * D + 1] = slot[3 * D + 2] = (_Float16)4096.0f;
+            const float reach = trim::sqrt_rn(xn2) + cmax;
+            float margin = reach * reach * (KS == 1 ? 1.25f / 131072.0f : 1.0f / 65536.0f);
+            if (!usable || !(xmax < 32768.0f)) margin = __builtin_inff();
+            const float bias = margin < __builtin_inff() ? xn2 + margin : 0.0f;
+            v16f start;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) start[i] = bias;
+            h8 xf[KS];
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                h8 f0, f1;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) { f0[e] = slot[16 * ks + e]; f1[e] = slot[16 * ks + 8 + e]; }
+                typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+                const u4 w0 = __builtin_bit_cast(u4, f0), w1 = __builtin_bit_cast(u4, f1);
+                u4 w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = half ? w1[e] : w0[e];
+                xf[ks] = __builtin_bit_cast(h8, w);
+            }
+            int gmin[8];
+#pragma unroll
+            for (int t = 0; t < 8; t += 2) {
+                v16f acc[2] = {start, start};
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+                        acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(frag[(ks * 2 + half) * kC + (t + u) * 32 + col], xf[ks], acc[u], 0, 0, 0);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    int g = __float_as_int(acc[u][0]);
+#pragma unroll
+                    for (int i = 1; i < 16; ++i) g = g < __float_as_int(acc[u][i]) ? g : __float_as_int(acc[u][i]);
+                    gmin[t + u] = g;
+                }
+            }
+            int bi = gmin[0];
+#pragma unroll
+            for (int t = 1; t < 8; ++t) bi = bi < gmin[t] ? bi : gmin[t];
+            const int ob = __shfl_xor(bi, 32);
+            bi = bi < ob ? bi : ob;
+            const float thr = __int_as_float(bi) + margin;
+            uint32_t todo = 0;      // bit 2 t + half: group t of a half
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                if (!(__int_as_float(gmin[t]) > thr)) todo |= 1u << (2 * t);
+            todo <<= half;
+            todo |= (uint32_t)__shfl_xor((int)todo, 32);
+            float best = __builtin_inff();
+            int arg = 0;
+            while (__any(todo != 0)) {
+                if (todo != 0) {
+                    const int g = __ffs((int)todo) - 1;
+                    todo &= todo - 1;
+                    const int c0 = g * 16 + 8 * half;
+                    const float *run = cf + (2 * g + half) * (8 * D + 4);     // ascending from group to group: strict < keeps the smallest index
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        float acc = 0.0f;
+#pragma unroll
+                        for (int t = 0; t < D; ++t) {
+                            const float e = x[t] - run[i * D + t];
+                            acc = __builtin_fmaf(e, e, acc);
+                        }
+                        if (acc < best) { best = acc; arg = c0 + i; }
+                    }
+                }
+            }
+            const float od = __shfl_xor(best, 32);
+            const int oa = __shfl_xor(arg, 32);
+            if (od < best || (od == best && oa < arg)) { best = od; arg = oa; }
+            tot[b] = tot[b] + best;
+            packed[b] |= (uint32_t)arg << (8 * (j & 3));
+            if ((j & 3) == 3) {
+                const int64_t xi = x0 + (wave * BLK + b) * 32 + col;
+                if (half == 0 && xi < n) *reinterpret_cast<uint32_t *>(codes + (size_t)xi * M + (j - 3)) = packed[b];
+                packed[b] = 0;
+            }
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < BLK; ++b) {
+        const int64_t xi = x0 + (wave * BLK + b) * 32 + col;
+        if (half == 0 && xi < n) dlx[xi] = trim::sqrt_rn(tot[b]);
+    }
+}
+
+// Any other sub-vector length: one thread per vector; the block stages one subspace's 256
+// centroids in LDS at a time.
 __global__ __launch_bounds__(256) void encode_kernel(const float *__restrict__ base, int64_t n,
                                                      int d, const float *__restrict__ codebooks,
-                                                     int M, int dsub_rt,
+                                                     int M, int dsub,
                                                      uint8_t *__restrict__ codes,
                                                      float *__restrict__ dlx) {
     extern __shared__ __align__(16) unsigned char smem[];
     float *cb = reinterpret_cast<float *>(smem);  // [256][dsub]
-    const int dsub = DSUB > 0 ? DSUB : dsub_rt;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const bool valid = i < n;
     const float *x = base + (size_t)(valid ? i : 0) * d;
@@ -731,28 +973,13 @@ __global__ __launch_bounds__(256) void encode_kernel(const float *__restrict__ b
         __syncthreads();
         float best = __builtin_inff();
         int arg = 0;
-        if constexpr (DSUB > 0) {
-            float xr[DSUB];
-#pragma unroll
-            for (int t = 0; t < DSUB; ++t) xr[t] = x[j * DSUB + t];
-            for (int c = 0; c < kC; ++c) {
-                float acc = 0.0f;
-#pragma unroll
-                for (int t = 0; t < DSUB; ++t) {
-                    const float e = xr[t] - cb[c * DSUB + t];
-                    acc = __builtin_fmaf(e, e, acc);
-                }
-                if (acc < best) { best = acc; arg = c; }
+        for (int c = 0; c < kC; ++c) {
+            float acc = 0.0f;
+            for (int t = 0; t < dsub; ++t) {
+                const float e = x[j * dsub + t] - cb[c * dsub + t];
+                acc = __builtin_fmaf(e, e, acc);
             }
-        } else {
-            for (int c = 0; c < kC; ++c) {
-                float acc = 0.0f;
-                for (int t = 0; t < dsub; ++t) {
-                    const float e = x[j * dsub + t] - cb[c * dsub + t];
-                    acc = __builtin_fmaf(e, e, acc);
-                }
-                if (acc < best) { best = acc; arg = c; }
-            }
+            if (acc < best) { best = acc; arg = c; }
         }
         tot = tot + best;
         packed |= (uint32_t)arg << (8 * (j & 3));
@@ -765,9 +992,86 @@ __global__ __launch_bounds__(256) void encode_kernel(const float *__restrict__ b
 }
 
 // ---- PQ encode with 16 centroids per subspace (4-bit codes; Section 6.1, FastScan variants) ----
-// One thread per vector; a subspace's 16 centroids are read through the cache (every thread of
-// the block reads the same ones).  PACKED: two codes per byte, the even subspace's in the low
-// half (the stored index); else one byte per subspace (the assignments training works on).
+// PACKED: two codes per byte, the even subspace's in the low half (the stored index); else one
+// byte per subspace (the assignments training works on).
+//
+// Sub-vectors of two values (m = d/2, the paper's variant): one thread per vector; the block's
+// rows pass through the LDS 32 columns at a time (whole cache lines from memory, 16-byte reads
+// without bank conflicts), a subspace's 16 centroids are the same for every thread and arrive in
+// scalar registers.  What is left is the vector ALU: 7 operations per centroid.
+// 200,000 x 256: 0.11 ms (11.0 ms when every thread read its own row and centroids came through LDS).
+constexpr int kFsRows = 256, kFsCols = 32, kFsStride = kFsCols + 4;
+template <bool PACKED>
+__global__ __launch_bounds__(kFsRows) void encode_fs2_kernel(const float *__restrict__ base, int64_t n, int d,
+                                                             const float *__restrict__ codebooks, int m,
+                                                             uint8_t *__restrict__ codes, float *__restrict__ dlx) {
+    __shared__ __align__(16) float xt[kFsRows * kFsStride];
+    const int64_t x0 = (int64_t)blockIdx.x * kFsRows, i = x0 + threadIdx.x;
+    const bool valid = i < n;
+    const bool vec_rows = (d & 3) == 0 && (reinterpret_cast<uintptr_t>(base) & 15u) == 0;
+    const int per_row = PACKED ? m / 2 : m;     // bytes
+    const bool vec_out = per_row % (PACKED ? 8 : 16) == 0 && (reinterpret_cast<uintptr_t>(codes) & (PACKED ? 7u : 15u)) == 0;
+    float tot = 0.0f;
+    for (int c0 = 0; c0 < d; c0 += kFsCols) {
+        const int cols = d - c0 < kFsCols ? d - c0 : kFsCols;
+        __syncthreads();
+        if (vec_rows) {
+            for (int e = threadIdx.x; e < kFsRows * (kFsCols / 4); e += kFsRows) {
+                const int r = e / (kFsCols / 4), g = e % (kFsCols / 4);
+                const int64_t x = x0 + r < n ? x0 + r : n - 1;
+                if (4 * g < cols)
+                    *reinterpret_cast<float4 *>(xt + r * kFsStride + 4 * g) =
+                        *reinterpret_cast<const float4 *>(base + (size_t)x * d + c0 + 4 * g);
+            }
+        } else {
+            for (int e = threadIdx.x; e < kFsRows * kFsCols; e += kFsRows) {
+                const int r = e / kFsCols, g = e % kFsCols;
+                const int64_t x = x0 + r < n ? x0 + r : n - 1;
+                if (g < cols) xt[r * kFsStride + g] = base[(size_t)x * d + c0 + g];
+            }
+        }
+        __syncthreads();
+        uint32_t out[PACKED ? 2 : 4] = {};
+        const float *xr = xt + threadIdx.x * kFsStride;
+#pragma clang loop unroll(disable)
+        for (int wd = 0; wd < (PACKED ? 2 : 4); ++wd) {    // output words: 8 packed codes, or 4 bytes
+            constexpr int kPer = PACKED ? 8 : 4;
+            uint32_t word = 0;
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {               // one subspace: two values
+                const int q = wd * kPer + u;
+                if (2 * q < cols) {
+                    const float2 xv = *reinterpret_cast<const float2 *>(xr + 2 * q);
+                    const float *cb = codebooks + (size_t)(c0 / 2 + q) * kC4 * 2;
+                    float best = __builtin_inff();
+                    int arg = 0;
+#pragma unroll
+                    for (int c = 0; c < kC4; ++c) {
+                        float e, acc = 0.0f;
+                        e = xv.x - cb[2 * c]; acc = __builtin_fmaf(e, e, acc);
+                        e = xv.y - cb[2 * c + 1]; acc = __builtin_fmaf(e, e, acc);
+                        if (acc < best) { best = acc; arg = c; }
+                    }
+                    tot = tot + best;
+                    word |= (uint32_t)arg << (PACKED ? 4 * u : 8 * u);
+                }
+            }
+#pragma unroll
+            for (int o = 0; o < (PACKED ? 2 : 4); ++o) out[o] = o == wd ? word : out[o];
+        }
+        if (!valid) continue;
+        uint8_t *to = codes + (size_t)i * per_row + (PACKED ? c0 / 4 : c0 / 2);
+        if (cols == kFsCols && vec_out) {
+            if constexpr (PACKED) *reinterpret_cast<uint2 *>(to) = make_uint2(out[0], out[1]);
+            else *reinterpret_cast<uint4 *>(to) = make_uint4(out[0], out[1], out[PACKED ? 0 : 2], out[PACKED ? 1 : 3]);
+        } else {
+            for (int b = 0; b < cols / (PACKED ? 4 : 2); ++b) to[b] = (uint8_t)(out[b >> 2] >> (8 * (b & 3)));
+        }
+    }
+    if (valid && dlx) dlx[i] = trim::sqrt_rn(tot);
+}
+
+// Any other sub-vector length: one thread per vector; the two subspaces of one code byte at a time in LDS.
 template <bool PACKED>
 __global__ __launch_bounds__(256) void encode_fs_kernel(const float *__restrict__ base, int64_t n, int d,
                                                         const float *__restrict__ codebooks, int m,

@@ -45,6 +45,43 @@ def test_update_of_codebooks(T, oracle, ns, d, M, bits):
     np.testing.assert_array_equal(got.view(np.uint32), want.view(np.uint32))
 
 
+# every sub-vector length with the matrix-core filter and one without; rows around the workgroup's 128
+# and 256 vectors; unaligned rows; ties, all-zero centroids, magnitudes outside the filter's range
+@pytest.mark.parametrize("dsub,M,n", [(4, 4, 1), (4, 8, 129), (5, 4, 255), (6, 4, 700), (8, 8, 1000), (7, 4, 300),
+                                      (4, 4, 131073), (8, 4, 131100)])
+def test_encode_filter(T, oracle, dsub, M, n):
+    import torch
+    rng = np.random.default_rng(dsub * 1000 + n)
+    d = dsub * M
+    x = rng.standard_normal((n, d)).astype(np.float32)
+    cb = rng.standard_normal((M, 256, dsub)).astype(np.float32)
+    cb[0, 200:] = cb[0, :56]                       # ties: the smaller index wins
+    cb[1] = np.round(cb[1] * 2) / 2                # a grid: many ties
+    x[: n // 2, dsub: 2 * dsub] = np.round(x[: n // 2, dsub: 2 * dsub] * 2) / 2 + 0.25
+    cb[2] = 0 if n % 2 else cb[2] * np.float32(1e-3) + np.float32(100)   # zeros / a far, tight cloud
+    cb[3] *= np.float32(1e-20) if n % 3 else np.float32(1e17)
+    x[n // 3, :dsub] = 3e6                         # a vector far beyond the centroids
+    rc, rd = oracle.encode(x, cb)
+    codes, dlx = T.trim_encode(torch.from_numpy(x).cuda(), torch.from_numpy(cb).cuda())
+    np.testing.assert_array_equal(codes.cpu().numpy(), rc)
+    np.testing.assert_array_equal(dlx.cpu().numpy().view(np.uint32), rd.view(np.uint32))
+
+
+# 4-bit codes: sub-vectors of two values (whole and ragged 32-column slices, odd row counts) and of four
+@pytest.mark.parametrize("d,m,n", [(128, 64, 257), (36, 18, 100), (24, 12, 1), (100, 50, 513), (64, 16, 300)])
+def test_encode_four_bit(T, d, m, n):
+    import torch
+    from oracle import trim_oracle_fs
+    rng = np.random.default_rng(d + n)
+    x = rng.standard_normal((n, d)).astype(np.float32)
+    cb = rng.standard_normal((m, 16, d // m)).astype(np.float32)
+    cb[0, 8:] = cb[0, :8]
+    rc, rd = trim_oracle_fs.encode(x, cb)
+    codes, dlx = T.trim_fs_encode(torch.from_numpy(x).cuda(), torch.from_numpy(cb).cuda())
+    np.testing.assert_array_equal(codes.cpu().numpy(), rc)
+    np.testing.assert_array_equal(dlx.cpu().numpy().view(np.uint32), rd.view(np.uint32))
+
+
 # one and many queries, an odd vector left over, vectors longer than a half wave's step, values too
 # many for two vectors' worth of LDS, and a rank at either end
 @pytest.mark.parametrize("S,Q,d,M,p", [(1, 1, 8, 4, 0.5), (3, 7, 128, 32, 1.0), (5, 1000, 260, 20, 0.0),
