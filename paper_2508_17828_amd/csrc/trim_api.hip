@@ -891,6 +891,24 @@ int trim_ivf_probe(const float *queries, int64_t nq, int32_t d, const float *cen
     if (!queries || !centroids || !probes_out || !aligned16(centroids)) return TRIM_INVALID_ARG;
     if (nq > 0x7fffffff) return TRIM_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    // The nearest list of many vectors: scored on the matrix cores.  Below 4096 vectors fewer than 16
+    // workgroups would do it, and below 64 lists a 256-wide tile is mostly padding.
+    if (nprobe == 1 && nq >= 4096 && nlist >= 64 && d <= kAsgMaxD && aligned16(queries)) {
+        const size_t lds1 = assign_lds(d), lds2 = (size_t)8 * d * 4;
+        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(assign_mfma_kernel),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1));
+        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(assign_fix_kernel),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2));
+        hipLaunchKernelGGL(assign_mfma_kernel, dim3((unsigned)((nq + kAsgTile - 1) / kAsgTile)), dim3(kAsgThreads), lds1, st,
+                           queries, nq, d, centroids, nlist, probes_out);
+        HIP_TRY(hipGetLastError());
+        int span = kFixSpan;
+        while (span > 64 && nq / span < 512) span >>= 1;     // (two workgroups per CU, where there are so many vectors)
+        hipLaunchKernelGGL(assign_fix_kernel, dim3((unsigned)((nq + span - 1) / span)), dim3(kFixThreads), lds2, st,
+                           queries, nq, d, centroids, nlist, span, probes_out);
+        HIP_TRY(hipGetLastError());
+        return TRIM_OK;
+    }
     void (*fn)(const float *, int64_t, int, const float *, int, int, int, int32_t *) =
         qt == 8 ? ivf_probe_kernel<8> : qt == 4 ? ivf_probe_kernel<4> : qt == 2 ? ivf_probe_kernel<2> : ivf_probe_kernel<1>;
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(fn),

@@ -248,16 +248,20 @@ __global__ void kmeans_init_kernel(const float *__restrict__ x, int64_t ns, int6
 // (a PQ subspace; grid.y) uses element y of every row's assignments, columns y*dim.., centroid block y.
 //
 // A workgroup serves 2^cg_log2 clusters.  A chunk of kChunk assignments is put in cluster order
-// by a stable counting sort (ranks inside a wave by matching ballots, wave offsets through LDS),
-// then a thread per (cluster, coordinate) adds its rows, eight loads in flight.  What is left is
+// by a stable counting sort (ranks inside a wave by matching ballots, wave offsets through LDS);
+// then (the next chunk's assignments are on their way meanwhile) a thread per (cluster, coordinate)
+// adds its rows, straight from memory where that keeps half of the threads busy (long rows),
+// else from LDS, where all threads bring the rows found together.  What is left is
 // the scan of the assignments by every workgroup (L2 reads) and one gather of each row: 65,536
-// rows, 32 x 256 x 4 coordinates: 0.144 ms per iteration (4.28 when each coordinate's thread compared
-// every row with its cluster); 1024 x 128 coordinates: 0.065 ms (3.43).
+// rows, 32 x 256 x 4 coordinates: 0.136 ms per iteration (4.28 when each coordinate's thread compared
+// every row with its cluster); 1024 x 128 coordinates: 0.067 ms (3.43).
 constexpr int kUpdThreads = 512, kUpdPer = 16, kUpdChunk = kUpdThreads * kUpdPer;
 constexpr int kUpdMaxLog2 = 5;
-constexpr int kUpdCols = 1024;   // coordinates per workgroup at most (grid.z: slices of that many)
+constexpr int kUpdVals = 8192;   // row values in LDS at a time
+constexpr int kUpdCols = 256;    // coordinates per workgroup at most (grid.z: slices of that many)
+__host__ __device__ inline bool kmeans_update_direct(int cg_log2, int cols) { return (cols << cg_log2) >= kUpdThreads / 2; }
 __host__ __device__ inline size_t kmeans_update_lds(int cg_log2, int cols) {
-    return ((size_t)cols << cg_log2) * 8 + (size_t)kUpdChunk * 2 + (((size_t)kUpdThreads / kWave + 2) * 4 << cg_log2) + 16;
+    return ((size_t)cols << cg_log2) * 8 + (size_t)kUpdChunk * 2 + (kmeans_update_direct(cg_log2, cols) ? 0 : (size_t)kUpdVals * 4) + (((size_t)kUpdThreads / kWave + 2) * 4 << cg_log2) + 16;
 }
 template <int ABYTES>
 __global__ __launch_bounds__(kUpdThreads) void kmeans_update_kernel(const float *__restrict__ x, int64_t ns,
@@ -269,7 +273,10 @@ __global__ __launch_bounds__(kUpdThreads) void kmeans_update_kernel(const float 
     extern __shared__ __align__(16) unsigned char smem[];
     const int CG = 1 << cg_log2;
     const int t0 = blockIdx.z * kUpdCols, cols = dim - t0 < kUpdCols ? dim - t0 : kUpdCols;
-    double *sums = reinterpret_cast<double *>(smem);                       // [CG][cols]
+    float *vals = reinterpret_cast<float *>(smem);                         // [rows][cols]
+    // (the last slice of columns may be narrower than the others: the launch's layout is that of the first)
+    const bool direct = kmeans_update_direct(cg_log2, dim < kUpdCols ? dim : kUpdCols);
+    double *sums = reinterpret_cast<double *>(vals + (direct ? 0 : kUpdVals));   // [CG][cols]
     int *wcount = reinterpret_cast<int *>(sums + (size_t)CG * cols);       // [kWaves][CG]
     int *rows_of = wcount + kWaves * CG;                                   // [CG] rows per cluster so far
     int *start = rows_of + CG;                                             // [CG + 1] runs of list[]
@@ -282,9 +289,9 @@ __global__ __launch_bounds__(kUpdThreads) void kmeans_update_kernel(const float 
     for (int c = tid; c < CG; c += kUpdThreads) rows_of[c] = 0;
     int *mine = wcount + wave * CG;
     const unsigned long long below = (1ull << lane) - 1ull;
-    for (int64_t i0 = 0; i0 < ns; i0 += kUpdChunk) {
-        // a wave takes kUpdPer x 64 consecutive rows, 64 at a time in row order
-        int a[kUpdPer], rank[kUpdPer];
+    // a wave takes kUpdPer x 64 consecutive rows of a chunk, 64 at a time in row order
+    int a[kUpdPer], rank[kUpdPer];
+    auto load_chunk = [&](int64_t i0) {
 #pragma unroll
         for (int s = 0; s < kUpdPer; ++s) {
             const int64_t r = i0 + wave * (kUpdPer * kWave) + s * kWave + lane;
@@ -295,6 +302,9 @@ __global__ __launch_bounds__(kUpdThreads) void kmeans_update_kernel(const float 
                                     : static_cast<const int32_t *>(assign)[at]) - c_first;
             }
         }
+    };
+    load_chunk(0);
+    for (int64_t i0 = 0; i0 < ns; i0 += kUpdChunk) {
         for (int c = lane; c < CG; c += kWave) mine[c] = 0;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -340,32 +350,49 @@ __global__ __launch_bounds__(kUpdThreads) void kmeans_update_kernel(const float 
         for (int s = 0; s < kUpdPer; ++s)
             if ((unsigned)a[s] < (unsigned)CG)
                 list[mine[a[s]] + rank[s]] = (uint16_t)(wave * (kUpdPer * kWave) + s * kWave + lane);
+        if (i0 + kUpdChunk < ns) load_chunk(i0 + kUpdChunk);
         __syncthreads();
-        for (int e = tid; e < CG * cols; e += kUpdThreads) {
-            const int c = e / cols, t = e - c * cols;
-            const float *xt = x + (size_t)i0 * stride + t;
-            double sum = sums[e];
-            int i = start[c];
-            const int end = start[c + 1];
-            for (; i + 8 <= end; i += 8) {
-                float v[8];
+        const int found = start[CG], piece = kUpdVals / cols;
+        const float *xi = x + (size_t)i0 * stride;
+        if (direct) {
+            for (int e = tid; e < CG * cols; e += kUpdThreads) {
+                const int c = e / cols;
+                const float *xt = xi + (e - c * cols);
+                int i = start[c];
+                const int end = start[c + 1];
+                if (i >= end) continue;
+                double sum = sums[e];
+                for (; i < end; i += 8) {
+                    float v[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = xt[(size_t)list[i + u] * stride];
+                    for (int u = 0; u < 8; ++u) v[u] = xt[(size_t)list[i + u < end ? i + u : i] * stride];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) sum += (double)v[u];
+                    for (int u = 0; u < 8; ++u)
+                        if (i + u < end) sum += (double)v[u];
+                }
+                sums[e] = sum;
             }
-            if (i < end) {
-                float v[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = xt[(size_t)list[i + u < end ? i + u : i] * stride];
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (i + u < end) sum += (double)v[u];
-            }
-            sums[e] = sum;
+            continue;    // (the next chunk writes list[] and start[] after barriers that come after this)
         }
-        // (the next chunk writes list[] and start[] after barriers that every thread reaches
-        // only when it is done with this one)
+        for (int p0 = 0; p0 < found; p0 += piece) {
+            const int p1 = p0 + piece < found ? p0 + piece : found;
+            for (int e = tid; e < (p1 - p0) * cols; e += kUpdThreads) {
+                const int i = e / cols;
+                vals[e] = xi[(size_t)list[p0 + i] * stride + (e - i * cols)];
+            }
+            __syncthreads();
+            for (int e = tid; e < CG * cols; e += kUpdThreads) {
+                const int c = e / cols, t = e - c * cols;
+                const int lo = start[c] > p0 ? start[c] : p0, hi = start[c + 1] < p1 ? start[c + 1] : p1;
+                if (lo >= hi) continue;
+                double sum = sums[e];
+                const float *v = vals + t - (ptrdiff_t)p0 * cols;
+#pragma unroll 4
+                for (int i = lo; i < hi; ++i) sum += (double)v[i * cols];
+                sums[e] = sum;
+            }
+            __syncthreads();
+        }
     }
     for (int e = tid; e < CG * cols; e += kUpdThreads) {
         const int c = e / cols;
@@ -1560,6 +1587,303 @@ __global__ __launch_bounds__(512) void ivf_probe_kernel(const float *__restrict_
     for (int w = tid; w < nqt * nprobe; w += T) {
         const int qi = w / nprobe, p = w - qi * nprobe;
         probes[(size_t)(q0 + qi) * nprobe + p] = (int32_t)(keys[(size_t)qi * npow2 + p] & 0xffffffffu);
+    }
+}
+
+// ---- nearest list of many vectors (assignment of a base set, training) ----
+// The same rule as ivf_probe_kernel with one probe (exact distances in the R-order of exact_d2_half,
+// ties to the smaller id).  Measuring every pair exactly is bound by the vector ALU (two
+// operations per coordinate and pair).  Here the matrix cores score the pairs and the exact rule
+// decides only where scores are too close:
+//
+//   scores   |x - c|^2 = |x|^2 + |c|^2 - 2 x.c with x and c taken relative to the mean mu of a few centroids,
+//            the products by v_mfma_f32_32x32x16_bf16 on values split in two (hi hi + hi lo + lo hi),
+//            256 vectors x 256 centroids per workgroup and step, the split made while a 32-column
+//            slice is staged in LDS (double buffered), |x|^2 and |c|^2 summed on the way.
+//   trackers a lane keeps, per 32 x 32 tile position, the least score, its centroid and the second least: 16
+//            trackers per vector, each over a sixteenth of the centroids.
+//   decision leasts within the margin of the best are compared by the exact rule (usually there is
+//            just one: nothing to compare); a second least within the margin means that a centroid is not known:
+//            the vector is marked (-1) and assign_fix_kernel measures it against every centroid.
+//
+// Margin: twice E = (2^-16 + (3 d + 16) 2^-24) 2 |x||c|max     split, binary32 accumulation
+//                 + d 2^-24 |c|max^2 + d 2^-24 |x|^2             the norms
+//                 + (d / 32 + 8) 2^-24 (|x| + |c|max)^2          the exact rule's own roundings
+// 1,000,000 x 128 against 1024 lists: 1.33 ms with the marked vectors (9.3 ms measured exactly).
+constexpr int kAsgThreads = 512, kAsgTile = 256, kAsgSlice = 32, kAsgMaxD = 4096;
+inline size_t assign_lds(int d) { return (size_t)2 * 4 * 4 * kAsgTile * 16 + (size_t)((d + kAsgSlice - 1) / kAsgSlice * kAsgSlice) * 4 + 2 * kAsgTile * 4 + 64; }
+
+__global__ __launch_bounds__(kAsgThreads) void assign_mfma_kernel(const float *__restrict__ xs, int64_t n, int d,
+                                                                  const float *__restrict__ cent, int nlist,
+                                                                  int32_t *__restrict__ out) {
+    typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+    typedef float v16f __attribute__((ext_vector_type(16)));
+    extern __shared__ __align__(16) unsigned char smem[];
+    // a buffer: [x hi, x lo, c hi, c lo][16-column step][8-column half][256 rows] of 8 values
+    b8 *buf = reinterpret_cast<b8 *>(smem);
+    constexpr int kPart = 4 * kAsgTile, kBuf = 4 * kPart;
+    float *mu = reinterpret_cast<float *>(buf + 2 * kBuf);
+    const int dpad = (d + kAsgSlice - 1) / kAsgSlice * kAsgSlice;
+    float *xn2 = mu + dpad, *cn2 = xn2 + kAsgTile;
+    uint32_t *cmax_bits = reinterpret_cast<uint32_t *>(cn2 + kAsgTile);
+    int *namb = reinterpret_cast<int *>(cmax_bits + 1);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int col = lane & 31, half = lane >> 5;
+    const int xg = wave & 3, cg = wave >> 2;       // this wave: 64 vectors, 128 centroids of the tile
+    const int64_t x0 = (int64_t)blockIdx.x * kAsgTile;
+    for (int t = tid; t < dpad; t += kAsgThreads) {
+        float sum = 0.0f;
+        for (int i = 0; i < 16; ++i) sum += t < d ? cent[(size_t)((int64_t)i * nlist >> 4) * d + t] : 0.0f;
+        mu[t] = sum * (1.0f / 16.0f);
+    }
+    if (tid == 0) { *cmax_bits = 0; *namb = 0; }
+    __syncthreads();
+    // staging: two threads per row, 16 columns of a slice each
+    const int srow = tid >> 1, sstep = tid & 1;
+    const int64_t xr = x0 + srow < n ? x0 + srow : n - 1;
+    const float *xrow = xs + (size_t)xr * d + sstep * 16;
+    float4 xv[4], cv[4];
+    float xsum = 0.0f, csum = 0.0f;
+    auto load = [&](const float *crow, int k0) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const bool in = k0 + sstep * 16 + 4 * g < d;
+            xv[g] = in ? *reinterpret_cast<const float4 *>(xrow + k0 + 4 * g) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            cv[g] = in ? *reinterpret_cast<const float4 *>(crow + k0 + 4 * g) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
+    };
+    auto split = [&](const float (&v)[16], b8 *hi_at, b8 *lo_at) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            b8 hi, lo;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                hi[e] = (__bf16)v[8 * h + e];
+                lo[e] = (__bf16)(v[8 * h + e] - (float)hi[e]);
+            }
+            hi_at[h * kAsgTile] = hi;
+            lo_at[h * kAsgTile] = lo;
+        }
+    };
+    auto stage = [&](int which, int k0) {
+        b8 *at = buf + which * kBuf + sstep * 2 * kAsgTile + srow;
+        float vx[16], vc[16];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const float4 m = *reinterpret_cast<const float4 *>(mu + k0 + sstep * 16 + 4 * g);   // (columns past d: all zero)
+            const float ax[4] = {xv[g].x - m.x, xv[g].y - m.y, xv[g].z - m.z, xv[g].w - m.w};
+            const float ac[4] = {cv[g].x - m.x, cv[g].y - m.y, cv[g].z - m.z, cv[g].w - m.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                xsum = __builtin_fmaf(ax[e], ax[e], xsum);
+                csum = __builtin_fmaf(ac[e], ac[e], csum);
+                vx[4 * g + e] = ax[e];
+                vc[4 * g + e] = -2.0f * ac[e];
+            }
+        }
+        split(vx, at, at + kPart);
+        split(vc, at + 2 * kPart, at + 3 * kPart);
+    };
+    uint32_t m1[2][4], m2[2][4];
+    int i1[2][4];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) { m1[u][t] = m2[u][t] = 0x7f800000u; i1[u][t] = 0; }
+    float cmax2 = 0.0f;
+    const int nblk = (nlist + kAsgTile - 1) / kAsgTile, nk = dpad / kAsgSlice;
+    for (int cb = 0; cb < nblk; ++cb) {
+        const int cr = cb * kAsgTile + srow;
+        const float *crow = cent + (size_t)(cr < nlist ? cr : nlist - 1) * d + sstep * 16;
+        xsum = 0.0f;
+        csum = 0.0f;
+        v16f acc[2][4];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[u][t][i] = 0.0f;
+        load(crow, 0);
+        stage(0, 0);
+        __syncthreads();
+        for (int kc = 0; kc < nk; ++kc) {
+            if (kc + 1 < nk) load(crow, (kc + 1) * kAsgSlice);
+            const b8 *b = buf + (kc & 1) * kBuf + half * kAsgTile + col;
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                b8 xh[2], xl[2];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    xh[u] = b[ks * 2 * kAsgTile + xg * 64 + u * 32];
+                    xl[u] = b[kPart + ks * 2 * kAsgTile + xg * 64 + u * 32];
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const b8 ch = b[2 * kPart + ks * 2 * kAsgTile + cg * 128 + t * 32];
+                    const b8 cl = b[3 * kPart + ks * 2 * kAsgTile + cg * 128 + t * 32];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) acc[u][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ch, xh[u], acc[u][t], 0, 0, 0);
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) acc[u][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ch, xl[u], acc[u][t], 0, 0, 0);
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) acc[u][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cl, xh[u], acc[u][t], 0, 0, 0);
+                }
+            }
+            if (kc + 1 < nk) stage((kc + 1) & 1, (kc + 1) * kAsgSlice);
+            __syncthreads();
+        }
+        xsum += __shfl_xor(xsum, 1);
+        csum += __shfl_xor(csum, 1);
+        if (sstep == 0) {
+            xn2[srow] = xsum;
+            cn2[srow] = cr < nlist ? csum : __builtin_inff();     // (rows past the end never win)
+            if (cr < nlist) cmax2 = __builtin_fmaxf(cmax2, csum);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const float xb = xn2[xg * 64 + u * 32 + col];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float4 c2 = *reinterpret_cast<const float4 *>(cn2 + cg * 128 + t * 32 + 8 * q + 4 * half);
+                    const float cq[4] = {c2.x, c2.y, c2.z, c2.w};
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) {
+                        // (a score below zero is one within the margin of zero)
+                        const float f = __builtin_fmaxf((acc[u][t][4 * q + s] + xb) + cq[s], 0.0f);
+                        const uint32_t v = __float_as_uint(f);
+                        const bool less = v < m1[u][t];
+                        const uint32_t hi = less ? m1[u][t] : v;
+                        m2[u][t] = m2[u][t] < hi ? m2[u][t] : hi;
+                        m1[u][t] = less ? v : m1[u][t];
+                        i1[u][t] = less ? cb * 16 + 4 * q + s : i1[u][t];
+                    }
+                }
+            }
+        }
+    }
+    // the trackers of every vector side by side (over the staging buffers, which are done with)
+    uint32_t *t1 = reinterpret_cast<uint32_t *>(smem), *t2 = t1 + 16 * kAsgTile;
+    int *tc = reinterpret_cast<int *>(t2 + 16 * kAsgTile);
+    uint32_t *amb = reinterpret_cast<uint32_t *>(tc + 16 * kAsgTile);      // [256] (trackers << 8) | vector
+    atomicMax(cmax_bits, __float_as_uint(cmax2));
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int at = ((cg * 2 + half) * 4 + t) * kAsgTile + xg * 64 + u * 32 + col;
+            const int i = i1[u][t];
+            t1[at] = m1[u][t];
+            t2[at] = m2[u][t];
+            tc[at] = (i >> 4) * kAsgTile + cg * 128 + t * 32 + 8 * ((i & 15) >> 2) + 4 * half + (i & 3);
+        }
+    __syncthreads();
+    if (tid < kAsgTile && x0 + tid < n) {
+        const float c2 = __uint_as_float(*cmax_bits), x2 = xn2[tid];
+        const float xl = trim::sqrt_rn(x2), cl = trim::sqrt_rn(c2);
+        constexpr float kUlp = 1.0f / 16777216.0f;
+        const float e = (1.0f / 65536.0f + (3.0f * d + 16.0f) * kUlp) * 2.0f * xl * cl + d * kUlp * (c2 + x2) +
+                        (d / 32 + 8) * kUlp * (xl + cl) * (xl + cl);
+        uint32_t best = 0x7f800000u, sec = 0x7f800000u;
+        for (int k = 0; k < 16; ++k) {
+            const uint32_t a = t1[k * kAsgTile + tid], b = t2[k * kAsgTile + tid];
+            best = a < best ? a : best;
+            sec = b < sec ? b : sec;
+        }
+        const float thr = __uint_as_float(best) + 2.0f * e;
+        uint32_t close = 0;
+        int one = 0;
+        for (int k = 0; k < 16; ++k)
+            if (!(__uint_as_float(t1[k * kAsgTile + tid]) > thr)) { close |= 1u << k; one = tc[k * kAsgTile + tid]; }
+        if (!(e < 1e30f) || !(e > 1e-30f) || !(__uint_as_float(sec) > thr)) out[x0 + tid] = -1;
+        else if ((close & (close - 1)) == 0) out[x0 + tid] = one;
+        else amb[atomicAdd(namb, 1)] = (close << 8) | (uint32_t)tid;
+    }
+    __syncthreads();
+    const int na = *namb;
+    for (int i = tid >> 5; i < na; i += kAsgThreads >> 5) {        // a half wave per undecided vector
+        const int x = (int)(amb[i] & 255u);
+        uint32_t close = amb[i] >> 8;
+        const float *q = xs + (size_t)(x0 + x) * d;
+        unsigned long long best = ~0ull;
+        while (close) {
+            const int k = __ffs((int)close) - 1;
+            close &= close - 1;
+            const int c = tc[k * kAsgTile + x];
+            const float dist = exact_d2_half(cent + (size_t)c * d, q, d, lane & 31);
+            const unsigned long long key = ((unsigned long long)__float_as_uint(dist) << 32) | (uint32_t)c;
+            best = key < best ? key : best;
+        }
+        if ((lane & 31) == 0) out[x0 + x] = (int32_t)(best & 0xffffffffu);
+    }
+}
+
+// The vectors that assign_mfma_kernel marked: every centroid measured by the exact rule, eight
+// vectors at a time (ivf_probe_kernel's distance loop).  A workgroup looks after up to kFixSpan
+// vectors, so that even a mark in a hundred fills its groups.
+constexpr int kFixSpan = 1024, kFixThreads = 512;   // (at most kFixSpan)
+__global__ __launch_bounds__(kFixThreads) void assign_fix_kernel(const float *__restrict__ xs, int64_t n, int d,
+                                                                 const float *__restrict__ cent, int nlist,
+                                                                 int span, int32_t *__restrict__ out) {
+    constexpr int QT = 8, kRows = 4, NP = QT * kRows;
+    extern __shared__ __align__(16) unsigned char smem[];
+    float *q_lds = reinterpret_cast<float *>(smem);                      // [QT][d]
+    __shared__ int todo[kFixSpan];
+    __shared__ int count;
+    __shared__ unsigned long long best[QT];
+    const int tid = threadIdx.x, lane32 = tid & 31;
+    const int64_t x0 = (int64_t)blockIdx.x * span;
+    if (tid == 0) count = 0;
+    __syncthreads();
+    for (int i = tid; i < span; i += kFixThreads)
+        if (x0 + i < n && out[x0 + i] < 0) todo[atomicAdd(&count, 1)] = i;
+    __syncthreads();
+    const int total = count, ng = d >> 2;
+    for (int g0 = 0; g0 < total; g0 += QT) {
+        const int nqt = total - g0 < QT ? total - g0 : QT;
+        if (tid < QT) best[tid] = ~0ull;
+        for (int t = tid; t < QT * d; t += kFixThreads) {
+            const int qi = t / d;
+            q_lds[t] = xs[(size_t)(x0 + todo[g0 + (qi < nqt ? qi : 0)]) * d + (t - qi * d)];
+        }
+        __syncthreads();
+        unsigned long long mine = ~0ull;
+        for (int l0 = (tid >> 5) * kRows; l0 < nlist; l0 += (kFixThreads >> 5) * kRows) {
+            const float4 *row0 = reinterpret_cast<const float4 *>(cent + (size_t)l0 * d);
+            const int last = nlist - 1 - l0;
+            float acc[NP];
+#pragma unroll
+            for (int i = 0; i < NP; ++i) acc[i] = 0.0f;
+            for (int g = lane32; g < ng; g += 32) {
+                float4 x[kRows];
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) x[r] = row0[(size_t)(r < last ? r : last) * ng + g];
+#pragma unroll
+                for (int qi = 0; qi < QT; ++qi) {
+                    const float4 qv = *reinterpret_cast<const float4 *>(q_lds + qi * d + 4 * g);
+#pragma unroll
+                    for (int r = 0; r < kRows; ++r) {
+                        float e, a0 = acc[r * QT + qi];
+                        e = qv.x - x[r].x; a0 = __builtin_fmaf(e, e, a0);
+                        e = qv.y - x[r].y; a0 = __builtin_fmaf(e, e, a0);
+                        e = qv.z - x[r].z; a0 = __builtin_fmaf(e, e, a0);
+                        e = qv.w - x[r].w; a0 = __builtin_fmaf(e, e, a0);
+                        acc[r * QT + qi] = a0;
+                    }
+                }
+            }
+            const float dist = reduce_pairs<NP>(acc, lane32);   // lane: row (bits 3..4), vector (bits 0..2)
+            const int l = l0 + (lane32 >> 3);
+            const unsigned long long key = ((unsigned long long)__float_as_uint(dist) << 32) | (uint32_t)l;
+            if (l < nlist && key < mine) mine = key;
+        }
+        atomicMin(&best[lane32 & 7], mine);
+        __syncthreads();
+        if (tid < nqt) out[x0 + todo[g0 + tid]] = (int32_t)(best[tid] & 0xffffffffu);
+        __syncthreads();
     }
 }
 

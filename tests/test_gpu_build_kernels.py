@@ -67,6 +67,27 @@ def test_encode_filter(T, oracle, dsub, M, n):
     np.testing.assert_array_equal(dlx.cpu().numpy().view(np.uint32), rd.view(np.uint32))
 
 
+# the nearest list of many vectors: ragged vector, list and column counts, ties between lists, vectors
+# halfway between two lists, lists far from the origin, one far vector, magnitudes that overflow
+@pytest.mark.parametrize("n,d,nlist,scale", [(4096, 4, 64, 1), (4099, 128, 1024, 1), (5000, 36, 257, 1), (4353, 100, 300, 1),
+                                             (4200, 132, 70, 1e19), (4100, 64, 511, 1e-20), (4097, 768, 90, 1)])
+def test_assignment(T, oracle, n, d, nlist, scale):
+    import torch
+    rng = np.random.default_rng(n)
+    cent = rng.standard_normal((nlist, d)).astype(np.float32)
+    cent[nlist // 2:nlist // 2 + 20] = cent[:20]                              # the smaller id wins
+    cent[40:60] = cent[20:40] + np.float32(1e-3)                              # nearly the same
+    x = cent[rng.integers(0, nlist, n)] + (0.3 * rng.standard_normal((n, d))).astype(np.float32)
+    x[:500] = (cent[rng.integers(0, nlist, 500)] + cent[rng.integers(0, nlist, 500)]) / 2
+    if nlist == 300:
+        cent, x = cent * np.float32(1e-2) + np.float32(10), x * np.float32(1e-2) + np.float32(10)
+    x[77] = 1e4
+    cent, x = (cent * np.float32(scale)), (x * np.float32(scale)).astype(np.float32)
+    want = oracle.ivf_probe(x, cent, 1)
+    got = T.trim_ivf_probe(torch.from_numpy(x).cuda(), torch.from_numpy(cent).cuda(), 1).cpu().numpy()
+    np.testing.assert_array_equal(got, want)
+
+
 # 4-bit codes: sub-vectors of two values (whole and ragged 32-column slices, odd row counts) and of four
 @pytest.mark.parametrize("d,m,n", [(128, 64, 257), (36, 18, 100), (24, 12, 1), (100, 50, 513), (64, 16, 300)])
 def test_encode_four_bit(T, d, m, n):
