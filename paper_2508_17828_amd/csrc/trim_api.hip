@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdio>
@@ -313,11 +314,21 @@ template <int D>
 int launch_encode(const float *base, int64_t n, int d, const float *codebooks, int M, uint8_t *codes, float *dlx, hipStream_t st) {
     const bool wide = n >= 512 * kEncThreads;
     const int per = wide ? kEncThreads : kEncThreads / 2;
-    void (*fn)(const float *, int64_t, int, const float *, int, uint8_t *, float *) =
+    void (*fn)(const float *, int64_t, int, const float *, int, int, uint8_t *, float *) =
         wide ? encode_mfma_kernel<D, 2> : encode_mfma_kernel<D, 1>;
     const size_t lds = wide ? encode_lds<D, 2>() : encode_lds<D, 1>();
+    const int64_t blocks = (n + per - 1) / per;
+    int jper = M;       // subspaces per workgroup: all, or fewer until there are about three workgroups per CU
+    if (blocks < 384) {
+        const int64_t split = std::min<int64_t>(M / 4, (768 + blocks - 1) / blocks);
+        jper = (int)((M / 4 + split - 1) / split) * 4;
+    }
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL(fn, dim3((unsigned)((n + per - 1) / per)), dim3(kEncThreads), lds, st, base, n, d, codebooks, M, codes, dlx);
+    hipLaunchKernelGGL(fn, dim3((unsigned)blocks, (unsigned)((M + jper - 1) / jper)), dim3(kEncThreads), lds, st, base, n, d,
+                       codebooks, M, jper, codes, dlx);
+    if (jper < M && dlx)
+        hipLaunchKernelGGL(encode_dlx_kernel, dim3((unsigned)((n + kDlxRows - 1) / kDlxRows)), dim3(256), 0, st, base, n, d,
+                           codebooks, M, D, codes, dlx);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
 }
@@ -331,6 +342,22 @@ int launch_encode_fs(const float *base, int64_t n, int d, const float *codebooks
     else
         hipLaunchKernelGGL(encode_fs_kernel<PACKED>, dim3((unsigned)((n + 255) / 256)), dim3(256), (size_t)2 * kC4 * dsub * 4,
                            st, base, n, d, codebooks, m, dsub, codes, dlx);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+
+// trim_encode past its checks.  dlx may be null where the caller needs the codes only (training).
+int encode_codes(const float *base, int64_t n, int d, const float *codebooks, int M, uint8_t *codes, float *dlx, hipStream_t st) {
+    const int dsub = d / M;
+    switch (dsub) {
+        case 4: return launch_encode<4>(base, n, d, codebooks, M, codes, dlx, st);
+        case 5: return launch_encode<5>(base, n, d, codebooks, M, codes, dlx, st);
+        case 6: return launch_encode<6>(base, n, d, codebooks, M, codes, dlx, st);
+        case 8: return launch_encode<8>(base, n, d, codebooks, M, codes, dlx, st);
+        default: break;
+    }
+    hipLaunchKernelGGL(encode_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), (size_t)kC * dsub * 4, st, base, n, d,
+                       codebooks, M, dsub, codes, dlx);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
 }
@@ -515,18 +542,7 @@ int trim_encode(const float *base, int64_t n, int32_t d, const float *codebooks,
     if (n == 0) return TRIM_OK;
     if (!base || !codebooks || !codes_out || !dlx_out) return TRIM_INVALID_ARG;
     if (reinterpret_cast<uintptr_t>(codes_out) & 3u) return TRIM_INVALID_ARG;
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    switch (dsub) {
-        case 4: return launch_encode<4>(base, n, d, codebooks, M, codes_out, dlx_out, st);
-        case 5: return launch_encode<5>(base, n, d, codebooks, M, codes_out, dlx_out, st);
-        case 6: return launch_encode<6>(base, n, d, codebooks, M, codes_out, dlx_out, st);
-        case 8: return launch_encode<8>(base, n, d, codebooks, M, codes_out, dlx_out, st);
-        default: break;
-    }
-    hipLaunchKernelGGL(encode_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), (size_t)kC * dsub * 4, st, base, n, d,
-                       codebooks, M, dsub, codes_out, dlx_out);
-    HIP_TRY(hipGetLastError());
-    return TRIM_OK;
+    return encode_codes(base, n, d, codebooks, M, codes_out, dlx_out, static_cast<hipStream_t>(stream));
 }
 
 size_t trim_list_bounds_bytes(int32_t nlist, int32_t M) {
@@ -607,13 +623,16 @@ int trim_train_pq(const float *train, int64_t ns, int32_t d, int32_t M, int32_t 
     if (d % M || M % 4 || M > 65535) return TRIM_UNSUPPORTED_SHAPE;
     if (!train || !init_rows || !codebooks_out || !codes_ws || !dlx_ws) return TRIM_INVALID_ARG;
     const int dsub = d / M;
+    if (iters > 0 && (size_t)kC * dsub * 4 > 64 * 1024) return TRIM_UNSUPPORTED_SHAPE;
+    if (iters > 0 && (reinterpret_cast<uintptr_t>(codes_ws) & 3u)) return TRIM_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int per = kC * dsub;  // centroid coordinates per subspace
     hipLaunchKernelGGL(kmeans_init_kernel, dim3((per + 255) / 256, M), dim3(256), 0, st, train, ns, (int64_t)d, dsub,
                        init_rows, kC, codebooks_out);
     HIP_TRY(hipGetLastError());
     for (int it = 0; it < iters; ++it) {
-        int rc = trim_encode(train, ns, d, codebooks_out, M, codes_ws, dlx_ws, stream);
+        // (the landmark distances that the caller sees are the last iteration's)
+        int rc = encode_codes(train, ns, d, codebooks_out, M, codes_ws, it + 1 < iters ? nullptr : dlx_ws, st);
         if (rc) return rc;
         if ((rc = launch_kmeans_update<1>(train, ns, d, dsub, codes_ws, M, kC, M, codebooks_out, st))) return rc;
     }

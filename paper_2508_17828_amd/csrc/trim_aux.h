@@ -760,6 +760,9 @@ __global__ __launch_bounds__(256) void gamma_normal_kernel(const GammaNormalArgs
 //
 // 1,000,000 x 128, d/M = 4: 0.65 ms (1.75 ms on the vector ALU alone); 83,333 x 1536, d/M = 8: 0.84 ms.
 // BLK: blocks of 32 vectors per wave (2; 1 where that leaves fewer than two workgroups per CU).
+// Where there are still fewer, grid.y workgroups take jper subspaces each of the same vectors and
+// encode_dlx_kernel adds the landmark distances up afterwards (their order of summation crosses
+// all subspaces): 9,000 x 768: 0.056 + 0.044 ms (0.285 ms with one workgroup per 128 vectors).
 template <int D> constexpr int kEncSteps = (3 * D + 3 + 15) / 16;
 constexpr int kEncThreads = 256;
 template <int D, int BLK>
@@ -768,7 +771,7 @@ constexpr size_t encode_lds() {
 }
 template <int D, int BLK>
 __global__ __launch_bounds__(kEncThreads) void encode_mfma_kernel(const float *__restrict__ base, int64_t n, int d,
-                                                                  const float *__restrict__ codebooks, int M,
+                                                                  const float *__restrict__ codebooks, int M, int jper,
                                                                   uint8_t *__restrict__ codes, float *__restrict__ dlx) {
     typedef _Float16 h8 __attribute__((ext_vector_type(8)));
     typedef float v16f __attribute__((ext_vector_type(16)));
@@ -788,14 +791,15 @@ __global__ __launch_bounds__(kEncThreads) void encode_mfma_kernel(const float *_
     // where this thread's centroid sits in its 32-row tile: a lane of the result holds rows
     // 8 q + 4 half + s, which are made the consecutive centroids 16 half + 4 q + s
     const int my_row = (tid & ~31) | (((tid >> 2) & 3) << 3) | (((tid >> 4) & 1) << 2) | (tid & 3);
+    const int jlo = blockIdx.y * jper, jhi = jlo + jper < M ? jlo + jper : M;    // (multiples of four)
     float c[D];
 #pragma unroll
-    for (int t = 0; t < D; ++t) c[t] = codebooks[(size_t)tid * D + t];
+    for (int t = 0; t < D; ++t) c[t] = codebooks[((size_t)jlo * kC + tid) * D + t];
     float tot[BLK];
     uint32_t packed[BLK];
 #pragma unroll
     for (int b = 0; b < BLK; ++b) { tot[b] = 0.0f; packed[b] = 0; }
-    for (int j = 0; j < M; ++j) {
+    for (int j = jlo; j < jhi; ++j) {
         // (the same values in every lane: scalar loads)
         float mu[D];
 #pragma unroll
@@ -865,7 +869,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_mfma_kernel(const float *_
             }
         }
         __syncthreads();
-        if (j + 1 < M) {
+        if (j + 1 < jhi) {
 #pragma unroll
             for (int t = 0; t < D; ++t) c[t] = codebooks[((size_t)(j + 1) * kC + tid) * D + t];
         }
@@ -972,11 +976,43 @@ __global__ __launch_bounds__(kEncThreads) void encode_mfma_kernel(const float *_
             }
         }
     }
+    if (jper < M || !dlx) return;
 #pragma unroll
     for (int b = 0; b < BLK; ++b) {
         const int64_t xi = x0 + (wave * BLK + b) * 32 + col;
         if (half == 0 && xi < n) dlx[xi] = trim::sqrt_rn(tot[b]);
     }
+}
+
+// Landmark distances from finished codes: the same sub-distances, added in subspace order.  A
+// workgroup takes kDlxRows vectors; their sub-distances wait in LDS, slices of kDlxSub subspaces.
+constexpr int kDlxRows = 16, kDlxSub = 128;
+__global__ __launch_bounds__(256) void encode_dlx_kernel(const float *__restrict__ base, int64_t n, int d,
+                                                         const float *__restrict__ codebooks, int M, int dsub,
+                                                         const uint8_t *__restrict__ codes, float *__restrict__ dlx) {
+    __shared__ float part[kDlxRows * (kDlxSub + 1)];
+    const int64_t x0 = (int64_t)blockIdx.x * kDlxRows;
+    float tot = 0.0f;
+    for (int j0 = 0; j0 < M; j0 += kDlxSub) {
+        const int nj = M - j0 < kDlxSub ? M - j0 : kDlxSub;
+        for (int e = threadIdx.x; e < kDlxRows * nj; e += 256) {
+            const int r = e / nj, j = e - r * nj;
+            const int64_t x = x0 + r < n ? x0 + r : n - 1;
+            const float *xr = base + (size_t)x * d + (size_t)(j0 + j) * dsub;
+            const float *c = codebooks + ((size_t)(j0 + j) * kC + codes[(size_t)x * M + j0 + j]) * dsub;
+            float acc = 0.0f;
+            for (int t = 0; t < dsub; ++t) {
+                const float v = xr[t] - c[t];
+                acc = __builtin_fmaf(v, v, acc);
+            }
+            part[r * (kDlxSub + 1) + j] = acc;
+        }
+        __syncthreads();
+        if (threadIdx.x < kDlxRows)
+            for (int j = 0; j < nj; ++j) tot = tot + part[threadIdx.x * (kDlxSub + 1) + j];
+        __syncthreads();
+    }
+    if (threadIdx.x < kDlxRows && x0 + threadIdx.x < n) dlx[x0 + threadIdx.x] = trim::sqrt_rn(tot);
 }
 
 // Any other sub-vector length: one thread per vector; the block stages one subspace's 256
@@ -1015,7 +1051,7 @@ __global__ __launch_bounds__(256) void encode_kernel(const float *__restrict__ b
             packed = 0;
         }
     }
-    if (valid) dlx[i] = trim::sqrt_rn(tot);
+    if (valid && dlx) dlx[i] = trim::sqrt_rn(tot);
 }
 
 // ---- PQ encode with 16 centroids per subspace (4-bit codes; Section 6.1, FastScan variants) ----
