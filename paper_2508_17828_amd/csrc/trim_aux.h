@@ -401,46 +401,6 @@ __global__ __launch_bounds__(kUpdThreads) void kmeans_update_kernel(const float 
     }
 }
 
-// Half-wave totals of N (32, 16 or 8) lane sums per lane at once: v[i] is the calling lane's share
-// of sum i; lane l of the half wave returns the total of sum l >> (5 - log2 N).  The additions are
-// those of half_reduce, pair by pair (lane ^ 16, ^ 8, ^ 4, ^ 2, ^ 1; binary32 addition commutes,
-// so it does not matter which lane of a pair adds): while a lane still holds several sums, it
-// hands half of them to its partner at each step and keeps the other half, so N sums take
-// N - 1 exchanges (plus one per remaining step) instead of 5 N.
-template <int BIT>
-__device__ __forceinline__ float lane_xor(float x) {
-    const int v = __float_as_int(x);
-    if constexpr (BIT == 16) return __int_as_float(__builtin_amdgcn_ds_swizzle(v, 0x401F));
-    else if constexpr (BIT == 8) return __int_as_float(__builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, false));  // row rotation by 8
-    else if constexpr (BIT == 4) return __int_as_float(__builtin_amdgcn_ds_swizzle(v, 0x101F));
-    else if constexpr (BIT == 2) return __int_as_float(__builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, false));
-    else return __int_as_float(__builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, false));
-}
-template <int N, int BIT, int CAP>
-__device__ __forceinline__ void reduce_step(float (&v)[CAP], int lane32) {
-    if constexpr (N > 1) {
-        const bool up = (lane32 & BIT) != 0;   // these lanes keep the upper half of the sums
-#pragma unroll
-        for (int i = 0; i < N / 2; ++i) {
-            const float keep = up ? v[i + N / 2] : v[i];
-            const float send = up ? v[i] : v[i + N / 2];
-            v[i] = keep + lane_xor<BIT>(send);
-        }
-    } else {
-        v[0] = v[0] + lane_xor<BIT>(v[0]);
-    }
-}
-template <int N>
-__device__ __forceinline__ float reduce_pairs(float (&v)[N], int lane32) {
-    static_assert(N == 32 || N == 16 || N == 8, "sums per lane");
-    reduce_step<N, 16>(v, lane32);
-    reduce_step<(N / 2 > 1 ? N / 2 : 1), 8>(v, lane32);
-    reduce_step<(N / 4 > 1 ? N / 4 : 1), 4>(v, lane32);
-    reduce_step<(N / 8 > 1 ? N / 8 : 1), 2>(v, lane32);
-    reduce_step<(N / 16 > 1 ? N / 16 : 1), 1>(v, lane32);
-    return v[0];
-}
-
 // ---- gamma from a confidence level p (Section 3.2), empirical route ----
 // A workgroup takes kGammaRows (2; 1 where the values of two do not fit the LDS) sampled data vectors x: landmark l = PQ reconstruction of x; for
 // every sampled query the value 1 - cos(x - l, q - l); the value of the given rank is gamma_x;

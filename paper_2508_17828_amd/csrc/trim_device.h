@@ -70,18 +70,17 @@ __device__ __forceinline__ float subvec_sqdist(const float *__restrict__ x,
 // global), out at LDS or global.  All threads of the block take part.
 // FS: j0 and nj count code bytes; byte j covers subspaces 2j and 2j+1 of 16 centroids each, dsub
 // is the length of one of THOSE sub-vectors, and the entries of a byte are [2][16].
-template <bool FS = false>
-__device__ __forceinline__ void build_table_rows(float *__restrict__ out,
-                                                 const float *__restrict__ q,
-                                                 const float *__restrict__ codebooks, int dsub,
-                                                 int j0, int nj) {
+// put(e, value) takes entry e of the slab (table_rows; build_table_rows stores it).
+template <bool FS, typename Put>
+__device__ __forceinline__ void table_rows(const float *__restrict__ q, const float *__restrict__ codebooks, int dsub,
+                                           int j0, int nj, Put put) {
     const int T = blockDim.x;
     int e = threadIdx.x;
     if constexpr (FS) {
         // entry e of the slab: subspace 2*j0 + e/16, centroid e%16 -- exactly the [m][16] order
         for (; e < nj * kByteEntries<true>; e += T) {
             const int sj = 2 * j0 + (e >> 4);
-            out[e] = subvec_sqdist(q + sj * dsub, codebooks + ((size_t)sj * kC4 + (e & 15)) * dsub, dsub);
+            put(e, subvec_sqdist(q + sj * dsub, codebooks + ((size_t)sj * kC4 + (e & 15)) * dsub, dsub));
         }
         return;
     }
@@ -99,15 +98,48 @@ __device__ __forceinline__ void build_table_rows(float *__restrict__ out,
                 t = xv.y - cv[u].y; acc = __builtin_fmaf(t, t, acc);
                 t = xv.z - cv[u].z; acc = __builtin_fmaf(t, t, acc);
                 t = xv.w - cv[u].w; acc = __builtin_fmaf(t, t, acc);
-                out[e + u * T] = acc;
+                put(e + u * T, acc);
+            }
+        }
+    }
+    if (dsub == 8) {  // the same with eight values per centroid (one at a time: 12 us for the 96 rows of 768 values, of 24 rounds of latency)
+        for (; e + 3 * T < nj * kC; e += 4 * T) {
+            float4 cv[4][2];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float4 *c = reinterpret_cast<const float4 *>(codebooks + ((size_t)j0 * kC + e + u * T) * 8);
+                cv[u][0] = c[0];
+                cv[u][1] = c[1];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float4 *x = reinterpret_cast<const float4 *>(q + (j0 + ((e + u * T) >> 8)) * 8);
+                float acc = 0.0f, t;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const float4 xv = x[h];
+                    t = xv.x - cv[u][h].x; acc = __builtin_fmaf(t, t, acc);
+                    t = xv.y - cv[u][h].y; acc = __builtin_fmaf(t, t, acc);
+                    t = xv.z - cv[u][h].z; acc = __builtin_fmaf(t, t, acc);
+                    t = xv.w - cv[u][h].w; acc = __builtin_fmaf(t, t, acc);
+                }
+                put(e + u * T, acc);
             }
         }
     }
     for (; e < nj * kC; e += T) {
         const int j = j0 + (e >> 8);
         const int c = e & (kC - 1);
-        out[e] = subvec_sqdist(q + j * dsub, codebooks + ((size_t)j * kC + c) * dsub, dsub);
+        put(e, subvec_sqdist(q + j * dsub, codebooks + ((size_t)j * kC + c) * dsub, dsub));
     }
+}
+
+template <bool FS = false>
+__device__ __forceinline__ void build_table_rows(float *__restrict__ out,
+                                                 const float *__restrict__ q,
+                                                 const float *__restrict__ codebooks, int dsub,
+                                                 int j0, int nj) {
+    table_rows<FS>(q, codebooks, dsub, j0, nj, [&](int e, float v) { out[e] = v; });
 }
 
 // Equation 3 from s = Gamma(l,q)^2 and b = Gamma(l,x).
@@ -180,6 +212,46 @@ __device__ __forceinline__ float half_reduce_x4(const float (&v)[4], int lane32)
 // The row whose total half_reduce_x4 leaves in a lane, and the lanes that store the four totals.
 __device__ __forceinline__ int half_reduce_x4_row(int lane32) { return ((lane32 >> 4) << 1) | ((lane32 >> 1) & 1); }
 __device__ __forceinline__ bool half_reduce_x4_writer(int lane32) { return (lane32 & 13) == 0; }
+
+// Half-wave totals of N (32, 16 or 8) lane sums per lane at once: v[i] is the calling lane's share
+// of sum i; lane l of the half wave returns the total of sum l >> (5 - log2 N).  The additions are
+// those of half_reduce, pair by pair (lane ^ 16, ^ 8, ^ 4, ^ 2, ^ 1; binary32 addition commutes,
+// so it does not matter which lane of a pair adds): while a lane still holds several sums, it
+// hands half of them to its partner at each step and keeps the other half, so N sums take
+// N - 1 exchanges (plus one per remaining step) instead of 5 N.
+template <int BIT>
+__device__ __forceinline__ float lane_xor(float x) {
+    const int v = __float_as_int(x);
+    if constexpr (BIT == 16) return __int_as_float(__builtin_amdgcn_ds_swizzle(v, 0x401F));
+    else if constexpr (BIT == 8) return __int_as_float(__builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, false));  // row rotation by 8
+    else if constexpr (BIT == 4) return __int_as_float(__builtin_amdgcn_ds_swizzle(v, 0x101F));
+    else if constexpr (BIT == 2) return __int_as_float(__builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, false));
+    else return __int_as_float(__builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, false));
+}
+template <int N, int BIT, int CAP>
+__device__ __forceinline__ void reduce_step(float (&v)[CAP], int lane32) {
+    if constexpr (N > 1) {
+        const bool up = (lane32 & BIT) != 0;   // these lanes keep the upper half of the sums
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i) {
+            const float keep = up ? v[i + N / 2] : v[i];
+            const float send = up ? v[i] : v[i + N / 2];
+            v[i] = keep + lane_xor<BIT>(send);
+        }
+    } else {
+        v[0] = v[0] + lane_xor<BIT>(v[0]);
+    }
+}
+template <int N>
+__device__ __forceinline__ float reduce_pairs(float (&v)[N], int lane32) {
+    static_assert(N == 32 || N == 16 || N == 8, "sums per lane");
+    reduce_step<N, 16>(v, lane32);
+    reduce_step<(N / 2 > 1 ? N / 2 : 1), 8>(v, lane32);
+    reduce_step<(N / 4 > 1 ? N / 4 : 1), 4>(v, lane32);
+    reduce_step<(N / 8 > 1 ? N / 8 : 1), 2>(v, lane32);
+    reduce_step<(N / 16 > 1 ? N / 16 : 1), 1>(v, lane32);
+    return v[0];
+}
 
 // Four rows at once (same arithmetic per row as exact_d2_half; the four loads of each step
 // are in flight together).  PIPE: the next step's four loads are issued before the current
@@ -441,31 +513,68 @@ __host__ __device__ inline size_t list_record_bytes(int M) { return (list_record
 
 // Early-abandon threshold on the running table sum (an exact shortcut, not part of the
 // paper's method).  Table entries are >= 0, so the binary32 running sum never decreases, and
-// for a = sqrt(s) >= b the computed bound of Equation 3 is >= (a - b)^2.  Hence, once
-// s > (b + sqrt(tau))^2 by a margin that covers all rounding, the finished bound is
-// certain to exceed tau and the remaining subspaces need not be read: the candidate is
-// pruned exactly as the full evaluation would prune it.  Margin: the computed chain
-// sqrt -> subtract -> square loses < 4 ulp (2.4e-7 relative); the threshold is inflated by
-// 1e-5.  tau = +inf gives +inf (never abandons).
+// Equation 3, g(a, b) = (a - b)^2 + 2 gamma a b with a = sqrt(s), grows with a from a = (1 - gamma) b on.
+// Hence, once a exceeds the larger root of g = tau by a margin that covers all rounding, the
+// finished bound is certain to exceed tau and the remaining subspaces need not be read: the
+// candidate is pruned exactly as the full evaluation would prune it.
 //
-// Per threshold tau:   st = abandon_scale(tau) = c * max(sqrt(tau), 1e-15), c = 1.000025
-// Per candidate:       thr = (c*b + st)^2 = c^2 (b + max(sqrt(tau),1e-15))^2 >= 1.00005 (b + sqrt(tau))^2
-// (the floor keeps thr >= 1e-30, inside the normal range, so the margin argument holds for
-// arbitrarily small tau as well).
+// With y = min(gamma, 1) (g grows with gamma, so a smaller one only prunes less), c1 = 1 - y,
+// c2 = y (2 - y) = 1 - c1^2, the root is f(b) = c1 b + sqrt(tau - c2 b^2) (no root: always pruned).
+// f is concave in b, so a tangent lies above it everywhere: the threshold of a candidate is the
+// square of a line in its landmark distance,
+//     thr = r |r|,  r = alpha + beta b        (r < 0: nothing passes)
+// with the tangent taken at b0, a typical landmark distance of the query's candidates (they are
+// narrowly distributed, so the tangent is nearly the root itself).  For y < 0.01 the line is that of the
+// strict bound, b + sqrt(tau), which holds for every gamma.
+//
+// What the relaxation is worth here: with gamma = 0.6 and unit vectors (landmark distances 0.7, tau 0.94)
+// a candidate is out at s = 1.0, while the strict bound's threshold, which was used for every gamma
+// before, let sums run to 2.8: next to nothing was abandoned early.
+//
+// Rounding.  e = 2^-17: tau (1 + e) and c2 - e take the place of tau and c2, which moves the root to where the true
+// g exceeds tau by e (tau + b^2); the computed chain sqrt, subtract, square, fma loses at
+// most about 8 * 2^-24 of (a + b)^2 (1 + y) <= 2^-18 (tau + b^2) there, and beyond the root g grows faster than
+// that.  For the strict line the chain loses < 4 ulp of (a - b)^2.  The line is inflated by 4e-6 for its own
+// evaluation and by c = 1.000025, i.e. the threshold by 5e-5, of which the roundings of partial
+// sums below use 3.1e-5.  tau = +inf gives +inf (never abandons); the floor of 1e-30 under tau keeps
+// thr inside the normal range.
 //
 // The cruise tests a running sum s_j (subspaces 0..j-1) against thr - rest_j, where rest_j is
 // the binary32 sum over the remaining subspaces of their smallest table entry: the finished
 // sum is at least s_j + (true rest) up to the rounding of at most M additions on either side,
 //   s_full >= (s_j + rest_j) (1 - 2 M u),  u = 2^-24,  2 M u <= 3.1e-5 for M <= 256,
-// and the subtraction thr - rest_j errs by at most u thr; the 5e-5 of the margin cover the
-// 1e-5 of the first argument, these 3.1e-5 and that u.
+// and the subtraction thr - rest_j errs by at most u thr.
 constexpr float kAbandonC = 1.000025f;
-__device__ __forceinline__ float abandon_scale(float tau) {
-    return kAbandonC * fmaxf(sqrt_rn(tau), 1e-15f);
+constexpr float kAbandonE = 1.0f / 131072.0f;
+struct AbandonLine {
+    float alpha, beta;
+};
+__device__ __forceinline__ AbandonLine abandon_line(float tau, float two_gamma, float b0) {
+    if (!(tau < 1e37f)) return AbandonLine{__builtin_inff(), 0.0f};
+    tau = fmaxf(tau, 1e-30f);
+    const float y = fminf(0.5f * two_gamma, 1.0f);
+    if (y < 0.01f) return AbandonLine{kAbandonC * sqrt_rn(tau), kAbandonC};
+    const float c1 = 1.0f - y, c2 = y * (2.0f - y) - kAbandonE, t = tau * (1.0f + kAbandonE);
+    // (the tangent point stays where the root is, at most 0.97 of the way to its end)
+    const float x = fminf(b0 * b0 * c2, 0.95f * t);          // c2 b0^2
+    const float s0 = sqrt_rn(t - x), slope = sqrt_rn(x * c2) / s0;
+    return AbandonLine{kAbandonC * 1.000004f * (t / s0), kAbandonC * (c1 - slope + 4e-6f * (c1 + slope))};
 }
-__device__ __forceinline__ float abandon_threshold(float b, float st) {
-    const float r = __builtin_fmaf(b, kAbandonC, st);
-    return r * r;
+__device__ __forceinline__ float abandon_threshold(float b, AbandonLine line) {
+    const float r = __builtin_fmaf(b, line.beta, line.alpha);
+    return r * __builtin_fabsf(r);
+}
+// The threshold tau below which a whole list is passed over: the least Equation 3 can give a vector
+// whose table sum is at least lb and whose landmark distance is at most bm (see above for y, c1,
+// c2; over b the least is at b = c1 a, or at bm where that is smaller), less what rounding can take: lb is a
+// binary32 sum of at most 256 terms (3.1e-5), the chain of Equation 3 as above.
+__device__ __forceinline__ float list_threshold(float lb, float bm, float two_gamma) {
+    const float y = fminf(0.5f * two_gamma, 1.0f), c1 = 1.0f - y;
+    const float a = sqrt_rn(lb) * (1.0f - 2.5e-5f), b = bm * (1.0f + 1e-6f);
+    const float e = a - b;
+    const float least = b <= c1 * a ? __builtin_fmaf(2.0f * y * a, b, e * e) : a * a * (y * (2.0f - y));
+    const float v = least - 2.0f * kAbandonE * (a * a + b * b);
+    return v == v ? v : -__builtin_inff();
 }
 
 }  // namespace trim

@@ -98,6 +98,7 @@ struct Ctl {
     int32_t nposs;       // cruise: number of possibles found in the stretch
     int32_t npassed;     // cruise: candidates of the stretch that passed the first subspaces
     int32_t hold;        // candidates still to be taken span by span before the next stretch is tried
+    float b0;            // mean landmark distance of a sample of the query's candidates
     int32_t nfail;       // stretches that failed in a row (the next one is a short trial while > 0)
     uint32_t work[8];    // WorkCounter totals of this workgroup (only kept when asked for)
 };
@@ -396,7 +397,7 @@ void search_kernel(const SearchArgs a) {
     int *segd = reinterpret_cast<int *>(smem + a.off_segd);   // [nseg] start - prefix
     float *restv = reinterpret_cast<float *>(smem + a.off_rest);  // [M/4+1] remaining minima (cruise)
     float *rowmin = reinterpret_cast<float *>(smem + a.off_plb);     // [M] smallest entry of each table row (prologue only)
-    float2 *seglist = reinterpret_cast<float2 *>(smem + a.off_seglb); // [nseg] list-level pruning {slack, rest}: see the prologue
+    float2 *seglist = reinterpret_cast<float2 *>(smem + a.off_seglb); // [nseg] list-level pruning {threshold, rest}: see the prologue
     int32_t *spos = reinterpret_cast<int32_t *>(smem + a.off_spos);  // survivor position -> id
     float *sd2 = reinterpret_cast<float *>(smem + a.off_sd2);        // exact d2 (shares the queue area)
     int32_t *sidx = reinterpret_cast<int32_t *>(smem + a.off_sidx);  // range: scan-order number
@@ -530,9 +531,9 @@ void search_kernel(const SearchArgs a) {
     // List-level bounds (kNN over inverted lists whose summaries the caller supplies): for the
     // list of segment p, lb = sum over all subspaces j of the smallest T[j][c] over the codes c
     // that occur in the list, a lower bound of every table sum of the list; rest = the same
-    // over the subspaces from H0 on; bm = the list's largest landmark distance.  Every abandon
-    // threshold of the list is at most (c bm + st)^2 (abandon_threshold grows with the
-    // landmark distance), so while lb exceeds that, nothing in the list can survive.
+    // over the subspaces from H0 on; bm = the list's largest landmark distance.  Equation 3 is at
+    // least list_threshold(lb, bm) for every vector of the list: while that exceeds the threshold
+    // in force, nothing in the list can survive.
     // Two segments per wave and round; a lane takes 16 recorded codes of one subspace (4 lanes
     // per subspace, 32 subspaces of either list per step, all loads of a step issued together).
     if (MODE == kKnn && use_rest && a.nseg > 0 && a.list_bounds != nullptr) {
@@ -604,10 +605,8 @@ void search_kernel(const SearchArgs a) {
                     lb[t] = lb[t] + __shfl_xor(lb[t], off);
                     rest[t] = rest[t] + __shfl_xor(rest[t], off);
                 }
-                // the list is passed over while lb > (c bm + st)^2, i.e. while
-                // sqrt(lb) - c bm > st: the left side is kept, rounded against passing over
-                float slack = sqrt_rn(lb[t]) * (1.0f - 1e-6f) - kAbandonC * bm[t] * (1.0f + 1e-6f);
-                if (!(slack == slack)) slack = -__builtin_inff();
+                // the list is passed over while the threshold in force is below this
+                const float slack = list_threshold(lb[t], bm[t], a.two_gamma);
                 if (lane == 0 && p0 + t < nseg) seglist[p0 + t] = make_float2(slack, rest[t]);
             }
         }
@@ -791,6 +790,14 @@ void search_kernel(const SearchArgs a) {
         }
     };
 
+    // a typical landmark distance (see abandon_line): the mean over 64 candidates spread over the scan
+    if (tid < kWave) {
+        float b = total > 0 ? a.dlx[locate((int)((int64_t)lane * total >> 6))] : 0.0f;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) b = b + __shfl_xor(b, off);
+        if (lane == 0) ctl->b0 = b * (1.0f / 64.0f);
+    }   // (read after the next barrier)
+
     // ---- seed: the first k candidates populate R, all with exact distances ----
     if (kseed > 0) {
         for (int i0 = 0; i0 < kseed; i0 += T) append(i0 + tid < kseed, i0 + tid);
@@ -843,7 +850,7 @@ void search_kernel(const SearchArgs a) {
     for (int c0 = c_begin + kseed; c0 < c_end;) {
         __syncthreads();  // every thread is done with the previous stretch
         const float tau0 = ctl->tau;
-        const float sqrt_tau0 = abandon_scale(tau0);  // scaled: see abandon_threshold
+        const AbandonLine line0 = abandon_line(tau0, a.two_gamma, ctl->b0);
 
         // ---- cruise: once tau is finite, bound a long stretch of candidates with no block-wide
         // barrier at all.  Every wave runs its own software pipeline over interleaved blocks of
@@ -905,7 +912,7 @@ void search_kernel(const SearchArgs a) {
                 };
                 auto drain_finish = [&]() {
                     if (lane < d_n) {
-                        const float thr = abandon_threshold(d_b, sqrt_tau0);
+                        const float thr = abandon_threshold(d_b, line0);
                         const CodeRow cr = code_row<kTiledOk>(a, d_pos);
                         // every test of a running sum is against the threshold less what the
                         // subspaces still to come add at the least (restv; a half-way stop inside
@@ -967,10 +974,10 @@ void search_kernel(const SearchArgs a) {
                 // what subspaces H0.. add at the least, in a scalar register
                 const float rest_h0 = __builtin_bit_cast(
                     float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, restv[H0 / 4])));
-                // list-level pruning: a list is passed over while its slack > st (both compared as
-                // integers: st > 0, and a negative slack is a negative integer)
+                // list-level pruning: a list is passed over while its threshold > tau0 (both compared as
+                // integers: tau0 >= 0, and a negative threshold is a negative integer)
                 const bool have_lb = use_rest && a.nseg > 0 && a.list_bounds != nullptr;
-                const int st_bits = __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, sqrt_tau0));
+                const int tau_bits = __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, tau0));
                 for (int blk = wave; blk < nblk; blk += nwaves) {
                     // this block's loads fly while the previous drain is finished; the next
                     // drain's loads fly while this block is bounded
@@ -994,7 +1001,7 @@ void search_kernel(const SearchArgs a) {
                             const float2 sr = seglist[s_seg];
                             const int sl = __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, sr.x));
                             const int rs = __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, sr.y));
-                            if (sl > st_bits) {                  // same for the whole wave
+                            if (sl > tau_bits) {                  // same for the whole wave
                                 if (acct && lane == 0) tally(kWorkSkipped, U * kWave);
                                 continue;
                             }
@@ -1004,7 +1011,7 @@ void search_kernel(const SearchArgs a) {
                             const int e2 = __builtin_amdgcn_readfirstlane(segp[s_seg + 2]);
                             const int sl1 = __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, seglist[s_seg].x));
                             const int sl2 = __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, seglist[s_seg + 1].x));
-                            if (cf + U * kWave <= e2 && sl1 > st_bits && sl2 > st_bits) {
+                            if (cf + U * kWave <= e2 && sl1 > tau_bits && sl2 > tau_bits) {
                                 if (acct && lane == 0) tally(kWorkSkipped, U * kWave);
                                 continue;
                             }
@@ -1087,7 +1094,7 @@ void search_kernel(const SearchArgs a) {
                         }
                         const float sum = sums[u];
                         const int cl = cb + u * kWave + lane;
-                        const float thr = abandon_threshold(bq[u], sqrt_tau0) - blk_rest;
+                        const float thr = abandon_threshold(bq[u], line0) - blk_rest;
                         // lanes beyond the stretch carry a NaN landmark distance (issue_loads):
                         // their threshold is NaN and the comparison is false
                         const bool alive = sum <= thr;
@@ -1276,7 +1283,7 @@ void search_kernel(const SearchArgs a) {
                         for (int u = 0; u < U; ++u) {
                             const float sum = gather_add<H0 / 4, false, FS>(0.0f, kTabAt<FS>, w[u], __builtin_inff());
                             const int cl = base + u * kWave + lane;
-                            const float thr = abandon_threshold(bq[u], sqrt_tau0);
+                            const float thr = abandon_threshold(bq[u], line0);
                             const bool valid = cl < whi;
                             bool alive = valid && !(sum > thr);
                             float keep = alive ? sum : __builtin_inff();
@@ -1331,7 +1338,7 @@ void search_kernel(const SearchArgs a) {
                                     if (c < n16) load_codes<4>(w16[c], cr.at(jp + ja + 16 * c));
                             }
                             const float b = a.dlx[pos];
-                            const float thr = abandon_threshold(b, sqrt_tau0);
+                            const float thr = abandon_threshold(b, line0);
                             float sum = slice_round ? 0.0f : plbs[cl];
                             int j = h0;
                             int used16 = 0;  // 16-byte pieces of a bulk round whose sum was begun
