@@ -301,6 +301,28 @@ int trim_search_knn(const trim_index_view *index, const float *queries, int64_t 
                     void *stream);
 
 /*
+ * The same search with work space (Section 4.2; same results, masks and counters).  With few
+ * queries, or with long vectors that many queries come close to, the scan is better done in
+ * passes: the bounds of a stretch of candidates, the exact distances of those that pass (a
+ * stored vector is read once for all the queries that want it), the batch rule over them.  The
+ * passes keep a bit and two binary32 values per (query, candidate) pair in the work space,
+ * query sets being split so that it stays below about 8 GiB.
+ * trim_knn_workspace_bytes: the bytes such a search wants, or 0 where the single kernel of
+ * trim_search_knn is the better way (a host function of the sizes in its arguments).
+ * workspace: device, 256-byte aligned, contents on entry ignored; NULL or fewer bytes than that:
+ * exactly trim_search_knn.  A search that keeps the work counters (trim_stats.work) runs as the
+ * single kernel.
+ */
+size_t trim_knn_workspace_bytes(const trim_index_view *index, int64_t nq, const trim_candidates *cand,
+                                int32_t k, int32_t batch);
+int trim_search_knn_ws(const trim_index_view *index, const float *queries, int64_t nq,
+                       const float *lut, const trim_candidates *cand, int32_t k, float gamma,
+                       int32_t batch, const int32_t *query_order,
+                       int32_t *out_ids, float *out_d2,
+                       const trim_stats *stats, uint32_t *survivor_mask, int64_t mask_words,
+                       void *workspace, size_t workspace_bytes, void *stream);
+
+/*
  * Approximate range search by the scan of Section 4.2 (problem statement: Section 2.1):
  * tau = radius^2 (squared once in binary32) for every candidate; a candidate survives iff
  * g <= tau; a survivor is a result iff its exact squared distance <= tau.
@@ -321,6 +343,28 @@ int trim_search_range(const trim_index_view *index, const float *queries, int64_
                       int64_t *required, const trim_stats *stats, uint32_t *survivor_mask,
                       int64_t mask_words, void *workspace, size_t workspace_bytes,
                       void *stream);
+
+/*
+ * The same search (Section 4.2; same results, masks and counters) with scratch memory beside the
+ * workspace: many queries over long vectors are then searched in passes (see trim_search_knn_ws).
+ * trim_range_scratch_bytes: the bytes such a search wants, or 0 where trim_search_range is the better way.
+ * scratch: device, 256-byte aligned, contents on entry ignored; NULL or fewer bytes: exactly trim_search_range.
+ *
+ * trim_range_collect: the CSR arrays of a search that has been counted.  After a call of
+ * trim_search_range or trim_search_range_ws with too small a capacity, or none, the workspace holds the results
+ * until it is used for something else; this call writes them, in scan order, without searching
+ * again.  index, nq and cand as in that call.
+ */
+size_t trim_range_scratch_bytes(const trim_index_view *index, int64_t nq, const trim_candidates *cand);
+int trim_search_range_ws(const trim_index_view *index, const float *queries, int64_t nq,
+                         const float *lut, const trim_candidates *cand, float radius, float gamma,
+                         const int32_t *query_order, int64_t *out_offsets, int32_t *out_ids,
+                         float *out_d2, int64_t capacity,
+                         int64_t *required, const trim_stats *stats, uint32_t *survivor_mask,
+                         int64_t mask_words, void *workspace, size_t workspace_bytes, void *scratch,
+                         size_t scratch_bytes, void *stream);
+int trim_range_collect(const trim_index_view *index, int64_t nq, const trim_candidates *cand, int32_t *out_ids,
+                       float *out_d2, int64_t capacity, void *workspace, size_t workspace_bytes, void *stream);
 
 /*
  * trim_search_range for callers that cannot allocate device memory (code under HIP graph

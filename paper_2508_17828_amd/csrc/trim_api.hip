@@ -428,14 +428,280 @@ int scratch_for_current_device(void **out) {
     return TRIM_OK;
 }
 
-// The range search behind both entry points: `workspace` is the caller's buffer or this
-// device's copy of the static scratch area.
+// ---- the scan in separate passes (trim_mark.h) ----
+
+// Table phases, block size and LDS layout of the finish pass: two workgroups of 512 threads per CU
+// where they fit, else one of 1024.
+struct FinishPlan {
+    int threads, P, Mp, vec;
+    size_t lds;
+    uint32_t off_q, off_segp, off_segd, off_bits, off_ring;
+};
+bool make_finish_plan(int d, int M, bool fs, int nseg, FinishPlan *pl) {
+    const int row_bytes = fs ? (int)kByteRow<true> : (int)kByteRow<false>;
+    const int ns = nseg > 0 ? nseg : 1;
+    for (int P = 1; P <= M / 4; ++P) {
+        if (M % P || (M / P) % 4) continue;
+        const int Mp = M / P;
+        for (int threads = 512; threads <= 1024; threads *= 2) {
+            size_t off = (size_t)Mp * row_bytes;
+            pl->off_q = (uint32_t)off;    off += up16((size_t)d * 4);
+            pl->off_segp = (uint32_t)off; off += up16((size_t)(ns + 1) * 4);
+            pl->off_segd = (uint32_t)off; off += up16((size_t)ns * 4);
+            pl->off_bits = (uint32_t)off; off += kFinishPiece / 8 + 64;
+            pl->off_ring = (uint32_t)off; off += kFinishList * 2;
+            if (off > (threads == 512 ? (size_t)81920 : kLdsBytes)) continue;
+            pl->threads = threads; pl->P = P; pl->Mp = Mp; pl->lds = off;
+            pl->vec = (M % 16 == 0 && Mp % 16 == 0) ? 4 : (M % 8 == 0 && Mp % 8 == 0) ? 2 : 1;
+            return true;
+        }
+    }
+    return false;
+}
+void fill_finish(FinishArgs &m, const FinishPlan &pl, const SearchArgs &a) {
+    m.codes = a.codes; m.dlx = a.dlx; m.codebooks = a.codebooks; m.n = a.n; m.d = a.d; m.M = a.M; m.dsub = a.dsub;
+    m.queries = a.queries; m.nq = a.nq; m.order = a.order; m.lut = a.lut;
+    m.list_offsets = a.list_offsets; m.probes = a.probes;
+    m.nlist = a.nlist; m.nseg = a.nseg; m.max_cand = a.max_cand;
+    m.P = pl.P; m.Mp = pl.Mp; m.two_gamma = a.two_gamma; m.n_scanned = a.n_scanned;
+    m.off_q = pl.off_q; m.off_segp = pl.off_segp; m.off_segd = pl.off_segd; m.off_bits = pl.off_bits; m.off_ring = pl.off_ring;
+}
+
+// Whether a search runs in passes: many queries (a list's landmarks are shared by the queries that scan it; a tile
+// of the filter holds 128) over long rows (what the single kernel reads once per query and survivor).
+constexpr int64_t kManyQueries = 128;
+constexpr int kLongRow = 256;
+constexpr size_t kKnnSlabBytes = size_t(8) << 30;
+bool worth_passes(const trim_index_view *ix, int64_t nq) {
+    return nq > kManyQueries && ix->n > 0 && ix->d >= kLongRow && filter_padded(ix->d / ix->M, is_fs(ix)) != 0;
+}
+
+inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
+
+// Work space of the filter and measure passes for `rows` queries (offsets from `at`; 0 bytes: shape without a filter).
+struct FilterLayout {
+    int padded, kpad, kpad_rows;
+    size_t off_start, off_cnt, off_tasks, off_inv, off_mu, off_max, off_books, off_q16, off_q16r, off_qpar, end;
+};
+size_t filter_bytes_per_query(const trim_index_view *ix, const trim_candidates *cand) {
+    const int padded = filter_padded(ix->d / ix->M, is_fs(ix));
+    return (size_t)(cand ? cand->nprobe : 0) * 8 + ((size_t)ix->M * padded + ix->d + 2 * kFltSlice) * 2 + 8;
+}
+FilterLayout filter_layout(const trim_index_view *ix, int64_t rows, const trim_candidates *cand, size_t at) {
+    FilterLayout L{};
+    L.padded = filter_padded(ix->d / ix->M, is_fs(ix));
+    L.kpad = (ix->M * L.padded + kFltSlice - 1) / kFltSlice * kFltSlice;
+    L.kpad_rows = (ix->d + kFltSlice - 1) / kFltSlice * kFltSlice;
+    size_t off = at;
+    if (cand) {
+        L.off_start = off; off += up256((size_t)(cand->nlist + 1) * 4);
+        L.off_cnt = off;   off += up256((size_t)cand->nlist * 4);
+        L.off_tasks = off; off += up256((size_t)(cand->nlist + 1) * 8);
+        L.off_inv = off;   off += up256((size_t)rows * cand->nprobe * 8);
+    }
+    L.off_mu = off;    off += up256((size_t)ix->d * 4);
+    L.off_max = off;   off += 256;
+    L.off_books = off; off += up256((size_t)L.kpad * (is_fs(ix) ? kC4 : kC) * 2);
+    L.off_q16 = off;   off += up256((size_t)rows * L.kpad * 2);
+    L.off_q16r = L.off_q16;
+    if (ix->d / ix->M != L.padded) { L.off_q16r = off; off += up256((size_t)rows * L.kpad_rows * 2); }
+    L.off_qpar = off;  off += up256((size_t)rows * 8);
+    L.end = off;
+    return L;
+}
+// Arguments of the passes that do not change from one to the next.
+void fill_filter(FilterArgs &f, InvertArgs &v, const trim_index_view *ix, const SearchArgs &a, const FilterLayout &L, unsigned char *ws) {
+    if (a.nseg > 0) {
+        v.probes = a.probes; v.nq = a.nq; v.order = a.order; v.nseg = a.nseg; v.nlist = a.nlist;
+        v.list_offsets = a.list_offsets; v.n = a.n;
+        v.cnt = reinterpret_cast<int32_t *>(ws + L.off_cnt);
+        v.start = reinterpret_cast<int32_t *>(ws + L.off_start);
+        v.inv = reinterpret_cast<int2 *>(ws + L.off_inv);
+        v.tasks = reinterpret_cast<int32_t *>(ws + L.off_tasks);
+        v.row_tasks = v.tasks + a.nlist + 1;
+    }
+    f.codes = a.codes; f.dlx = a.dlx; f.codebooks = a.codebooks; f.n = a.n; f.d = a.d; f.M = a.M; f.dsub = a.dsub;
+    f.nsub = ix->M; f.ncent = is_fs(ix) ? kC4 : kC; f.queries = a.queries; f.nq = a.nq; f.order = a.order;
+    f.list_offsets = a.nseg > 0 ? a.list_offsets : nullptr; f.nlist = a.nlist;
+    f.inv_start = v.start; f.inv = v.inv; f.tasks = v.tasks; f.row_tasks = v.row_tasks;
+    f.two_gamma = a.two_gamma; f.padded = L.padded; f.kpad = L.kpad; f.kpad_rows = L.kpad_rows; f.base = a.base;
+    f.mu = reinterpret_cast<float *>(ws + L.off_mu);
+    f.max_bits = reinterpret_cast<uint32_t *>(ws + L.off_max);
+    f.books = reinterpret_cast<_Float16 *>(ws + L.off_books);
+    f.q16 = reinterpret_cast<_Float16 *>(ws + L.off_q16);
+    f.q16_rows = reinterpret_cast<_Float16 *>(ws + L.off_q16r);
+    f.qpar = reinterpret_cast<float *>(ws + L.off_qpar);
+}
+// The inverted probe lists and the 16-bit operands of the queries [slot0, slot0 + nslots).
+int prepare_filter(FilterArgs &f, InvertArgs &v, int64_t slot0, int64_t nslots, hipStream_t st) {
+    int rc;
+    f.slot0 = v.slot0 = slot0;
+    f.nslots = v.nslots = nslots;
+    if (v.cnt) {
+        if ((rc = fill_u32(reinterpret_cast<uint32_t *>(v.cnt), (size_t)v.nlist, 0u, st))) return rc;
+        if ((rc = launch_invert(v, st))) return rc;
+    }
+    if ((rc = fill_u32(f.max_bits, 1, 0u, st))) return rc;
+    return launch_filter_operands(f, st);
+}
+
+struct KnnLayout {
+    int64_t words, slab;      // bit words per query, queries per slab (0: one kernel)
+    FilterLayout f;
+    size_t off_possible, off_g, off_d2, total;   // totals at 0
+};
+KnnLayout knn_layout(const trim_index_view *ix, int64_t nq, const trim_candidates *cand) {
+    KnnLayout L{};
+    const int64_t hard = (int64_t(1) << 31) - 1 - TRIM_MAX_BATCH - 2048;
+    int64_t mc = cand ? cand->max_candidates : ix->n;
+    if (mc <= 0 || mc > ix->n + (int64_t)(cand ? cand->nprobe : 0) * ix->n || !worth_passes(ix, nq)) return L;
+    if (mc > hard) mc = hard;
+    L.words = (mc + 31) / 32 + 1;
+    const size_t per = (size_t)L.words * (4 + 32 * 8) + 4 + filter_bytes_per_query(ix, cand);
+    L.slab = std::min<int64_t>((int64_t)(kKnnSlabBytes / per), std::min<int64_t>(nq, 1 << 20));
+    if (L.slab < 64) { L.slab = 0; return L; }
+    size_t off = up256((size_t)L.slab * 4);
+    L.off_possible = off; off += up256((size_t)L.slab * L.words * 4);
+    L.off_g = off;        off += up256((size_t)L.slab * L.words * 32 * 4);
+    L.off_d2 = off;       off += up256((size_t)L.slab * L.words * 32 * 4);
+    L.f = filter_layout(ix, L.slab, cand, off);
+    L.total = L.f.end;
+    return L;
+}
+
+int knn_in_passes(const trim_index_view *ix, const KnnLayout &L, const SearchArgs &a, const FinishPlan &pl, unsigned char *ws,
+                  hipStream_t st) {
+    FinishArgs m{};
+    fill_finish(m, pl, a);
+    m.totals = reinterpret_cast<int32_t *>(ws);
+    m.possible = reinterpret_cast<uint32_t *>(ws + L.off_possible);
+    m.g = reinterpret_cast<float *>(ws + L.off_g);
+    m.words = L.words;
+    m.tau_stride = a.k;
+    InvertArgs v{};
+    FilterArgs f{};
+    fill_filter(f, v, ix, a, L.f, ws);
+    f.tau_stride = a.k; f.tau_of = a.out_d2 + (a.k - 1);
+    f.totals = m.totals; f.possible = m.possible; f.words = L.words;
+    f.d2 = reinterpret_cast<float *>(ws + L.off_d2);
+    ReplayArgs y{};
+    y.base = a.base; y.queries = a.queries; y.d = a.d;
+    y.ids = a.ids; y.n = a.n; y.nq = a.nq; y.list_offsets = a.list_offsets; y.probes = a.probes; y.nlist = a.nlist;
+    y.nseg = a.nseg; y.max_cand = a.max_cand; y.k = a.k; y.batch = a.batch; y.order = a.order; y.totals = m.totals;
+    y.possible = m.possible; y.g = m.g; y.d2 = f.d2; y.words = L.words; y.out_ids = a.out_ids; y.out_d2 = a.out_d2;
+    y.n_exact = a.n_exact; y.mask = a.mask; y.mask_words = a.mask_words;
+    const int64_t most = a.max_cand;
+    for (int64_t s0 = 0; s0 < a.nq; s0 += L.slab) {
+        const int64_t ns = a.nq - s0 < L.slab ? a.nq - s0 : L.slab;
+        m.slot0 = y.slot0 = s0;
+        m.nslots = ns;
+        int rc;
+        if ((rc = prepare_filter(f, v, s0, ns, st))) return rc;
+        if ((rc = fill_u32(m.possible, (size_t)ns * L.words, 0u, st))) return rc;
+        // The seed and the first batch (no threshold yet), then everything else against the
+        // threshold that they leave.  Where that is no threshold to speak of yet (short first batches;
+        // candidates in no particular order), eight times as many candidates from pass to pass.
+        int64_t lo = 0, hi = (int64_t)a.k + a.batch;
+        for (;;) {
+            if (hi > most) hi = most;
+            m.lo = y.lo = f.lo = (int)lo;
+            m.hi = y.hi = f.hi = (int)hi;
+            m.tau_of = lo > 0 ? a.out_d2 + (a.k - 1) : nullptr;
+            m.all = lo == 0;            // (all of the first pass's candidates are bounded; after that the filter goes first)
+            if (lo > 0 && (rc = launch_filter(f, st))) return rc;
+            if ((rc = launch_finish(m, pl.vec, is_fs(ix), pl.threads, pl.lds, (ns + kXcds - 1) / kXcds * kXcds, st))) return rc;
+            if ((rc = launch_measure(f, st))) return rc;
+            if ((rc = launch_replay(y, ns, st))) return rc;
+            if (hi >= most) break;
+            lo = hi;
+            if (a.nseg == 0 || hi < 1024) {
+                hi = (int64_t)a.k + (hi - a.k) * 8;
+                if (hi > most / 2) hi = most;
+            } else {
+                hi = most;
+            }
+        }
+    }
+    return TRIM_OK;
+}
+
+int search_knn(const trim_index_view *index, const float *queries, int64_t nq, const float *lut, const trim_candidates *cand,
+               int32_t k, float gamma, int32_t batch, const int32_t *query_order, int32_t *out_ids, float *out_d2,
+               const trim_stats *stats, uint32_t *survivor_mask, int64_t mask_words, void *workspace, size_t workspace_bytes,
+               void *stream) {
+    int rc = check_index(index);
+    if (rc) return rc;
+    if ((rc = check_cand(cand))) return rc;
+    if (nq < 0 || nq > TRIM_MAX_QUERIES || k < 1 || k > TRIM_MAX_K || batch < 1 || batch > TRIM_MAX_BATCH)
+        return TRIM_INVALID_ARG;
+    if (!(gamma >= 0.0f) || std::isinf(gamma)) return TRIM_INVALID_ARG;
+    if (nq == 0) return TRIM_OK;
+    if (!queries || !out_ids || !out_d2) return TRIM_INVALID_ARG;
+    if (!lut && !index->codebooks) return TRIM_INVALID_ARG;
+    if (lut && !aligned16(lut)) return TRIM_INVALID_ARG;
+    if (survivor_mask && mask_words <= 0) return TRIM_INVALID_ARG;
+    Plan pl;
+    const int cap = batch > k ? batch : k;
+    if (!make_plan(index->d, code_bytes(index), is_fs(index), cand ? cand->nprobe : 0, cap, batch, k, false, &pl))
+        return TRIM_UNSUPPORTED_SHAPE;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (survivor_mask && (rc = fill_u32(survivor_mask, (size_t)nq * mask_words, 0u, st))) return rc;
+    SearchArgs a{};
+    fill_common(a, index, queries, lut, cand, gamma, stats, survivor_mask, mask_words, pl);
+    a.k = k; a.batch = batch; a.radius2 = 0.0f;
+    a.out_ids = out_ids; a.out_d2 = out_d2;
+    a.chunk = 0; a.nsplit = 1;
+    a.nq = nq; a.order = query_order;
+    if (workspace && !a.work && (reinterpret_cast<uintptr_t>(workspace) & 255u) == 0 && aligned16(queries)) {
+        const KnnLayout L = knn_layout(index, nq, cand);
+        FinishPlan fp;
+        if (L.slab > 0 && workspace_bytes >= L.total && index->codebooks &&
+            make_finish_plan(index->d, a.M, is_fs(index), a.nseg, &fp) && replay_lds(index->d, k, a.nseg) <= kLdsBytes)
+            return knn_in_passes(index, L, a, fp, static_cast<unsigned char *>(workspace), st);
+    }
+    const int64_t slots = (nq + kXcds - 1) / kXcds * kXcds;
+    if (slots * pl.threads >= (int64_t(1) << 32)) return TRIM_INVALID_ARG;  // threads per launch
+    return launch_search(false, is_fs(index), a, pl, dim3((unsigned)slots, 1), st);
+}
+
+// The pass that writes the CSR arrays from the marks, distances and offsets that a search left in its work space.
+int range_fill(const SearchArgs &a, const RangeLayout &L, unsigned char *ws, int32_t *out_ids, float *out_d2, int64_t capacity,
+               hipStream_t st) {
+    RangeFillArgs f{};
+    f.base = a.base; f.ids = a.ids; f.queries = a.queries;
+    f.list_offsets = a.list_offsets; f.probes = a.probes; f.n = a.n; f.d = a.d;
+    f.nlist = a.nlist; f.nseg = a.nseg; f.max_cand = a.max_cand; f.chunk = L.chunk;
+    f.nsplit = L.nsplit; f.result_mask = reinterpret_cast<uint32_t *>(ws); f.rmask_words = L.rmask_words;
+    f.result_d2 = reinterpret_cast<float *>(ws + L.off_d2);
+    f.chunk_base = reinterpret_cast<int64_t *>(ws + L.off_cbase);
+    f.out_ids = out_ids; f.out_d2 = out_d2; f.capacity = capacity;
+    const int nsegs = a.nseg > 0 ? a.nseg : 1;
+    size_t off = 0;
+    f.off_q = (uint32_t)off;
+    f.off_segp = (uint32_t)off; off += up16((size_t)(nsegs + 1) * 4);
+    f.off_segd = (uint32_t)off; off += up16((size_t)nsegs * 4);
+    f.off_list = (uint32_t)off; off += 2048 * 4;
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(range_fill_kernel),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)off));
+    hipLaunchKernelGGL(range_fill_kernel, dim3((unsigned)a.nq, (unsigned)L.nsplit), dim3(256), off, st, f);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+
+// Scratch of a range search in passes: totals, then the filter's operands.  0: such a search runs as one kernel.
+size_t range_scratch_bytes(const trim_index_view *ix, int64_t nq, const trim_candidates *cand) {
+    if (!worth_passes(ix, nq)) return 0;
+    return filter_layout(ix, nq, cand, up256((size_t)nq * 4)).end;
+}
+
+// The range search behind all entry points: `workspace` is the caller's buffer or this
+// device's copy of the static scratch area; scratch: see range_scratch_bytes (or null).
 int range_search(const trim_index_view *index, const float *queries, int64_t nq,
                  const float *lut, const trim_candidates *cand, float radius, float gamma,
                  const int32_t *query_order, int64_t *out_offsets, int32_t *out_ids,
                  float *out_d2, int64_t capacity,
                  int64_t *required, const trim_stats *stats, uint32_t *survivor_mask,
-                 int64_t mask_words, void *workspace, size_t workspace_bytes, void *stream) {
+                 int64_t mask_words, void *workspace, size_t workspace_bytes, void *scratch, size_t scratch_bytes, void *stream) {
     int rc = check_index(index);
     if (rc) return rc;
     if ((rc = check_cand(cand))) return rc;
@@ -486,35 +752,70 @@ int range_search(const trim_index_view *index, const float *queries, int64_t nq,
     if (query_order && (rc = fill_u32(reinterpret_cast<uint32_t *>(counts), (size_t)nq * L.nsplit, 0u, st))) return rc;
     if (a.max_cand > max_cand) a.max_cand = (int32_t)max_cand;
 
-    RangeFillArgs f{};
-    f.base = index->base; f.ids = index->ids; f.queries = queries;
-    f.list_offsets = a.list_offsets; f.probes = a.probes; f.n = index->n; f.d = index->d;
-    f.nlist = a.nlist; f.nseg = a.nseg; f.max_cand = a.max_cand; f.chunk = L.chunk;
-    f.nsplit = L.nsplit; f.result_mask = rmask; f.rmask_words = L.rmask_words; f.result_d2 = rd2;
-    f.chunk_base = cbase; f.out_ids = out_ids; f.out_d2 = out_d2; f.capacity = capacity;
-    const int nsegs = a.nseg > 0 ? a.nseg : 1;
-    size_t off = 0;
-    f.off_q = (uint32_t)off;    off += up16((size_t)index->d * 4);
-    f.off_segp = (uint32_t)off; off += up16((size_t)(nsegs + 1) * 4);
-    f.off_segd = (uint32_t)off; off += up16((size_t)nsegs * 4);
-    f.off_list = (uint32_t)off; off += 2048 * 4;
-    const size_t fill_lds = off;
-
     a.nq = nq;
-    const int64_t slots = (nq + kXcds - 1) / kXcds * kXcds;
-    if (slots * pl.threads >= (int64_t(1) << 32)) return TRIM_INVALID_ARG;  // threads per launch
-    if ((rc = launch_search(true, is_fs(index), a, pl, dim3((unsigned)slots, (unsigned)L.nsplit), st))) return rc;
+    FinishPlan fpl;
+    const size_t want = range_scratch_bytes(index, nq, cand);
+    if (scratch && want > 0 && scratch_bytes >= want && !a.work && (reinterpret_cast<uintptr_t>(scratch) & 255u) == 0 &&
+        aligned16(queries) && index->codebooks && make_finish_plan(index->d, a.M, is_fs(index), a.nseg, &fpl) &&
+        replay_lds(index->d, 1, a.nseg) <= kLdsBytes) {
+        unsigned char *sc = static_cast<unsigned char *>(scratch);
+        // (rows of the work space by query number; a query that the order does not name has no candidates)
+        if (query_order && (rc = fill_u32(reinterpret_cast<uint32_t *>(sc), (size_t)nq, 0u, st))) return rc;
+        if (!query_order && (rc = fill_u32(reinterpret_cast<uint32_t *>(counts), (size_t)nq * L.nsplit, 0u, st))) return rc;
+        InvertArgs v{};
+        FilterArgs fa{};
+        fill_filter(fa, v, index, a, filter_layout(index, nq, cand, up256((size_t)nq * 4)), sc);
+        fa.by_query = v.by_query = 1;
+        fa.range = 1; fa.radius2 = a.radius2; fa.lo = 0; fa.hi = a.max_cand;
+        fa.totals = reinterpret_cast<int32_t *>(sc); fa.possible = rmask; fa.words = L.rmask_words; fa.d2 = rd2;
+        FinishArgs m{};
+        fill_finish(m, fpl, a);
+        m.slot0 = 0; m.nslots = nq; m.by_query = 1; m.range = 1; m.radius2 = a.radius2; m.lo = 0; m.hi = a.max_cand;
+        m.totals = reinterpret_cast<int32_t *>(sc); m.possible = rmask; m.words = L.rmask_words; m.g = rd2;
+        m.n_exact = a.n_exact; m.mask = a.mask; m.mask_words = a.mask_words;
+        ReplayArgs y{};
+        y.base = a.base; y.queries = a.queries; y.d = a.d; y.n = a.n; y.nq = nq; y.list_offsets = a.list_offsets;
+        y.probes = a.probes; y.nlist = a.nlist; y.nseg = a.nseg; y.max_cand = a.max_cand; y.order = query_order;
+        y.totals = m.totals; y.bits = rmask; y.d2_out = rd2; y.words = L.rmask_words; y.radius2 = a.radius2;
+        y.chunk = L.chunk; y.nchunk = L.nsplit; y.counts = counts;
+        if ((rc = prepare_filter(fa, v, 0, nq, st))) return rc;
+        // candidates per query: the filter needs them before the finish pass writes them
+        if ((rc = launch_totals(m, st))) return rc;
+        if ((rc = launch_filter(fa, st))) return rc;
+        if ((rc = launch_finish(m, fpl.vec, is_fs(index), fpl.threads, fpl.lds, (nq + kXcds - 1) / kXcds * kXcds, st))) return rc;
+        if ((rc = launch_measure(fa, st))) return rc;
+        if ((rc = launch_range_exact(y, nq, L.nsplit, st))) return rc;
+    } else {
+        const int64_t slots = (nq + kXcds - 1) / kXcds * kXcds;
+        if (slots * pl.threads >= (int64_t(1) << 32)) return TRIM_INVALID_ARG;  // threads per launch
+        if ((rc = launch_search(true, is_fs(index), a, pl, dim3((unsigned)slots, (unsigned)L.nsplit), st))) return rc;
+    }
     hipLaunchKernelGGL(range_offsets_kernel, dim3(1), dim3(1024), 0, st, counts, nq, L.nsplit, cbase,
                        out_offsets, required);
     HIP_TRY(hipGetLastError());
-    if (capacity > 0) {
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(range_fill_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)fill_lds));
-        hipLaunchKernelGGL(range_fill_kernel, dim3((unsigned)nq, (unsigned)L.nsplit), dim3(256), fill_lds,
-                           st, f);
-        HIP_TRY(hipGetLastError());
-    }
+    if (capacity > 0) return range_fill(a, L, ws, out_ids, out_d2, capacity, st);
     return TRIM_OK;
+}
+
+// The CSR arrays of a search that has been counted (trim_range_collect).
+int range_collect(const trim_index_view *index, int64_t nq, const trim_candidates *cand, int32_t *out_ids, float *out_d2,
+                  int64_t capacity, void *workspace, size_t workspace_bytes, void *stream) {
+    int rc = check_index(index);
+    if (rc) return rc;
+    if ((rc = check_cand(cand))) return rc;
+    if (nq < 0 || nq > TRIM_MAX_QUERIES || capacity < 0) return TRIM_INVALID_ARG;
+    if (nq == 0 || capacity == 0) return TRIM_OK;
+    if (!out_ids || !out_d2) return TRIM_INVALID_ARG;
+    const int64_t max_cand = cand ? cand->max_candidates : index->n;
+    if (cand && max_cand <= 0) return TRIM_INVALID_ARG;
+    const RangeLayout L = range_layout(nq, max_cand);
+    if (!workspace || workspace_bytes < L.total || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return TRIM_WORKSPACE;
+    SearchArgs a{};
+    Plan pl{};
+    fill_common(a, index, nullptr, nullptr, cand, 0.0f, nullptr, nullptr, 0, pl);
+    a.nq = nq;
+    if (a.max_cand > max_cand) a.max_cand = (int32_t)max_cand;
+    return range_fill(a, L, static_cast<unsigned char *>(workspace), out_ids, out_d2, capacity, static_cast<hipStream_t>(stream));
 }
 
 }  // namespace
@@ -827,33 +1128,23 @@ int trim_search_knn(const trim_index_view *index, const float *queries, int64_t 
                     int32_t *out_ids, float *out_d2,
                     const trim_stats *stats, uint32_t *survivor_mask, int64_t mask_words,
                     void *stream) {
-    int rc = check_index(index);
-    if (rc) return rc;
-    if ((rc = check_cand(cand))) return rc;
-    if (nq < 0 || nq > TRIM_MAX_QUERIES || k < 1 || k > TRIM_MAX_K || batch < 1 || batch > TRIM_MAX_BATCH)
-        return TRIM_INVALID_ARG;
-    if (!(gamma >= 0.0f) || std::isinf(gamma)) return TRIM_INVALID_ARG;
-    if (nq == 0) return TRIM_OK;
-    if (!queries || !out_ids || !out_d2) return TRIM_INVALID_ARG;
-    if (!lut && !index->codebooks) return TRIM_INVALID_ARG;
-    if (lut && !aligned16(lut)) return TRIM_INVALID_ARG;
-    if (survivor_mask && mask_words <= 0) return TRIM_INVALID_ARG;
-    Plan pl;
-    const int cap = batch > k ? batch : k;
-    if (!make_plan(index->d, code_bytes(index), is_fs(index), cand ? cand->nprobe : 0, cap, batch, k, false, &pl))
-        return TRIM_UNSUPPORTED_SHAPE;
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    if (survivor_mask && (rc = fill_u32(survivor_mask, (size_t)nq * mask_words, 0u, st))) return rc;
-    SearchArgs a{};
-    fill_common(a, index, queries, lut, cand, gamma, stats, survivor_mask, mask_words, pl);
-    a.k = k; a.batch = batch; a.radius2 = 0.0f;
-    a.out_ids = out_ids; a.out_d2 = out_d2;
-    a.chunk = 0; a.nsplit = 1;
-    a.nq = nq; a.order = query_order;
-    const int64_t slots = (nq + kXcds - 1) / kXcds * kXcds;
-    if (slots * pl.threads >= (int64_t(1) << 32)) return TRIM_INVALID_ARG;  // threads per launch
-    if ((rc = launch_search(false, is_fs(index), a, pl, dim3((unsigned)slots, 1), st))) return rc;
-    return TRIM_OK;
+    return search_knn(index, queries, nq, lut, cand, k, gamma, batch, query_order, out_ids, out_d2, stats, survivor_mask,
+                      mask_words, nullptr, 0, stream);
+}
+
+size_t trim_knn_workspace_bytes(const trim_index_view *index, int64_t nq, const trim_candidates *cand, int32_t k, int32_t batch) {
+    if (check_index(index) || check_cand(cand) || nq <= 0 || k < 1 || batch < 1) return 0;
+    return knn_layout(index, nq, cand).total;
+}
+
+int trim_search_knn_ws(const trim_index_view *index, const float *queries, int64_t nq,
+                       const float *lut, const trim_candidates *cand, int32_t k, float gamma,
+                       int32_t batch, const int32_t *query_order,
+                       int32_t *out_ids, float *out_d2,
+                       const trim_stats *stats, uint32_t *survivor_mask, int64_t mask_words,
+                       void *workspace, size_t workspace_bytes, void *stream) {
+    return search_knn(index, queries, nq, lut, cand, k, gamma, batch, query_order, out_ids, out_d2, stats, survivor_mask,
+                      mask_words, workspace, workspace_bytes, stream);
 }
 
 size_t trim_range_workspace_bytes(int64_t nq, int64_t max_candidates) {
@@ -869,7 +1160,7 @@ int trim_search_range(const trim_index_view *index, const float *queries, int64_
                       int64_t mask_words, void *workspace, size_t workspace_bytes, void *stream) {
     return range_search(index, queries, nq, lut, cand, radius, gamma, query_order, out_offsets, out_ids, out_d2,
                         capacity, required, stats, survivor_mask, mask_words, workspace,
-                        workspace_bytes, stream);
+                        workspace_bytes, nullptr, 0, stream);
 }
 
 int trim_search_range_static(const trim_index_view *index, const float *queries, int64_t nq,
@@ -888,7 +1179,29 @@ int trim_search_range_static(const trim_index_view *index, const float *queries,
     const int rc = scratch_for_current_device(&ws);
     if (rc) return rc;
     return range_search(index, queries, nq, lut, cand, radius, gamma, query_order, out_offsets, out_ids, out_d2,
-                        capacity, required, stats, survivor_mask, mask_words, ws, kScratchBytes, stream);
+                        capacity, required, stats, survivor_mask, mask_words, ws, kScratchBytes, nullptr, 0, stream);
+}
+
+size_t trim_range_scratch_bytes(const trim_index_view *index, int64_t nq, const trim_candidates *cand) {
+    if (check_index(index) || check_cand(cand) || nq <= 0) return 0;
+    return range_scratch_bytes(index, nq, cand);
+}
+
+int trim_search_range_ws(const trim_index_view *index, const float *queries, int64_t nq,
+                         const float *lut, const trim_candidates *cand, float radius, float gamma,
+                         const int32_t *query_order, int64_t *out_offsets, int32_t *out_ids,
+                         float *out_d2, int64_t capacity,
+                         int64_t *required, const trim_stats *stats, uint32_t *survivor_mask,
+                         int64_t mask_words, void *workspace, size_t workspace_bytes, void *scratch,
+                         size_t scratch_bytes, void *stream) {
+    return range_search(index, queries, nq, lut, cand, radius, gamma, query_order, out_offsets, out_ids, out_d2,
+                        capacity, required, stats, survivor_mask, mask_words, workspace,
+                        workspace_bytes, scratch, scratch_bytes, stream);
+}
+
+int trim_range_collect(const trim_index_view *index, int64_t nq, const trim_candidates *cand, int32_t *out_ids, float *out_d2,
+                       int64_t capacity, void *workspace, size_t workspace_bytes, void *stream) {
+    return range_collect(index, nq, cand, out_ids, out_d2, capacity, workspace, workspace_bytes, stream);
 }
 
 size_t trim_static_scratch_bytes(void) { return kScratchBytes; }

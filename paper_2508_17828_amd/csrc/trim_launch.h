@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include "../../include/trim.h"
+#include "trim_passes.h"
 #include "trim_search.h"
 
 namespace trim {
@@ -35,6 +36,17 @@ int hip_fail(hipError_t e);
 // instance of search_kernel (with or without the work counters, by SearchArgs::work).
 #define TRIM_DECLARE_LAUNCH(name) \
     int name(const SearchArgs &a, const Plan &pl, dim3 grid, hipStream_t st)
+// The separate passes (trim_mark_inst.hip).
+int launch_finish(const FinishArgs &a, int vec, bool fs, int threads, size_t lds, int64_t slots, hipStream_t st);
+int launch_totals(const FinishArgs &a, hipStream_t st);
+int launch_filter_operands(const FilterArgs &a, hipStream_t st);
+int launch_filter(const FilterArgs &a, hipStream_t st);
+int launch_invert(const InvertArgs &a, hipStream_t st);
+int launch_measure(const FilterArgs &a, hipStream_t st);
+int launch_range_exact(ReplayArgs a, int64_t nslots, int nchunk, hipStream_t st);
+size_t replay_lds(int d, int k, int nseg);      // LDS of one of their workgroups
+int launch_replay(ReplayArgs a, int64_t nslots, hipStream_t st);
+
 TRIM_DECLARE_LAUNCH(launch_search_knnlean_e1_c8);
 TRIM_DECLARE_LAUNCH(launch_search_knnlean_e1_c4);
 TRIM_DECLARE_LAUNCH(launch_search_knnleanlong_e1_c8);

@@ -1,0 +1,1358 @@
+// The scan in separate passes (Section 4.2), for launches whose exact distances are better computed
+// apart from the bounds:
+//
+//   filter  holds a stretch of every query's candidates against ONE threshold, on the matrix cores, list by
+//           list for all the queries that scan the list, and marks who may pass: a bit per candidate
+//   finish  the bounds of the marked candidates, by the rule; who does not pass is unmarked
+//   measure a lower bound of the distance of everyone still marked, on the matrix cores: a raw row is read once for
+//           all the queries that want it, and few exact distances are left to take
+//   replay  (kNN) walks a query's marked candidates in scan order, batch by batch, with the threshold
+//           rule of Section 4.2, and merges the survivors into R
+//   range_exact  (range) the exact distances of those that the lower bound leaves
+//
+// search_kernel does all of it inside one workgroup per query, so every survivor's row is read by
+// that query alone.  With long rows this is what bounds the search: on 2,500 queries over 500,000 x 768
+// every query refines the 3,940 rows of its own mixture component, 30 GB of the same few rows over
+// and over, and the distance table leaves one workgroup per CU, whose lookups wait while its rows
+// are fetched.  Thresholds only fall, so the candidates marked against the threshold at the start
+// of a stretch contain every survivor of it; the replay decides which they are, exactly as in search_kernel.
+#pragma once
+
+#include "trim_passes.h"
+#include "trim_search.h"
+
+namespace trim {
+
+// ---- what the passes share ----
+
+// The segment table of a query (see SearchArgs): segp[0..nseg] prefix of the lengths, cut at max_cand,
+// segd[p] = storage position of the segment's first candidate less its scan-order number.  All
+// threads of the workgroup; ends with a barrier.  Sums saturate at max_cand < 2^31, so 32 bits do.
+__device__ __forceinline__ void segment_table(const int64_t *list_offsets, const int32_t *probes, int nlist, int nseg,
+                                              int64_t n, int max_cand, int64_t q, int *segp, int *segd) {
+    const int ns = nseg > 0 ? nseg : 1;
+    for (int p = threadIdx.x; p < ns; p += blockDim.x) {
+        int64_t s = 0, e = n;
+        if (nseg > 0) {
+            const int32_t l = probes[(size_t)q * nseg + p];
+            if (l >= 0 && l < nlist) {
+                s = list_offsets[l];
+                e = list_offsets[l + 1];
+                s = s < 0 ? 0 : (s > n ? n : s);
+                e = e < s ? s : (e > n ? n : e);
+            } else {
+                s = e = 0;
+            }
+        }
+        segd[p] = (int)s;
+        segp[p + 1] = (int)(e - s);
+    }
+    __syncthreads();
+    if (threadIdx.x < kWave) {
+        const int lane = threadIdx.x;
+        uint32_t carry = 0;
+        const uint32_t cap = (uint32_t)max_cand;
+        for (int p0 = 0; p0 < ns; p0 += kWave) {
+            const int p = p0 + lane;
+            uint32_t incl = p < ns ? (uint32_t)segp[p + 1] : 0u;
+            incl = incl < cap ? incl : cap;
+#pragma unroll
+            for (int off = 1; off < kWave; off <<= 1) {
+                const uint32_t v = (uint32_t)__shfl_up((int)incl, off);
+                if (lane >= off) { incl += v; incl = incl < cap ? incl : cap; }
+            }
+            incl += carry;
+            incl = incl < cap ? incl : cap;
+            uint32_t before = (uint32_t)__shfl_up((int)incl, 1);
+            if (lane == 0) before = carry;
+            if (p < ns) { segp[p + 1] = (int)incl; segd[p] -= (int)before; }
+            carry = (uint32_t)__shfl((int)incl, kWave - 1);
+        }
+        if (lane == 0) segp[0] = 0;
+    }
+    __syncthreads();
+}
+
+__device__ __forceinline__ int segment_position(int c, const int *segp, const int *segd, int nseg) {
+    int lo = 0, hi = (nseg > 0 ? nseg : 1) - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (c >= segp[mid + 1]) lo = mid + 1; else hi = mid;
+    }
+    return c + segd[lo];
+}
+
+// ---- filter: who can pass, on the matrix cores ----
+// With long codes the table lookups of the bounds are what a search costs, and early abandon saves
+// little of them where no part of a code decides (unit vectors: half of the subspaces have to be summed
+// before far candidates are out).  But Gamma(l,q)^2 = |q|^2 + |l|^2 - 2 q.l is a contraction, and
+// queries that probe the same list share its landmarks: list by list, 256 landmarks x 128 queries
+// per workgroup and tile, by v_mfma_f32_32x32x16_f16.  A landmark's operand is its centroids, so it is never built:
+// a lane gathers 16 bytes of the (16-bit) centroids of its code byte from LDS and that is the operand.
+//
+// The filter only decides who is looked at again: whoever may pass is marked, and finish_kernel takes
+// the marked candidates' table sums by the rule.  Soundness: with q', l' the rounded operands (relative
+// to the centroids' means mu, scaled by a power of two), |q - l| >= |q' - l'| - |q - q'| - |l - l'|;
+// the two distances moved by rounding are added to the line that bounds sqrt(s) (see abandon_line),
+//     r = alpha + beta b + moved(q) + moved(l),    out if s' > r |r|,
+// moved(q) measured, moved(l) <= (2^-11 + 2^-22) |l'| and what 16-bit subnormals lose; the binary32
+// accumulation of s' errs by at most (4 d + 64) 2^-24 of |q'|^2 + |l'|^2, taken off.
+// A query out of the 16-bit range after scaling has alpha = inf: all its candidates are marked.
+__global__ __launch_bounds__(256) void filter_means_kernel(const FilterArgs a) {
+    const int j = blockIdx.x, c = threadIdx.x, wave = c >> 6;
+    __shared__ float part[4];
+    float most = 0.0f;
+    for (int t = 0; t < a.dsub; ++t) {
+        const float v = c < a.ncent ? a.codebooks[((size_t)j * a.ncent + c) * a.dsub + t] : 0.0f;
+        float sum = v;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+        if ((c & 63) == 0) part[wave] = sum;
+        __syncthreads();
+        const float mu = (part[0] + part[1] + part[2] + part[3]) / (float)a.ncent;
+        __syncthreads();
+        if (c == 0) a.mu[j * a.dsub + t] = mu;
+        if (c < a.ncent) most = __builtin_fmaxf(most, __builtin_fabsf(v - mu));
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) most = __builtin_fmaxf(most, __shfl_xor(most, off));
+    if ((c & 63) == 0) atomicMax(a.max_bits, __float_as_uint(most));
+}
+// The power of two that brings the largest centered centroid value to 2^9 .. 2^10.
+__device__ __forceinline__ float filter_scale(uint32_t max_bits) {
+    const float m = __uint_as_float(max_bits);
+    if (!(m > 1e-30f && m < 1e30f)) return 0.0f;           // (no scale: everything is marked)
+    const int k = 9 - ((int)(max_bits >> 23) - 127);
+    return __uint_as_float((uint32_t)(k + 127) << 23);
+}
+// grid.x: the padded subspaces first (one thread per centroid), then one workgroup per query row
+__global__ __launch_bounds__(256) void filter_operands_kernel(const FilterArgs a) {
+    const float sc = filter_scale(*a.max_bits);
+    const int nb = a.kpad / a.padded;
+    if ((int)blockIdx.x < nb) {
+        const int j = blockIdx.x, c = threadIdx.x;
+        if (c >= a.ncent) return;
+        _Float16 *out = a.books + ((size_t)j * a.ncent + c) * a.padded;
+        for (int t = 0; t < a.padded; ++t) {
+            float v = 0.0f;
+            if (j < a.nsub && t < a.dsub) v = (a.codebooks[((size_t)j * a.ncent + c) * a.dsub + t] - a.mu[j * a.dsub + t]) * sc;
+            out[t] = (_Float16)v;
+        }
+        return;
+    }
+    const int64_t slot = blockIdx.x - nb;
+    const int64_t q = a.order ? a.order[a.slot0 + slot] : a.slot0 + slot;
+    if (q < 0 || q >= a.nq) return;
+    const int64_t row = a.by_query ? q : slot;
+    if (a.q16_rows != a.q16)               // the same values without the padding between sub-vectors, for the raw rows
+        for (int k = threadIdx.x; k < a.kpad_rows; k += 256) {
+            float v = 0.0f;
+            if (k < a.d) v = (a.queries[(size_t)q * a.d + k] - a.mu[k]) * sc;
+            if (!(__builtin_fabsf(v) <= 16384.0f)) v = 0.0f;
+            a.q16_rows[(size_t)row * a.kpad_rows + k] = (_Float16)(-2.0f * (float)(_Float16)v);
+        }
+    __shared__ float part[3][4];
+    float n2 = 0.0f, moved = 0.0f, most = 0.0f;
+    for (int k = threadIdx.x; k < a.kpad; k += 256) {
+        const int j = k / a.padded, t = k - j * a.padded;
+        float v = 0.0f;
+        if (j < a.nsub && t < a.dsub) v = (a.queries[(size_t)q * a.d + j * a.dsub + t] - a.mu[j * a.dsub + t]) * sc;
+        const float av = __builtin_fabsf(v);
+        most = av <= 16384.0f ? __builtin_fmaxf(most, av) : __builtin_inff();
+        if (!(av <= 16384.0f)) v = 0.0f;
+        const _Float16 h = (_Float16)v;
+        const float f = (float)h, e = v - f;
+        n2 = __builtin_fmaf(f, f, n2);
+        moved = __builtin_fmaf(e, e, moved);
+        a.q16[(size_t)row * a.kpad + k] = (_Float16)(-2.0f * f);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        n2 += __shfl_xor(n2, off);
+        moved += __shfl_xor(moved, off);
+        most = __builtin_fmaxf(most, __shfl_xor(most, off));
+    }
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) { part[0][wave] = n2; part[1][wave] = moved; part[2][wave] = most; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        n2 = part[0][0] + part[0][1] + part[0][2] + part[0][3];
+        moved = part[1][0] + part[1][1] + part[1][2] + part[1][3];
+        most = __builtin_fmaxf(__builtin_fmaxf(part[2][0], part[2][1]), __builtin_fmaxf(part[2][2], part[2][3]));
+        float m = sqrt_rn(moved) * 1.001f + sqrt_rn(n2) * (1.0f / 4194304.0f) + sqrt_rn((float)a.d) * (1.0f / 16384.0f);
+        if (!(most < __builtin_inff()) || sc == 0.0f) m = __builtin_inff();
+        a.qpar[2 * row] = n2;
+        a.qpar[2 * row + 1] = m;
+    }
+}
+
+// Candidates per query (what the filter cuts its tiles at), one wave per query.
+__global__ __launch_bounds__(256) void totals_kernel(const FinishArgs a) {
+    const int lane = threadIdx.x & 63;
+    const int64_t slot = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (slot >= a.nslots) return;
+    const int64_t q = a.order ? a.order[a.slot0 + slot] : a.slot0 + slot;
+    const int64_t row = a.by_query ? q : slot;
+    if (q < 0 || q >= a.nq) {
+        if (!a.by_query && lane == 0) a.totals[row] = 0;
+        return;
+    }
+    int64_t sum = 0;
+    if (a.nseg == 0) sum = lane == 0 ? a.n : 0;
+    for (int p = lane; p < a.nseg; p += kWave) {
+        const int32_t l = a.probes[(size_t)q * a.nseg + p];
+        if (l >= 0 && l < a.nlist) {
+            int64_t s = a.list_offsets[l], e = a.list_offsets[l + 1];
+            s = s < 0 ? 0 : (s > a.n ? a.n : s);
+            e = e < s ? s : (e > a.n ? a.n : e);
+            sum += e - s;
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor((long long)sum, off);
+    if (lane == 0) a.totals[row] = (int)(sum < a.max_cand ? sum : a.max_cand);
+}
+
+// PAD: values per sub-vector after padding; FS: two 4-bit codes per byte.  Persistent: workgroups take tiles until
+// there are no more.
+template <int PAD, bool FS>
+__global__ __launch_bounds__(kFltThreads, 2) void filter_kernel(const FilterArgs a) {
+    typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+    typedef float v16f __attribute__((ext_vector_type(16)));
+    constexpr int kCent = FS ? kC4 : kC;
+    constexpr int kSubs = kFltSlice / PAD;                        // subspaces per slice
+    constexpr int kBytes = FS ? kSubs / 2 : kSubs;                // code bytes per slice
+    constexpr int kBookBytes = kFltSlice * kCent * 2;             // 16 KB (FS: 1 KB)
+    __shared__ __align__(16) unsigned char s_book[2][kBookBytes];
+    __shared__ __align__(16) h8 s_q[2][4 * kFltQ];                // [16-value step][half][query]
+    __shared__ __align__(16) float s_b[kFltRows], s_nl[kFltRows], s_ml[kFltRows];
+    __shared__ float s_al[kFltQ], s_be[kFltQ], s_nq[kFltQ];
+    __shared__ int s_row[kFltQ], s_c0[kFltQ], s_end[kFltQ];
+    __shared__ float s_b0[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, half = lane >> 5;
+    const float sc = filter_scale(*a.max_bits);
+    const int nslice = a.kpad / kFltSlice;
+    const int64_t rows_all = a.n < a.hi ? a.n : a.hi, qall = a.by_query ? a.nq : a.nslots;
+    const int total_tasks = a.list_offsets ? a.tasks[a.nlist]
+                            : (int)((rows_all + kFltRows - 1) / kFltRows * ((qall + kFltQ - 1) / kFltQ));
+    for (int task = blockIdx.x; task < total_tasks; task += gridDim.x) {
+        // which list, rows, queries
+        int64_t ls = 0, le = a.n;
+        int i0 = 0, i1 = (int)qall, t = task;
+        if (a.list_offsets) {
+            int x = 0, y = a.nlist - 1;
+            while (x < y) {
+                const int mid = (x + y) >> 1;
+                if (a.tasks[mid + 1] <= task) x = mid + 1; else y = mid;
+            }
+            ls = a.list_offsets[x];
+            le = a.list_offsets[x + 1];
+            ls = ls < 0 ? 0 : (ls > a.n ? a.n : ls);
+            le = le < ls ? ls : (le > a.n ? a.n : le);
+            i0 = a.inv_start[x];
+            i1 = a.inv_start[x + 1];
+            t -= a.tasks[x];
+        }
+        const int nqt = (i1 - i0 + kFltQ - 1) / kFltQ;
+        const int rt = t / nqt, qt = t - rt * nqt;
+        const int64_t r0 = ls + (int64_t)rt * kFltRows;
+        const int nrows = le - r0 < kFltRows ? (int)(le - r0) : kFltRows;
+        const int q0 = i0 + qt * kFltQ, nqs = i1 - q0 < kFltQ ? i1 - q0 : kFltQ;
+        __syncthreads();     // the previous tile is done with
+        // landmark distances of the rows, their mean (the tangent point)
+        {
+            float b = 0.0f;
+            if (tid < nrows) b = a.dlx[r0 + tid];
+            s_b[tid] = b * sc;
+            float sum = b;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+            if (lane == 0) s_b0[wave] = sum;
+        }
+        __syncthreads();
+        bool any = false;
+        if (tid < kFltQ) {
+            float al = -1.0f, be = 0.0f, nq = 0.0f;
+            int row = 0, c0 = 0, end = 0;
+            if (tid < nqs) {
+                int64_t c = 0;
+                row = q0 + tid;
+                if (a.list_offsets) { const int2 v = a.inv[q0 + tid]; row = v.x; c = v.y; }
+                c += r0 - ls;
+                end = a.totals[row];
+                end = end < a.hi ? end : a.hi;
+                c0 = c < end ? (int)c : end;
+                if (c < end && c + nrows > a.lo) {
+                    const int64_t q = a.by_query ? row : a.order ? a.order[a.slot0 + row] : a.slot0 + row;
+                    const float tau = a.range ? a.radius2 : a.tau_of ? a.tau_of[(size_t)q * a.tau_stride] : __builtin_inff();
+                    const float b0 = ((s_b0[0] + s_b0[1]) + (s_b0[2] + s_b0[3])) / (float)nrows;
+                    const AbandonLine line = abandon_line(tau, a.two_gamma, b0);
+                    nq = a.qpar[2 * (size_t)row];
+                    al = line.alpha * sc + a.qpar[2 * (size_t)row + 1];
+                    be = line.beta;
+                    if (!(al == al)) al = __builtin_inff();
+                    any = true;
+                } else {
+                    end = c0;      // nothing of this query in these rows
+                }
+            }
+            s_al[tid] = al; s_be[tid] = be; s_nq[tid] = nq;
+            s_row[tid] = row; s_c0[tid] = c0; s_end[tid] = end;
+        }
+        if (!__syncthreads_or(any)) continue;
+        // staging: a slice of the centroids (contiguous) and of the queries
+        typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+        const u4 *book_src = reinterpret_cast<const u4 *>(a.books);
+        constexpr int kBookV = kBookBytes / 16;
+        const int sq = tid >> 1, sh = tid & 1;                     // query, 16-value step
+        const u4 *q_src = reinterpret_cast<const u4 *>(a.q16 + (size_t)s_row[sq] * a.kpad + sh * 16);
+        u4 bk[kBookV > kFltThreads ? kBookV / kFltThreads : 1], qv[2];
+        auto load = [&](int sl) {
+#pragma unroll
+            for (int i = 0; i < (kBookV > kFltThreads ? kBookV / kFltThreads : 1); ++i)
+                if (kBookV >= kFltThreads || tid < kBookV) bk[i] = book_src[(size_t)sl * kBookV + i * kFltThreads + tid];
+            qv[0] = q_src[(size_t)sl * (kFltSlice / 8)];
+            qv[1] = q_src[(size_t)sl * (kFltSlice / 8) + 1];
+        };
+        auto stage = [&](int buf) {
+            u4 *bd = reinterpret_cast<u4 *>(s_book[buf]);
+#pragma unroll
+            for (int i = 0; i < (kBookV > kFltThreads ? kBookV / kFltThreads : 1); ++i)
+                if (kBookV >= kFltThreads || tid < kBookV) bd[i * kFltThreads + tid] = bk[i];
+            u4 *qd = reinterpret_cast<u4 *>(s_q[buf]);
+            qd[(sh * 2) * kFltQ + sq] = qv[0];
+            qd[(sh * 2 + 1) * kFltQ + sq] = qv[1];
+        };
+        // the code bytes of this lane's two rows, a slice at a time
+        const uint8_t *code[2];
+        uint32_t cw[2][(kBytes + 3) / 4], cn[2][(kBytes + 3) / 4];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int r = wave * 64 + u * 32 + col;
+            code[u] = a.codes + (size_t)(r0 + (r < nrows ? r : 0)) * a.M;
+        }
+        auto load_code = [&](int sl, uint32_t (&w)[2][(kBytes + 3) / 4]) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int v = 0; v < (kBytes + 3) / 4; ++v) {
+                    const int at = sl * kBytes + 4 * v;            // (past the code: padding subspaces, all centroids zero)
+                    w[u][v] = at < a.M ? *reinterpret_cast<const uint32_t *>(code[u] + (at & ~3)) >> (8 * (at & 3)) : 0u;
+                }
+        };
+        v16f acc[2][4];
+        float nl[2] = {0.0f, 0.0f};
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[u][v][i] = 0.0f;
+        const bool busy = wave * 64 < nrows;
+        const int nv = (nqs + 31) >> 5;               // query tiles of this one in use
+        load(0);
+        load_code(0, cw);
+        stage(0);
+        __syncthreads();
+        for (int sl = 0; sl < nslice; ++sl) {
+            if (sl + 1 < nslice) {
+                load(sl + 1);
+                load_code(sl + 1, cn);
+            }
+            if (busy) {
+                const unsigned char *bb = s_book[sl & 1];
+                const h8 *qq = s_q[sl & 1];
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    h8 lm[2], qf[4];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (v < nv) qf[v] = qq[(ks * 2 + half) * kFltQ + v * 32 + col];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        if constexpr (FS) {                       // four sub-vectors of two values
+                            const uint32_t word = cw[u][ks] >> (16 * half);
+                            h2 p[4];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                p[e] = *reinterpret_cast<const h2 *>(bb + (((ks * 8 + half * 4 + e) * kCent + ((word >> (4 * e)) & 15u)) << 2));
+                            lm[u] = h8{p[0][0], p[0][1], p[1][0], p[1][1], p[2][0], p[2][1], p[3][0], p[3][1]};
+                        } else if constexpr (PAD == 4) {          // two
+                            const uint32_t word = cw[u][ks] >> (16 * half);
+                            const h4 p0 = *reinterpret_cast<const h4 *>(bb + (((ks * 4 + half * 2) * kCent + (word & 255u)) << 3));
+                            const h4 p1 = *reinterpret_cast<const h4 *>(bb + (((ks * 4 + half * 2 + 1) * kCent + ((word >> 8) & 255u)) << 3));
+                            lm[u] = h8{p0[0], p0[1], p0[2], p0[3], p1[0], p1[1], p1[2], p1[3]};
+                        } else {                                  // one, or a part of one
+                            constexpr int kParts = PAD >= 8 ? PAD / 8 : 1;       // operands per sub-vector
+                            const int op = ks * 2 + half, sub = op / kParts, part = op % kParts;
+                            const uint32_t c = (cw[u][0] >> (8 * sub)) & 255u;
+                            lm[u] = *reinterpret_cast<const h8 *>(bb + (sub * kCent + c) * (PAD * 2) + part * 16);
+                        }
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const h2 p = {lm[u][2 * e], lm[u][2 * e + 1]};
+                            nl[u] = __builtin_amdgcn_fdot2(p, p, nl[u], false);
+                        }
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (v < nv) {
+#pragma unroll
+                            for (int u = 0; u < 2; ++u) acc[u][v] = __builtin_amdgcn_mfma_f32_32x32x16_f16(lm[u], qf[v], acc[u][v], 0, 0, 0);
+                        }
+                }
+            }
+            if (sl + 1 < nslice) {
+                stage((sl + 1) & 1);
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int v = 0; v < (kBytes + 3) / 4; ++v) cw[u][v] = cn[u][v];
+            }
+            __syncthreads();
+        }
+        constexpr float kUlp = 1.0f / 16777216.0f;
+        const float keep = 1.0f - (4.0f * a.d + 64.0f) * kUlp;
+        if (busy) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {                         // (this wave's rows only: no barrier needed)
+                const float n2 = nl[u] + __shfl_xor(nl[u], 32);
+                const int r = wave * 64 + u * 32 + col;
+                if (half == 0) {
+                    s_nl[r] = n2 * keep;
+                    s_ml[r] = sqrt_rn(n2) * (1.0f / 2048.0f + 1.0f / 4194304.0f) * 1.001f + sqrt_rn((float)a.d) * (1.0f / 16384.0f);
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                float rb[16], rn[16], rm[16];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int r = wave * 64 + u * 32 + 8 * i + 4 * half;
+                    const float4 x = *reinterpret_cast<const float4 *>(s_b + r), y = *reinterpret_cast<const float4 *>(s_nl + r),
+                                 z = *reinterpret_cast<const float4 *>(s_ml + r);
+                    rb[4 * i] = x.x; rb[4 * i + 1] = x.y; rb[4 * i + 2] = x.z; rb[4 * i + 3] = x.w;
+                    rn[4 * i] = y.x; rn[4 * i + 1] = y.y; rn[4 * i + 2] = y.z; rn[4 * i + 3] = y.w;
+                    rm[4 * i] = z.x; rm[4 * i + 1] = z.y; rm[4 * i + 2] = z.z; rm[4 * i + 3] = z.w;
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    if (v >= nv) break;
+                    const int qi = v * 32 + col;
+                    const float al = s_al[qi], be = s_be[qi], nq = s_nq[qi] * keep;
+                    uint32_t m = 0;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const float r = __builtin_fmaf(be, rb[i], al) + rm[i];
+                        const float s = acc[u][v][i] + (nq + rn[i]);
+                        if (!(s > r * __builtin_fabsf(r))) m |= 1u << (8 * (i >> 2) + (i & 3));
+                    }
+                    m <<= 4 * half;
+                    m |= (uint32_t)__shfl_xor((int)m, 32);
+                    // rows of the tile that exist, candidates of this pass
+                    const int c0 = s_c0[qi] + wave * 64 + u * 32, end = s_end[qi];
+                    if (c0 + 32 > end) m &= c0 < end ? (1u << (end - c0)) - 1u : 0u;
+                    if (c0 < a.lo) m &= a.lo - c0 < 32 ? ~0u << (a.lo - c0) : 0u;
+                    const int left = nrows - (wave * 64 + u * 32);
+                    if (left < 32) m &= left > 0 ? (1u << left) - 1u : 0u;
+                    const int shf = c0 & 31;
+                    const uint32_t part = half == 0 ? m << shf : (shf ? m >> (32 - shf) : 0u);
+                    if (part) atomicOr(&a.possible[(size_t)s_row[qi] * a.words + (c0 >> 5) + half], part);
+                }
+            }
+        }
+    }
+}
+
+// ---- measure: lower bounds of the exact distances of the marked candidates ----
+// The filter's contraction over the raw rows (16-bit, relative to mu, scaled; converted while they are staged), list by
+// list, 256 rows at a time against the queries that have a candidate marked among them (up to 128 together):
+//     d2 >= ((|q' - x'| - moved(q) - moved(x)) / scale)^2   less the exact rule's own roundings.
+// Only where that does not exceed the threshold is the exact distance taken (replay_kernel,
+// range_exact_kernel).  A row is read once for all its queries, and the contraction takes the place of 2 d
+// vector operations per survivor: of 3,940 survivors per query (2,500 queries x 500,000 x 768) some forty
+// can still matter.  Bound by reading the rows (and their conversion).
+__global__ __launch_bounds__(kFltThreads, 2) void measure_kernel(const FilterArgs a) {
+    typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+    typedef float v16f __attribute__((ext_vector_type(16)));
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    constexpr int kXRows = kFltRows + 2;                          // rows per 8 columns (two spare: bank spread)
+    __shared__ __align__(16) unsigned char s_x[2][4 * kXRows * 16];
+    __shared__ __align__(16) h8 s_q[2][4 * kFltQ];                // [8 columns][query]
+    __shared__ __align__(16) float s_nx[kFltRows], s_mx[kFltRows];
+    __shared__ float s_mq[2 * kFltQ], s_nq[2 * kFltQ];
+    __shared__ int s_row[2 * kFltQ], s_c0[2 * kFltQ], s_end[2 * kFltQ];
+    __shared__ int s_n;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, half = lane >> 5;
+    const float sc = filter_scale(*a.max_bits);
+    const int nslice = a.kpad_rows / kFltSlice;
+    const int64_t rows_all = a.n < a.hi ? a.n : a.hi, qall = a.by_query ? a.nq : a.nslots;
+    constexpr float kUlp = 1.0f / 16777216.0f;
+    const float keep = 1.0f - (4.0f * a.d + 64.0f) * kUlp;
+    const float back = sc > 0.0f ? (1.0f - (a.d / 32 + 16.0f) * 2.0f * kUlp) / (sc * sc) : 0.0f;
+    const float lost = sqrt_rn((float)a.d) * (1.0f / 16384.0f);
+    const int total_tasks = a.list_offsets ? a.row_tasks[a.nlist]
+                            : (int)((rows_all + kFltRows - 1) / kFltRows * ((qall + kFltQ - 1) / kFltQ));
+    for (int task = blockIdx.x; task < total_tasks; task += gridDim.x) {
+        int64_t ls = 0, r0, le = a.n;
+        int qb, q1;
+        if (a.list_offsets) {
+            int x = 0, y = a.nlist - 1;
+            while (x < y) {
+                const int mid = (x + y) >> 1;
+                if (a.row_tasks[mid + 1] <= task) x = mid + 1; else y = mid;
+            }
+            ls = a.list_offsets[x];
+            le = a.list_offsets[x + 1];
+            ls = ls < 0 ? 0 : (ls > a.n ? a.n : ls);
+            le = le < ls ? ls : (le > a.n ? a.n : le);
+            qb = a.inv_start[x];
+            q1 = a.inv_start[x + 1];
+            r0 = ls + (int64_t)(task - a.row_tasks[x]) * kFltRows;
+        } else {
+            const int nqt = (int)((qall + kFltQ - 1) / kFltQ);
+            const int rt = task / nqt;
+            qb = (task - rt * nqt) * kFltQ;
+            q1 = qb + kFltQ < (int)qall ? qb + kFltQ : (int)qall;
+            r0 = (int64_t)rt * kFltRows;
+        }
+        const int nrows = le - r0 < kFltRows ? (int)(le - r0) : kFltRows;
+        int have = 0;                     // queries waiting in the arrays (the same for all threads)
+        __syncthreads();                  // (the previous tile is done with)
+        while (qb < q1 || have > 0) {
+            // gather queries with a mark in these rows until there are 128, or no more
+            while (qb < q1 && have < kFltQ) {
+                if (tid == 0) s_n = have;
+                __syncthreads();
+                if (tid < kFltQ && qb + tid < q1) {
+                    int row = qb + tid;
+                    int64_t c = 0;
+                    if (a.list_offsets) { const int2 v = a.inv[qb + tid]; row = v.x; c = v.y; }
+                    c += r0 - ls;
+                    int end = a.totals[row];
+                    end = end < a.hi ? end : a.hi;
+                    if (c < end && c + nrows > a.lo) {
+                        const uint32_t *bits = a.possible + (size_t)row * a.words;
+                        const int64_t c1 = c + nrows < end ? c + nrows : end, c2 = c > a.lo ? c : a.lo;
+                        const int w0 = (int)(c2 >> 5), w1 = (int)((c1 - 1) >> 5);
+                        uint32_t any = 0;
+                        for (int w = w0; w <= w1; ++w) {
+                            uint32_t b = bits[w];
+                            if (w == w0) b &= ~0u << (c2 & 31);
+                            if (w == w1 && (c1 & 31)) b &= (1u << (c1 & 31)) - 1u;
+                            any |= b;
+                        }
+                        if (any) {
+                            const int at = atomicAdd(&s_n, 1);
+                            s_row[at] = row; s_c0[at] = (int)c; s_end[at] = end;
+                            s_nq[at] = a.qpar[2 * (size_t)row];
+                            s_mq[at] = a.qpar[2 * (size_t)row + 1];
+                        }
+                    }
+                }
+                qb += kFltQ;
+                __syncthreads();
+                have = s_n;
+                __syncthreads();
+            }
+            if (have == 0) break;
+            const int nqs = have < kFltQ ? have : kFltQ, nv = (nqs + 31) >> 5;
+            // staging: eight threads per row (a whole cache line together), eight rows each, 32 apart; two per query
+            const int xr = tid >> 3, xc = tid & 7, sq = tid >> 1, sh = tid & 1;
+            f4 xv[8], xmu = {0.0f, 0.0f, 0.0f, 0.0f};
+            float nx[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) nx[i] = 0.0f;
+            const bool q_on = sq < nv * 32;
+            const u4 *q_src = reinterpret_cast<const u4 *>(a.q16_rows + (size_t)s_row[sq < nqs ? sq : 0] * a.kpad_rows + sh * 16);
+            u4 qv[2];
+            auto load = [&](int sl) {
+                const int k = sl * kFltSlice + 4 * xc;
+                const bool in = k < a.d;
+                if (in) xmu = *reinterpret_cast<const f4 *>(a.mu + k);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int r = xr + 32 * i;
+                    xv[i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+                    if (in && r < nrows) xv[i] = *reinterpret_cast<const f4 *>(a.base + (size_t)(r0 + r) * a.d + k);
+                }
+                if (q_on) {
+                    qv[0] = q_src[(size_t)sl * (kFltSlice / 8)];
+                    qv[1] = q_src[(size_t)sl * (kFltSlice / 8) + 1];
+                }
+            };
+            auto stage = [&](int buf, int sl) {
+                const bool in = sl * kFltSlice + 4 * xc < a.d;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    h4 h = {0, 0, 0, 0};
+                    if (in) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) h[e] = (_Float16)__builtin_fmaf(xv[i][e], sc, -(xmu[e] * sc));
+                        nx[i] = __builtin_amdgcn_fdot2(h2{h[0], h[1]}, h2{h[0], h[1]}, nx[i], false);
+                        nx[i] = __builtin_amdgcn_fdot2(h2{h[2], h[3]}, h2{h[2], h[3]}, nx[i], false);
+                    }
+                    *reinterpret_cast<h4 *>(s_x[buf] + ((xc >> 1) * kXRows + xr + 32 * i) * 16 + (xc & 1) * 8) = h;
+                }
+                if (q_on) {
+                    u4 *qd = reinterpret_cast<u4 *>(s_q[buf]);
+                    qd[(sh * 2) * kFltQ + sq] = qv[0];
+                    qd[(sh * 2 + 1) * kFltQ + sq] = qv[1];
+                }
+            };
+            v16f acc[2][4];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[u][v][i] = 0.0f;
+            const bool busy = wave * 64 < nrows;
+            load(0);
+            stage(0, 0);
+            __syncthreads();
+            for (int sl = 0; sl < nslice; ++sl) {
+                if (sl + 1 < nslice) load(sl + 1);
+                if (busy) {
+                    const unsigned char *bb = s_x[sl & 1];
+                    const h8 *qq = s_q[sl & 1];
+#pragma unroll
+                    for (int ks = 0; ks < 2; ++ks) {
+                        h8 xf[2];
+#pragma unroll
+                        for (int u = 0; u < 2; ++u)
+                            xf[u] = *reinterpret_cast<const h8 *>(bb + ((ks * 2 + half) * kXRows + wave * 64 + u * 32 + col) * 16);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            if (v < nv) {
+                                const h8 qf = qq[(ks * 2 + half) * kFltQ + v * 32 + col];
+#pragma unroll
+                                for (int u = 0; u < 2; ++u) acc[u][v] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xf[u], qf, acc[u][v], 0, 0, 0);
+                            }
+                    }
+                }
+                if (sl + 1 < nslice) stage((sl + 1) & 1, sl + 1);
+                __syncthreads();
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                float v = nx[i];
+                v += __shfl_xor(v, 1);
+                v += __shfl_xor(v, 2);
+                v += __shfl_xor(v, 4);
+                if (xc == 0) {
+                    s_nx[xr + 32 * i] = v * keep;
+                    s_mx[xr + 32 * i] = sqrt_rn(v) * (1.0f / 2048.0f + 1.0f / 4194304.0f) * 1.001f + lost;
+                }
+            }
+            __syncthreads();
+            if (busy) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    if (v >= nv) break;
+                    const int qi = v * 32 + col;
+                    const bool real = qi < nqs;
+                    const float mq = real ? s_mq[qi] : 0.0f, nq = real ? s_nq[qi] * keep : 0.0f;
+                    const int cq = real ? s_c0[qi] : 0, end = real ? s_end[qi] : 0;
+                    const size_t at = (size_t)(real ? s_row[qi] : 0) * a.words;
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const int c0 = cq + wave * 64 + u * 32;
+                        uint32_t m = 0;
+                        if (c0 < end) {
+                            m = a.possible[at + (c0 >> 5)] >> (c0 & 31);
+                            if (c0 & 31) m |= a.possible[at + (c0 >> 5) + 1] << (32 - (c0 & 31));
+                            if (c0 + 32 > end) m &= (1u << (end - c0)) - 1u;
+                            if (c0 < a.lo) m &= a.lo - c0 < 32 ? ~0u << (a.lo - c0) : 0u;
+                            const int left = nrows - (wave * 64 + u * 32);
+                            if (left < 32) m &= left > 0 ? (1u << left) - 1u : 0u;
+                        }
+                        if (!__any(m != 0)) continue;
+                        float *out = a.d2 + at * 32 + c0;
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) {
+                            const int r = 8 * (i >> 2) + 4 * half + (i & 3);
+                            if ((m >> r) & 1u) {
+                                const float s = acc[u][v][i] + (nq + s_nx[wave * 64 + u * 32 + r]);
+                                float dist = sqrt_rn(__builtin_fmaxf(s, 0.0f)) - (mq + s_mx[wave * 64 + u * 32 + r]);
+                                // (out of the 16-bit range: nothing is known)
+                                dist = dist < 1e18f && s < 1e36f ? __builtin_fmaxf(dist, 0.0f) : 0.0f;
+                                out[r] = dist * dist * back;
+                            }
+                        }
+                    }
+                }
+            }
+            __syncthreads();
+            // who did not fit comes to the front
+            const int rest = have - nqs;
+            int r_row = 0, r_c0 = 0, r_end = 0;
+            float r_nq = 0.0f, r_mq = 0.0f;
+            if (tid < rest) {
+                r_row = s_row[nqs + tid]; r_c0 = s_c0[nqs + tid]; r_end = s_end[nqs + tid];
+                r_nq = s_nq[nqs + tid]; r_mq = s_mq[nqs + tid];
+            }
+            __syncthreads();
+            if (tid < rest) { s_row[tid] = r_row; s_c0[tid] = r_c0; s_end[tid] = r_end; s_nq[tid] = r_nq; s_mq[tid] = r_mq; }
+            have = rest;
+            __syncthreads();
+        }
+    }
+}
+
+// ---- finish: the bounds of the marked candidates, by the rule ----
+// One workgroup per query: its table in the LDS (rows of one phase at a time), its marked candidates
+// (or, all: every candidate of the pass) listed a few thousand at a time, one per thread; who does not
+// pass is unmarked.
+template <int VEC, bool FS>
+__global__ __launch_bounds__(1024)
+__attribute__((amdgpu_waves_per_eu(4)))
+void finish_kernel(const FinishArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    float *tab = reinterpret_cast<float *>(smem);
+    float *q_lds = reinterpret_cast<float *>(smem + a.off_q);
+    int *segp = reinterpret_cast<int *>(smem + a.off_segp);
+    int *segd = reinterpret_cast<int *>(smem + a.off_segd);
+    uint32_t *bits = reinterpret_cast<uint32_t *>(smem + a.off_bits);   // [kFinishPiece / 32], then the waves' counts
+    int *part = reinterpret_cast<int *>(bits + kFinishPiece / 32);      // [16]
+    uint16_t *list = reinterpret_cast<uint16_t *>(smem + a.off_ring);   // [kFinishList]
+    const int tid = threadIdx.x, T = blockDim.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    const int64_t per_xcd = (a.nslots + kXcds - 1) / kXcds;
+    const int64_t slot = (int64_t)(blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+    if (slot >= a.nslots) return;
+    const int64_t q = a.order ? a.order[a.slot0 + slot] : a.slot0 + slot;
+    if (q < 0 || q >= a.nq) {
+        if (!a.by_query && a.totals && a.lo == 0 && tid == 0) a.totals[slot] = 0;
+        return;
+    }
+    const int64_t row = a.by_query ? q : slot;
+    const int nseg = a.nseg > 0 ? a.nseg : 1;
+    for (int t = tid; t < a.d; t += T) q_lds[t] = a.queries[(size_t)q * a.d + t];
+    segment_table(a.list_offsets, a.probes, a.nlist, a.nseg, a.n, a.max_cand, q, segp, segd);
+    const int total = segp[nseg];
+    if (a.lo == 0 && tid == 0) {
+        a.totals[row] = total;
+        if (a.n_scanned) a.n_scanned[q] = total;
+    }
+    const int lo = a.lo < total ? a.lo : total, hi = a.hi < total ? a.hi : total;
+    if (lo >= hi) return;
+    const float tau = a.range ? a.radius2 : a.tau_of ? a.tau_of[(size_t)q * a.tau_stride] : __builtin_inff();
+    auto fill = [&](int j0, int nj) {
+        if (a.lut) {
+            const float4 *src = reinterpret_cast<const float4 *>(a.lut + ((size_t)q * a.M + j0) * kByteEntries<FS>);
+            float4 *dst = reinterpret_cast<float4 *>(tab);
+            for (int e = tid; e < nj * (kByteEntries<FS> / 4); e += T) dst[e] = src[e];
+        } else {
+            build_table_rows<FS>(tab, q_lds, a.codebooks, a.dsub, j0, nj);
+        }
+    };
+    uint32_t *row_bits = a.possible + (size_t)row * a.words;
+    float *row_g = a.g + (size_t)row * a.words * 32;
+    int n_marked = 0, in_place = -1;            // the phase whose rows are in place
+    // The filter went by the centroids.  A caller's table may hold something else: unless its entries are the
+    // centroids' distances bit for bit, every candidate of the query counts as marked.
+    bool all_marked = a.all != 0;
+    if (a.lut && !all_marked) {
+        bool bad = false;
+        for (int ph = a.P - 1; ph >= 0; --ph) {
+            __syncthreads();
+            fill(ph * a.Mp, a.Mp);
+            __syncthreads();
+            table_rows<FS>(q_lds, a.codebooks, a.dsub, ph * a.Mp, a.Mp,
+                           [&](int e, float v) { bad = bad || __float_as_uint(tab[e]) != __float_as_uint(v); });
+        }
+        in_place = 0;
+        if (tid == 0) part[0] = 0;      // (no __syncthreads_or: its static LDS would displace the table)
+        __syncthreads();
+        if (bad) part[0] = 1;
+        __syncthreads();
+        all_marked = part[0] != 0;
+        __syncthreads();
+    }
+    for (int p0 = lo & ~31; p0 < hi; p0 += kFinishPiece) {
+        const int S = hi - p0 < kFinishPiece ? hi - p0 : kFinishPiece;
+        const int nwords = (S + 31) >> 5;
+        // (one word per thread and step; T >= 512)
+        int all = 0;
+        for (int w = tid; w < kFinishPiece / 32; w += T) {
+            uint32_t b = 0;
+            if (w < nwords) {
+                b = all_marked ? ~0u : row_bits[(p0 >> 5) + w];
+                if (p0 + w * 32 < lo) b &= ~0u << (lo - p0 - w * 32);
+                if (p0 + w * 32 + 32 > hi) b &= (1u << (hi - p0 - w * 32)) - 1u;
+            }
+            bits[w] = b;
+        }
+        __syncthreads();
+        for (int ph = 0; ph < a.P; ++ph) {
+            const bool last = ph == a.P - 1;
+            if (in_place != ph) { fill(ph * a.Mp, a.Mp); in_place = ph; __syncthreads(); }
+            for (int w0 = 0; w0 < nwords; w0 += T) {
+                const uint32_t b = w0 + tid < nwords ? bits[w0 + tid] : 0u;
+                const int cnt = __popc(b);
+                int incl = cnt;
+#pragma unroll
+                for (int off = 1; off < kWave; off <<= 1) {
+                    const int v = __shfl_up(incl, off);
+                    if (lane >= off) incl += v;
+                }
+                if (lane == kWave - 1) part[wave] = incl;
+                __syncthreads();
+                int before = incl - cnt;
+                all = 0;
+                for (int v = 0; v < T / kWave; ++v) {
+                    const int x = part[v];
+                    if (v < wave) before += x;
+                    all += x;
+                }
+                for (int e0 = 0; e0 < all; e0 += kFinishList) {
+                    const int np = all - e0 < kFinishList ? all - e0 : kFinishList;
+                    uint32_t rem = b;
+                    int at = before - e0;
+                    while (rem) {
+                        if (at >= 0 && at < np) list[at] = (uint16_t)((w0 + tid) * 32 + (__ffs((int)rem) - 1));
+                        rem &= rem - 1;
+                        ++at;
+                    }
+                    __syncthreads();
+                    for (int i = tid; i < np; i += T) {
+                        const int cl = list[i];
+                        const int pos = segment_position(p0 + cl, segp, segd, nseg);
+                        const uint8_t *code = a.codes + (size_t)pos * a.M + ph * a.Mp;
+                        const float b1 = last ? a.dlx[pos] : 0.0f;
+                        float sum = ph > 0 ? row_g[p0 + cl] : 0.0f;
+                        constexpr int kAhead = 6;
+                        for (int j = 0; j < a.Mp; j += kAhead * 4 * VEC) {
+                            uint32_t w[kAhead][VEC];
+#pragma unroll
+                            for (int c = 0; c < kAhead; ++c)
+                                if (j + c * 4 * VEC < a.Mp) load_codes<VEC>(w[c], code + j + c * 4 * VEC);
+#pragma unroll
+                            for (int c = 0; c < kAhead; ++c)
+                                if (j + c * 4 * VEC < a.Mp)
+                                    sum = gather_add<VEC, false, FS>(sum, (j + c * 4 * VEC) * kByteRow<FS>, w[c], __builtin_inff());
+                        }
+                        float keep = sum;
+                        if (last) {
+                            keep = plb_from_s(sum, b1, a.two_gamma);
+                            if (!(keep <= tau)) atomicAnd(&bits[cl >> 5], ~(1u << (cl & 31)));
+                        }
+                        row_g[p0 + cl] = keep;
+                    }
+                    __syncthreads();
+                }
+            }
+        }
+        for (int w = tid; w < nwords; w += T) {
+            const uint32_t b = bits[w];
+            if (a.range) {
+                n_marked += __popc(b);
+                if (a.mask && b) {
+                    const int64_t wi = (p0 >> 5) + w;
+                    if (wi < a.mask_words) atomicOr(&a.mask[(size_t)q * a.mask_words + wi], b);
+                }
+            }
+            row_bits[(p0 >> 5) + w] = b;
+        }
+        __syncthreads();
+    }
+    if (a.range && a.n_exact) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) n_marked += __shfl_xor(n_marked, off);
+        if (lane == 0 && n_marked) atomicAdd(&a.n_exact[q], n_marked);
+    }
+}
+
+// ---- which queries scan a list ----
+
+__global__ void invert_count_kernel(const InvertArgs a) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= a.nslots * a.nseg) return;
+    const int64_t slot = i / a.nseg, q = a.query(slot);
+    if (q < 0) return;
+    const int32_t l = a.probes[(size_t)q * a.nseg + (i - slot * a.nseg)];
+    if (l >= 0 && l < a.nlist) atomicAdd(&a.cnt[l], 1);
+}
+// cnt [nlist] -> start [nlist + 1], and cnt becomes the running slots.  Single workgroup.
+__global__ __launch_bounds__(1024) void invert_scan_kernel(const InvertArgs a) {
+    int32_t *cnt = a.cnt, *start = a.start;
+    const int nlist = a.nlist;
+    __shared__ int part[16], tpart[16], rpart[16];
+    __shared__ int carry, tcarry, rcarry;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (tid == 0) carry = tcarry = rcarry = 0;
+    __syncthreads();
+    for (int l0 = 0; l0 < nlist; l0 += 1024) {
+        const int l = l0 + tid, v = l < nlist ? cnt[l] : 0;
+        int t = 0;
+        if (l < nlist && v > 0) {        // tiles of the filter: rows x queries
+            int64_t s = a.list_offsets[l], e = a.list_offsets[l + 1];
+            s = s < 0 ? 0 : (s > a.n ? a.n : s);
+            e = e < s ? s : (e > a.n ? a.n : e);
+            t = (int)((e - s + kFltRows - 1) / kFltRows) * ((v + kFltQ - 1) / kFltQ);
+        }
+        const int rt = (v > 0) ? t / ((v + kFltQ - 1) / kFltQ) : 0;      // rows alone (measure)
+        int incl = v, tincl = t, rincl = rt;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int o = __shfl_up(incl, off), to = __shfl_up(tincl, off), ro = __shfl_up(rincl, off);
+            if (lane >= off) { incl += o; tincl += to; rincl += ro; }
+        }
+        if (lane == 63) { part[wave] = incl; tpart[wave] = tincl; rpart[wave] = rincl; }
+        __syncthreads();
+        int before = carry, tbefore = tcarry, rbefore = rcarry;
+        for (int w = 0; w < wave; ++w) { before += part[w]; tbefore += tpart[w]; rbefore += rpart[w]; }
+        if (l < nlist) {
+            start[l] = before + incl - v;
+            cnt[l] = before + incl - v;
+            a.tasks[l] = tbefore + tincl - t;
+            a.row_tasks[l] = rbefore + rincl - rt;
+        }
+        __syncthreads();
+        if (tid == 1023) { carry = before + incl; tcarry = tbefore + tincl; rcarry = rbefore + rincl; }
+        __syncthreads();
+    }
+    if (tid == 0) {
+        start[nlist] = carry;
+        a.tasks[nlist] = tcarry;
+        a.row_tasks[nlist] = rcarry;
+    }
+}
+// One wave per query.
+__global__ __launch_bounds__(256) void invert_place_kernel(const InvertArgs a) {
+    const int lane = threadIdx.x & 63;
+    const int64_t slot = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (slot >= a.nslots) return;
+    const int64_t q = a.query(slot);
+    if (q < 0) return;
+    const int nseg = a.nseg;
+    int64_t carry = 0;
+    for (int p0 = 0; p0 < nseg; p0 += kWave) {
+        const int p = p0 + lane;
+        int32_t l = p < nseg ? a.probes[(size_t)q * nseg + p] : -1;
+        int64_t len = 0;
+        if (l >= 0 && l < a.nlist) {
+            int64_t s = a.list_offsets[l], e = a.list_offsets[l + 1];
+            s = s < 0 ? 0 : (s > a.n ? a.n : s);
+            e = e < s ? s : (e > a.n ? a.n : e);
+            len = e - s;
+        } else {
+            l = -1;
+        }
+        int64_t incl = len;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int64_t v = __shfl_up((long long)incl, off);
+            if (lane >= off) incl += v;
+        }
+        const int64_t c0 = carry + incl - len;
+        // (beyond 2^31 candidates nothing is scanned: such a list is placed out of reach)
+        if (l >= 0) a.inv[atomicAdd(&a.cnt[l], 1)] = make_int2((int)(a.by_query ? q : slot), c0 < 0x7fffffff ? (int)c0 : 0x7fffffff);
+        carry += __shfl((long long)incl, kWave - 1);
+    }
+}
+
+// ---- replay (kNN) ----
+// The batch rule over entries in scan order (replay_batches; the state of a batch that the next
+// call goes on with is kept in frozen_b and tau_f).  cl: candidate number; the first k candidates
+// are the seed: a batch of their own (-1) with no threshold.
+template <int E>
+__device__ __forceinline__ int replay_entries(ResultRegs<E> &R, int &frozen_b, float &tau_f, const int32_t *s_cl, const float *s_g,
+                                              const float *s_d2, const int32_t *s_id, int np, int batch, uint32_t *mask_row,
+                                              int64_t mask_words) {
+    int total = 0;
+    for (int i0 = 0; i0 < np; i0 += kWave) {
+        // Four chunks at once where nothing in them beats the k-th distance (most of a long scan): they only
+        // count, each entry against the threshold of its batch.
+        if (i0 + 4 * kWave <= np) {
+            float g4[4], d4[4];
+            int c4[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { g4[u] = s_g[i0 + u * kWave + R.lane]; d4[u] = s_d2[i0 + u * kWave + R.lane]; c4[u] = s_cl[i0 + u * kWave + R.lane]; }
+            bool better = false, on[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int b4 = c4[u] < R.k ? -1 : (c4[u] - R.k) / batch;
+                on[u] = b4 < 0 || g4[u] <= (b4 == frozen_b ? tau_f : R.t_d2);
+                better = better || (on[u] && d4[u] <= R.t_d2);
+            }
+            if (!__any(better)) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    total += __popcll(__ballot(on[u]));
+                    if (on[u] && mask_row) {
+                        const int64_t wi = c4[u] >> 5;
+                        if (wi < mask_words) atomicOr(&mask_row[wi], 1u << (c4[u] & 31));
+                    }
+                }
+                i0 += 3 * kWave;
+                continue;
+            }
+        }
+        const int i = i0 + R.lane;
+        bool pending = i < np;
+        int cl = 0, b = 0x7fffffff;
+        int32_t id = 0;
+        float g = __builtin_inff(), d2 = 0.0f;
+        if (pending) {
+            cl = s_cl[i]; g = s_g[i]; d2 = s_d2[i]; id = s_id[i];
+            b = cl < R.k ? -1 : (cl - R.k) / batch;
+            if (b < 0) g = -__builtin_inff();
+        }
+        auto mark = [&](bool on) {
+            total += __popcll(__ballot(on));
+            if (on && mask_row) {
+                const int64_t wi = cl >> 5;
+                if (wi < mask_words) atomicOr(&mask_row[wi], 1u << (cl & 31));
+            }
+        };
+        for (;;) {
+            // (see replay_batches: survivors that do not beat the k-th distance are taken all at once)
+            pending = pending && g <= (b == frozen_b ? tau_f : R.t_d2);
+            const unsigned long long mi = __ballot(pending && hit_less(d2, id, R.t_d2, R.t_id));
+            int fb = 0x7fffffff;
+            if (mi != 0) fb = __builtin_amdgcn_readlane(b, __ffsll((long long)mi) - 1);
+            const bool plain = pending && b < fb;
+            mark(plain);
+            pending = pending && !plain;
+            if (mi == 0) break;
+            if (fb != frozen_b) { frozen_b = fb; tau_f = R.t_d2; }
+            const bool sel = pending && b == fb;
+            mark(sel);
+            R.insert_pending(sel, d2, id);
+            pending = pending && !sel;
+        }
+    }
+    return total;
+}
+
+// Ascending bitonic sort of n keys in LDS (n a power of two) by all threads.  Ends with a barrier.
+__device__ __forceinline__ void sort_keys(unsigned long long *key, int n) {
+    for (int size = 2; size <= n; size <<= 1)
+        for (int j = size >> 1; j > 0; j >>= 1) {
+            for (int i = threadIdx.x; i < n / 2; i += blockDim.x) {
+                const int x = ((i & ~(j - 1)) << 1) | (i & (j - 1)), y = x | j;
+                const unsigned long long p = key[x], q = key[y];
+                if ((p > q) == ((x & size) == 0)) { key[x] = q; key[y] = p; }
+            }
+            __syncthreads();
+        }
+}
+
+// One workgroup per query.  The entries of a stretch are listed in scan order; the exact distance is taken
+// here of those whose lower bound (a.d2) does not exceed the threshold at the start, and the first wave
+// goes through the batch rule.
+// The first pass (seed and first batch, lo == 0) is done by all threads: the seed's distances give the
+// batch its threshold; of its survivors the k with the least lower bounds are measured, the largest of those
+// distances bounds the k-th, so that only bounds up to it need measuring; a sort gives R.
+template <int E>
+__global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    int *segp = reinterpret_cast<int *>(smem + a.off_segp), *segd = reinterpret_cast<int *>(smem + a.off_segd);
+    int32_t *s_cl = reinterpret_cast<int32_t *>(smem + a.off_cl), *s_id = reinterpret_cast<int32_t *>(smem + a.off_id);
+    float *s_g = reinterpret_cast<float *>(smem + a.off_g), *s_d2 = reinterpret_cast<float *>(smem + a.off_d2);
+    float *rd2 = reinterpret_cast<float *>(smem + a.off_rd2);
+    int32_t *rid = reinterpret_cast<int32_t *>(smem + a.off_rid);
+    float *q_lds = reinterpret_cast<float *>(smem + a.off_q);
+    unsigned long long *s_key = reinterpret_cast<unsigned long long *>(smem + a.off_key);   // [kReplayCap]
+    uint16_t *s_todo = reinterpret_cast<uint16_t *>(smem + a.off_todo);                     // [kReplayCap]
+    __shared__ int part[kReplayThreads / kWave];
+    __shared__ int s_ntodo, s_count;
+    __shared__ uint32_t s_most;
+    __shared__ float s_tau;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t row = blockIdx.x;       // one workgroup per place in the order
+    const int64_t q = a.order ? a.order[a.slot0 + row] : a.slot0 + row;
+    if (q < 0 || q >= a.nq) return;
+    const int total = a.totals[row];
+    const int lo = a.lo < total ? a.lo : total, hi = a.hi < total ? a.hi : total;
+    if (a.lo > 0 && lo >= hi) return;        // nothing of this query in this pass: R stays as it is
+    for (int t = tid; t < a.d; t += kReplayThreads) q_lds[t] = a.queries[(size_t)q * a.d + t];
+    segment_table(a.list_offsets, a.probes, a.nlist, a.nseg, a.n, a.max_cand, q, segp, segd);
+    for (int i = tid; i < kWave * E; i += kReplayThreads) {
+        const bool have = a.lo > 0 && i < a.k;
+        const int32_t id = have ? a.out_ids[(size_t)q * a.k + i] : -1;
+        rd2[i] = have ? a.out_d2[(size_t)q * a.k + i] : __builtin_inff();
+        rid[i] = id < 0 ? kEmptyId : id;
+    }
+    __syncthreads();
+    ResultRegs<E> R;
+    int frozen_b = -2, survivors = 0;
+    float tau_f = 0.0f;
+    if (wave == 0) {
+        R.load(rd2, rid, a.k, lane);
+        if (lane == 0) s_tau = R.t_d2;
+    }
+    const uint32_t *bits = a.possible + (size_t)row * a.words;
+    const float *row_g = a.g + (size_t)row * a.words * 32, *row_d2 = a.d2 + (size_t)row * a.words * 32;
+    uint32_t *mask_row = a.mask ? a.mask + (size_t)q * a.mask_words : nullptr;
+    // the exact distances of the entries s_todo[0 .. n), by half waves, two rows each; s_id: positions before, ids after
+    auto measure = [&](int n) {
+        const int half = tid >> 5, lane32 = tid & 31;
+        constexpr int kHalves = kReplayThreads / 32;
+        for (int i = half; i < n; i += 2 * kHalves) {
+            const int e0 = s_todo[i], e1 = s_todo[i + kHalves < n ? i + kHalves : i];
+            const int p0 = segment_position(s_cl[e0], segp, segd, a.nseg), p1 = segment_position(s_cl[e1], segp, segd, a.nseg);
+            const int32_t id0 = a.ids ? a.ids[p0] : p0, id1 = a.ids ? a.ids[p1] : p1;
+            float d2[2];
+            exact_d2_half_x2_deep<4>(a.base + (size_t)p0 * a.d, a.base + (size_t)p1 * a.d, q_lds, a.d, lane32, d2);
+            if (lane32 == 0) {
+                s_d2[e0] = d2[0]; s_id[e0] = id0;
+                s_d2[e1] = d2[1]; s_id[e1] = id1;
+            }
+        }
+        __syncthreads();
+    };
+    const int w_end = (hi + 31) >> 5;
+    for (int w0 = lo >> 5; w0 < w_end; w0 += kReplayThreads) {
+        const int w = w0 + tid;
+        uint32_t b = w < w_end ? bits[w] : 0u;
+        if (w == lo >> 5) b &= ~0u << (lo & 31);
+        if (w == hi >> 5) b &= (1u << (hi & 31)) - 1u;
+        const int cnt = __popc(b);
+        int incl = cnt;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int v = __shfl_up(incl, off);
+            if (lane >= off) incl += v;
+        }
+        if (lane == 63) part[wave] = incl;
+        __syncthreads();
+        int before = incl - cnt, all = 0;
+        for (int v = 0; v < kReplayThreads / kWave; ++v) {
+            const int p = part[v];
+            if (v < wave) before += p;
+            all += p;
+        }
+        for (int e0 = 0; e0 < all; e0 += kReplayCap) {
+            const int np = all - e0 < kReplayCap ? all - e0 : kReplayCap;
+            uint32_t rem = b;
+            int at = before - e0;
+            while (rem) {
+                const int c = w * 32 + (__ffs((int)rem) - 1);
+                rem &= rem - 1;
+                if (at >= 0 && at < np) s_cl[at] = c;
+                ++at;
+            }
+            if (tid == 0) s_ntodo = 0;
+            __syncthreads();
+            const float tau = s_tau;
+            // the seed and the first batch, whole (the candidates of this pass are all marked)
+            if (a.lo == 0 && hi <= (int64_t)a.k + a.batch && all == np && np == hi) {
+                const int ns = np < a.k ? np : a.k;
+                for (int i = tid; i < np; i += kReplayThreads) {
+                    const int c = s_cl[i];
+                    s_g[i] = row_g[c];
+                    s_d2[i] = row_d2[c];
+                    if (i < ns) s_todo[i] = (uint16_t)i;
+                }
+                if (tid == 0) { s_most = 0; s_count = 0; }
+                __syncthreads();
+                measure(ns);
+                uint32_t most = 0;
+                for (int i = tid; i < ns; i += kReplayThreads) most = max(most, __float_as_uint(s_d2[i]));
+                if (most) atomicMax(&s_most, most);
+                __syncthreads();
+                const float tau1 = ns == a.k ? __uint_as_float(s_most) : __builtin_inff();
+                int mine = 0;
+                for (int i = tid; i < np; i += kReplayThreads) {
+                    const bool on = i < ns || s_g[i] <= tau1;
+                    if (on) {
+                        ++mine;
+                        if (mask_row && (i >> 5) < a.mask_words) atomicOr(&mask_row[i >> 5], 1u << (i & 31));
+                        // who could enter R at all, by lower bound (seeds: measured already)
+                        if (i >= ns && s_d2[i] <= tau1)
+                            s_key[atomicAdd(&s_ntodo, 1)] = ((unsigned long long)__float_as_uint(s_d2[i]) << 32) | (uint32_t)i;
+                    }
+                }
+                if (mine) atomicAdd(&s_count, mine);
+                __syncthreads();
+                int nc = s_ntodo;
+                if (wave == 0) survivors += s_count;
+                int size = 1;
+                while (size < nc) size <<= 1;
+                for (int i = nc + tid; i < size; i += kReplayThreads) s_key[i] = ~0ull;
+                __syncthreads();
+                sort_keys(s_key, size);
+                const int first = nc < a.k ? nc : a.k;
+                for (int i = tid; i < first; i += kReplayThreads) s_todo[i] = (uint16_t)s_key[i];
+                if (tid == 0) s_most = 0;
+                __syncthreads();
+                measure(first);
+                most = 0;
+                for (int i = tid; i < first; i += kReplayThreads) most = max(most, __float_as_uint(s_d2[s_todo[i]]));
+                if (most) atomicMax(&s_most, most);
+                if (tid == 0) s_ntodo = 0;
+                __syncthreads();
+                const float cut = first == a.k ? __uint_as_float(s_most) : __builtin_inff();
+                int more = 0;                         // bounds are ascending: a prefix
+                for (int i = first + tid; i < nc; i += kReplayThreads) {
+                    const bool need = __uint_as_float((uint32_t)(s_key[i] >> 32)) <= cut;
+                    if (need) { s_todo[i - first] = (uint16_t)s_key[i]; ++more; }
+                }
+                if (more) atomicAdd(&s_ntodo, more);
+                __syncthreads();
+                const int n2 = s_ntodo;
+                measure(n2);
+                nc = first + n2;
+                // R: the k least of the seed and the measured ones, by (distance, id)
+                for (int i = tid; i < nc; i += kReplayThreads) {
+                    const int e = (int)(uint32_t)s_key[i];
+                    s_key[i] = ((unsigned long long)__float_as_uint(s_d2[e]) << 32) | ((uint32_t)s_id[e] ^ 0x80000000u);   // (ids order as signed)
+                }
+                size = 1;
+                while (size < nc + ns) size <<= 1;
+                for (int i = tid; i < ns; i += kReplayThreads)
+                    s_key[nc + i] = ((unsigned long long)__float_as_uint(s_d2[i]) << 32) | ((uint32_t)s_id[i] ^ 0x80000000u);
+                for (int i = nc + ns + tid; i < size; i += kReplayThreads) s_key[i] = ~0ull;
+                __syncthreads();
+                sort_keys(s_key, size);
+                const int have = nc + ns < a.k ? nc + ns : a.k;
+                for (int i = tid; i < kWave * E; i += kReplayThreads) {
+                    rd2[i] = i < have ? __uint_as_float((uint32_t)(s_key[i] >> 32)) : __builtin_inff();
+                    rid[i] = i < have ? (int32_t)((uint32_t)s_key[i] ^ 0x80000000u) : kEmptyId;
+                }
+                __syncthreads();
+                if (wave == 0) R.load(rd2, rid, a.k, lane);
+                continue;
+            }
+            for (int i = tid; i < np; i += kReplayThreads) {
+                const int c = s_cl[i];
+                const float d2 = row_d2[c], g = row_g[c];
+                s_g[i] = g;
+                // (its bound is held against the threshold of its own batch, later)
+                if (d2 <= tau) s_todo[atomicAdd(&s_ntodo, 1)] = (uint16_t)i;
+                s_d2[i] = __builtin_inff();    // what does not beat the k-th distance needs neither distance nor id
+                s_id[i] = kEmptyId;
+            }
+            __syncthreads();
+            measure(s_ntodo);
+            if (wave == 0) {
+                survivors += replay_entries<E>(R, frozen_b, tau_f, s_cl, s_g, s_d2, s_id, np, a.batch, mask_row, a.mask_words);
+                if (lane == 0) s_tau = R.t_d2;
+            }
+            __syncthreads();
+        }
+        __syncthreads();
+    }
+    if (wave == 0) {
+        R.store(rd2, rid);
+        if (lane == 0 && a.n_exact) a.n_exact[q] = survivors + (a.lo > 0 ? a.n_exact[q] : 0);
+    }
+    __syncthreads();
+    for (int i = tid; i < a.k; i += kReplayThreads) {
+        const int32_t id = rid[i];
+        a.out_ids[(size_t)q * a.k + i] = id == kEmptyId ? -1 : id;
+        a.out_d2[(size_t)q * a.k + i] = rd2[i];
+    }
+}
+
+// ---- exact distances of a range search's marked candidates (a.d2: their lower bounds) ----
+// One workgroup per (query, chunk): those whose bound does not exceed the radius are listed and measured by half waves;
+// results keep their mark and leave their distance, the others are unmarked.
+__global__ __launch_bounds__(kReplayThreads) void range_exact_kernel(const ReplayArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    int *segp = reinterpret_cast<int *>(smem + a.off_segp), *segd = reinterpret_cast<int *>(smem + a.off_segd);
+    int32_t *s_cl = reinterpret_cast<int32_t *>(smem + a.off_cl);     // [kReplayCap]
+    float *q_lds = reinterpret_cast<float *>(smem + a.off_q);
+    uint32_t *s_word = reinterpret_cast<uint32_t *>(smem + a.off_key);  // [kReplayThreads] words in work
+    __shared__ int part[kReplayThreads / kWave];
+    __shared__ int s_n;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t q = a.order ? a.order[blockIdx.x] : (int64_t)blockIdx.x;
+    if (q < 0 || q >= a.nq) return;
+    const int total = a.totals[q];
+    const int lo = (int)blockIdx.y * a.chunk, hi = lo + a.chunk < total ? lo + a.chunk : total;
+    if (lo >= hi) return;
+    for (int t = tid; t < a.d; t += kReplayThreads) q_lds[t] = a.queries[(size_t)q * a.d + t];
+    segment_table(a.list_offsets, a.probes, a.nlist, a.nseg, a.n, a.max_cand, q, segp, segd);
+    uint32_t *bits = a.bits + (size_t)q * a.words;
+    float *row_d2 = a.d2_out + (size_t)q * a.words * 32;
+    const int half = tid >> 5, lane32 = tid & 31;
+    int results = 0;
+    const int w_end = (hi + 31) >> 5;
+    for (int w0 = lo >> 5; w0 < w_end; w0 += kReplayThreads) {
+        const int w = w0 + tid;
+        uint32_t b = w < w_end ? bits[w] : 0u, out = b;
+        const int cnt = __popc(b);
+        int incl = cnt;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int v = __shfl_up(incl, off);
+            if (lane >= off) incl += v;
+        }
+        if (lane == 63) part[wave] = incl;
+        s_word[tid] = b;
+        __syncthreads();
+        int before = incl - cnt, all = 0;
+        for (int v = 0; v < kReplayThreads / kWave; ++v) {
+            const int p = part[v];
+            if (v < wave) before += p;
+            all += p;
+        }
+        for (int e0 = 0; e0 < all; e0 += kReplayCap) {
+            const int np = all - e0 < kReplayCap ? all - e0 : kReplayCap;
+            uint32_t rem = b;
+            int at = before - e0;
+            while (rem) {
+                if (at >= 0 && at < np) s_cl[at] = w * 32 + (__ffs((int)rem) - 1);
+                rem &= rem - 1;
+                ++at;
+            }
+            if (tid == 0) s_n = 0;
+            __syncthreads();
+            // bounds beyond the radius leave at once; the others are listed in place of the candidates
+            int keep[kReplayCap / kReplayThreads];
+#pragma unroll
+            for (int v = 0; v < kReplayCap / kReplayThreads; ++v) {
+                const int i = tid + v * kReplayThreads;
+                keep[v] = -1;
+                if (i < np) {
+                    const int c = s_cl[i];
+                    if (row_d2[c] <= a.radius2) keep[v] = c;
+                    else atomicAnd(&s_word[(c >> 5) - w0], ~(1u << (c & 31)));
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int v = 0; v < kReplayCap / kReplayThreads; ++v)
+                if (keep[v] >= 0) s_cl[atomicAdd(&s_n, 1)] = keep[v];
+            __syncthreads();
+            const int n = s_n;
+            constexpr int kHalves = kReplayThreads / 32;
+            for (int i = half; i < n; i += 2 * kHalves) {
+                const int c0 = s_cl[i], c1 = s_cl[i + kHalves < n ? i + kHalves : i];
+                const int p0 = segment_position(c0, segp, segd, a.nseg), p1 = segment_position(c1, segp, segd, a.nseg);
+                float d2[2];
+                exact_d2_half_x2_deep<4>(a.base + (size_t)p0 * a.d, a.base + (size_t)p1 * a.d, q_lds, a.d, lane32, d2);
+                if (lane32 == 0) {
+#pragma unroll
+                    for (int v = 0; v < 2; ++v) {           // (the last one twice where their number is odd)
+                        const int c = v == 0 ? c0 : c1;
+                        if (d2[v] <= a.radius2) row_d2[c] = d2[v];
+                        else atomicAnd(&s_word[(c >> 5) - w0], ~(1u << (c & 31)));
+                    }
+                }
+            }
+            __syncthreads();
+        }
+        out = s_word[tid];
+        if (w < w_end) {
+            if (out != b) bits[w] = out;
+            results += __popc(out);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) results += __shfl_xor(results, off);
+    if (lane == 0 && results) atomicAdd(&a.counts[(size_t)q * a.nchunk + blockIdx.y], results);
+}
+
+}  // namespace trim

@@ -1,0 +1,124 @@
+// The instances of the passes and their launchers (see trim_mark.h).
+#include <atomic>
+
+#include "trim_launch.h"
+#include "trim_mark.h"
+
+namespace trim {
+
+int launch_invert(const InvertArgs &a, hipStream_t st) {
+    const int64_t total = a.nslots * a.nseg;
+    hipLaunchKernelGGL(invert_count_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(invert_scan_kernel, dim3(1), dim3(1024), 0, st, a);
+    hipLaunchKernelGGL(invert_place_kernel, dim3((unsigned)((a.nslots + 3) / 4)), dim3(256), 0, st, a);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+
+int launch_finish(const FinishArgs &a, int vec, bool fs, int threads, size_t lds, int64_t slots, hipStream_t st) {
+    void (*fn)(const FinishArgs) = nullptr;
+    if (fs) {
+        if (vec == 1) return TRIM_UNSUPPORTED_SHAPE;
+        fn = vec == 4 ? finish_kernel<4, true> : finish_kernel<2, true>;
+    } else {
+        fn = vec == 4 ? finish_kernel<4, false> : vec == 2 ? finish_kernel<2, false> : finish_kernel<1, false>;
+    }
+    // (the table must start at LDS address 0: see launch_instance)
+    static std::atomic<int> lds_checked[6];
+    std::atomic<int> &seen = lds_checked[(fs ? 3 : 0) + (vec == 4 ? 2 : vec == 2 ? 1 : 0)];
+    if (seen.load(std::memory_order_acquire) == 0) {
+        hipFuncAttributes fa;
+        HIP_TRY(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(fn)));
+        seen.store(fa.sharedSizeBytes == 0 ? 1 : -1, std::memory_order_release);
+    }
+    if (seen.load(std::memory_order_acquire) < 0) return TRIM_INTERNAL;
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(fn, dim3((unsigned)slots), dim3(threads), lds, st, a);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+
+int launch_totals(const FinishArgs &a, hipStream_t st) {
+    hipLaunchKernelGGL(totals_kernel, dim3((unsigned)((a.nslots + 3) / 4)), dim3(256), 0, st, a);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+
+// The operands of the filter (once per slab of queries).
+int launch_filter_operands(const FilterArgs &a, hipStream_t st) {
+    hipLaunchKernelGGL(filter_means_kernel, dim3((unsigned)a.nsub), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(filter_operands_kernel, dim3((unsigned)(a.kpad / a.padded + a.nslots)), dim3(256), 0, st, a);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+
+int launch_filter(const FilterArgs &a, hipStream_t st) {
+    const int64_t blocks = 256 * 2 * 4;      // (two per CU at a time)
+    void (*fn)(const FilterArgs) = nullptr;
+    if (a.ncent == kC4) fn = filter_kernel<2, true>;
+    else switch (a.padded) {
+        case 4: fn = filter_kernel<4, false>; break;
+        case 8: fn = filter_kernel<8, false>; break;
+        case 16: fn = filter_kernel<16, false>; break;
+        case 32: fn = filter_kernel<32, false>; break;
+        default: return TRIM_UNSUPPORTED_SHAPE;
+    }
+    hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(kFltThreads), 0, st, a);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+
+int launch_measure(const FilterArgs &a, hipStream_t st) {
+    hipLaunchKernelGGL(measure_kernel, dim3(256 * 2 * 4), dim3(kFltThreads), 0, st, a);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+
+namespace {
+// LDS of the replay and range_exact passes.
+size_t replay_carve(ReplayArgs &a) {
+    const int ns = a.nseg > 0 ? a.nseg : 1, E = result_slots(a.k);
+    auto up = [](size_t x) { return (x + 15) & ~size_t(15); };
+    size_t off = 0;
+    a.off_segp = (uint32_t)off; off += up((size_t)(ns + 1) * 4);
+    a.off_segd = (uint32_t)off; off += up((size_t)ns * 4);
+    a.off_q = (uint32_t)off;    off += up((size_t)a.d * 4);
+    a.off_cl = (uint32_t)off;   off += kReplayCap * 4;
+    a.off_key = (uint32_t)off;  off += (size_t)kReplayCap * 8;
+    a.off_g = (uint32_t)off;    off += kReplayCap * 4;
+    a.off_d2 = (uint32_t)off;   off += kReplayCap * 4;
+    a.off_id = (uint32_t)off;   off += kReplayCap * 4;
+    a.off_rd2 = (uint32_t)off;  off += (size_t)kWave * E * 4;
+    a.off_rid = (uint32_t)off;  off += (size_t)kWave * E * 4;
+    a.off_todo = (uint32_t)off; off += (size_t)kReplayCap * 2;
+    return off;
+}
+}  // namespace
+
+size_t replay_lds(int d, int k, int nseg) {
+    ReplayArgs a{};
+    a.d = d; a.k = k; a.nseg = nseg;
+    return replay_carve(a) + 256;        // (and the kernels' static part)
+}
+
+int launch_range_exact(ReplayArgs a, int64_t nslots, int nchunk, hipStream_t st) {
+    a.k = 1;
+    replay_carve(a);
+    const size_t off = a.off_g;          // (what follows is the replay's)
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(range_exact_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)off));
+    hipLaunchKernelGGL(range_exact_kernel, dim3((unsigned)nslots, (unsigned)nchunk), dim3(kReplayThreads), off, st, a);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+
+int launch_replay(ReplayArgs a, int64_t nslots, hipStream_t st) {
+    const int E = result_slots(a.k);
+    const size_t off = replay_carve(a);
+    void (*fn)(const ReplayArgs) = E == 1 ? replay_kernel<1> : E == 2 ? replay_kernel<2> : E == 4 ? replay_kernel<4> : replay_kernel<16>;
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)off));
+    hipLaunchKernelGGL(fn, dim3((unsigned)nslots), dim3(kReplayThreads), off, st, a);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+
+}  // namespace trim

@@ -22,8 +22,8 @@ TRIM_MAX_NPROBE = 4096
 
 EXPORTS = ("trim_shape_supported", "trim_fs_shape_supported", "trim_fs_encode", "trim_fs_build_lut",
            "trim_fs_train_pq", "trim_train_pq", "trim_train_ivf", "trim_estimate_gamma", "trim_estimate_gamma_normal", "trim_encode", "trim_pack_scan_head", "trim_codes_tiled_bytes", "trim_pack_codes_tiled",
-           "trim_build_lut", "trim_search_knn",
-           "trim_search_range", "trim_search_range_static", "trim_static_scratch_bytes", "trim_range_workspace_bytes", "trim_ivf_probe", "trim_query_order",
+           "trim_build_lut", "trim_search_knn", "trim_search_knn_ws", "trim_knn_workspace_bytes",
+           "trim_search_range", "trim_search_range_static", "trim_search_range_ws", "trim_range_scratch_bytes", "trim_range_collect", "trim_static_scratch_bytes", "trim_range_workspace_bytes", "trim_ivf_probe", "trim_query_order",
            "trim_list_bounds_bytes", "trim_pack_list_bounds",
            "trim_ceiling_stream_read", "trim_ceiling_lds_gather",
            "trim_strerror", "trim_last_hip_error", "trim_version")
@@ -109,6 +109,9 @@ def lib() -> C.CDLL:
         L.trim_search_knn.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p,
                                       C.c_int32, C.c_float, C.c_int32, C.c_void_p, C.c_void_p,
                                       C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p]
+        L.trim_search_knn_ws.argtypes = L.trim_search_knn.argtypes[:-1] + [C.c_void_p, C.c_size_t, C.c_void_p]
+        L.trim_knn_workspace_bytes.restype = C.c_size_t
+        L.trim_knn_workspace_bytes.argtypes = [C.c_void_p, C.c_int64, C.c_void_p, C.c_int32, C.c_int32]
         L.trim_list_bounds_bytes.restype = C.c_size_t
         L.trim_list_bounds_bytes.argtypes = [C.c_int32, C.c_int32]
         L.trim_pack_list_bounds.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p]
@@ -120,6 +123,11 @@ def lib() -> C.CDLL:
                                         C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64,
                                         C.c_void_p, C.c_size_t, C.c_void_p]
         L.trim_search_range_static.argtypes = L.trim_search_range.argtypes[:16] + [C.c_void_p]
+        L.trim_search_range_ws.argtypes = L.trim_search_range.argtypes[:-1] + [C.c_void_p, C.c_size_t, C.c_void_p]
+        L.trim_range_scratch_bytes.restype = C.c_size_t
+        L.trim_range_scratch_bytes.argtypes = [C.c_void_p, C.c_int64, C.c_void_p]
+        L.trim_range_collect.argtypes = [C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64,
+                                         C.c_void_p, C.c_size_t, C.c_void_p]
         L.trim_static_scratch_bytes.restype = C.c_size_t
         L.trim_ivf_probe.argtypes = [C.c_void_p, C.c_int64, C.c_int32, C.c_void_p, C.c_int32,
                                      C.c_int32, C.c_void_p, C.c_void_p]
@@ -377,15 +385,23 @@ def trim_search_knn(index: Index, queries: torch.Tensor, k: int, gamma: float, b
         mw = (mc + 31) // 32
         mask = torch.empty((nq, mw), dtype=torch.int32, device=dev)
     view = index._view()
-    _check(lib().trim_search_knn(C.byref(view), _ptr(queries, torch.float32, "queries"), nq,
-                                 _ptr(lut, torch.float32, "lut"),
-                                 C.byref(cand) if cand is not None else None, k, gamma, batch,
-                                 _ptr(query_order, torch.int32, "query_order"),
-                                 _ptr(out_ids, torch.int32, "out_ids"),
-                                 _ptr(out_d2, torch.float32, "out_d2"),
-                                 C.byref(stats) if stats is not None else None,
-                                 _ptr(mask, torch.int32, "mask"), mw, _stream()),
-           "trim_search_knn")
+    pcand = C.byref(cand) if cand is not None else None
+    # work space for the search in passes, where the library wants it (see trim_search_knn_ws)
+    need = 0 if want_work else lib().trim_knn_workspace_bytes(C.byref(view), nq, pcand, k, batch)
+    ws = None
+    if need:
+        try:
+            ws = torch.empty((need,), dtype=torch.uint8, device=dev)
+        except torch.cuda.OutOfMemoryError:      # the single kernel does without
+            need = 0
+    _check(lib().trim_search_knn_ws(C.byref(view), _ptr(queries, torch.float32, "queries"), nq,
+                                    _ptr(lut, torch.float32, "lut"), pcand, k, gamma, batch,
+                                    _ptr(query_order, torch.int32, "query_order"),
+                                    _ptr(out_ids, torch.int32, "out_ids"),
+                                    _ptr(out_d2, torch.float32, "out_d2"),
+                                    C.byref(stats) if stats is not None else None,
+                                    _ptr(mask, torch.int32, "mask"), mw, _ptr(ws, torch.uint8, "workspace"), need,
+                                    _stream()), "trim_search_knn")
     return dict(ids=out_ids, d2=out_d2, n_scanned=ns, n_exact=ne, mask=mask, work=work)
 
 
@@ -428,36 +444,50 @@ def trim_search_range(index: Index, queries: torch.Tensor, radius: float, gamma:
         mw = (mc + 31) // 32
         mask = torch.empty((nq, mw), dtype=torch.int32, device=dev)
     view = index._view()
+    pcand = C.byref(cand) if cand is not None else None
 
     def call(cap, oi, od):
-        if static_scratch:
-            _check(lib().trim_search_range_static(
-                C.byref(view), _ptr(queries, torch.float32, "queries"), nq,
-                _ptr(lut, torch.float32, "lut"), C.byref(cand) if cand is not None else None,
+        args = [C.byref(view), _ptr(queries, torch.float32, "queries"), nq,
+                _ptr(lut, torch.float32, "lut"), pcand,
                 radius, gamma, _ptr(query_order, torch.int32, "query_order"),
                 _ptr(offsets, torch.int64, "offsets"), _ptr(oi, torch.int32, "out_ids"),
                 _ptr(od, torch.float32, "out_d2"), cap, _ptr(required, torch.int64, "required"),
-                C.byref(stats) if stats is not None else None, _ptr(mask, torch.int32, "mask"), mw,
-                _stream()), "trim_search_range_static")
+                C.byref(stats) if stats is not None else None, _ptr(mask, torch.int32, "mask"), mw]
+        if static_scratch:
+            _check(lib().trim_search_range_static(*args, _stream()), "trim_search_range_static")
             return
-        _check(lib().trim_search_range(
-            C.byref(view), _ptr(queries, torch.float32, "queries"), nq,
-            _ptr(lut, torch.float32, "lut"), C.byref(cand) if cand is not None else None,
-            radius, gamma, _ptr(query_order, torch.int32, "query_order"),
-            _ptr(offsets, torch.int64, "offsets"), _ptr(oi, torch.int32, "out_ids"),
-            _ptr(od, torch.float32, "out_d2"), cap, _ptr(required, torch.int64, "required"),
-            C.byref(stats) if stats is not None else None, _ptr(mask, torch.int32, "mask"), mw,
-            C.c_void_p(workspace.data_ptr()), workspace.numel(), _stream()), "trim_search_range")
+        # scratch for the search in passes, where the library wants it (see trim_search_range_ws)
+        more = 0 if want_work else lib().trim_range_scratch_bytes(C.byref(view), nq, pcand)
+        scratch = None
+        if more:
+            try:
+                scratch = torch.empty((more,), dtype=torch.uint8, device=dev)
+            except torch.cuda.OutOfMemoryError:      # the single kernel does without
+                more = 0
+        _check(lib().trim_search_range_ws(*args, C.c_void_p(workspace.data_ptr()), workspace.numel(),
+                                          _ptr(scratch, torch.uint8, "scratch"), more, _stream()), "trim_search_range")
 
     if capacity <= 0:
+        # count, size the buffers, collect: the workspace keeps the results, nothing is searched twice
+        # (the static area is not the caller's alone: there the second step is a search as well)
         call(0, None, None)
-        capacity = max(1, int(required.item()))
-    out_ids = torch.empty((capacity,), dtype=torch.int32, device=dev)
-    out_d2 = torch.empty((capacity,), dtype=torch.float32, device=dev)
-    call(capacity, out_ids, out_d2)
-    req = int(required.item())
-    if req > capacity:
-        raise TrimCapacityError(req, capacity)
+        req = int(required.item())
+        out_ids = torch.empty((max(1, req),), dtype=torch.int32, device=dev)
+        out_d2 = torch.empty((max(1, req),), dtype=torch.float32, device=dev)
+        if static_scratch:
+            call(max(1, req), out_ids, out_d2)
+        elif req:
+            _check(lib().trim_range_collect(C.byref(view), nq, pcand, _ptr(out_ids, torch.int32, "out_ids"),
+                                            _ptr(out_d2, torch.float32, "out_d2"), req,
+                                            C.c_void_p(workspace.data_ptr()), workspace.numel(), _stream()),
+                   "trim_range_collect")
+    else:
+        out_ids = torch.empty((capacity,), dtype=torch.int32, device=dev)
+        out_d2 = torch.empty((capacity,), dtype=torch.float32, device=dev)
+        call(capacity, out_ids, out_d2)
+        req = int(required.item())
+        if req > capacity:
+            raise TrimCapacityError(req, capacity)
     return dict(offsets=offsets, ids=out_ids[:req], d2=out_d2[:req], n_scanned=ns, n_exact=ne,
                 mask=mask, required=req, work=work)
 

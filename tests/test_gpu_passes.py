@@ -1,0 +1,163 @@
+"""The searches in passes (trim_search_knn_ws, trim_search_range_ws with their work space) against the
+single kernel (trim_search_knn, trim_search_range), which the other GPU tests hold against the oracle: ids,
+distances, counters, offsets and survivor masks are the same bit for bit."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def T():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2508_17828_amd import trim
+    trim.lib()
+    return trim
+
+
+def built(T, n, d, M, bits, nlist, nq, nprobe, spread, offset, seed):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    means = torch.randn((max(2, n // 300), d), device="cuda", generator=g) * spread
+
+    def draw(count):
+        at = torch.randint(0, means.shape[0], (count,), device="cuda", generator=g)
+        return (torch.randn((count, d), device="cuda", generator=g) * 0.5 + means[at] + offset).contiguous()
+
+    base, queries = draw(n), draw(nq)
+    init = torch.randperm(n, device="cuda", generator=g)[: 256 if bits == 8 else 16].to(torch.int32)
+    cb = (T.trim_train_pq if bits == 8 else T.trim_fs_train_pq)(base[:4096].contiguous(), M, 2, init % min(n, 4096))
+    ids = offsets = probes = None
+    longest = 0
+    if nlist:
+        cent = base[torch.randperm(n, device="cuda", generator=g)[:nlist]].contiguous()
+        at = T.trim_ivf_probe(base, cent, 1)[:, 0].long()
+        at[at == 1] = 0                                   # an empty list
+        order = torch.argsort(at, stable=True)
+        offsets = torch.zeros((nlist + 1,), dtype=torch.int64, device="cuda")
+        offsets[1:] = torch.cumsum(torch.bincount(at, minlength=nlist), 0)
+        longest = int((offsets[1:] - offsets[:-1]).max())
+        base, ids = base[order].contiguous(), order.to(torch.int32)
+        probes = T.trim_ivf_probe(queries, cent, nprobe)
+        probes[3, 1] = probes[3, 0]                       # a list twice
+        probes[5, 0] = nlist + 7                          # no such list
+        probes[6, :] = 1                                  # nothing to scan
+    codes, dlx = (T.trim_encode if bits == 8 else T.trim_fs_encode)(base, cb)
+    ix = T.Index(base, codes, dlx, cb, ids=ids, list_offsets=offsets, max_list_len=longest, code_bits=bits)
+    if codes.shape[1] % 8 == 0:
+        ix.scan_head = T.trim_pack_scan_head(codes, dlx)
+    if nlist:
+        ix.list_bounds = T.trim_pack_list_bounds(ix)
+    return ix, queries, probes
+
+
+def single_kernel(T, ix, q, k, gamma, batch, probes, order, lut=None):
+    import torch
+    nq = q.shape[0]
+    ids = torch.full((nq, k), -7, dtype=torch.int32, device="cuda")
+    d2 = torch.full((nq, k), -7.0, device="cuda")
+    ns, ne = torch.zeros((2, nq), dtype=torch.int32, device="cuda").unbind(0)
+    cand, mc = ix._cand(probes)
+    mw = (mc + 31) // 32
+    mask = torch.zeros((nq, mw), dtype=torch.int32, device="cuda")
+    view, stats = ix._view(), T._Stats(ns.data_ptr(), ne.data_ptr(), None)
+    p = lambda t: None if t is None else C.c_void_p(t.data_ptr())
+    rc = T.lib().trim_search_knn(C.byref(view), p(q), nq, p(lut), C.byref(cand) if cand is not None else None, k, gamma, batch,
+                                 p(order), p(ids), p(d2), C.byref(stats), p(mask), mw,
+                                 C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    return dict(ids=ids, d2=d2, n_scanned=ns, n_exact=ne, mask=mask)
+
+
+# every padded sub-vector length; 4-bit codes; with and without lists; result sets of every width;
+# batches of a few and of thousands; gamma 0, between, above 1; rows and queries that leave tiles unfilled
+CASES = [
+    # n, d, M, bits, nlist, nq, nprobe, k, batch, gamma, spread, offset
+    (5000, 300, 60, 8, 0, 129, 0, 100, 1, 0.7, 1.0, 3.0),
+    (20000, 256, 64, 8, 40, 140, 12, 10, 512, 0.5, 1.0, 0.0),
+    (20000, 384, 48, 8, 33, 300, 9, 10, 1024, 0.2, 0.3, 10.0),
+    (12000, 400, 80, 8, 20, 150, 7, 100, 300, 0.6, 0.2, 0.0),
+    (15000, 768, 96, 8, 0, 130, 0, 100, 512, 0.3, 0.3, 0.0),
+    (9000, 512, 32, 8, 16, 200, 16, 300, 4096, 1.5, 0.5, 0.0),
+    (6000, 256, 8, 8, 10, 129, 4, 1, 7, 0.0, 0.5, 0.0),
+    (10000, 256, 128, 4, 24, 260, 8, 10, 256, 0.4, 0.5, 0.0),
+    (7000, 1536, 192, 8, 12, 131, 6, 64, 1000, 0.7, 0.1, 0.0),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
+def test_passes_equal_the_single_kernel(T, case):
+    import torch
+    n, d, M, bits, nlist, nq, nprobe, k, batch, gamma, spread, offset = case
+    ix, q, probes = built(T, n, d, M, bits, nlist, nq, nprobe, spread, offset, n + d)
+    cand, _ = ix._cand(probes)
+    view = ix._view()
+    assert T.lib().trim_knn_workspace_bytes(C.byref(view), nq, C.byref(cand) if cand is not None else None, k, batch) > 0
+    order = torch.randperm(nq, device="cuda").to(torch.int32)
+    order[2] = nq + 5                                    # a query that is not named
+    missing = sorted(set(range(nq)) - set(order.tolist()))
+    for o in (None, order):
+        want = single_kernel(T, ix, q, k, gamma, batch, probes, o)
+        out = (torch.full((nq, k), -7, dtype=torch.int32, device="cuda"), torch.full((nq, k), -7.0, device="cuda"))
+        got = T.trim_search_knn(ix, q, k, gamma, batch, probes=probes, want_mask=True, out=out, query_order=o)
+        rows = np.array([i for i in range(nq) if o is None or i not in missing])
+        for name in ("ids", "d2", "n_scanned", "n_exact", "mask"):
+            a, b = got[name].cpu().numpy(), want[name].cpu().numpy()
+            np.testing.assert_array_equal(a[rows], b[rows], err_msg=name)
+        np.testing.assert_array_equal(got["ids"].cpu().numpy(), want["ids"].cpu().numpy())
+
+
+def single_range(T, ix, q, radius, gamma, probes, order, lut):
+    import torch
+    nq = q.shape[0]
+    ns, ne = torch.zeros((2, nq), dtype=torch.int32, device="cuda").unbind(0)
+    cand, mc = ix._cand(probes)
+    mw = (mc + 31) // 32
+    mask = torch.zeros((nq, mw), dtype=torch.int32, device="cuda")
+    offsets = torch.zeros((nq + 1,), dtype=torch.int64, device="cuda")
+    required = torch.zeros((1,), dtype=torch.int64, device="cuda")
+    view, stats = ix._view(), T._Stats(ns.data_ptr(), ne.data_ptr(), None)
+    ws = torch.empty((T.trim_range_workspace_bytes(nq, mc),), dtype=torch.uint8, device="cuda")
+    p = lambda t: None if t is None else C.c_void_p(t.data_ptr())
+    cap = 4_000_000
+    ids = torch.empty((cap,), dtype=torch.int32, device="cuda")
+    d2 = torch.empty((cap,), device="cuda")
+    rc = T.lib().trim_search_range(C.byref(view), p(q), nq, p(lut), C.byref(cand) if cand is not None else None, radius, gamma,
+                                   p(order), p(offsets), p(ids), p(d2), cap, p(required), C.byref(stats), p(mask), mw,
+                                   p(ws), ws.numel(), C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    r = int(required)
+    assert r < cap
+    return dict(offsets=offsets, ids=ids[:r], d2=d2[:r], n_scanned=ns, n_exact=ne, mask=mask)
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
+@pytest.mark.parametrize("percent", (0.05, 5.0))
+def test_range_in_passes_equals_the_single_kernel(T, case, percent):
+    import torch
+    n, d, M, bits, nlist, nq, nprobe, _, _, gamma, spread, offset = case
+    ix, q, probes = built(T, n, d, M, bits, nlist, nq, nprobe, spread, offset, n + d)
+    cand, _ = ix._cand(probes)
+    view = ix._view()
+    assert T.lib().trim_range_scratch_bytes(C.byref(view), nq, C.byref(cand) if cand is not None else None) > 0
+    radius = float(torch.quantile(torch.cdist(q[:64], ix.base).flatten()[:4_000_000].cpu().double(), percent / 100))
+    lut = (T.trim_build_lut if bits == 8 else T.trim_fs_build_lut)(q, ix.codebooks)
+    other = lut.clone()
+    other[4:9] *= 0.75                                   # tables that are not the centroids' distances
+    order = torch.randperm(nq, device="cuda").to(torch.int32)
+    order[2] = nq + 5
+    missing = (set(range(nq)) - set(order.tolist())).pop()
+    for o, table in ((None, None), (order, None), (None, lut), (order, other)):
+        want = single_range(T, ix, q, radius, gamma, probes, o, table)
+        r = want["ids"].shape[0]
+        for capacity in (0, r + 3):
+            got = T.trim_search_range(ix, q, radius, gamma, probes=probes, lut=table, want_mask=True, query_order=o,
+                                      capacity=capacity)
+            rows = np.array([i for i in range(nq) if o is None or i != missing])
+            for name in ("n_scanned", "n_exact", "mask"):
+                np.testing.assert_array_equal(got[name].cpu().numpy()[rows], want[name].cpu().numpy()[rows], err_msg=name)
+            for name in ("offsets", "ids", "d2"):
+                np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
