@@ -467,13 +467,19 @@ void fill_finish(FinishArgs &m, const FinishPlan &pl, const SearchArgs &a) {
     m.off_q = pl.off_q; m.off_segp = pl.off_segp; m.off_segd = pl.off_segd; m.off_bits = pl.off_bits; m.off_ring = pl.off_ring;
 }
 
-// Whether a search runs in passes: many queries (a list's landmarks are shared by the queries that scan it; a tile
-// of the filter holds 128) over long rows (what the single kernel reads once per query and survivor).
-constexpr int64_t kManyQueries = 128;
-constexpr int kLongRow = 256;
+// Whether a search runs in passes.  They pay where rows are long (what the single kernel reads once per query and
+// survivor), a list is scanned by a few queries at a time (its tiles hold 128 of them) and the single
+// kernel has more queries than CUs.  Measured, single kernel / passes: 768 values, queries per list 5: 400 / 539 us
+// (200 queries), 6: 942 / 970 us, 11: 1263 / 911 us, 20: 1337 / 715 us; 1536 values, 7: 932 / 944 us (200 queries), 15:
+// 1533 / 1112 us; range, 768 values, 6: 275 / 315 us, 131: 1712 / 743 us; 256 values, 58: 517 / 706 us.
+constexpr int64_t kManyQueries = 256;
+constexpr int kLongRow = 512;
+constexpr double kSharedValues = 8192.0;      // values per row times queries per list
 constexpr size_t kKnnSlabBytes = size_t(8) << 30;
-bool worth_passes(const trim_index_view *ix, int64_t nq) {
-    return nq > kManyQueries && ix->n > 0 && ix->d >= kLongRow && filter_padded(ix->d / ix->M, is_fs(ix)) != 0;
+bool worth_passes(const trim_index_view *ix, int64_t nq, const trim_candidates *cand) {
+    if (nq <= kManyQueries || ix->n <= 0 || ix->d < kLongRow || !filter_padded(ix->d / ix->M, is_fs(ix))) return false;
+    const double share = cand ? (double)nq * cand->nprobe / cand->nlist : (double)nq;
+    return share * ix->d >= kSharedValues;
 }
 
 inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -554,7 +560,7 @@ KnnLayout knn_layout(const trim_index_view *ix, int64_t nq, const trim_candidate
     KnnLayout L{};
     const int64_t hard = (int64_t(1) << 31) - 1 - TRIM_MAX_BATCH - 2048;
     int64_t mc = cand ? cand->max_candidates : ix->n;
-    if (mc <= 0 || mc > ix->n + (int64_t)(cand ? cand->nprobe : 0) * ix->n || !worth_passes(ix, nq)) return L;
+    if (mc <= 0 || mc > ix->n + (int64_t)(cand ? cand->nprobe : 0) * ix->n || !worth_passes(ix, nq, cand)) return L;
     if (mc > hard) mc = hard;
     L.words = (mc + 31) / 32 + 1;
     const size_t per = (size_t)L.words * (4 + 32 * 8) + 4 + filter_bytes_per_query(ix, cand);
@@ -690,7 +696,7 @@ int range_fill(const SearchArgs &a, const RangeLayout &L, unsigned char *ws, int
 
 // Scratch of a range search in passes: totals, then the filter's operands.  0: such a search runs as one kernel.
 size_t range_scratch_bytes(const trim_index_view *ix, int64_t nq, const trim_candidates *cand) {
-    if (!worth_passes(ix, nq)) return 0;
+    if (!worth_passes(ix, nq, cand)) return 0;
     return filter_layout(ix, nq, cand, up256((size_t)nq * 4)).end;
 }
 

@@ -76,15 +76,15 @@ def single_kernel(T, ix, q, k, gamma, batch, probes, order, lut=None):
 # batches of a few and of thousands; gamma 0, between, above 1; rows and queries that leave tiles unfilled
 CASES = [
     # n, d, M, bits, nlist, nq, nprobe, k, batch, gamma, spread, offset
-    (5000, 300, 60, 8, 0, 129, 0, 100, 1, 0.7, 1.0, 3.0),
-    (20000, 256, 64, 8, 40, 140, 12, 10, 512, 0.5, 1.0, 0.0),
-    (20000, 384, 48, 8, 33, 300, 9, 10, 1024, 0.2, 0.3, 10.0),
-    (12000, 400, 80, 8, 20, 150, 7, 100, 300, 0.6, 0.2, 0.0),
-    (15000, 768, 96, 8, 0, 130, 0, 100, 512, 0.3, 0.3, 0.0),
-    (9000, 512, 32, 8, 16, 200, 16, 300, 4096, 1.5, 0.5, 0.0),
-    (6000, 256, 8, 8, 10, 129, 4, 1, 7, 0.0, 0.5, 0.0),
-    (10000, 256, 128, 4, 24, 260, 8, 10, 256, 0.4, 0.5, 0.0),
-    (7000, 1536, 192, 8, 12, 131, 6, 64, 1000, 0.7, 0.1, 0.0),
+    (5000, 600, 120, 8, 0, 257, 0, 100, 1, 0.7, 1.0, 3.0),
+    (20000, 512, 128, 8, 40, 300, 12, 10, 512, 0.5, 1.0, 0.0),
+    (20000, 768, 96, 8, 33, 300, 9, 10, 1024, 0.2, 0.3, 10.0),
+    (12000, 800, 160, 8, 20, 270, 7, 100, 300, 0.6, 0.2, 0.0),
+    (15000, 768, 96, 8, 0, 260, 0, 100, 512, 0.3, 0.3, 0.0),
+    (9000, 512, 32, 8, 16, 290, 16, 300, 4096, 1.5, 0.5, 0.0),
+    (6000, 512, 16, 8, 10, 259, 4, 1, 7, 0.0, 0.5, 0.0),
+    (10000, 512, 256, 4, 24, 400, 8, 10, 256, 0.4, 0.5, 0.0),
+    (7000, 1536, 192, 8, 12, 261, 6, 64, 1000, 0.7, 0.1, 0.0),
 ]
 
 
@@ -122,7 +122,7 @@ def single_range(T, ix, q, radius, gamma, probes, order, lut):
     view, stats = ix._view(), T._Stats(ns.data_ptr(), ne.data_ptr(), None)
     ws = torch.empty((T.trim_range_workspace_bytes(nq, mc),), dtype=torch.uint8, device="cuda")
     p = lambda t: None if t is None else C.c_void_p(t.data_ptr())
-    cap = 4_000_000
+    cap = 8_000_000
     ids = torch.empty((cap,), dtype=torch.int32, device="cuda")
     d2 = torch.empty((cap,), device="cuda")
     rc = T.lib().trim_search_range(C.byref(view), p(q), nq, p(lut), C.byref(cand) if cand is not None else None, radius, gamma,
