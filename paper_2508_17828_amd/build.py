@@ -61,7 +61,7 @@ def _without_remarks(stderr: str):
 def check_resources(res) -> None:
     """The search kernels address their distance table from LDS address 0: none may carry
     static LDS in front of its dynamic area."""
-    bad = [n for n, r in res.items() if ("search_kernel" in n or "finish_kernel" in n) and r["static_lds"] != 0]
+    bad = [n for n, r in res.items() if any(k in n for k in ("search_kernel", "finish_kernel", "bound_kernel")) and r["static_lds"] != 0]
     if bad:
         raise RuntimeError("search kernels with static LDS (their table would not start at LDS "
                            "address 0): " + ", ".join(bad))
@@ -98,7 +98,8 @@ def build(verbose: bool = False, extra=()) -> str:
         jobs.append([hipcc] + cflags + [f"-DTRIM_INST_MODE={mode}", f"-DTRIM_INST_E={e}",
                                         f"-DTRIM_INST_BITS={bits}", f"-DTRIM_INST_LEAN={lean}", "-o", obj,
                                         os.path.join(CSRC, "trim_search_inst.hip")])
-    jobs.append([hipcc] + cflags + ["-o", os.path.join(objdir, "trim_mark.o"), os.path.join(CSRC, "trim_mark_inst.hip")])
+    for name in ("mark", "few"):
+        jobs.append([hipcc] + cflags + ["-o", os.path.join(objdir, f"trim_{name}.o"), os.path.join(CSRC, f"trim_{name}_inst.hip")])
     workers = max(1, min(len(jobs), int(os.environ.get("MAX_JOBS", os.cpu_count() or 4))))
     res = {}
     with ThreadPoolExecutor(max_workers=workers) as pool:

@@ -34,7 +34,6 @@ static_assert(kWorkCounters == TRIM_WORK_COUNTERS && kWorkFirstPass == TRIM_WORK
               kWorkLookups == TRIM_WORK_LOOKUPS && kWorkRows == TRIM_WORK_ROWS &&
               kWorkFullCode == TRIM_WORK_FULL_CODE, "header and kernel disagree on the work counters");
 
-constexpr size_t kLdsBytes = 160 * 1024;  // LDS per workgroup on gfx950
 
 
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -631,6 +630,56 @@ int knn_in_passes(const trim_index_view *ix, const KnnLayout &L, const SearchArg
     return TRIM_OK;
 }
 
+// Probe selection in two kernels (distances, selection): up to 64 probes, and few enough queries for one
+// workgroup per 8 of them to leave CUs idle.
+bool probe_in_two(int64_t nq, int d, int nlist, int nprobe) {
+    return nprobe <= 64 && nprobe > 1 && nq <= 4096 && (size_t)8 * d * 4 <= kLdsBytes / 2 && nlist >= 64 &&
+           (size_t)nq * nlist <= size_t(1) << 26;
+}
+
+// Few queries: bound_kernel and settle_kernel (see trim_few.h).
+constexpr int64_t kFewQueries = 128;
+constexpr size_t kFewBytes = size_t(1) << 30;
+struct FewLayout {
+    int64_t stride;           // bounds per query (0: not this way)
+    size_t off_g, off_d2, total;      // totals at 0
+    bool measure_first;
+};
+FewLayout few_layout(const trim_index_view *ix, int64_t nq, const trim_candidates *cand, int k, int batch) {
+    FewLayout L{};
+    const int64_t mc = cand ? std::min<int64_t>(cand->max_candidates, (int64_t)cand->nprobe * ix->n) : ix->n;
+    if (nq <= 0 || nq > kFewQueries || mc <= 0 || k + batch > kSettleFirst || k < 1 || batch < 1) return L;
+    const int64_t stride = (mc + 15) / 16 * 16;
+    const size_t g_bytes = (size_t)nq * stride * 4;
+    if ((size_t)stride > kFewBytes || g_bytes > kFewBytes || mc > 0x40000000 || !few_fits(ix->d, code_bytes(ix), is_fs(ix), k, cand ? cand->nprobe : 0)) return L;
+    L.stride = stride;
+    // The seed and the first batch measured beside the bounds, survivors or not, while that is little to read.
+    L.measure_first = (size_t)nq * (k + batch) * ix->d * 4 <= (size_t(32) << 20);
+    L.off_g = up256((size_t)nq * 4);
+    L.off_d2 = L.off_g + up256(g_bytes);
+    L.total = L.off_d2 + (L.measure_first ? up256((size_t)nq * (k + batch) * 4) : 0);
+    return L;
+}
+int knn_few(const trim_index_view *ix, const FewLayout &L, const SearchArgs &a, unsigned char *ws, hipStream_t st) {
+    FewArgs f{};
+    f.base = a.base; f.codes = a.codes; f.dlx = a.dlx; f.codebooks = a.codebooks; f.ids = a.ids; f.n = a.n;
+    f.d = a.d; f.M = a.M; f.dsub = a.dsub; f.queries = a.queries; f.nq = a.nq; f.order = a.order; f.lut = a.lut;
+    f.list_offsets = a.list_offsets; f.probes = a.probes; f.nlist = a.nlist; f.nseg = a.nseg;
+    f.max_cand = (int32_t)std::min<int64_t>(a.max_cand, L.stride);
+    f.two_gamma = a.two_gamma; f.k = a.k; f.batch = a.batch;
+    f.totals = reinterpret_cast<int32_t *>(ws);
+    f.g = reinterpret_cast<float *>(ws + L.off_g);
+    f.stride = L.stride;
+    f.d2 = L.measure_first ? reinterpret_cast<float *>(ws + L.off_d2) : nullptr;
+    f.out_ids = a.out_ids; f.out_d2 = a.out_d2; f.n_scanned = a.n_scanned; f.n_exact = a.n_exact;
+    f.mask = a.mask; f.mask_words = a.mask_words;
+    // two workgroups per CU over all queries, each with a candidate per thread at the least
+    const int64_t split = std::max<int64_t>(1, std::min<int64_t>((512 + a.nq - 1) / a.nq, (f.max_cand + kBoundThreads - 1) / kBoundThreads));
+    int rc;
+    if ((rc = launch_bound(f, is_fs(ix), (int)split, st))) return rc;
+    return launch_settle(f, st);
+}
+
 int search_knn(const trim_index_view *index, const float *queries, int64_t nq, const float *lut, const trim_candidates *cand,
                int32_t k, float gamma, int32_t batch, const int32_t *query_order, int32_t *out_ids, float *out_d2,
                const trim_stats *stats, uint32_t *survivor_mask, int64_t mask_words, void *workspace, size_t workspace_bytes,
@@ -659,6 +708,8 @@ int search_knn(const trim_index_view *index, const float *queries, int64_t nq, c
     a.chunk = 0; a.nsplit = 1;
     a.nq = nq; a.order = query_order;
     if (workspace && !a.work && (reinterpret_cast<uintptr_t>(workspace) & 255u) == 0 && aligned16(queries)) {
+        const FewLayout F = few_layout(index, nq, cand, k, batch);
+        if (F.stride > 0 && workspace_bytes >= F.total) return knn_few(index, F, a, static_cast<unsigned char *>(workspace), st);
         const KnnLayout L = knn_layout(index, nq, cand);
         FinishPlan fp;
         if (L.slab > 0 && workspace_bytes >= L.total && index->codebooks &&
@@ -1140,7 +1191,8 @@ int trim_search_knn(const trim_index_view *index, const float *queries, int64_t 
 
 size_t trim_knn_workspace_bytes(const trim_index_view *index, int64_t nq, const trim_candidates *cand, int32_t k, int32_t batch) {
     if (check_index(index) || check_cand(cand) || nq <= 0 || k < 1 || batch < 1) return 0;
-    return knn_layout(index, nq, cand).total;
+    const FewLayout F = few_layout(index, nq, cand, k, batch);
+    return F.stride > 0 ? F.total : knn_layout(index, nq, cand).total;
 }
 
 int trim_search_knn_ws(const trim_index_view *index, const float *queries, int64_t nq,
@@ -1211,6 +1263,35 @@ int trim_range_collect(const trim_index_view *index, int64_t nq, const trim_cand
 }
 
 size_t trim_static_scratch_bytes(void) { return kScratchBytes; }
+
+size_t trim_ivf_probe_workspace_bytes(int64_t nq, int32_t d, int32_t nlist, int32_t nprobe) {
+    if (nq <= 0 || d <= 0 || nlist <= 0 || nprobe <= 0) return 0;
+    return probe_in_two(nq, d, nlist, nprobe) ? (size_t)nq * nlist * 4 : 0;
+}
+
+int trim_ivf_probe_ws(const float *queries, int64_t nq, int32_t d, const float *centroids, int32_t nlist, int32_t nprobe,
+                      int32_t *probes_out, void *workspace, size_t workspace_bytes, void *stream) {
+    if (nq <= 0 || d <= 0 || nlist <= 0 || nprobe <= 0 || nprobe > nlist || d % 4 || !queries || !centroids || !probes_out ||
+        !aligned16(centroids) || !workspace || (reinterpret_cast<uintptr_t>(workspace) & 3u) ||
+        !probe_in_two(nq, d, nlist, nprobe) || workspace_bytes < (size_t)nq * nlist * 4)
+        return trim_ivf_probe(queries, nq, d, centroids, nlist, nprobe, probes_out, stream);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    uint32_t *dist = static_cast<uint32_t *>(workspace);
+    const int qt = nq >= 8 ? 8 : nq >= 4 ? 4 : nq >= 2 ? 2 : 1, rows = kProbeThreads / 32 * (qt == 8 ? 4 : 8);
+    void (*fn)(const float *, int64_t, int, const float *, int, uint32_t *) =
+        qt == 8 ? probe_distance_kernel<8> : qt == 4 ? probe_distance_kernel<4> : qt == 2 ? probe_distance_kernel<2> : probe_distance_kernel<1>;
+    const size_t lds = (size_t)qt * d * 4;
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(fn, dim3((unsigned)((nlist + rows - 1) / rows), (unsigned)((nq + qt - 1) / qt)), dim3(kProbeThreads), lds, st,
+                       queries, nq, d, centroids, nlist, dist);
+    HIP_TRY(hipGetLastError());
+    if (nprobe <= 32)
+        hipLaunchKernelGGL(probe_select_kernel<1>, dim3((unsigned)nq), dim3(kWave), 0, st, dist, nlist, nprobe, probes_out);
+    else
+        hipLaunchKernelGGL(probe_select_kernel<2>, dim3((unsigned)nq), dim3(kWave), 0, st, dist, nlist, nprobe, probes_out);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
 
 int trim_ivf_probe(const float *queries, int64_t nq, int32_t d, const float *centroids,
                    int32_t nlist, int32_t nprobe, int32_t *probes_out, void *stream) {

@@ -1361,6 +1361,164 @@ __global__ __launch_bounds__(256) void range_fill_kernel(const RangeFillArgs a) 
     }
 }
 
+// ---- coarse probe selection in two kernels: few queries ----
+// ivf_probe_kernel gives 8 queries one workgroup, which walks all centroids: 35 us for one query over 1024 lists of
+// 128 values, 75 us for 67 over 1024 of 384, on one and nine of the CUs.  Here the lists are split over the grid as
+// well (grid.x, 8 kRows per workgroup) and the distances pass through memory: dist [nq][nlist], bit patterns.
+constexpr int kProbeThreads = 256;
+template <int QT>
+__global__ __launch_bounds__(kProbeThreads) void probe_distance_kernel(const float *__restrict__ queries, int64_t nq, int d,
+                                                                      const float *__restrict__ centroids, int nlist,
+                                                                      uint32_t *__restrict__ dist) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    float *q_lds = reinterpret_cast<float *>(smem);                            // [QT][d]
+    const int tid = threadIdx.x, lane32 = tid & 31, ng = d >> 2;
+    const int64_t q0 = (int64_t)blockIdx.y * QT;
+    const int nqt = (int)(nq - q0 < QT ? nq - q0 : QT);
+    for (int t = tid; t < QT * d; t += kProbeThreads) q_lds[t] = t < nqt * d ? queries[(size_t)q0 * d + t] : 0.0f;
+    __syncthreads();
+    // (the loop of ivf_probe_kernel: eight or four rows per half wave against the queries, sums reduced together)
+    constexpr int kRows = QT == 8 ? 4 : 8, NP = kRows * QT;
+    constexpr int kShift = NP == 32 ? 0 : NP == 16 ? 1 : 2;
+    const int l0 = ((int)blockIdx.x * (kProbeThreads / 32) + (tid >> 5)) * kRows;
+    if (l0 >= nlist) return;
+    const float4 *row0 = reinterpret_cast<const float4 *>(centroids + (size_t)l0 * d);
+    const int last = nlist - 1 - l0;     // (rows past the end: the last row again, never stored)
+    float acc[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) acc[i] = 0.0f;
+    for (int g = lane32; g < ng; g += 32) {
+        float4 x[kRows];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) x[r] = row0[(r < last ? r : last) * ng + g];
+#pragma unroll
+        for (int qi = 0; qi < QT; ++qi) {
+            const float4 qv = *reinterpret_cast<const float4 *>(q_lds + qi * d + 4 * g);
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                float e, a0 = acc[r * QT + qi];
+                e = qv.x - x[r].x; a0 = __builtin_fmaf(e, e, a0);
+                e = qv.y - x[r].y; a0 = __builtin_fmaf(e, e, a0);
+                e = qv.z - x[r].z; a0 = __builtin_fmaf(e, e, a0);
+                e = qv.w - x[r].w; a0 = __builtin_fmaf(e, e, a0);
+                acc[r * QT + qi] = a0;
+            }
+        }
+    }
+    const float v = reduce_pairs<NP>(acc, lane32);
+    const int pair = lane32 >> kShift, l = l0 + pair / QT, qi = pair % QT;
+    if ((lane32 & ((1 << kShift) - 1)) == 0 && l < nlist && qi < nqt) dist[(size_t)(q0 + qi) * nlist + l] = __float_as_uint(v);
+}
+// The nprobe (at most 64) least (distance, list) of a query: one wave each.  The lists are 64 S columns (lane, slot); the
+// nprobe-th least of the columns' minima bounds the nprobe-th least of all, so whatever is not above it
+// is sorted -- if that is more than fits (rare: many near lists in one column), the least are taken one by one.
+template <int S>
+__global__ __launch_bounds__(kWave) void probe_select_kernel(const uint32_t *__restrict__ dist, int nlist, int nprobe,
+                                                             int32_t *__restrict__ probes) {
+    __shared__ unsigned long long s_key[kWave * S];
+    const int lane = threadIdx.x;
+    const uint32_t *row = dist + (size_t)blockIdx.x * nlist;
+    int32_t *out = probes + (size_t)blockIdx.x * nprobe;
+    auto exchange = [](unsigned long long v, int j) {
+        const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, j), hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), j);
+        return ((unsigned long long)hi << 32) | lo;
+    };
+    // ascending bitonic sort of 64 S keys (element 64 slot + lane)
+    auto sort_across = [&](unsigned long long (&key)[S]) {
+#pragma unroll
+        for (int size = 2; size <= kWave * S; size <<= 1)
+#pragma unroll
+            for (int j = size >> 1; j > 0; j >>= 1) {
+                if (j >= kWave) {                    // (S == 2, the last merge)
+                    const unsigned long long a = key[0], b = key[S - 1];
+                    key[0] = a < b ? a : b;
+                    key[S - 1] = a < b ? b : a;
+                    continue;
+                }
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    const unsigned long long other = exchange(key[s], j);
+                    const bool keep_min = ((lane & j) == 0) == (((kWave * s + lane) & size) == 0);
+                    if (keep_min ? other < key[s] : other > key[s]) key[s] = other;
+                }
+            }
+    };
+    unsigned long long least[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) least[s] = ~0ull;
+    for (int i0 = 0; i0 < nlist; i0 += 8 * kWave * S) {
+        uint32_t v[8][S];
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                const int i = i0 + (t * S + s) * kWave + lane;
+                v[t][s] = i < nlist ? row[i] : ~0u;
+            }
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                const int i = i0 + (t * S + s) * kWave + lane;
+                const unsigned long long key = ((unsigned long long)v[t][s] << 32) | (uint32_t)i;
+                if (i < nlist && key < least[s]) least[s] = key;
+            }
+    }
+    sort_across(least);
+    const unsigned long long at = nprobe > kWave ? least[S - 1] : least[0];
+    const int src = (nprobe - 1) & 63;
+    const unsigned long long cut =
+        ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(at >> 32), src) << 32) |
+        (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)at, src);
+    // (fewer columns in use than probes: everything qualifies)
+    int n = 0;
+    for (int i0 = 0; i0 < nlist; i0 += 8 * kWave) {
+        uint32_t v[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const int i = i0 + t * kWave + lane;
+            v[t] = i < nlist ? row[i] : ~0u;
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const int i = i0 + t * kWave + lane;
+            const unsigned long long key = ((unsigned long long)v[t] << 32) | (uint32_t)i;
+            const bool take = i < nlist && key <= cut;
+            const unsigned long long m = __ballot(take);
+            const int to = n + __popcll(m & ((1ull << lane) - 1ull));
+            if (take && to < kWave * S) s_key[to] = key;
+            n += __popcll(m);
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (n <= kWave * S) {
+        unsigned long long key[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) key[s] = kWave * s + lane < n ? s_key[kWave * s + lane] : ~0ull;
+        sort_across(key);
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+            if (kWave * s + lane < nprobe) out[kWave * s + lane] = (int32_t)(key[s] & 0xffffffffu);
+        return;
+    }
+    unsigned long long after = 0;                    // the least key not taken yet is at least this
+    for (int p = 0; p < nprobe; ++p) {
+        unsigned long long m = ~0ull;
+        for (int i = lane; i < nlist; i += kWave) {
+            const unsigned long long key = ((unsigned long long)row[i] << 32) | (uint32_t)i;
+            if (key >= after && key < m) m = key;
+        }
+#pragma unroll
+        for (int j = 32; j > 0; j >>= 1) {
+            const unsigned long long other = exchange(m, j);
+            m = other < m ? other : m;
+        }
+        if (lane == 0) out[p] = (int32_t)(m & 0xffffffffu);
+        after = m + 1;
+    }
+}
+
 // ---- coarse probe selection (Section 6.1: IVFPQ with C' lists, nprobe probed) ----
 // One workgroup handles QT queries: every centroid row is read once and measured against
 // all QT queries (exact distances by half waves, rounding order as in exact_d2_half; the lane

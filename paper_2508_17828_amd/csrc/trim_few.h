@@ -1,0 +1,340 @@
+// The kNN search of few queries (Section 4.2), in two kernels.
+//
+// search_kernel gives a query one workgroup, and a launch of few queries leaves most of the chip idle while each
+// workgroup goes through its chain of dependent steps: one query over 32,000 candidates takes it
+// 60 us, whatever the other 255 CUs do.  Here
+//
+//   bound_kernel   many workgroups per query, each with the query's table: the bounds of ALL candidates, by
+//                  the rule, and (where a first batch is small) the exact distances of the seed and the first batch
+//   settle_kernel  one workgroup per query: the seed, the first batch, then whoever is not above the
+//                  threshold, measured and replayed batch by batch
+//
+// No candidate is abandoned early and no list is passed over: with CUs to spare the lookups cost less than the chain
+// of thresholds they would have to wait for.  Bound by latency: launches, the table, the measured rows.
+#pragma once
+
+#include "trim_passes.h"
+#include "trim_steps.h"
+
+namespace trim {
+
+template <int VEC, bool FS>
+__global__ __launch_bounds__(kBoundThreads) void bound_kernel(const FewArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    float *tab = reinterpret_cast<float *>(smem);
+    float *q_lds = reinterpret_cast<float *>(smem + a.off_q);
+    int *segp = reinterpret_cast<int *>(smem + a.off_segp), *segd = reinterpret_cast<int *>(smem + a.off_segd);
+    const int tid = threadIdx.x, split = blockIdx.x, nsplit = gridDim.x;
+    const int64_t slot = blockIdx.y;
+    const int64_t q = a.order ? a.order[slot] : slot;
+    if (q < 0 || q >= a.nq) return;
+    for (int t = tid; t < a.d; t += kBoundThreads) q_lds[t] = a.queries[(size_t)q * a.d + t];
+    segment_table(a.list_offsets, a.probes, a.nlist, a.nseg, a.n, a.max_cand, q, segp, segd);
+    const int total = segp[a.nseg > 0 ? a.nseg : 1];
+    if (split == 0 && tid == 0) {
+        a.totals[slot] = total;
+        if (a.n_scanned) a.n_scanned[q] = total;
+    }
+    // exact distances of this workgroup's share of the seed and the first batch, four rows per half wave
+    if (a.d2) {
+        const int fb = total < a.k + a.batch ? total : a.k + a.batch;
+        const int f0 = (int)((int64_t)fb * split / nsplit), f1 = (int)((int64_t)fb * (split + 1) / nsplit);
+        const int half = tid >> 5, lane32 = tid & 31;
+        float *out = a.d2 + (size_t)slot * (a.k + a.batch);
+        for (int c = f0 + half * 4; c < f1; c += kBoundThreads / 32 * 4) {
+            const float *rows[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                rows[u] = a.base + (size_t)segment_position(c + u < f1 ? c + u : c, segp, segd, a.nseg) * a.d;
+            const float v = exact_d2_half_x4<true>(rows[0], rows[1], rows[2], rows[3], q_lds, a.d, lane32);
+            const int mine = c + half_reduce_x4_row(lane32);
+            if (half_reduce_x4_writer(lane32) && mine < f1) out[mine] = v;
+        }
+    }
+    const int chunk = ((total + nsplit - 1) / nsplit + 63) & ~63;
+    const int64_t cb = (int64_t)split * chunk;
+    if (cb >= total) return;
+    const int c0 = (int)cb, c1 = c0 + chunk < total ? c0 + chunk : total;
+    float *row_g = a.g + (size_t)slot * a.stride;
+    for (int ph = 0; ph < a.P; ++ph) {
+        if (ph > 0) __syncthreads();
+        if (a.lut) {
+            const float4 *src = reinterpret_cast<const float4 *>(a.lut + ((size_t)q * a.M + ph * a.Mp) * kByteEntries<FS>);
+            float4 *dst = reinterpret_cast<float4 *>(tab);
+            for (int e = tid; e < a.Mp * (kByteEntries<FS> / 4); e += kBoundThreads) dst[e] = src[e];
+        } else {
+            build_table_rows<FS>(tab, q_lds, a.codebooks, a.dsub, ph * a.Mp, a.Mp);
+        }
+        __syncthreads();
+        const bool last = ph == a.P - 1;
+        for (int c = c0 + tid; c < c1; c += kBoundThreads) {
+            const int pos = segment_position(c, segp, segd, a.nseg);
+            const uint8_t *code = a.codes + (size_t)pos * a.M + ph * a.Mp;
+            const float b = last ? a.dlx[pos] : 0.0f;
+            float sum = ph > 0 ? row_g[c] : 0.0f;
+            constexpr int kAhead = 2;
+            for (int j = 0; j < a.Mp; j += kAhead * 4 * VEC) {
+                uint32_t w[kAhead][VEC];
+#pragma unroll
+                for (int i = 0; i < kAhead; ++i)
+                    if (j + i * 4 * VEC < a.Mp) load_codes<VEC>(w[i], code + j + i * 4 * VEC);
+#pragma unroll
+                for (int i = 0; i < kAhead; ++i)
+                    if (j + i * 4 * VEC < a.Mp)
+                        sum = gather_add<VEC, false, FS>(sum, (j + i * 4 * VEC) * kByteRow<FS>, w[i], __builtin_inff());
+            }
+            row_g[c] = last ? plb_from_s(sum, b, a.two_gamma) : sum;
+        }
+    }
+}
+
+// One workgroup per query.  R after the first batch is its k least distances: a histogram of the distances' bit
+// patterns leaves little more than k of them to sort.  Then stretches of candidates, each as long as what
+// has been seen (4,096 or 16,384; half of that with wide R), listed against the threshold at their start, measured, and replayed
+// by the first wave.
+template <int E>
+__global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs a) {
+    constexpr int T = settle_threads(E);
+    extern __shared__ __align__(16) unsigned char smem[];
+    float *q_lds = reinterpret_cast<float *>(smem + a.off_q);
+    int *segp = reinterpret_cast<int *>(smem + a.off_segp), *segd = reinterpret_cast<int *>(smem + a.off_segd);
+    float *rd2 = reinterpret_cast<float *>(smem + a.off_rd2);
+    int32_t *rid = reinterpret_cast<int32_t *>(smem + a.off_rid);
+    float *f_d2 = reinterpret_cast<float *>(smem + a.off_fd2);                              // [k + batch]
+    unsigned long long *s_key = reinterpret_cast<unsigned long long *>(smem + a.off_key);   // [kSettleFirst]
+    uint16_t *s_todo = reinterpret_cast<uint16_t *>(smem + a.off_todo);                     // [kSettleFirst]
+    // (stretches; over the keys)
+    int32_t *s_cl = reinterpret_cast<int32_t *>(smem + a.off_key), *s_id = s_cl + kSettleList;
+    float *s_g = reinterpret_cast<float *>(s_id + kSettleList), *s_d2 = s_g + kSettleList;
+    __shared__ int hist[256], part[T / kWave];
+    __shared__ uint32_t s_most, s_least;
+    __shared__ int s_n, s_count, s_frozen;
+    __shared__ float s_tau, s_tau_f;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t slot = blockIdx.x;
+    const int64_t q = a.order ? a.order[slot] : slot;
+    if (q < 0 || q >= a.nq) return;
+    for (int t = tid; t < a.d; t += T) q_lds[t] = a.queries[(size_t)q * a.d + t];
+    if (tid < 256) hist[tid] = 0;
+    if (tid == 0) { s_most = 0; s_least = ~0u; s_n = 0; s_count = 0; }
+    segment_table(a.list_offsets, a.probes, a.nlist, a.nseg, a.n, a.max_cand, q, segp, segd);
+    const int total = a.totals[slot];
+    const int ns = total < a.k ? total : a.k, fb = total < a.k + a.batch ? total : a.k + a.batch;
+    const float *row_g = a.g + (size_t)slot * a.stride;
+    uint32_t *mask_row = a.mask ? a.mask + (size_t)q * a.mask_words : nullptr;
+    // exact distances of n candidates at(i), four rows per half wave; put(i, d2, storage position)
+    auto measure = [&](int n, auto at, auto put) {
+        const int half = tid >> 5, lane32 = tid & 31;
+        for (int i = half * 4; i < n; i += T / 32 * 4) {
+            int pos[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) pos[u] = segment_position(at(i + u < n ? i + u : i), segp, segd, a.nseg);
+            const float v = exact_d2_half_x4<true>(a.base + (size_t)pos[0] * a.d, a.base + (size_t)pos[1] * a.d,
+                                                   a.base + (size_t)pos[2] * a.d, a.base + (size_t)pos[3] * a.d, q_lds, a.d, lane32);
+            const int r = half_reduce_x4_row(lane32);
+            const int p = r == 0 ? pos[0] : r == 1 ? pos[1] : r == 2 ? pos[2] : pos[3];
+            if (half_reduce_x4_writer(lane32) && i + r < n) put(i + r, v, p);
+        }
+        __syncthreads();
+    };
+    // ---- the seed: its largest distance is the first batch's threshold ----
+    if (a.d2) {
+        for (int i = tid; i < fb; i += T) f_d2[i] = a.d2[(size_t)slot * (a.k + a.batch) + i];
+        __syncthreads();
+    } else {
+        measure(ns, [&](int i) { return i; }, [&](int i, float v, int) { f_d2[i] = v; });
+    }
+    uint32_t most = 0;
+    for (int i = tid; i < ns; i += T) most = max(most, __float_as_uint(f_d2[i]));
+    if (most) atomicMax(&s_most, most);
+    __syncthreads();
+    // (a distance that is no number is never in R: then R is not full yet)
+    const bool full = ns == a.k && s_most <= 0x7f800000u;
+    const float tau1 = full ? __uint_as_float(s_most) : __builtin_inff();
+    // ---- the first batch ----
+    {
+        int mine = 0;
+        for (int i = tid; i < fb; i += T) {
+            const bool on = i < ns || row_g[i] <= tau1;
+            mine += on;
+            if (on && mask_row && (i >> 5) < a.mask_words) atomicOr(&mask_row[i >> 5], 1u << (i & 31));
+            if (on && (a.d2 != nullptr || i >= ns)) s_todo[atomicAdd(&s_n, 1)] = (uint16_t)i;
+        }
+        if (mine) atomicAdd(&s_count, mine);
+    }
+    __syncthreads();
+    int n = s_n;
+    if (!a.d2) {
+        measure(n, [&](int i) { return (int)s_todo[i]; }, [&](int i, float v, int) { f_d2[s_todo[i]] = v; });
+        for (int i = tid; i < ns; i += T) s_todo[n + i] = (uint16_t)i;
+        n += ns;
+        __syncthreads();
+    }
+    // the k least distances by (distance, id)
+    const uint32_t top = full ? __float_as_uint(tau1) : 0x7f800000u;    // (nothing above it can be among them)
+    uint32_t least = ~0u, cut = top;
+    int nk = 0;
+    for (int i = tid; i < n; i += T) least = min(least, __float_as_uint(f_d2[s_todo[i]]));
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) least = min(least, (uint32_t)__shfl_xor((int)least, off));
+    if (lane == 0) atomicMin(&s_least, least);
+    if (tid == 0) s_n = 0;
+    __syncthreads();
+    least = s_least;
+    if (full) {                                  // (else all of them are wanted, as far as they go)
+        const uint32_t span = top - least;       // least <= top: the seed is among them
+        const int shift = span < 256 ? 0 : 24 - __clz((int)span);
+        for (int i = tid; i < n; i += T) {
+            const uint32_t key = __float_as_uint(f_d2[s_todo[i]]);
+            if (key <= top) atomicAdd(&hist[(key - least) >> shift], 1);
+        }
+        __syncthreads();
+        if (wave == 0) {
+            int h[4], sum = 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { h[u] = hist[4 * lane + u]; sum += h[u]; }
+            int incl = sum;
+#pragma unroll
+            for (int off = 1; off < kWave; off <<= 1) {
+                const int v = __shfl_up(incl, off);
+                if (lane >= off) incl += v;
+            }
+            int before = incl - sum;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (before < a.k && before + h[u] >= a.k) s_least = least + (((uint32_t)(4 * lane + u + 1)) << shift) - 1u;
+                before += h[u];
+            }
+        }
+        __syncthreads();
+        cut = s_least < top ? s_least : top;
+    }
+    for (int i = tid; i < n; i += T) {
+        const int c = s_todo[i];
+        const uint32_t key = __float_as_uint(f_d2[c]);
+        if (key <= cut) {
+            const int pos = segment_position(c, segp, segd, a.nseg);
+            const int32_t id = a.ids ? a.ids[pos] : pos;
+            s_key[atomicAdd(&s_n, 1)] = ((unsigned long long)key << 32) | ((uint32_t)id ^ 0x80000000u);   // (ids order as signed)
+        }
+    }
+    __syncthreads();
+    nk = s_n;
+    if (nk <= kWave) {                           // (one wave, in registers)
+        if (wave == 0) {
+            unsigned long long key = lane < nk ? s_key[lane] : ~0ull;
+#pragma unroll
+            for (int size = 2; size <= kWave; size <<= 1)
+#pragma unroll
+                for (int j = size >> 1; j > 0; j >>= 1) {
+                    const uint32_t olo = (uint32_t)__shfl_xor((int)(uint32_t)key, j), ohi = (uint32_t)__shfl_xor((int)(uint32_t)(key >> 32), j);
+                    const unsigned long long other = ((unsigned long long)ohi << 32) | olo;
+                    const bool keep_min = ((lane & j) == 0) == ((lane & size) == 0);
+                    if (keep_min ? other < key : other > key) key = other;
+                }
+            if (lane < nk) s_key[lane] = key;
+        }
+        __syncthreads();
+    } else {
+        int size = 1;
+        while (size < nk) size <<= 1;
+        for (int i = nk + tid; i < size; i += T) s_key[i] = ~0ull;
+        __syncthreads();
+        sort_keys(s_key, size);
+    }
+    const int have = nk < a.k ? nk : a.k;
+    for (int i = tid; i < kWave * E; i += T) {
+        rd2[i] = i < have ? __uint_as_float((uint32_t)(s_key[i] >> 32)) : __builtin_inff();
+        rid[i] = i < have ? (int32_t)((uint32_t)s_key[i] ^ 0x80000000u) : kEmptyId;
+    }
+    __syncthreads();
+    ResultRegs<E> R;
+    int frozen_b = -2, survivors = s_count;
+    float tau_f = 0.0f;
+    if (wave == 0) {
+        R.load(rd2, rid, a.k, lane);
+        if (lane == 0) { s_tau = R.t_d2; s_frozen = -2; s_tau_f = 0.0f; }
+    }
+    __syncthreads();
+    // ---- the rest ----
+    for (int w0 = fb; w0 < total;) {
+        const int V = w0 < 16384 ? 4 : 16, base = w0 & ~3;
+        const int w1 = total - base < V * T ? total : base + V * T;
+        // (the batch that the last stretch ended in keeps the threshold that it began with)
+        const float tau = s_tau, tau_b = __builtin_fmaxf(tau, s_tau_f);
+        const int end_b = s_frozen >= 0 ? a.k + (s_frozen + 1) * a.batch : 0;
+        // (rows are allocated to a multiple of 16 floats)
+        float g[16];
+        uint32_t m = 0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int c = base + tid * V + 4 * v;
+            if (4 * v < V && c < w1) {
+                const float4 x = *reinterpret_cast<const float4 *>(row_g + c);
+                g[4 * v] = x.x; g[4 * v + 1] = x.y; g[4 * v + 2] = x.z; g[4 * v + 3] = x.w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (g[4 * v + e] <= (c + e < end_b ? tau_b : tau) && c + e >= w0 && c + e < w1) m |= 1u << (4 * v + e);
+            }
+        }
+        const int cnt = __popc(m);
+        int incl = cnt;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int v = __shfl_up(incl, off);
+            if (lane >= off) incl += v;
+        }
+        if (lane == 63) part[wave] = incl;
+        __syncthreads();
+        int before = incl - cnt, all = 0;
+#pragma unroll
+        for (int v = 0; v < T / kWave; ++v) {
+            const int p = part[v];
+            if (v < wave) before += p;
+            all += p;
+        }
+        for (int e0 = 0; e0 < all; e0 += kSettleList) {
+            const int np = all - e0 < kSettleList ? all - e0 : kSettleList;
+            int at = before - e0;
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                if ((m >> v) & 1u) {
+                    if (at >= 0 && at < np) { s_cl[at] = base + tid * V + v; s_g[at] = g[v]; }
+                    ++at;
+                }
+            if (tid == 0) s_n = 0;
+            __syncthreads();
+            // who is a survivor by now (a batch keeps the threshold that it began with) is measured
+            const float now = s_tau, tf = s_tau_f;
+            const int fz = s_frozen;
+            for (int i = tid; i < np; i += T) {
+                const int c = s_cl[i], b = (c - a.k) / a.batch;
+                s_d2[i] = __builtin_inff();
+                s_id[i] = kEmptyId;
+                if (s_g[i] <= (b == fz ? tf : now)) s_todo[atomicAdd(&s_n, 1)] = (uint16_t)i;
+            }
+            __syncthreads();
+            measure(s_n, [&](int i) { return s_cl[s_todo[i]]; },
+                    [&](int i, float v, int pos) { s_d2[s_todo[i]] = v; s_id[s_todo[i]] = a.ids ? a.ids[pos] : pos; });
+            if (wave == 0) {
+                survivors += replay_entries<E>(R, frozen_b, tau_f, s_cl, s_g, s_d2, s_id, np, a.batch, mask_row, a.mask_words);
+                if (lane == 0) { s_tau = R.t_d2; s_frozen = frozen_b; s_tau_f = tau_f; }
+            }
+            __syncthreads();
+        }
+        __syncthreads();
+        w0 = w1;
+    }
+    if (wave == 0) {
+        R.store(rd2, rid);
+        if (lane == 0 && a.n_exact) a.n_exact[q] = survivors;
+    }
+    __syncthreads();
+    for (int i = tid; i < a.k; i += T) {
+        const int32_t id = rid[i];
+        a.out_ids[(size_t)q * a.k + i] = id == kEmptyId ? -1 : id;
+        a.out_d2[(size_t)q * a.k + i] = rd2[i];
+    }
+}
+
+}  // namespace trim

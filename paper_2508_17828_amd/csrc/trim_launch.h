@@ -32,6 +32,8 @@ int hip_fail(hipError_t e);
         if (_e != hipSuccess) return ::trim::hip_fail(_e);    \
     } while (0)
 
+constexpr size_t kLdsBytes = 160 * 1024;  // LDS per workgroup on gfx950
+
 // launch_search_<mode>_e<result entries per lane>_c<bits per code>: enqueue the matching
 // instance of search_kernel (with or without the work counters, by SearchArgs::work).
 #define TRIM_DECLARE_LAUNCH(name) \
@@ -45,6 +47,10 @@ int launch_invert(const InvertArgs &a, hipStream_t st);
 int launch_measure(const FilterArgs &a, hipStream_t st);
 int launch_range_exact(ReplayArgs a, int64_t nslots, int nchunk, hipStream_t st);
 size_t replay_lds(int d, int k, int nseg);      // LDS of one of their workgroups
+// The search of few queries (trim_few_inst.hip).
+bool few_fits(int d, int M, bool fs, int k, int nseg);
+int launch_bound(FewArgs a, bool fs, int nsplit, hipStream_t st);
+int launch_settle(FewArgs a, hipStream_t st);
 int launch_replay(ReplayArgs a, int64_t nslots, hipStream_t st);
 
 TRIM_DECLARE_LAUNCH(launch_search_knnlean_e1_c8);

@@ -144,4 +144,40 @@ struct ReplayArgs {
 };
 constexpr int kReplayThreads = 512, kReplayCap = 2048;   // (a power of two)
 
+// ---- few queries (trim_few.h) ----
+constexpr int kBoundThreads = 512;
+constexpr int kSettleFirst = 4096, kSettleList = 2048;   // largest k + batch, listed candidates at a time
+constexpr int settle_threads(int E) { return E <= 2 ? 1024 : 512; }   // (R's registers)
+struct FewArgs {
+    // index, queries, candidate structure: as in SearchArgs
+    const float *base;
+    const uint8_t *codes;
+    const float *dlx;
+    const float *codebooks;
+    const int32_t *ids;
+    int64_t n;
+    int32_t d, M, dsub;
+    const float *queries;
+    int64_t nq;
+    const int32_t *order;
+    const float *lut;
+    const int64_t *list_offsets;
+    const int32_t *probes;
+    int32_t nlist, nseg, max_cand;
+    int32_t P, Mp;            // table phases
+    float two_gamma;
+    int32_t k, batch;
+    // work space, by place in the query order
+    int32_t *totals;          // candidates of the query
+    float *g;                 // [stride] their bounds
+    int64_t stride;           // (a multiple of 16)
+    float *d2;                // [k + batch] exact distances of the seed and the first batch, or null: settle measures
+    int32_t *out_ids;
+    float *out_d2;
+    int32_t *n_scanned, *n_exact;
+    uint32_t *mask;
+    int64_t mask_words;
+    uint32_t off_q, off_segp, off_segd, off_rd2, off_rid, off_fd2, off_key, off_todo;
+};
+
 }  // namespace trim

@@ -1,0 +1,151 @@
+// Device functions that the kernels of trim_mark.h and trim_few.h share.
+#pragma once
+
+#include "trim_search.h"
+
+namespace trim {
+
+// The segment table of a query (see SearchArgs): segp[0..nseg] prefix of the lengths, cut at max_cand,
+// segd[p] = storage position of the segment's first candidate less its scan-order number.  All
+// threads of the workgroup; ends with a barrier.  Sums saturate at max_cand < 2^31, so 32 bits do.
+__device__ __forceinline__ void segment_table(const int64_t *list_offsets, const int32_t *probes, int nlist, int nseg,
+                                              int64_t n, int max_cand, int64_t q, int *segp, int *segd) {
+    const int ns = nseg > 0 ? nseg : 1;
+    for (int p = threadIdx.x; p < ns; p += blockDim.x) {
+        int64_t s = 0, e = n;
+        if (nseg > 0) {
+            const int32_t l = probes[(size_t)q * nseg + p];
+            if (l >= 0 && l < nlist) {
+                s = list_offsets[l];
+                e = list_offsets[l + 1];
+                s = s < 0 ? 0 : (s > n ? n : s);
+                e = e < s ? s : (e > n ? n : e);
+            } else {
+                s = e = 0;
+            }
+        }
+        segd[p] = (int)s;
+        segp[p + 1] = (int)(e - s);
+    }
+    __syncthreads();
+    if (threadIdx.x < kWave) {
+        const int lane = threadIdx.x;
+        uint32_t carry = 0;
+        const uint32_t cap = (uint32_t)max_cand;
+        for (int p0 = 0; p0 < ns; p0 += kWave) {
+            const int p = p0 + lane;
+            uint32_t incl = p < ns ? (uint32_t)segp[p + 1] : 0u;
+            incl = incl < cap ? incl : cap;
+#pragma unroll
+            for (int off = 1; off < kWave; off <<= 1) {
+                const uint32_t v = (uint32_t)__shfl_up((int)incl, off);
+                if (lane >= off) { incl += v; incl = incl < cap ? incl : cap; }
+            }
+            incl += carry;
+            incl = incl < cap ? incl : cap;
+            uint32_t before = (uint32_t)__shfl_up((int)incl, 1);
+            if (lane == 0) before = carry;
+            if (p < ns) { segp[p + 1] = (int)incl; segd[p] -= (int)before; }
+            carry = (uint32_t)__shfl((int)incl, kWave - 1);
+        }
+        if (lane == 0) segp[0] = 0;
+    }
+    __syncthreads();
+}
+
+__device__ __forceinline__ int segment_position(int c, const int *segp, const int *segd, int nseg) {
+    int lo = 0, hi = (nseg > 0 ? nseg : 1) - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (c >= segp[mid + 1]) lo = mid + 1; else hi = mid;
+    }
+    return c + segd[lo];
+}
+
+// The batch rule over entries in scan order (replay_batches; the state of a batch that the next
+// call goes on with is kept in frozen_b and tau_f).  cl: candidate number; the first k candidates
+// are the seed: a batch of their own (-1) with no threshold.
+template <int E>
+__device__ __forceinline__ int replay_entries(ResultRegs<E> &R, int &frozen_b, float &tau_f, const int32_t *s_cl, const float *s_g,
+                                              const float *s_d2, const int32_t *s_id, int np, int batch, uint32_t *mask_row,
+                                              int64_t mask_words) {
+    int total = 0;
+    for (int i0 = 0; i0 < np; i0 += kWave) {
+        // Four chunks at once where nothing in them beats the k-th distance (most of a long scan): they only
+        // count, each entry against the threshold of its batch.
+        if (i0 + 4 * kWave <= np) {
+            float g4[4], d4[4];
+            int c4[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { g4[u] = s_g[i0 + u * kWave + R.lane]; d4[u] = s_d2[i0 + u * kWave + R.lane]; c4[u] = s_cl[i0 + u * kWave + R.lane]; }
+            bool better = false, on[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int b4 = c4[u] < R.k ? -1 : (c4[u] - R.k) / batch;
+                on[u] = b4 < 0 || g4[u] <= (b4 == frozen_b ? tau_f : R.t_d2);
+                better = better || (on[u] && d4[u] <= R.t_d2);
+            }
+            if (!__any(better)) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    total += __popcll(__ballot(on[u]));
+                    if (on[u] && mask_row) {
+                        const int64_t wi = c4[u] >> 5;
+                        if (wi < mask_words) atomicOr(&mask_row[wi], 1u << (c4[u] & 31));
+                    }
+                }
+                i0 += 3 * kWave;
+                continue;
+            }
+        }
+        const int i = i0 + R.lane;
+        bool pending = i < np;
+        int cl = 0, b = 0x7fffffff;
+        int32_t id = 0;
+        float g = __builtin_inff(), d2 = 0.0f;
+        if (pending) {
+            cl = s_cl[i]; g = s_g[i]; d2 = s_d2[i]; id = s_id[i];
+            b = cl < R.k ? -1 : (cl - R.k) / batch;
+            if (b < 0) g = -__builtin_inff();
+        }
+        auto mark = [&](bool on) {
+            total += __popcll(__ballot(on));
+            if (on && mask_row) {
+                const int64_t wi = cl >> 5;
+                if (wi < mask_words) atomicOr(&mask_row[wi], 1u << (cl & 31));
+            }
+        };
+        for (;;) {
+            // (see replay_batches: survivors that do not beat the k-th distance are taken all at once)
+            pending = pending && g <= (b == frozen_b ? tau_f : R.t_d2);
+            const unsigned long long mi = __ballot(pending && hit_less(d2, id, R.t_d2, R.t_id));
+            int fb = 0x7fffffff;
+            if (mi != 0) fb = __builtin_amdgcn_readlane(b, __ffsll((long long)mi) - 1);
+            const bool plain = pending && b < fb;
+            mark(plain);
+            pending = pending && !plain;
+            if (mi == 0) break;
+            if (fb != frozen_b) { frozen_b = fb; tau_f = R.t_d2; }
+            const bool sel = pending && b == fb;
+            mark(sel);
+            R.insert_pending(sel, d2, id);
+            pending = pending && !sel;
+        }
+    }
+    return total;
+}
+
+// Ascending bitonic sort of n keys in LDS (n a power of two) by all threads.  Ends with a barrier.
+__device__ __forceinline__ void sort_keys(unsigned long long *key, int n) {
+    for (int size = 2; size <= n; size <<= 1)
+        for (int j = size >> 1; j > 0; j >>= 1) {
+            for (int i = threadIdx.x; i < n / 2; i += blockDim.x) {
+                const int x = ((i & ~(j - 1)) << 1) | (i & (j - 1)), y = x | j;
+                const unsigned long long p = key[x], q = key[y];
+                if ((p > q) == ((x & size) == 0)) { key[x] = q; key[y] = p; }
+            }
+            __syncthreads();
+        }
+}
+
+}  // namespace trim

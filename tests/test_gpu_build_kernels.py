@@ -125,3 +125,21 @@ def test_gamma_rank(T, S, Q, d, M, p):
     want = (1.0 - cos).sort(dim=1).values[:, Q - m]
     np.testing.assert_allclose(each.cpu().numpy(), want.cpu().numpy(), atol=2e-5)
     assert gamma.item() == max(0.0, each.min().item())
+
+
+# one query to more than a tile of them; lists that leave tiles and columns unfilled; ties; the nearest lists all
+# in one column of the selection (8192 lists)
+@pytest.mark.parametrize("nq,nlist,d,nprobe", ((1, 64, 4, 2), (1, 1000, 128, 32), (2, 65, 100, 64), (5, 300, 1536, 33),
+                                              (9, 4097, 128, 64), (67, 1024, 384, 64), (3, 8192, 96, 32), (4, 8192, 32, 50)))
+def test_probe_of_few_queries(T, oracle, nq, nlist, d, nprobe):
+    import torch
+    assert T.lib().trim_ivf_probe_workspace_bytes(nq, d, nlist, nprobe) > 0
+    rng = np.random.default_rng(nlist + d)
+    cent = rng.integers(-3, 4, (nlist, d)).astype(np.float32)
+    q = rng.integers(-3, 4, (nq, d)).astype(np.float32)
+    if nlist == 8192:
+        cent[::64] = q[0] + rng.integers(0, 2, (128, d)).astype(np.float32)
+    cent[nlist // 2] = cent[3]
+    want = oracle.ivf_probe(q, cent, nprobe)
+    got = T.trim_ivf_probe(torch.from_numpy(q).cuda(), torch.from_numpy(cent).cuda(), nprobe).cpu().numpy()
+    np.testing.assert_array_equal(got, want)

@@ -110,6 +110,50 @@ def test_passes_equal_the_single_kernel(T, case):
         np.testing.assert_array_equal(got["ids"].cpu().numpy(), want["ids"].cpu().numpy())
 
 
+# few queries (bounds by many workgroups, one to settle): one query; first batches measured beside the bounds and not
+# (the three largest); codes of every width; table phases; more results than candidates
+FEW = [
+    (3000, 128, 32, 8, 12, 8, 5, 10, 256, 0.4, 2.0, 0.0),
+    (60000, 64, 16, 8, 40, 67, 19, 10, 64, 0.0, 1.0, 0.0),
+    (25000, 100, 20, 8, 0, 9, 0, 100, 1, 0.7, 1.0, 3.0),
+    (70000, 256, 64, 8, 0, 11, 0, 10, 1024, 0.2, 0.3, 0.0),
+    (20000, 768, 96, 8, 33, 30, 9, 10, 1024, 0.2, 0.3, 10.0),
+    (9000, 1536, 192, 8, 12, 8, 6, 64, 1000, 0.7, 0.1, 0.0),
+    (9000, 512, 32, 8, 16, 100, 16, 300, 3796, 1.5, 0.5, 0.0),
+    (6000, 256, 4, 8, 10, 100, 4, 5, 64, 0.3, 0.5, 0.0),
+    (10000, 256, 128, 4, 24, 60, 8, 10, 256, 0.4, 0.5, 0.0),
+    (2000, 128, 64, 4, 10, 9, 3, 1000, 512, 0.6, 0.5, 0.0),
+    (3000, 96, 12, 8, 300, 9, 2, 64, 100, 0.3, 0.5, 0.0),
+]
+
+
+@pytest.mark.parametrize("case", FEW, ids=lambda c: "-".join(map(str, c)))
+def test_few_queries_equal_the_single_kernel(T, case):
+    import torch
+    n, d, M, bits, nlist, nq, nprobe, k, batch, gamma, spread, offset = case
+    ix, queries, probes = built(T, n, d, M, bits, nlist, nq, nprobe, spread, offset, n + d)
+    cand, _ = ix._cand(probes)
+    view = ix._view()
+    for count in (nq, 1):
+        q = queries[:count].contiguous()
+        pr = None if probes is None else probes[:count].contiguous()
+        assert T.lib().trim_knn_workspace_bytes(C.byref(view), count, C.byref(cand) if cand is not None else None, k, batch) > 0
+        order = torch.randperm(count, device="cuda").to(torch.int32)
+        if count > 2:
+            order[2] = count + 5
+        named = np.array(sorted(set(range(count)) & set(order.tolist())))
+        lut = (T.trim_build_lut if bits == 8 else T.trim_fs_build_lut)(q, ix.codebooks) * 0.9
+        for o, table in ((None, None), (order, lut)):
+            want = single_kernel(T, ix, q, k, gamma, batch, pr, o, table)
+            out = (torch.full((count, k), -7, dtype=torch.int32, device="cuda"), torch.full((count, k), -7.0, device="cuda"))
+            got = T.trim_search_knn(ix, q, k, gamma, batch, probes=pr, lut=table, want_mask=True, out=out, query_order=o)
+            rows = np.arange(count) if o is None else named
+            for name in ("n_scanned", "n_exact", "mask"):
+                np.testing.assert_array_equal(got[name].cpu().numpy()[rows], want[name].cpu().numpy()[rows], err_msg=name)
+            for name in ("ids", "d2"):
+                np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
+
+
 def single_range(T, ix, q, radius, gamma, probes, order, lut):
     import torch
     nq = q.shape[0]
