@@ -288,6 +288,16 @@ int fill_u32(uint32_t *p, size_t count, uint32_t v, hipStream_t st) {
     return TRIM_OK;
 }
 
+int zero_areas(const ZeroAreas &z, hipStream_t st) {
+    if (z.count > ZeroAreas::kMost) return TRIM_INTERNAL;
+    size_t most = 0;
+    for (int i = 0; i < z.count; ++i) most = std::max(most, z.words[i]);
+    if (most == 0) return TRIM_OK;
+    hipLaunchKernelGGL(zero_areas_kernel, dim3((unsigned)std::min<size_t>((most + 255) / 256, 4096)), dim3(256), 0, st, z);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+
 // Clusters per workgroup of the k-means update: as many as 32 (every workgroup reads all the
 // assignments), fewer until there are two workgroups per CU or one cluster is left, and never
 // more than 48 KB of float64 sums.
@@ -298,8 +308,7 @@ int launch_kmeans_update(const float *x, int64_t ns, int d, int dim, const void 
     int lg = kUpdMaxLog2;
     while (lg > 0 && ((int64_t)((K + (1 << lg) - 1) >> lg) * ny * nz < 512 || ((size_t)cols << lg) * 8 > 48 * 1024)) --lg;
     const size_t lds = kmeans_update_lds(lg, cols);
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kmeans_update_kernel<ABYTES>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(kmeans_update_kernel<ABYTES>), lds));
     hipLaunchKernelGGL(kmeans_update_kernel<ABYTES>, dim3((unsigned)((K + (1 << lg) - 1) >> lg), (unsigned)ny, (unsigned)nz),
                        dim3(kUpdThreads), lds, st, x, ns, (int64_t)d, dim, assign, astride, K, lg, cent);
     HIP_TRY(hipGetLastError());
@@ -322,7 +331,7 @@ int launch_encode(const float *base, int64_t n, int d, const float *codebooks, i
         const int64_t split = std::min<int64_t>(M / 4, (768 + blocks - 1) / blocks);
         jper = (int)((M / 4 + split - 1) / split) * 4;
     }
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), lds));
     hipLaunchKernelGGL(fn, dim3((unsigned)blocks, (unsigned)((M + jper - 1) / jper)), dim3(kEncThreads), lds, st, base, n, d,
                        codebooks, M, jper, codes, dlx);
     if (jper < M && dlx)
@@ -537,16 +546,15 @@ void fill_filter(FilterArgs &f, InvertArgs &v, const trim_index_view *ix, const 
     f.q16_rows = reinterpret_cast<_Float16 *>(ws + L.off_q16r);
     f.qpar = reinterpret_cast<float *>(ws + L.off_qpar);
 }
-// The inverted probe lists and the 16-bit operands of the queries [slot0, slot0 + nslots).
-int prepare_filter(FilterArgs &f, InvertArgs &v, int64_t slot0, int64_t nslots, hipStream_t st) {
+// The inverted probe lists and the 16-bit operands of the queries [slot0, slot0 + nslots); z: what else is to be cleared.
+int prepare_filter(FilterArgs &f, InvertArgs &v, int64_t slot0, int64_t nslots, ZeroAreas z, hipStream_t st) {
     int rc;
     f.slot0 = v.slot0 = slot0;
     f.nslots = v.nslots = nslots;
-    if (v.cnt) {
-        if ((rc = fill_u32(reinterpret_cast<uint32_t *>(v.cnt), (size_t)v.nlist, 0u, st))) return rc;
-        if ((rc = launch_invert(v, st))) return rc;
-    }
-    if ((rc = fill_u32(f.max_bits, 1, 0u, st))) return rc;
+    if (v.cnt) z.add(v.cnt, (size_t)v.nlist);
+    z.add(f.max_bits, 1);
+    if ((rc = zero_areas(z, st))) return rc;
+    if (v.cnt && (rc = launch_invert(v, st))) return rc;
     return launch_filter_operands(f, st);
 }
 
@@ -601,8 +609,9 @@ int knn_in_passes(const trim_index_view *ix, const KnnLayout &L, const SearchArg
         m.slot0 = y.slot0 = s0;
         m.nslots = ns;
         int rc;
-        if ((rc = prepare_filter(f, v, s0, ns, st))) return rc;
-        if ((rc = fill_u32(m.possible, (size_t)ns * L.words, 0u, st))) return rc;
+        ZeroAreas z;
+        z.add(m.possible, (size_t)ns * L.words);
+        if ((rc = prepare_filter(f, v, s0, ns, z, st))) return rc;
         // The seed and the first batch (no threshold yet), then everything else against the
         // threshold that they leave.  Where that is no threshold to speak of yet (short first batches;
         // candidates in no particular order), eight times as many candidates from pass to pass.
@@ -738,8 +747,7 @@ int range_fill(const SearchArgs &a, const RangeLayout &L, unsigned char *ws, int
     f.off_segp = (uint32_t)off; off += up16((size_t)(nsegs + 1) * 4);
     f.off_segd = (uint32_t)off; off += up16((size_t)nsegs * 4);
     f.off_list = (uint32_t)off; off += 2048 * 4;
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(range_fill_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)off));
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(range_fill_kernel), off));
     hipLaunchKernelGGL(range_fill_kernel, dim3((unsigned)a.nq, (unsigned)L.nsplit), dim3(256), off, st, f);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
@@ -791,11 +799,13 @@ int range_search(const trim_index_view *index, const float *queries, int64_t nq,
     int64_t *cbase = reinterpret_cast<int64_t *>(ws + L.off_cbase);
     float *rd2 = reinterpret_cast<float *>(ws + L.off_d2);
 
-    if ((rc = fill_u32(rmask, (size_t)nq * L.rmask_words, 0u, st))) return rc;
-    if (survivor_mask && (rc = fill_u32(survivor_mask, (size_t)nq * mask_words, 0u, st))) return rc;
-    if (stats && stats->n_exact && (rc = fill_u32(reinterpret_cast<uint32_t *>(stats->n_exact), (size_t)nq, 0u, st)))
-        return rc;
-    if (stats && stats->work && (rc = fill_u32(stats->work, (size_t)nq * kWorkCounters, 0u, st))) return rc;
+    ZeroAreas z;
+    z.add(rmask, (size_t)nq * L.rmask_words);
+    z.add(survivor_mask, (size_t)nq * mask_words);
+    if (stats) {
+        z.add(stats->n_exact, (size_t)nq);
+        z.add(stats->work, (size_t)nq * kWorkCounters);
+    }
 
     SearchArgs a{};
     fill_common(a, index, queries, lut, cand, gamma, stats, survivor_mask, mask_words, pl);
@@ -805,8 +815,6 @@ int range_search(const trim_index_view *index, const float *queries, int64_t nq,
     a.result_mask = rmask; a.rmask_words = L.rmask_words; a.chunk_counts = counts;
     a.result_d2 = rd2;
     a.order = query_order;
-    // a query that the order does not name is not searched: its counts must read zero
-    if (query_order && (rc = fill_u32(reinterpret_cast<uint32_t *>(counts), (size_t)nq * L.nsplit, 0u, st))) return rc;
     if (a.max_cand > max_cand) a.max_cand = (int32_t)max_cand;
 
     a.nq = nq;
@@ -817,8 +825,8 @@ int range_search(const trim_index_view *index, const float *queries, int64_t nq,
         replay_lds(index->d, 1, a.nseg) <= kLdsBytes) {
         unsigned char *sc = static_cast<unsigned char *>(scratch);
         // (rows of the work space by query number; a query that the order does not name has no candidates)
-        if (query_order && (rc = fill_u32(reinterpret_cast<uint32_t *>(sc), (size_t)nq, 0u, st))) return rc;
-        if (!query_order && (rc = fill_u32(reinterpret_cast<uint32_t *>(counts), (size_t)nq * L.nsplit, 0u, st))) return rc;
+        if (query_order) z.add(sc, (size_t)nq);
+        z.add(counts, (size_t)nq * L.nsplit);
         InvertArgs v{};
         FilterArgs fa{};
         fill_filter(fa, v, index, a, filter_layout(index, nq, cand, up256((size_t)nq * 4)), sc);
@@ -835,7 +843,7 @@ int range_search(const trim_index_view *index, const float *queries, int64_t nq,
         y.probes = a.probes; y.nlist = a.nlist; y.nseg = a.nseg; y.max_cand = a.max_cand; y.order = query_order;
         y.totals = m.totals; y.bits = rmask; y.d2_out = rd2; y.words = L.rmask_words; y.radius2 = a.radius2;
         y.chunk = L.chunk; y.nchunk = L.nsplit; y.counts = counts;
-        if ((rc = prepare_filter(fa, v, 0, nq, st))) return rc;
+        if ((rc = prepare_filter(fa, v, 0, nq, z, st))) return rc;
         // candidates per query: the filter needs them before the finish pass writes them
         if ((rc = launch_totals(m, st))) return rc;
         if ((rc = launch_filter(fa, st))) return rc;
@@ -843,6 +851,9 @@ int range_search(const trim_index_view *index, const float *queries, int64_t nq,
         if ((rc = launch_measure(fa, st))) return rc;
         if ((rc = launch_range_exact(y, nq, L.nsplit, st))) return rc;
     } else {
+        // a query that the order does not name is not searched: its counts must read zero
+        if (query_order) z.add(counts, (size_t)nq * L.nsplit);
+        if ((rc = zero_areas(z, st))) return rc;
         const int64_t slots = (nq + kXcds - 1) / kXcds * kXcds;
         if (slots * pl.threads >= (int64_t(1) << 32)) return TRIM_INVALID_ARG;  // threads per launch
         if ((rc = launch_search(true, is_fs(index), a, pl, dim3((unsigned)slots, (unsigned)L.nsplit), st))) return rc;
@@ -1043,7 +1054,7 @@ int trim_estimate_gamma(const trim_index_view *index, const int32_t *sample_rows
     a.rank = (int32_t)(Q - m);
     a.gamma_x = gamma_x_out; a.gamma_bits = reinterpret_cast<uint32_t *>(gamma_out);
     void (*fn)(GammaArgs) = per == 2 ? gamma_kernel<2> : gamma_kernel<1>;
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), lds));
     hipLaunchKernelGGL(fn, dim3((unsigned)((S + per - 1) / per)), dim3(kGammaThreads), lds, st, a);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
@@ -1074,8 +1085,7 @@ int trim_estimate_gamma_normal(const trim_index_view *index, const int32_t *samp
     a.triples = work; a.n = index->n; a.d = index->d; a.M = index->M; a.Q = Q; a.npow2 = npow2;
     a.grid = grid; a.one_minus_p = 1.0 - (double)p;
     a.gamma_x = gamma_x_out; a.gamma_bits = reinterpret_cast<uint32_t *>(gamma_out);
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(gamma_normal_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(gamma_normal_kernel), lds));
     hipLaunchKernelGGL(gamma_normal_kernel, dim3((unsigned)S), dim3(256), lds, st, a);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
@@ -1281,7 +1291,7 @@ int trim_ivf_probe_ws(const float *queries, int64_t nq, int32_t d, const float *
     void (*fn)(const float *, int64_t, int, const float *, int, uint32_t *) =
         qt == 8 ? probe_distance_kernel<8> : qt == 4 ? probe_distance_kernel<4> : qt == 2 ? probe_distance_kernel<2> : probe_distance_kernel<1>;
     const size_t lds = (size_t)qt * d * 4;
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), lds));
     hipLaunchKernelGGL(fn, dim3((unsigned)((nlist + rows - 1) / rows), (unsigned)((nq + qt - 1) / qt)), dim3(kProbeThreads), lds, st,
                        queries, nq, d, centroids, nlist, dist);
     HIP_TRY(hipGetLastError());
@@ -1314,10 +1324,8 @@ int trim_ivf_probe(const float *queries, int64_t nq, int32_t d, const float *cen
     // workgroups would do it, and below 64 lists a 256-wide tile is mostly padding.
     if (nprobe == 1 && nq >= 4096 && nlist >= 64 && d <= kAsgMaxD && aligned16(queries)) {
         const size_t lds1 = assign_lds(d), lds2 = (size_t)8 * d * 4;
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(assign_mfma_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1));
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(assign_fix_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2));
+        HIP_TRY(allow_lds(reinterpret_cast<const void *>(assign_mfma_kernel), lds1));
+        HIP_TRY(allow_lds(reinterpret_cast<const void *>(assign_fix_kernel), lds2));
         hipLaunchKernelGGL(assign_mfma_kernel, dim3((unsigned)((nq + kAsgTile - 1) / kAsgTile)), dim3(kAsgThreads), lds1, st,
                            queries, nq, d, centroids, nlist, probes_out);
         HIP_TRY(hipGetLastError());
@@ -1330,8 +1338,7 @@ int trim_ivf_probe(const float *queries, int64_t nq, int32_t d, const float *cen
     }
     void (*fn)(const float *, int64_t, int, const float *, int, int, int, int32_t *) =
         qt == 8 ? ivf_probe_kernel<8> : qt == 4 ? ivf_probe_kernel<4> : qt == 2 ? ivf_probe_kernel<2> : ivf_probe_kernel<1>;
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), lds));
     // a launch holds fewer than 2^32 threads: walk the queries in slabs
     const int64_t slab = (int64_t)qt * (1 << 22);
     for (int64_t q0 = 0; q0 < nq; q0 += slab) {
@@ -1352,8 +1359,7 @@ int trim_query_order(const int32_t *probes, int64_t nq, int32_t nprobe, int32_t 
     const int nbucket = nlist < 32768 ? nlist : 32768;
     const size_t lds = (size_t)nbucket * 4;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(query_order_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(query_order_kernel), lds));
     hipLaunchKernelGGL(query_order_kernel, dim3(1), dim3(1024), lds, st, probes, nq, nprobe, nbucket,
                        order_out);
     HIP_TRY(hipGetLastError());

@@ -13,6 +13,26 @@ __global__ void fill_u32_kernel(uint32_t *p, size_t count, uint32_t v) {
         p[i] = v;
 }
 
+// Several areas cleared by one launch (a launch of its own for each costs a small search 3 to 5 us).
+struct ZeroAreas {
+    static constexpr int kMost = 8;
+    uint32_t *at[kMost];
+    size_t words[kMost];
+    int count = 0;
+    void add(void *p, size_t n) {
+        if (!p || n == 0) return;
+        if (count < kMost) {
+            at[count] = static_cast<uint32_t *>(p);
+            words[count] = n;
+        }
+        ++count;             // (more than there is room for: zero_areas refuses)
+    }
+};
+__global__ __launch_bounds__(256) void zero_areas_kernel(const ZeroAreas z) {
+    for (int i = 0; i < z.count; ++i)
+        for (size_t w = (size_t)blockIdx.x * 256 + threadIdx.x; w < z.words[i]; w += (size_t)gridDim.x * 256) z.at[i][w] = 0u;
+}
+
 // ---- ceilings of the machine for the two resources the scan leans on (measurement aids) ----
 // Streaming read: every 16-byte piece of the buffer is read once, four loads in flight per
 // thread; the xor of everything read goes to sink[block] so that the loads cannot be dropped.
@@ -1226,24 +1246,28 @@ __global__ __launch_bounds__(1024) void range_offsets_kernel(const int32_t *__re
                                                              int64_t *__restrict__ chunk_base,
                                                              int64_t *__restrict__ out_offsets,
                                                              int64_t *__restrict__ required) {
-    __shared__ int64_t part[1024];
+    __shared__ long long part[16];
     const int64_t total_items = nq * nsplit;
-    const int T = blockDim.x;
+    const int T = 1024, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t per = (total_items + T - 1) / T;
     const int64_t lo = (int64_t)threadIdx.x * per;
     const int64_t hi = lo + per < total_items ? lo + per : total_items;
     int64_t s = 0;
     for (int64_t i = lo; i < hi; ++i) s += counts[i];
-    part[threadIdx.x] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int64_t run = 0;
-        for (int t = 0; t < T; ++t) { const int64_t v = part[t]; part[t] = run; run += v; }
-        out_offsets[nq] = run;
-        if (required) *required = run;
+    long long incl = s;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const long long v = __shfl_up(incl, off);
+        if (lane >= off) incl += v;
     }
+    if (lane == 63) part[wave] = incl;
     __syncthreads();
-    int64_t run = part[threadIdx.x];
+    int64_t run = incl - s;
+    for (int w = 0; w < wave; ++w) run += part[w];
+    if (threadIdx.x == 1023) {
+        out_offsets[nq] = run + s;
+        if (required) *required = run + s;
+    }
     for (int64_t i = lo; i < hi; ++i) {
         chunk_base[i] = run;
         if (i % nsplit == 0) out_offsets[i / nsplit] = run;

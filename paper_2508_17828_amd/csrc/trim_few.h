@@ -89,7 +89,7 @@ __global__ __launch_bounds__(kBoundThreads) void bound_kernel(const FewArgs a) {
 }
 
 // One workgroup per query.  R after the first batch is its k least distances: a histogram of the distances' bit
-// patterns leaves little more than k of them to sort.  Then stretches of candidates, each as long as what
+// patterns leaves little more than k of them to sort.  Then stretches of candidates, each about as long as what
 // has been seen (4,096 or 16,384; half of that with wide R), listed against the threshold at their start, measured, and replayed
 // by the first wave.
 template <int E>
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
     __syncthreads();
     // ---- the rest ----
     for (int w0 = fb; w0 < total;) {
-        const int V = w0 < 16384 ? 4 : 16, base = w0 & ~3;
+        const int V = a.nseg == 0 && w0 < 16384 ? 4 : 16, base = w0 & ~3;
         const int w1 = total - base < V * T ? total : base + V * T;
         // (the batch that the last stretch ended in keeps the threshold that it began with)
         const float tau = s_tau, tau_b = __builtin_fmaxf(tau, s_tau_f);

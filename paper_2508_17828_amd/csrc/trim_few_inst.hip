@@ -63,7 +63,7 @@ int launch_bound(FewArgs a, bool fs, int nsplit, hipStream_t st) {
         seen.store(fa.sharedSizeBytes == 0 ? 1 : -1, std::memory_order_release);
     }
     if (seen.load(std::memory_order_acquire) < 0) return TRIM_INTERNAL;
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), lds));
     hipLaunchKernelGGL(fn, dim3((unsigned)nsplit, (unsigned)a.nq), dim3(kBoundThreads), lds, st, a);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
@@ -73,7 +73,7 @@ int launch_settle(FewArgs a, hipStream_t st) {
     const size_t lds = settle_carve(a);
     const int E = result_slots(a.k);
     void (*fn)(const FewArgs) = E == 1 ? settle_kernel<1> : E == 2 ? settle_kernel<2> : E == 4 ? settle_kernel<4> : settle_kernel<16>;
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), lds));
     hipLaunchKernelGGL(fn, dim3((unsigned)a.nq), dim3(settle_threads(E)), lds, st, a);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;

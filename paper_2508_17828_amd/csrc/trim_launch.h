@@ -34,6 +34,11 @@ int hip_fail(hipError_t e);
 
 constexpr size_t kLdsBytes = 160 * 1024;  // LDS per workgroup on gfx950
 
+// Lets a kernel be launched with `bytes` of dynamic LDS (up to 64 KB it may be without asking).
+inline hipError_t allow_lds(const void *fn, size_t bytes) {
+    return bytes <= 65536 ? hipSuccess : hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
 // launch_search_<mode>_e<result entries per lane>_c<bits per code>: enqueue the matching
 // instance of search_kernel (with or without the work counters, by SearchArgs::work).
 #define TRIM_DECLARE_LAUNCH(name) \

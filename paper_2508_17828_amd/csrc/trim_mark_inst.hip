@@ -32,7 +32,7 @@ int launch_finish(const FinishArgs &a, int vec, bool fs, int threads, size_t lds
         seen.store(fa.sharedSizeBytes == 0 ? 1 : -1, std::memory_order_release);
     }
     if (seen.load(std::memory_order_acquire) < 0) return TRIM_INTERNAL;
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), lds));
     hipLaunchKernelGGL(fn, dim3((unsigned)slots), dim3(threads), lds, st, a);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
@@ -105,7 +105,7 @@ int launch_range_exact(ReplayArgs a, int64_t nslots, int nchunk, hipStream_t st)
     a.k = 1;
     replay_carve(a);
     const size_t off = a.off_g;          // (what follows is the replay's)
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(range_exact_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)off));
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(range_exact_kernel), off));
     hipLaunchKernelGGL(range_exact_kernel, dim3((unsigned)nslots, (unsigned)nchunk), dim3(kReplayThreads), off, st, a);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
@@ -115,7 +115,7 @@ int launch_replay(ReplayArgs a, int64_t nslots, hipStream_t st) {
     const int E = result_slots(a.k);
     const size_t off = replay_carve(a);
     void (*fn)(const ReplayArgs) = E == 1 ? replay_kernel<1> : E == 2 ? replay_kernel<2> : E == 4 ? replay_kernel<4> : replay_kernel<16>;
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)off));
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), off));
     hipLaunchKernelGGL(fn, dim3((unsigned)nslots), dim3(kReplayThreads), off, st, a);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;

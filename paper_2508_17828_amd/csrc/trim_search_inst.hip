@@ -57,8 +57,7 @@ int launch_instance(const SearchArgs &a, const Plan &pl, dim3 grid, hipStream_t 
         seen.store(fa.sharedSizeBytes == 0 ? 1 : -1, std::memory_order_release);
     }
     if (seen.load(std::memory_order_acquire) < 0) return TRIM_INTERNAL;
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds));
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), pl.lds));
     hipLaunchKernelGGL(fn, grid, dim3(pl.threads), pl.lds, st, a);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
