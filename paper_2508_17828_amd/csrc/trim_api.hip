@@ -663,7 +663,7 @@ FewLayout few_layout(const trim_index_view *ix, int64_t nq, const trim_candidate
     if ((size_t)stride > kFewBytes || g_bytes > kFewBytes || mc > 0x40000000 || !few_fits(ix->d, code_bytes(ix), is_fs(ix), k, cand ? cand->nprobe : 0)) return L;
     L.stride = stride;
     // The seed and the first batch measured beside the bounds, survivors or not, while that is little to read.
-    L.measure_first = (size_t)nq * (k + batch) * ix->d * 4 <= (size_t(32) << 20);
+    L.measure_first = (size_t)nq * (k + batch) * ix->d * 4 <= (size_t(128) << 20);
     L.off_g = up256((size_t)nq * 4);
     L.off_d2 = L.off_g + up256(g_bytes);
     L.total = L.off_d2 + (L.measure_first ? up256((size_t)nq * (k + batch) * 4) : 0);

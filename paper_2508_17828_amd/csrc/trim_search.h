@@ -207,12 +207,92 @@ struct ResultRegs {
         t_d2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(vd), kl));  // kl is uniform
         t_id = __builtin_amdgcn_readlane(vi, kl);
     }
+    // An entry as one number that orders like hit_less (d2 >= 0; empty entries last).
+    static __device__ __forceinline__ unsigned long long key_of(float d2, int32_t id) {
+        return ((unsigned long long)__float_as_uint(d2) << 32) | ((uint32_t)id ^ 0x80000000u);
+    }
+    template <int BIT>
+    static __device__ __forceinline__ unsigned long long key_xor(unsigned long long v) {
+        uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+        if constexpr (BIT == 32) {
+            lo = (uint32_t)__shfl_xor((int)lo, 32);
+            hi = (uint32_t)__shfl_xor((int)hi, 32);
+        } else {
+            lo = __float_as_uint(lane_xor<BIT>(__uint_as_float(lo)));
+            hi = __float_as_uint(lane_xor<BIT>(__uint_as_float(hi)));
+        }
+        return ((unsigned long long)hi << 32) | lo;
+    }
+    // One compare-exchange of a bitonic network with lane ^ BIT.
+    template <int BIT>
+    static __device__ __forceinline__ void order_step(unsigned long long &v, bool up, int lane) {
+        const unsigned long long o = key_xor<BIT>(v);
+        if (((lane & BIT) == 0) == up ? o < v : o > v) v = o;
+    }
+    template <int SIZE, int BIT>
+    static __device__ __forceinline__ void order_run(unsigned long long &v, int lane) {
+        order_step<BIT>(v, (lane & SIZE) == 0, lane);
+        if constexpr (BIT > 1) order_run<SIZE, BIT / 2>(v, lane);
+    }
+    template <int BIT>
+    static __device__ __forceinline__ void merge_run(unsigned long long (&v)[E], int lane) {
+#pragma unroll
+        for (int s = 0; s < E; ++s) order_step<BIT>(v[s], true, lane);
+        if constexpr (BIT > 1) merge_run<BIT / 2>(v, lane);
+    }
+    // Many items at once: sorted across the lanes, set against the end of R in reverse, and what is
+    // the smaller of each pair put back in order (a bitonic merge): 21 + 6 steps whatever their number.
+    __device__ __forceinline__ void merge_items(bool on, float d2, int32_t id) {
+        unsigned long long x = on ? key_of(d2, id) : ~0ull;
+        order_run<2, 1>(x, lane);
+        order_run<4, 2>(x, lane);
+        order_run<8, 4>(x, lane);
+        order_run<16, 8>(x, lane);
+        order_run<32, 16>(x, lane);
+        order_run<64, 32>(x, lane);
+        unsigned long long v[E];
+#pragma unroll
+        for (int s = 0; s < E; ++s) {
+            v[s] = key_of(r_d2[s], r_id[s]);
+            const int j = kWave * E - 1 - (lane * E + s);         // item set against entry lane E + s
+            const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)x, j & 63), hi = (uint32_t)__shfl((int)(uint32_t)(x >> 32), j & 63);
+            const unsigned long long o = ((unsigned long long)hi << 32) | lo;
+            if (j < kWave && o < v[s]) v[s] = o;
+        }
+        merge_run<32>(v, lane);
+#pragma unroll
+        for (int h = E / 2; h > 0; h >>= 1)
+#pragma unroll
+            for (int s = 0; s < E; ++s)
+                if ((s & h) == 0) {
+                    const unsigned long long p = v[s], q = v[s | h];
+                    v[s] = p < q ? p : q;
+                    v[s | h] = p < q ? q : p;
+                }
+#pragma unroll
+        for (int s = 0; s < E; ++s) {
+            const bool in = lane * E + s < k;
+            r_d2[s] = in ? __uint_as_float((uint32_t)(v[s] >> 32)) : __builtin_inff();
+            r_id[s] = in ? (int32_t)((uint32_t)v[s] ^ 0x80000000u) : kEmptyId;
+        }
+        load_kth();
+    }
     // Insert the lanes' items (one per lane with `pending` set) that beat the k-th entry, one at
-    // a time: an insertion is a ballot (rank), one cross-lane shift and a few selects.
+    // a time: an insertion is a ballot (rank), one cross-lane shift and a few selects.  Many of them
+    // (kMergeFrom, where a merge costs what that many insertions do) are merged instead.  One entry per
+    // lane: few enough come at a time, and the kernels with 80 registers were 4% slower with the code in
+    // them; result sets beyond 256: registers.
+    static constexpr int kMergeFrom = 8;
     __device__ __forceinline__ void insert_pending(bool pending, float d2, int32_t id) {
         for (;;) {
             const unsigned long long m = __ballot(pending && hit_less(d2, id, t_d2, t_id));
             if (m == 0) break;
+            if constexpr (E == 2 || E == 4) {
+                if (__popcll(m) >= kMergeFrom) {
+                    merge_items(pending && hit_less(d2, id, t_d2, t_id), d2, id);
+                    break;
+                }
+            }
             const int src = __ffsll((long long)m) - 1;
             const float xd2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d2), src));
             const int32_t xid = __builtin_amdgcn_readlane(id, src);  // src is the same in all lanes
@@ -243,14 +323,16 @@ struct ResultRegs {
 // Merge the refined survivors of a batch into R and publish tau (the "result queue update"
 // of Section 4.2).  Executed by ONE whole wave.
 template <int E>
-__device__ __forceinline__ void merge_batch(const float *sd2, const int32_t *sid, int ns,
+__device__ __forceinline__ void merge_batch(float *sd2, int32_t *sid, int ns,
                                             float *rd2, int32_t *rid, Ctl *ctl, int k, int lane) {
     ResultRegs<E> R;
     R.load(rd2, rid, k, lane);
     // A long list (the first batch after the seed) is pre-filtered: lane l takes the minimum of
     // entries l, l+64, ...; the k-th smallest of these 64 minima (distinct entries) is an upper
     // bound on the k-th distance after the merge, so entries above it never enter R and skip
-    // the one-at-a-time insertion below.  (One entry per lane: result sets up to 64.)
+    // the insertion below.  Larger result sets: the same over 64 E columns, E per lane, their
+    // k-th least minimum found bit by bit, and whoever is left is moved together so that R takes 64 at a time.
+    // (R of 100 entries after a first batch of 1024: 60 us of single insertions before.)
     float cut = __builtin_inff();
     if constexpr (E == 1) {
         if (ns > 2 * kWave) {
@@ -267,6 +349,39 @@ __device__ __forceinline__ void merge_batch(const float *sd2, const int32_t *sid
             }
             cut = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cmin), k - 1));
         }
+    } else if (ns > 2 * kWave * E) {
+        uint32_t cmin[E];
+#pragma unroll
+        for (int s = 0; s < E; ++s) {
+            float m = __builtin_inff();
+            for (int i = s * kWave + lane; i < ns; i += kWave * E) m = __builtin_fminf(m, sd2[i]);
+            cmin[s] = __float_as_uint(m);
+        }
+        uint32_t at = 0;                     // the largest pattern with fewer than k minima below it
+#pragma unroll 1
+        for (int bit = 30; bit >= 0; --bit) {
+            const uint32_t mid = at | (1u << bit);
+            int below = 0;
+#pragma unroll
+            for (int s = 0; s < E; ++s) below += __popcll(__ballot(cmin[s] < mid));
+            if (below < k) at = mid;
+        }
+        cut = __uint_as_float(at);
+        int to = 0;
+        for (int i0 = 0; i0 < ns; i0 += kWave) {
+            const int i = i0 + lane;
+            const float d2 = i < ns ? sd2[i] : __builtin_inff();
+            const int32_t id = i < ns ? sid[i] : 0;
+            const bool on = i < ns && d2 <= cut;
+            const unsigned long long m = __ballot(on);
+            if (on) {
+                const int p = to + __popcll(m & ((1ull << lane) - 1ull));
+                sd2[p] = d2;
+                sid[p] = id;
+            }
+            to += __popcll(m);
+        }
+        ns = to;
     }
     for (int i0 = 0; i0 < ns; i0 += kWave) {
         const int i = i0 + lane;
