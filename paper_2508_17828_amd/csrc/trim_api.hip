@@ -646,8 +646,14 @@ bool probe_in_two(int64_t nq, int d, int nlist, int nprobe) {
            (size_t)nq * nlist <= size_t(1) << 26;
 }
 
-// Few queries: bound_kernel and settle_kernel (see trim_few.h).
-constexpr int64_t kFewQueries = 128;
+// Few queries: bound_kernel and settle_kernel (see trim_few.h).  They pay while the single kernel, a workgroup per
+// query, leaves CUs idle (up to 128 queries; 256 where it is slowed by results of more than one entry per lane), and
+// while the lookups of all candidates (it abandons most of them early) cost less than that: up to 500,000
+// per value of a row, since long rows are what its workgroups wait for.  Measured, single kernel / these
+// two: 1M x 128, 32 of 1024 lists, 1 / 64 / 96 queries: 74 / 44, 117 / 114, 120 / 145 us; 300000 x 768, 32 of 512, 128
+// queries: 548 / 490 us; 158482 x 960, no lists, 16 / 64 queries: 1564 / 991, 1550 / 1500 us.
+constexpr int64_t kFewQueries = 128, kFewQueriesWide = 256;
+constexpr double kFewLookups = 500000.0;
 constexpr size_t kFewBytes = size_t(1) << 30;
 struct FewLayout {
     int64_t stride;           // bounds per query (0: not this way)
@@ -657,7 +663,10 @@ struct FewLayout {
 FewLayout few_layout(const trim_index_view *ix, int64_t nq, const trim_candidates *cand, int k, int batch) {
     FewLayout L{};
     const int64_t mc = cand ? std::min<int64_t>(cand->max_candidates, (int64_t)cand->nprobe * ix->n) : ix->n;
-    if (nq <= 0 || nq > kFewQueries || mc <= 0 || k + batch > kSettleFirst || k < 1 || batch < 1) return L;
+    if (nq <= 0 || nq > (k > kWave ? kFewQueriesWide : kFewQueries) || mc <= 0 || k + batch > kSettleFirst || k < 1 || batch < 1) return L;
+    // (a query's share of the base set, lists as long as each other)
+    const double scanned = cand ? (double)ix->n * std::min(1.0, (double)cand->nprobe / cand->nlist) : (double)ix->n;
+    if ((double)nq * scanned * ix->M > kFewLookups * ix->d && nq > 1) return L;
     const int64_t stride = (mc + 15) / 16 * 16;
     const size_t g_bytes = (size_t)nq * stride * 4;
     if ((size_t)stride > kFewBytes || g_bytes > kFewBytes || mc > 0x40000000 || !few_fits(ix->d, code_bytes(ix), is_fs(ix), k, cand ? cand->nprobe : 0)) return L;

@@ -114,7 +114,7 @@ def test_passes_equal_the_single_kernel(T, case):
 # (the three largest); codes of every width; table phases; more results than candidates
 FEW = [
     (3000, 128, 32, 8, 12, 8, 5, 10, 256, 0.4, 2.0, 0.0),
-    (60000, 64, 16, 8, 40, 67, 19, 10, 64, 0.0, 1.0, 0.0),
+    (40000, 64, 16, 8, 40, 67, 19, 10, 64, 0.0, 1.0, 0.0),
     (25000, 100, 20, 8, 0, 9, 0, 100, 1, 0.7, 1.0, 3.0),
     (70000, 256, 64, 8, 0, 11, 0, 10, 1024, 0.2, 0.3, 0.0),
     (20000, 768, 96, 8, 33, 30, 9, 10, 1024, 0.2, 0.3, 10.0),
