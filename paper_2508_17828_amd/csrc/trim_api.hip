@@ -495,17 +495,20 @@ inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 // Work space of the filter and measure passes for `rows` queries (offsets from `at`; 0 bytes: shape without a filter).
 struct FilterLayout {
     int padded, kpad, kpad_rows;
-    size_t off_start, off_cnt, off_tasks, off_inv, off_mu, off_max, off_books, off_q16, off_q16r, off_qpar, end;
+    bool tables;              // distance tables beside (lut_tile_kernel)
+    size_t off_start, off_cnt, off_tasks, off_inv, off_mu, off_max, off_books, off_q16, off_q16r, off_qpar, off_bad, off_lut, end;
 };
+size_t table_bytes(const trim_index_view *ix) { return (size_t)ix->M * (is_fs(ix) ? kC4 : kC) * 4; }
 size_t filter_bytes_per_query(const trim_index_view *ix, const trim_candidates *cand) {
     const int padded = filter_padded(ix->d / ix->M, is_fs(ix));
-    return (size_t)(cand ? cand->nprobe : 0) * 8 + ((size_t)ix->M * padded + ix->d + 2 * kFltSlice) * 2 + 8;
+    return (size_t)(cand ? cand->nprobe : 0) * 8 + ((size_t)ix->M * padded + ix->d + 4 * kFltSlice) * 2 + 8 + 4 +
+           (lut_tiled(ix->d / ix->M, is_fs(ix)) ? table_bytes(ix) : 0);
 }
-FilterLayout filter_layout(const trim_index_view *ix, int64_t rows, const trim_candidates *cand, size_t at) {
+FilterLayout filter_layout(const trim_index_view *ix, int64_t rows, int64_t rows_all, const trim_candidates *cand, size_t at) {
     FilterLayout L{};
     L.padded = filter_padded(ix->d / ix->M, is_fs(ix));
-    L.kpad = (ix->M * L.padded + kFltSlice - 1) / kFltSlice * kFltSlice;
-    L.kpad_rows = (ix->d + kFltSlice - 1) / kFltSlice * kFltSlice;
+    L.kpad = (ix->M * L.padded + 2 * kFltSlice - 1) / (2 * kFltSlice) * (2 * kFltSlice);     // (slices come in pairs)
+    L.kpad_rows = (ix->d + 2 * kFltSlice - 1) / (2 * kFltSlice) * (2 * kFltSlice);
     size_t off = at;
     if (cand) {
         L.off_start = off; off += up256((size_t)(cand->nlist + 1) * 4);
@@ -520,6 +523,10 @@ FilterLayout filter_layout(const trim_index_view *ix, int64_t rows, const trim_c
     L.off_q16r = L.off_q16;
     if (ix->d / ix->M != L.padded) { L.off_q16r = off; off += up256((size_t)rows * L.kpad_rows * 2); }
     L.off_qpar = off;  off += up256((size_t)rows * 8);
+    L.off_bad = off;   off += up256((size_t)rows_all * 4);
+    // (tables of queries that are not taken in slabs: up to 2 GB of them)
+    L.tables = lut_tiled(ix->d / ix->M, is_fs(ix)) && rows * table_bytes(ix) <= kKnnSlabBytes / 4;
+    L.off_lut = off;   off += L.tables ? up256((size_t)rows * table_bytes(ix)) : 0;
     L.end = off;
     return L;
 }
@@ -536,7 +543,7 @@ void fill_filter(FilterArgs &f, InvertArgs &v, const trim_index_view *ix, const 
     }
     f.codes = a.codes; f.dlx = a.dlx; f.codebooks = a.codebooks; f.n = a.n; f.d = a.d; f.M = a.M; f.dsub = a.dsub;
     f.nsub = ix->M; f.ncent = is_fs(ix) ? kC4 : kC; f.queries = a.queries; f.nq = a.nq; f.order = a.order;
-    f.list_offsets = a.nseg > 0 ? a.list_offsets : nullptr; f.nlist = a.nlist;
+    f.list_offsets = a.nseg > 0 ? a.list_offsets : nullptr; f.nlist = a.nlist; f.nseg = a.nseg;
     f.inv_start = v.start; f.inv = v.inv; f.tasks = v.tasks; f.row_tasks = v.row_tasks;
     f.two_gamma = a.two_gamma; f.padded = L.padded; f.kpad = L.kpad; f.kpad_rows = L.kpad_rows; f.base = a.base;
     f.mu = reinterpret_cast<float *>(ws + L.off_mu);
@@ -558,6 +565,26 @@ int prepare_filter(FilterArgs &f, InvertArgs &v, int64_t slot0, int64_t nslots, 
     return launch_filter_operands(f, st);
 }
 
+// The tables of the finish pass, for the queries [slot0, slot0 + nslots): made here, or a caller's compared with the
+// centroids (by_query: rows of the work space are at the queries' numbers).  z must have cleared the `bad` words.
+int prepare_tables(FinishArgs &m, const trim_index_view *ix, const SearchArgs &a, const FilterLayout &L, unsigned char *ws, hipStream_t st) {
+    LutArgs t{};
+    t.queries = a.queries; t.nq = a.nq; t.d = a.d; t.codebooks = a.codebooks; t.nsub = ix->M; t.order = a.order;
+    t.slot0 = m.slot0; t.nslots = m.nslots;
+    if (a.lut) {
+        t.lut = const_cast<float *>(a.lut);
+        t.bad = reinterpret_cast<uint32_t *>(ws + L.off_bad);
+        m.bad = t.bad;
+        return launch_lut(t, a.dsub, is_fs(ix), true, st);
+    }
+    if (!L.tables) return TRIM_OK;
+    t.lut = reinterpret_cast<float *>(ws + L.off_lut);
+    t.by_slot = !m.by_query;
+    m.lut = t.lut;
+    m.lut_by_row = 1;
+    return launch_lut(t, a.dsub, is_fs(ix), false, st);
+}
+
 struct KnnLayout {
     int64_t words, slab;      // bit words per query, queries per slab (0: one kernel)
     FilterLayout f;
@@ -577,7 +604,7 @@ KnnLayout knn_layout(const trim_index_view *ix, int64_t nq, const trim_candidate
     L.off_possible = off; off += up256((size_t)L.slab * L.words * 4);
     L.off_g = off;        off += up256((size_t)L.slab * L.words * 32 * 4);
     L.off_d2 = off;       off += up256((size_t)L.slab * L.words * 32 * 4);
-    L.f = filter_layout(ix, L.slab, cand, off);
+    L.f = filter_layout(ix, L.slab, nq, cand, off);
     L.total = L.f.end;
     return L;
 }
@@ -611,7 +638,9 @@ int knn_in_passes(const trim_index_view *ix, const KnnLayout &L, const SearchArg
         int rc;
         ZeroAreas z;
         z.add(m.possible, (size_t)ns * L.words);
+        if (a.lut && s0 == 0) z.add(ws + L.f.off_bad, (size_t)a.nq);
         if ((rc = prepare_filter(f, v, s0, ns, z, st))) return rc;
+        if ((rc = prepare_tables(m, ix, a, L.f, ws, st))) return rc;
         // The seed and the first batch (no threshold yet), then everything else against the
         // threshold that they leave.  Where that is no threshold to speak of yet (short first batches;
         // candidates in no particular order), eight times as many candidates from pass to pass.
@@ -730,7 +759,7 @@ int search_knn(const trim_index_view *index, const float *queries, int64_t nq, c
         if (F.stride > 0 && workspace_bytes >= F.total) return knn_few(index, F, a, static_cast<unsigned char *>(workspace), st);
         const KnnLayout L = knn_layout(index, nq, cand);
         FinishPlan fp;
-        if (L.slab > 0 && workspace_bytes >= L.total && index->codebooks &&
+        if (L.slab > 0 && workspace_bytes >= L.total && index->codebooks && (!lut || lut_tiled(a.dsub, is_fs(index))) &&
             make_finish_plan(index->d, a.M, is_fs(index), a.nseg, &fp) && replay_lds(index->d, k, a.nseg) <= kLdsBytes)
             return knn_in_passes(index, L, a, fp, static_cast<unsigned char *>(workspace), st);
     }
@@ -765,7 +794,7 @@ int range_fill(const SearchArgs &a, const RangeLayout &L, unsigned char *ws, int
 // Scratch of a range search in passes: totals, then the filter's operands.  0: such a search runs as one kernel.
 size_t range_scratch_bytes(const trim_index_view *ix, int64_t nq, const trim_candidates *cand) {
     if (!worth_passes(ix, nq, cand)) return 0;
-    return filter_layout(ix, nq, cand, up256((size_t)nq * 4)).end;
+    return filter_layout(ix, nq, nq, cand, up256((size_t)nq * 4)).end;
 }
 
 // The range search behind all entry points: `workspace` is the caller's buffer or this
@@ -830,7 +859,7 @@ int range_search(const trim_index_view *index, const float *queries, int64_t nq,
     FinishPlan fpl;
     const size_t want = range_scratch_bytes(index, nq, cand);
     if (scratch && want > 0 && scratch_bytes >= want && !a.work && (reinterpret_cast<uintptr_t>(scratch) & 255u) == 0 &&
-        aligned16(queries) && index->codebooks && make_finish_plan(index->d, a.M, is_fs(index), a.nseg, &fpl) &&
+        aligned16(queries) && index->codebooks && (!lut || lut_tiled(a.dsub, is_fs(index))) && make_finish_plan(index->d, a.M, is_fs(index), a.nseg, &fpl) &&
         replay_lds(index->d, 1, a.nseg) <= kLdsBytes) {
         unsigned char *sc = static_cast<unsigned char *>(scratch);
         // (rows of the work space by query number; a query that the order does not name has no candidates)
@@ -838,7 +867,8 @@ int range_search(const trim_index_view *index, const float *queries, int64_t nq,
         z.add(counts, (size_t)nq * L.nsplit);
         InvertArgs v{};
         FilterArgs fa{};
-        fill_filter(fa, v, index, a, filter_layout(index, nq, cand, up256((size_t)nq * 4)), sc);
+        const FilterLayout FL = filter_layout(index, nq, nq, cand, up256((size_t)nq * 4));
+        fill_filter(fa, v, index, a, FL, sc);
         fa.by_query = v.by_query = 1;
         fa.range = 1; fa.radius2 = a.radius2; fa.lo = 0; fa.hi = a.max_cand;
         fa.totals = reinterpret_cast<int32_t *>(sc); fa.possible = rmask; fa.words = L.rmask_words; fa.d2 = rd2;
@@ -852,7 +882,9 @@ int range_search(const trim_index_view *index, const float *queries, int64_t nq,
         y.probes = a.probes; y.nlist = a.nlist; y.nseg = a.nseg; y.max_cand = a.max_cand; y.order = query_order;
         y.totals = m.totals; y.bits = rmask; y.d2_out = rd2; y.words = L.rmask_words; y.radius2 = a.radius2;
         y.chunk = L.chunk; y.nchunk = L.nsplit; y.counts = counts;
+        if (a.lut) z.add(sc + FL.off_bad, (size_t)nq);
         if ((rc = prepare_filter(fa, v, 0, nq, z, st))) return rc;
+        if ((rc = prepare_tables(m, index, a, FL, sc, st))) return rc;
         // candidates per query: the filter needs them before the finish pass writes them
         if ((rc = launch_totals(m, st))) return rc;
         if ((rc = launch_filter(fa, st))) return rc;
@@ -1155,6 +1187,11 @@ int trim_fs_build_lut(const float *queries, int64_t nq, int32_t d, const float *
     if (d % M || M % 2) return TRIM_UNSUPPORTED_SHAPE;
     if (nq == 0) return TRIM_OK;
     if (!queries || !codebooks || !lut_out) return TRIM_INVALID_ARG;
+    if (lut_tiled(d / M, true) && M % 8 == 0 && aligned16(lut_out)) {
+        LutArgs a{};
+        a.queries = queries; a.nq = a.nslots = nq; a.d = d; a.codebooks = codebooks; a.nsub = M; a.lut = lut_out;
+        return launch_lut(a, d / M, true, false, static_cast<hipStream_t>(stream));
+    }
     const int bper = 64;   // code bytes per block: 2048 entries
     for (int64_t q0 = 0; q0 < nq; q0 += 65535) {
         const int64_t cnt = nq - q0 < 65535 ? nq - q0 : 65535;
@@ -1185,6 +1222,11 @@ int trim_build_lut(const float *queries, int64_t nq, int32_t d, const float *cod
             hipLaunchKernelGGL(lut_mfma_kernel<8>, grid, dim3(256), 0, st, queries, nq, d, codebooks, M, lut_out);
         HIP_TRY(hipGetLastError());
         return TRIM_OK;
+    }
+    if (lut_tiled(dsub, false) && aligned16(lut_out)) {
+        LutArgs a{};
+        a.queries = queries; a.nq = a.nslots = nq; a.d = d; a.codebooks = codebooks; a.nsub = M; a.lut = lut_out;
+        return launch_lut(a, dsub, false, false, st);
     }
     const int jper = 8;
     // grid.y is limited to 65535: walk the queries in slabs

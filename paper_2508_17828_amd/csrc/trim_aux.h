@@ -15,7 +15,7 @@ __global__ void fill_u32_kernel(uint32_t *p, size_t count, uint32_t v) {
 
 // Several areas cleared by one launch (a launch of its own for each costs a small search 3 to 5 us).
 struct ZeroAreas {
-    static constexpr int kMost = 8;
+    static constexpr int kMost = 10;
     uint32_t *at[kMost];
     size_t words[kMost];
     int count = 0;

@@ -45,6 +45,7 @@ inline hipError_t allow_lds(const void *fn, size_t bytes) {
     int name(const SearchArgs &a, const Plan &pl, dim3 grid, hipStream_t st)
 // The separate passes (trim_mark_inst.hip).
 int launch_finish(const FinishArgs &a, int vec, bool fs, int threads, size_t lds, int64_t slots, hipStream_t st);
+int launch_lut(const LutArgs &a, int dsub, bool fs, bool verify, hipStream_t st);
 int launch_totals(const FinishArgs &a, hipStream_t st);
 int launch_filter_operands(const FilterArgs &a, hipStream_t st);
 int launch_filter(const FilterArgs &a, hipStream_t st);

@@ -27,7 +27,7 @@ namespace trim {
 // With long codes the table lookups of the bounds are what a search costs, and early abandon saves
 // little of them where no part of a code decides (unit vectors: half of the subspaces have to be summed
 // before far candidates are out).  But Gamma(l,q)^2 = |q|^2 + |l|^2 - 2 q.l is a contraction, and
-// queries that probe the same list share its landmarks: list by list, 256 landmarks x 128 queries
+// queries that probe the same list share its landmarks: list by list, 512 landmarks x 128 queries
 // per workgroup and tile, by v_mfma_f32_32x32x16_f16.  A landmark's operand is its centroids, so it is never built:
 // a lane gathers 16 bytes of the (16-bit) centroids of its code byte from LDS and that is the operand.
 //
@@ -154,40 +154,63 @@ __global__ __launch_bounds__(256) void totals_kernel(const FinishArgs a) {
     if (lane == 0) a.totals[row] = (int)(sum < a.max_cand ? sum : a.max_cand);
 }
 
-// PAD: values per sub-vector after padding; FS: two 4-bit codes per byte.  Persistent: workgroups take tiles until
-// there are no more.
-template <int PAD, bool FS>
-__global__ __launch_bounds__(kFltThreads, 2) void filter_kernel(const FilterArgs a) {
+// The list whose tiles hold tile `task` (start: prefix of the lists' tiles, start[0] = 0), by one wave, 64 lists at a
+// look: 2 dependent loads for 1024 lists instead of 10.
+__device__ __forceinline__ int list_of_task(const int32_t *start, int nlist, int task) {
+    const int lane = threadIdx.x & 63;
+    int lo = 0, len = nlist;
+    while (len > 1) {
+        const int step = (len + 63) >> 6, at = lo + lane * step;
+        const int cnt = __popcll(__ballot(at < nlist && at < lo + len && start[at < nlist ? at : 0] <= task));
+        lo += (cnt - 1) * step;
+        len = step;
+    }
+    return lo;
+}
+
+// PAD: values per sub-vector after padding; FS: two 4-bit codes per byte; AL: code words (4 bytes) that may be loaded together.
+// Persistent: workgroups take tiles until there are no more.  512 landmarks x 128 queries per tile, eight waves of
+// 64 x 128.  A slice is 32 values: 16 KB of centroids and 8 KB of queries go through the LDS, two buffers and two
+// slices ahead in registers (with 256 x 128 tiles, two workgroups per CU and one slice ahead a
+// slice took 2.9 us, most of it waiting).  2,500 queries x 500,000 x 768: 551 -> 496 us; whatever is spilled inside a slice
+// costs more than the tile gains (679 us with 16-byte code loads).  What is left is the LDS: a gather of 16 bytes per landmark and 8 values.
+template <int PAD, bool FS, int AL>
+__global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs a) {
     typedef _Float16 h8 __attribute__((ext_vector_type(8)));
     typedef _Float16 h4 __attribute__((ext_vector_type(4)));
     typedef _Float16 h2 __attribute__((ext_vector_type(2)));
     typedef float v16f __attribute__((ext_vector_type(16)));
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
     constexpr int kCent = FS ? kC4 : kC;
     constexpr int kSubs = kFltSlice / PAD;                        // subspaces per slice
     constexpr int kBytes = FS ? kSubs / 2 : kSubs;                // code bytes per slice
     constexpr int kBookBytes = kFltSlice * kCent * 2;             // 16 KB (FS: 1 KB)
+    constexpr int kBookV = kBookBytes / 16, kBooks = kBookV > kFltThreads ? kBookV / kFltThreads : 1;
+    constexpr int CH = AL > kBytes / 4 ? AL : kBytes / 4;         // code words at hand
+    constexpr int kSpc = 4 * CH / kBytes;                         // slices they last
+    constexpr int kQStride = kFltQ + 4;                           // (bank spread)
     __shared__ __align__(16) unsigned char s_book[2][kBookBytes];
-    __shared__ __align__(16) h8 s_q[2][4 * kFltQ];                // [16-value step][half][query]
+    __shared__ __align__(16) h8 s_q[2][4 * kQStride];             // [8 values][query]
     __shared__ __align__(16) float s_b[kFltRows], s_nl[kFltRows], s_ml[kFltRows];
     __shared__ float s_al[kFltQ], s_be[kFltQ], s_nq[kFltQ];
     __shared__ int s_row[kFltQ], s_c0[kFltQ], s_end[kFltQ];
-    __shared__ float s_b0[4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, half = lane >> 5;
+    __shared__ float s_b0[kFltThreads / kWave];
     const float sc = filter_scale(*a.max_bits);
     const int nslice = a.kpad / kFltSlice;
     const int64_t rows_all = a.n < a.hi ? a.n : a.hi, qall = a.by_query ? a.nq : a.nslots;
     const int total_tasks = a.list_offsets ? a.tasks[a.nlist]
                             : (int)((rows_all + kFltRows - 1) / kFltRows * ((qall + kFltQ - 1) / kFltQ));
     for (int task = blockIdx.x; task < total_tasks; task += gridDim.x) {
+        // (opaque: addresses that depend on the thread are made per tile; kept over the tiles they would not fit the
+        // registers, and a reload inside the slices waits for everything that is on its way)
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int lane = tid & 63, wave = tid >> 6, col = lane & 31, half = lane >> 5;
         // which list, rows, queries
         int64_t ls = 0, le = a.n;
         int i0 = 0, i1 = (int)qall, t = task;
         if (a.list_offsets) {
-            int x = 0, y = a.nlist - 1;
-            while (x < y) {
-                const int mid = (x + y) >> 1;
-                if (a.tasks[mid + 1] <= task) x = mid + 1; else y = mid;
-            }
+            const int x = list_of_task(a.tasks, a.nlist, task);
             ls = a.list_offsets[x];
             le = a.list_offsets[x + 1];
             ls = ls < 0 ? 0 : (ls > a.n ? a.n : ls);
@@ -202,7 +225,19 @@ __global__ __launch_bounds__(kFltThreads, 2) void filter_kernel(const FilterArgs
         const int nrows = le - r0 < kFltRows ? (int)(le - r0) : kFltRows;
         const int q0 = i0 + qt * kFltQ, nqs = i1 - q0 < kFltQ ? i1 - q0 : kFltQ;
         __syncthreads();     // the previous tile is done with
-        // landmark distances of the rows, their mean (the tangent point)
+        // the queries' rows of the workspace; landmark distances of the rows, their mean (the tangent point)
+        int row = 0, c0q = 0, endq = 0;
+        if (tid < kFltQ) {
+            row = q0 + (tid < nqs ? tid : 0);
+            int64_t c = 0;
+            if (a.list_offsets) { const int2 v = a.inv[row]; row = v.x; c = v.y; }
+            c += r0 - ls;
+            s_row[tid] = row;
+            endq = a.totals[row];
+            endq = endq < a.hi ? endq : a.hi;
+            c0q = c < endq ? (int)c : endq;
+            if (tid >= nqs || c >= endq || c + nrows <= a.lo) endq = c0q;      // nothing of this query in these rows
+        }
         {
             float b = 0.0f;
             if (tid < nrows) b = a.dlx[r0 + tid];
@@ -212,77 +247,74 @@ __global__ __launch_bounds__(kFltThreads, 2) void filter_kernel(const FilterArgs
             for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
             if (lane == 0) s_b0[wave] = sum;
         }
-        __syncthreads();
-        bool any = false;
-        if (tid < kFltQ) {
-            float al = -1.0f, be = 0.0f, nq = 0.0f;
-            int row = 0, c0 = 0, end = 0;
-            if (tid < nqs) {
-                int64_t c = 0;
-                row = q0 + tid;
-                if (a.list_offsets) { const int2 v = a.inv[q0 + tid]; row = v.x; c = v.y; }
-                c += r0 - ls;
-                end = a.totals[row];
-                end = end < a.hi ? end : a.hi;
-                c0 = c < end ? (int)c : end;
-                if (c < end && c + nrows > a.lo) {
-                    const int64_t q = a.by_query ? row : a.order ? a.order[a.slot0 + row] : a.slot0 + row;
-                    const float tau = a.range ? a.radius2 : a.tau_of ? a.tau_of[(size_t)q * a.tau_stride] : __builtin_inff();
-                    const float b0 = ((s_b0[0] + s_b0[1]) + (s_b0[2] + s_b0[3])) / (float)nrows;
-                    const AbandonLine line = abandon_line(tau, a.two_gamma, b0);
-                    nq = a.qpar[2 * (size_t)row];
-                    al = line.alpha * sc + a.qpar[2 * (size_t)row + 1];
-                    be = line.beta;
-                    if (!(al == al)) al = __builtin_inff();
-                    any = true;
-                } else {
-                    end = c0;      // nothing of this query in these rows
-                }
-            }
-            s_al[tid] = al; s_be[tid] = be; s_nq[tid] = nq;
-            s_row[tid] = row; s_c0[tid] = c0; s_end[tid] = end;
-        }
-        if (!__syncthreads_or(any)) continue;
-        // staging: a slice of the centroids (contiguous) and of the queries
-        typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+        if (!__syncthreads_or(c0q < endq)) continue;
+        // staging: a slice of the centroids (contiguous) and of the queries (four threads each)
         const u4 *book_src = reinterpret_cast<const u4 *>(a.books);
-        constexpr int kBookV = kBookBytes / 16;
-        const int sq = tid >> 1, sh = tid & 1;                     // query, 16-value step
-        const u4 *q_src = reinterpret_cast<const u4 *>(a.q16 + (size_t)s_row[sq] * a.kpad + sh * 16);
-        u4 bk[kBookV > kFltThreads ? kBookV / kFltThreads : 1], qv[2];
-        auto load = [&](int sl) {
+        const int sq = tid >> 2, sp = tid & 3;
+        const u4 *q_src = reinterpret_cast<const u4 *>(a.q16 + (size_t)s_row[sq] * a.kpad) + sp;
+        struct Ahead { u4 bk[kBooks], qv; };
+        auto load = [&](int sl, Ahead &r) {
+            sl = sl < nslice ? sl : nslice - 1;             // (past the end: loaded and staged, never used)
 #pragma unroll
-            for (int i = 0; i < (kBookV > kFltThreads ? kBookV / kFltThreads : 1); ++i)
-                if (kBookV >= kFltThreads || tid < kBookV) bk[i] = book_src[(size_t)sl * kBookV + i * kFltThreads + tid];
-            qv[0] = q_src[(size_t)sl * (kFltSlice / 8)];
-            qv[1] = q_src[(size_t)sl * (kFltSlice / 8) + 1];
+            for (int i = 0; i < kBooks; ++i)
+                if (kBookV >= kFltThreads || tid < kBookV) r.bk[i] = book_src[(size_t)sl * kBookV + i * kFltThreads + tid];
+            r.qv = q_src[(size_t)sl * (kFltSlice / 8)];
         };
-        auto stage = [&](int buf) {
-            u4 *bd = reinterpret_cast<u4 *>(s_book[buf]);
+        auto stage = [&](int sl, const Ahead &r) {
+            u4 *bd = reinterpret_cast<u4 *>(s_book[sl & 1]);
 #pragma unroll
-            for (int i = 0; i < (kBookV > kFltThreads ? kBookV / kFltThreads : 1); ++i)
-                if (kBookV >= kFltThreads || tid < kBookV) bd[i * kFltThreads + tid] = bk[i];
-            u4 *qd = reinterpret_cast<u4 *>(s_q[buf]);
-            qd[(sh * 2) * kFltQ + sq] = qv[0];
-            qd[(sh * 2 + 1) * kFltQ + sq] = qv[1];
+            for (int i = 0; i < kBooks; ++i)
+                if (kBookV >= kFltThreads || tid < kBookV) bd[i * kFltThreads + tid] = r.bk[i];
+            reinterpret_cast<u4 *>(s_q[sl & 1])[sp * kQStride + sq] = r.qv;
         };
-        // the code bytes of this lane's two rows, a slice at a time
-        const uint8_t *code[2];
-        uint32_t cw[2][(kBytes + 3) / 4], cn[2][(kBytes + 3) / 4];
+        // the code words of this lane's two rows: the ones in use and the next
+        const uint8_t *codes = a.codes + (size_t)r0 * a.M;
+        uint32_t code[2];
+        uint32_t cw[2][CH], cn[2][CH];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const int r = wave * 64 + u * 32 + col;
-            code[u] = a.codes + (size_t)(r0 + (r < nrows ? r : 0)) * a.M;
+            code[u] = (uint32_t)((r < nrows ? r : 0) * a.M);
         }
-        auto load_code = [&](int sl, uint32_t (&w)[2][(kBytes + 3) / 4]) {
+        auto load_code = [&](int at, uint32_t (&w)[2][CH]) {       // (past the code: padding subspaces, all centroids zero)
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll
-                for (int v = 0; v < (kBytes + 3) / 4; ++v) {
-                    const int at = sl * kBytes + 4 * v;            // (past the code: padding subspaces, all centroids zero)
-                    w[u][v] = at < a.M ? *reinterpret_cast<const uint32_t *>(code[u] + (at & ~3)) >> (8 * (at & 3)) : 0u;
+                for (int v = 0; v < CH; v += AL) {
+                    if (at + 4 * v < a.M) {
+                        uint32_t x[AL];
+                        load_codes<AL>(x, codes + (code[u] + (uint32_t)(at + 4 * v)));
+#pragma unroll
+                        for (int e = 0; e < AL; ++e) w[u][v + e] = x[e];
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < AL; ++e) w[u][v + e] = 0u;
+                    }
                 }
         };
+        Ahead r0a, r1a;
+        load(0, r0a);
+        load_code(0, cw);
+        load(1, r1a);
+        load_code(4 * CH, cn);
+        // (while these are under way) the lines that bound the queries' table sums
+        if (tid < kFltQ) {
+            float al = -1.0f, be = 0.0f, nq = 0.0f;
+            if (c0q < endq) {
+                const int64_t q = a.by_query ? row : a.order ? a.order[a.slot0 + row] : a.slot0 + row;
+                const float tau = a.range ? a.radius2 : a.tau_of ? a.tau_of[(size_t)q * a.tau_stride] : __builtin_inff();
+                float b0 = 0.0f;
+#pragma unroll
+                for (int w = 0; w < kFltThreads / kWave; ++w) b0 += s_b0[w];
+                const AbandonLine line = abandon_line(tau, a.two_gamma, b0 / (float)nrows);
+                nq = a.qpar[2 * (size_t)row];
+                al = line.alpha * sc + a.qpar[2 * (size_t)row + 1];
+                be = line.beta;
+                if (!(al == al)) al = __builtin_inff();
+            }
+            s_al[tid] = al; s_be[tid] = be; s_nq[tid] = nq;
+            s_c0[tid] = c0q; s_end[tid] = endq;
+        }
         v16f acc[2][4];
         float nl[2] = {0.0f, 0.0f};
 #pragma unroll
@@ -293,24 +325,22 @@ __global__ __launch_bounds__(kFltThreads, 2) void filter_kernel(const FilterArgs
                 for (int i = 0; i < 16; ++i) acc[u][v][i] = 0.0f;
         const bool busy = wave * 64 < nrows;
         const int nv = (nqs + 31) >> 5;               // query tiles of this one in use
-        load(0);
-        load_code(0, cw);
-        stage(0);
+        stage(0, r0a);
+        load(2, r0a);
         __syncthreads();
-        for (int sl = 0; sl < nslice; ++sl) {
-            if (sl + 1 < nslice) {
-                load(sl + 1);
-                load_code(sl + 1, cn);
-            }
+        auto slice = [&](int sl, Ahead &r) {         // r: slice sl + 1
+            stage(sl + 1, r);
+            load(sl + 3, r);
             if (busy) {
                 const unsigned char *bb = s_book[sl & 1];
                 const h8 *qq = s_q[sl & 1];
 #pragma unroll
                 for (int ks = 0; ks < 2; ++ks) {
+                    __builtin_amdgcn_sched_barrier(0);     // (registers: one step's operands at a time)
                     h8 lm[2], qf[4];
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
-                        if (v < nv) qf[v] = qq[(ks * 2 + half) * kFltQ + v * 32 + col];
+                        qf[v] = qq[(ks * 2 + half) * kQStride + v * 32 + col];
 #pragma unroll
                     for (int u = 0; u < 2; ++u) {
                         if constexpr (FS) {                       // four sub-vectors of two values
@@ -345,14 +375,31 @@ __global__ __launch_bounds__(kFltThreads, 2) void filter_kernel(const FilterArgs
                         }
                 }
             }
-            if (sl + 1 < nslice) {
-                stage((sl + 1) & 1);
+            // the next slice's code bytes to the front
+            if ((sl + 1) % kSpc == 0) {
 #pragma unroll
                 for (int u = 0; u < 2; ++u)
 #pragma unroll
-                    for (int v = 0; v < (kBytes + 3) / 4; ++v) cw[u][v] = cn[u][v];
+                    for (int v = 0; v < CH; ++v) cw[u][v] = cn[u][v];
+                load_code((sl + 1 + kSpc) / kSpc * (4 * CH), cn);
+            } else {
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int v = 0; v < CH; ++v) {
+                        if constexpr (kBytes >= 4) {
+                            cw[u][v] = v + kBytes / 4 < CH ? cw[u][v + kBytes / 4 < CH ? v + kBytes / 4 : 0] : 0u;
+                        } else {
+                            cw[u][v] = (cw[u][v] >> (8 * kBytes)) | (v + 1 < CH ? cw[u][v + 1 < CH ? v + 1 : 0] << (32 - 8 * kBytes) : 0u);
+                        }
+                    }
             }
             __syncthreads();
+        };
+#pragma unroll 1
+        for (int sl = 0; sl < nslice; sl += 2) {      // (an even number)
+            slice(sl, r1a);
+            slice(sl + 1, r0a);
         }
         constexpr float kUlp = 1.0f / 16777216.0f;
         const float keep = 1.0f - (4.0f * a.d + 64.0f) * kUlp;
@@ -383,6 +430,7 @@ __global__ __launch_bounds__(kFltThreads, 2) void filter_kernel(const FilterArgs
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     if (v >= nv) break;
+                    __builtin_amdgcn_sched_barrier(0);
                     const int qi = v * 32 + col;
                     const float al = s_al[qi], be = s_be[qi], nq = s_nq[qi] * keep;
                     uint32_t m = 0;
@@ -411,27 +459,34 @@ __global__ __launch_bounds__(kFltThreads, 2) void filter_kernel(const FilterArgs
 
 // ---- measure: lower bounds of the exact distances of the marked candidates ----
 // The filter's contraction over the raw rows (16-bit, relative to mu, scaled; converted while they are staged), list by
-// list, 256 rows at a time against the queries that have a candidate marked among them (up to 128 together):
+// list, 256 rows at a time against the queries that have a candidate marked among them (up to 64 WQ together):
 //     d2 >= ((|q' - x'| - moved(q) - moved(x)) / scale)^2   less the exact rule's own roundings.
 // Only where that does not exceed the threshold is the exact distance taken (replay_kernel,
 // range_exact_kernel).  A row is read once for all its queries, and the contraction takes the place of 2 d
 // vector operations per survivor: of 3,940 survivors per query (2,500 queries x 500,000 x 768) some forty
-// can still matter.  Bound by reading the rows (and their conversion).
-__global__ __launch_bounds__(kFltThreads, 2) void measure_kernel(const FilterArgs a) {
+// can still matter.  Bound by reading the rows; one or two slices of 32 values are on their way while one is used: 440 -> 405 us,
+// 500 queries x 300,000 x 960: 906 -> 547 us (WQ = 4: 256 queries at a time, so that rows are read half as often).
+// Queries go to workgroups in blocks of 512, so that a list that many want is not one workgroup's tail.
+template <int WQ>
+__global__ __launch_bounds__(256 * WQ, 4) void measure_kernel(const FilterArgs a) {
     typedef _Float16 h8 __attribute__((ext_vector_type(8)));
     typedef _Float16 h4 __attribute__((ext_vector_type(4)));
     typedef _Float16 h2 __attribute__((ext_vector_type(2)));
     typedef float v16f __attribute__((ext_vector_type(16)));
     typedef float f4 __attribute__((ext_vector_type(4)));
     typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-    constexpr int kXRows = kFltRows + 2;                          // rows per 8 columns (two spare: bank spread)
+    constexpr int kMsrThreads = 256 * WQ, kMsrQ = 64 * WQ;
+    constexpr int kPer = 8 / WQ, kApart = kMsrThreads / 8;        // rows staged by a thread
+    constexpr int kSets = WQ / 2;                                 // slices ahead in registers
+    constexpr int kXRows = kMsrRows + 2;                          // rows per 8 columns (two spare: bank spread)
+    constexpr int kQStride = kMsrQ + 4;                           // (bank spread)
     __shared__ __align__(16) unsigned char s_x[2][4 * kXRows * 16];
-    __shared__ __align__(16) h8 s_q[2][4 * kFltQ];                // [8 columns][query]
-    __shared__ __align__(16) float s_nx[kFltRows], s_mx[kFltRows];
-    __shared__ float s_mq[2 * kFltQ], s_nq[2 * kFltQ];
-    __shared__ int s_row[2 * kFltQ], s_c0[2 * kFltQ], s_end[2 * kFltQ];
+    __shared__ __align__(16) h8 s_q[2][4 * kQStride];             // [8 columns][query]
+    __shared__ __align__(16) float s_nx[kMsrRows], s_mx[kMsrRows];
+    __shared__ float s_mq[2 * kMsrQ], s_nq[2 * kMsrQ];
+    __shared__ int s_row[2 * kMsrQ], s_c0[2 * kMsrQ], s_end[2 * kMsrQ];
     __shared__ int s_n;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, half = lane >> 5;
+    extern __shared__ __align__(16) float s_mu[];                 // [d]
     const float sc = filter_scale(*a.max_bits);
     const int nslice = a.kpad_rows / kFltSlice;
     const int64_t rows_all = a.n < a.hi ? a.n : a.hi, qall = a.by_query ? a.nq : a.nslots;
@@ -439,40 +494,42 @@ __global__ __launch_bounds__(kFltThreads, 2) void measure_kernel(const FilterArg
     const float keep = 1.0f - (4.0f * a.d + 64.0f) * kUlp;
     const float back = sc > 0.0f ? (1.0f - (a.d / 32 + 16.0f) * 2.0f * kUlp) / (sc * sc) : 0.0f;
     const float lost = sqrt_rn((float)a.d) * (1.0f / 16384.0f);
+    for (int t = threadIdx.x; t < a.d; t += kMsrThreads) s_mu[t] = a.mu[t];      // (barriers follow)
     const int total_tasks = a.list_offsets ? a.row_tasks[a.nlist]
-                            : (int)((rows_all + kFltRows - 1) / kFltRows * ((qall + kFltQ - 1) / kFltQ));
+                            : (int)((rows_all + kMsrRows - 1) / kMsrRows * ((qall + a.msr_block - 1) / a.msr_block));
     for (int task = blockIdx.x; task < total_tasks; task += gridDim.x) {
+        int tid = threadIdx.x;            // (opaque: see filter_kernel)
+        asm volatile("" : "+v"(tid));
         int64_t ls = 0, r0, le = a.n;
         int qb, q1;
         if (a.list_offsets) {
-            int x = 0, y = a.nlist - 1;
-            while (x < y) {
-                const int mid = (x + y) >> 1;
-                if (a.row_tasks[mid + 1] <= task) x = mid + 1; else y = mid;
-            }
+            const int x = list_of_task(a.row_tasks, a.nlist, task);
             ls = a.list_offsets[x];
             le = a.list_offsets[x + 1];
             ls = ls < 0 ? 0 : (ls > a.n ? a.n : ls);
             le = le < ls ? ls : (le > a.n ? a.n : le);
             qb = a.inv_start[x];
             q1 = a.inv_start[x + 1];
-            r0 = ls + (int64_t)(task - a.row_tasks[x]) * kFltRows;
+            const int nqb = (q1 - qb + a.msr_block - 1) / a.msr_block, t = task - a.row_tasks[x], rt = t / nqb;
+            qb += (t - rt * nqb) * a.msr_block;
+            q1 = qb + a.msr_block < q1 ? qb + a.msr_block : q1;
+            r0 = ls + (int64_t)rt * kMsrRows;
         } else {
-            const int nqt = (int)((qall + kFltQ - 1) / kFltQ);
-            const int rt = task / nqt;
-            qb = (task - rt * nqt) * kFltQ;
-            q1 = qb + kFltQ < (int)qall ? qb + kFltQ : (int)qall;
-            r0 = (int64_t)rt * kFltRows;
+            const int nqb = (int)((qall + a.msr_block - 1) / a.msr_block);
+            const int rt = task / nqb;
+            qb = (task - rt * nqb) * a.msr_block;
+            q1 = qb + a.msr_block < (int)qall ? qb + a.msr_block : (int)qall;
+            r0 = (int64_t)rt * kMsrRows;
         }
-        const int nrows = le - r0 < kFltRows ? (int)(le - r0) : kFltRows;
+        const int nrows = le - r0 < kMsrRows ? (int)(le - r0) : kMsrRows;
         int have = 0;                     // queries waiting in the arrays (the same for all threads)
         __syncthreads();                  // (the previous tile is done with)
         while (qb < q1 || have > 0) {
-            // gather queries with a mark in these rows until there are 128, or no more
-            while (qb < q1 && have < kFltQ) {
+            // gather queries with a mark in these rows until there are 64 WQ, or no more
+            while (qb < q1 && have < kMsrQ) {
                 if (tid == 0) s_n = have;
                 __syncthreads();
-                if (tid < kFltQ && qb + tid < q1) {
+                if (tid < kMsrQ && qb + tid < q1) {
                     int row = qb + tid;
                     int64_t c = 0;
                     if (a.list_offsets) { const int2 v = a.inv[qb + tid]; row = v.x; c = v.y; }
@@ -498,107 +555,112 @@ __global__ __launch_bounds__(kFltThreads, 2) void measure_kernel(const FilterArg
                         }
                     }
                 }
-                qb += kFltQ;
+                qb += kMsrQ;
                 __syncthreads();
                 have = s_n;
                 __syncthreads();
             }
             if (have == 0) break;
-            const int nqs = have < kFltQ ? have : kFltQ, nv = (nqs + 31) >> 5;
-            // staging: eight threads per row (a whole cache line together), eight rows each, 32 apart; two per query
-            const int xr = tid >> 3, xc = tid & 7, sq = tid >> 1, sh = tid & 1;
-            f4 xv[8], xmu = {0.0f, 0.0f, 0.0f, 0.0f};
-            float nx[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) nx[i] = 0.0f;
-            const bool q_on = sq < nv * 32;
-            const u4 *q_src = reinterpret_cast<const u4 *>(a.q16_rows + (size_t)s_row[sq < nqs ? sq : 0] * a.kpad_rows + sh * 16);
-            u4 qv[2];
-            auto load = [&](int sl) {
+            asm volatile("" : "+v"(tid));
+            const int lane = tid & 63, wave = (tid >> 6) & 3, wq = tid >> 8, col = lane & 31, half = lane >> 5;
+            const int nqs = have < kMsrQ ? have : kMsrQ, nq32 = (nqs + 31) >> 5;
+            const int nv = nq32 - 2 * wq < 2 ? nq32 - 2 * wq : 2;        // query tiles of this wave
+            // staging: eight threads per row (a whole cache line together), kPer rows each, kApart apart; four per query
+            const int xr = tid >> 3, xc = tid & 7, sq = tid >> 2, sp = tid & 3;
+            float nx[kPer] = {};
+            const u4 *q_src = reinterpret_cast<const u4 *>(a.q16_rows);
+            const uint32_t q_at = (uint32_t)s_row[sq < nqs ? sq : 0] * (uint32_t)(a.kpad_rows / 8) + sp;     // (16 bytes)
+            const unsigned char *x_src = reinterpret_cast<const unsigned char *>(a.base + (size_t)r0 * a.d);
+            struct Ahead { f4 x[kPer]; u4 q; };
+            auto load = [&](int sl, Ahead &r) {
+                sl = sl < nslice ? sl : nslice - 1;
                 const int k = sl * kFltSlice + 4 * xc;
                 const bool in = k < a.d;
-                if (in) xmu = *reinterpret_cast<const f4 *>(a.mu + k);
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const int r = xr + 32 * i;
-                    xv[i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-                    if (in && r < nrows) xv[i] = *reinterpret_cast<const f4 *>(a.base + (size_t)(r0 + r) * a.d + k);
+                for (int i = 0; i < kPer; ++i) {
+                    const int w = xr + kApart * i;
+                    r.x[i] = *reinterpret_cast<const f4 *>(x_src + (uint32_t)((w < nrows ? w : 0) * a.d + (in ? k : 0)) * 4u);
                 }
-                if (q_on) {
-                    qv[0] = q_src[(size_t)sl * (kFltSlice / 8)];
-                    qv[1] = q_src[(size_t)sl * (kFltSlice / 8) + 1];
-                }
+                r.q = q_src[q_at + (uint32_t)sl * (kFltSlice / 8)];
             };
-            auto stage = [&](int buf, int sl) {
-                const bool in = sl * kFltSlice + 4 * xc < a.d;
+            auto stage = [&](int sl, const Ahead &r) {
+                const bool in = sl * kFltSlice + 4 * xc < a.d;     // (nothing past the end)
+                f4 mu = {0.0f, 0.0f, 0.0f, 0.0f};
+                if (in) mu = *reinterpret_cast<const f4 *>(s_mu + sl * kFltSlice + 4 * xc);
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
+                for (int i = 0; i < kPer; ++i) {
                     h4 h = {0, 0, 0, 0};
                     if (in) {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) h[e] = (_Float16)__builtin_fmaf(xv[i][e], sc, -(xmu[e] * sc));
+                        for (int e = 0; e < 4; ++e) h[e] = (_Float16)__builtin_fmaf(r.x[i][e], sc, -(mu[e] * sc));
                         nx[i] = __builtin_amdgcn_fdot2(h2{h[0], h[1]}, h2{h[0], h[1]}, nx[i], false);
                         nx[i] = __builtin_amdgcn_fdot2(h2{h[2], h[3]}, h2{h[2], h[3]}, nx[i], false);
                     }
-                    *reinterpret_cast<h4 *>(s_x[buf] + ((xc >> 1) * kXRows + xr + 32 * i) * 16 + (xc & 1) * 8) = h;
+                    *reinterpret_cast<h4 *>(s_x[sl & 1] + ((xc >> 1) * kXRows + xr + kApart * i) * 16 + (xc & 1) * 8) = h;
                 }
-                if (q_on) {
-                    u4 *qd = reinterpret_cast<u4 *>(s_q[buf]);
-                    qd[(sh * 2) * kFltQ + sq] = qv[0];
-                    qd[(sh * 2 + 1) * kFltQ + sq] = qv[1];
-                }
+                reinterpret_cast<u4 *>(s_q[sl & 1])[sp * kQStride + sq] = r.q;
             };
-            v16f acc[2][4];
+            v16f acc[2][2];
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
+                for (int v = 0; v < 2; ++v)
 #pragma unroll
                     for (int i = 0; i < 16; ++i) acc[u][v][i] = 0.0f;
-            const bool busy = wave * 64 < nrows;
-            load(0);
-            stage(0, 0);
+            const bool busy = wave * 64 < nrows && nv > 0;
+            Ahead ra, rb;
+            load(0, ra);
+            if constexpr (kSets > 1) load(1, rb);
+            stage(0, ra);
+            load(kSets, ra);
             __syncthreads();
-            for (int sl = 0; sl < nslice; ++sl) {
-                if (sl + 1 < nslice) load(sl + 1);
+            auto slice = [&](int sl, Ahead &r) {     // r: slice sl + 1
+                stage(sl + 1, r);
+                load(sl + 1 + kSets, r);
                 if (busy) {
                     const unsigned char *bb = s_x[sl & 1];
                     const h8 *qq = s_q[sl & 1];
 #pragma unroll
                     for (int ks = 0; ks < 2; ++ks) {
+                        __builtin_amdgcn_sched_barrier(0);     // (registers: one step's operands at a time)
                         h8 xf[2];
 #pragma unroll
                         for (int u = 0; u < 2; ++u)
                             xf[u] = *reinterpret_cast<const h8 *>(bb + ((ks * 2 + half) * kXRows + wave * 64 + u * 32 + col) * 16);
 #pragma unroll
-                        for (int v = 0; v < 4; ++v)
+                        for (int v = 0; v < 2; ++v)
                             if (v < nv) {
-                                const h8 qf = qq[(ks * 2 + half) * kFltQ + v * 32 + col];
+                                const h8 qf = qq[(ks * 2 + half) * kQStride + wq * 64 + v * 32 + col];
 #pragma unroll
                                 for (int u = 0; u < 2; ++u) acc[u][v] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xf[u], qf, acc[u][v], 0, 0, 0);
                             }
                     }
                 }
-                if (sl + 1 < nslice) stage((sl + 1) & 1, sl + 1);
                 __syncthreads();
+            };
+#pragma unroll 1
+            for (int sl = 0; sl < nslice; sl += 2) {
+                if constexpr (kSets > 1) slice(sl, rb); else slice(sl, ra);
+                slice(sl + 1, ra);
             }
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
+            for (int i = 0; i < kPer; ++i) {
                 float v = nx[i];
                 v += __shfl_xor(v, 1);
                 v += __shfl_xor(v, 2);
                 v += __shfl_xor(v, 4);
                 if (xc == 0) {
-                    s_nx[xr + 32 * i] = v * keep;
-                    s_mx[xr + 32 * i] = sqrt_rn(v) * (1.0f / 2048.0f + 1.0f / 4194304.0f) * 1.001f + lost;
+                    s_nx[xr + kApart * i] = v * keep;
+                    s_mx[xr + kApart * i] = sqrt_rn(v) * (1.0f / 2048.0f + 1.0f / 4194304.0f) * 1.001f + lost;
                 }
             }
             __syncthreads();
             if (busy) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
+                for (int v = 0; v < 2; ++v) {
                     if (v >= nv) break;
-                    const int qi = v * 32 + col;
+                    __builtin_amdgcn_sched_barrier(0);
+                    const int qi = wq * 64 + v * 32 + col;
                     const bool real = qi < nqs;
                     const float mq = real ? s_mq[qi] : 0.0f, nq = real ? s_nq[qi] * keep : 0.0f;
                     const int cq = real ? s_c0[qi] : 0, end = real ? s_end[qi] : 0;
@@ -622,7 +684,7 @@ __global__ __launch_bounds__(kFltThreads, 2) void measure_kernel(const FilterArg
                             const int r = 8 * (i >> 2) + 4 * half + (i & 3);
                             if ((m >> r) & 1u) {
                                 const float s = acc[u][v][i] + (nq + s_nx[wave * 64 + u * 32 + r]);
-                                float dist = sqrt_rn(__builtin_fmaxf(s, 0.0f)) - (mq + s_mx[wave * 64 + u * 32 + r]);
+                                float dist = __builtin_amdgcn_sqrtf(__builtin_fmaxf(s, 0.0f)) * (1.0f - 8.0f * kUlp) - (mq + s_mx[wave * 64 + u * 32 + r]);
                                 // (out of the 16-bit range: nothing is known)
                                 dist = dist < 1e18f && s < 1e36f ? __builtin_fmaxf(dist, 0.0f) : 0.0f;
                                 out[r] = dist * dist * back;
@@ -644,6 +706,54 @@ __global__ __launch_bounds__(kFltThreads, 2) void measure_kernel(const FilterArg
             if (tid < rest) { s_row[tid] = r_row; s_c0[tid] = r_c0; s_end[tid] = r_end; s_nq[tid] = r_nq; s_mq[tid] = r_mq; }
             have = rest;
             __syncthreads();
+        }
+    }
+}
+
+// ---- distance tables of many queries ----
+// 256 entries per workgroup (a subspace; 16 of them with 4-bit codes), four centroids per lane kept in registers, and
+// one wave per query and step: a query's 256 entries are one 1 KB store.  The kernel before it built a query's
+// rows from the centroids' memory (1.5 MB per query of 1536 values): 175 us for 2000 x 192 rows, 393 MB; now 97 us (4.1 TB/s).
+// Bound by writing.  VERIFY: lut is a caller's, bad[query] is set unless its entries are the
+// centroids' distances bit for bit.  by_slot: a query's table is at its place in the order, else at its number.
+template <int DSUB, bool FS, bool VERIFY>
+__global__ __launch_bounds__(256) void lut_tile_kernel(const LutArgs a) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int entries = a.nsub * (FS ? kC4 : kC), e = blockIdx.x * 256 + 4 * lane;
+    const bool on = e < entries;
+    const int sj = FS ? (on ? e >> 4 : 0) : (int)blockIdx.x;
+    float c[4][DSUB];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int t = 0; t < DSUB; ++t) c[u][t] = a.codebooks[(size_t)(on ? e + u : u) * DSUB + t];
+    const int64_t s0 = (int64_t)blockIdx.y * kLutQueries + wave;
+#pragma unroll 2
+    for (int i = 0; i < kLutQueries; i += 4) {
+        const int64_t slot = s0 + i;
+        if (slot >= a.nslots) break;
+        const int64_t q = a.order ? a.order[a.slot0 + slot] : a.slot0 + slot;
+        if (q < 0 || q >= a.nq) continue;
+        const float *x = a.queries + (size_t)q * a.d + sj * DSUB;
+        float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int t = 0; t < DSUB; ++t) {
+            const float xt = x[t];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float v = xt - c[u][t];
+                acc[u] = __builtin_fmaf(v, v, acc[u]);
+            }
+        }
+        if (!on) continue;
+        float4 *out = reinterpret_cast<float4 *>(a.lut + (size_t)(a.by_slot ? slot : q) * entries + e);
+        if constexpr (VERIFY) {
+            const float4 v = *out;
+            if (__float_as_uint(v.x) != __float_as_uint(acc[0]) || __float_as_uint(v.y) != __float_as_uint(acc[1]) ||
+                __float_as_uint(v.z) != __float_as_uint(acc[2]) || __float_as_uint(v.w) != __float_as_uint(acc[3]))
+                a.bad[q] = 1;
+        } else {
+            *out = make_float4(acc[0], acc[1], acc[2], acc[3]);
         }
     }
 }
@@ -687,7 +797,7 @@ void finish_kernel(const FinishArgs a) {
     const float tau = a.range ? a.radius2 : a.tau_of ? a.tau_of[(size_t)q * a.tau_stride] : __builtin_inff();
     auto fill = [&](int j0, int nj) {
         if (a.lut) {
-            const float4 *src = reinterpret_cast<const float4 *>(a.lut + ((size_t)q * a.M + j0) * kByteEntries<FS>);
+            const float4 *src = reinterpret_cast<const float4 *>(a.lut + ((size_t)(a.lut_by_row ? row : q) * a.M + j0) * kByteEntries<FS>);
             float4 *dst = reinterpret_cast<float4 *>(tab);
             for (int e = tid; e < nj * (kByteEntries<FS> / 4); e += T) dst[e] = src[e];
         } else {
@@ -698,25 +808,8 @@ void finish_kernel(const FinishArgs a) {
     float *row_g = a.g + (size_t)row * a.words * 32;
     int n_marked = 0, in_place = -1;            // the phase whose rows are in place
     // The filter went by the centroids.  A caller's table may hold something else: unless its entries are the
-    // centroids' distances bit for bit, every candidate of the query counts as marked.
-    bool all_marked = a.all != 0;
-    if (a.lut && !all_marked) {
-        bool bad = false;
-        for (int ph = a.P - 1; ph >= 0; --ph) {
-            __syncthreads();
-            fill(ph * a.Mp, a.Mp);
-            __syncthreads();
-            table_rows<FS>(q_lds, a.codebooks, a.dsub, ph * a.Mp, a.Mp,
-                           [&](int e, float v) { bad = bad || __float_as_uint(tab[e]) != __float_as_uint(v); });
-        }
-        in_place = 0;
-        if (tid == 0) part[0] = 0;      // (no __syncthreads_or: its static LDS would displace the table)
-        __syncthreads();
-        if (bad) part[0] = 1;
-        __syncthreads();
-        all_marked = part[0] != 0;
-        __syncthreads();
-    }
+    // centroids' distances bit for bit (lut_tile_kernel), every candidate of the query counts as marked.
+    const bool all_marked = a.all != 0 || (a.bad != nullptr && a.bad[q] != 0);
     for (int p0 = lo & ~31; p0 < hi; p0 += kFinishPiece) {
         const int S = hi - p0 < kFinishPiece ? hi - p0 : kFinishPiece;
         const int nwords = (S + 31) >> 5;
@@ -832,14 +925,14 @@ __global__ __launch_bounds__(1024) void invert_scan_kernel(const InvertArgs a) {
     __syncthreads();
     for (int l0 = 0; l0 < nlist; l0 += 1024) {
         const int l = l0 + tid, v = l < nlist ? cnt[l] : 0;
-        int t = 0;
+        int t = 0, rt = 0;
         if (l < nlist && v > 0) {        // tiles of the filter: rows x queries
             int64_t s = a.list_offsets[l], e = a.list_offsets[l + 1];
             s = s < 0 ? 0 : (s > a.n ? a.n : s);
             e = e < s ? s : (e > a.n ? a.n : e);
             t = (int)((e - s + kFltRows - 1) / kFltRows) * ((v + kFltQ - 1) / kFltQ);
+            rt = (int)((e - s + kMsrRows - 1) / kMsrRows) * ((v + kMsrBlock - 1) / kMsrBlock);     // (measure)
         }
-        const int rt = (v > 0) ? t / ((v + kFltQ - 1) / kFltQ) : 0;      // rows alone (measure)
         int incl = v, tincl = t, rincl = rt;
 #pragma unroll
         for (int off = 1; off < kWave; off <<= 1) {

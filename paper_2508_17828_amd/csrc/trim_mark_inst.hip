@@ -1,4 +1,5 @@
 // The instances of the passes and their launchers (see trim_mark.h).
+#include <algorithm>
 #include <atomic>
 
 #include "trim_launch.h"
@@ -38,6 +39,28 @@ int launch_finish(const FinishArgs &a, int vec, bool fs, int threads, size_t lds
     return TRIM_OK;
 }
 
+template <bool VERIFY>
+static int launch_lut_as(const LutArgs &a, int dsub, bool fs, hipStream_t st) {
+    void (*fn)(const LutArgs) = fs ? lut_tile_kernel<2, true, VERIFY>
+                                : dsub == 4 ? lut_tile_kernel<4, false, VERIFY>
+                                : dsub == 8 ? lut_tile_kernel<8, false, VERIFY> : lut_tile_kernel<16, false, VERIFY>;
+    const int64_t entries = (int64_t)a.nsub * (fs ? kC4 : kC);
+    LutArgs b = a;
+    for (int64_t s0 = 0; s0 < a.nslots; s0 += (int64_t)kLutQueries * 65535) {       // (grid.y)
+        b.nslots = std::min<int64_t>(a.nslots - s0, (int64_t)kLutQueries * 65535);
+        b.slot0 = a.slot0 + s0;
+        if (a.by_slot) b.lut = a.lut + (size_t)s0 * entries;
+        hipLaunchKernelGGL(fn, dim3((unsigned)((entries + 255) / 256), (unsigned)((b.nslots + kLutQueries - 1) / kLutQueries)),
+                           dim3(256), 0, st, b);
+        HIP_TRY(hipGetLastError());
+    }
+    return TRIM_OK;
+}
+int launch_lut(const LutArgs &a, int dsub, bool fs, bool verify, hipStream_t st) {
+    if (!lut_tiled(dsub, fs)) return TRIM_UNSUPPORTED_SHAPE;
+    return verify ? launch_lut_as<true>(a, dsub, fs, st) : launch_lut_as<false>(a, dsub, fs, st);
+}
+
 int launch_totals(const FinishArgs &a, hipStream_t st) {
     hipLaunchKernelGGL(totals_kernel, dim3((unsigned)((a.nslots + 3) / 4)), dim3(256), 0, st, a);
     HIP_TRY(hipGetLastError());
@@ -52,24 +75,39 @@ int launch_filter_operands(const FilterArgs &a, hipStream_t st) {
     return TRIM_OK;
 }
 
-int launch_filter(const FilterArgs &a, hipStream_t st) {
-    const int64_t blocks = 256 * 2 * 4;      // (two per CU at a time)
-    void (*fn)(const FilterArgs) = nullptr;
-    if (a.ncent == kC4) fn = filter_kernel<2, true>;
-    else switch (a.padded) {
-        case 4: fn = filter_kernel<4, false>; break;
-        case 8: fn = filter_kernel<8, false>; break;
-        case 16: fn = filter_kernel<16, false>; break;
-        case 32: fn = filter_kernel<32, false>; break;
-        default: return TRIM_UNSUPPORTED_SHAPE;
+template <int AL>
+static void (*filter_of(const FilterArgs &a))(const FilterArgs) {
+    if (a.ncent == kC4) return filter_kernel<2, true, AL>;
+    switch (a.padded) {
+        case 4: return filter_kernel<4, false, AL>;
+        case 8: return filter_kernel<8, false, AL>;
+        case 16: return filter_kernel<16, false, AL>;
+        case 32: return filter_kernel<32, false, AL>;
+        default: return nullptr;
     }
+}
+int launch_filter(const FilterArgs &a, hipStream_t st) {
+    const int64_t blocks = 256 * 4;      // (one per CU at a time)
+    void (*fn)(const FilterArgs) = a.M % 8 == 0 ? filter_of<2>(a) : filter_of<1>(a);
+    if (!fn) return TRIM_UNSUPPORTED_SHAPE;
     hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(kFltThreads), 0, st, a);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
 }
 
 int launch_measure(const FilterArgs &a, hipStream_t st) {
-    hipLaunchKernelGGL(measure_kernel, dim3(256 * 2 * 4), dim3(kFltThreads), 0, st, a);
+    // 256 queries at a time where a row tile meets that many (rows are then read half as often: 500 queries x 300,000 x
+    // 960: 906 -> 547 us), else 128 and two workgroups per CU (2500 queries in 1024 lists, 768: 414 -> 405, 332 -> 285 us).
+    // Without lists the queries are cut finer while there are fewer row tiles than CUs.
+    const int64_t row_tiles = (std::min<int64_t>(a.n, a.hi) + kMsrRows - 1) / kMsrRows;
+    const bool few_rows = !a.list_offsets && row_tiles < 256;
+    const double share = a.list_offsets ? (double)a.nslots * a.nseg / a.nlist : (double)a.nslots;
+    const int wq = share >= 192.0 && !few_rows ? 4 : 2;
+    FilterArgs b = a;
+    b.msr_block = few_rows ? 64 * wq : kMsrBlock;
+    void (*fn)(const FilterArgs) = wq == 4 ? measure_kernel<4> : measure_kernel<2>;
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, a.d * 4));
+    hipLaunchKernelGGL(fn, dim3(256 * 4), dim3(256 * wq), (size_t)a.d * 4, st, b);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
 }

@@ -20,7 +20,9 @@ struct FinishArgs {
     const int32_t *order;
     int64_t slot0, nslots;    // this launch: places [slot0, slot0 + nslots) of the query order
     int32_t by_query;         // a query's rows of the workspace are at its number, else at its place less slot0
-    const float *lut;
+    const float *lut;         // tables by query number, or (lut_by_row) by row of the workspace; null: built here
+    int32_t lut_by_row;
+    const uint32_t *bad;      // by query number: the table is not the centroids' (or null)
     const int64_t *list_offsets;
     const int32_t *probes;
     int32_t nlist, nseg, max_cand;
@@ -45,6 +47,22 @@ struct FinishArgs {
     uint32_t off_q, off_segp, off_segd, off_bits, off_ring;
 };
 
+// Distance tables of many queries (lut_tile_kernel).
+constexpr int kLutQueries = 32;      // queries per workgroup
+inline bool lut_tiled(int dsub, bool fs) { return fs ? dsub == 2 : dsub == 4 || dsub == 8 || dsub == 16; }
+struct LutArgs {
+    const float *queries;
+    int64_t nq;
+    int32_t d;
+    const float *codebooks;
+    int32_t nsub;
+    const int32_t *order;
+    int64_t slot0, nslots;
+    int32_t by_slot;
+    float *lut;
+    uint32_t *bad;
+};
+
 // Which queries scan a list, and where: inv[start[l] .. start[l+1]) = (workspace row, scan-order number
 // of the list's first vector).
 struct InvertArgs {
@@ -67,7 +85,8 @@ struct InvertArgs {
 };
 
 // ---- filter: who can pass, on the matrix cores (see filter_kernel) ----
-constexpr int kFltRows = 256, kFltQ = 128, kFltThreads = 256, kFltSlice = 32;
+constexpr int kFltRows = 512, kFltQ = 128, kFltThreads = 512, kFltSlice = 32;
+constexpr int kMsrRows = 256, kMsrBlock = 512;        // measure: rows at a time, queries per task
 // Values per sub-vector after padding: what a 16-byte operand holds, a part or a multiple of it.
 __host__ __device__ inline int filter_padded(int dsub, bool fs) {
     if (fs) return dsub == 2 ? 2 : 0;
@@ -86,7 +105,7 @@ struct FilterArgs {
     int64_t slot0, nslots;
     int32_t by_query;
     const int64_t *list_offsets;
-    int32_t nlist;
+    int32_t nlist, nseg;
     const int32_t *inv_start;
     const int2 *inv;
     const int32_t *tasks, *row_tasks;
@@ -103,6 +122,7 @@ struct FilterArgs {
     // measure
     const float *base;
     float *d2;                 // [rows][words * 32]
+    int32_t msr_block;         // queries per task
     int32_t kpad_rows;         // d rounded up to kFltSlice
     _Float16 *q16_rows;        // [rows][kpad_rows]: q16 without the padding between sub-vectors (or q16 itself)
     int32_t padded, kpad;      // values per sub-vector, per vector (a multiple of kFltSlice)

@@ -92,6 +92,16 @@ def test_build_lut(T, oracle, name):
     np.testing.assert_array_equal(lut.cpu().numpy().view(np.uint32), ref.view(np.uint32))
 
 
+@pytest.mark.parametrize("d,M", [(4, 1), (100, 25), (24, 3), (128, 8)])
+@pytest.mark.parametrize("nq", [1, 31, 33, 130])
+def test_build_lut_around_its_tiles(T, oracle, d, M, nq):
+    import torch
+    g = np.random.default_rng(nq + d)
+    q, cb = g.standard_normal((nq, d), np.float32), g.standard_normal((M, 256, d // M), np.float32)
+    lut = T.trim_build_lut(torch.from_numpy(q).cuda(), torch.from_numpy(cb).cuda())
+    np.testing.assert_array_equal(lut.cpu().numpy().view(np.uint32), oracle.build_lut(q, cb).view(np.uint32))
+
+
 @pytest.mark.parametrize("name", ["c1", "c2s", "c3s", "c4s"])
 def test_build_lut_matrix_cores(T, oracle, name):
     # expanded form on the MFMA units: equal to the direct form up to rounding of the

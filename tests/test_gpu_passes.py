@@ -85,6 +85,8 @@ CASES = [
     (6000, 512, 16, 8, 10, 259, 4, 1, 7, 0.0, 0.5, 0.0),
     (10000, 512, 256, 4, 24, 400, 8, 10, 256, 0.4, 0.5, 0.0),
     (7000, 1536, 192, 8, 12, 261, 6, 64, 1000, 0.7, 0.1, 0.0),
+    (66000, 528, 44, 8, 0, 261, 0, 10, 512, 0.4, 0.3, 0.0),          # rows for every CU, sub-vectors of 12
+    (5000, 544, 136, 8, 5, 300, 4, 10, 512, 0.4, 0.3, 0.0),          # lists of more than one tile, 240 queries each
 ]
 
 
