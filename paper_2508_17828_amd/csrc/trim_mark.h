@@ -882,6 +882,7 @@ void finish_kernel(const FinishArgs a) {
                     }
                     __syncthreads();
                 }
+                __syncthreads();     // part[] is read (where nothing is marked no barrier has come since)
             }
         }
         for (int w = tid; w < nwords; w += T) {

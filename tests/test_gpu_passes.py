@@ -207,3 +207,45 @@ def test_range_in_passes_equals_the_single_kernel(T, case, percent):
                 np.testing.assert_array_equal(got[name].cpu().numpy()[rows], want[name].cpu().numpy()[rows], err_msg=name)
             for name in ("offsets", "ids", "d2"):
                 np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
+
+
+def host_index(ix):
+    """The same stored data for the oracle."""
+    from oracle import trim_oracle, trim_oracle_fs
+    a = lambda t: None if t is None else np.ascontiguousarray(t.cpu().numpy())
+    return (trim_oracle if ix.code_bits == 8 else trim_oracle_fs), \
+        (trim_oracle if ix.code_bits == 8 else trim_oracle_fs).Index(a(ix.base), a(ix.codes), a(ix.dlx), a(ix.codebooks), ids=a(ix.ids),
+                                                                     list_offsets=a(ix.list_offsets))
+
+
+# The bounds of a stretch are taken 16,384 candidates at a time where two workgroups share a CU, and a step that marks
+# nobody goes on to the next without listing anyone: a few vectors that matter, far behind tens of thousands that do not.
+@pytest.mark.parametrize("M,bits", ((32, 8), (256, 4)))
+def test_marks_that_begin_late(T, M, bits):
+    import torch
+    n, d, nq, k, batch, gamma = 70_000, 512, 260, 10, 512, 0.5
+    g = torch.Generator(device="cuda").manual_seed(n + M)
+    draw = lambda rows, far: (torch.randn((rows, d), device="cuda", generator=g) * 0.1 + far).contiguous()
+    near = torch.tensor(list(range(k)) + [17_000, 20_001, 32_767, 32_768, 51_200, 51_201, 69_999], device="cuda")
+    base = draw(n, 1.0)
+    base[near] = draw(near.numel(), 0.0)
+    queries = draw(nq, 0.0)
+    train = torch.cat((base[near], base[torch.randperm(n, device="cuda", generator=g)[:4000]])).contiguous()
+    init = torch.arange(256 if bits == 8 else 16, device="cuda", dtype=torch.int32)
+    cb = (T.trim_train_pq if bits == 8 else T.trim_fs_train_pq)(train, M, 2, init)
+    codes, dlx = (T.trim_encode if bits == 8 else T.trim_fs_encode)(base, cb)
+    ix = T.Index(base, codes, dlx, cb, code_bits=bits)
+    view = ix._view()
+    assert T.lib().trim_knn_workspace_bytes(C.byref(view), nq, None, k, batch) > 0
+    O, oix = host_index(ix)
+    want = O.search_knn(oix, queries.cpu().numpy(), k, gamma, batch, want_mask=True)
+    assert want["n_exact"].max() < 2000                    # the far ones are not marked
+    got = T.trim_search_knn(ix, queries, k, gamma, batch, want_mask=True)
+    for name in ("ids", "d2", "n_scanned", "n_exact", "mask"):
+        np.testing.assert_array_equal(got[name].cpu().numpy().view(want[name].dtype), want[name], err_msg=name)
+    radius = float(np.sqrt(want["d2"][:, -1].max()))
+    want = O.search_range(oix, queries.cpu().numpy(), radius, gamma, want_mask=True)
+    assert 0 < want["n_exact"].max() < 2000
+    got = T.trim_search_range(ix, queries, radius, gamma, want_mask=True)
+    for name in ("offsets", "ids", "d2", "n_scanned", "n_exact", "mask"):
+        np.testing.assert_array_equal(got[name].cpu().numpy().view(want[name].dtype), want[name], err_msg=name)
