@@ -109,6 +109,7 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
     __shared__ int hist[256], part[T / kWave];
     __shared__ uint32_t s_most, s_least;
     __shared__ int s_n, s_count, s_frozen;
+    __shared__ int s_nk;          // (the sorted ones are not counted in s_n: it is read while they already are)
     __shared__ float s_tau, s_tau_f;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t slot = blockIdx.x;
@@ -116,7 +117,7 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
     if (q < 0 || q >= a.nq) return;
     for (int t = tid; t < a.d; t += T) q_lds[t] = a.queries[(size_t)q * a.d + t];
     if (tid < 256) hist[tid] = 0;
-    if (tid == 0) { s_most = 0; s_least = ~0u; s_n = 0; s_count = 0; }
+    if (tid == 0) { s_most = 0; s_least = ~0u; s_n = 0; s_nk = 0; s_count = 0; }
     segment_table(a.list_offsets, a.probes, a.nlist, a.nseg, a.n, a.max_cand, q, segp, segd);
     const int total = a.totals[slot];
     const int ns = total < a.k ? total : a.k, fb = total < a.k + a.batch ? total : a.k + a.batch;
@@ -178,7 +179,6 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) least = min(least, (uint32_t)__shfl_xor((int)least, off));
     if (lane == 0) atomicMin(&s_least, least);
-    if (tid == 0) s_n = 0;
     __syncthreads();
     least = s_least;
     if (full) {                                  // (else all of them are wanted, as far as they go)
@@ -215,11 +215,11 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
         if (key <= cut) {
             const int pos = segment_position(c, segp, segd, a.nseg);
             const int32_t id = a.ids ? a.ids[pos] : pos;
-            s_key[atomicAdd(&s_n, 1)] = ((unsigned long long)key << 32) | ((uint32_t)id ^ 0x80000000u);   // (ids order as signed)
+            s_key[atomicAdd(&s_nk, 1)] = ((unsigned long long)key << 32) | ((uint32_t)id ^ 0x80000000u);   // (ids order as signed)
         }
     }
     __syncthreads();
-    nk = s_n;
+    nk = s_nk;
     if (nk <= kWave) {                           // (one wave, in registers)
         if (wave == 0) {
             unsigned long long key = lane < nk ? s_key[lane] : ~0ull;

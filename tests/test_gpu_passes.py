@@ -249,3 +249,24 @@ def test_marks_that_begin_late(T, M, bits):
     got = T.trim_search_range(ix, queries, radius, gamma, want_mask=True)
     for name in ("offsets", "ids", "d2", "n_scanned", "n_exact", "mask"):
         np.testing.assert_array_equal(got[name].cpu().numpy().view(want[name].dtype), want[name], err_msg=name)
+
+
+# Everyone of a first batch that is measured beside the bounds is a survivor (gamma 0, one landmark for all): the waves that count
+# and the one that goes on to sort must agree on how many there are.
+@pytest.mark.parametrize("k,batch", ((10, 4086), (64, 4032), (100, 1500), (1000, 3096)))
+def test_first_batches_of_many_survivors(T, k, batch):
+    import torch
+    n, d, M, nq = 5000, 64, 16, 40
+    g = torch.Generator(device="cuda").manual_seed(k + batch)
+    base = torch.randn((n, d), device="cuda", generator=g)
+    queries = torch.randn((nq, d), device="cuda", generator=g)
+    cb = torch.zeros((M, 256, d // M), device="cuda")
+    codes, dlx = T.trim_encode(base, cb)
+    ix = T.Index(base, codes, dlx, cb)
+    O, oix = host_index(ix)
+    want = O.search_knn(oix, queries.cpu().numpy(), k, 0.0, batch, want_mask=True)
+    assert want["n_exact"].max() > 0.9 * n
+    for _ in range(3):
+        got = T.trim_search_knn(ix, queries, k, 0.0, batch, want_mask=True)
+        for name in ("ids", "d2", "n_scanned", "n_exact", "mask"):
+            np.testing.assert_array_equal(got[name].cpu().numpy().view(want[name].dtype), want[name], err_msg=name)
