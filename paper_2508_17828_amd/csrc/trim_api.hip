@@ -486,6 +486,7 @@ constexpr double kSharedValues = 8192.0;      // values per row times queries pe
 constexpr size_t kKnnSlabBytes = size_t(8) << 30;
 bool worth_passes(const trim_index_view *ix, int64_t nq, const trim_candidates *cand) {
     if (nq <= kManyQueries || ix->n <= 0 || ix->d < kLongRow || !filter_padded(ix->d / ix->M, is_fs(ix))) return false;
+    if (measure_lds(ix->d, 2) > kLdsBytes) return false;
     const double share = cand ? (double)nq * cand->nprobe / cand->nlist : (double)nq;
     return share * ix->d >= kSharedValues;
 }

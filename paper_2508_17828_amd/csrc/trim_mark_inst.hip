@@ -102,7 +102,8 @@ int launch_measure(const FilterArgs &a, hipStream_t st) {
     const int64_t row_tiles = (std::min<int64_t>(a.n, a.hi) + kMsrRows - 1) / kMsrRows;
     const bool few_rows = !a.list_offsets && row_tiles < 256;
     const double share = a.list_offsets ? (double)a.nslots * a.nseg / a.nlist : (double)a.nslots;
-    const int wq = share >= 192.0 && !few_rows ? 4 : 2;
+    // (the means of more than 21,000 values leave the LDS no room for 256)
+    const int wq = share >= 192.0 && !few_rows && measure_lds(a.d, 4) <= kLdsBytes ? 4 : 2;
     FilterArgs b = a;
     b.msr_block = few_rows ? 64 * wq : kMsrBlock;
     void (*fn)(const FilterArgs) = wq == 4 ? measure_kernel<4> : measure_kernel<2>;

@@ -270,3 +270,21 @@ def test_first_batches_of_many_survivors(T, k, batch):
         got = T.trim_search_knn(ix, queries, k, 0.0, batch, want_mask=True)
         for name in ("ids", "d2", "n_scanned", "n_exact", "mask"):
             np.testing.assert_array_equal(got[name].cpu().numpy().view(want[name].dtype), want[name], err_msg=name)
+
+
+# Rows so long that the measure pass has no LDS for 256 queries at a time (24,576 values), or for 128 (26,752): the search is
+# done with fewer, or by the single kernel.
+@pytest.mark.parametrize("d,M", ((24576, 768), (26752, 836)))
+def test_the_longest_rows(T, d, M):
+    n, nq, nlist, nprobe, k, batch, gamma = 1500, 300, 3, 2, 10, 256, 0.4
+    ix, q, probes = built(T, n, d, M, 8, nlist, nq, nprobe, 0.3, 0.0, d)
+    for pr in (probes, None):
+        want = single_kernel(T, ix, q, k, gamma, batch, pr, None)
+        got = T.trim_search_knn(ix, q, k, gamma, batch, probes=pr, want_mask=True)
+        for name in ("ids", "d2", "n_scanned", "n_exact", "mask"):
+            np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
+        radius = float(np.sqrt(want["d2"][:, -1].cpu().numpy()[7:].max()))
+        want = single_range(T, ix, q, radius, gamma, pr, None, None)
+        got = T.trim_search_range(ix, q, radius, gamma, probes=pr, want_mask=True)
+        for name in ("offsets", "ids", "d2", "n_scanned", "n_exact", "mask"):
+            np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
