@@ -154,6 +154,17 @@ def _stream():
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
+def _scratch(need: int, device):
+    """Work space for an entry point that is faster with it and does without: (tensor, bytes), or (None, 0) where nothing is
+    wanted or there is no memory for it."""
+    if need:
+        try:
+            return torch.empty((need,), dtype=torch.uint8, device=device), need
+        except torch.cuda.OutOfMemoryError:
+            pass
+    return None, 0
+
+
 def _check(status: int, where: str):
     if status != 0:
         raise TrimError(status, where)
@@ -393,13 +404,7 @@ def trim_search_knn(index: Index, queries: torch.Tensor, k: int, gamma: float, b
     view = index._view()
     pcand = C.byref(cand) if cand is not None else None
     # work space for the search in passes, where the library wants it (see trim_search_knn_ws)
-    need = 0 if want_work else lib().trim_knn_workspace_bytes(C.byref(view), nq, pcand, k, batch)
-    ws = None
-    if need:
-        try:
-            ws = torch.empty((need,), dtype=torch.uint8, device=dev)
-        except torch.cuda.OutOfMemoryError:      # the single kernel does without
-            need = 0
+    ws, need = _scratch(0 if want_work else lib().trim_knn_workspace_bytes(C.byref(view), nq, pcand, k, batch), dev)
     _check(lib().trim_search_knn_ws(C.byref(view), _ptr(queries, torch.float32, "queries"), nq,
                                     _ptr(lut, torch.float32, "lut"), pcand, k, gamma, batch,
                                     _ptr(query_order, torch.int32, "query_order"),
@@ -463,13 +468,7 @@ def trim_search_range(index: Index, queries: torch.Tensor, radius: float, gamma:
             _check(lib().trim_search_range_static(*args, _stream()), "trim_search_range_static")
             return
         # scratch for the search in passes, where the library wants it (see trim_search_range_ws)
-        more = 0 if want_work else lib().trim_range_scratch_bytes(C.byref(view), nq, pcand)
-        scratch = None
-        if more:
-            try:
-                scratch = torch.empty((more,), dtype=torch.uint8, device=dev)
-            except torch.cuda.OutOfMemoryError:      # the single kernel does without
-                more = 0
+        scratch, more = _scratch(0 if want_work else lib().trim_range_scratch_bytes(C.byref(view), nq, pcand), dev)
         _check(lib().trim_search_range_ws(*args, workspace.data_ptr(), workspace.numel(),
                                           _ptr(scratch, torch.uint8, "scratch"), more, _stream()), "trim_search_range")
 
@@ -502,8 +501,7 @@ def trim_ivf_probe(queries: torch.Tensor, centroids: torch.Tensor, nprobe: int) 
     nq, d = queries.shape
     nlist = centroids.shape[0]
     probes = torch.empty((nq, nprobe), dtype=torch.int32, device=queries.device)
-    need = lib().trim_ivf_probe_workspace_bytes(nq, d, nlist, nprobe)
-    ws = torch.empty((need,), dtype=torch.uint8, device=queries.device) if need else None
+    ws, need = _scratch(lib().trim_ivf_probe_workspace_bytes(nq, d, nlist, nprobe), queries.device)
     _check(lib().trim_ivf_probe_ws(_ptr(queries, torch.float32, "queries"), nq, d,
                                    _ptr(centroids, torch.float32, "centroids"), nlist,
                                    nprobe, _ptr(probes, torch.int32, "probes"), _ptr(ws, torch.uint8, "workspace"), need,

@@ -288,3 +288,34 @@ def test_the_longest_rows(T, d, M):
         got = T.trim_search_range(ix, q, radius, gamma, probes=pr, want_mask=True)
         for name in ("offsets", "ids", "d2", "n_scanned", "n_exact", "mask"):
             np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
+
+
+# A GPU without room for the work space: the single kernels do without it.
+@pytest.mark.parametrize("nq", (1, 300))
+def test_no_memory_for_the_work_space(T, nq, monkeypatch):
+    import torch
+    ix, queries, probes = built(T, 12000, 512, 128, 8, 70, 300, 12, 0.5, 0.0, 3)
+    cent = ix.base[torch.randperm(12000, device="cuda")[:70]].contiguous()
+    q, pr = queries[:nq].contiguous(), probes[:nq].contiguous()
+    radius = float(torch.cdist(q, ix.base).quantile(0.01, dim=1).max().cpu())
+    keep = torch.empty((T.trim_range_workspace_bytes(nq, 12000),), dtype=torch.uint8, device="cuda")
+
+    def all_three():
+        r = T.trim_search_range(ix, q, radius, 0.4, probes=pr, workspace=keep, capacity=3_000_000)
+        s = T.trim_search_knn(ix, q, 10, 0.4, 512, probes=pr)
+        return T.trim_ivf_probe(q, cent, 9), s["ids"], s["d2"], s["n_exact"], r["offsets"], r["ids"], r["d2"]
+
+    assert T.lib().trim_ivf_probe_workspace_bytes(nq, 512, 70, 9) > 0
+    want = all_three()
+    empty = torch.empty
+
+    def full(*size, **kw):
+        if kw.get("dtype") is torch.uint8:
+            raise torch.cuda.OutOfMemoryError("no room")
+        return empty(*size, **kw)
+
+    monkeypatch.setattr(torch, "empty", full)
+    got = all_three()
+    monkeypatch.undo()
+    for a, b in zip(got, want):
+        np.testing.assert_array_equal(a.cpu().numpy(), b.cpu().numpy())
