@@ -1868,7 +1868,7 @@ __global__ __launch_bounds__(kAsgThreads) void assign_mfma_kernel(const float *_
     for (int u = 0; u < 2; ++u)
 #pragma unroll
         for (int t = 0; t < 4; ++t) { m1[u][t] = m2[u][t] = 0x7f800000u; i1[u][t] = 0; }
-    float cmax2 = 0.0f;
+    uint32_t cmax2 = 0;        // (bit patterns: a centroid that is no number is the largest, and everybody is measured exactly)
     const int nblk = (nlist + kAsgTile - 1) / kAsgTile, nk = dpad / kAsgSlice;
     for (int cb = 0; cb < nblk; ++cb) {
         const int cr = cb * kAsgTile + srow;
@@ -1916,7 +1916,7 @@ __global__ __launch_bounds__(kAsgThreads) void assign_mfma_kernel(const float *_
         if (sstep == 0) {
             xn2[srow] = xsum;
             cn2[srow] = cr < nlist ? csum : __builtin_inff();     // (rows past the end never win)
-            if (cr < nlist) cmax2 = __builtin_fmaxf(cmax2, csum);
+            if (cr < nlist) cmax2 = max(cmax2, __float_as_uint(csum));
         }
         __syncthreads();
 #pragma unroll
@@ -1947,7 +1947,7 @@ __global__ __launch_bounds__(kAsgThreads) void assign_mfma_kernel(const float *_
     uint32_t *t1 = reinterpret_cast<uint32_t *>(smem), *t2 = t1 + 16 * kAsgTile;
     int *tc = reinterpret_cast<int *>(t2 + 16 * kAsgTile);
     uint32_t *amb = reinterpret_cast<uint32_t *>(tc + 16 * kAsgTile);      // [256] (trackers << 8) | vector
-    atomicMax(cmax_bits, __float_as_uint(cmax2));
+    atomicMax(cmax_bits, cmax2);
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll

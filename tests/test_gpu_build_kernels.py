@@ -143,3 +143,19 @@ def test_probe_of_few_queries(T, oracle, nq, nlist, d, nprobe):
     want = oracle.ivf_probe(q, cent, nprobe)
     got = T.trim_ivf_probe(torch.from_numpy(q).cuda(), torch.from_numpy(cent).cuda(), nprobe).cpu().numpy()
     np.testing.assert_array_equal(got, want)
+
+
+def test_nearest_list_with_centroids_that_are_no_numbers():
+    """A centroid that is no number (its list held such a row in training) is nobody's nearest; infinite ones neither."""
+    import torch
+    from paper_2508_17828_amd import trim as T
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.randn((5000, 64), device="cuda", generator=g)
+    cent = torch.randn((70, 64), device="cuda", generator=g)
+    for bad in (float("nan"), -float("nan"), float("inf")):
+        c = cent.clone()
+        c[5, 3] = bad
+        few = torch.cat([T.trim_ivf_probe(x[i:i + 1000].contiguous(), c, 1) for i in range(0, 5000, 1000)])
+        many = T.trim_ivf_probe(x, c, 1)
+        assert not (few == 5).any()
+        assert torch.equal(many, few)
