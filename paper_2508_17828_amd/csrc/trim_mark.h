@@ -59,10 +59,11 @@ __global__ __launch_bounds__(256) void filter_means_kernel(const FilterArgs a) {
     for (int off = 32; off > 0; off >>= 1) most = __builtin_fmaxf(most, __shfl_xor(most, off));
     if ((c & 63) == 0) atomicMax(a.max_bits, __float_as_uint(most));
 }
-// The power of two that brings the largest centered centroid value to 2^9 .. 2^10.
+// The power of two that brings the largest centered centroid value to 2^9 .. 2^10.  From 1e18 on its square leaves the
+// binary32 range and the measured distances could not be scaled back; below, a square above the range only makes them 0.
 __device__ __forceinline__ float filter_scale(uint32_t max_bits) {
     const float m = __uint_as_float(max_bits);
-    if (!(m > 1e-30f && m < 1e30f)) return 0.0f;           // (no scale: everything is marked)
+    if (!(m > 1e-30f && m < 1e18f)) return 0.0f;           // (no scale: everything is marked)
     const int k = 9 - ((int)(max_bits >> 23) - 127);
     return __uint_as_float((uint32_t)(k + 127) << 23);
 }
@@ -241,7 +242,8 @@ __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs
         {
             float b = 0.0f;
             if (tid < nrows) b = a.dlx[r0 + tid];
-            s_b[tid] = b * sc;
+            const float bs = b * sc;
+            s_b[tid] = bs < 1e30f ? bs : __builtin_nanf("");       // (marked: the line would fall to -inf there)
             float sum = b;
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);

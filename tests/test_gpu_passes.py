@@ -319,3 +319,28 @@ def test_no_memory_for_the_work_space(T, nq, monkeypatch):
     monkeypatch.undo()
     for a, b in zip(got, want):
         np.testing.assert_array_equal(a.cpu().numpy(), b.cpu().numpy())
+
+
+def test_centroids_far_apart(T):
+    """Two groups of vectors 1e23 apart: the scale of the 16-bit operands comes from the distance between them, and its
+    square is no binary32 number any more."""
+    import torch
+    n, d, M, nq, k, batch, gamma = 6000, 512, 128, 300, 10, 256, 0.3
+    g = torch.Generator(device="cuda").manual_seed(5)
+    base = torch.randn((n, d), device="cuda", generator=g)
+    base[1::2] += 1e23
+    queries = torch.randn((nq, d), device="cuda", generator=g)
+    init = torch.arange(256, device="cuda", dtype=torch.int32)
+    cb = T.trim_train_pq(base[:4096].contiguous(), M, 0, init)
+    codes, dlx = T.trim_encode(base, cb)
+    ix = T.Index(base, codes, dlx, cb)
+    O, oix = host_index(ix)
+    want = O.search_knn(oix, queries.cpu().numpy(), k, gamma, batch, want_mask=True)
+    got = T.trim_search_knn(ix, queries, k, gamma, batch, want_mask=True)
+    for name in ("ids", "d2", "n_scanned", "n_exact", "mask"):
+        np.testing.assert_array_equal(got[name].cpu().numpy().view(want[name].dtype), want[name], err_msg=name)
+    radius = float(np.sqrt(want["d2"][:, -1].max()))
+    want = O.search_range(oix, queries.cpu().numpy(), radius, gamma, want_mask=True)
+    got = T.trim_search_range(ix, queries, radius, gamma, want_mask=True)
+    for name in ("offsets", "ids", "d2", "n_scanned", "n_exact", "mask"):
+        np.testing.assert_array_equal(got[name].cpu().numpy().view(want[name].dtype), want[name], err_msg=name)
