@@ -878,7 +878,8 @@ void finish_kernel(const FinishArgs a) {
                         float keep = sum;
                         if (last) {
                             keep = plb_from_s(sum, b1, a.two_gamma);
-                            if (!(keep <= tau)) atomicAnd(&bits[cl >> 5], ~(1u << (cl & 31)));
+                            // (the seed is measured whatever its bounds, also where they are no numbers)
+                            if (!a.all && !(keep <= tau)) atomicAnd(&bits[cl >> 5], ~(1u << (cl & 31)));
                         }
                         row_g[p0 + cl] = keep;
                     }

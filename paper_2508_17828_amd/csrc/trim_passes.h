@@ -30,7 +30,7 @@ struct FinishArgs {
     float two_gamma;
     // this pass: candidates [lo, hi) of every query
     int32_t lo, hi;
-    int32_t all;              // every candidate of the pass counts as marked
+    int32_t all;              // every candidate of the pass counts as marked, and stays it
     int32_t range;            // the threshold is radius2; else tau_of[q * tau_stride], or +inf where tau_of is null
     float radius2;
     const float *tau_of;

@@ -344,3 +344,66 @@ def test_centroids_far_apart(T):
     got = T.trim_search_range(ix, queries, radius, gamma, want_mask=True)
     for name in ("offsets", "ids", "d2", "n_scanned", "n_exact", "mask"):
         np.testing.assert_array_equal(got[name].cpu().numpy().view(want[name].dtype), want[name], err_msg=name)
+
+
+def plant(what, ix, q, table):
+    """Infinities, NaN and values out of every 16-bit range where they do harm: among the seeds, in the first batch and later."""
+    at = [2, 7, 40, 300, 700, 2000, 4999, 5003, 6000]
+    nan, inf = float("nan"), float("inf")
+    if what == "landmark distances":            # (as they come out for rows that hold such values)
+        ix.dlx[at[0::3]] = nan
+        ix.dlx[at[1::3]] = inf
+        ix.dlx[at[2::3]] = 1e30
+    elif what == "rows":                        # (landmark distances of other rows)
+        ix.base[at[0::3], 5] = nan
+        ix.base[at[1::3], 6] = inf
+        ix.base[at[2::3], 7] = -1e30
+    elif what == "queries":
+        q[3, 5] = nan
+        q[9, 100] = inf
+        q[11, 200] = -1e30
+        q[12] = 1e25
+        q[13] *= 1e-30
+    elif what == "centroids":
+        ix.codebooks[0, 7] = nan
+        ix.codebooks[3, 11, 1] = inf
+        ix.codebooks[4, 12, 2] = 1e25
+    elif what == "table":
+        table[3, 0, ::7] = nan
+        table[5, 1, ::9] = inf
+        table[8] = inf
+        table[9] = nan
+
+
+SPECIAL = ("landmark distances",)
+
+
+@pytest.mark.parametrize("lists", (False, True))
+@pytest.mark.parametrize("nq", (300, 20))
+@pytest.mark.parametrize("what", SPECIAL)
+def test_values_that_are_no_numbers(T, what, nq, lists):
+    """The passes (300 queries) and the search of few queries against the single kernel, and against the oracle where every
+    distance is a number."""
+    n, d, M, gamma = 7000, 512, 128, 0.4
+    ix, q, probes = built(T, n, d, M, 8, 12 if lists else 0, nq, 7 if lists else 0, 0.5, 0.0, 11)
+    ix.list_bounds = None
+    table = T.trim_build_lut(q, ix.codebooks) if what == "table" else None
+    plant(what, ix, q, table)
+    ix.scan_head = T.trim_pack_scan_head(ix.codes, ix.dlx)
+    for k, batch in ((10, 512), (100, 3000), (10, 1)):
+        want = single_kernel(T, ix, q, k, gamma, batch, probes, None, table)
+        if what == "landmark distances" and not lists:
+            O, oix = host_index(ix)
+            ref = O.search_knn(oix, q.cpu().numpy(), k, gamma, batch, want_mask=True)
+            for name in ("ids", "d2", "n_scanned", "n_exact", "mask"):
+                np.testing.assert_array_equal(want[name].cpu().numpy().view(ref[name].dtype), ref[name], err_msg=name)
+        got = T.trim_search_knn(ix, q, k, gamma, batch, probes=probes, lut=table, want_mask=True)
+        for name in ("ids", "d2", "n_scanned", "n_exact", "mask"):
+            np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=f"{name}, {k}, {batch}")
+    if nq < 300:
+        return
+    for radius in (float(np.sqrt(np.nanmedian(want["d2"].cpu().numpy()))), float("inf")):
+        want = single_range(T, ix, q, radius, gamma, probes, None, table)
+        got = T.trim_search_range(ix, q, radius, gamma, probes=probes, lut=table, want_mask=True)
+        for name in ("offsets", "ids", "d2", "n_scanned", "n_exact", "mask"):
+            np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=f"{name}, {radius}")
