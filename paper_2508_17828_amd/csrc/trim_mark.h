@@ -1144,7 +1144,8 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                 if (most) atomicMax(&s_most, most);
                 if (tid == 0) s_ntodo = 0;
                 __syncthreads();
-                const float cut = first == a.k ? __uint_as_float(s_most) : __builtin_inff();
+                // (a distance that is no number bounds nothing)
+                const float cut = first == a.k && s_most <= 0x7f800000u ? __uint_as_float(s_most) : __builtin_inff();
                 int more = 0;                         // bounds are ascending: a prefix
                 for (int i = first + tid; i < nc; i += kReplayThreads) {
                     const bool need = __uint_as_float((uint32_t)(s_key[i] >> 32)) <= cut;
@@ -1169,8 +1170,9 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                 sort_keys(s_key, size);
                 const int have = nc + ns < a.k ? nc + ns : a.k;
                 for (int i = tid; i < kWave * E; i += kReplayThreads) {
-                    rd2[i] = i < have ? __uint_as_float((uint32_t)(s_key[i] >> 32)) : __builtin_inff();
-                    rid[i] = i < have ? (int32_t)((uint32_t)s_key[i] ^ 0x80000000u) : kEmptyId;
+                    const bool in = i < have && (uint32_t)(s_key[i] >> 32) <= 0x7f800000u;      // (what is no number sorts last)
+                    rd2[i] = in ? __uint_as_float((uint32_t)(s_key[i] >> 32)) : __builtin_inff();
+                    rid[i] = in ? (int32_t)((uint32_t)s_key[i] ^ 0x80000000u) : kEmptyId;
                 }
                 __syncthreads();
                 if (wave == 0) R.load(rd2, rid, a.k, lane);

@@ -375,7 +375,7 @@ def plant(what, ix, q, table):
         table[9] = nan
 
 
-SPECIAL = ("landmark distances",)
+SPECIAL = ("landmark distances", "rows", "queries", "centroids", "table")
 
 
 @pytest.mark.parametrize("lists", (False, True))
