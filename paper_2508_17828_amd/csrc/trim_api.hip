@@ -491,6 +491,16 @@ bool worth_passes(const trim_index_view *ix, int64_t nq, const trim_candidates *
     return share * ix->d >= kSharedValues;
 }
 
+// The passes count (query, list) pairs and tiles in 32 bits, and number the 16-byte pieces of the queries' 16-bit operands
+// by as many.  mc: candidates per query.  A list that v queries scan has at most (mc / 256 + 1) (v / 128 + 1) tiles, v adding up to
+// the pairs.
+bool counts_fit(const trim_index_view *ix, int64_t rows, const trim_candidates *cand, int64_t mc) {
+    const double pairs = (double)rows * (cand ? cand->nprobe : 1), lists = cand ? cand->nlist : 1;
+    const double reach = (double)std::min(mc, ix->n);
+    const double tiles = (reach / kMsrRows + 1) * (pairs / kFltQ + 1) + (double)ix->n / kMsrRows + lists;
+    return pairs < 2147483648.0 && tiles < 2147483648.0 && (double)rows * (ix->d + 2 * kFltSlice) / 8 < 4294967296.0;
+}
+
 inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Work space of the filter and measure passes for `rows` queries (offsets from `at`; 0 bytes: shape without a filter).
@@ -535,7 +545,7 @@ FilterLayout filter_layout(const trim_index_view *ix, int64_t rows, int64_t rows
 void fill_filter(FilterArgs &f, InvertArgs &v, const trim_index_view *ix, const SearchArgs &a, const FilterLayout &L, unsigned char *ws) {
     if (a.nseg > 0) {
         v.probes = a.probes; v.nq = a.nq; v.order = a.order; v.nseg = a.nseg; v.nlist = a.nlist;
-        v.list_offsets = a.list_offsets; v.n = a.n;
+        v.list_offsets = a.list_offsets; v.n = a.n; v.max_cand = a.max_cand;
         v.cnt = reinterpret_cast<int32_t *>(ws + L.off_cnt);
         v.start = reinterpret_cast<int32_t *>(ws + L.off_start);
         v.inv = reinterpret_cast<int2 *>(ws + L.off_inv);
@@ -600,7 +610,7 @@ KnnLayout knn_layout(const trim_index_view *ix, int64_t nq, const trim_candidate
     L.words = (mc + 31) / 32 + 1;
     const size_t per = (size_t)L.words * (4 + 32 * 8) + 4 + filter_bytes_per_query(ix, cand);
     L.slab = std::min<int64_t>((int64_t)(kKnnSlabBytes / per), std::min<int64_t>(nq, 1 << 20));
-    if (L.slab < 64) { L.slab = 0; return L; }
+    if (L.slab < 64 || !counts_fit(ix, L.slab, cand, mc)) { L.slab = 0; return L; }
     size_t off = up256((size_t)L.slab * 4);
     L.off_possible = off; off += up256((size_t)L.slab * L.words * 4);
     L.off_g = off;        off += up256((size_t)L.slab * L.words * 32 * 4);
@@ -794,7 +804,7 @@ int range_fill(const SearchArgs &a, const RangeLayout &L, unsigned char *ws, int
 
 // Scratch of a range search in passes: totals, then the filter's operands.  0: such a search runs as one kernel.
 size_t range_scratch_bytes(const trim_index_view *ix, int64_t nq, const trim_candidates *cand) {
-    if (!worth_passes(ix, nq, cand)) return 0;
+    if (!worth_passes(ix, nq, cand) || !counts_fit(ix, nq, cand, cand && cand->max_candidates > 0 ? cand->max_candidates : ix->n)) return 0;
     return filter_layout(ix, nq, nq, cand, up256((size_t)nq * 4)).end;
 }
 

@@ -934,8 +934,9 @@ __global__ __launch_bounds__(1024) void invert_scan_kernel(const InvertArgs a) {
             int64_t s = a.list_offsets[l], e = a.list_offsets[l + 1];
             s = s < 0 ? 0 : (s > a.n ? a.n : s);
             e = e < s ? s : (e > a.n ? a.n : e);
-            t = (int)((e - s + kFltRows - 1) / kFltRows) * ((v + kFltQ - 1) / kFltQ);
-            rt = (int)((e - s + kMsrRows - 1) / kMsrRows) * ((v + kMsrBlock - 1) / kMsrBlock);     // (measure)
+            const int64_t len = e - s < a.max_cand ? e - s : a.max_cand;       // (no query comes further; see counts_fit)
+            t = (int)((len + kFltRows - 1) / kFltRows) * ((v + kFltQ - 1) / kFltQ);
+            rt = (int)((len + kMsrRows - 1) / kMsrRows) * ((v + kMsrBlock - 1) / kMsrBlock);     // (measure)
         }
         int incl = v, tincl = t, rincl = rt;
 #pragma unroll

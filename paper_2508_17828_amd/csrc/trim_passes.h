@@ -70,7 +70,7 @@ struct InvertArgs {
     int64_t nq;
     const int32_t *order;
     int64_t slot0, nslots;
-    int32_t by_query, nseg, nlist;
+    int32_t by_query, nseg, nlist, max_cand;
     const int64_t *list_offsets;
     int64_t n;
     int32_t *cnt;      // [nlist], zero; then the running slots

@@ -79,6 +79,28 @@ def test_host_side_validation(L):
     assert L.trim_ceiling_stream_read(None, 1024, 8, None, None) == -1
 
 
+def view_of(n, d, M, codebooks=1024):
+    from paper_2508_17828_amd import trim
+    return trim._IndexView(n, d, M, 1024, 1024, 1024, None, codebooks, None, None, 8)
+
+
+def cand_of(nlist, nprobe, max_candidates):
+    from paper_2508_17828_amd import trim
+    return trim._Candidates(nlist, nprobe, 1024, 1024, max_candidates, None)
+
+
+def test_searches_too_large_for_32_bit_counts_do_not_run_in_passes(L):
+    """(query, list) pairs are counted in 32 bits, the operands of the queries addressed by as many."""
+    view, cand = view_of(4096, 512, 32), cand_of(2048, 2048, 4096)
+    assert L.trim_range_scratch_bytes(C.byref(view), 1_000_000, C.byref(cand)) > 0
+    assert L.trim_range_scratch_bytes(C.byref(view), 1_048_576, C.byref(cand)) == 0      # 2^31 pairs
+    view = view_of(2048, 20480, 640)
+    assert L.trim_range_scratch_bytes(C.byref(view), 1_600_000, None) > 0
+    assert L.trim_range_scratch_bytes(C.byref(view), 1_700_000, None) == 0               # 2^32 pieces of operands
+    assert L.trim_range_scratch_bytes(C.byref(view_of(10_000_000, 512, 32)), 4_000_000, None) > 0
+    assert L.trim_range_scratch_bytes(C.byref(view_of(20_000_000, 512, 32)), 4_000_000, None) == 0      # 2^31 tiles
+
+
 def test_product_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_2508_17828_amd")
     for dirpath, _, files in os.walk(pkg):
