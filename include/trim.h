@@ -308,7 +308,9 @@ int trim_search_knn(const trim_index_view *index, const float *queries, int64_t 
  * passes keep a bit and two binary32 values per (query, candidate) pair in the work space,
  * query sets being split so that it stays below about 8 GiB.
  * trim_knn_workspace_bytes: the bytes such a search wants, or 0 where the single kernel of
- * trim_search_knn is the better way (a host function of the sizes in its arguments).
+ * trim_search_knn is the better way (a host function of the sizes in its arguments; of the pointers only whether
+ * index->codebooks is given, which many queries in passes need).  A caller's table (lut) of sub-vectors of other than 4, 8 or 16
+ * values (2 with 4-bit codes) keeps many queries on the single kernel: ask without codebooks to learn what is used then.
  * workspace: device, 256-byte aligned, contents on entry ignored; NULL or fewer bytes than that:
  * exactly trim_search_knn.  A search that keeps the work counters (trim_stats.work) runs as the
  * single kernel.

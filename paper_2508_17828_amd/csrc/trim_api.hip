@@ -486,7 +486,6 @@ constexpr double kSharedValues = 8192.0;      // values per row times queries pe
 constexpr size_t kKnnSlabBytes = size_t(8) << 30;
 bool worth_passes(const trim_index_view *ix, int64_t nq, const trim_candidates *cand) {
     if (nq <= kManyQueries || ix->n <= 0 || ix->d < kLongRow || !filter_padded(ix->d / ix->M, is_fs(ix))) return false;
-    if (measure_lds(ix->d, 2) > kLdsBytes) return false;
     const double share = cand ? (double)nq * cand->nprobe / cand->nlist : (double)nq;
     return share * ix->d >= kSharedValues;
 }
@@ -499,6 +498,13 @@ bool counts_fit(const trim_index_view *ix, int64_t rows, const trim_candidates *
     const double reach = (double)std::min(mc, ix->n);
     const double tiles = (reach / kMsrRows + 1) * (pairs / kFltQ + 1) + (double)ix->n / kMsrRows + lists;
     return pairs < 2147483648.0 && tiles < 2147483648.0 && (double)rows * (ix->d + 2 * kFltSlice) / 8 < 4294967296.0;
+}
+
+// What else a search in passes needs: room in the LDS for every one of them, and the centroids.
+bool passes_fit(const trim_index_view *ix, const trim_candidates *cand, int k, FinishPlan *fp) {
+    const int nseg = cand ? cand->nprobe : 0;
+    return ix->codebooks && make_finish_plan(ix->d, code_bytes(ix), is_fs(ix), nseg, fp) &&
+           replay_lds(ix->d, k, nseg) <= kLdsBytes && measure_lds(ix->d, 2) <= kLdsBytes;
 }
 
 inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -601,11 +607,11 @@ struct KnnLayout {
     FilterLayout f;
     size_t off_possible, off_g, off_d2, total;   // totals at 0
 };
-KnnLayout knn_layout(const trim_index_view *ix, int64_t nq, const trim_candidates *cand) {
+KnnLayout knn_layout(const trim_index_view *ix, int64_t nq, const trim_candidates *cand, int k, FinishPlan *fp) {
     KnnLayout L{};
     const int64_t hard = (int64_t(1) << 31) - 1 - TRIM_MAX_BATCH - 2048;
     int64_t mc = cand ? cand->max_candidates : ix->n;
-    if (mc <= 0 || mc > ix->n + (int64_t)(cand ? cand->nprobe : 0) * ix->n || !worth_passes(ix, nq, cand)) return L;
+    if (mc <= 0 || mc > ix->n + (int64_t)(cand ? cand->nprobe : 0) * ix->n || !worth_passes(ix, nq, cand) || !passes_fit(ix, cand, k, fp)) return L;
     if (mc > hard) mc = hard;
     L.words = (mc + 31) / 32 + 1;
     const size_t per = (size_t)L.words * (4 + 32 * 8) + 4 + filter_bytes_per_query(ix, cand);
@@ -768,10 +774,9 @@ int search_knn(const trim_index_view *index, const float *queries, int64_t nq, c
     if (workspace && !a.work && (reinterpret_cast<uintptr_t>(workspace) & 255u) == 0 && aligned16(queries)) {
         const FewLayout F = few_layout(index, nq, cand, k, batch);
         if (F.stride > 0 && workspace_bytes >= F.total) return knn_few(index, F, a, static_cast<unsigned char *>(workspace), st);
-        const KnnLayout L = knn_layout(index, nq, cand);
         FinishPlan fp;
-        if (L.slab > 0 && workspace_bytes >= L.total && index->codebooks && (!lut || lut_tiled(a.dsub, is_fs(index))) &&
-            make_finish_plan(index->d, a.M, is_fs(index), a.nseg, &fp) && replay_lds(index->d, k, a.nseg) <= kLdsBytes)
+        const KnnLayout L = knn_layout(index, nq, cand, k, &fp);
+        if (L.slab > 0 && workspace_bytes >= L.total && (!lut || lut_tiled(a.dsub, is_fs(index))))
             return knn_in_passes(index, L, a, fp, static_cast<unsigned char *>(workspace), st);
     }
     const int64_t slots = (nq + kXcds - 1) / kXcds * kXcds;
@@ -803,8 +808,8 @@ int range_fill(const SearchArgs &a, const RangeLayout &L, unsigned char *ws, int
 }
 
 // Scratch of a range search in passes: totals, then the filter's operands.  0: such a search runs as one kernel.
-size_t range_scratch_bytes(const trim_index_view *ix, int64_t nq, const trim_candidates *cand) {
-    if (!worth_passes(ix, nq, cand) || !counts_fit(ix, nq, cand, cand && cand->max_candidates > 0 ? cand->max_candidates : ix->n)) return 0;
+size_t range_scratch_bytes(const trim_index_view *ix, int64_t nq, const trim_candidates *cand, FinishPlan *fp) {
+    if (!worth_passes(ix, nq, cand) || !passes_fit(ix, cand, 1, fp) || !counts_fit(ix, nq, cand, cand && cand->max_candidates > 0 ? cand->max_candidates : ix->n)) return 0;
     return filter_layout(ix, nq, nq, cand, up256((size_t)nq * 4)).end;
 }
 
@@ -868,10 +873,9 @@ int range_search(const trim_index_view *index, const float *queries, int64_t nq,
 
     a.nq = nq;
     FinishPlan fpl;
-    const size_t want = range_scratch_bytes(index, nq, cand);
+    const size_t want = range_scratch_bytes(index, nq, cand, &fpl);
     if (scratch && want > 0 && scratch_bytes >= want && !a.work && (reinterpret_cast<uintptr_t>(scratch) & 255u) == 0 &&
-        aligned16(queries) && index->codebooks && (!lut || lut_tiled(a.dsub, is_fs(index))) && make_finish_plan(index->d, a.M, is_fs(index), a.nseg, &fpl) &&
-        replay_lds(index->d, 1, a.nseg) <= kLdsBytes) {
+        aligned16(queries) && (!lut || lut_tiled(a.dsub, is_fs(index)))) {
         unsigned char *sc = static_cast<unsigned char *>(scratch);
         // (rows of the work space by query number; a query that the order does not name has no candidates)
         if (query_order) z.add(sc, (size_t)nq);
@@ -1264,7 +1268,8 @@ int trim_search_knn(const trim_index_view *index, const float *queries, int64_t 
 size_t trim_knn_workspace_bytes(const trim_index_view *index, int64_t nq, const trim_candidates *cand, int32_t k, int32_t batch) {
     if (check_index(index) || check_cand(cand) || nq <= 0 || k < 1 || batch < 1) return 0;
     const FewLayout F = few_layout(index, nq, cand, k, batch);
-    return F.stride > 0 ? F.total : knn_layout(index, nq, cand).total;
+    FinishPlan fp;
+    return F.stride > 0 ? F.total : knn_layout(index, nq, cand, k, &fp).total;
 }
 
 int trim_search_knn_ws(const trim_index_view *index, const float *queries, int64_t nq,
@@ -1314,7 +1319,8 @@ int trim_search_range_static(const trim_index_view *index, const float *queries,
 
 size_t trim_range_scratch_bytes(const trim_index_view *index, int64_t nq, const trim_candidates *cand) {
     if (check_index(index) || check_cand(cand) || nq <= 0) return 0;
-    return range_scratch_bytes(index, nq, cand);
+    FinishPlan fp;
+    return range_scratch_bytes(index, nq, cand, &fp);
 }
 
 int trim_search_range_ws(const trim_index_view *index, const float *queries, int64_t nq,

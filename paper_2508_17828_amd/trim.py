@@ -207,6 +207,14 @@ class Index:
                           _ptr(self.scan_head, torch.uint8, "scan_head"),
                           _ptr(self.codes_tiled, torch.uint8, "codes_tiled"), self.code_bits)
 
+    def _size_view(self, lut: Optional[torch.Tensor]) -> _IndexView:
+        """What the size functions are asked about: a caller's tables can be compared with the centroids, which the passes
+        need, for sub-vectors of 4, 8 and 16 values (2 with 4-bit codes); with others the centroids may as well not be there."""
+        view = self._view()
+        if lut is not None and self.d // self.M not in ((2,) if self.code_bits == 4 else (4, 8, 16)):
+            view.codebooks = None
+        return view
+
     def _cand(self, probes: Optional[torch.Tensor], max_candidates: int = 0):
         if probes is None:
             return None, self.n
@@ -404,7 +412,7 @@ def trim_search_knn(index: Index, queries: torch.Tensor, k: int, gamma: float, b
     view = index._view()
     pcand = C.byref(cand) if cand is not None else None
     # work space for the search in passes, where the library wants it (see trim_search_knn_ws)
-    ws, need = _scratch(0 if want_work else lib().trim_knn_workspace_bytes(C.byref(view), nq, pcand, k, batch), dev)
+    ws, need = _scratch(0 if want_work else lib().trim_knn_workspace_bytes(C.byref(index._size_view(lut)), nq, pcand, k, batch), dev)
     _check(lib().trim_search_knn_ws(C.byref(view), _ptr(queries, torch.float32, "queries"), nq,
                                     _ptr(lut, torch.float32, "lut"), pcand, k, gamma, batch,
                                     _ptr(query_order, torch.int32, "query_order"),
@@ -468,7 +476,7 @@ def trim_search_range(index: Index, queries: torch.Tensor, radius: float, gamma:
             _check(lib().trim_search_range_static(*args, _stream()), "trim_search_range_static")
             return
         # scratch for the search in passes, where the library wants it (see trim_search_range_ws)
-        scratch, more = _scratch(0 if want_work else lib().trim_range_scratch_bytes(C.byref(view), nq, pcand), dev)
+        scratch, more = _scratch(0 if want_work else lib().trim_range_scratch_bytes(C.byref(index._size_view(lut)), nq, pcand), dev)
         _check(lib().trim_search_range_ws(*args, workspace.data_ptr(), workspace.numel(),
                                           _ptr(scratch, torch.uint8, "scratch"), more, _stream()), "trim_search_range")
 

@@ -101,6 +101,20 @@ def test_searches_too_large_for_32_bit_counts_do_not_run_in_passes(L):
     assert L.trim_range_scratch_bytes(C.byref(view_of(20_000_000, 512, 32)), 4_000_000, None) == 0      # 2^31 tiles
 
 
+def test_no_work_space_is_asked_for_where_the_passes_are_refused(L):
+    """The size functions ask what the searches ask: centroids, and LDS for every pass at this k and row length."""
+    def sizes(view, k):
+        return L.trim_knn_workspace_bytes(C.byref(view), 300, None, k, 256), L.trim_range_scratch_bytes(C.byref(view), 300, None)
+    assert all(sizes(view_of(4096, 768, 96), 10))
+    assert sizes(view_of(4096, 768, 96, codebooks=None), 10) == (0, 0)
+    assert all(sizes(view_of(700, 26624, 832), 10))
+    assert sizes(view_of(700, 26624, 832), 1000)[0] == 0         # the replay's lists and 1024 result slots
+    assert sizes(view_of(700, 26752, 836), 10) == (0, 0)         # the measure pass's means
+    # few queries take their bounds from a caller's table as well
+    few = view_of(100_000, 100, 20, codebooks=None)
+    assert L.trim_knn_workspace_bytes(C.byref(few), 1, None, 10, 256) > 0
+
+
 def test_product_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_2508_17828_amd")
     for dirpath, _, files in os.walk(pkg):

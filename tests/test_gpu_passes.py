@@ -407,3 +407,28 @@ def test_values_that_are_no_numbers(T, what, nq, lists):
         got = T.trim_search_range(ix, q, radius, gamma, probes=probes, lut=table, want_mask=True)
         for name in ("offsets", "ids", "d2", "n_scanned", "n_exact", "mask"):
             np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=f"{name}, {radius}")
+
+
+@pytest.mark.parametrize("M,asked", ((44, False), (132, True)))
+def test_work_space_beside_a_callers_table(T, M, asked, monkeypatch):
+    """Tables of sub-vectors that are not compared with the centroids (12 values) leave the search with the single kernel."""
+    import torch
+    ix, q, _ = built(T, 3000, 528, M, 8, 0, 300, 0, 0.5, 0.0, 3)
+    lut, empty, asked_for = T.trim_build_lut(q, ix.codebooks), torch.empty, []
+
+    def count(*size, **kw):
+        if kw.get("dtype") is torch.uint8:
+            asked_for.append(size)
+        return empty(*size, **kw)
+
+    monkeypatch.setattr(torch, "empty", count)
+    got = T.trim_search_knn(ix, q, 10, 0.4, 256, lut=lut)
+    assert bool(asked_for) == asked
+    ws = empty((T.trim_range_workspace_bytes(300, 3000),), dtype=torch.uint8, device="cuda")
+    del asked_for[:]
+    T.trim_search_range(ix, q, 1.0, 0.4, lut=lut, workspace=ws)
+    assert bool(asked_for) == asked
+    monkeypatch.undo()
+    want = single_kernel(T, ix, q, 10, 0.4, 256, None, None, lut)
+    for name in ("ids", "d2", "n_exact"):
+        np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
