@@ -154,9 +154,11 @@ def _stream():
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
-def _scratch(need: int, device):
+def _scratch(need: int, device, given: Optional[torch.Tensor] = None):
     """Work space for an entry point that is faster with it and does without: (tensor, bytes), or (None, 0) where nothing is
-    wanted or there is no memory for it."""
+    wanted, there is no memory for it, or what the caller has given is too small."""
+    if given is not None:
+        return (given, given.numel()) if 0 < need <= given.numel() else (None, 0)
     if need:
         try:
             return torch.empty((need,), dtype=torch.uint8, device=device), need
@@ -383,8 +385,12 @@ def trim_build_lut(queries: torch.Tensor, codebooks: torch.Tensor, mfma: bool = 
 def trim_search_knn(index: Index, queries: torch.Tensor, k: int, gamma: float, batch: int,
                     probes: Optional[torch.Tensor] = None, lut: Optional[torch.Tensor] = None,
                     want_stats: bool = True, want_mask: bool = False, out=None,
-                    query_order: Optional[torch.Tensor] = None, want_work: bool = False):
-    """Returns dict(ids [nq][k] int32, d2 [nq][k] float32, n_scanned, n_exact, mask, work)."""
+                    query_order: Optional[torch.Tensor] = None, want_work: bool = False,
+                    workspace: Optional[torch.Tensor] = None):
+    """Returns dict(ids [nq][k] int32, d2 [nq][k] float32, n_scanned, n_exact, mask, work).
+
+    workspace: uint8 tensor that the search may use instead of allocating (trim_knn_workspace_bytes; up to about
+    8 GiB).  With a smaller one than that, an empty one for instance, it runs as the single kernel, which needs none."""
     nq = queries.shape[0]
     dev = queries.device
     if out is None:
@@ -412,7 +418,7 @@ def trim_search_knn(index: Index, queries: torch.Tensor, k: int, gamma: float, b
     view = index._view()
     pcand = C.byref(cand) if cand is not None else None
     # work space for the search in passes, where the library wants it (see trim_search_knn_ws)
-    ws, need = _scratch(0 if want_work else lib().trim_knn_workspace_bytes(C.byref(index._size_view(lut)), nq, pcand, k, batch), dev)
+    ws, need = _scratch(0 if want_work else lib().trim_knn_workspace_bytes(C.byref(index._size_view(lut)), nq, pcand, k, batch), dev, workspace)
     _check(lib().trim_search_knn_ws(C.byref(view), _ptr(queries, torch.float32, "queries"), nq,
                                     _ptr(lut, torch.float32, "lut"), pcand, k, gamma, batch,
                                     _ptr(query_order, torch.int32, "query_order"),
@@ -424,6 +430,20 @@ def trim_search_knn(index: Index, queries: torch.Tensor, k: int, gamma: float, b
     return dict(ids=out_ids, d2=out_d2, n_scanned=ns, n_exact=ne, mask=mask, work=work)
 
 
+def trim_knn_workspace_bytes(index: Index, nq: int, k: int, batch: int, probes: Optional[torch.Tensor] = None,
+                             lut: Optional[torch.Tensor] = None) -> int:
+    """Bytes that trim_search_knn takes beside its results for such a search (0: none)."""
+    cand, _ = index._cand(probes)
+    return int(lib().trim_knn_workspace_bytes(C.byref(index._size_view(lut)), nq, C.byref(cand) if cand is not None else None, k, batch))
+
+
+def trim_range_scratch_bytes(index: Index, nq: int, probes: Optional[torch.Tensor] = None,
+                             lut: Optional[torch.Tensor] = None) -> int:
+    """Bytes that trim_search_range takes beside its workspace and results for such a search (0: none)."""
+    cand, _ = index._cand(probes)
+    return int(lib().trim_range_scratch_bytes(C.byref(index._size_view(lut)), nq, C.byref(cand) if cand is not None else None))
+
+
 def trim_range_workspace_bytes(nq: int, max_candidates: int) -> int:
     return int(lib().trim_range_workspace_bytes(nq, max_candidates))
 
@@ -432,12 +452,15 @@ def trim_search_range(index: Index, queries: torch.Tensor, radius: float, gamma:
                       probes: Optional[torch.Tensor] = None, lut: Optional[torch.Tensor] = None,
                       capacity: int = 0, want_stats: bool = True, want_mask: bool = False,
                       workspace: Optional[torch.Tensor] = None, static_scratch: bool = False,
-                      want_work: bool = False, query_order: Optional[torch.Tensor] = None):
+                      want_work: bool = False, query_order: Optional[torch.Tensor] = None,
+                      scratch: Optional[torch.Tensor] = None):
     """CSR results in scan order: dict(offsets [nq+1] int64, ids, d2, n_scanned, n_exact, mask).
 
     Synchronises once to read the result count; raises TrimCapacityError if a caller-given
     capacity is too small (capacity 0 = size the buffers from a first counting call).
-    static_scratch: call trim_search_range_static (the library's own scratch area, no workspace)."""
+    static_scratch: call trim_search_range_static (the library's own scratch area, no workspace).
+    scratch: uint8 tensor that the search may use instead of allocating (trim_range_scratch_bytes); with a smaller one, an
+    empty one for instance, it runs as the single kernel."""
     nq = queries.shape[0]
     dev = queries.device
     cand, mc = index._cand(probes)
@@ -476,9 +499,9 @@ def trim_search_range(index: Index, queries: torch.Tensor, radius: float, gamma:
             _check(lib().trim_search_range_static(*args, _stream()), "trim_search_range_static")
             return
         # scratch for the search in passes, where the library wants it (see trim_search_range_ws)
-        scratch, more = _scratch(0 if want_work else lib().trim_range_scratch_bytes(C.byref(index._size_view(lut)), nq, pcand), dev)
+        extra, more = _scratch(0 if want_work else lib().trim_range_scratch_bytes(C.byref(index._size_view(lut)), nq, pcand), dev, scratch)
         _check(lib().trim_search_range_ws(*args, workspace.data_ptr(), workspace.numel(),
-                                          _ptr(scratch, torch.uint8, "scratch"), more, _stream()), "trim_search_range")
+                                          _ptr(extra, torch.uint8, "scratch"), more, _stream()), "trim_search_range")
 
     if capacity <= 0:
         # count, size the buffers, collect: the workspace keeps the results, nothing is searched twice

@@ -432,3 +432,30 @@ def test_work_space_beside_a_callers_table(T, M, asked, monkeypatch):
     want = single_kernel(T, ix, q, 10, 0.4, 256, None, None, lut)
     for name in ("ids", "d2", "n_exact"):
         np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
+
+
+def test_work_space_of_the_caller(T, monkeypatch):
+    """A buffer of the caller takes the place of an allocation; with too small a one nothing is allocated either."""
+    import torch
+    ix, q, probes = built(T, 6000, 512, 128, 8, 12, 300, 6, 0.5, 0.0, 3)
+    need, more = T.trim_knn_workspace_bytes(ix, 300, 10, 256, probes), T.trim_range_scratch_bytes(ix, 300, probes)
+    assert need > 0 and more > 0
+    cand, mc = ix._cand(probes)
+    rws = torch.empty((T.trim_range_workspace_bytes(300, mc),), dtype=torch.uint8, device="cuda")
+    knn = lambda ws: T.trim_search_knn(ix, q, 10, 0.4, 256, probes=probes, want_mask=True, workspace=ws)
+    rng = lambda ws: T.trim_search_range(ix, q, 20.0, 0.4, probes=probes, want_mask=True, workspace=rws, scratch=ws)
+    want = knn(None), rng(None)
+    buffers = [(torch.empty((a,), dtype=torch.uint8, device="cuda"), torch.empty((b,), dtype=torch.uint8, device="cuda"))
+               for a, b in ((need, more), (need - 1, more - 1), (0, 0))]
+    empty = torch.empty
+
+    def nothing(*size, **kw):
+        assert kw.get("dtype") is not torch.uint8
+        return empty(*size, **kw)
+
+    monkeypatch.setattr(torch, "empty", nothing)
+    for a, b in buffers:
+        for got, ref in zip((knn(a), rng(b)), want):
+            for name in ref:
+                if isinstance(ref[name], torch.Tensor):
+                    assert torch.equal(got[name], ref[name]), (name, a.numel())
