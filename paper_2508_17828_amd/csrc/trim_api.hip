@@ -477,9 +477,17 @@ void fill_finish(FinishArgs &m, const FinishPlan &pl, const SearchArgs &a) {
 
 // Whether a search runs in passes.  They pay where rows are long (what the single kernel reads once per query and
 // survivor), a list is scanned by a few queries at a time (its tiles hold 128 of them) and the single
-// kernel has more queries than CUs.  Measured, single kernel / passes: 768 values, queries per list 5: 400 / 539 us
-// (200 queries), 6: 942 / 970 us, 11: 1263 / 911 us, 20: 1337 / 715 us; 1536 values, 7: 932 / 944 us (200 queries), 15:
-// 1533 / 1112 us; range, 768 values, 6: 275 / 315 us, 131: 1712 / 743 us; 256 values, 58: 517 / 706 us.
+// kernel has more queries than CUs.  How much depends on the data, which the host does not see: what the passes save are the rows and
+// lookups of survivors, of which there are few where the vectors' groups lie far apart.  Measured, passes / single kernel
+// (100,000 and 400,000 vectors, 20 of 316 and 40 of 632 lists, k = 10, gamma 0.3 and 0.6; queries 260 / 1000 / 3000):
+//   unit vectors, groups of 4000:   512 values 0.59-0.77 / 0.37-0.63 / 0.38-0.55;  768: 0.57-0.71 / 0.38-0.55 / 0.36-0.47;  1536: 0.45-0.55 / 0.36-0.45 / 0.28-0.36
+//   uneven variances, groups of 2000:   512: 0.99-1.73 / 0.80-1.31 / 0.68-1.00;  768: 0.87-1.74 / 0.73-1.17 / 0.61-0.88;  1536: 0.81-1.15 / 0.58-0.81 / 0.48-0.57
+//   the same, no lists (60,000 vectors):   512: 1.10-1.13 / 0.79-0.87 / 0.75-0.80;  1024: 0.43-0.54 / 0.40-0.43 / 0.34-0.37
+//   far apart, groups of 1000:   512: 1.46-2.18 / 1.33-1.76 / 1.05-1.53;  768: 1.33-2.44 / 1.18-1.96 / 0.93-1.54;  1536: 0.69-1.21 / 0.64-1.04 / 0.48-0.85
+// The line is drawn for the first kind, which rows of 512 values and more (embeddings) usually are: of 69 searches of
+// the first two kinds drawn over sizes, codes and gammas, kNN and range, 66 are faster in passes (0.17-0.98) and three
+// slower (1.05-1.14).  A program whose data are of the last kind keeps the single kernel by giving no work space.  Below 512
+// values: 256 values, 300 to 1200 queries: 1.4-1.7.
 constexpr int64_t kManyQueries = 256;
 constexpr int kLongRow = 512;
 constexpr double kSharedValues = 8192.0;      // values per row times queries per list
@@ -693,13 +701,23 @@ bool probe_in_two(int64_t nq, int d, int nlist, int nprobe) {
 }
 
 // Few queries: bound_kernel and settle_kernel (see trim_few.h).  They pay while the single kernel, a workgroup per
-// query, leaves CUs idle (up to 128 queries; 256 where it is slowed by results of more than one entry per lane), and
-// while the lookups of all candidates (it abandons most of them early) cost less than that: up to 500,000
-// per value of a row, since long rows are what its workgroups wait for.  Measured, single kernel / these
-// two: 1M x 128, 32 of 1024 lists, 1 / 64 / 96 queries: 74 / 44, 117 / 114, 120 / 145 us; 300000 x 768, 32 of 512, 128
-// queries: 548 / 490 us; 158482 x 960, no lists, 16 / 64 queries: 1564 / 991, 1550 / 1500 us.
+// query, leaves CUs idle (up to 128 queries; 256 where it is slowed by results of more than one entry per lane and the
+// rows are short), and while the lookups of all candidates (it abandons most of them early) cost less than that: up to 500,000
+// per value of a row, since long rows are what its workgroups wait for; but with short rows no more than 105 million, and
+// without lists, where each of its workgroups has a long scan to overlap its waits with, no more than 250 million.
+// Measured, single kernel / these two, us (k = 10 and gamma = 0.4 where nothing is said):
+//   1M x 128, 32 of 1024 lists, 1 / 64 / 96 queries                79 / 46   100 / 96   100 / 121
+//   500,000 x 384, 64 of 1024 (M = 48), 64 / 96                   109 / 89   110 / 121
+//   800,000 x 384, 44 of 894, gamma 0.5, 16 / 48 / 96              77 / 63    85 / 114   85 / 175
+//   800,000 x 256, 44 of 894 (M = 64), gamma 0.5, 16 / 48          98 / 71   105 / 149
+//   500,000 x 768, 64 of 1024, 64 / 96                            620 / 460  638 / 558
+//   100,000 x 768, 15 of 316, k = 100, 128 / 160 / 256            422 / 408  432 / 490  505 / 627
+//   30,000 x 128, 8 of 173, k = 100, 256 queries: 0.78 of the single kernel's time; x 384: 1.0; x 1536: 1.39
+//   30,000 x 960, no lists, 64 / 80 / 128                         357 / 311  355 / 403  357 / 457
+// What is left on the wrong side: 800,000 x 384 and 256 at gamma 0.5, 30 to 55 queries, up to 1.4 times the single kernel's time
+// (it abandons nearly everything early there, which depends on the data), 30,000 x 768 and 1536 from 96 queries on, up to 1.14.
 constexpr int64_t kFewQueries = 128, kFewQueriesWide = 256;
-constexpr double kFewLookups = 500000.0;
+constexpr double kFewLookups = 500000.0, kFewShortRows = 1.05e8, kFewNoLists = 2.5e8;
 constexpr size_t kFewBytes = size_t(1) << 30;
 struct FewLayout {
     int64_t stride;           // bounds per query (0: not this way)
@@ -709,10 +727,11 @@ struct FewLayout {
 FewLayout few_layout(const trim_index_view *ix, int64_t nq, const trim_candidates *cand, int k, int batch) {
     FewLayout L{};
     const int64_t mc = cand ? std::min<int64_t>(cand->max_candidates, (int64_t)cand->nprobe * ix->n) : ix->n;
-    if (nq <= 0 || nq > (k > kWave ? kFewQueriesWide : kFewQueries) || mc <= 0 || k + batch > kSettleFirst || k < 1 || batch < 1) return L;
+    if (nq <= 0 || nq > (k > kWave && ix->d < kLongRow ? kFewQueriesWide : kFewQueries) || mc <= 0 || k + batch > kSettleFirst || k < 1 || batch < 1) return L;
     // (a query's share of the base set, lists as long as each other)
     const double scanned = cand ? (double)ix->n * std::min(1.0, (double)cand->nprobe / cand->nlist) : (double)ix->n;
-    if ((double)nq * scanned * ix->M > kFewLookups * ix->d && nq > 1) return L;
+    const double lookups = (double)nq * scanned * ix->M;
+    if (nq > 1 && (lookups > kFewLookups * ix->d || (ix->d < kLongRow && lookups > kFewShortRows) || (!cand && lookups > kFewNoLists))) return L;
     const int64_t stride = (mc + 15) / 16 * 16;
     const size_t g_bytes = (size_t)nq * stride * 4;
     if ((size_t)stride > kFewBytes || g_bytes > kFewBytes || mc > 0x40000000 || !few_fits(ix->d, code_bytes(ix), is_fs(ix), k, cand ? cand->nprobe : 0)) return L;

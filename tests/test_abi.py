@@ -144,3 +144,21 @@ def test_build_refuses_search_kernels_with_static_lds(L):
     rec = [l.split() for l in open(build.RESOURCES)]
     search = [r for r in rec if "search_kernel" in r[0]]
     assert len(search) >= 12 and all("static_lds=0" in r for r in search)
+
+
+def test_which_searches_of_few_queries_are_split(L):
+    """More than one query is split over the chip up to a number of lookups that depends on the rows (csrc/trim_api.hip)."""
+    def split(n, d, M, nq, k, nlist=0, nprobe=0):
+        view = view_of(n, d, M)
+        cand = C.byref(cand_of(nlist, nprobe, n)) if nlist else None
+        return L.trim_knn_workspace_bytes(C.byref(view), nq, cand, k, 256) > 0
+    assert split(1_000_000, 128, 32, 1, 10, 1024, 32) and split(1_000_000, 128, 32, 64, 10, 1024, 32)
+    assert not split(1_000_000, 128, 32, 65, 10, 1024, 32)            # 500,000 lookups per value
+    assert split(500_003, 384, 48, 67, 10, 1024, 64)
+    assert not split(500_003, 384, 48, 71, 10, 1024, 64)              # short rows: 105 million
+    assert split(500_000, 768, 96, 96, 10, 1024, 64)                  # long rows: 288 million here
+    assert split(30_000, 960, 120, 69, 10) and not split(30_000, 960, 120, 70, 10)      # no lists: 250 million
+    assert split(30_000, 128, 32, 128, 10, 173, 8) and not split(30_000, 128, 32, 129, 10, 173, 8)
+    assert split(30_000, 128, 32, 256, 100, 173, 8) and not split(30_000, 128, 32, 257, 100, 173, 8)
+    assert split(30_000, 768, 96, 128, 100, 173, 8) and not split(30_000, 768, 96, 129, 100, 173, 8)
+    assert split(10_000_000, 1536, 192, 1, 10)
