@@ -459,3 +459,63 @@ def test_work_space_of_the_caller(T, monkeypatch):
             for name in ref:
                 if isinstance(ref[name], torch.Tensor):
                     assert torch.equal(got[name], ref[name]), (name, a.numel())
+
+
+@pytest.mark.parametrize("case", [CASES[i] for i in (1, 3, 4, 5, 7, 8)], ids=lambda c: "-".join(map(str, c)))
+def test_passes_equal_the_oracle(T, case):
+    import torch
+    n, d, M, bits, nlist, nq, nprobe, k, batch, gamma, spread, offset = case
+    ix, q, probes = built(T, n, d, M, bits, nlist, nq, nprobe, spread, offset, n + d)
+    if nlist:
+        probes[5, 0] = 2                                 # (the oracle takes lists that exist)
+    O, oix = host_index(ix)
+    hq, hp = q.cpu().numpy(), None if probes is None else np.ascontiguousarray(probes.cpu().numpy())
+
+    def same(got, want, names):
+        assert T.trim_knn_workspace_bytes(ix, nq, k, batch, probes) > 0 and T.trim_range_scratch_bytes(ix, nq, probes) > 0
+        for name in names:
+            np.testing.assert_array_equal(got[name].cpu().numpy(), want[name], err_msg=name)
+        mask = got["mask"].cpu().numpy().view(np.uint32)             # (as wide as the longest lists could make it)
+        np.testing.assert_array_equal(mask[:, :want["mask"].shape[1]], want["mask"])
+        assert not mask[:, want["mask"].shape[1]:].any()
+
+    want = O.search_knn(oix, hq, k, gamma, batch, probes=hp, want_mask=True)
+    same(T.trim_search_knn(ix, q, k, gamma, batch, probes=probes, want_mask=True), want, ("ids", "d2", "n_scanned", "n_exact"))
+    radius = float(np.sqrt(np.quantile(want["d2"][np.isfinite(want["d2"])], 0.9)))
+    want = O.search_range(oix, hq, radius, gamma, probes=hp, want_mask=True)
+    assert want["offsets"][-1] > (nq if gamma <= 1.0 else 0)       # (gamma above 1 prunes what is near as well)
+    same(T.trim_search_range(ix, q, radius, gamma, probes=probes, want_mask=True), want, ("offsets", "ids", "d2", "n_scanned", "n_exact"))
+
+
+def test_more_queries_than_one_slab(T):
+    """The work space is kept below 8 GiB by splitting the queries: with room for 384,000 candidates each, 2600 at a time."""
+    import torch
+    n, d, M, nq, k, batch, gamma = 6000, 512, 128, 2800, 10, 256, 0.4
+    ix, q, probes = built(T, n, d, M, 8, 12, nq, 7, 0.5, 0.0, 3)
+    probes = probes.repeat(1, 9).contiguous()            # (every list nine times)
+    order = torch.randperm(nq, device="cuda").to(torch.int32)
+    order[2] = nq + 5
+    order[2700] = -1
+    cand, mc = ix._cand(probes, max_candidates=64 * n)
+    view, lut = ix._view(), T.trim_build_lut(q, ix.codebooks)
+    need = T.lib().trim_knn_workspace_bytes(C.byref(view), nq, C.byref(cand), k, batch)
+    per = T.lib().trim_knn_workspace_bytes(C.byref(view), 300, C.byref(cand), k, batch) / 300
+    assert 7 << 30 < need < 9 << 30 and need < (nq - 150) * per        # (more than one slab, the second of some length)
+    ws = torch.empty((need,), dtype=torch.uint8, device="cuda")
+    p = lambda t: None if t is None else C.c_void_p(t.data_ptr())
+    mw = (mc + 31) // 32
+    for o, table in ((None, None), (order, None), (order, lut)):
+        out = []
+        for space, size in ((None, 0), (ws, need)):
+            ids = torch.full((nq, k), -7, dtype=torch.int32, device="cuda")
+            d2 = torch.full((nq, k), -7.0, device="cuda")
+            ns, ne = torch.zeros((2, nq), dtype=torch.int32, device="cuda").unbind(0)
+            mask = torch.zeros((nq, mw), dtype=torch.int32, device="cuda")
+            stats = T._Stats(ns.data_ptr(), ne.data_ptr(), None)
+            rc = T.lib().trim_search_knn_ws(C.byref(view), p(q), nq, p(table), C.byref(cand), k, gamma, batch, p(o), p(ids), p(d2),
+                                            C.byref(stats), p(mask), mw, p(space), size,
+                                            C.c_void_p(torch.cuda.current_stream().cuda_stream))
+            assert rc == 0
+            out.append((ids, d2, ns, ne, mask))
+        for a, b in zip(*out):
+            assert torch.equal(a, b)
