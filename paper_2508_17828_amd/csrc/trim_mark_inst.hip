@@ -77,7 +77,6 @@ int launch_filter_operands(const FilterArgs &a, hipStream_t st) {
 
 template <int AL>
 static void (*filter_of(const FilterArgs &a))(const FilterArgs) {
-    if (a.ncent == kC4) return filter_kernel<2, true, AL>;
     switch (a.padded) {
         case 4: return filter_kernel<4, false, AL>;
         case 8: return filter_kernel<8, false, AL>;
@@ -88,7 +87,8 @@ static void (*filter_of(const FilterArgs &a))(const FilterArgs) {
 }
 int launch_filter(const FilterArgs &a, hipStream_t st) {
     const int64_t blocks = 256 * 4;      // (one per CU at a time)
-    void (*fn)(const FilterArgs) = a.M % 8 == 0 ? filter_of<2>(a) : filter_of<1>(a);
+    // (4-bit codes have a multiple of eight bytes)
+    void (*fn)(const FilterArgs) = a.ncent == kC4 ? filter_kernel<2, true, 2> : a.M % 8 == 0 ? filter_of<2>(a) : filter_of<1>(a);
     if (!fn) return TRIM_UNSUPPORTED_SHAPE;
     hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(kFltThreads), 0, st, a);
     HIP_TRY(hipGetLastError());
