@@ -149,9 +149,12 @@ def _ptr(t: Optional[torch.Tensor], dtype, what: str):
     return t.data_ptr()
 
 
+# (the handle alone: a Stream object costs 3 us, a tenth of a small search's time on the host; the name is private to torch)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    # (the handle alone: a Stream object costs 3 us, a tenth of a small search's time on the host)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream if _raw_stream is None else _raw_stream(torch.cuda.current_device())
 
 
 def _scratch(need: int, device, given: Optional[torch.Tensor] = None):
