@@ -29,6 +29,7 @@ HBM_PEAK_GBS = 8000.0
 # LDS peak derived from the chip's unit counts: 256 CUs x 128 bytes per clock x 2.4 GHz; a table
 # lookup moves 4 bytes.
 LDS_PEAK_GLOOKUPS = 256 * 128 * 2.4 / 4
+MFMA_PEAK_TFLOPS = 2500.0      # dense, 16-bit operands
 
 
 def parse():
@@ -104,6 +105,29 @@ def machine_ceilings(trim):
         for blocks in (768, 1024))
     return dict(stream_read_GBps=round(read, 1), lds_random_lookup_Glookups=round(look, 1),
                 lds_rows_of_16_lookup_Glookups=round(look16, 1))
+
+
+# The kernels of a search in passes (many queries over long rows; csrc/trim_mark.h).  A range search's tables are built
+# before it by trim_build_lut; it only compares them.
+PASS_KERNELS = ("zero_areas_kernel", "invert_", "filter_", "totals_kernel", "finish_kernel", "measure_kernel", "replay_kernel",
+                "range_exact_kernel", "range_offsets_kernel", "range_fill_kernel", "lut_tile_kernel")
+
+
+def _passes_per_search(csv_path, searches, is_range):
+    """A counter's value per search in passes: every search of the process launches each of the kernels equally often."""
+    import csv
+    rows = {}
+    with open(csv_path, newline="") as f:
+        for r in csv.DictReader(f):
+            name = r["Kernel_Name"]
+            if any(k in name for k in PASS_KERNELS) and not (is_range and "lut_tile" in name and "true>" not in name):
+                d = rows.setdefault(name, {})
+                d[int(r["Dispatch_Id"])] = d.get(int(r["Dispatch_Id"]), 0.0) + float(r["Counter_Value"])
+    total = 0.0
+    for d in rows.values():
+        per = len(d) // searches
+        total += sum(d[k] for k in sorted(d)[-3 * per:]) / 3 if per else 0.0
+    return total
 
 
 def _counter_rows(csv_path, needle):
@@ -190,6 +214,12 @@ def measure_traffic(args):
                 if r.returncode != 0 or not files:
                     shutil.rmtree(out, ignore_errors=True)
                     return None
+                told = json.loads([l for l in r.stdout.splitlines() if l.startswith("{")][-1])
+                if what == "kernel" and told.get("passes"):
+                    got[(counter, what)] = _passes_per_search(files[0], told["searches"], told["range"])
+                    got["passes"] = True
+                    shutil.rmtree(out, ignore_errors=True)
+                    continue
                 vals = _counter_rows(files[0], needle)
                 shutil.rmtree(out, ignore_errors=True)
                 if len(vals) < 3:
@@ -197,16 +227,17 @@ def measure_traffic(args):
                 # the kernel: its last three launches are the timed configuration; the copy: its
                 # three largest dispatches are the three passes (the fill before them reads nothing)
                 got[(counter, what)] = (sum(vals[-3:]) / 3 if what == "kernel" else sum(sorted(vals)[-3:]) / 3)
-    except (OSError, KeyError, ValueError):
+    except (OSError, KeyError, ValueError, IndexError):
         return None
     units = None
-    try:        # how busy the units were: a run of its own, and no reason to lose the traffic if it fails
+    passes = got.pop("passes", False)
+    try:        # how busy the units were (of the one kernel, where it is one): a run of its own, and no reason to lose the traffic if it fails
         out = tempfile.mkdtemp(prefix="trim_pmc_", dir="/tmp")
         cmd = ["timeout", "-s", "KILL", "600", prof, "--pmc", *UNIT_COUNTERS, "-d", out, "-o", "p",
                "--output-format", "csv", "--", "python3", me] + child
-        r = subprocess.run(cmd, cwd="/tmp", env=env, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)
+        r = None if passes else subprocess.run(cmd, cwd="/tmp", env=env, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)
         files = glob.glob(os.path.join(out, "**", "p_counter_collection.csv"), recursive=True)
-        if r.returncode == 0 and files:
+        if r is not None and r.returncode == 0 and files:
             units = units_busy(_counter_table(files[0], "search_kernel"))
         shutil.rmtree(out, ignore_errors=True)
     except (OSError, KeyError, ValueError):
@@ -219,8 +250,8 @@ def measure_traffic(args):
     return dict(bytes_per_launch=int(fetch_b + write_b), fetch_bytes=int(fetch_b), write_bytes=int(write_b),
                 FETCH_SIZE_KiB=round(got[("FETCH_SIZE", "kernel")], 1), WRITE_SIZE_KiB=round(got[("WRITE_SIZE", "kernel")], 1),
                 scale_fetch=round(sf, 4), scale_write=round(sw, 4), units_busy=units,
-                method="rocprofv3 --pmc, one counter per child run of this script (last 3 launches of the "
-                       "search kernel), scaled by the same counter on a 1 GiB read + 1 GiB write pass")
+                method="rocprofv3 --pmc, one counter per child run of this script (last 3 " +
+                       ("searches, all their kernels" if passes else "launches of the search kernel") + "), scaled by the same counter on a 1 GiB read + 1 GiB write pass")
 
 
 def host_index(orc, ix, centroids):
@@ -270,6 +301,30 @@ def touched_bytes(w, nq, k_or_results, wt, use_lut, ncent=256):
     return dict(codes=wt["code_bytes"], rows=wt["rows"] * (4 * w.d + 4), queries=nq * 4 * w.d,
                 table_source=table_src, results=k_or_results * 8,
                 total=wt["code_bytes"] + wt["rows"] * (4 * w.d + 4) + nq * 4 * w.d + table_src + k_or_results * 8)
+
+
+def roofline_of_passes(w, scan_ms, alg_bytes, scanned, ceil, kernel, traffic):
+    """A search in passes: its lookups and rows are not those of the single kernel, whose instance keeps the counters.  The
+    bytes of the accounting model would exceed the peak (a row is read once for all its queries), so the traffic measured in the
+    run is set against it, and the filter's contraction (one multiply-add per value and scanned candidate) beside it."""
+    sec = scan_ms * 1e-3
+    flops = 2.0 * scanned * w.d / sec / 1e12
+    moved = traffic["bytes_per_launch"] / sec / 1e9 if traffic else None
+    head = dict(bound="hbm", achieved=round(moved, 1) if moved else None, peak=HBM_PEAK_GBS, unit="GB/s",
+                frac=round(moved / HBM_PEAK_GBS, 4) if moved else None,
+                achieved_is="HBM traffic of all kernels of the search, measured in this run (rocprofv3 counters) / its time")
+    if moved is None or moved / HBM_PEAK_GBS < flops / MFMA_PEAK_TFLOPS:
+        head = dict(bound="mfma", achieved=round(flops, 1), peak=MFMA_PEAK_TFLOPS, unit="TFLOP/s",
+                    frac=round(flops / MFMA_PEAK_TFLOPS, 4),
+                    achieved_is="2 d operations per scanned candidate (the filter's contraction) / the search's time")
+    head.update(traffic=traffic["bytes_per_launch"] if traffic else None, traffic_detail=traffic, units_busy=None,
+                kernel=kernel, kernel_ms=round(scan_ms, 4),
+                hbm=dict(algorithmic_bytes=alg_bytes, algorithmic_GBps=round(alg_bytes / sec / 1e9, 1),
+                         measured_traffic_GBps=round(moved, 1) if moved else None, peak_GBps=HBM_PEAK_GBS,
+                         stream_read_ceiling_GBps=ceil.get("stream_read_GBps")),
+                mfma=dict(filter_TFLOPs=round(flops, 1), peak_TFLOPs=MFMA_PEAK_TFLOPS), lds=None, work=None,
+                candidates_per_s=dict(counted=round(scanned / sec, 1)))
+    return head
 
 
 def roofline_object(w, nq, scan_ms, alg_bytes, wt, touched, ceil, kernel, fs=False, traffic=None):
@@ -399,6 +454,7 @@ def bench_range(args, w, bw, probes_for, setup_s, ceil, traffic=None):
     # candidates: then the tables are built once per step by trim_build_lut and copied from there.
     use_lut = w.M * 1024 > 128 * 1024
     lut_buf = torch.empty((nq, w.M, 256), dtype=torch.float32, device="cuda") if use_lut else None
+    passes = trim.trim_range_scratch_bytes(ix, nq, probes_for(queries), lut_buf) > 0
     last = {}
 
     def step(ev):
@@ -415,7 +471,7 @@ def bench_range(args, w, bw, probes_for, setup_s, ceil, traffic=None):
         for _ in range(4):
             step(None)
         torch.cuda.synchronize()
-        print(json.dumps({"traffic_child": True, "gamma": gamma}))
+        print(json.dumps({"traffic_child": True, "gamma": gamma, "range": True, "passes": passes, "searches": len(gammas) + 4}))
         return None
     t = timed_steps(args, step)
     got = last["r"]
@@ -428,8 +484,12 @@ def bench_range(args, w, bw, probes_for, setup_s, ceil, traffic=None):
     touched = touched_bytes(w, nq, chosen["results"], wt, use_lut)
     alg_bytes = (chosen["n_scanned"] * (w.M + 4) + chosen["n_exact"] * (4 * w.d + 4) + nq * 4 * w.d +
                  chosen["results"] * 8 + (nq + 1) * 8)
-    roof = roofline_object(w, nq, t["scan_mean"], alg_bytes, wt, touched, ceil,
-                           "search_kernel<range> + range_offsets_kernel + range_fill_kernel", traffic=traffic)
+    if passes:
+        roof = roofline_of_passes(w, t["scan_mean"], alg_bytes, chosen["n_scanned"], ceil,
+                                  "filter, finish, measure, range_exact, offsets, fill (all kernels of the search)", traffic)
+    else:
+        roof = roofline_object(w, nq, t["scan_mean"], alg_bytes, wt, touched, ceil,
+                               "search_kernel<range> + range_offsets_kernel + range_fill_kernel", traffic=traffic)
 
     # ---- CPU baseline: the oracle on a bounded sample, results compared with the GPU's ----
     cpu = None
@@ -583,6 +643,8 @@ def main():
     out = (torch.empty((nq, k), dtype=torch.int32, device="cuda"),
            torch.empty((nq, k), dtype=torch.float32, device="cuda"))
 
+    passes = nq > 256 and trim.trim_knn_workspace_bytes(main_ix, nq, k, batch, probes_for(queries)) > 0
+
     def make_step(index):
         def step(ev):
             if ev: ev[0].record()
@@ -599,7 +661,7 @@ def main():
         for _ in range(4):
             step(None)
         torch.cuda.synchronize()
-        print(json.dumps({"traffic_child": True, "gamma": gamma}))
+        print(json.dumps({"traffic_child": True, "gamma": gamma, "range": False, "passes": passes, "searches": len(gammas) + 4}))
         return
     t = timed_steps(args, make_step(main_ix))
     got = out[0].cpu().numpy()
@@ -621,8 +683,12 @@ def main():
     # exact distance, the query itself and the k results; the table never leaves LDS
     alg_bytes = (chosen["n_scanned"] * (code_bytes + 4) + chosen["n_exact"] * (4 * w.d + 4) +
                  nq * (4 * w.d + 8 * k))
-    roof = roofline_object(w, nq, t["scan_mean"], alg_bytes, wt, touched, ceil,
-                           "search_kernel<knn, 4-bit codes>" if fs else "search_kernel<knn>", fs, traffic)
+    if passes:
+        roof = roofline_of_passes(w, t["scan_mean"], alg_bytes, chosen["n_scanned"], ceil,
+                                  "filter, finish, measure, replay (all kernels of the search)", traffic)
+    else:
+        roof = roofline_object(w, nq, t["scan_mean"], alg_bytes, wt, touched, ceil,
+                               "search_kernel<knn, 4-bit codes>" if fs else "search_kernel<knn>", fs, traffic)
 
     # ---- CPU baseline: the oracle as it stands, on a bounded sample of the same workload ----
     cpu = None
