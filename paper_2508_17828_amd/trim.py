@@ -212,11 +212,11 @@ class Index:
                           _ptr(self.scan_head, torch.uint8, "scan_head"),
                           _ptr(self.codes_tiled, torch.uint8, "codes_tiled"), self.code_bits)
 
-    def _size_view(self, lut: Optional[torch.Tensor]) -> _IndexView:
+    def _size_view(self, view: _IndexView, lut: Optional[torch.Tensor]) -> _IndexView:
         """What the size functions are asked about: a caller's tables can be compared with the centroids, which the passes
         need, for sub-vectors of 4, 8 and 16 values (2 with 4-bit codes); with others the centroids may as well not be there."""
-        view = self._view()
         if lut is not None and self.d // self.M not in ((2,) if self.code_bits == 4 else (4, 8, 16)):
+            view = self._view()
             view.codebooks = None
         return view
 
@@ -421,7 +421,7 @@ def trim_search_knn(index: Index, queries: torch.Tensor, k: int, gamma: float, b
     view = index._view()
     pcand = C.byref(cand) if cand is not None else None
     # work space for the search in passes, where the library wants it (see trim_search_knn_ws)
-    ws, need = _scratch(0 if want_work else lib().trim_knn_workspace_bytes(C.byref(index._size_view(lut)), nq, pcand, k, batch), dev, workspace)
+    ws, need = _scratch(0 if want_work else lib().trim_knn_workspace_bytes(C.byref(index._size_view(view, lut)), nq, pcand, k, batch), dev, workspace)
     _check(lib().trim_search_knn_ws(C.byref(view), _ptr(queries, torch.float32, "queries"), nq,
                                     _ptr(lut, torch.float32, "lut"), pcand, k, gamma, batch,
                                     _ptr(query_order, torch.int32, "query_order"),
@@ -437,14 +437,14 @@ def trim_knn_workspace_bytes(index: Index, nq: int, k: int, batch: int, probes: 
                              lut: Optional[torch.Tensor] = None) -> int:
     """Bytes that trim_search_knn takes beside its results for such a search (0: none)."""
     cand, _ = index._cand(probes)
-    return int(lib().trim_knn_workspace_bytes(C.byref(index._size_view(lut)), nq, C.byref(cand) if cand is not None else None, k, batch))
+    return int(lib().trim_knn_workspace_bytes(C.byref(index._size_view(index._view(), lut)), nq, C.byref(cand) if cand is not None else None, k, batch))
 
 
 def trim_range_scratch_bytes(index: Index, nq: int, probes: Optional[torch.Tensor] = None,
                              lut: Optional[torch.Tensor] = None) -> int:
     """Bytes that trim_search_range takes beside its workspace and results for such a search (0: none)."""
     cand, _ = index._cand(probes)
-    return int(lib().trim_range_scratch_bytes(C.byref(index._size_view(lut)), nq, C.byref(cand) if cand is not None else None))
+    return int(lib().trim_range_scratch_bytes(C.byref(index._size_view(index._view(), lut)), nq, C.byref(cand) if cand is not None else None))
 
 
 def trim_range_workspace_bytes(nq: int, max_candidates: int) -> int:
@@ -502,7 +502,7 @@ def trim_search_range(index: Index, queries: torch.Tensor, radius: float, gamma:
             _check(lib().trim_search_range_static(*args, _stream()), "trim_search_range_static")
             return
         # scratch for the search in passes, where the library wants it (see trim_search_range_ws)
-        extra, more = _scratch(0 if want_work else lib().trim_range_scratch_bytes(C.byref(index._size_view(lut)), nq, pcand), dev, scratch)
+        extra, more = _scratch(0 if want_work else lib().trim_range_scratch_bytes(C.byref(index._size_view(view, lut)), nq, pcand), dev, scratch)
         _check(lib().trim_search_range_ws(*args, workspace.data_ptr(), workspace.numel(),
                                           _ptr(extra, torch.uint8, "scratch"), more, _stream()), "trim_search_range")
 
