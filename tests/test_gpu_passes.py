@@ -519,3 +519,108 @@ def test_more_queries_than_one_slab(T):
             out.append((ids, d2, ns, ne, mask))
         for a, b in zip(*out):
             assert torch.equal(a, b)
+
+
+# Hardly any candidates: fewer vectors than neighbours wanted, than a word of marks, than a tile; lists that nobody names.
+@pytest.mark.parametrize("n", (1, 3, 33, 300))
+@pytest.mark.parametrize("nlist", (0, 4))
+def test_hardly_any_candidates(T, n, nlist):
+    import torch
+    d, M, nq, k, batch, gamma = 512, 64, 300, 10, 16, 0.3
+    g = torch.Generator(device="cuda").manual_seed(n + nlist)
+    base, q = torch.randn((n, d), device="cuda", generator=g), torch.randn((nq, d), device="cuda", generator=g)
+    cb = torch.randn((M, 256, d // M), device="cuda", generator=g)
+    codes, dlx = T.trim_encode(base, cb)
+    offsets = probes = None
+    longest = 0
+    if nlist:
+        offsets = torch.tensor([0, 0, n // 2, n, n], device="cuda")
+        probes = torch.randint(-1, nlist + 1, (nq, 3), device="cuda", generator=g).to(torch.int32)
+        longest = n - n // 2
+    ix = T.Index(base, codes, dlx, cb, list_offsets=offsets, max_list_len=longest)
+    every = [probes] if probes is None else [probes, torch.full_like(probes, 3), torch.full_like(probes, -1)]
+    for pr in every:
+        assert T.trim_knn_workspace_bytes(ix, nq, k, batch, pr) > 0
+        want = single_kernel(T, ix, q, k, gamma, batch, pr, None)
+        got = T.trim_search_knn(ix, q, k, gamma, batch, probes=pr, want_mask=True)
+        for name in ("ids", "d2", "n_scanned", "n_exact", "mask"):
+            np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
+        for radius in (0.0, 30.0, 35.0):
+            want = single_range(T, ix, q, radius, gamma, pr, None, None)
+            got = T.trim_search_range(ix, q, radius, gamma, probes=pr, want_mask=True)
+            for name in ("offsets", "ids", "d2", "n_scanned", "n_exact", "mask"):
+                np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
+
+
+# A query with more candidates than max_candidates is cut there: inside a list, at its end, before the first batch ends.
+@pytest.mark.parametrize("nq", (300, 20))
+@pytest.mark.parametrize("cut", (5, 31, 500, 513, 2000, 2048))
+def test_candidates_are_cut(T, cut, nq, monkeypatch):
+    import torch
+    ix, q, probes = built(T, 9000, 512, 128, 8, 6, nq, 4, 0.5, 0.0, 3)
+    plain = T.Index._cand
+    monkeypatch.setattr(T.Index, "_cand", lambda self, p, max_candidates=0: plain(self, p, cut))
+    k, batch, gamma = 10, 256, 0.4
+    assert T.trim_knn_workspace_bytes(ix, nq, k, batch, probes) > 0
+    want = single_kernel(T, ix, q, k, gamma, batch, probes, None)
+    got = T.trim_search_knn(ix, q, k, gamma, batch, probes=probes, want_mask=True)
+    assert int(got["n_scanned"].max()) == cut
+    for name in ("ids", "d2", "n_scanned", "n_exact", "mask"):
+        np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
+    if nq < 300:
+        return
+    want = single_range(T, ix, q, 20.0, gamma, probes, None, None)
+    got = T.trim_search_range(ix, q, 20.0, gamma, probes=probes, want_mask=True)
+    for name in ("offsets", "ids", "d2", "n_scanned", "n_exact", "mask"):
+        np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
+
+
+@pytest.mark.parametrize("nq", (300, 20))
+def test_captured_and_replayed(T, nq):
+    """Probe selection, ordering, kNN and the range search as one graph (nothing in them allocates outside torch or waits):
+    every replay, on other queries, against the eager calls."""
+    import torch
+    n, d, M, nlist, nprobe, k = 9000, 512, 128, 70, 6, 10
+    ix, queries, _ = built(T, n, d, M, 8, nlist, 3 * nq, nprobe, 0.5, 0.0, 9)
+    cent = ix.base[torch.arange(0, n, n // nlist, device="cuda")[:nlist]].contiguous()
+    cand_max = min(n, nprobe * ix.max_list_len)
+    rws = torch.empty((T.trim_range_workspace_bytes(nq, cand_max),), dtype=torch.uint8, device="cuda")
+    offsets, required = torch.empty((nq + 1,), dtype=torch.int64, device="cuda"), torch.empty((1,), dtype=torch.int64, device="cuda")
+    cap = 400_000
+    rids, rd2 = torch.empty((cap,), dtype=torch.int32, device="cuda"), torch.empty((cap,), device="cuda")
+
+    def both(q):
+        pr = T.trim_ivf_probe(q, cent, nprobe)
+        order = T.trim_query_order(pr, nlist)
+        r = T.trim_search_knn(ix, q, k, 0.4, 256, probes=pr, query_order=order, want_mask=True)
+        cand, _ = ix._cand(pr)
+        view, more = ix._view(), T.trim_range_scratch_bytes(ix, nq, pr)
+        sc = torch.empty((max(more, 1),), dtype=torch.uint8, device="cuda")
+        rc = T.lib().trim_search_range_ws(C.byref(view), q.data_ptr(), nq, None, C.byref(cand), 22.0, 0.4, order.data_ptr(),
+                                          offsets.data_ptr(), rids.data_ptr(), rd2.data_ptr(), cap, required.data_ptr(), None, None, 0,
+                                          rws.data_ptr(), rws.numel(), sc.data_ptr(), more, torch.cuda.current_stream().cuda_stream)
+        assert rc == 0
+        return pr, r["ids"], r["d2"], r["n_scanned"], r["n_exact"], r["mask"]
+
+    x = queries[:nq].clone()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        both(x)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = both(x)
+    for rep in range(4):
+        x.copy_(queries[(rep % 3) * nq:(rep % 3 + 1) * nq])
+        graph.replay()
+        torch.cuda.synchronize()
+        total = int(required)
+        assert 0 < total <= cap
+        got = [t.clone() for t in out] + [offsets.clone(), rids[:total].clone(), rd2[:total].clone()]
+        want = list(both(x))
+        torch.cuda.synchronize()
+        want += [offsets, rids[:total], rd2[:total]]
+        for a, b in zip(got, want):
+            assert torch.equal(a, b), rep
