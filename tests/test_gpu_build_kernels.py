@@ -159,3 +159,25 @@ def test_nearest_list_with_centroids_that_are_no_numbers():
         many = T.trim_ivf_probe(x, c, 1)
         assert not (few == 5).any()
         assert torch.equal(many, few)
+
+
+@pytest.mark.parametrize("nq", (1, 3, 20))
+def test_probe_of_few_queries_with_values_that_are_no_numbers(nq):
+    """The two kernels for few queries and the one for many put NaN and infinite distances in the same places."""
+    import ctypes as C
+    import torch
+    from paper_2508_17828_amd import trim as T
+    g = torch.Generator(device="cuda").manual_seed(nq)
+    q, cent = torch.randn((nq, 100), device="cuda", generator=g), torch.randn((300, 100), device="cuda", generator=g)
+    cent[7, 3] = float("nan")
+    cent[0] = float("inf")
+    cent[200:210, 5] = float("nan")
+    q[nq - 1, 2] = float("inf")
+    if nq > 2:
+        q[1] = 1e30                           # (no NaN here: which of two a sum keeps, and their signs differ, is nobody's rule)
+    for nprobe in (2, 33, 64):
+        assert T.lib().trim_ivf_probe_workspace_bytes(nq, 100, 300, nprobe) > 0
+        out = torch.empty((nq, nprobe), dtype=torch.int32, device="cuda")
+        assert T.lib().trim_ivf_probe(C.c_void_p(q.data_ptr()), nq, 100, C.c_void_p(cent.data_ptr()), 300, nprobe,
+                                      C.c_void_p(out.data_ptr()), C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+        assert torch.equal(T.trim_ivf_probe(q, cent, nprobe), out)
