@@ -985,7 +985,7 @@ __global__ __launch_bounds__(256) void encode_dlx_kernel(const float *__restrict
                 const float v = xr[t] - c[t];
                 acc = __builtin_fmaf(v, v, acc);
             }
-            part[r * (kDlxSub + 1) + j] = acc;
+            part[r * (kDlxSub + 1) + j] = acc < __builtin_inff() ? acc : __builtin_inff();     // (the least distance begins at infinity: no NaN)
         }
         __syncthreads();
         if (threadIdx.x < kDlxRows)

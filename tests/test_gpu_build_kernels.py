@@ -181,3 +181,34 @@ def test_probe_of_few_queries_with_values_that_are_no_numbers(nq):
         assert T.lib().trim_ivf_probe(C.c_void_p(q.data_ptr()), nq, 100, C.c_void_p(cent.data_ptr()), 300, nprobe,
                                       C.c_void_p(out.data_ptr()), C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
         assert torch.equal(T.trim_ivf_probe(q, cent, nprobe), out)
+
+
+@pytest.mark.parametrize("n", (40, 3000, 200_000))
+@pytest.mark.parametrize("dsub,M", ((4, 8), (5, 8), (6, 8), (8, 8), (7, 4), (12, 4)))
+def test_encode_values_that_are_no_numbers(T, oracle, dsub, M, n):
+    """Rows and centroids with NaN, infinities and values out of the 16-bit range, however the vectors are dealt out: a sub-vector
+    without a finite distance takes centroid 0 and makes the landmark distance infinite."""
+    import torch
+    rng = np.random.default_rng(n + dsub)
+    base, cb = rng.normal(size=(n, dsub * M)).astype(np.float32), rng.normal(size=(M, 256, dsub)).astype(np.float32)
+    base[3, 1], base[5, 2], base[7, 0], base[9], base[11] = np.nan, np.inf, -1e30, 1e25, np.nan
+    cb[1, 7, 0], cb[1, 40, 1], cb[2, 32, 2], cb[3, 9, 3] = np.nan, np.inf, 1e30, -np.inf
+    want = oracle.encode(base, cb)
+    codes, dlx = T.trim_encode(torch.from_numpy(base).cuda(), torch.from_numpy(cb).cuda())
+    np.testing.assert_array_equal(codes.cpu().numpy(), want[0])
+    np.testing.assert_array_equal(dlx.cpu().numpy(), want[1])
+
+
+@pytest.mark.parametrize("n", (40, 3000))
+@pytest.mark.parametrize("dsub,M", ((2, 16), (3, 8)))
+def test_encode_four_bit_values_that_are_no_numbers(T, dsub, M, n):
+    import torch
+    from oracle import trim_oracle_fs
+    rng = np.random.default_rng(n + dsub)
+    base, cb = rng.normal(size=(n, dsub * M)).astype(np.float32), rng.normal(size=(M, 16, dsub)).astype(np.float32)
+    base[3, 1], base[5, 2], base[7, 0], base[9] = np.nan, np.inf, -1e30, 1e25
+    cb[1, 7, 0], cb[1, 4, 1], cb[3, 9, 1] = np.nan, np.inf, -np.inf
+    want = trim_oracle_fs.encode(base, cb)
+    codes, dlx = T.trim_fs_encode(torch.from_numpy(base).cuda(), torch.from_numpy(cb).cuda())
+    np.testing.assert_array_equal(codes.cpu().numpy(), want[0])
+    np.testing.assert_array_equal(dlx.cpu().numpy(), want[1])
