@@ -212,3 +212,21 @@ def test_encode_four_bit_values_that_are_no_numbers(T, dsub, M, n):
     codes, dlx = T.trim_fs_encode(torch.from_numpy(base).cuda(), torch.from_numpy(cb).cuda())
     np.testing.assert_array_equal(codes.cpu().numpy(), want[0])
     np.testing.assert_array_equal(dlx.cpu().numpy(), want[1])
+
+
+@pytest.mark.parametrize("ns", (600, 9000))
+def test_training_rows_that_are_no_numbers(T, oracle, ns):
+    import torch
+    from oracle import index_build
+    rng = np.random.default_rng(ns)
+    x = rng.standard_normal((ns, 64)).astype(np.float32)
+    x[100, 3], x[200, 20], x[300] = np.nan, np.inf, -np.inf
+    init = rng.permutation(np.setdiff1d(np.arange(ns), (100, 200, 300)))[:256].astype(np.int32)
+    init[9] = 200
+    g = lambda a: torch.from_numpy(a).cuda()
+    np.testing.assert_array_equal(T.trim_train_pq(g(x), 16, 3, g(init)).cpu().numpy(), index_build.train_pq_fixed(x, 16, 3, init))
+    np.testing.assert_array_equal(T.trim_fs_train_pq(g(x), 32, 3, g(init[:16].copy())).cpu().numpy(),
+                                  index_build.train_pq_fs_fixed(x, 32, 3, init[:16]))
+    # (one iteration: the oracle's lists take what is no number to the first, and stay there once its centroid is none)
+    np.testing.assert_array_equal(T.trim_train_ivf(g(x), 70, 1, g(init[:70].copy())).cpu().numpy(),
+                                  index_build.train_ivf_fixed(x, 70, 1, init[:70]))
