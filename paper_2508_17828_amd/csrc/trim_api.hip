@@ -480,14 +480,14 @@ void fill_finish(FinishArgs &m, const FinishPlan &pl, const SearchArgs &a) {
 // kernel has more queries than CUs.  How much depends on the data, which the host does not see: what the passes save are the rows and
 // lookups of survivors, of which there are few where the vectors' groups lie far apart.  Measured, passes / single kernel
 // (100,000 and 400,000 vectors, 20 of 316 and 40 of 632 lists, k = 10, gamma 0.3 and 0.6; queries 260 / 1000 / 3000):
-//   unit vectors, groups of 4000:   512 values 0.59-0.77 / 0.37-0.63 / 0.38-0.55;  768: 0.57-0.71 / 0.38-0.55 / 0.36-0.47;  1536: 0.45-0.55 / 0.36-0.45 / 0.28-0.36
+//   unit vectors, groups of 4000:   512 values 0.59-0.77 / 0.37-0.63 / 0.38-0.55;  768: 0.57-0.71 / 0.38-0.55 / 0.36-0.47;  1536: 0.45-0.55 / 0.36-0.45 / 0.29-0.36
 //   uneven variances, groups of 2000:   512: 0.99-1.73 / 0.80-1.31 / 0.68-1.00;  768: 0.87-1.74 / 0.73-1.17 / 0.61-0.88;  1536: 0.81-1.15 / 0.58-0.81 / 0.48-0.57
 //   the same, no lists (60,000 vectors):   512: 1.10-1.13 / 0.79-0.87 / 0.75-0.80;  1024: 0.43-0.54 / 0.40-0.43 / 0.34-0.37
 //   far apart, groups of 1000:   512: 1.46-2.18 / 1.33-1.76 / 1.05-1.53;  768: 1.33-2.44 / 1.18-1.96 / 0.93-1.54;  1536: 0.69-1.21 / 0.64-1.04 / 0.48-0.85
 // The line is drawn for the first kind, which rows of 512 values and more (embeddings) usually are: of 69 searches of
 // the first two kinds drawn over sizes, codes and gammas, kNN and range, 66 are faster in passes (0.17-0.98) and three
 // slower (1.05-1.14).  A program whose data are of the last kind keeps the single kernel by giving no work space.  Below 512
-// values: 256 values, 300 to 1200 queries: 1.4-1.7.
+// values: 256 values, 300 to 1200 queries: 1.4-1.8.
 constexpr int64_t kManyQueries = 256;
 constexpr int kLongRow = 512;
 constexpr double kSharedValues = 8192.0;      // values per row times queries per list
