@@ -208,6 +208,17 @@ int trim_estimate_gamma(const trim_index_view *index, const int32_t *sample_rows
                         float *gamma_out, void *stream);
 
 /*
+ * The same, the same result bit for bit, with device work space: the values are bounded on the matrix cores and only those
+ * around the wanted rank are computed.  trim_estimate_gamma_workspace_bytes: the size wanted (0: none, or a shape
+ * out of range; at most about 400 MB beside 4 d bytes per vector and 2 d per query).  workspace 256-byte aligned; with NULL or less
+ * than that size the call is trim_estimate_gamma.
+ */
+size_t trim_estimate_gamma_workspace_bytes(int32_t d, int32_t S, int32_t Q);
+int trim_estimate_gamma_ws(const trim_index_view *index, const int32_t *sample_rows, int32_t S,
+                           const float *sample_queries, int32_t Q, float p, float *gamma_x_out,
+                           float *gamma_out, void *workspace, size_t workspace_bytes, void *stream);
+
+/*
  * The same for queries with a known distribution, the standard normal (Section 3.2: the theorem
  * that gives Z^2 = A / (A + B + C) for Z = cos(theta), with A = (Q1 + h1)^2, B = (Q2 - h2)^2,
  * C the sum of the other d - 2 squared coordinates, h1 = (x - l).l / |x - l|,

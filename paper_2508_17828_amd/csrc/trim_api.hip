@@ -11,6 +11,7 @@
 #include <mutex>
 
 #include "trim_aux.h"
+#include "trim_gamma.h"
 #include "trim_launch.h"
 
 // Scratch area of trim_search_range_static (see below): device memory inside the library's code
@@ -961,6 +962,64 @@ int range_collect(const trim_index_view *index, int64_t nq, const trim_candidate
     return range_fill(a, L, static_cast<unsigned char *>(workspace), out_ids, out_d2, capacity, static_cast<hipStream_t>(stream));
 }
 
+// The work space of a gamma estimate through the matrix cores (trim_gamma.h): vectors in chunks whose keys take
+// at most 400 MB.  total = 0: gamma_kernel computes every value: few pairs of long rows, whose operands cost more than they save
+// (S Q < 100 d; 100 x 500 x 768: 47 against 42 us, 100 x 1000 x 768: 50 against 57, 100 x 500 x 384: 33 against 35).
+struct GammaLayout {
+    int32_t chunk, dpad, qpad;
+    size_t off_l, off_u, off_q, off_vpar, off_qpar, off_keys, off_lists, total;
+};
+GammaLayout gamma_layout(int32_t d, int32_t S, int32_t Q) {
+    GammaLayout L{};
+    if (d <= 0 || S <= 0 || Q <= 0 || Q > 16384 || (int64_t)S * Q < 100 * (int64_t)d) return L;
+    L.dpad = (d + 15) / 16 * 16;
+    L.qpad = (Q + kGrQueries - 1) / kGrQueries * kGrQueries;
+    if (gamma_rank_lds(d) + 1024 > kLdsBytes || (size_t)L.dpad * 4 + 8192 > kLdsBytes) return L;
+    const int64_t most = std::max<int64_t>(32, (int64_t(1) << 26) / L.qpad / 32 * 32);
+    L.chunk = (int32_t)std::min<int64_t>(most, ((int64_t)S + 31) / 32 * 32);
+    size_t off = 0;
+    L.off_l = off;    off += up256((size_t)L.chunk * L.dpad * 2);
+    L.off_u = off;    off += up256((size_t)L.chunk * L.dpad * 2);
+    L.off_q = off;    off += up256((size_t)L.qpad * L.dpad * 2);
+    L.off_vpar = off; off += up256((size_t)L.chunk * 32);
+    L.off_qpar = off; off += up256((size_t)L.qpad * 16);
+    L.off_keys = off; off += up256((size_t)L.chunk * L.qpad * 2);
+    L.off_lists = off; off += (size_t)L.chunk * L.qpad * 4;
+    L.total = off;
+    return L;
+}
+
+int launch_gamma_ranked(const GammaArgs &g, const GammaLayout &L, unsigned char *ws, hipStream_t st) {
+    GammaRankArgs a{};
+    a.g = g;
+    a.dpad = L.dpad; a.qpad = L.qpad;
+    a.l16 = reinterpret_cast<_Float16 *>(ws + L.off_l);
+    a.u16 = reinterpret_cast<_Float16 *>(ws + L.off_u);
+    a.q16 = reinterpret_cast<_Float16 *>(ws + L.off_q);
+    a.vpar = reinterpret_cast<float *>(ws + L.off_vpar);
+    a.qpar = reinterpret_cast<float4 *>(ws + L.off_qpar);
+    a.keys = reinterpret_cast<uint16_t *>(ws + L.off_keys);
+    a.lists = reinterpret_cast<uint32_t *>(ws + L.off_lists);
+    const size_t lds_mu = (size_t)L.dpad * 4, lds_rank = gamma_rank_lds(g.d);
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(gamma_operands_kernel), lds_mu));
+    const int threads = L.chunk <= 512 ? 512 : 256;
+    void (*rank)(GammaRankArgs) = threads == 512 ? gamma_rank_kernel<512> : gamma_rank_kernel<256>;
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(rank), lds_rank));
+    for (int64_t s0 = 0; s0 < g.S; s0 += L.chunk) {
+        a.s0 = (int32_t)s0;
+        a.ns = (int32_t)std::min<int64_t>(L.chunk, g.S - s0);
+        a.vector_blocks = (a.ns + 31) / 32;
+        const int groups = a.vector_blocks * (32 / kGrRows) + (s0 == 0 ? L.qpad / kGrRows : 0);
+        hipLaunchKernelGGL(gamma_operands_kernel, dim3((unsigned)groups), dim3(256), lds_mu, st, a);
+        HIP_TRY(hipGetLastError());
+        hipLaunchKernelGGL(gamma_bins_kernel, dim3((unsigned)(L.qpad / kGrQueries), (unsigned)a.vector_blocks), dim3(256), 0, st, a);
+        HIP_TRY(hipGetLastError());
+        hipLaunchKernelGGL(rank, dim3((unsigned)a.ns), dim3(threads), lds_rank, st, a);
+        HIP_TRY(hipGetLastError());
+    }
+    return TRIM_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1105,6 +1164,16 @@ int trim_train_ivf(const float *train, int64_t ns, int32_t d, int32_t nlist, int
 int trim_estimate_gamma(const trim_index_view *index, const int32_t *sample_rows, int32_t S,
                         const float *sample_queries, int32_t Q, float p, float *gamma_x_out,
                         float *gamma_out, void *stream) {
+    return trim_estimate_gamma_ws(index, sample_rows, S, sample_queries, Q, p, gamma_x_out, gamma_out, nullptr, 0, stream);
+}
+
+size_t trim_estimate_gamma_workspace_bytes(int32_t d, int32_t S, int32_t Q) {
+    return gamma_layout(d, S, Q).total;
+}
+
+int trim_estimate_gamma_ws(const trim_index_view *index, const int32_t *sample_rows, int32_t S,
+                           const float *sample_queries, int32_t Q, float p, float *gamma_x_out,
+                           float *gamma_out, void *workspace, size_t workspace_bytes, void *stream) {
     if (!index || index->n <= 0 || index->d <= 0 || index->M <= 0) return TRIM_INVALID_ARG;
     if (index->code_bits == 4) return TRIM_UNSUPPORTED_SHAPE;   // 8-bit landmark codes only
     if (index->d % 4 || index->d % index->M) return TRIM_UNSUPPORTED_SHAPE;
@@ -1117,8 +1186,6 @@ int trim_estimate_gamma(const trim_index_view *index, const int32_t *sample_rows
     const size_t lds = gamma_lds(per, index->d, Q);
     if (lds + 1024 > kLdsBytes) return TRIM_UNSUPPORTED_SHAPE;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    int rc = fill_u32(reinterpret_cast<uint32_t *>(gamma_out), 1, 0x7f800000u, st);  // +inf
-    if (rc) return rc;
     GammaArgs a{};
     a.base = index->base; a.codes = index->codes; a.codebooks = index->codebooks;
     a.rows = sample_rows; a.queries = sample_queries; a.n = index->n; a.d = index->d; a.M = index->M;
@@ -1128,6 +1195,11 @@ int trim_estimate_gamma(const trim_index_view *index, const int32_t *sample_rows
     if (m > Q) m = Q;
     a.rank = (int32_t)(Q - m);
     a.gamma_x = gamma_x_out; a.gamma_bits = reinterpret_cast<uint32_t *>(gamma_out);
+    const GammaLayout L = gamma_layout(index->d, S, Q);
+    if (workspace && L.total > 0 && workspace_bytes >= L.total && (reinterpret_cast<uintptr_t>(workspace) & 255u) == 0)
+        return launch_gamma_ranked(a, L, static_cast<unsigned char *>(workspace), st);
+    int rc = fill_u32(reinterpret_cast<uint32_t *>(gamma_out), 1, 0x7f800000u, st);  // +inf
+    if (rc) return rc;
     void (*fn)(GammaArgs) = per == 2 ? gamma_kernel<2> : gamma_kernel<1>;
     HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), lds));
     hipLaunchKernelGGL(fn, dim3((unsigned)((S + per - 1) / per)), dim3(kGammaThreads), lds, st, a);

@@ -460,6 +460,87 @@ __device__ __forceinline__ float from_ordered_bits(uint32_t k) {
     return __uint_as_float(k & 0x80000000u ? k & 0x7fffffffu : ~k);
 }
 
+// One 16-byte group of a query against l and u = x - l: w = q - l, dot += w.u, nn += w.w.
+__device__ __forceinline__ void gamma_step(const float4 &q, const float4 &l, const float4 &u, float &dot, float &nn) {
+    float w;
+    w = q.x - l.x; dot = __builtin_fmaf(w, u.x, dot); nn = __builtin_fmaf(w, w, nn);
+    w = q.y - l.y; dot = __builtin_fmaf(w, u.y, dot); nn = __builtin_fmaf(w, w, nn);
+    w = q.z - l.z; dot = __builtin_fmaf(w, u.z, dot); nn = __builtin_fmaf(w, w, nn);
+    w = q.w - l.w; dot = __builtin_fmaf(w, u.w, dot); nn = __builtin_fmaf(w, w, nn);
+}
+__device__ __forceinline__ uint32_t gamma_key(float dot, float nn, float nu) {
+    const float den = trim::sqrt_rn(nn) * nu;
+    return ordered_bits(1.0f - (den > 0.0f ? dot / den : 0.0f));
+}
+__device__ __forceinline__ void gamma_store(const GammaArgs &a, int64_t s, uint32_t key) {
+    const float g = from_ordered_bits(key);
+    if (a.gamma_x) a.gamma_x[s] = g;
+    atomicMin(a.gamma_bits, __float_as_uint(g < 0.0f ? 0.0f : g));
+}
+
+// The key of a rank, by all T threads of a workgroup (hist: kGammaBins counts of LDS): the keys in [lo, hi] are counted
+// in at most kGammaBins equal bins of integer width, the bin that holds the rank becomes the new [lo, hi] (its
+// smallest and largest key).  The range shrinks at least a thousandfold per round, so three
+// rounds are the most; two is usual.
+template <int T>
+__device__ uint32_t key_of_rank(const uint32_t *keys, int count, int rank, int *hist) {
+    constexpr int kPer = kGammaBins / T;
+    __shared__ uint32_t s_lo, s_hi, s_bin;
+    __shared__ int s_rank;
+    __shared__ int part[T / kWave];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    if (tid == 0) { s_lo = 0xffffffffu; s_hi = 0u; s_rank = rank; }
+    __syncthreads();
+    uint32_t mn = 0xffffffffu, mx = 0u;
+    for (int i = tid; i < count; i += T) { const uint32_t k = keys[i]; mn = k < mn ? k : mn; mx = k > mx ? k : mx; }
+    atomicMin(&s_lo, mn);
+    atomicMax(&s_hi, mx);
+    __syncthreads();
+    uint32_t lo = s_lo, hi = s_hi;
+    while (lo < hi) {
+        const int bits = 32 - __builtin_clz(hi - lo);
+        const int sh = bits > 11 ? bits - 11 : 0;      // (hi - lo) >> sh < 2048
+        for (int b = tid; b < kGammaBins; b += T) hist[b] = 0;
+        __syncthreads();
+        for (int i = tid; i < count; i += T) {
+            const uint32_t k = keys[i];
+            if (k >= lo && k <= hi) atomicAdd(&hist[(k - lo) >> sh], 1);
+        }
+        __syncthreads();
+        // the bin of the rank: a few bins per thread, prefix over the lanes, then over the waves
+        int h[kPer], sum = 0;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) { h[i] = hist[kPer * tid + i]; sum += h[i]; }
+        int incl = sum;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int v = __shfl_up(incl, off);
+            if (lane >= off) incl += v;
+        }
+        if (lane == kWave - 1) part[wave] = incl;
+        const int want = s_rank;
+        __syncthreads();
+        int before = incl - sum;
+        for (int w = 0; w < wave; ++w) before += part[w];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            if (want >= before && want < before + h[i]) { s_bin = kPer * tid + i; s_rank = want - before; s_lo = 0xffffffffu; s_hi = 0u; }
+            before += h[i];
+        }
+        __syncthreads();
+        const uint32_t bin = s_bin;
+        for (int i = tid; i < count; i += T) {
+            const uint32_t k = keys[i];
+            if (k >= lo && k <= hi && (k - lo) >> sh == bin) { atomicMin(&s_lo, k); atomicMax(&s_hi, k); }
+        }
+        __syncthreads();
+        lo = s_lo;
+        hi = s_hi;
+    }
+    __syncthreads();
+    return lo;
+}
+
 template <int kGammaRows>
 __global__ __launch_bounds__(kGammaThreads) void gamma_kernel(const GammaArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -467,8 +548,6 @@ __global__ __launch_bounds__(kGammaThreads) void gamma_kernel(const GammaArgs a)
     uint32_t *keys = reinterpret_cast<uint32_t *>(smem + gamma_keys_offset(kGammaRows, a.d));  // [rows][Q], order-preserving bits
     int *hist = reinterpret_cast<int *>(smem);      // [kGammaBins]
     __shared__ float norm2[kGammaRows];
-    __shared__ uint32_t s_lo, s_hi, s_bin;
-    __shared__ int s_rank;
     __shared__ int part[kGammaThreads / kWave];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
     const int s0 = blockIdx.x * kGammaRows;
@@ -522,80 +601,19 @@ __global__ __launch_bounds__(kGammaThreads) void gamma_kernel(const GammaArgs a)
                 const float4 lv = lu4[(2 * x) * ng + g], uv = lu4[(2 * x + 1) * ng + g];
 #pragma unroll
                 for (int i = 0; i < QB; ++i) {
-                    float w, dot = acc[2 * x * QB + i], nn = acc[(2 * x + 1) * QB + i];
-                    w = qv[i].x - lv.x; dot = __builtin_fmaf(w, uv.x, dot); nn = __builtin_fmaf(w, w, nn);
-                    w = qv[i].y - lv.y; dot = __builtin_fmaf(w, uv.y, dot); nn = __builtin_fmaf(w, w, nn);
-                    w = qv[i].z - lv.z; dot = __builtin_fmaf(w, uv.z, dot); nn = __builtin_fmaf(w, w, nn);
-                    w = qv[i].w - lv.w; dot = __builtin_fmaf(w, uv.w, dot); nn = __builtin_fmaf(w, w, nn);
-                    acc[2 * x * QB + i] = dot;
-                    acc[(2 * x + 1) * QB + i] = nn;
+                    gamma_step(qv[i], lv, uv, acc[2 * x * QB + i], acc[(2 * x + 1) * QB + i]);
                 }
             }
         }
         const float sum = reduce_pairs<kGammaRows * 2 * QB>(acc, lane32);   // mine: vector (bit 4), dot / norm (bit 3), query (bits 0..2)
         const float nn = __shfl_xor(sum, 8 << kShift);
         const int qi = q0 + (mine & 7);
-        if (!(mine & 8) && qi < a.Q) {
-            const float den = trim::sqrt_rn(nn) * nu;
-            keys[(size_t)(mine >> 4) * a.Q + qi] = ordered_bits(1.0f - (den > 0.0f ? sum / den : 0.0f));
-        }
+        if (!(mine & 8) && qi < a.Q) keys[(size_t)(mine >> 4) * a.Q + qi] = gamma_key(sum, nn, nu);
     }
     __syncthreads();
-    // The key of rank `rank` of each vector: the keys in [lo, hi] are counted in at most kGammaBins
-    // equal bins of integer width, the bin that holds the rank becomes the new [lo, hi] (its
-    // smallest and largest key).  The range shrinks at least a thousandfold per round, so three
-    // rounds are the most; two is usual.
     for (int x = 0; x < kGammaRows && s0 + x < a.S; ++x) {
-        const uint32_t *kx = keys + (size_t)x * a.Q;
-        if (tid == 0) { s_lo = 0xffffffffu; s_hi = 0u; s_rank = a.rank; }
-        __syncthreads();
-        uint32_t mn = 0xffffffffu, mx = 0u;
-        for (int i = tid; i < a.Q; i += kGammaThreads) { const uint32_t k = kx[i]; mn = k < mn ? k : mn; mx = k > mx ? k : mx; }
-        atomicMin(&s_lo, mn);
-        atomicMax(&s_hi, mx);
-        __syncthreads();
-        uint32_t lo = s_lo, hi = s_hi;
-        while (lo < hi) {
-            const int bits = 32 - __builtin_clz(hi - lo);
-            const int sh = bits > 11 ? bits - 11 : 0;      // (hi - lo) >> sh < 2048
-            for (int b = tid; b < kGammaBins; b += kGammaThreads) hist[b] = 0;
-            __syncthreads();
-            for (int i = tid; i < a.Q; i += kGammaThreads) {
-                const uint32_t k = kx[i];
-                if (k >= lo && k <= hi) atomicAdd(&hist[(k - lo) >> sh], 1);
-            }
-            __syncthreads();
-            // the bin of the rank: two bins per thread, prefix over the lanes, then over the waves
-            const int h0 = hist[2 * tid], h1 = hist[2 * tid + 1];
-            int incl = h0 + h1;
-#pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) {
-                const int v = __shfl_up(incl, off);
-                if (lane >= off) incl += v;
-            }
-            if (lane == kWave - 1) part[wave] = incl;
-            const int want = s_rank;
-            __syncthreads();
-            int before = incl - h0 - h1;
-            for (int w = 0; w < wave; ++w) before += part[w];
-            if (want >= before && want < before + h0) { s_bin = 2 * tid; s_rank = want - before; s_lo = 0xffffffffu; s_hi = 0u; }
-            else if (want >= before + h0 && want < before + h0 + h1) { s_bin = 2 * tid + 1; s_rank = want - before - h0; s_lo = 0xffffffffu; s_hi = 0u; }
-            __syncthreads();
-            const uint32_t bin = s_bin;
-            for (int i = tid; i < a.Q; i += kGammaThreads) {
-                const uint32_t k = kx[i];
-                if (k >= lo && k <= hi && (k - lo) >> sh == bin) { atomicMin(&s_lo, k); atomicMax(&s_hi, k); }
-            }
-            __syncthreads();
-            lo = s_lo;
-            hi = s_hi;
-        }
-        if (tid == 0) {
-            const float g = from_ordered_bits(lo);
-            if (a.gamma_x) a.gamma_x[s0 + x] = g;
-            atomicMin(a.gamma_bits, __float_as_uint(g < 0.0f ? 0.0f : g));
-        }
-        __syncthreads();
+        const uint32_t k = key_of_rank<kGammaThreads>(keys + (size_t)x * a.Q, a.Q, a.rank, hist);
+        if (tid == 0) gamma_store(a, s0 + x, k);
     }
 }
 

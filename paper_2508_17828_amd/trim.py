@@ -21,7 +21,7 @@ TRIM_MAX_BATCH = 4096
 TRIM_MAX_NPROBE = 4096
 
 EXPORTS = ("trim_shape_supported", "trim_fs_shape_supported", "trim_fs_encode", "trim_fs_build_lut",
-           "trim_fs_train_pq", "trim_train_pq", "trim_train_ivf", "trim_estimate_gamma", "trim_estimate_gamma_normal", "trim_encode", "trim_pack_scan_head", "trim_codes_tiled_bytes", "trim_pack_codes_tiled",
+           "trim_fs_train_pq", "trim_train_pq", "trim_train_ivf", "trim_estimate_gamma", "trim_estimate_gamma_ws", "trim_estimate_gamma_workspace_bytes", "trim_estimate_gamma_normal", "trim_encode", "trim_pack_scan_head", "trim_codes_tiled_bytes", "trim_pack_codes_tiled",
            "trim_build_lut", "trim_search_knn", "trim_search_knn_ws", "trim_knn_workspace_bytes",
            "trim_search_range", "trim_search_range_static", "trim_search_range_ws", "trim_range_scratch_bytes", "trim_range_collect", "trim_static_scratch_bytes", "trim_range_workspace_bytes", "trim_ivf_probe", "trim_ivf_probe_ws",
            "trim_ivf_probe_workspace_bytes", "trim_query_order",
@@ -99,6 +99,9 @@ def lib() -> C.CDLL:
                                      C.c_void_p, C.c_void_p, C.c_void_p]
         L.trim_estimate_gamma.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_int32, C.c_float,
                                           C.c_void_p, C.c_void_p, C.c_void_p]
+        L.trim_estimate_gamma_ws.argtypes = L.trim_estimate_gamma.argtypes[:-1] + [C.c_void_p, C.c_size_t, C.c_void_p]
+        L.trim_estimate_gamma_workspace_bytes.restype = C.c_size_t
+        L.trim_estimate_gamma_workspace_bytes.argtypes = [C.c_int32, C.c_int32, C.c_int32]
         L.trim_estimate_gamma_normal.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_int32,
                                                  C.c_float, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p,
                                                  C.c_void_p]
@@ -319,10 +322,11 @@ def trim_estimate_gamma(index: "Index", sample_rows: torch.Tensor, sample_querie
     gx = torch.empty((S,), dtype=torch.float32, device=sample_queries.device)
     g = torch.empty((1,), dtype=torch.float32, device=sample_queries.device)
     view = index._view()
-    _check(lib().trim_estimate_gamma(C.byref(view), _ptr(sample_rows, torch.int32, "sample_rows"), S,
-                                     _ptr(sample_queries, torch.float32, "sample_queries"), Q, p,
-                                     _ptr(gx, torch.float32, "gamma_x"), _ptr(g, torch.float32, "gamma"),
-                                     _stream()), "trim_estimate_gamma")
+    ws, need = _scratch(lib().trim_estimate_gamma_workspace_bytes(index.d, S, Q), sample_queries.device)
+    _check(lib().trim_estimate_gamma_ws(C.byref(view), _ptr(sample_rows, torch.int32, "sample_rows"), S,
+                                        _ptr(sample_queries, torch.float32, "sample_queries"), Q, p,
+                                        _ptr(gx, torch.float32, "gamma_x"), _ptr(g, torch.float32, "gamma"),
+                                        _ptr(ws, torch.uint8, "workspace"), need, _stream()), "trim_estimate_gamma")
     return g, gx
 
 

@@ -127,6 +127,45 @@ def test_gamma_rank(T, S, Q, d, M, p):
     assert gamma.item() == max(0.0, each.min().item())
 
 
+# with work space (bins from the matrix cores, exact values around the rank) the same bits as without: one tile and odd
+# remainders of rows, queries and coordinates; more values to evaluate than fit the LDS; vectors in two chunks; rows, queries
+# and landmarks that are no numbers, out of the scaled range, or in one place
+@pytest.mark.parametrize("S,Q,d,M,p,kind", [
+    (32, 256, 16, 4, 0.9, ""), (33, 1001, 100, 20, 0.7, ""), (1, 16384, 128, 16, 0.99, ""), (700, 300, 392, 56, 0.5, ""),
+    (40, 5000, 128, 32, 0.0, ""), (5, 5000, 36, 12, 1.0, "same"), (4099, 16300, 4, 4, 0.8, ""), (65, 2000, 64, 16, 0.9, "odd"),
+    (65, 3000, 64, 16, 0.3, "tiny"), (65, 3000, 64, 16, 0.3, "huge"), (65, 3000, 64, 16, 0.6, "landmarks")])
+def test_gamma_with_work_space(T, S, Q, d, M, p, kind):
+    import ctypes
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(S + Q + d)
+    base = torch.rand((max(S, 300), d), device="cuda", generator=g) * 200
+    q = torch.rand((Q, d), device="cuda", generator=g) * 200
+    cb = torch.rand((M, 256, d // M), device="cuda", generator=g) * 200
+    rows = torch.randperm(base.shape[0], device="cuda", generator=g)[:S].int()
+    if kind == "same":
+        q[:] = q[0]
+    if kind == "odd":
+        base[rows[:6].long(), 3] = torch.tensor([float("nan"), float("inf"), -float("inf"), 1e20, 3e38, 1e-40], device="cuda")
+        q[:9, 5] = torch.tensor([float("nan"), float("inf"), -float("inf"), 1e20, 3e38, 1e-40, -1e14, 1e11, 0.0], device="cuda")
+    if kind in ("tiny", "huge"):
+        scale = 1e-18 if kind == "tiny" else 1e16
+        base, q, cb = base * scale, q * scale, cb * scale
+    codes, dlx = T.trim_encode(base, cb)
+    if kind == "landmarks":                  # vectors, and queries, at a landmark
+        land = torch.stack([cb[j][codes[:, j].long()] for j in range(M)], 1).reshape(-1, d)
+        base[rows[:20].long()] = land[rows[:20].long()]
+        q[::3] = land[rows[torch.arange(0, Q, 3, device="cuda") % S].long()]
+    index = T.Index(base, codes, dlx, cb)
+    assert T.lib().trim_estimate_gamma_workspace_bytes(d, S, Q) > 0
+    gamma, each = T.trim_estimate_gamma(index, rows, q, p)
+    gamma0, each0 = torch.zeros(1, device="cuda"), torch.zeros(S, device="cuda")
+    view = index._view()
+    assert T.lib().trim_estimate_gamma(ctypes.byref(view), rows.data_ptr(), S, q.data_ptr(), Q, p, each0.data_ptr(),
+                                       gamma0.data_ptr(), T._stream()) == 0
+    np.testing.assert_array_equal(each.cpu().numpy().view(np.uint32), each0.cpu().numpy().view(np.uint32))
+    np.testing.assert_array_equal(gamma.cpu().numpy().view(np.uint32), gamma0.cpu().numpy().view(np.uint32))
+
+
 # one query to more than a tile of them; lists that leave tiles and columns unfilled; ties; the nearest lists all
 # in one column of the selection (8192 lists)
 @pytest.mark.parametrize("nq,nlist,d,nprobe", ((1, 64, 4, 2), (1, 1000, 128, 32), (2, 65, 100, 64), (5, 300, 1536, 33),
