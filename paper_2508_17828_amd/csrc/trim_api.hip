@@ -303,15 +303,21 @@ int zero_areas(const ZeroAreas &z, hipStream_t st) {
 // assignments), fewer until there are two workgroups per CU or one cluster is left, and never
 // more than 48 KB of float64 sums.
 template <int ABYTES>
-int launch_kmeans_update(const float *x, int64_t ns, int d, int dim, const void *assign, int64_t astride, int K, int ny,
-                         float *cent, hipStream_t st) {
+int launch_kmeans_update(const float *x, int64_t ns, int d, int dim, const void *assign, int64_t astride, int64_t ystride, int K,
+                         int ny, float *cent, hipStream_t st) {
     const int cols = dim < kUpdCols ? dim : kUpdCols, nz = (dim + kUpdCols - 1) / kUpdCols;
     int lg = kUpdMaxLog2;
-    while (lg > 0 && ((int64_t)((K + (1 << lg) - 1) >> lg) * ny * nz < 512 || ((size_t)cols << lg) * 8 > 48 * 1024)) --lg;
+    while (lg > 0 && ((int64_t)((K + (1 << lg) - 1) >> lg) * ny * nz < 256 || ((size_t)cols << lg) * 8 > 48 * 1024)) --lg;
     const size_t lds = kmeans_update_lds(lg, cols);
+    UpdateArgs a{};
+    a.x = x; a.assign = assign; a.ns = ns; a.stride = d; a.astride = astride; a.ystride = ystride;
+    a.dim = dim; a.K = K; a.cg_log2 = lg; a.groups = (K + (1 << lg) - 1) >> lg; a.ny = ny; a.cent = cent;
+    const int64_t total = (int64_t)a.groups * ny * nz;
+    if (total > 0x7fffffff - kXcds) return TRIM_UNSUPPORTED_SHAPE;
+    a.total = (int32_t)total;
     HIP_TRY(allow_lds(reinterpret_cast<const void *>(kmeans_update_kernel<ABYTES>), lds));
-    hipLaunchKernelGGL(kmeans_update_kernel<ABYTES>, dim3((unsigned)((K + (1 << lg) - 1) >> lg), (unsigned)ny, (unsigned)nz),
-                       dim3(kUpdThreads), lds, st, x, ns, (int64_t)d, dim, assign, astride, K, lg, cent);
+    hipLaunchKernelGGL(kmeans_update_kernel<ABYTES>, dim3((unsigned)((total + kXcds - 1) / kXcds * kXcds)), dim3(kUpdThreads), lds,
+                       st, a);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
 }
@@ -320,11 +326,13 @@ int launch_kmeans_update(const float *x, int64_t ns, int d, int dim, const void 
 // than two workgroups per CU (a workgroup splits the centroids for its own vectors, so fewer of
 // them cost more).
 template <int D>
-int launch_encode(const float *base, int64_t n, int d, const float *codebooks, int M, uint8_t *codes, float *dlx, hipStream_t st) {
+int launch_encode(const float *base, int64_t n, int d, const float *codebooks, int M, uint8_t *codes, int64_t across, float *dlx,
+                  hipStream_t st) {
     const bool wide = n >= 512 * kEncThreads;
     const int per = wide ? kEncThreads : kEncThreads / 2;
-    void (*fn)(const float *, int64_t, int, const float *, int, int, uint8_t *, float *) =
-        wide ? encode_mfma_kernel<D, 2> : encode_mfma_kernel<D, 1>;
+    void (*fn)(const float *, int64_t, int, const float *, int, int, uint8_t *, int64_t, float *) =
+        across ? (wide ? encode_mfma_kernel<D, 2, true> : encode_mfma_kernel<D, 1, true>)
+               : (wide ? encode_mfma_kernel<D, 2, false> : encode_mfma_kernel<D, 1, false>);
     const size_t lds = wide ? encode_lds<D, 2>() : encode_lds<D, 1>();
     const int64_t blocks = (n + per - 1) / per;
     int jper = M;       // subspaces per workgroup: all, or fewer until there are about three workgroups per CU
@@ -334,7 +342,7 @@ int launch_encode(const float *base, int64_t n, int d, const float *codebooks, i
     }
     HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), lds));
     hipLaunchKernelGGL(fn, dim3((unsigned)blocks, (unsigned)((M + jper - 1) / jper)), dim3(kEncThreads), lds, st, base, n, d,
-                       codebooks, M, jper, codes, dlx);
+                       codebooks, M, jper, codes, across, dlx);
     if (jper < M && dlx)
         hipLaunchKernelGGL(encode_dlx_kernel, dim3((unsigned)((n + kDlxRows - 1) / kDlxRows)), dim3(256), 0, st, base, n, d,
                            codebooks, M, D, codes, dlx);
@@ -343,30 +351,32 @@ int launch_encode(const float *base, int64_t n, int d, const float *codebooks, i
 }
 
 template <bool PACKED>
-int launch_encode_fs(const float *base, int64_t n, int d, const float *codebooks, int m, uint8_t *codes, float *dlx, hipStream_t st) {
+int launch_encode_fs(const float *base, int64_t n, int d, const float *codebooks, int m, uint8_t *codes, int64_t across, float *dlx,
+                     hipStream_t st) {
     const int dsub = d / m;
     if (dsub == 2)
         hipLaunchKernelGGL(encode_fs2_kernel<PACKED>, dim3((unsigned)((n + kFsRows - 1) / kFsRows)), dim3(kFsRows), 0, st, base,
-                           n, d, codebooks, m, codes, dlx);
+                           n, d, codebooks, m, codes, across, dlx);
     else
         hipLaunchKernelGGL(encode_fs_kernel<PACKED>, dim3((unsigned)((n + 255) / 256)), dim3(256), (size_t)2 * kC4 * dsub * 4,
-                           st, base, n, d, codebooks, m, dsub, codes, dlx);
+                           st, base, n, d, codebooks, m, dsub, codes, across, dlx);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
 }
 
 // trim_encode past its checks.  dlx may be null where the caller needs the codes only (training).
-int encode_codes(const float *base, int64_t n, int d, const float *codebooks, int M, uint8_t *codes, float *dlx, hipStream_t st) {
+int encode_codes(const float *base, int64_t n, int d, const float *codebooks, int M, uint8_t *codes, int64_t across, float *dlx,
+                 hipStream_t st) {
     const int dsub = d / M;
     switch (dsub) {
-        case 4: return launch_encode<4>(base, n, d, codebooks, M, codes, dlx, st);
-        case 5: return launch_encode<5>(base, n, d, codebooks, M, codes, dlx, st);
-        case 6: return launch_encode<6>(base, n, d, codebooks, M, codes, dlx, st);
-        case 8: return launch_encode<8>(base, n, d, codebooks, M, codes, dlx, st);
+        case 4: return launch_encode<4>(base, n, d, codebooks, M, codes, across, dlx, st);
+        case 5: return launch_encode<5>(base, n, d, codebooks, M, codes, across, dlx, st);
+        case 6: return launch_encode<6>(base, n, d, codebooks, M, codes, across, dlx, st);
+        case 8: return launch_encode<8>(base, n, d, codebooks, M, codes, across, dlx, st);
         default: break;
     }
     hipLaunchKernelGGL(encode_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), (size_t)kC * dsub * 4, st, base, n, d,
-                       codebooks, M, dsub, codes, dlx);
+                       codebooks, M, dsub, codes, across, dlx);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
 }
@@ -1045,7 +1055,7 @@ int trim_encode(const float *base, int64_t n, int32_t d, const float *codebooks,
     if (n == 0) return TRIM_OK;
     if (!base || !codebooks || !codes_out || !dlx_out) return TRIM_INVALID_ARG;
     if (reinterpret_cast<uintptr_t>(codes_out) & 3u) return TRIM_INVALID_ARG;
-    return encode_codes(base, n, d, codebooks, M, codes_out, dlx_out, static_cast<hipStream_t>(stream));
+    return encode_codes(base, n, d, codebooks, M, codes_out, 0, dlx_out, static_cast<hipStream_t>(stream));
 }
 
 size_t trim_list_bounds_bytes(int32_t nlist, int32_t M) {
@@ -1134,10 +1144,12 @@ int trim_train_pq(const float *train, int64_t ns, int32_t d, int32_t M, int32_t 
                        init_rows, kC, codebooks_out);
     HIP_TRY(hipGetLastError());
     for (int it = 0; it < iters; ++it) {
-        // (the landmark distances that the caller sees are the last iteration's)
-        int rc = encode_codes(train, ns, d, codebooks_out, M, codes_ws, it + 1 < iters ? nullptr : dlx_ws, st);
+        // The codes and landmark distances that the caller sees are the last iteration's; before that the codes are laid out for
+        // the update, subspace by subspace (a workgroup reads 64 KB of 2 MB; row by row every one brings all of it in).
+        const bool last = it + 1 == iters;
+        int rc = encode_codes(train, ns, d, codebooks_out, M, codes_ws, last ? 0 : ns, last ? dlx_ws : nullptr, st);
         if (rc) return rc;
-        if ((rc = launch_kmeans_update<1>(train, ns, d, dsub, codes_ws, M, kC, M, codebooks_out, st))) return rc;
+        if ((rc = launch_kmeans_update<1>(train, ns, d, dsub, codes_ws, last ? M : 1, last ? 1 : ns, kC, M, codebooks_out, st))) return rc;
     }
     return TRIM_OK;
 }
@@ -1156,7 +1168,7 @@ int trim_train_ivf(const float *train, int64_t ns, int32_t d, int32_t nlist, int
     for (int it = 0; it < iters; ++it) {
         int rc = trim_ivf_probe(train, ns, d, centroids_out, nlist, 1, assign_ws, stream);
         if (rc) return rc;
-        if ((rc = launch_kmeans_update<4>(train, ns, d, d, assign_ws, 1, nlist, 1, centroids_out, st))) return rc;
+        if ((rc = launch_kmeans_update<4>(train, ns, d, d, assign_ws, 1, 0, nlist, 1, centroids_out, st))) return rc;
     }
     return TRIM_OK;
 }
@@ -1265,7 +1277,7 @@ int trim_fs_encode(const float *base, int64_t n, int32_t d, const float *codeboo
     if ((size_t)2 * kC4 * dsub * 4 > 64 * 1024) return TRIM_UNSUPPORTED_SHAPE;
     if (n == 0) return TRIM_OK;
     if (!base || !codebooks || !codes_out || !dlx_out) return TRIM_INVALID_ARG;
-    return launch_encode_fs<true>(base, n, d, codebooks, M, codes_out, dlx_out, static_cast<hipStream_t>(stream));
+    return launch_encode_fs<true>(base, n, d, codebooks, M, codes_out, 0, dlx_out, static_cast<hipStream_t>(stream));
 }
 
 int trim_fs_train_pq(const float *train, int64_t ns, int32_t d, int32_t M, int32_t iters,
@@ -1281,8 +1293,10 @@ int trim_fs_train_pq(const float *train, int64_t ns, int32_t d, int32_t M, int32
                        init_rows, kC4, codebooks_out);
     HIP_TRY(hipGetLastError());
     for (int it = 0; it < iters; ++it) {
-        if (const int rc = launch_encode_fs<false>(train, ns, d, codebooks_out, M, assign_ws, nullptr, st)) return rc;
-        if (const int rc = launch_kmeans_update<1>(train, ns, d, dsub, assign_ws, M, kC4, M, codebooks_out, st)) return rc;
+        const bool last = it + 1 == iters;      // (see trim_train_pq)
+        if (const int rc = launch_encode_fs<false>(train, ns, d, codebooks_out, M, assign_ws, last ? 0 : ns, nullptr, st)) return rc;
+        if (const int rc = launch_kmeans_update<1>(train, ns, d, dsub, assign_ws, last ? M : 1, last ? 1 : ns, kC4, M, codebooks_out, st))
+            return rc;
     }
     return TRIM_OK;
 }

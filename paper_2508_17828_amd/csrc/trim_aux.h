@@ -2,6 +2,8 @@
 // assembly, coarse-probe selection, small fills.
 #pragma once
 
+#include <type_traits>
+
 #include "trim_device.h"
 
 namespace trim {
@@ -264,97 +266,108 @@ __global__ void kmeans_init_kernel(const float *__restrict__ x, int64_t ns, int6
 // Update step with every rounding fixed: for cluster c and coordinate t the float64 sum, in
 // ascending row order, of that coordinate over the rows assigned to c; the centroid becomes
 // sum / count rounded once to binary32; a cluster without rows keeps its centroid.
-// Assignments are bytes (ABYTES = 1) or 32-bit integers (ABYTES = 4) with a stride; clustering y
-// (a PQ subspace; grid.y) uses element y of every row's assignments, columns y*dim.., centroid block y.
+// Assignments are bytes (ABYTES = 1) or 32-bit integers (ABYTES = 4); clustering y (a PQ subspace) uses the elements
+// assign[row * astride + y * ystride], columns y*dim.., centroid block y.
 //
-// A workgroup serves 2^cg_log2 clusters.  A chunk of kChunk assignments is put in cluster order
-// by a stable counting sort (ranks inside a wave by matching ballots, wave offsets through LDS);
-// then (the next chunk's assignments are on their way meanwhile) a thread per (cluster, coordinate)
-// adds its rows, straight from memory where that keeps half of the threads busy (long rows),
-// else from LDS, where all threads bring the rows found together.  What is left is
-// the scan of the assignments by every workgroup (L2 reads) and one gather of each row: 65,536
-// rows, 32 x 256 x 4 coordinates: 0.136 ms per iteration (4.28 when each coordinate's thread compared
-// every row with its cluster); 1024 x 128 coordinates: 0.067 ms (3.43).
-constexpr int kUpdThreads = 512, kUpdPer = 16, kUpdChunk = kUpdThreads * kUpdPer;
+// A workgroup serves 2^cg_log2 clusters.  Its rows are found first: kUpdChunk assignments at a time are looked at, 16
+// consecutive rows per lane, and the rows of its clusters are appended to a list, in row order.  The
+// list, some 1/8 of the rows, is put in cluster order by a stable counting sort (ranks
+// inside a wave by matching ballots, wave offsets through LDS) when it is full or the rows are through; then a thread per
+// (cluster, coordinate) adds its rows, straight from memory where that is work for 256 threads and more (long rows),
+// else from LDS, where all threads bring the rows found together.
+// (Sorting the assignments chunk by chunk ranked all of them in every workgroup.)  65,536 rows, 32 x 256 x 4 coordinates: 59 us
+// an iteration (134), 1024 x 128 coordinates: 38 .. 65 us by the largest cluster (72).  Bound by short steps one after
+// the other, one workgroup per CU; about half of it is bringing the rows: 16 bytes of every cache line.
+constexpr int kUpdThreads = 512, kUpdRows = 16, kUpdChunk = kUpdThreads * kUpdRows;
 constexpr int kUpdMaxLog2 = 5;
-constexpr int kUpdVals = 8192;   // row values in LDS at a time
-constexpr int kUpdCols = 256;    // coordinates per workgroup at most (grid.z: slices of that many)
-__host__ __device__ inline bool kmeans_update_direct(int cg_log2, int cols) { return (cols << cg_log2) >= kUpdThreads / 2; }
+constexpr int kUpdList = 16384;  // rows found
+constexpr int kUpdVals = 8192, kUpdPiece = 2048;   // row values, rows in LDS at a time
+constexpr int kUpdCols = 256;    // coordinates per workgroup at most (grid: slices of that many)
+static_assert(kUpdList >= kUpdChunk, "a chunk's rows fit the list");
+__host__ __device__ inline bool kmeans_update_direct(int cg_log2, int cols) { return (cols << cg_log2) >= 256; }
 __host__ __device__ inline size_t kmeans_update_lds(int cg_log2, int cols) {
-    return ((size_t)cols << cg_log2) * 8 + (size_t)kUpdChunk * 2 + (kmeans_update_direct(cg_log2, cols) ? 0 : (size_t)kUpdVals * 4) + (((size_t)kUpdThreads / kWave + 2) * 4 << cg_log2) + 16;
+    return ((size_t)cols << cg_log2) * 8 + (size_t)kUpdList * 4 + (kmeans_update_direct(cg_log2, cols) ? 0 : (size_t)kUpdVals * 4 + kUpdPiece * 2) + (((size_t)kUpdThreads / kWave + 2) * 4 << cg_log2) + 16 + kUpdThreads / kWave * 4;
 }
+struct UpdateArgs {
+    const float *x;            // [ns][stride]
+    const void *assign;
+    int64_t ns, stride, astride, ystride;
+    int32_t dim, K, cg_log2, groups, ny, total;     // total: workgroups that have work
+    float *cent;
+};
 template <int ABYTES>
-__global__ __launch_bounds__(kUpdThreads) void kmeans_update_kernel(const float *__restrict__ x, int64_t ns,
-                                                            int64_t stride, int dim,
-                                                            const void *__restrict__ assign,
-                                                            int64_t astride, int K, int cg_log2,
-                                                            float *__restrict__ cent) {
+__global__ __launch_bounds__(kUpdThreads) void kmeans_update_kernel(const UpdateArgs a) {
     constexpr int kWaves = kUpdThreads / kWave;
     extern __shared__ __align__(16) unsigned char smem[];
-    const int CG = 1 << cg_log2;
-    const int t0 = blockIdx.z * kUpdCols, cols = dim - t0 < kUpdCols ? dim - t0 : kUpdCols;
+    const int CG = 1 << a.cg_log2, dim = a.dim;
+    // an XCD takes neighbouring subspaces: their columns share cache lines
+    const int per_xcd = (a.total + kXcds - 1) / kXcds, w = (int)(blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+    if (w >= a.total || (int)(blockIdx.x / kXcds) >= per_xcd) return;
+    const int group = w % a.groups, y = w / a.groups % a.ny, t0 = w / a.groups / a.ny * kUpdCols;
+    const int cols = dim - t0 < kUpdCols ? dim - t0 : kUpdCols;
     float *vals = reinterpret_cast<float *>(smem);                         // [rows][cols]
     // (the last slice of columns may be narrower than the others: the launch's layout is that of the first)
-    const bool direct = kmeans_update_direct(cg_log2, dim < kUpdCols ? dim : kUpdCols);
+    const bool direct = kmeans_update_direct(a.cg_log2, dim < kUpdCols ? dim : kUpdCols);
     double *sums = reinterpret_cast<double *>(vals + (direct ? 0 : kUpdVals));   // [CG][cols]
-    int *wcount = reinterpret_cast<int *>(sums + (size_t)CG * cols);       // [kWaves][CG]
+    uint32_t *list = reinterpret_cast<uint32_t *>(sums + (size_t)CG * cols);     // [kUpdList] row << 5 | cluster, direct: then rows by cluster
+    int *wcount = reinterpret_cast<int *>(list + kUpdList);                // [kWaves][CG]
     int *rows_of = wcount + kWaves * CG;                                   // [CG] rows per cluster so far
     int *start = rows_of + CG;                                             // [CG + 1] runs of list[]
-    uint16_t *list = reinterpret_cast<uint16_t *>(start + CG + 4);         // [kUpdChunk] rows by cluster
+    int *part = start + CG + 4;                                            // [kWaves]
+    uint16_t *place = reinterpret_cast<uint16_t *>(part + kWaves);         // [kUpdPiece] in cluster order (not direct)
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
-    const int y = blockIdx.y, c_first = blockIdx.x << cg_log2;
-    x += (size_t)y * dim + t0;
-    cent += (size_t)y * K * dim + t0;
+    const int c_first = group << a.cg_log2, wave_id = __builtin_amdgcn_readfirstlane(wave);
+    const float *x = a.x + (size_t)y * dim + t0;
+    float *cent = a.cent + (size_t)y * a.K * dim + t0;
     for (int e = tid; e < CG * cols; e += kUpdThreads) sums[e] = 0.0;
     for (int c = tid; c < CG; c += kUpdThreads) rows_of[c] = 0;
     int *mine = wcount + wave * CG;
     const unsigned long long below = (1ull << lane) - 1ull;
-    // a wave takes kUpdPer x 64 consecutive rows of a chunk, 64 at a time in row order
-    int a[kUpdPer], rank[kUpdPer];
-    auto load_chunk = [&](int64_t i0) {
-#pragma unroll
-        for (int s = 0; s < kUpdPer; ++s) {
-            const int64_t r = i0 + wave * (kUpdPer * kWave) + s * kWave + lane;
-            a[s] = -1;
-            if (r < ns) {
-                const size_t at = (size_t)r * astride + y;
-                a[s] = (ABYTES == 1 ? (int)static_cast<const uint8_t *>(assign)[at]
-                                    : static_cast<const int32_t *>(assign)[at]) - c_first;
-            }
-        }
-    };
-    load_chunk(0);
-    for (int64_t i0 = 0; i0 < ns; i0 += kUpdChunk) {
+    const bool vec = ((cols | dim) & 3) == 0 && (a.stride & 3) == 0 && (reinterpret_cast<uintptr_t>(a.x) & 15u) == 0;
+    int64_t row0 = 0;        // the list's rows are relative to this one
+    int found = 0;           // (the same for all threads)
+    // Places in cluster order of the entries list[p0 .. p1), by a stable counting sort: f(entry of the list, what it holds, its
+    // place), start[] the clusters' first places.  Barriers before and after.
+    auto sort_rows = [&](int p0, int p1, auto loops, auto &&f) {
+        constexpr int kLoops = decltype(loops)::value;
+        uint32_t mem[kLoops];
+        int rank[kLoops];
+        const int seg = ((p1 - p0 + kWaves - 1) / kWaves + kWave - 1) / kWave * kWave, s0 = p0 + wave * seg;
         for (int c = lane; c < CG; c += kWave) mine[c] = 0;
+#pragma unroll
+        for (int s = 0; s < kLoops; ++s) mem[s] = s * kWave < seg && s0 + s * kWave + lane < p1 ? list[s0 + s * kWave + lane] : 0u;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int s = 0; s < kUpdPer; ++s) {
-            const bool in = (unsigned)a[s] < (unsigned)CG;
+        for (int s = 0; s < kLoops; ++s) {
+            rank[s] = -1;
+            if (s * kWave >= seg || s0 + s * kWave >= p1) continue;      // same for the wave
+            const bool in = s0 + s * kWave + lane < p1;
+            const int c = (int)(mem[s] & 31u);
             unsigned long long same = __ballot(in);
-            rank[s] = 0;
-            if (same == 0) continue;                     // same for the wave
-            for (int b = 0; b < cg_log2; ++b) {
-                const bool bit = (a[s] >> b) & 1;
+            for (int b = 0; b < a.cg_log2; ++b) {
+                const bool bit = (c >> b) & 1;
                 const unsigned long long m = __ballot(bit);
                 same &= bit ? m : ~m;
             }
             const int before = __popcll(same & below);
-            if (in) rank[s] = mine[a[s]] + before;
+            if (in) rank[s] = mine[c] + before;
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
-            if (in && before == 0) mine[a[s]] += __popcll(same);
+            if (in && before == 0) mine[c] += __popcll(same);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }
         __syncthreads();
         if (wave == 0) {                                 // counts -> first slots
-            int run = 0;
-            if (lane < CG)
-                for (int w = 0; w < kWaves; ++w) { const int v = wcount[w * CG + lane]; wcount[w * CG + lane] = run; run += v; }
+            int n[kWaves], run = 0;
+#pragma unroll
+            for (int v = 0; v < kWaves; ++v) n[v] = lane < CG ? wcount[v * CG + lane] : 0;
+#pragma unroll
+            for (int v = 0; v < kWaves; ++v) { const int k = n[v]; n[v] = run; run += k; }
             int incl = run;
 #pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) {
+            for (int off = 1; off < 1 << kUpdMaxLog2; off <<= 1) {
                 const int v = __shfl_up(incl, off);
                 if (lane >= off) incl += v;
             }
@@ -362,19 +375,21 @@ __global__ __launch_bounds__(kUpdThreads) void kmeans_update_kernel(const float 
                 rows_of[lane] += run;
                 start[lane] = incl - run;
                 if (lane == CG - 1) start[CG] = incl;
-                for (int w = 0; w < kWaves; ++w) wcount[w * CG + lane] += incl - run;
+#pragma unroll
+                for (int v = 0; v < kWaves; ++v) wcount[v * CG + lane] = n[v] + incl - run;
             }
         }
         __syncthreads();
 #pragma unroll
-        for (int s = 0; s < kUpdPer; ++s)
-            if ((unsigned)a[s] < (unsigned)CG)
-                list[mine[a[s]] + rank[s]] = (uint16_t)(wave * (kUpdPer * kWave) + s * kWave + lane);
-        if (i0 + kUpdChunk < ns) load_chunk(i0 + kUpdChunk);
+        for (int s = 0; s < kLoops; ++s)
+            if (rank[s] >= 0) f(s0 + s * kWave + lane, mem[s], mine[mem[s] & 31u] + rank[s]);
         __syncthreads();
-        const int found = start[CG], piece = kUpdVals / cols;
-        const float *xi = x + (size_t)i0 * stride;
+    };
+    // the rows in list[0 .. found) are added
+    auto add_rows = [&]() {
+        const float *xi = x + (size_t)row0 * a.stride;
         if (direct) {
+            sort_rows(0, found, std::integral_constant<int, kUpdList / kUpdThreads>(), [&](int, uint32_t m, int at) { list[at] = m >> 5; });
             for (int e = tid; e < CG * cols; e += kUpdThreads) {
                 const int c = e / cols;
                 const float *xt = xi + (e - c * cols);
@@ -382,41 +397,151 @@ __global__ __launch_bounds__(kUpdThreads) void kmeans_update_kernel(const float 
                 const int end = start[c + 1];
                 if (i >= end) continue;
                 double sum = sums[e];
-                for (; i < end; i += 8) {
-                    float v[8];
+                constexpr int kFly = 32;       // loads in flight
+                for (; i < end; i += kFly) {
+                    float v[kFly];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) v[u] = xt[(size_t)list[i + u < end ? i + u : i] * stride];
+                    for (int u = 0; u < kFly; ++u) v[u] = xt[(size_t)list[i + u < end ? i + u : i] * a.stride];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u)
+                    for (int u = 0; u < kFly; ++u)
                         if (i + u < end) sum += (double)v[u];
                 }
                 sums[e] = sum;
             }
-            continue;    // (the next chunk writes list[] and start[] after barriers that come after this)
+            __syncthreads();
+            return;
         }
+        // Short rows: read in row order, so that workgroups of neighbouring subspaces, whose columns share cache lines, read a
+        // line at about the same time, and that all clusters have something to add in a piece; stored in cluster order.
+        const int piece = kUpdVals / cols < kUpdPiece ? kUpdVals / cols : kUpdPiece;
         for (int p0 = 0; p0 < found; p0 += piece) {
             const int p1 = p0 + piece < found ? p0 + piece : found;
-            for (int e = tid; e < (p1 - p0) * cols; e += kUpdThreads) {
-                const int i = e / cols;
-                vals[e] = xi[(size_t)list[p0 + i] * stride + (e - i * cols)];
+            sort_rows(p0, p1, std::integral_constant<int, kUpdPiece / kUpdThreads>(), [&](int i, uint32_t, int at) { place[i - p0] = (uint16_t)at; });
+            const int g4 = vec ? cols >> 2 : cols, all = (p1 - p0) * g4;
+            for (int e0 = tid; e0 < all; e0 += 4 * kUpdThreads) {
+                float4 v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int e = e0 + u * kUpdThreads < all ? e0 + u * kUpdThreads : e0, i = e / g4;
+                    const float *at = xi + (size_t)(list[p0 + i] >> 5) * a.stride;
+                    if (vec) v[u] = *reinterpret_cast<const float4 *>(at + 4 * (e - i * g4));
+                    else v[u].x = at[e - i * g4];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int e = e0 + u * kUpdThreads, i = e / g4;
+                    if (e >= all) continue;
+                    float *to = vals + (int)place[i] * cols;
+                    if (vec) *reinterpret_cast<float4 *>(to + 4 * (e - i * g4)) = v[u];
+                    else to[e - i * g4] = v[u].x;
+                }
             }
             __syncthreads();
             for (int e = tid; e < CG * cols; e += kUpdThreads) {
                 const int c = e / cols, t = e - c * cols;
-                const int lo = start[c] > p0 ? start[c] : p0, hi = start[c + 1] < p1 ? start[c + 1] : p1;
-                if (lo >= hi) continue;
+                int i = start[c];
+                const int hi = start[c + 1];
+                if (i >= hi) continue;
                 double sum = sums[e];
-                const float *v = vals + t - (ptrdiff_t)p0 * cols;
-#pragma unroll 4
-                for (int i = lo; i < hi; ++i) sum += (double)v[i * cols];
+                const float *v = vals + t + i * cols;
+                // (16 values on their way before the first is added: one by one an addition took 110 clocks)
+                constexpr int kFly = 16;
+                float f[kFly];
+                for (; i + kFly <= hi; i += kFly) {
+#pragma unroll
+                    for (int u = 0; u < kFly; ++u) { f[u] = *v; v += cols; }
+#pragma unroll
+                    for (int u = 0; u < kFly; ++u) sum += (double)f[u];
+                }
+                for (; i < hi; ++i, v += cols) sum += (double)*v;
                 sums[e] = sum;
             }
             __syncthreads();
         }
+    };
+    constexpr int kWords = 4 * ABYTES;
+    const unsigned char *assign = static_cast<const unsigned char *>(a.assign) + (size_t)y * a.ystride * ABYTES;
+    uint32_t next[kWords];       // the assignments of this lane's rows of a chunk
+    auto load_chunk = [&](int64_t i0) {
+        const int64_t r0 = i0 + tid * kUpdRows;
+        if (a.astride == 1 && i0 + kUpdChunk <= a.ns) {
+            __builtin_memcpy(next, assign + (size_t)r0 * ABYTES, sizeof(next));
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < kWords; ++i) next[i] = 0;
+#pragma unroll
+        for (int i = 0; i < kUpdRows; ++i) {
+            const size_t e = (size_t)(r0 + i < a.ns ? r0 + i : a.ns - 1) * a.astride;      // (not counted past the end)
+            if constexpr (ABYTES == 1) next[i / 4] |= (uint32_t)assign[e] << (8 * (i & 3));
+            else next[i % kWords] = reinterpret_cast<const uint32_t *>(assign)[e];
+        }
+    };
+    const uint32_t pattern = (uint32_t)c_first * 0x01010101u, group_bits = (uint32_t)(0xff & ~(CG - 1)) * 0x01010101u;
+    load_chunk(0);
+    __syncthreads();
+    for (int64_t i0 = 0;; i0 += kUpdChunk) {      // (past the last chunk once more: no rows, the list is added)
+        uint32_t w[kWords], in = 0;               // this lane's rows: assignments, and a bit for each of the group's
+#pragma unroll
+        for (int i = 0; i < kWords; ++i) {
+            w[i] = next[i];
+            if constexpr (ABYTES == 1) {          // four bytes at a time: a byte's top bit is set where it is in the group
+                const uint32_t v = (w[i] ^ pattern) & group_bits;
+                const uint32_t hit = ~(((v & 0x7f7f7f7fu) + 0x7f7f7f7fu) | v | 0x7f7f7f7fu);
+                in |= ((hit >> 7) * 0x01020408u >> 24) << (4 * i);
+            } else {
+                in |= (w[i] - (uint32_t)c_first < (uint32_t)CG ? 1u : 0u) << i;
+            }
+        }
+        const int64_t left = a.ns - i0 - tid * kUpdRows;
+        in &= left >= kUpdRows ? 0xffffu : left > 0 ? (1u << left) - 1u : 0u;
+        if (i0 + kUpdChunk < a.ns) load_chunk(i0 + kUpdChunk);
+        const uint32_t cnt = (uint32_t)__popc(in);
+        int lower = 0, total = 0;                 // rows of the lanes below, of the wave
+#pragma unroll
+        for (int b = 0; b < 5; ++b) {
+            const unsigned long long m = __ballot(cnt >> b & 1u);
+            lower += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)) << b;
+            total += __popcll(m) << b;
+        }
+        if (lane == 0) part[wave] = total;
+        __syncthreads();
+        int n = part[lane & (kWaves - 1)];        // the waves' prefix, in every wave
+        int incl = n;
+#pragma unroll
+        for (int off = 1; off < kWaves; off <<= 1) {
+            const int v = __shfl_up(incl, off, kWaves);
+            if ((lane & (kWaves - 1)) >= off) incl += v;
+        }
+        const int before = __builtin_amdgcn_readlane(incl - n, wave_id), all = __builtin_amdgcn_readlane(incl, kWaves - 1);
+        if (i0 >= a.ns || found + all > kUpdList || i0 - row0 > (int64_t(1) << 26)) {      // (a row takes 27 bits of an entry)
+            if (found > 0) add_rows();
+            if (i0 >= a.ns) break;
+            found = 0;
+            row0 = i0;
+        }
+        int to = found + before + lower;
+        const uint32_t r = (uint32_t)(i0 - row0) + tid * kUpdRows;
+        while (in) {
+            const int i = __ffs((int)in) - 1;
+            in &= in - 1;
+            uint32_t c = 0;
+            if constexpr (ABYTES == 1) {
+                const uint32_t v = i & 8 ? (i & 4 ? w[3] : w[2]) : (i & 4 ? w[1] : w[0]);
+                c = v >> (8 * (i & 3));
+            } else {
+#pragma unroll
+                for (int k = 0; k < kWords; ++k) c = k == i ? w[k] : c;
+                c -= (uint32_t)c_first;
+            }
+            list[to++] = (r + i) << 5 | (c & (uint32_t)(CG - 1));
+        }
+        found += all;
+        __syncthreads();
     }
     for (int e = tid; e < CG * cols; e += kUpdThreads) {
         const int c = e / cols;
-        if (c_first + c < K && rows_of[c] > 0)
+        if (c_first + c < a.K && rows_of[c] > 0)
             cent[(size_t)(c_first + c) * dim + (e - c * cols)] = (float)(sums[e] / (double)rows_of[c]);
     }
 }
@@ -757,6 +882,7 @@ __global__ __launch_bounds__(256) void gamma_normal_kernel(const GammaNormalArgs
 // margin: every group is then evaluated exactly.
 //
 // 1,000,000 x 128, d/M = 4: 0.65 ms (1.75 ms on the vector ALU alone); 83,333 x 1536, d/M = 8: 0.84 ms.
+// across: 0, or (ACROSS) the codes are stored subspace by subspace, that many bytes apart (what training's update reads best).
 // BLK: blocks of 32 vectors per wave (2; 1 where that leaves fewer than two workgroups per CU).
 // Where there are still fewer, grid.y workgroups take jper subspaces each of the same vectors and
 // encode_dlx_kernel adds the landmark distances up afterwards (their order of summation crosses
@@ -767,10 +893,11 @@ template <int D, int BLK>
 constexpr size_t encode_lds() {
     return (size_t)kEncSteps<D> * 2 * kC * 16 + (size_t)(kC / 8) * (8 * D + 4) * 4 + (size_t)(kEncThreads / 2) * BLK * (4 * D + 4) * 4 + 16;
 }
-template <int D, int BLK>
+template <int D, int BLK, bool ACROSS>
 __global__ __launch_bounds__(kEncThreads) void encode_mfma_kernel(const float *__restrict__ base, int64_t n, int d,
                                                                   const float *__restrict__ codebooks, int M, int jper,
-                                                                  uint8_t *__restrict__ codes, float *__restrict__ dlx) {
+                                                                  uint8_t *__restrict__ codes, int64_t across,
+                                                                  float *__restrict__ dlx) {
     typedef _Float16 h8 __attribute__((ext_vector_type(8)));
     typedef float v16f __attribute__((ext_vector_type(16)));
     constexpr int KS = kEncSteps<D>, NX = kEncThreads / 2 * BLK, XS = 4 * D + 4;
@@ -969,7 +1096,14 @@ __global__ __launch_bounds__(kEncThreads) void encode_mfma_kernel(const float *_
             packed[b] |= (uint32_t)arg << (8 * (j & 3));
             if ((j & 3) == 3) {
                 const int64_t xi = x0 + (wave * BLK + b) * 32 + col;
-                if (half == 0 && xi < n) *reinterpret_cast<uint32_t *>(codes + (size_t)xi * M + (j - 3)) = packed[b];
+                if (half == 0 && xi < n) {
+                    if constexpr (ACROSS) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) codes[(size_t)(j - 3 + i) * across + xi] = (uint8_t)(packed[b] >> (8 * i));
+                    } else {
+                        *reinterpret_cast<uint32_t *>(codes + (size_t)xi * M + (j - 3)) = packed[b];
+                    }
+                }
                 packed[b] = 0;
             }
         }
@@ -1018,7 +1152,7 @@ __global__ __launch_bounds__(256) void encode_dlx_kernel(const float *__restrict
 __global__ __launch_bounds__(256) void encode_kernel(const float *__restrict__ base, int64_t n,
                                                      int d, const float *__restrict__ codebooks,
                                                      int M, int dsub,
-                                                     uint8_t *__restrict__ codes,
+                                                     uint8_t *__restrict__ codes, int64_t across,
                                                      float *__restrict__ dlx) {
     extern __shared__ __align__(16) unsigned char smem[];
     float *cb = reinterpret_cast<float *>(smem);  // [256][dsub]
@@ -1043,9 +1177,10 @@ __global__ __launch_bounds__(256) void encode_kernel(const float *__restrict__ b
             if (acc < best) { best = acc; arg = c; }
         }
         tot = tot + best;
+        if (across && valid) codes[(size_t)j * across + i] = (uint8_t)arg;
         packed |= (uint32_t)arg << (8 * (j & 3));
         if ((j & 3) == 3) {
-            if (valid) *reinterpret_cast<uint32_t *>(codes + (size_t)i * M + (j - 3)) = packed;
+            if (valid && !across) *reinterpret_cast<uint32_t *>(codes + (size_t)i * M + (j - 3)) = packed;
             packed = 0;
         }
     }
@@ -1054,7 +1189,7 @@ __global__ __launch_bounds__(256) void encode_kernel(const float *__restrict__ b
 
 // ---- PQ encode with 16 centroids per subspace (4-bit codes; Section 6.1, FastScan variants) ----
 // PACKED: two codes per byte, the even subspace's in the low half (the stored index); else one
-// byte per subspace (the assignments training works on).
+// byte per subspace (the assignments training works on; across: see encode_mfma_kernel).
 //
 // Sub-vectors of two values (m = d/2, the paper's variant): one thread per vector; the block's
 // rows pass through the LDS 32 columns at a time (whole cache lines from memory, 16-byte reads
@@ -1065,7 +1200,8 @@ constexpr int kFsRows = 256, kFsCols = 32, kFsStride = kFsCols + 4;
 template <bool PACKED>
 __global__ __launch_bounds__(kFsRows) void encode_fs2_kernel(const float *__restrict__ base, int64_t n, int d,
                                                              const float *__restrict__ codebooks, int m,
-                                                             uint8_t *__restrict__ codes, float *__restrict__ dlx) {
+                                                             uint8_t *__restrict__ codes, int64_t across,
+                                                             float *__restrict__ dlx) {
     __shared__ __align__(16) float xt[kFsRows * kFsStride];
     const int64_t x0 = (int64_t)blockIdx.x * kFsRows, i = x0 + threadIdx.x;
     const bool valid = i < n;
@@ -1121,6 +1257,10 @@ __global__ __launch_bounds__(kFsRows) void encode_fs2_kernel(const float *__rest
             for (int o = 0; o < (PACKED ? 2 : 4); ++o) out[o] = o == wd ? word : out[o];
         }
         if (!valid) continue;
+        if (!PACKED && across) {
+            for (int b = 0; b < cols / 2; ++b) codes[(size_t)(c0 / 2 + b) * across + i] = (uint8_t)(out[b >> 2] >> (8 * (b & 3)));
+            continue;
+        }
         uint8_t *to = codes + (size_t)i * per_row + (PACKED ? c0 / 4 : c0 / 2);
         if (cols == kFsCols && vec_out) {
             if constexpr (PACKED) *reinterpret_cast<uint2 *>(to) = make_uint2(out[0], out[1]);
@@ -1136,7 +1276,7 @@ __global__ __launch_bounds__(kFsRows) void encode_fs2_kernel(const float *__rest
 template <bool PACKED>
 __global__ __launch_bounds__(256) void encode_fs_kernel(const float *__restrict__ base, int64_t n, int d,
                                                         const float *__restrict__ codebooks, int m,
-                                                        int dsub, uint8_t *__restrict__ codes,
+                                                        int dsub, uint8_t *__restrict__ codes, int64_t across,
                                                         float *__restrict__ dlx) {
     extern __shared__ __align__(16) unsigned char smem[];
     float *cb = reinterpret_cast<float *>(smem);  // [2][16][dsub]: the two subspaces of one code byte
@@ -1165,7 +1305,7 @@ __global__ __launch_bounds__(256) void encode_fs_kernel(const float *__restrict_
             }
             tot = tot + best;
             if (PACKED) byte |= (uint32_t)arg << (4 * h);
-            else if (valid) codes[(size_t)i * m + j] = (uint8_t)arg;
+            else if (valid) codes[across ? (size_t)j * across + i : (size_t)i * m + j] = (uint8_t)arg;
         }
         if (PACKED && valid) codes[(size_t)i * (m / 2) + jb] = (uint8_t)byte;
     }

@@ -17,6 +17,7 @@ namespace trim {
 constexpr int kC = 256;          // centroids per subspace (the paper's C)
 constexpr int kC4 = 16;          // centroids per subspace with 4-bit codes (Section 6.1: FastScan variants)
 constexpr int kWave = 64;
+constexpr int kXcds = 8;  // accelerator dies of an MI355X, each with its own L2
 
 // Layout of a query's distance table in LDS, per code BYTE.  8-bit codes: a byte selects one of
 // the 256 entries of its subspace's row.  4-bit codes (FS): a byte holds the codes of two

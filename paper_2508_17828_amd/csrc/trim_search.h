@@ -25,7 +25,6 @@ constexpr uint32_t kTabLds = 0;
 // roundings of a partial sum (see abandon_threshold), and every candidate that passes has its
 // sum redone from the 16-entry rows in subspace order.  The table proper follows at kTabAt.
 template <bool FS> constexpr uint32_t kTabAt = FS ? 8 * kC * 4 : kTabLds;
-constexpr int kXcds = 8;  // accelerator dies of an MI355X, each with its own L2
 
 struct SearchArgs {
     // index (Section 3.3 preprocessing output)

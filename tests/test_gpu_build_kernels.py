@@ -15,8 +15,8 @@ def T():
 
 
 # rows around the 8192-row chunks of the update; clusters that leave a last group partly empty; a row
-# longer than one 1024-column slice; one cluster that takes nearly everything
-@pytest.mark.parametrize("ns,d,nlist", [(8191, 8, 7), (8193, 12, 33), (16385, 4, 130), (9000, 1028, 5)])
+# longer than one 1024-column slice; one cluster that takes nearly everything; a list of rows that fills several times
+@pytest.mark.parametrize("ns,d,nlist", [(8191, 8, 7), (8193, 12, 33), (16385, 4, 130), (9000, 1028, 5), (1, 4, 1), (70001, 4, 2)])
 def test_update_of_coarse_centroids(T, oracle, ns, d, nlist):
     import torch
     from oracle import index_build
@@ -29,7 +29,8 @@ def test_update_of_coarse_centroids(T, oracle, ns, d, nlist):
     np.testing.assert_array_equal(got.view(np.uint32), want.view(np.uint32))
 
 
-@pytest.mark.parametrize("ns,d,M,bits", [(8192, 16, 4, 8), (8200, 20, 4, 8), (300, 64, 4, 8), (8300, 8, 4, 4)])
+@pytest.mark.parametrize("ns,d,M,bits", [(8192, 16, 4, 8), (8200, 20, 4, 8), (300, 64, 4, 8), (8300, 8, 4, 4),
+                                         (40003, 28, 4, 8), (40001, 24, 8, 4), (257, 132, 4, 8)])
 def test_update_of_codebooks(T, oracle, ns, d, M, bits):
     import torch
     from oracle import index_build
@@ -40,8 +41,8 @@ def test_update_of_codebooks(T, oracle, ns, d, M, bits):
     init = rng.choice(ns, K, replace=False).astype(np.int32)
     fn = T.trim_train_pq if bits == 8 else T.trim_fs_train_pq
     ref = index_build.train_pq_fixed if bits == 8 else index_build.train_pq_fs_fixed
-    want = ref(x, M, 2, init)
-    got = fn(torch.from_numpy(x).cuda(), M, 2, torch.from_numpy(init).cuda()).cpu().numpy()
+    want = ref(x, M, 3, init)
+    got = fn(torch.from_numpy(x).cuda(), M, 3, torch.from_numpy(init).cuda()).cpu().numpy()
     np.testing.assert_array_equal(got.view(np.uint32), want.view(np.uint32))
 
 
