@@ -1069,7 +1069,8 @@ int trim_pack_list_bounds(const trim_index_view *index, const int64_t *list_offs
     if (rc != TRIM_OK) return rc;
     if (nlist <= 0 || !list_offsets || !out || !aligned16(out)) return TRIM_INVALID_ARG;
     const int Mb = code_bytes(index);   // summaries are kept per code byte
-    hipLaunchKernelGGL(list_bounds_kernel, dim3((unsigned)nlist), dim3(256), (size_t)Mb * 32,
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(list_bounds_kernel), (size_t)Mb * kBoundsPitch * 4));
+    hipLaunchKernelGGL(list_bounds_kernel, dim3((unsigned)nlist), dim3(kBoundsThreads), (size_t)Mb * kBoundsPitch * 4,
                        static_cast<hipStream_t>(stream), index->codes, index->dlx, index->n, Mb,
                        list_offsets, static_cast<uint8_t *>(out));
     HIP_TRY(hipGetLastError());
