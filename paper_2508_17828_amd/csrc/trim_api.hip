@@ -335,9 +335,11 @@ int launch_encode(const float *base, int64_t n, int d, const float *codebooks, i
                : (wide ? encode_mfma_kernel<D, 2, false> : encode_mfma_kernel<D, 1, false>);
     const size_t lds = wide ? encode_lds<D, 2>() : encode_lds<D, 1>();
     const int64_t blocks = (n + per - 1) / per;
-    int jper = M;       // subspaces per workgroup: all, or fewer until there are about three workgroups per CU
-    if (blocks < 384) {
-        const int64_t split = std::min<int64_t>(M / 4, (768 + blocks - 1) / blocks);
+    // subspaces per workgroup: all, or fewer until there are about three workgroups per CU; four where nobody wants the landmark
+    // distances, which take a pass of their own then (training, 65,536 x 128: 57 us an iteration, 76 with two)
+    int jper = M;
+    if (blocks < (dlx ? 384 : 768)) {
+        const int64_t split = std::min<int64_t>(M / 4, ((dlx ? 768 : 1024) + blocks - 1) / blocks);
         jper = (int)((M / 4 + split - 1) / split) * 4;
     }
     HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), lds));
