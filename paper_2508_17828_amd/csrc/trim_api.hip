@@ -1500,9 +1500,11 @@ int trim_ivf_probe(const float *queries, int64_t nq, int32_t d, const float *cen
     // workgroups would do it, and below 64 lists a 256-wide tile is mostly padding.
     if (nprobe == 1 && nq >= 4096 && nlist >= 64 && d <= kAsgMaxD && aligned16(queries)) {
         const size_t lds1 = assign_lds(d), lds2 = (size_t)8 * d * 4;
-        HIP_TRY(allow_lds(reinterpret_cast<const void *>(assign_mfma_kernel), lds1));
+        void (*assign)(const float *, int64_t, int, const float *, int, int32_t *) = assign_mfma_kernel;
+        if (d <= kAsrCols) assign = d <= kAsrCols / 2 ? assign_rows_kernel<4> : assign_rows_kernel<8>;
+        else HIP_TRY(allow_lds(reinterpret_cast<const void *>(assign_mfma_kernel), lds1));
         HIP_TRY(allow_lds(reinterpret_cast<const void *>(assign_fix_kernel), lds2));
-        hipLaunchKernelGGL(assign_mfma_kernel, dim3((unsigned)((nq + kAsgTile - 1) / kAsgTile)), dim3(kAsgThreads), lds1, st,
+        hipLaunchKernelGGL(assign, dim3((unsigned)((nq + kAsgTile - 1) / kAsgTile)), dim3(kAsgThreads), d <= kAsrCols ? 0 : lds1, st,
                            queries, nq, d, centroids, nlist, probes_out);
         HIP_TRY(hipGetLastError());
         int span = kFixSpan;

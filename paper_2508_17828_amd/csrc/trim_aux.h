@@ -1967,7 +1967,7 @@ __global__ __launch_bounds__(512) void ivf_probe_kernel(const float *__restrict_
 // Margin: twice E = (2^-16 + (3 d + 16) 2^-24) 2 |x||c|max     split, binary32 accumulation
 //                 + d 2^-24 |c|max^2 + d 2^-24 |x|^2             the norms
 //                 + (d / 32 + 8) 2^-24 (|x| + |c|max)^2          the exact rule's own roundings
-// 1,000,000 x 128 against 1024 lists: 1.33 ms with the marked vectors (9.3 ms measured exactly).
+// 1,000,000 x 128 against 1024 lists: 1.33 ms with the marked vectors (9.3 ms measured exactly).  Rows of up to 128 values: assign_rows_kernel.
 constexpr int kAsgThreads = 512, kAsgTile = 256, kAsgSlice = 32, kAsgMaxD = 4096;
 inline size_t assign_lds(int d) { return (size_t)2 * 4 * 4 * kAsgTile * 16 + (size_t)((d + kAsgSlice - 1) / kAsgSlice * kAsgSlice) * 4 + 2 * kAsgTile * 4 + 64; }
 
@@ -2179,10 +2179,342 @@ __global__ __launch_bounds__(kAsgThreads) void assign_mfma_kernel(const float *_
     }
 }
 
+// The same for rows of at most 128 values (KS: steps of 16 values, 4 or 8), where a wave keeps its vectors' operands
+// in registers: 64 vectors per wave for all columns, and only the centroids pass through the LDS, converted once per
+// workgroup of 256 vectors.
+//   operands  values relative to mu, scaled by a power of two, as ONE binary16 value each (x', c'); what is scored is
+//             |x' - c'|^2, so that what rounding moved counts against the distance and not against the lengths: with r' = |x' - c'|,
+//             whoever may be nearest has r' <= r'min + 2 (moved(x) + moved(c)max).  |x'|^2 and |c'|^2 come in by one
+//             more step of the matrix cores, as three binary16 pieces each against 2^15.
+//   trackers  scores are ordered by their bits, as signed numbers (one below zero is within the bound of zero), the low ones
+//             replaced by the centroid's number; a lane keeps the three least of every other centroid of its quarter:
+//             one insertion of the number, one minimum and two medians of three a score
+//   schedule  waves 0 to 3 and 4 to 7 share the SIMDs; the ones multiply while the others track
+//   decision  everybody within the bound is measured by the exact rule, four pairs to a half wave; the vector is marked only
+//             where the third of a tracker is within the bound too
+// 1,000,000 x 128 against 1024 lists: 650 us (1215 with the kernel above), 65,536: 41 us (77), and hardly any marks: 5 us
+// for them (103).  A workgroup: 18,000 clocks until its vectors are in registers (rows from memory, by all workgroups at once), 3,700 a stage
+// of 64 centroids (vector ALU: 4 operations a score, 5 a value converted), 6,000 for the decision.
+constexpr int kAsrCols = 128;
+template <int KS>
+struct AsrShape {
+    static constexpr int kTiles = 8 / KS, kRows = 64 * kTiles, kPitch = kRows + 8;     // 32-row tiles per wave; centroids per stage (and spare ones: bank spread)
+    static constexpr int kStage = (KS * 2 + 1) * kPitch * 16;                          // bytes
+};
+template <int KS>
+__global__ __launch_bounds__(kAsgThreads, 2) void assign_rows_kernel(const float *__restrict__ xs, int64_t n, int d,
+                                                                     const float *__restrict__ cent, int nlist,
+                                                                     int32_t *__restrict__ out) {
+    typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+    typedef float v16f __attribute__((ext_vector_type(16)));
+    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    using Shape = AsrShape<KS>;
+    constexpr int TT = Shape::kTiles, R = Shape::kRows, P = Shape::kPitch, kTrk = 8;
+    constexpr int kAreaA = 2 * Shape::kStage, kAreaB = 3 * kTrk * kAsgTile * 4;
+    __shared__ __align__(16) unsigned char s_buf[kAreaA > kAreaB ? kAreaA : kAreaB];   // the stages; then the trackers
+    __shared__ __align__(16) float s_mu[kAsrCols];
+    __shared__ float s_xn[kAsgTile], s_xm[kAsgTile];
+    __shared__ uint32_t s_pair[kAsgTile * 2 * kTrk];                            // vector | centroid << 8
+    __shared__ unsigned long long s_best[kAsgTile];
+    __shared__ uint32_t s_top[2], s_cmax, s_mmax;
+    __shared__ int s_np;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, half = lane >> 5, xg = wave & 3, cg = wave >> 2;
+    const int64_t x0 = (int64_t)blockIdx.x * kAsgTile;
+    // KS lanes bring a row, 16 bytes each at a time: values 4 (g KS + s_ks) and the next three
+    const int s_row = tid / KS, s_ks = tid & (KS - 1);
+    auto bring = [&](const float *row, f4 (&v)[4]) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int k = 4 * (g * KS + s_ks);
+            v[g] = *reinterpret_cast<const f4 *>(row + (k < d ? k : 0));       // (columns past d: not used)
+        }
+    };
+    // the vectors, all on their way at once
+    constexpr int NX = kAsgTile / R;
+    f4 xv[NX][4];
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+        const int r = i * R + s_row;
+        bring(xs + (size_t)(x0 + r < n ? x0 + r : n - 1) * d, xv[i]);
+    }
+    if (tid < kAsrCols) {           // mean and spread of 16 centroids
+        float v[16], sum = 0.0f, most = 0.0f;
+        const int t = tid < d ? tid : 0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = cent[(size_t)((int64_t)i * nlist >> 4) * d + t];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sum += v[i];
+        const float mu = sum * (1.0f / 16.0f);
+        uint32_t top = 0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) { most = __builtin_fabsf(v[i] - mu); top = max(top, __float_as_uint(most)); }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) top = max(top, (uint32_t)__shfl_xor((int)top, off));
+        s_mu[tid] = mu;
+        if (lane == 0) s_top[wave] = top;
+    }
+    if (tid == 0) { s_cmax = s_mmax = 0; s_np = 0; }
+    if (tid < kAsgTile) s_best[tid] = ~0ull;
+    __syncthreads();
+    const uint32_t top = max(s_top[0], s_top[1]);
+    const bool usable = __uint_as_float(top) > 1e-30f && __uint_as_float(top) < 1e30f;
+    const float sc = __uint_as_float((uint32_t)((usable ? 6 - ((int)(top >> 23) - 127) : 0) + 127) << 23);     // (the spread: 2^6 .. 2^7)
+    constexpr float kPiece = 32768.0f, kReach = 2.0e9f;
+    // three pieces of a norm, in the slots from `at` on; the other side of them is kPiece
+    auto pieces = [](h8 &f, int at, float norm) {
+        const float q = norm * (1.0f / kPiece);
+        const _Float16 p1 = (_Float16)q, p2 = (_Float16)(q - (float)p1), p3 = (_Float16)((q - (float)p1) - (float)p2);
+        f[at] = p1; f[at + 1] = p2; f[at + 2] = p3;
+    };
+    // a row's values as operands, times `by`, into buffer b; norm: of what is stored, moved: by rounding (the row's sums, in all its lanes)
+    auto put = [&](int b, const f4 (&a)[4], float by, float &norm, float &moved, float &most) {
+        norm = moved = most = 0.0f;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int k = 4 * (g * KS + s_ks);
+            const f4 m = *reinterpret_cast<const f4 *>(s_mu + k);
+            const float scale = k < d ? by : 0.0f;
+            h2 f[2];
+#pragma unroll
+            for (int e = 0; e < 4; e += 2) {       // (the power of two: one rounding, that of the difference)
+                const f2 v = {__builtin_fmaf(a[g][e], scale, -(m[e] * scale)), __builtin_fmaf(a[g][e + 1], scale, -(m[e + 1] * scale))};
+                const h2 h = __builtin_convertvector(v, h2);
+                const f2 back = __builtin_convertvector(h, f2);
+                const float r0 = v[0] - back[0], r1 = v[1] - back[1];
+                moved = __builtin_fmaf(r0, r0, moved);
+                moved = __builtin_fmaf(r1, r1, moved);
+                most = __builtin_fmaxf(most, __builtin_fmaxf(__builtin_fabsf(v[0]), __builtin_fabsf(v[1])));
+                norm = __builtin_amdgcn_fdot2(h, h, norm, false);
+                f[e / 2] = h;
+            }
+            *reinterpret_cast<h4 *>(s_buf + b * Shape::kStage + ((k >> 3) * P + s_row) * 16 + (k & 4) * 2) = h4{f[0][0], f[0][1], f[1][0], f[1][1]};
+        }
+        auto over = [&](auto &&f) {
+            f(std::integral_constant<int, 1>());
+            f(std::integral_constant<int, 2>());
+            if constexpr (KS == 8) f(std::integral_constant<int, 4>());
+        };
+        over([&](auto bit) {
+            constexpr int kBit = decltype(bit)::value;
+            norm = norm + lane_xor<kBit>(norm);
+            moved = moved + lane_xor<kBit>(moved);
+            most = __builtin_fmaxf(most, lane_xor<kBit>(most));
+        });
+    };
+    f4 ahead[4];
+    auto load = [&](int st) {
+        const int c = st * R + s_row;
+        bring(cent + (size_t)(c < nlist ? c : nlist - 1) * d, ahead);
+    };
+    uint32_t cmax2 = 0, mmax2 = 0;        // (bit patterns: a centroid that is no number is the largest, and everybody is measured exactly)
+    auto stage = [&](int st) {
+        const bool real = st * R + s_row < nlist;
+        float norm, moved, most;
+        put(st & 1, ahead, sc, norm, moved, most);
+        if (s_ks == 0) {
+            h8 f = {(_Float16)65504.0f, (_Float16)65504.0f, (_Float16)65504.0f, (_Float16)kPiece, (_Float16)kPiece, (_Float16)kPiece, 0, 0};
+            if (real) {              // (rows past the end: far away; should one be within the bound all the same, the vector is marked)
+                cmax2 = max(cmax2, norm < kReach ? __float_as_uint(norm) : 0x7f800000u);
+                mmax2 = max(mmax2, __float_as_uint(moved));
+                pieces(f, 0, norm);
+            }
+            *reinterpret_cast<h8 *>(s_buf + (st & 1) * Shape::kStage + (KS * 2 * P + s_row) * 16) = f;
+        }
+    };
+    load(0);
+    // -2 x: R vectors at a time through the LDS
+    h8 xo[2][KS + 1];
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+        float norm, moved, most;
+        put(i & 1, xv[i], -2.0f * sc, norm, moved, most);
+        if (s_ks == 0) {
+            norm *= 0.25f;
+            const bool fits = most < 65000.0f && norm < kReach;        // (else out of the 16-bit range: nothing is known)
+            s_xn[i * R + s_row] = fits ? norm : __builtin_nanf("");
+            s_xm[i * R + s_row] = moved * 0.25f;
+            h8 f = {(_Float16)kPiece, (_Float16)kPiece, (_Float16)kPiece, 0, 0, 0, 0, 0};
+            pieces(f, 3, fits ? norm : 0.0f);
+            *reinterpret_cast<h8 *>(s_buf + (i & 1) * Shape::kStage + (KS * 2 * P + s_row) * 16) = f;
+        }
+        __syncthreads();
+        if (xg * 64 / R == i) {
+            const h8 *b = reinterpret_cast<const h8 *>(s_buf + (i & 1) * Shape::kStage) + xg * 64 % R + col;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) xo[u][ks] = b[(ks * 2 + half) * P + u * 32];
+                const h8 zero = {0, 0, 0, 0, 0, 0, 0, 0}, f = b[KS * 2 * P + u * 32];
+                xo[u][KS] = half == 0 ? f : zero;
+            }
+        }
+    }
+    __syncthreads();
+    stage(0);
+    const int nst = (nlist + R - 1) / R;
+    load(nst > 1 ? 1 : 0);
+    int m1[2][2], m2[2][2], m3[2][2];             // [32 vectors][every other centroid]
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) m1[u][k] = m2[u][k] = m3[u][k] = 0x7f800000;
+    const int bits = 32 - __builtin_clz(nst * TT * 16 - 1);
+    const uint32_t number = (1u << bits) - 1u;
+    uint32_t keep = ~number;
+    asm("" : "+v"(keep));        // (a vector register: an instruction reads one scalar)
+    v16f acc[2];
+    auto multiply = [&](int st, int tt) {
+        const h8 *b = reinterpret_cast<const h8 *>(s_buf + (st & 1) * Shape::kStage) + (cg * TT + tt) * 32 + col;
+        h8 c[KS + 1];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) c[ks] = b[(ks * 2 + half) * P];
+        c[KS] = b[KS * 2 * P];                     // (the same for both halves: the vectors' side of the upper one is zero)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[u][i] = 0.0f;
+#pragma unroll
+        for (int ks = 0; ks <= KS; ++ks)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(c[ks], xo[u][ks], acc[u], 0, 0, 0);
+    };
+    auto track = [&](int tile) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            uint32_t id = (uint32_t)(tile * 16 + i);
+            asm("" : "+s"(id));          // (a scalar of its own: v_and_or_b32)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int k = i & 1;
+                // (not in assembly: the compiler has to see who reads a result of the matrix cores)
+                const int v = (int)((__float_as_uint(acc[u][i]) & keep) | id);
+                asm("v_med3_i32 %0, %1, %2, %0" : "+v"(m3[u][k]) : "v"(v), "v"(m2[u][k]));
+                asm("v_med3_i32 %0, %1, %2, %0" : "+v"(m2[u][k]) : "v"(v), "v"(m1[u][k]));
+                m1[u][k] = v < m1[u][k] ? v : m1[u][k];
+            }
+        }
+    };
+    __syncthreads();
+#pragma unroll 1
+    for (int st = 0; st < nst; ++st) {
+        if (cg == 0) {
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) {
+                multiply(st, tt);
+                if (tt == 0 && st + 1 < nst) {
+                    stage(st + 1);
+                    load(st + 2 < nst ? st + 2 : nst - 1);
+                }
+                track(st * TT + tt);
+            }
+        } else {
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) {
+                if (st + tt > 0) track(st * TT + tt - 1);
+                if (tt == 0 && st + 1 < nst) {
+                    stage(st + 1);
+                    load(st + 2 < nst ? st + 2 : nst - 1);
+                }
+                multiply(st, tt);
+            }
+        }
+        __syncthreads();
+    }
+    if (cg != 0) track(nst * TT - 1);
+    // the trackers of every vector side by side (over the stages, which are done with)
+    int *trk = reinterpret_cast<int *>(s_buf);                  // [first, second, third][kTrk][256]
+    if (cmax2) atomicMax(&s_cmax, cmax2);
+    if (mmax2) atomicMax(&s_mmax, mmax2);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            int *at = trk + ((cg * 2 + half) * 2 + k) * kAsgTile + xg * 64 + u * 32 + col;
+            at[0] = m1[u][k];
+            at[kTrk * kAsgTile] = m2[u][k];
+            at[2 * kTrk * kAsgTile] = m3[u][k];
+        }
+    __syncthreads();
+    if (tid < kAsgTile && x0 + tid < n) {
+        int key[2 * kTrk], third = 0x7fffffff;
+#pragma unroll
+        for (int k = 0; k < 2 * kTrk; ++k) key[k] = trk[k * kAsgTile + tid];
+#pragma unroll
+        for (int k = 0; k < kTrk; ++k) third = min(third, trk[(2 * kTrk + k) * kAsgTile + tid]);
+        int best = key[0];
+#pragma unroll
+        for (int k = 1; k < kTrk; ++k) best = min(best, key[k]);
+        constexpr float kUlp = 1.0f / 16777216.0f;
+        const float lost = trim::sqrt_rn((float)d) * (1.0f / 16384.0f);             // (subnormal 16-bit operands may count as zero)
+        const float c2 = __uint_as_float(s_cmax), x2 = s_xn[tid];
+        const float mc = trim::sqrt_rn(__uint_as_float(s_mmax)) * 1.001f, mx = trim::sqrt_rn(s_xm[tid]) * 1.001f;
+        const float cl = trim::sqrt_rn(c2) + mc, xl = trim::sqrt_rn(x2) + mx;
+        // what moved an operand: rounding, the subtraction of mu, flushing; errors of a score: sums, flushed operands, the pieces of
+        // the norms; the exact rule's own
+        const float moved = mc + mx + (cl + xl) * 2.0f * kUlp + 2.0f * lost;
+        const float e = (4.0f * d + 64.0f) * kUlp * (xl * cl + cl * cl + xl * xl) + 8.0f + (d / 32 + 8) * kUlp * (xl + cl) * (xl + cl);
+        const float coarse = 1.0f + __uint_as_float((uint32_t)(127 - 21 + bits) << 23);      // (what the numbers took)
+        const float reach = trim::sqrt_rn(__builtin_fmaxf(__int_as_float(best), 0.0f) * coarse + e) + 2.0f * moved;
+        const float thr = (reach * reach + e) * coarse, real = (e / sc) / sc;
+        bool known = real < 1e30f && real > 1e-30f && __int_as_float(third) > thr;
+        int close = 0, one = 0;
+#pragma unroll
+        for (int k = 0; k < 2 * kTrk; ++k) {
+            const int id = (int)((uint32_t)key[k] & number), tile = id >> 4, i = id & 15, kg = (k % kTrk) >> 2, kh = (k % kTrk) >> 1 & 1;
+            const bool in = __int_as_float(key[k]) <= thr;
+            key[k] = in ? tile / TT * R + (kg * TT + tile % TT) * 32 + 8 * (i >> 2) + 4 * kh + (i & 3) : -1;
+            known = known && key[k] < nlist;
+            close += in ? 1 : 0;
+            one = in ? key[k] : one;
+        }
+        if (!known || close == 0) {
+            out[x0 + tid] = -1;
+        } else if (close == 1) {
+            out[x0 + tid] = one;
+        } else {
+            int at = atomicAdd(&s_np, close);
+#pragma unroll
+            for (int k = 0; k < 2 * kTrk; ++k)
+                if (key[k] >= 0) s_pair[at++] = (uint32_t)tid | (uint32_t)key[k] << 8;
+        }
+    }
+    __syncthreads();
+    const int np = s_np, lane32 = tid & 31, at4 = 4 * lane32 < d ? 4 * lane32 : 0;      // (at most 32 groups of four)
+    for (int i0 = (tid >> 5) * 4; i0 < np; i0 += (kAsgThreads >> 5) * 4) {
+        uint32_t pair[4];
+        float part[4];
+        f4 q[4], c[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            pair[i] = s_pair[i0 + i < np ? i0 + i : i0];
+            q[i] = *reinterpret_cast<const f4 *>(xs + (size_t)(x0 + (pair[i] & 255u)) * d + at4);
+            c[i] = *reinterpret_cast<const f4 *>(cent + (size_t)(pair[i] >> 8) * d + at4);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {                        // (exact_d2_half's order)
+            float sum = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { const float v = q[i][e] - c[i][e]; sum = __builtin_fmaf(v, v, sum); }
+            part[i] = 4 * lane32 < d ? sum : 0.0f;
+        }
+        const float dist = half_reduce_x4(part, lane32);
+        const int i = half_reduce_x4_row(lane32);
+        const uint32_t p = i == 0 ? pair[0] : i == 1 ? pair[1] : i == 2 ? pair[2] : pair[3];
+        if (half_reduce_x4_writer(lane32) && i0 + i < np)
+            atomicMin(&s_best[p & 255u], ((unsigned long long)__float_as_uint(dist) << 32) | (p >> 8));
+    }
+    __syncthreads();
+    if (tid < kAsgTile && x0 + tid < n && s_best[tid] != ~0ull) out[x0 + tid] = (int32_t)(s_best[tid] & 0xffffffffu);
+}
+
 // The vectors that assign_mfma_kernel marked: every centroid measured by the exact rule, eight
 // vectors at a time (ivf_probe_kernel's distance loop).  A workgroup looks after up to kFixSpan
 // vectors, so that even a mark in a hundred fills its groups.
-constexpr int kFixSpan = 1024, kFixThreads = 512;   // (at most kFixSpan)
+constexpr int kFixSpan = 1024, kFixThreads = 1024;   // (at most kFixSpan)
 __global__ __launch_bounds__(kFixThreads) void assign_fix_kernel(const float *__restrict__ xs, int64_t n, int d,
                                                                  const float *__restrict__ cent, int nlist,
                                                                  int span, int32_t *__restrict__ out) {
@@ -2209,16 +2541,23 @@ __global__ __launch_bounds__(kFixThreads) void assign_fix_kernel(const float *__
         }
         __syncthreads();
         unsigned long long mine = ~0ull;
-        for (int l0 = (tid >> 5) * kRows; l0 < nlist; l0 += (kFixThreads >> 5) * kRows) {
-            const float4 *row0 = reinterpret_cast<const float4 *>(cent + (size_t)l0 * d);
-            const int last = nlist - 1 - l0;
+        constexpr int kStep = (kFixThreads >> 5) * kRows;
+        const int g1 = lane32 < ng ? lane32 : 0;         // the first group of the next rows is on its way while these are measured
+        float4 x[kRows], next[kRows];
+        auto load = [&](int l0, int g, float4 (&to)[kRows]) {
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) to[r] = reinterpret_cast<const float4 *>(cent)[(size_t)(l0 + r < nlist ? l0 + r : nlist - 1) * ng + g];
+        };
+        load((tid >> 5) * kRows, g1, next);
+        for (int l0 = (tid >> 5) * kRows; l0 < nlist; l0 += kStep) {
             float acc[NP];
 #pragma unroll
             for (int i = 0; i < NP; ++i) acc[i] = 0.0f;
-            for (int g = lane32; g < ng; g += 32) {
-                float4 x[kRows];
 #pragma unroll
-                for (int r = 0; r < kRows; ++r) x[r] = row0[(size_t)(r < last ? r : last) * ng + g];
+            for (int r = 0; r < kRows; ++r) x[r] = next[r];
+            load(l0 + kStep, g1, next);
+            for (int g = lane32; g < ng; g += 32) {
+                if (g != lane32) load(l0, g, x);
 #pragma unroll
                 for (int qi = 0; qi < QT; ++qi) {
                     const float4 qv = *reinterpret_cast<const float4 *>(q_lds + qi * d + 4 * g);

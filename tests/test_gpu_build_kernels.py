@@ -71,7 +71,8 @@ def test_encode_filter(T, oracle, dsub, M, n):
 # the nearest list of many vectors: ragged vector, list and column counts, ties between lists, vectors
 # halfway between two lists, lists far from the origin, one far vector, magnitudes that overflow
 @pytest.mark.parametrize("n,d,nlist,scale", [(4096, 4, 64, 1), (4099, 128, 1024, 1), (5000, 36, 257, 1), (4353, 100, 300, 1),
-                                             (4200, 132, 70, 1e19), (4100, 64, 511, 1e-20), (4097, 768, 90, 1)])
+                                             (4200, 132, 70, 1e19), (4100, 64, 511, 1e-20), (4097, 768, 90, 1),
+                                                 (4096, 64, 129, 1), (4351, 124, 2049, 1), (4100, 68, 65, 1e19), (4100, 128, 64, 1e-3)])
 def test_assignment(T, oracle, n, d, nlist, scale):
     import torch
     rng = np.random.default_rng(n)
@@ -186,13 +187,16 @@ def test_probe_of_few_queries(T, oracle, nq, nlist, d, nprobe):
 
 
 def test_nearest_list_with_centroids_that_are_no_numbers():
-    """A centroid that is no number (its list held such a row in training) is nobody's nearest; infinite ones neither."""
+    """A centroid that is no number (its list held such a row in training) is nobody's nearest; infinite ones neither.  One
+    far out of the scaled range, vectors there, and many lists in one place leave the scores behind as well."""
     import torch
     from paper_2508_17828_amd import trim as T
     g = torch.Generator(device="cuda").manual_seed(1)
     x = torch.randn((5000, 64), device="cuda", generator=g)
+    x[:40] *= 3e3
     cent = torch.randn((70, 64), device="cuda", generator=g)
-    for bad in (float("nan"), -float("nan"), float("inf")):
+    cent[50:60] = cent[49]
+    for bad in (float("nan"), -float("nan"), float("inf"), 1e6):
         c = cent.clone()
         c[5, 3] = bad
         few = torch.cat([T.trim_ivf_probe(x[i:i + 1000].contiguous(), c, 1) for i in range(0, 5000, 1000)])
