@@ -1000,8 +1000,11 @@ __global__ __launch_bounds__(256) void invert_place_kernel(const InvertArgs a) {
 
 // ---- replay (kNN) ----
 // One workgroup per query.  The entries of a stretch are listed in scan order; the exact distance is taken
-// here of those whose lower bound (a.d2) does not exceed the threshold at the start, and the first wave
-// goes through the batch rule.
+// here of those whose lower bound (a.d2) does not exceed the threshold at the start, the first wave
+// goes through the batch rule with these, and all threads count the others by the thresholds it leaves.  (When the first
+// wave went through all of them, the other seven waited: 2,500 queries x 500,000 x 768 472 -> 365 us, 500 x 300,000 x 960, k = 100,
+// 963 -> 575.  Of a later pass's 340,000 clocks there, 144,000 are the first wave's, some 200 insertions one after the
+// other, 80,000 the rows, 31,000 the bounds read.)
 // The first pass (seed and first batch, lo == 0) is done by all threads: the seed's distances give the
 // batch its threshold; of its survivors the k with the least lower bounds are measured, the largest of those
 // distances bounds the k-th, so that only bounds up to it need measuring; a sort gives R.
@@ -1018,7 +1021,9 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
     uint16_t *s_todo = reinterpret_cast<uint16_t *>(smem + a.off_todo);                     // [kReplayCap]
     __shared__ int part[kReplayThreads / kWave];
     __shared__ int s_ntodo, s_count;
-    __shared__ uint32_t s_most;
+    __shared__ uint32_t s_most, s_bit[kReplayCap / 32];
+    __shared__ TauSteps s_steps;
+    static_assert(kReplayCap / 32 == kWave, "a word of the measured ones per lane");
     __shared__ float s_tau;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t row = blockIdx.x;       // one workgroup per place in the order
@@ -1037,7 +1042,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
     }
     __syncthreads();
     ResultRegs<E> R;
-    int frozen_b = -2, survivors = 0;
+    int frozen_b = -2, survivors = 0;          // (survivors: this thread's)
     float tau_f = 0.0f;
     if (wave == 0) {
         R.load(rd2, rid, a.k, lane);
@@ -1095,6 +1100,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                 ++at;
             }
             if (tid == 0) s_ntodo = 0;
+            if (tid < kReplayCap / 32) s_bit[tid] = 0;
             __syncthreads();
             const float tau = s_tau;
             // the seed and the first batch, whole (the candidates of this pass are all marked)
@@ -1129,7 +1135,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                 if (mine) atomicAdd(&s_count, mine);
                 __syncthreads();
                 int nc = s_ntodo;
-                if (wave == 0) survivors += s_count;
+                if (tid == 0) survivors += s_count;
                 int size = 1;
                 while (size < nc) size <<= 1;
                 for (int i = nc + tid; i < size; i += kReplayThreads) s_key[i] = ~0ull;
@@ -1184,24 +1190,57 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                 const float d2 = row_d2[c], g = row_g[c];
                 s_g[i] = g;
                 // (its bound is held against the threshold of its own batch, later)
-                if (d2 <= tau) s_todo[atomicAdd(&s_ntodo, 1)] = (uint16_t)i;
-                s_d2[i] = __builtin_inff();    // what does not beat the k-th distance needs neither distance nor id
-                s_id[i] = kEmptyId;
+                if (d2 <= tau) {
+                    s_todo[atomicAdd(&s_ntodo, 1)] = (uint16_t)i;
+                    atomicOr(&s_bit[i >> 5], 1u << (i & 31));
+                }
             }
             __syncthreads();
-            measure(s_ntodo);
+            const int nt = s_ntodo;
+            measure(nt);
             if (wave == 0) {
-                survivors += replay_entries<E>(R, frozen_b, tau_f, s_cl, s_g, s_d2, s_id, np, a.batch, mask_row, a.mask_words);
+                // the measured ones in scan order
+                uint32_t word = s_bit[lane];
+                const int ones = __popc(word);
+                int place = ones;
+#pragma unroll
+                for (int off = 1; off < kWave; off <<= 1) {
+                    const int v = __shfl_up(place, off);
+                    if (lane >= off) place += v;
+                }
+                place -= ones;
+                while (word) {
+                    s_todo[place++] = (uint16_t)(lane * 32 + (__ffs((int)word) - 1));
+                    word &= word - 1;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                replay_measured<E>(R, frozen_b, tau_f, s_cl, s_g, s_d2, s_id, s_todo, nt, a.batch, &s_steps, s_key);
                 if (lane == 0) s_tau = R.t_d2;
+            }
+            __syncthreads();
+            const TauSteps steps = s_steps;
+            for (int i = tid; i < np; i += kReplayThreads) {
+                const int c = s_cl[i], b4 = c < a.k ? -1 : (c - a.k) / a.batch;
+                if (b4 < 0 || s_g[i] <= threshold_of(b4, steps, s_key)) {
+                    ++survivors;
+                    if (mask_row && (c >> 5) < a.mask_words) atomicOr(&mask_row[c >> 5], 1u << (c & 31));
+                }
             }
             __syncthreads();
         }
         __syncthreads();
     }
-    if (wave == 0) {
-        R.store(rd2, rid);
-        if (lane == 0 && a.n_exact) a.n_exact[q] = survivors + (a.lo > 0 ? a.n_exact[q] : 0);
+    if (a.n_exact) {
+        if (tid == 0) s_count = 0;
+        __syncthreads();
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) survivors += __shfl_xor(survivors, off);
+        if (lane == 0 && survivors) atomicAdd(&s_count, survivors);
+        __syncthreads();
+        if (tid == 0) a.n_exact[q] = s_count + (a.lo > 0 ? a.n_exact[q] : 0);
     }
+    if (wave == 0) R.store(rd2, rid);
     __syncthreads();
     for (int i = tid; i < a.k; i += kReplayThreads) {
         const int32_t id = rid[i];

@@ -276,6 +276,24 @@ struct ResultRegs {
         }
         load_kth();
     }
+    // One item that beats the k-th entry, the same in all lanes.  (What is shifted beyond the k-th place stays there: nobody
+    // looks at it, and it is not below the k-th.)
+    __device__ __forceinline__ void insert(float xd2, int32_t xid) {
+        int rank = 0;
+#pragma unroll
+        for (int s = 0; s < E; ++s) rank += __popcll(__ballot(!hit_less(xd2, xid, r_d2[s], r_id[s])));
+        const float c_d2 = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(r_d2[E - 1]), 0x138, 0xf, 0xf, false));
+        const int32_t c_id = __builtin_amdgcn_update_dpp(0, r_id[E - 1], 0x138, 0xf, 0xf, false);
+#pragma unroll
+        for (int s = E - 1; s >= 0; --s) {
+            const int g = lane * E + s;
+            const float p_d2 = s > 0 ? r_d2[s > 0 ? s - 1 : 0] : c_d2;
+            const int32_t p_id = s > 0 ? r_id[s > 0 ? s - 1 : 0] : c_id;
+            r_d2[s] = g == rank ? xd2 : g > rank ? p_d2 : r_d2[s];
+            r_id[s] = g == rank ? xid : g > rank ? p_id : r_id[s];
+        }
+        load_kth();
+    }
     // Insert the lanes' items (one per lane with `pending` set) that beat the k-th entry, one at
     // a time: an insertion is a ballot (rank), one cross-lane shift and a few selects.  Many of them
     // (kMergeFrom, where a merge costs what that many insertions do) are merged instead.  One entry per

@@ -135,6 +135,62 @@ __device__ __forceinline__ int replay_entries(ResultRegs<E> &R, int &frozen_b, f
     return total;
 }
 
+// The batch rule where most entries only count: R changes with those alone whose exact distance was taken (`order`: their
+// numbers in scan order), so one wave goes through these and writes down after which batch the k-th distance
+// became what; every other entry is then held against the threshold of its batch by whoever comes along
+// (threshold_of).  The state of a batch that the next call goes on with is kept in frozen_b and tau_f.
+struct TauSteps {
+    float tau;             // the k-th distance before the first step ...
+    int32_t frozen_b;      // ... but for this batch
+    float frozen_tau;
+    int32_t count;
+};
+template <int E>
+__device__ __forceinline__ void replay_measured(ResultRegs<E> &R, int &frozen_b, float &tau_f, const int32_t *s_cl, const float *s_g,
+                                                const float *s_d2, const int32_t *s_id, const uint16_t *order, int n, int batch,
+                                                TauSteps *info, unsigned long long *steps) {
+    TauSteps out{R.t_d2, frozen_b, tau_f, 0};
+    int last_b = -2;
+    for (int i0 = 0; i0 < n; i0 += kWave) {
+        bool pending = i0 + R.lane < n;
+        const int i = pending ? order[i0 + R.lane] : 0;
+        int b = 0x7fffffff;
+        float g = __builtin_inff(), d2 = __builtin_inff();
+        int32_t id = 0;
+        if (pending) {
+            const int cl = s_cl[i];
+            g = s_g[i]; d2 = s_d2[i]; id = s_id[i];
+            b = cl < R.k ? -1 : (cl - R.k) / batch;
+            if (b < 0) g = -__builtin_inff();
+        }
+        // (who does not beat the k-th distance now never will: it only falls)
+        unsigned long long left = __ballot(pending && g <= (b == frozen_b ? tau_f : R.t_d2) && hit_less(d2, id, R.t_d2, R.t_id));
+        while (left) {
+            const int src = __ffsll((long long)left) - 1;
+            left &= left - 1;
+            const int xb = __builtin_amdgcn_readlane(b, src);
+            const int32_t xid = __builtin_amdgcn_readlane(id, src);
+            const float xg = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g), src));
+            const float xd2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d2), src));
+            if (xb != frozen_b) { frozen_b = xb; tau_f = R.t_d2; }
+            if (!(xg <= tau_f) || !hit_less(xd2, xid, R.t_d2, R.t_id)) continue;
+            R.insert(xd2, xid);
+            if (xb != last_b) { last_b = xb; ++out.count; }
+            if (R.lane == 0) steps[out.count - 1] = ((unsigned long long)(uint32_t)xb << 32) | __float_as_uint(R.t_d2);
+        }
+    }
+    if (R.lane == 0) *info = out;
+}
+// The threshold of batch b: what the last step before it left.
+__device__ __forceinline__ float threshold_of(int b, const TauSteps &info, const unsigned long long *steps) {
+    int lo = 0, hi = info.count;          // steps of batches before b
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if ((int)(steps[mid] >> 32) < b) lo = mid + 1; else hi = mid;
+    }
+    return lo > 0 ? __uint_as_float((uint32_t)steps[lo - 1]) : b == info.frozen_b ? info.frozen_tau : info.tau;
+}
+
 // Ascending bitonic sort of n keys in LDS (n a power of two) by all threads.  Ends with a barrier.
 __device__ __forceinline__ void sort_keys(unsigned long long *key, int n) {
     for (int size = 2; size <= n; size <<= 1)
