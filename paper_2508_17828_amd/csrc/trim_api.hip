@@ -534,12 +534,12 @@ inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 struct FilterLayout {
     int padded, kpad, kpad_rows;
     bool tables;              // distance tables beside (lut_tile_kernel)
-    size_t off_start, off_cnt, off_tasks, off_inv, off_mu, off_max, off_books, off_q16, off_q16r, off_qpar, off_bad, off_lut, end;
+    size_t off_start, off_cnt, off_tasks, off_inv, off_seg, off_mu, off_max, off_books, off_q16, off_q16r, off_qpar, off_bad, off_lut, end;
 };
 size_t table_bytes(const trim_index_view *ix) { return (size_t)ix->M * (is_fs(ix) ? kC4 : kC) * 4; }
 size_t filter_bytes_per_query(const trim_index_view *ix, const trim_candidates *cand) {
     const int padded = filter_padded(ix->d / ix->M, is_fs(ix));
-    return (size_t)(cand ? cand->nprobe : 0) * 8 + ((size_t)ix->M * padded + ix->d + 4 * kFltSlice) * 2 + 8 + 4 +
+    return (size_t)(cand ? cand->nprobe : 0) * 16 + ((size_t)ix->M * padded + ix->d + 4 * kFltSlice) * 2 + 8 + 4 +
            (lut_tiled(ix->d / ix->M, is_fs(ix)) ? table_bytes(ix) : 0);
 }
 FilterLayout filter_layout(const trim_index_view *ix, int64_t rows, int64_t rows_all, const trim_candidates *cand, size_t at) {
@@ -553,6 +553,7 @@ FilterLayout filter_layout(const trim_index_view *ix, int64_t rows, int64_t rows
         L.off_cnt = off;   off += up256((size_t)cand->nlist * 4);
         L.off_tasks = off; off += up256((size_t)(cand->nlist + 1) * 8);
         L.off_inv = off;   off += up256((size_t)rows * cand->nprobe * 8);
+        L.off_seg = off;   off += up256((size_t)rows * cand->nprobe * 8);
     }
     L.off_mu = off;    off += up256((size_t)ix->d * 4);
     L.off_max = off;   off += 256;
@@ -576,6 +577,7 @@ void fill_filter(FilterArgs &f, InvertArgs &v, const trim_index_view *ix, const 
         v.cnt = reinterpret_cast<int32_t *>(ws + L.off_cnt);
         v.start = reinterpret_cast<int32_t *>(ws + L.off_start);
         v.inv = reinterpret_cast<int2 *>(ws + L.off_inv);
+        v.seg = reinterpret_cast<int32_t *>(ws + L.off_seg);
         v.tasks = reinterpret_cast<int32_t *>(ws + L.off_tasks);
         v.row_tasks = v.tasks + a.nlist + 1;
     }
@@ -668,6 +670,7 @@ int knn_in_passes(const trim_index_view *ix, const KnnLayout &L, const SearchArg
     y.nseg = a.nseg; y.max_cand = a.max_cand; y.k = a.k; y.batch = a.batch; y.order = a.order; y.totals = m.totals;
     y.possible = m.possible; y.g = m.g; y.d2 = f.d2; y.words = L.words; y.out_ids = a.out_ids; y.out_d2 = a.out_d2;
     y.n_exact = a.n_exact; y.mask = a.mask; y.mask_words = a.mask_words;
+    m.seg = y.seg = v.seg;
     const int64_t most = a.max_cand;
     for (int64_t s0 = 0; s0 < a.nq; s0 += L.slab) {
         const int64_t ns = a.nq - s0 < L.slab ? a.nq - s0 : L.slab;
@@ -929,6 +932,7 @@ int range_search(const trim_index_view *index, const float *queries, int64_t nq,
         y.probes = a.probes; y.nlist = a.nlist; y.nseg = a.nseg; y.max_cand = a.max_cand; y.order = query_order;
         y.totals = m.totals; y.bits = rmask; y.d2_out = rd2; y.words = L.rmask_words; y.radius2 = a.radius2;
         y.chunk = L.chunk; y.nchunk = L.nsplit; y.counts = counts;
+        m.seg = y.seg = v.seg;
         if (a.lut) z.add(sc + FL.off_bad, (size_t)nq);
         if ((rc = prepare_filter(fa, v, 0, nq, z, st))) return rc;
         if ((rc = prepare_tables(m, index, a, FL, sc, st))) return rc;

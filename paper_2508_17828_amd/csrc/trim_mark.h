@@ -787,8 +787,18 @@ void finish_kernel(const FinishArgs a) {
     }
     const int64_t row = a.by_query ? q : slot;
     const int nseg = a.nseg > 0 ? a.nseg : 1;
+    // the first rows of the table are on their way while the rest is made ready
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    constexpr int kPre = 8;
+    f4 pre[kPre] = {};
+    const f4 *lut = a.lut ? reinterpret_cast<const f4 *>(a.lut + (size_t)(a.lut_by_row ? row : q) * a.M * kByteEntries<FS>) : nullptr;
+    const int n_pre = lut ? a.Mp * (kByteEntries<FS> / 4) : 0;
+    if (lut) {
+#pragma unroll
+        for (int i = 0; i < kPre; ++i) pre[i] = lut[tid + i * T < n_pre ? tid + i * T : 0];
+    }
     for (int t = tid; t < a.d; t += T) q_lds[t] = a.queries[(size_t)q * a.d + t];
-    segment_table(a.list_offsets, a.probes, a.nlist, a.nseg, a.n, a.max_cand, q, segp, segd);
+    segment_table_ready(a.seg, a.nseg, a.n, a.max_cand, row, segp, segd);
     const int total = segp[nseg];
     if (a.lo == 0 && tid == 0) {
         a.totals[row] = total;
@@ -798,10 +808,18 @@ void finish_kernel(const FinishArgs a) {
     if (lo >= hi) return;
     const float tau = a.range ? a.radius2 : a.tau_of ? a.tau_of[(size_t)q * a.tau_stride] : __builtin_inff();
     auto fill = [&](int j0, int nj) {
-        if (a.lut) {
-            const float4 *src = reinterpret_cast<const float4 *>(a.lut + ((size_t)(a.lut_by_row ? row : q) * a.M + j0) * kByteEntries<FS>);
-            float4 *dst = reinterpret_cast<float4 *>(tab);
-            for (int e = tid; e < nj * (kByteEntries<FS> / 4); e += T) dst[e] = src[e];
+        if (lut) {
+            const f4 *src = lut + (size_t)j0 * (kByteEntries<FS> / 4);
+            f4 *dst = reinterpret_cast<f4 *>(tab);
+            const int all = nj * (kByteEntries<FS> / 4);
+            for (int e = tid; e < all; e += kPre * T) {
+                f4 v[kPre];
+#pragma unroll
+                for (int i = 0; i < kPre; ++i) v[i] = src[e + i * T < all ? e + i * T : e];
+#pragma unroll
+                for (int i = 0; i < kPre; ++i)
+                    if (e + i * T < all) dst[e + i * T] = v[i];
+            }
         } else {
             build_table_rows<FS>(tab, q_lds, a.codebooks, a.dsub, j0, nj);
         }
@@ -809,6 +827,14 @@ void finish_kernel(const FinishArgs a) {
     uint32_t *row_bits = a.possible + (size_t)row * a.words;
     float *row_g = a.g + (size_t)row * a.words * 32;
     int n_marked = 0, in_place = -1;            // the phase whose rows are in place
+    if (lut) {
+        f4 *dst = reinterpret_cast<f4 *>(tab);
+#pragma unroll
+        for (int i = 0; i < kPre; ++i)
+            if (tid + i * T < n_pre) dst[tid + i * T] = pre[i];
+        for (int e = tid + kPre * T; e < n_pre; e += T) dst[e] = lut[e];
+        in_place = 0;                            // (barriers follow)
+    }
     // The filter went by the centroids.  A caller's table may hold something else: unless its entries are the
     // centroids' distances bit for bit (lut_tile_kernel), every candidate of the query counts as marked.
     const bool all_marked = a.all != 0 || (a.bad != nullptr && a.bad[q] != 0);
@@ -910,13 +936,26 @@ void finish_kernel(const FinishArgs a) {
 
 // ---- which queries scan a list ----
 
-__global__ void invert_count_kernel(const InvertArgs a) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.nslots * a.nseg) return;
-    const int64_t slot = i / a.nseg, q = a.query(slot);
-    if (q < 0) return;
-    const int32_t l = a.probes[(size_t)q * a.nseg + (i - slot * a.nseg)];
-    if (l >= 0 && l < a.nlist) atomicAdd(&a.cnt[l], 1);
+// kInvPer (query, probe) pairs per workgroup, counted in the LDS first where the lists have room there (kInvLists): with one atomic
+// operation in memory per pair, 160,000 of them on 1024 counters took 35 us, now 7.
+constexpr int kInvPer = 2048, kInvLists = 16384;
+__global__ __launch_bounds__(1024) void invert_count_kernel(const InvertArgs a) {
+    extern __shared__ __align__(16) int32_t s_cnt[];      // [nlist], or nothing
+    const bool lds = a.nlist <= kInvLists;
+    if (lds) {
+        for (int l = threadIdx.x; l < a.nlist; l += blockDim.x) s_cnt[l] = 0;
+        __syncthreads();
+    }
+    for (int64_t i = (int64_t)blockIdx.x * kInvPer + threadIdx.x; i < ((int64_t)blockIdx.x + 1) * kInvPer && i < a.nslots * a.nseg; i += blockDim.x) {
+        const int64_t slot = i / a.nseg, q = a.query(slot);
+        if (q < 0) continue;
+        const int32_t l = a.probes[(size_t)q * a.nseg + (i - slot * a.nseg)];
+        if (l >= 0 && l < a.nlist) atomicAdd(lds ? &s_cnt[l] : &a.cnt[l], 1);
+    }
+    if (!lds) return;
+    __syncthreads();
+    for (int l = threadIdx.x; l < a.nlist; l += blockDim.x)
+        if (s_cnt[l]) atomicAdd(&a.cnt[l], s_cnt[l]);
 }
 // cnt [nlist] -> start [nlist + 1], and cnt becomes the running slots.  Single workgroup.
 __global__ __launch_bounds__(1024) void invert_scan_kernel(const InvertArgs a) {
@@ -964,37 +1003,67 @@ __global__ __launch_bounds__(1024) void invert_scan_kernel(const InvertArgs a) {
         a.row_tasks[nlist] = rcarry;
     }
 }
-// One wave per query.
-__global__ __launch_bounds__(256) void invert_place_kernel(const InvertArgs a) {
-    const int lane = threadIdx.x & 63;
-    const int64_t slot = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (slot >= a.nslots) return;
-    const int64_t q = a.query(slot);
-    if (q < 0) return;
-    const int nseg = a.nseg;
-    int64_t carry = 0;
-    for (int p0 = 0; p0 < nseg; p0 += kWave) {
-        const int p = p0 + lane;
-        int32_t l = p < nseg ? a.probes[(size_t)q * nseg + p] : -1;
-        int64_t len = 0;
-        if (l >= 0 && l < a.nlist) {
-            int64_t s = a.list_offsets[l], e = a.list_offsets[l + 1];
-            s = s < 0 ? 0 : (s > a.n ? a.n : s);
-            e = e < s ? s : (e > a.n ? a.n : e);
-            len = e - s;
-        } else {
-            l = -1;
-        }
-        int64_t incl = len;
+// One wave per query, kInvQueries queries per workgroup.  A workgroup takes its places of every list at once: its pairs are numbered in
+// the LDS, then the lists' counters are moved on by their numbers.
+constexpr int kInvQueries = 32;
+__global__ __launch_bounds__(1024) void invert_place_kernel(const InvertArgs a) {
+    extern __shared__ __align__(16) int32_t s_cnt[];      // [nlist]: pairs so far, then the first place; or nothing
+    const bool lds = a.nlist <= kInvLists;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nseg = a.nseg;
+    constexpr int kWaves = 1024 / kWave;
+    if (lds) {
+        for (int l = threadIdx.x; l < a.nlist; l += 1024) s_cnt[l] = 0;
+        __syncthreads();
+    }
+    // twice over the pairs: numbers and segment tables, then places
+    for (int round = lds ? 0 : 1; round < 2; ++round) {
+        for (int qi = wave; qi < kInvQueries; qi += kWaves) {
+            const int64_t slot = (int64_t)blockIdx.x * kInvQueries + qi;
+            if (slot >= a.nslots) continue;
+            const int64_t q = a.query(slot);
+            if (q < 0) continue;
+            const int64_t row = a.by_query ? q : slot;
+            int64_t carry = 0;
+            for (int p0 = 0; p0 < nseg; p0 += kWave) {
+                const int p = p0 + lane;
+                int32_t l = p < nseg ? a.probes[(size_t)q * nseg + p] : -1;
+                if (round == 0) {
+                    if (l >= 0 && l < a.nlist) atomicAdd(&s_cnt[l], 1);
+                    continue;
+                }
+                int64_t len = 0, first = 0;
+                if (l >= 0 && l < a.nlist) {
+                    int64_t s = a.list_offsets[l], e = a.list_offsets[l + 1];
+                    s = s < 0 ? 0 : (s > a.n ? a.n : s);
+                    e = e < s ? s : (e > a.n ? a.n : e);
+                    len = e - s;
+                    first = s;
+                } else {
+                    l = -1;
+                }
+                int64_t incl = len;
 #pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const int64_t v = __shfl_up((long long)incl, off);
-            if (lane >= off) incl += v;
+                for (int off = 1; off < kWave; off <<= 1) {
+                    const int64_t v = __shfl_up((long long)incl, off);
+                    if (lane >= off) incl += v;
+                }
+                const int64_t c0 = carry + incl - len, c1 = carry + incl;
+                // (beyond 2^31 candidates nothing is scanned: such a list is placed out of reach)
+                if (l >= 0) a.inv[atomicAdd(lds ? &s_cnt[l] : &a.cnt[l], 1)] = make_int2((int)row, c0 < 0x7fffffff ? (int)c0 : 0x7fffffff);
+                if (p < nseg) {
+                    const int64_t before = c0 < a.max_cand ? c0 : a.max_cand;
+                    a.seg[(size_t)row * 2 * nseg + p] = (int)(c1 < a.max_cand ? c1 : a.max_cand);
+                    a.seg[((size_t)row * 2 + 1) * nseg + p] = (int)(first - before);
+                }
+                carry += __shfl((long long)incl, kWave - 1);
+            }
         }
-        const int64_t c0 = carry + incl - len;
-        // (beyond 2^31 candidates nothing is scanned: such a list is placed out of reach)
-        if (l >= 0) a.inv[atomicAdd(&a.cnt[l], 1)] = make_int2((int)(a.by_query ? q : slot), c0 < 0x7fffffff ? (int)c0 : 0x7fffffff);
-        carry += __shfl((long long)incl, kWave - 1);
+        if (round == 0) {
+            __syncthreads();
+            for (int l = threadIdx.x; l < a.nlist; l += 1024)
+                if (s_cnt[l]) s_cnt[l] = atomicAdd(&a.cnt[l], s_cnt[l]);
+            __syncthreads();
+        }
     }
 }
 
@@ -1033,7 +1102,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
     const int lo = a.lo < total ? a.lo : total, hi = a.hi < total ? a.hi : total;
     if (a.lo > 0 && lo >= hi) return;        // nothing of this query in this pass: R stays as it is
     for (int t = tid; t < a.d; t += kReplayThreads) q_lds[t] = a.queries[(size_t)q * a.d + t];
-    segment_table(a.list_offsets, a.probes, a.nlist, a.nseg, a.n, a.max_cand, q, segp, segd);
+    segment_table_ready(a.seg, a.nseg, a.n, a.max_cand, row, segp, segd);
     for (int i = tid; i < kWave * E; i += kReplayThreads) {
         const bool have = a.lo > 0 && i < a.k;
         const int32_t id = have ? a.out_ids[(size_t)q * a.k + i] : -1;
@@ -1267,7 +1336,7 @@ __global__ __launch_bounds__(kReplayThreads) void range_exact_kernel(const Repla
     const int lo = (int)blockIdx.y * a.chunk, hi = lo + a.chunk < total ? lo + a.chunk : total;
     if (lo >= hi) return;
     for (int t = tid; t < a.d; t += kReplayThreads) q_lds[t] = a.queries[(size_t)q * a.d + t];
-    segment_table(a.list_offsets, a.probes, a.nlist, a.nseg, a.n, a.max_cand, q, segp, segd);
+    segment_table_ready(a.seg, a.nseg, a.n, a.max_cand, q, segp, segd);
     uint32_t *bits = a.bits + (size_t)q * a.words;
     float *row_d2 = a.d2_out + (size_t)q * a.words * 32;
     const int half = tid >> 5, lane32 = tid & 31;

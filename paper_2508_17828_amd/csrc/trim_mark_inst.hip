@@ -9,9 +9,10 @@ namespace trim {
 
 int launch_invert(const InvertArgs &a, hipStream_t st) {
     const int64_t total = a.nslots * a.nseg;
-    hipLaunchKernelGGL(invert_count_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, a);
+    const size_t lds = a.nlist <= kInvLists ? (size_t)a.nlist * 4 : 0;
+    hipLaunchKernelGGL(invert_count_kernel, dim3((unsigned)((total + kInvPer - 1) / kInvPer)), dim3(1024), lds, st, a);
     hipLaunchKernelGGL(invert_scan_kernel, dim3(1), dim3(1024), 0, st, a);
-    hipLaunchKernelGGL(invert_place_kernel, dim3((unsigned)((a.nslots + 3) / 4)), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(invert_place_kernel, dim3((unsigned)((a.nslots + kInvQueries - 1) / kInvQueries)), dim3(1024), lds, st, a);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
 }

@@ -25,6 +25,7 @@ struct FinishArgs {
     const uint32_t *bad;      // by query number: the table is not the centroids' (or null)
     const int64_t *list_offsets;
     const int32_t *probes;
+    const int32_t *seg;       // see InvertArgs (null: no lists)
     int32_t nlist, nseg, max_cand;
     int32_t P, Mp;
     float two_gamma;
@@ -78,6 +79,7 @@ struct InvertArgs {
     int32_t *tasks;    // [nlist + 1] prefix of the filter's tiles
     int32_t *row_tasks;   // [nlist + 1] prefix of the measure pass's
     int2 *inv;
+    int32_t *seg;      // [rows][2][nseg]: the queries' segment tables (segment_table), made here once for all passes
     __device__ __forceinline__ int64_t query(int64_t slot) const {
         const int64_t q = order ? order[slot0 + slot] : slot0 + slot;
         return q >= 0 && q < nq ? q : -1;
@@ -145,6 +147,7 @@ struct ReplayArgs {
     int64_t n, nq;
     const int64_t *list_offsets;
     const int32_t *probes;
+    const int32_t *seg;         // see InvertArgs (null: no lists)
     int32_t nlist, nseg, max_cand;
     int32_t k, batch;
     int32_t lo, hi;             // candidates of this pass; lo == 0: R is empty

@@ -53,6 +53,21 @@ __device__ __forceinline__ void segment_table(const int64_t *list_offsets, const
     __syncthreads();
 }
 
+// The same where it has been made already (invert_place_kernel): one look at memory instead of three, one after the other.
+__device__ __forceinline__ void segment_table_ready(const int32_t *seg, int nseg, int64_t n, int max_cand, int64_t row, int *segp, int *segd) {
+    if (seg) {
+        for (int p = threadIdx.x; p < nseg; p += blockDim.x) {
+            segp[p + 1] = seg[(size_t)row * 2 * nseg + p];
+            segd[p] = seg[((size_t)row * 2 + 1) * nseg + p];
+        }
+    } else if (threadIdx.x == 0) {
+        segp[1] = (int)(n < max_cand ? n : max_cand);
+        segd[0] = 0;
+    }
+    if (threadIdx.x == 0) segp[0] = 0;
+    __syncthreads();
+}
+
 __device__ __forceinline__ int segment_position(int c, const int *segp, const int *segd, int nseg) {
     int lo = 0, hi = (nseg > 0 ? nseg : 1) - 1;
     while (lo < hi) {
