@@ -844,8 +844,10 @@ int range_fill(const SearchArgs &a, const RangeLayout &L, unsigned char *ws, int
 
 // Scratch of a range search in passes: totals, then the filter's operands.  0: such a search runs as one kernel.
 size_t range_scratch_bytes(const trim_index_view *ix, int64_t nq, const trim_candidates *cand, FinishPlan *fp) {
-    if (!worth_passes(ix, nq, cand) || !passes_fit(ix, cand, 1, fp) || !counts_fit(ix, nq, cand, cand && cand->max_candidates > 0 ? cand->max_candidates : ix->n)) return 0;
-    return filter_layout(ix, nq, nq, cand, up256((size_t)nq * 4)).end;
+    const int64_t mc = cand && cand->max_candidates > 0 ? cand->max_candidates : ix->n;
+    if (!worth_passes(ix, nq, cand) || !passes_fit(ix, cand, 1, fp) || !counts_fit(ix, nq, cand, mc)) return 0;
+    // (behind the filter's: a bit per query and candidate, who passes for certain)
+    return filter_layout(ix, nq, nq, cand, up256((size_t)nq * 4)).end + up256((size_t)nq * range_layout(nq, mc).rmask_words * 4);
 }
 
 // The range search behind all entry points: `workspace` is the caller's buffer or this
@@ -922,8 +924,11 @@ int range_search(const trim_index_view *index, const float *queries, int64_t nq,
         fa.by_query = v.by_query = 1;
         fa.range = 1; fa.radius2 = a.radius2; fa.lo = 0; fa.hi = a.max_cand;
         fa.totals = reinterpret_cast<int32_t *>(sc); fa.possible = rmask; fa.words = L.rmask_words; fa.d2 = rd2;
+        fa.certain = reinterpret_cast<uint32_t *>(sc + FL.end);
+        z.add(fa.certain, (size_t)nq * L.rmask_words);
         FinishArgs m{};
         fill_finish(m, fpl, a);
+        m.certain = fa.certain;
         m.slot0 = 0; m.nslots = nq; m.by_query = 1; m.range = 1; m.radius2 = a.radius2; m.lo = 0; m.hi = a.max_cand;
         m.totals = reinterpret_cast<int32_t *>(sc); m.possible = rmask; m.words = L.rmask_words; m.g = rd2;
         m.n_exact = a.n_exact; m.mask = a.mask; m.mask_words = a.mask_words;

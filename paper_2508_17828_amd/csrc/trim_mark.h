@@ -39,6 +39,12 @@ namespace trim {
 // moved(q) measured, moved(l) <= (2^-11 + 2^-22) |l'| and what 16-bit subnormals lose; the binary32
 // accumulation of s' errs by at most (4 d + 64) 2^-24 of |q'|^2 + |l'|^2, taken off.
 // A query out of the 16-bit range after scaling has alpha = inf: all its candidates are marked.
+//
+// In a range search the threshold is the same for all queries, and next to all who may pass do (2,000 queries x 250,000 x 1536: all but
+// a per cent).  So the larger root of g(a, b) = tau is kept per row, and who lies below
+// it by more than what rounding moved passes for certain (CERTAIN): no table sums are taken of those (filter 621 -> 677 us, finish 512 -> 187).  tau is taken
+// (nsub + dsub + 64) 2^-23 (a + b)^2 lower for it: the rule's table sums err by (nsub + dsub + 2) 2^-24 of
+// s, i.e. 2 (a + b)^2 times half of that in g, its own chain by 2^-21 (a + b)^2.
 __global__ __launch_bounds__(256) void filter_means_kernel(const FilterArgs a) {
     const int j = blockIdx.x, c = threadIdx.x, wave = c >> 6;
     __shared__ float part[4];
@@ -175,7 +181,7 @@ __device__ __forceinline__ int list_of_task(const int32_t *start, int nlist, int
 // slices ahead in registers (with 256 x 128 tiles, two workgroups per CU and one slice ahead a
 // slice took 2.9 us, most of it waiting).  2,500 queries x 500,000 x 768: 551 -> 496 us; whatever is spilled inside a slice
 // costs more than the tile gains (679 us with 16-byte code loads).  What is left is the LDS: a gather of 16 bytes per landmark and 8 values.
-template <int PAD, bool FS, int AL>
+template <int PAD, bool FS, int AL, bool CERTAIN>
 __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs a) {
     typedef _Float16 h8 __attribute__((ext_vector_type(8)));
     typedef _Float16 h4 __attribute__((ext_vector_type(4)));
@@ -192,8 +198,9 @@ __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs
     constexpr int kQStride = kFltQ + 4;                           // (bank spread)
     __shared__ __align__(16) unsigned char s_book[2][kBookBytes];
     __shared__ __align__(16) h8 s_q[2][4 * kQStride];             // [8 values][query]
-    __shared__ __align__(16) float s_b[kFltRows], s_nl[kFltRows], s_ml[kFltRows];
-    __shared__ float s_al[kFltQ], s_be[kFltQ], s_nq[kFltQ];
+    __shared__ __align__(16) float s_b[kFltRows], s_nl[kFltRows], s_ml[kFltRows], s_hi[CERTAIN ? kFltRows : 4];
+    __shared__ float s_al[kFltQ], s_be[kFltQ], s_nq[kFltQ], s_mq[CERTAIN ? kFltQ : 1];
+    __shared__ uint32_t s_room;
     __shared__ int s_row[kFltQ], s_c0[kFltQ], s_end[kFltQ];
     __shared__ float s_b0[kFltThreads / kWave];
     const float sc = filter_scale(*a.max_bits);
@@ -226,6 +233,10 @@ __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs
         const int nrows = le - r0 < kFltRows ? (int)(le - r0) : kFltRows;
         const int q0 = i0 + qt * kFltQ, nqs = i1 - q0 < kFltQ ? i1 - q0 : kFltQ;
         __syncthreads();     // the previous tile is done with
+        if constexpr (CERTAIN) {
+            if (tid == 0) s_room = 0x7f800000u;
+            __syncthreads();
+        }
         // the queries' rows of the workspace; landmark distances of the rows, their mean (the tangent point)
         int row = 0, c0q = 0, endq = 0;
         if (tid < kFltQ) {
@@ -244,6 +255,26 @@ __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs
             if (tid < nrows) b = a.dlx[r0 + tid];
             const float bs = b * sc;
             s_b[tid] = bs < 1e30f ? bs : __builtin_nanf("");       // (marked: the line would fall to -inf there)
+            if constexpr (CERTAIN) {
+                // the larger root; the smaller one has to lie well below zero (it does while the radius exceeds the landmark
+                // distances by anything), s_room: by how much
+                const float c1 = 1.0f - 0.5f * a.two_gamma, tau = a.radius2, under = b * b * (1.0f - c1 * c1);
+                float hi = -__builtin_inff(), room = __builtin_inff();
+                if (tau > 1e-30f && tau < 1e30f) {
+                    const float end = __builtin_fabsf(c1 * b) + sqrt_rn(__builtin_fmaxf(tau - under, 0.0f)) + __builtin_fabsf(b);
+                    const float root2 = tau - end * end * ((float)(a.nsub + a.dsub + 64) * (1.0f / 8388608.0f)) - under;
+                    if (root2 > 0.0f) {
+                        const float root = sqrt_rn(root2);
+                        hi = (c1 * b + root) * sc * 0.999999f;
+                        room = __builtin_fmaxf((root - c1 * b) * sc * 0.999999f, 0.0f);
+                    }
+                }
+                s_hi[tid] = hi;
+                uint32_t least = tid < nrows && hi > -__builtin_inff() ? __float_as_uint(room) : 0x7f800000u;
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) least = min(least, (uint32_t)__shfl_xor((int)least, off));
+                if (lane == 0) atomicMin(&s_room, least);
+            }
             float sum = b;
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
@@ -301,7 +332,7 @@ __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs
         load_code(4 * CH, cn);
         // (while these are under way) the lines that bound the queries' table sums
         if (tid < kFltQ) {
-            float al = -1.0f, be = 0.0f, nq = 0.0f;
+            float al = -1.0f, be = 0.0f, nq = 0.0f, mq = 0.0f;
             if (c0q < endq) {
                 const int64_t q = a.by_query ? row : a.order ? a.order[a.slot0 + row] : a.slot0 + row;
                 const float tau = a.range ? a.radius2 : a.tau_of ? a.tau_of[(size_t)q * a.tau_stride] : __builtin_inff();
@@ -310,11 +341,13 @@ __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs
                 for (int w = 0; w < kFltThreads / kWave; ++w) b0 += s_b0[w];
                 const AbandonLine line = abandon_line(tau, a.two_gamma, b0 / (float)nrows);
                 nq = a.qpar[2 * (size_t)row];
-                al = line.alpha * sc + a.qpar[2 * (size_t)row + 1];
+                mq = a.qpar[2 * (size_t)row + 1];
+                al = line.alpha * sc + mq;
                 be = line.beta;
                 if (!(al == al)) al = __builtin_inff();
             }
             s_al[tid] = al; s_be[tid] = be; s_nq[tid] = nq;
+            if constexpr (CERTAIN) s_mq[tid] = mq;
             s_c0[tid] = c0q; s_end[tid] = endq;
         }
         v16f acc[2][4];
@@ -405,6 +438,7 @@ __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs
         }
         constexpr float kUlp = 1.0f / 16777216.0f;
         const float keep = 1.0f - (4.0f * a.d + 64.0f) * kUlp;
+        const float over = 2.5f * (4.0f * a.d + 64.0f) * kUlp;       // (of the norms, kept low: what a score may be too low by)
         if (busy) {
 #pragma unroll
             for (int u = 0; u < 2; ++u) {                         // (this wave's rows only: no barrier needed)
@@ -419,7 +453,7 @@ __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                float rb[16], rn[16], rm[16];
+                float rb[16], rn[16], rm[16], rh[16] = {}, widest = 0.0f;      // (rh: the larger root less what moved the landmark)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int r = wave * 64 + u * 32 + 8 * i + 4 * half;
@@ -428,6 +462,12 @@ __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs
                     rb[4 * i] = x.x; rb[4 * i + 1] = x.y; rb[4 * i + 2] = x.z; rb[4 * i + 3] = x.w;
                     rn[4 * i] = y.x; rn[4 * i + 1] = y.y; rn[4 * i + 2] = y.z; rn[4 * i + 3] = y.w;
                     rm[4 * i] = z.x; rm[4 * i + 1] = z.y; rm[4 * i + 2] = z.z; rm[4 * i + 3] = z.w;
+                    if constexpr (CERTAIN) {
+                        const float4 h = *reinterpret_cast<const float4 *>(s_hi + r);
+                        rh[4 * i] = h.x - z.x * 1.00001f; rh[4 * i + 1] = h.y - z.y * 1.00001f;
+                        rh[4 * i + 2] = h.z - z.z * 1.00001f; rh[4 * i + 3] = h.w - z.w * 1.00001f;
+                        widest = __builtin_fmaxf(__builtin_fmaxf(widest, __builtin_fmaxf(z.x, z.y)), __builtin_fmaxf(z.z, z.w));
+                    }
                 }
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
@@ -435,24 +475,40 @@ __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs
                     __builtin_amdgcn_sched_barrier(0);
                     const int qi = v * 32 + col;
                     const float al = s_al[qi], be = s_be[qi], nq = s_nq[qi] * keep;
-                    uint32_t m = 0;
+                    uint32_t m = 0, in = 0;
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
                         const float r = __builtin_fmaf(be, rb[i], al) + rm[i];
                         const float s = acc[u][v][i] + (nq + rn[i]);
                         if (!(s > r * __builtin_fabsf(r))) m |= 1u << (8 * (i >> 2) + (i & 3));
                     }
-                    m <<= 4 * half;
-                    m |= (uint32_t)__shfl_xor((int)m, 32);
+                    if constexpr (CERTAIN) {
+                        const float mq = s_mq[qi] * 1.00001f;
+#pragma unroll
+                        for (int i = 15; i >= 0; --i) {
+                            // (below zero: within.  A NaN counts as 1.)
+                            const float h = rh[i] - mq, base = nq + rn[i];
+                            const float past = __builtin_fmaf(-h, __builtin_fabsf(h), __builtin_fmaf(base, over, acc[u][v][i] + base));
+                            in = __builtin_amdgcn_alignbit(in, __float_as_uint(__builtin_fminf(past, 1.0f)), 31);
+                        }
+                        in = (in & 0xfu) | (in & 0xf0u) << 4 | (in & 0xf00u) << 8 | (in & 0xf000u) << 12;
+                        if (!((widest + mq) * 1.01f < __uint_as_float(s_room))) in = 0;
+                    }
                     // rows of the tile that exist, candidates of this pass
                     const int c0 = s_c0[qi] + wave * 64 + u * 32, end = s_end[qi];
-                    if (c0 + 32 > end) m &= c0 < end ? (1u << (end - c0)) - 1u : 0u;
-                    if (c0 < a.lo) m &= a.lo - c0 < 32 ? ~0u << (a.lo - c0) : 0u;
-                    const int left = nrows - (wave * 64 + u * 32);
-                    if (left < 32) m &= left > 0 ? (1u << left) - 1u : 0u;
-                    const int shf = c0 & 31;
-                    const uint32_t part = half == 0 ? m << shf : (shf ? m >> (32 - shf) : 0u);
-                    if (part) atomicOr(&a.possible[(size_t)s_row[qi] * a.words + (c0 >> 5) + half], part);
+                    auto put = [&](uint32_t bits, uint32_t *to) {
+                        bits <<= 4 * half;
+                        bits |= (uint32_t)__shfl_xor((int)bits, 32);
+                        if (c0 + 32 > end) bits &= c0 < end ? (1u << (end - c0)) - 1u : 0u;
+                        if (c0 < a.lo) bits &= a.lo - c0 < 32 ? ~0u << (a.lo - c0) : 0u;
+                        const int left = nrows - (wave * 64 + u * 32);
+                        if (left < 32) bits &= left > 0 ? (1u << left) - 1u : 0u;
+                        const int shf = c0 & 31;
+                        const uint32_t part = half == 0 ? bits << shf : (shf ? bits >> (32 - shf) : 0u);
+                        if (part) atomicOr(&to[(size_t)s_row[qi] * a.words + (c0 >> 5) + half], part);
+                    };
+                    put(m, a.possible);
+                    if constexpr (CERTAIN) put(in, a.certain);
                 }
             }
         }
@@ -792,8 +848,9 @@ void finish_kernel(const FinishArgs a) {
     constexpr int kPre = 8;
     f4 pre[kPre] = {};
     const f4 *lut = a.lut ? reinterpret_cast<const f4 *>(a.lut + (size_t)(a.lut_by_row ? row : q) * a.M * kByteEntries<FS>) : nullptr;
-    const int n_pre = lut ? a.Mp * (kByteEntries<FS> / 4) : 0;
-    if (lut) {
+    const bool ahead = lut && !a.certain;      // (few table sums: few queries need a table at all)
+    const int n_pre = a.Mp * (kByteEntries<FS> / 4);
+    if (ahead) {
 #pragma unroll
         for (int i = 0; i < kPre; ++i) pre[i] = lut[tid + i * T < n_pre ? tid + i * T : 0];
     }
@@ -827,7 +884,7 @@ void finish_kernel(const FinishArgs a) {
     uint32_t *row_bits = a.possible + (size_t)row * a.words;
     float *row_g = a.g + (size_t)row * a.words * 32;
     int n_marked = 0, in_place = -1;            // the phase whose rows are in place
-    if (lut) {
+    if (ahead) {
         f4 *dst = reinterpret_cast<f4 *>(tab);
 #pragma unroll
         for (int i = 0; i < kPre; ++i)
@@ -838,11 +895,13 @@ void finish_kernel(const FinishArgs a) {
     // The filter went by the centroids.  A caller's table may hold something else: unless its entries are the
     // centroids' distances bit for bit (lut_tile_kernel), every candidate of the query counts as marked.
     const bool all_marked = a.all != 0 || (a.bad != nullptr && a.bad[q] != 0);
+    const uint32_t *row_in = a.certain && !all_marked ? a.certain + (size_t)row * a.words : nullptr;
     for (int p0 = lo & ~31; p0 < hi; p0 += kFinishPiece) {
         const int S = hi - p0 < kFinishPiece ? hi - p0 : kFinishPiece;
         const int nwords = (S + 31) >> 5;
         // (one word per thread and step; T >= 512)
         int all = 0;
+        bool some = false;
         for (int w = tid; w < kFinishPiece / 32; w += T) {
             uint32_t b = 0;
             if (w < nwords) {
@@ -851,13 +910,25 @@ void finish_kernel(const FinishArgs a) {
                 if (p0 + w * 32 + 32 > hi) b &= (1u << (hi - p0 - w * 32)) - 1u;
             }
             bits[w] = b;
+            if (row_in && w < nwords) b &= ~row_in[(p0 >> 5) + w];
+            some = some || b != 0;
+        }
+        if (row_in) {           // (nobody's sum wanted in this piece: no table either)
+            const bool here = __any(some);
+            if (lane == 0) part[wave] = here ? 1 : 0;
+            __syncthreads();
+            some = false;
+            for (int v = 0; v < T / kWave; ++v) some = some || part[v] != 0;
+        } else {
+            some = true;
         }
         __syncthreads();
-        for (int ph = 0; ph < a.P; ++ph) {
+        for (int ph = 0; some && ph < a.P; ++ph) {
             const bool last = ph == a.P - 1;
             if (in_place != ph) { fill(ph * a.Mp, a.Mp); in_place = ph; __syncthreads(); }
             for (int w0 = 0; w0 < nwords; w0 += T) {
-                const uint32_t b = w0 + tid < nwords ? bits[w0 + tid] : 0u;
+                uint32_t b = w0 + tid < nwords ? bits[w0 + tid] : 0u;
+                if (row_in && w0 + tid < nwords) b &= ~row_in[(p0 >> 5) + w0 + tid];      // (these keep their mark)
                 const int cnt = __popc(b);
                 int incl = cnt;
 #pragma unroll

@@ -76,20 +76,22 @@ int launch_filter_operands(const FilterArgs &a, hipStream_t st) {
     return TRIM_OK;
 }
 
-template <int AL>
+template <int AL, bool CERTAIN>
 static void (*filter_of(const FilterArgs &a))(const FilterArgs) {
     switch (a.padded) {
-        case 4: return filter_kernel<4, false, AL>;
-        case 8: return filter_kernel<8, false, AL>;
-        case 16: return filter_kernel<16, false, AL>;
-        case 32: return filter_kernel<32, false, AL>;
+        case 4: return filter_kernel<4, false, AL, CERTAIN>;
+        case 8: return filter_kernel<8, false, AL, CERTAIN>;
+        case 16: return filter_kernel<16, false, AL, CERTAIN>;
+        case 32: return filter_kernel<32, false, AL, CERTAIN>;
         default: return nullptr;
     }
 }
 int launch_filter(const FilterArgs &a, hipStream_t st) {
     const int64_t blocks = 256 * 4;      // (one per CU at a time)
     // (4-bit codes have a multiple of eight bytes)
-    void (*fn)(const FilterArgs) = a.ncent == kC4 ? filter_kernel<2, true, 2> : a.M % 8 == 0 ? filter_of<2>(a) : filter_of<1>(a);
+    void (*fn)(const FilterArgs);
+    if (a.certain) fn = a.ncent == kC4 ? filter_kernel<2, true, 2, true> : a.M % 8 == 0 ? filter_of<2, true>(a) : filter_of<1, true>(a);
+    else fn = a.ncent == kC4 ? filter_kernel<2, true, 2, false> : a.M % 8 == 0 ? filter_of<2, false>(a) : filter_of<1, false>(a);
     if (!fn) return TRIM_UNSUPPORTED_SHAPE;
     hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(kFltThreads), 0, st, a);
     HIP_TRY(hipGetLastError());

@@ -39,6 +39,7 @@ struct FinishArgs {
     // by scan-order number
     int32_t *totals;          // [rows] candidates of the query
     uint32_t *possible;       // [rows][words] marks
+    const uint32_t *certain;  // range: of these, who passes whatever the table sums to in detail (or null)
     float *g;                 // [rows][words * 32] bounds of the marked (and partial sums between table phases)
     int64_t words;
     int32_t *n_scanned, *n_exact;   // n_exact: range only (the marked are the survivors), zeroed by the host
@@ -124,6 +125,7 @@ struct FilterArgs {
     int32_t lo, hi;
     const int32_t *totals;
     uint32_t *possible;
+    uint32_t *certain;         // range: who passes for certain, or null
     int64_t words;
     // prepared operands (work space)
     // measure

@@ -90,3 +90,26 @@ def test_abandon_threshold_implies_the_bound_exceeds_tau(oracle):
                     assert oracle.plb_from_s(s, b, gamma) > tau
                     checked += 1
     assert checked > 40000
+
+
+def test_between_the_lowered_roots_the_rule_lets_everybody_pass(oracle):
+    """filter_kernel's certain candidates: with tau lowered by (M + dsub + 64) 2^-23 (a + b)^2, a table sum whose root lies
+    between the roots of Equation 3 has a binary32 bound of at most tau, also where its M additions all erred one way."""
+    rng = np.random.default_rng(5)
+    f = np.float32
+    for _ in range(4000):
+        M, dsub = int(rng.choice([16, 96, 192, 256])), int(rng.choice([2, 4, 8, 32]))
+        gamma, b, tau = f(rng.choice([0.0, 0.2, 0.7, 1.0, 1.5])), f(rng.uniform(0, 2)), f(10.0 ** rng.uniform(-3, 2))
+        c1 = 1.0 - float(gamma)
+        under = float(b) ** 2 * (1 - c1 * c1)
+        end = abs(c1 * b) + np.sqrt(max(float(tau) - under, 0.0)) + abs(float(b))
+        root2 = float(tau) - end * end * (M + dsub + 64) * 2.0 ** -23 - under
+        if root2 <= 0:
+            continue
+        lo, hi = max(c1 * float(b) - np.sqrt(root2), 0.0), c1 * float(b) + np.sqrt(root2)
+        if hi <= 0:
+            continue
+        for a in (lo, hi, rng.uniform(lo, hi)):
+            for sign in (-1, 1):
+                s = f(a * a * (1 + sign * (M + dsub + 2) * 2.0 ** -24))
+                assert oracle.plb_from_s(s, b, float(gamma)) <= tau, (M, dsub, gamma, b, tau, a, sign)
