@@ -12,6 +12,7 @@
 
 #include "trim_aux.h"
 #include "trim_gamma.h"
+#include "trim_probe.h"
 #include "trim_launch.h"
 
 // Scratch area of trim_search_range_static (see below): device memory inside the library's code
@@ -714,6 +715,57 @@ int knn_in_passes(const trim_index_view *ix, const KnnLayout &L, const SearchArg
 bool probe_in_two(int64_t nq, int d, int nlist, int nprobe) {
     return nprobe <= 64 && nprobe > 1 && nq <= 4096 && (size_t)8 * d * 4 <= kLdsBytes / 2 && nlist >= 64 &&
            (size_t)nq * nlist <= size_t(1) << 26;
+}
+
+// The work space of a probe selection through the matrix cores (trim_probe.h); total = 0: another one.
+struct ProbeLayout {
+    int32_t dpad, lpad;
+    int64_t slab;              // queries at a time: 256 MB of scores and operands
+    size_t off_c, off_q, off_cpar, off_cnm, off_qpar, off_t, total;
+};
+ProbeLayout probe_layout(int64_t nq, int d, int nlist, int nprobe) {
+    ProbeLayout L{};
+    if (!probe_ranked_pays(nq, d, nlist, nprobe) || nprobe > 64 || nlist > 65536 || d % 4 || d > 4096 ||
+        (int64_t)nlist * d > int64_t(1) << 27) return L;
+    L.dpad = (d + 15) / 16 * 16;
+    L.lpad = (nlist + kPrbCols - 1) / kPrbCols * kPrbCols;
+    L.slab = std::min<int64_t>((nq + 31) / 32 * 32, std::max<int64_t>(32, (int64_t(1) << 26) / (L.lpad + L.dpad / 2) / 32 * 32));
+    size_t off = 0;
+    L.off_c = off;    off += up256((size_t)L.lpad * L.dpad * 2);
+    L.off_q = off;    off += up256((size_t)L.slab * L.dpad * 2);
+    L.off_cpar = off; off += up256((size_t)L.lpad * 16);
+    L.off_cnm = off;  off += up256((size_t)L.lpad * 8);
+    L.off_qpar = off; off += up256((size_t)L.slab * 16);
+    L.off_t = off;    off += up256((size_t)L.slab * L.lpad * 4);
+    L.total = off + 256;       // (the caller's memory need not be aligned)
+    return L;
+}
+
+int launch_probe_ranked(const float *queries, int64_t nq, int d, const float *cent, int nlist, int nprobe, int32_t *out,
+                        const ProbeLayout &L, unsigned char *ws, hipStream_t st) {
+    ProbeArgs a{};
+    a.cent = cent; a.d = d; a.nlist = nlist; a.nprobe = nprobe; a.dpad = L.dpad; a.lpad = L.lpad;
+    a.c16 = reinterpret_cast<_Float16 *>(ws + L.off_c);
+    a.q16 = reinterpret_cast<_Float16 *>(ws + L.off_q);
+    a.cpar = reinterpret_cast<float4 *>(ws + L.off_cpar);
+    a.cnm = reinterpret_cast<float2 *>(ws + L.off_cnm);
+    a.qpar = reinterpret_cast<float4 *>(ws + L.off_qpar);
+    a.t = reinterpret_cast<float *>(ws + L.off_t);
+    void (*nearest)(ProbeArgs) = d <= 128 ? probe_nearest_kernel<true> : probe_nearest_kernel<false>;
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(probe_operands_kernel), (size_t)L.dpad * 4));
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(nearest), (size_t)d * 4));
+    for (int64_t q0 = 0; q0 < nq; q0 += L.slab) {
+        a.nq = std::min<int64_t>(L.slab, nq - q0);
+        a.queries = queries + (size_t)q0 * d;
+        a.out = out + (size_t)q0 * nprobe;
+        a.list_groups = q0 == 0 ? L.lpad / kGrRows : 0;
+        const unsigned qblocks = (unsigned)((a.nq + 31) / 32);
+        hipLaunchKernelGGL(probe_operands_kernel, dim3((unsigned)a.list_groups + qblocks * (32 / kGrRows)), dim3(256), (size_t)L.dpad * 4, st, a);
+        hipLaunchKernelGGL(probe_scores_kernel, dim3((unsigned)(L.lpad / kPrbCols), qblocks), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(nearest, dim3((unsigned)a.nq), dim3(kWave), (size_t)d * 4, st, a);
+        HIP_TRY(hipGetLastError());
+    }
+    return TRIM_OK;
 }
 
 // Few queries: bound_kernel and settle_kernel (see trim_few.h).  They pay while the single kernel, a workgroup per
@@ -1461,11 +1513,18 @@ size_t trim_static_scratch_bytes(void) { return kScratchBytes; }
 
 size_t trim_ivf_probe_workspace_bytes(int64_t nq, int32_t d, int32_t nlist, int32_t nprobe) {
     if (nq <= 0 || d <= 0 || nlist <= 0 || nprobe <= 0) return 0;
-    return probe_in_two(nq, d, nlist, nprobe) ? (size_t)nq * nlist * 4 : 0;
+    const ProbeLayout L = probe_layout(nq, d, nlist, nprobe);
+    return L.total > 0 ? L.total : probe_in_two(nq, d, nlist, nprobe) ? (size_t)nq * nlist * 4 : 0;
 }
 
 int trim_ivf_probe_ws(const float *queries, int64_t nq, int32_t d, const float *centroids, int32_t nlist, int32_t nprobe,
                       int32_t *probes_out, void *workspace, size_t workspace_bytes, void *stream) {
+    const ProbeLayout L = nq > 0 && d > 0 && nlist > 0 ? probe_layout(nq, d, nlist, nprobe) : ProbeLayout{};
+    if (L.total > 0 && workspace && workspace_bytes >= L.total && queries && centroids && probes_out && aligned16(centroids) &&
+        aligned16(queries))
+        return launch_probe_ranked(queries, nq, d, centroids, nlist, nprobe, probes_out, L,
+                                   reinterpret_cast<unsigned char *>((reinterpret_cast<uintptr_t>(workspace) + 255) & ~uintptr_t(255)),
+                                   static_cast<hipStream_t>(stream));
     if (nq <= 0 || d <= 0 || nlist <= 0 || nprobe <= 0 || nprobe > nlist || d % 4 || !queries || !centroids || !probes_out ||
         !aligned16(centroids) || !workspace || (reinterpret_cast<uintptr_t>(workspace) & 3u) ||
         !probe_in_two(nq, d, nlist, nprobe) || workspace_bytes < (size_t)nq * nlist * 4)

@@ -227,6 +227,41 @@ def test_probe_of_few_queries_with_values_that_are_no_numbers(nq):
         assert torch.equal(T.trim_ivf_probe(q, cent, nprobe), out)
 
 
+# what the selection through the matrix cores takes: lists and values that leave its tiles unfilled, more queries than fit its
+# scores at a time, as many probes as it takes; ties, more lists in one place than a query's candidates can be (300 of 1501),
+# rows out of the scaled range, and what is no number: the same lists as the kernel that measures every pair
+@pytest.mark.parametrize("nq,nlist,d,nprobe", ((24001, 64, 36, 8), (5900, 257, 132, 32), (1000, 1501, 100, 33), (3001, 512, 128, 64),
+                                              (1000, 1024, 768, 8), (120, 8710, 1540, 50), (70001, 1030, 4, 3)))
+def test_probe_of_many_queries(nq, nlist, d, nprobe):
+    import ctypes as C
+    import torch
+    from paper_2508_17828_amd import trim as T
+    L = T.lib()
+    need = L.trim_ivf_probe_workspace_bytes(nq, d, nlist, nprobe)
+    assert need > 4 * nlist * min(nq, 60000)
+    g = torch.Generator(device="cuda").manual_seed(nlist + d)
+    q, cent = torch.randn((nq, d), device="cuda", generator=g), torch.randn((nlist, d), device="cuda", generator=g) * 0.7 + 3
+    q[: nq // 2] = (2 * q[: nq // 2]).round()              # (whole numbers: ties)
+    cent[: nlist // 2] = (2 * cent[: nlist // 2]).round()
+    cent[nlist // 2] = cent[3]
+    if nlist == 1501:
+        cent[600:1200:2] = q[17]
+    q[5], q[6], q[7], cent[8, 1], cent[9], cent[10] = 1e30, 3e5, 1e-30, 1e7, float("inf"), 1e-40
+    cent[11, 2] = q[nq - 1, 0] = float("nan")
+    stream = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    want = torch.empty((nq, nprobe), dtype=torch.int32, device="cuda")
+    args = (C.c_void_p(q.data_ptr()), nq, d, C.c_void_p(cent.data_ptr()), nlist, nprobe)
+    assert L.trim_ivf_probe(*args, C.c_void_p(want.data_ptr()), stream) == 0
+    ws = torch.empty((need + 4,), dtype=torch.uint8, device="cuda")
+    for shift, size in ((0, need), (4, need), (0, need - 1)):        # (the last: the exact kernels)
+        ws.fill_(0xff)
+        got = torch.full_like(want, -1)
+        assert L.trim_ivf_probe_ws(*args, C.c_void_p(got.data_ptr()), C.c_void_p(ws.data_ptr() + shift), size, stream) == 0
+        # (a query with a NaN is equally far from all: which NaN a sum keeps is nobody's rule)
+        assert torch.equal(got[:-1], want[:-1])
+        assert (got[-1].sort().values.diff() > 0).all()
+
+
 @pytest.mark.parametrize("n", (40, 3000, 200_000))
 @pytest.mark.parametrize("dsub,M", ((4, 8), (5, 8), (6, 8), (8, 8), (7, 4), (12, 4)))
 def test_encode_values_that_are_no_numbers(T, oracle, dsub, M, n):
