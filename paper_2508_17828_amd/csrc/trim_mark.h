@@ -177,10 +177,13 @@ __device__ __forceinline__ int list_of_task(const int32_t *start, int nlist, int
 
 // PAD: values per sub-vector after padding; FS: two 4-bit codes per byte; AL: code words (4 bytes) that may be loaded together.
 // Persistent: workgroups take tiles until there are no more.  512 landmarks x 128 queries per tile, eight waves of
-// 64 x 128.  A slice is 32 values: 16 KB of centroids and 8 KB of queries go through the LDS, two buffers and two
-// slices ahead in registers (with 256 x 128 tiles, two workgroups per CU and one slice ahead a
-// slice took 2.9 us, most of it waiting).  2,500 queries x 500,000 x 768: 551 -> 496 us; whatever is spilled inside a slice
-// costs more than the tile gains (679 us with 16-byte code loads).  What is left is the LDS: a gather of 16 bytes per landmark and 8 values.
+// 64 x 128.  A slice is 32 values: 16 KB of centroids and 8 KB of queries go through the LDS, four buffers: a slice is staged two
+// slices ahead, loaded into registers three ahead, and its first step's operands are read before the barrier that opens it.
+// 2,500 queries x 500,000 x 768: 455 -> 415 us; 2,000 x 250,000 x 1536 (range): 682 -> 588; 500 x 300,000 x 960, no lists: 471 ->
+// 437.  Taken out of copies one at a time, the gathers' bank conflicts cost 8 % of what is left, staging 5 to 8, the norms 4, barriers
+// 10; half the products are 76 us of the last: the products themselves, at the clock they leave, and a tile's ends (18,000
+// of 60,000 clocks at 24 slices: finding it, its queries' lines, marking) are most of it.  Six buffers and a barrier
+// every two slices: 416, 571, 442.
 template <int PAD, bool FS, int AL, bool CERTAIN>
 __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs a) {
     typedef _Float16 h8 __attribute__((ext_vector_type(8)));
@@ -193,11 +196,11 @@ __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs
     constexpr int kBytes = FS ? kSubs / 2 : kSubs;                // code bytes per slice
     constexpr int kBookBytes = kFltSlice * kCent * 2;             // 16 KB (FS: 1 KB)
     constexpr int kBookV = kBookBytes / 16, kBooks = kBookV > kFltThreads ? kBookV / kFltThreads : 1;
-    constexpr int CH = AL > kBytes / 4 ? AL : kBytes / 4;         // code words at hand
-    constexpr int kSpc = 4 * CH / kBytes;                         // slices they last
+    constexpr int CH = kBytes >= 2 ? kBytes / 2 : 1;              // code words of two slices
+    constexpr int kAl = AL < CH ? AL : CH;
     constexpr int kQStride = kFltQ + 4;                           // (bank spread)
-    __shared__ __align__(16) unsigned char s_book[2][kBookBytes];
-    __shared__ __align__(16) h8 s_q[2][4 * kQStride];             // [8 values][query]
+    __shared__ __align__(16) unsigned char s_book[4 * kBookBytes];
+    __shared__ __align__(16) h8 s_q[4 * 4 * kQStride];            // [8 values][query]
     __shared__ __align__(16) float s_b[kFltRows], s_nl[kFltRows], s_ml[kFltRows], s_hi[CERTAIN ? kFltRows : 4];
     __shared__ float s_al[kFltQ], s_be[kFltQ], s_nq[kFltQ], s_mq[CERTAIN ? kFltQ : 1];
     __shared__ uint32_t s_room;
@@ -294,42 +297,38 @@ __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs
             r.qv = q_src[(size_t)sl * (kFltSlice / 8)];
         };
         auto stage = [&](int sl, const Ahead &r) {
-            u4 *bd = reinterpret_cast<u4 *>(s_book[sl & 1]);
+            u4 *bd = reinterpret_cast<u4 *>(s_book + (sl & 3) * kBookBytes);
 #pragma unroll
             for (int i = 0; i < kBooks; ++i)
                 if (kBookV >= kFltThreads || tid < kBookV) bd[i * kFltThreads + tid] = r.bk[i];
-            reinterpret_cast<u4 *>(s_q[sl & 1])[sp * kQStride + sq] = r.qv;
+            reinterpret_cast<u4 *>(s_q + (sl & 3) * (4 * kQStride))[sp * kQStride + sq] = r.qv;
         };
-        // the code words of this lane's two rows: the ones in use and the next
+        // the code words of this lane's two rows, those of two slices at a time
         const uint8_t *codes = a.codes + (size_t)r0 * a.M;
         uint32_t code[2];
-        uint32_t cw[2][CH], cn[2][CH];
+        uint32_t cw[2][CH];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const int r = wave * 64 + u * 32 + col;
             code[u] = (uint32_t)((r < nrows ? r : 0) * a.M);
         }
-        auto load_code = [&](int at, uint32_t (&w)[2][CH]) {       // (past the code: padding subspaces, all centroids zero)
+        auto load_code = [&](int sl, uint32_t (&w)[2][CH]) {       // (past the code: padding subspaces, all centroids zero, any code)
+            const int at = sl * kBytes & ~3;
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll
-                for (int v = 0; v < CH; v += AL) {
-                    if (at + 4 * v < a.M) {
-                        uint32_t x[AL];
-                        load_codes<AL>(x, codes + (code[u] + (uint32_t)(at + 4 * v)));
+                for (int v = 0; v < CH; v += kAl) {
+                    uint32_t x[kAl];
+                    load_codes<kAl>(x, codes + (code[u] + (uint32_t)(at + 4 * v < a.M ? at + 4 * v : 0)));
 #pragma unroll
-                        for (int e = 0; e < AL; ++e) w[u][v + e] = x[e];
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < AL; ++e) w[u][v + e] = 0u;
-                    }
+                    for (int e = 0; e < kAl; ++e) w[u][v + e] = x[e];
                 }
         };
-        Ahead r0a, r1a;
-        load(0, r0a);
+        Ahead ahead, first[2];
+        load(0, first[0]);
         load_code(0, cw);
-        load(1, r1a);
-        load_code(4 * CH, cn);
+        load(1, first[1]);
+        load(2, ahead);
         // (while these are under way) the lines that bound the queries' table sums
         if (tid < kFltQ) {
             float al = -1.0f, be = 0.0f, nq = 0.0f, mq = 0.0f;
@@ -358,83 +357,117 @@ __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs
             for (int v = 0; v < 4; ++v)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) acc[u][v][i] = 0.0f;
-        const bool busy = wave * 64 < nrows;
+        const bool busy = __builtin_amdgcn_readfirstlane(wave) * 64 < nrows;
         const int nv = (nqs + 31) >> 5;               // query tiles of this one in use
-        stage(0, r0a);
-        load(2, r0a);
+        stage(0, first[0]);
+        stage(1, first[1]);
         __syncthreads();
-        auto slice = [&](int sl, Ahead &r) {         // r: slice sl + 1
-            stage(sl + 1, r);
-            load(sl + 3, r);
-            if (busy) {
-                const unsigned char *bb = s_book[sl & 1];
-                const h8 *qq = s_q[sl & 1];
+        // (the number of query tiles is fixed inside: a branch around each leaves its operands' latency open four times a step)
+        auto slices = [&](auto tiles) {
+            constexpr int NV = decltype(tiles)::value;
+            struct Operands { h8 lm[2], qf[NV]; };
+            auto operands = [&](int sl, auto odd, auto step, const uint32_t (&w)[2][CH], Operands &o) {
+                constexpr int j = decltype(odd)::value, ks = decltype(step)::value;
+                const unsigned char *bb = s_book + (sl & 3) * kBookBytes;
+                const h8 *qq = s_q + (sl & 3) * (4 * kQStride) + (ks * 2 + half) * kQStride + col;
 #pragma unroll
-                for (int ks = 0; ks < 2; ++ks) {
-                    __builtin_amdgcn_sched_barrier(0);     // (registers: one step's operands at a time)
-                    h8 lm[2], qf[4];
+                for (int u = 0; u < 2; ++u) {
+                    if constexpr (FS) {                       // four sub-vectors of two values
+                        const uint32_t word = w[u][2 * j + ks] >> (16 * half);
+                        h2 p[4];
 #pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        qf[v] = qq[(ks * 2 + half) * kQStride + v * 32 + col];
-#pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        if constexpr (FS) {                       // four sub-vectors of two values
-                            const uint32_t word = cw[u][ks] >> (16 * half);
-                            h2 p[4];
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                p[e] = *reinterpret_cast<const h2 *>(bb + (((ks * 8 + half * 4 + e) * kCent + ((word >> (4 * e)) & 15u)) << 2));
-                            lm[u] = h8{p[0][0], p[0][1], p[1][0], p[1][1], p[2][0], p[2][1], p[3][0], p[3][1]};
-                        } else if constexpr (PAD == 4) {          // two
-                            const uint32_t word = cw[u][ks] >> (16 * half);
-                            const h4 p0 = *reinterpret_cast<const h4 *>(bb + (((ks * 4 + half * 2) * kCent + (word & 255u)) << 3));
-                            const h4 p1 = *reinterpret_cast<const h4 *>(bb + (((ks * 4 + half * 2 + 1) * kCent + ((word >> 8) & 255u)) << 3));
-                            lm[u] = h8{p0[0], p0[1], p0[2], p0[3], p1[0], p1[1], p1[2], p1[3]};
-                        } else {                                  // one, or a part of one
-                            constexpr int kParts = PAD >= 8 ? PAD / 8 : 1;       // operands per sub-vector
-                            const int op = ks * 2 + half, sub = op / kParts, part = op % kParts;
-                            const uint32_t c = (cw[u][0] >> (8 * sub)) & 255u;
-                            lm[u] = *reinterpret_cast<const h8 *>(bb + (sub * kCent + c) * (PAD * 2) + part * 16);
-                        }
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const h2 p = {lm[u][2 * e], lm[u][2 * e + 1]};
-                            nl[u] = __builtin_amdgcn_fdot2(p, p, nl[u], false);
-                        }
+                        for (int e = 0; e < 4; ++e)
+                            p[e] = *reinterpret_cast<const h2 *>(bb + (((ks * 8 + half * 4 + e) * kCent + ((word >> (4 * e)) & 15u)) << 2));
+                        o.lm[u] = h8{p[0][0], p[0][1], p[1][0], p[1][1], p[2][0], p[2][1], p[3][0], p[3][1]};
+                    } else if constexpr (PAD == 4) {          // two
+                        const uint32_t word = w[u][2 * j + ks] >> (16 * half);
+                        const h4 p0 = *reinterpret_cast<const h4 *>(bb + (((ks * 4 + half * 2) * kCent + (word & 255u)) << 3));
+                        const h4 p1 = *reinterpret_cast<const h4 *>(bb + (((ks * 4 + half * 2 + 1) * kCent + ((word >> 8) & 255u)) << 3));
+                        o.lm[u] = h8{p0[0], p0[1], p0[2], p0[3], p1[0], p1[1], p1[2], p1[3]};
+                    } else {                                  // one, or a part of one
+                        constexpr int kParts = PAD >= 8 ? PAD / 8 : 1;       // operands per sub-vector
+                        const int op = ks * 2 + half, sub = op / kParts, part = op % kParts;
+                        const int at = PAD == 8 ? 0 : PAD == 16 ? 16 * j : 8 * (sl & 3);
+                        const uint32_t c = (w[u][PAD == 8 ? j : 0] >> (8 * sub + at)) & 255u;
+                        o.lm[u] = *reinterpret_cast<const h8 *>(bb + (sub * kCent + c) * (PAD * 2) + part * 16);
                     }
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        if (v < nv) {
-#pragma unroll
-                            for (int u = 0; u < 2; ++u) acc[u][v] = __builtin_amdgcn_mfma_f32_32x32x16_f16(lm[u], qf[v], acc[u][v], 0, 0, 0);
-                        }
                 }
-            }
-            // the next slice's code bytes to the front
-            if ((sl + 1) % kSpc == 0) {
+#pragma unroll
+                for (int v = 0; v < NV; ++v) o.qf[v] = qq[v * 32];
+            };
+            auto multiply = [&](const Operands &o) {
+#pragma unroll
+                for (int v = 0; v < NV; ++v)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) acc[u][v] = __builtin_amdgcn_mfma_f32_32x32x16_f16(o.lm[u], o.qf[v], acc[u][v], 0, 0, 0);
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const h2 p = {o.lm[u][2 * e], o.lm[u][2 * e + 1]};
+                        nl[u] = __builtin_amdgcn_fdot2(p, p, nl[u], false);
+                    }
+            };
+            // per slice: its second step's operands under way, the first step's products, slice sl + 2 to the LDS, the next slice's
+            // first operands under way, the second step's products
+            auto slice = [&](int sl, auto odd, const uint32_t (&w)[2][CH], const uint32_t (&next)[2][CH], Operands &o) {
+                constexpr int j = decltype(odd)::value;
+                Operands p;
+                __builtin_amdgcn_sched_barrier(0);
+                operands(sl, odd, std::integral_constant<int, 1>{}, w, p);
+                multiply(o);
+                stage(sl + 2, ahead);
+                load(sl + 3, ahead);
+                if constexpr (NV >= 3 && !FS && PAD >= 8) {
+#pragma unroll
+                    for (int i = 0; i < 2 + NV; ++i) {
+                        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    }
+                    __builtin_amdgcn_sched_group_barrier(0x8, NV - 2, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x200, kBooks + 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x20, kBooks + 1, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                operands(sl + 1, std::integral_constant<int, 1 - j>{}, std::integral_constant<int, 0>{}, next, o);
+                multiply(p);
+                if constexpr (NV >= 3 && !FS && PAD >= 8) {
+#pragma unroll
+                    for (int i = 0; i < 2 + NV; ++i) {
+                        __builtin_amdgcn_sched_group_barrier(0x8, 1, 1);
+                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 1);
+                    }
+                    __builtin_amdgcn_sched_group_barrier(0x8, NV - 2, 1);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                __syncthreads();
+            };
+            Operands o;
+            operands(0, std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{}, cw, o);
+#pragma unroll 1
+            for (int sl = 0; sl < nslice; sl += 2) {      // (an even number)
+                uint32_t cn[2][CH];
+                load_code(sl + 2, cn);
+                slice(sl, std::integral_constant<int, 0>{}, cw, cw, o);
+                slice(sl + 1, std::integral_constant<int, 1>{}, cw, cn, o);
 #pragma unroll
                 for (int u = 0; u < 2; ++u)
 #pragma unroll
                     for (int v = 0; v < CH; ++v) cw[u][v] = cn[u][v];
-                load_code((sl + 1 + kSpc) / kSpc * (4 * CH), cn);
-            } else {
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int v = 0; v < CH; ++v) {
-                        if constexpr (kBytes >= 4) {
-                            cw[u][v] = v + kBytes / 4 < CH ? cw[u][v + kBytes / 4 < CH ? v + kBytes / 4 : 0] : 0u;
-                        } else {
-                            cw[u][v] = (cw[u][v] >> (8 * kBytes)) | (v + 1 < CH ? cw[u][v + 1 < CH ? v + 1 : 0] << (32 - 8 * kBytes) : 0u);
-                        }
-                    }
             }
-            __syncthreads();
         };
+        if (!busy) {
 #pragma unroll 1
-        for (int sl = 0; sl < nslice; sl += 2) {      // (an even number)
-            slice(sl, r1a);
-            slice(sl + 1, r0a);
+            for (int sl = 0; sl < nslice; ++sl) {
+                stage(sl + 2, ahead);
+                load(sl + 3, ahead);
+                __syncthreads();
+            }
+        } else switch (nv) {
+            case 1: slices(std::integral_constant<int, 1>{}); break;
+            case 2: slices(std::integral_constant<int, 2>{}); break;
+            case 3: slices(std::integral_constant<int, 3>{}); break;
+            default: slices(std::integral_constant<int, 4>{}); break;
         }
         constexpr float kUlp = 1.0f / 16777216.0f;
         const float keep = 1.0f - (4.0f * a.d + 64.0f) * kUlp;

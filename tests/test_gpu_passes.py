@@ -112,6 +112,14 @@ def test_passes_equal_the_single_kernel(T, case):
         np.testing.assert_array_equal(got["ids"].cpu().numpy(), want["ids"].cpu().numpy())
 
 
+# a last tile of one to four blocks of 32 queries (the filter has a loop for each), rows that leave waves of the last row tile idle,
+# an uneven number of code words, sub-vectors of every padded length
+@pytest.mark.parametrize("nq", (288, 320, 350, 384))
+@pytest.mark.parametrize("d,M,bits,nlist", ((544, 68, 8, 0), (512, 128, 8, 3), (528, 44, 8, 0), (640, 20, 8, 0), (640, 320, 4, 3)))
+def test_tiles_of_one_to_four_blocks_of_queries(T, nq, d, M, bits, nlist):
+    test_passes_equal_the_single_kernel(T, (2300, d, M, bits, nlist, nq, nlist, 10, 300, 0.3, 0.4, 0.0))
+
+
 # few queries (bounds by many workgroups, one to settle): one query; first batches measured beside the bounds and not
 # (the three largest); codes of every width; table phases; more results than candidates
 FEW = [
