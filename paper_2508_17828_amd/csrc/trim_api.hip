@@ -725,7 +725,7 @@ struct ProbeLayout {
 };
 ProbeLayout probe_layout(int64_t nq, int d, int nlist, int nprobe) {
     ProbeLayout L{};
-    if (!probe_ranked_pays(nq, d, nlist, nprobe) || nprobe > 64 || nlist > 65536 || d % 4 || d > 4096 ||
+    if (!probe_ranked_pays(nq, d, nlist, nprobe) || nprobe < 2 || nprobe > 64 || nlist > 65536 || d % 4 || d > 4096 ||
         (int64_t)nlist * d > int64_t(1) << 27) return L;
     L.dpad = (d + 15) / 16 * 16;
     L.lpad = (nlist + kPrbCols - 1) / kPrbCols * kPrbCols;

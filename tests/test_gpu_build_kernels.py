@@ -239,6 +239,7 @@ def test_probe_of_many_queries(nq, nlist, d, nprobe):
     L = T.lib()
     need = L.trim_ivf_probe_workspace_bytes(nq, d, nlist, nprobe)
     assert need > 4 * nlist * min(nq, 60000)
+    assert L.trim_ivf_probe_workspace_bytes(nq, d, nlist, 1) == 0          # (one list: the kernels that assign vectors)
     g = torch.Generator(device="cuda").manual_seed(nlist + d)
     q, cent = torch.randn((nq, d), device="cuda", generator=g), torch.randn((nlist, d), device="cuda", generator=g) * 0.7 + 3
     q[: nq // 2] = (2 * q[: nq // 2]).round()              # (whole numbers: ties)
