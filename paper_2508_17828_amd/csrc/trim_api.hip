@@ -453,19 +453,22 @@ int scratch_for_current_device(void **out) {
 // ---- the scan in separate passes (trim_mark.h) ----
 
 // Table phases, block size and LDS layout of the finish pass: two workgroups of 512 threads per CU
-// where they fit, else one of 1024.
+// where they fit, else one of 1024.  few: most candidates' sums are not wanted (range searches), and a workgroup spends
+// its time on the table and on getting ready; two per CU then pay for up to four phases (2,000 queries, 192 code bytes, 36 sums
+// each: 188 -> 159 us; with every sum wanted, 120 code bytes: 555 -> 691).
 struct FinishPlan {
     int threads, P, Mp, vec;
     size_t lds;
     uint32_t off_q, off_segp, off_segd, off_bits, off_ring;
 };
-bool make_finish_plan(int d, int M, bool fs, int nseg, FinishPlan *pl) {
+bool make_finish_plan(int d, int M, bool fs, int nseg, bool few, FinishPlan *pl) {
     const int row_bytes = fs ? (int)kByteRow<true> : (int)kByteRow<false>;
     const int ns = nseg > 0 ? nseg : 1;
-    for (int P = 1; P <= M / 4; ++P) {
+    for (int i = few ? 0 : 4; i <= 3 + M / 4; ++i) {
+        const int P = i < 4 ? i + 1 : i - 3;         // (the first four: two workgroups per CU or not at all)
         if (M % P || (M / P) % 4) continue;
         const int Mp = M / P;
-        for (int threads = 512; threads <= 1024; threads *= 2) {
+        for (int threads = 512; threads <= (i < 4 ? 512 : 1024); threads *= 2) {
             size_t off = (size_t)Mp * row_bytes;
             pl->off_q = (uint32_t)off;    off += up16((size_t)d * 4);
             pl->off_segp = (uint32_t)off; off += up16((size_t)(ns + 1) * 4);
@@ -523,9 +526,9 @@ bool counts_fit(const trim_index_view *ix, int64_t rows, const trim_candidates *
 }
 
 // What else a search in passes needs: room in the LDS for every one of them, and the centroids.
-bool passes_fit(const trim_index_view *ix, const trim_candidates *cand, int k, FinishPlan *fp) {
+bool passes_fit(const trim_index_view *ix, const trim_candidates *cand, int k, bool few, FinishPlan *fp) {
     const int nseg = cand ? cand->nprobe : 0;
-    return ix->codebooks && make_finish_plan(ix->d, code_bytes(ix), is_fs(ix), nseg, fp) &&
+    return ix->codebooks && make_finish_plan(ix->d, code_bytes(ix), is_fs(ix), nseg, few, fp) &&
            replay_lds(ix->d, k, nseg) <= kLdsBytes && measure_lds(ix->d, 2) <= kLdsBytes;
 }
 
@@ -635,7 +638,7 @@ KnnLayout knn_layout(const trim_index_view *ix, int64_t nq, const trim_candidate
     KnnLayout L{};
     const int64_t hard = (int64_t(1) << 31) - 1 - TRIM_MAX_BATCH - 2048;
     int64_t mc = cand ? cand->max_candidates : ix->n;
-    if (mc <= 0 || mc > ix->n + (int64_t)(cand ? cand->nprobe : 0) * ix->n || !worth_passes(ix, nq, cand) || !passes_fit(ix, cand, k, fp)) return L;
+    if (mc <= 0 || mc > ix->n + (int64_t)(cand ? cand->nprobe : 0) * ix->n || !worth_passes(ix, nq, cand) || !passes_fit(ix, cand, k, false, fp)) return L;
     if (mc > hard) mc = hard;
     L.words = (mc + 31) / 32 + 1;
     const size_t per = (size_t)L.words * (4 + 32 * 8) + 4 + filter_bytes_per_query(ix, cand);
@@ -897,7 +900,7 @@ int range_fill(const SearchArgs &a, const RangeLayout &L, unsigned char *ws, int
 // Scratch of a range search in passes: totals, then the filter's operands.  0: such a search runs as one kernel.
 size_t range_scratch_bytes(const trim_index_view *ix, int64_t nq, const trim_candidates *cand, FinishPlan *fp) {
     const int64_t mc = cand && cand->max_candidates > 0 ? cand->max_candidates : ix->n;
-    if (!worth_passes(ix, nq, cand) || !passes_fit(ix, cand, 1, fp) || !counts_fit(ix, nq, cand, mc)) return 0;
+    if (!worth_passes(ix, nq, cand) || !passes_fit(ix, cand, 1, true, fp) || !counts_fit(ix, nq, cand, mc)) return 0;
     // (behind the filter's: a bit per query and candidate, who passes for certain)
     return filter_layout(ix, nq, nq, cand, up256((size_t)nq * 4)).end + up256((size_t)nq * range_layout(nq, mc).rmask_words * 4);
 }
