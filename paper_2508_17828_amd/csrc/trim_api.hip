@@ -1542,10 +1542,7 @@ int trim_ivf_probe_ws(const float *queries, int64_t nq, int32_t d, const float *
     hipLaunchKernelGGL(fn, dim3((unsigned)((nlist + rows - 1) / rows), (unsigned)((nq + qt - 1) / qt)), dim3(kProbeThreads), lds, st,
                        queries, nq, d, centroids, nlist, dist);
     HIP_TRY(hipGetLastError());
-    if (nprobe <= 32)
-        hipLaunchKernelGGL(probe_select_kernel<1>, dim3((unsigned)nq), dim3(kWave), 0, st, dist, nlist, nprobe, probes_out);
-    else
-        hipLaunchKernelGGL(probe_select_kernel<2>, dim3((unsigned)nq), dim3(kWave), 0, st, dist, nlist, nprobe, probes_out);
+    hipLaunchKernelGGL(probe_select_kernel, dim3((unsigned)nq), dim3(kWave), 0, st, dist, nlist, nprobe, probes_out);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
 }

@@ -22,14 +22,15 @@
 
 namespace trim {
 
-// From where on (both sides measured, us, exact kernels / these; 8 to 64 probes): 10000 x 1024 lists of 128 values 128 / 70, of 768
-// 453 / 102..180, of 1536 850 / 172..350; 3000 x 512 of 128 29 / 25, 1000 x 2048 of 128 35 / 31, 1000 x 1024 of 768 56 / 37..60.  With
-// less work the three launches and a wave's chain of candidates cost more: 1000 x 1024 of 128 22 / 24, 1000 x 512 of 768
-// 33 / 39; and the fewer queries, the longer that chain shows: 260 x 2048 of 1536 88 / 59..110, 260 x 4096 of 1536 159 / 74..122.
-// With more than an eighth of the lists probed most rows are measured anyway (10000 x 150 of 1536, 64 probes: 165 / 231).
+// From where on (both sides measured, us, two exact kernels (10000 queries: one) / these; 8, 32, 64 probes): 3000 x 1024 lists of 128
+// values 38 / 30, 34, 38, 10000 x 1024 128 / 70, 1000 x 4096 53 / 47, 50, 54; 10000 x 1024 of 768 453 / 102, 136, 179, of 1536 850 /
+// 172, 250, 350.  With less work the three launches and a wave's chain of candidates cost more: 1500 x 1024 of 128 24 / 24, 26, 31,
+// 1000 x 1024 of 768 51 / 37, 46, 61; and the fewer queries, the longer that chain shows: 300 x 4096 of 1536 180 / 73, 88, 123,
+// but 260 x 2048 88 / 59, 79, 110.  With more than an eighth of the lists probed most rows are measured anyway (10000 x 150 of
+// 1536, 64 probes: 165 / 231).
 inline bool probe_ranked_pays(int64_t nq, int d, int nlist, int nprobe) {
     const double pairs = (double)nq * nlist, values = pairs * d;
-    return nprobe <= nlist / 8 && ((nq >= 1000 && (pairs >= 1.5e6 || values >= 7.5e8)) || (nq >= 100 && values >= 1.6e9));
+    return nprobe <= nlist / 8 && ((nq >= 1000 && (pairs >= 2.5e6 || values >= 1e9)) || (nq >= 100 && values >= 1.6e9));
 }
 
 constexpr int kPrbList = 256, kPrbCols = 256, kPrbRows = 32;

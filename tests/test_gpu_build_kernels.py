@@ -227,11 +227,26 @@ def test_probe_of_few_queries_with_values_that_are_no_numbers(nq):
         assert torch.equal(T.trim_ivf_probe(q, cent, nprobe), out)
 
 
+# the lists a wave keeps in its registers and one more; more equally near lists than are ranked together
+@pytest.mark.parametrize("nlist", (1024, 1025, 2049))
+@pytest.mark.parametrize("same", (0, 256, 257, 700))
+@pytest.mark.parametrize("nprobe", (2, 31, 64))
+def test_probe_selection_of_equally_near_lists(T, oracle, nlist, same, nprobe):
+    import torch
+    rng = np.random.default_rng(nlist + same)
+    cent = rng.integers(-9, 10, (nlist, 8)).astype(np.float32)
+    q = rng.integers(-9, 10, (3, 8)).astype(np.float32)
+    cent[rng.permutation(nlist)[:same]] = q[1] + 1
+    assert T.lib().trim_ivf_probe_workspace_bytes(3, 8, nlist, nprobe) == 3 * nlist * 4
+    got = T.trim_ivf_probe(torch.from_numpy(q).cuda(), torch.from_numpy(cent).cuda(), nprobe).cpu().numpy()
+    np.testing.assert_array_equal(got, oracle.ivf_probe(q, cent, nprobe))
+
+
 # what the selection through the matrix cores takes: lists and values that leave its tiles unfilled, more queries than fit its
 # scores at a time, as many probes as it takes; ties, more lists in one place than a query's candidates can be (300 of 1501),
 # rows out of the scaled range, and what is no number: the same lists as the kernel that measures every pair
-@pytest.mark.parametrize("nq,nlist,d,nprobe", ((24001, 64, 36, 8), (5900, 257, 132, 32), (1000, 1501, 100, 33), (3001, 512, 128, 64),
-                                              (1000, 1024, 768, 8), (120, 8710, 1540, 50), (70001, 1030, 4, 3)))
+@pytest.mark.parametrize("nq,nlist,d,nprobe", ((40001, 64, 36, 8), (9800, 257, 132, 32), (1700, 1501, 100, 33), (5001, 512, 128, 64),
+                                              (1000, 1024, 1000, 8), (120, 8710, 1540, 50), (70001, 1030, 4, 3)))
 def test_probe_of_many_queries(nq, nlist, d, nprobe):
     import ctypes as C
     import torch
