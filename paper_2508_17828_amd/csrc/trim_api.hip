@@ -792,7 +792,7 @@ constexpr double kFewLookups = 500000.0, kFewShortRows = 1.05e8, kFewNoLists = 2
 constexpr size_t kFewBytes = size_t(1) << 30;
 struct FewLayout {
     int64_t stride;           // bounds per query (0: not this way)
-    size_t off_g, off_d2, total;      // totals at 0
+    size_t off_g, off_least, off_d2, total;      // totals at 0
     bool measure_first;
 };
 FewLayout few_layout(const trim_index_view *ix, int64_t nq, const trim_candidates *cand, int k, int batch) {
@@ -810,7 +810,8 @@ FewLayout few_layout(const trim_index_view *ix, int64_t nq, const trim_candidate
     // The seed and the first batch measured beside the bounds, survivors or not, while that is little to read.
     L.measure_first = (size_t)nq * (k + batch) * ix->d * 4 <= (size_t(128) << 20);
     L.off_g = up256((size_t)nq * 4);
-    L.off_d2 = L.off_g + up256(g_bytes);
+    L.off_least = L.off_g + up256(g_bytes);
+    L.off_d2 = L.off_least + up256((size_t)nq * ((stride + 63) / 64) * 4);
     L.total = L.off_d2 + (L.measure_first ? up256((size_t)nq * (k + batch) * 4) : 0);
     return L;
 }
@@ -824,6 +825,7 @@ int knn_few(const trim_index_view *ix, const FewLayout &L, const SearchArgs &a, 
     f.totals = reinterpret_cast<int32_t *>(ws);
     f.g = reinterpret_cast<float *>(ws + L.off_g);
     f.stride = L.stride;
+    f.least = reinterpret_cast<float *>(ws + L.off_least);
     f.d2 = L.measure_first ? reinterpret_cast<float *>(ws + L.off_d2) : nullptr;
     f.out_ids = a.out_ids; f.out_d2 = a.out_d2; f.n_scanned = a.n_scanned; f.n_exact = a.n_exact;
     f.mask = a.mask; f.mask_words = a.mask_words;

@@ -19,7 +19,9 @@
 namespace trim {
 
 template <int VEC, bool FS>
-__global__ __launch_bounds__(kBoundThreads) void bound_kernel(const FewArgs a) {
+// (six waves per SIMD: with 89 registers in place of 80 two workgroups fit a CU, and a grid of little more than two per CU takes
+// half as long again)
+__global__ __launch_bounds__(kBoundThreads) __attribute__((amdgpu_waves_per_eu(6))) void bound_kernel(const FewArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     float *tab = reinterpret_cast<float *>(smem);
     float *q_lds = reinterpret_cast<float *>(smem + a.off_q);
@@ -67,7 +69,10 @@ __global__ __launch_bounds__(kBoundThreads) void bound_kernel(const FewArgs a) {
         }
         __syncthreads();
         const bool last = ph == a.P - 1;
-        for (int c = c0 + tid; c < c1; c += kBoundThreads) {
+        // (a wave has 64 candidates that begin at a multiple of 64)
+        for (int cw = c0 + (tid & ~63); cw < c1; cw += kBoundThreads) {
+            const bool on = cw + (tid & 63) < c1;
+            const int c = on ? cw + (tid & 63) : c1 - 1;
             const int pos = segment_position(c, segp, segd, a.nseg);
             const uint8_t *code = a.codes + (size_t)pos * a.M + ph * a.Mp;
             const float b = last ? a.dlx[pos] : 0.0f;
@@ -83,7 +88,18 @@ __global__ __launch_bounds__(kBoundThreads) void bound_kernel(const FewArgs a) {
                     if (j + i * 4 * VEC < a.Mp)
                         sum = gather_add<VEC, false, FS>(sum, (j + i * 4 * VEC) * kByteRow<FS>, w[i], __builtin_inff());
             }
-            row_g[c] = last ? plb_from_s(sum, b, a.two_gamma) : sum;
+            const float g = last ? plb_from_s(sum, b, a.two_gamma) : sum;
+            if (on) row_g[c] = g;
+            if (last) {
+                float m = g;                          // (what is no number passes no threshold)
+                m = __builtin_fminf(m, lane_xor<1>(m));
+                m = __builtin_fminf(m, lane_xor<2>(m));
+                m = __builtin_fminf(m, lane_xor<4>(m));
+                m = __builtin_fminf(m, lane_xor<8>(m));
+                m = __builtin_fminf(m, lane_xor<16>(m));
+                m = __builtin_fminf(m, __shfl_xor(m, 32));
+                if ((tid & 63) == 0) a.least[(size_t)slot * ((a.stride + 63) / 64) + (cw >> 6)] = m;
+            }
         }
     }
 }
@@ -91,7 +107,9 @@ __global__ __launch_bounds__(kBoundThreads) void bound_kernel(const FewArgs a) {
 // One workgroup per query.  R after the first batch is its k least distances: a histogram of the distances' bit
 // patterns leaves little more than k of them to sort.  Then stretches of candidates, each about as long as what
 // has been seen (4,096 or 16,384; half of that with wide R), listed against the threshold at their start, measured, and replayed
-// by the first wave.
+// by the first wave; a stretch whose bounds' least (one of every 64, from bound_kernel) is above the threshold is not looked
+// at.  Bound by latency: bounds of 84,000 candidates read stretch by stretch, first-batch bounds read one after the other and a
+// sort across the lanes took 46,000 of a single query's 59,000 clocks (25.2 us; now 10.6).
 template <int E>
 __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs a) {
     constexpr int T = settle_threads(E);
@@ -111,17 +129,26 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
     __shared__ int s_n, s_count, s_frozen;
     __shared__ int s_nk;          // (the sorted ones are not counted in s_n: it is read while they already are)
     __shared__ float s_tau, s_tau_f;
+    __shared__ uint32_t s_ahead;  // of the T / 64 stretches looked at: those that have something to list
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t slot = blockIdx.x;
     const int64_t q = a.order ? a.order[slot] : slot;
     if (q < 0 || q >= a.nq) return;
+    const float *row_g = a.g + (size_t)slot * a.stride;
+    // the first batch's bounds and distances on their way (what lies beyond it is not used)
+    constexpr int kPre = 2;
+    float pre_g[kPre], pre_d2[kPre] = {};
+#pragma unroll
+    for (int u = 0; u < kPre; ++u) {
+        pre_g[u] = row_g[tid + u * T < a.stride ? tid + u * T : 0];
+        if (a.d2) pre_d2[u] = a.d2[(size_t)slot * (a.k + a.batch) + (tid + u * T < a.k + a.batch ? tid + u * T : 0)];
+    }
     for (int t = tid; t < a.d; t += T) q_lds[t] = a.queries[(size_t)q * a.d + t];
     if (tid < 256) hist[tid] = 0;
     if (tid == 0) { s_most = 0; s_least = ~0u; s_n = 0; s_nk = 0; s_count = 0; }
     segment_table(a.list_offsets, a.probes, a.nlist, a.nseg, a.n, a.max_cand, q, segp, segd);
     const int total = a.totals[slot];
     const int ns = total < a.k ? total : a.k, fb = total < a.k + a.batch ? total : a.k + a.batch;
-    const float *row_g = a.g + (size_t)slot * a.stride;
     uint32_t *mask_row = a.mask ? a.mask + (size_t)q * a.mask_words : nullptr;
     // exact distances of n candidates at(i), four rows per half wave; put(i, d2, storage position)
     auto measure = [&](int n, auto at, auto put) {
@@ -140,14 +167,17 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
     };
     // ---- the seed: its largest distance is the first batch's threshold ----
     if (a.d2) {
-        for (int i = tid; i < fb; i += T) f_d2[i] = a.d2[(size_t)slot * (a.k + a.batch) + i];
+#pragma unroll
+        for (int u = 0; u < kPre; ++u)
+            if (tid + u * T < fb) f_d2[tid + u * T] = pre_d2[u];
+        for (int i = tid + kPre * T; i < fb; i += T) f_d2[i] = a.d2[(size_t)slot * (a.k + a.batch) + i];
         __syncthreads();
     } else {
         measure(ns, [&](int i) { return i; }, [&](int i, float v, int) { f_d2[i] = v; });
     }
     uint32_t most = 0;
     for (int i = tid; i < ns; i += T) most = max(most, __float_as_uint(f_d2[i]));
-    if (most) atomicMax(&s_most, most);
+    wave_max(&s_most, most);
     __syncthreads();
     // (a distance that is no number is never in R: then R is not full yet)
     const bool full = ns == a.k && s_most <= 0x7f800000u;
@@ -155,13 +185,22 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
     // ---- the first batch ----
     {
         int mine = 0;
-        for (int i = tid; i < fb; i += T) {
-            const bool on = i < ns || row_g[i] <= tau1;
+        // (one atomic a wave: nearly all of them are in)
+        auto first = [&](int i, float g) {
+            const bool on = i < fb && (i < ns || g <= tau1);
             mine += on;
             if (on && mask_row && (i >> 5) < a.mask_words) atomicOr(&mask_row[i >> 5], 1u << (i & 31));
-            if (on && (a.d2 != nullptr || i >= ns)) s_todo[atomicAdd(&s_n, 1)] = (uint16_t)i;
-        }
-        if (mine) atomicAdd(&s_count, mine);
+            const unsigned long long put = __ballot(on && (a.d2 != nullptr || i >= ns));
+            if (put == 0) return;
+            int to = 0;
+            if (lane == 0) to = atomicAdd(&s_n, __popcll(put));
+            to = __builtin_amdgcn_readfirstlane(to) + __popcll(put & ((1ull << lane) - 1ull));
+            if ((put >> lane) & 1ull) s_todo[to] = (uint16_t)i;
+        };
+#pragma unroll
+        for (int u = 0; u < kPre; ++u) first(tid + u * T, pre_g[u]);
+        for (int i0 = kPre * T; i0 < fb; i0 += T) first(i0 + tid, row_g[i0 + tid < fb ? i0 + tid : 0]);
+        wave_add(&s_count, mine);
     }
     __syncthreads();
     int n = s_n;
@@ -220,32 +259,32 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
     }
     __syncthreads();
     nk = s_nk;
-    if (nk <= kWave) {                           // (one wave, in registers)
-        if (wave == 0) {
-            unsigned long long key = lane < nk ? s_key[lane] : ~0ull;
-#pragma unroll
-            for (int size = 2; size <= kWave; size <<= 1)
-#pragma unroll
-                for (int j = size >> 1; j > 0; j >>= 1) {
-                    const uint32_t olo = (uint32_t)__shfl_xor((int)(uint32_t)key, j), ohi = (uint32_t)__shfl_xor((int)(uint32_t)(key >> 32), j);
-                    const unsigned long long other = ((unsigned long long)ohi << 32) | olo;
-                    const bool keep_min = ((lane & j) == 0) == ((lane & size) == 0);
-                    if (keep_min ? other < key : other > key) key = other;
-                }
-            if (lane < nk) s_key[lane] = key;
+    const int have = nk < a.k ? nk : a.k;
+    if (nk <= 256) {                             // (a rank each; two entries may be one and the same)
+        if (tid < nk) {
+            const unsigned long long key = s_key[tid];
+            int rank = 0;
+#pragma unroll 8
+            for (int j = 0; j < nk; ++j) {
+                const unsigned long long o = s_key[j];
+                rank += o < key || (o == key && j < tid);
+            }
+            if (rank < have) {
+                rd2[rank] = __uint_as_float((uint32_t)(key >> 32));
+                rid[rank] = (int32_t)((uint32_t)key ^ 0x80000000u);
+            }
         }
-        __syncthreads();
+        for (int i = have + tid; i < kWave * E; i += T) { rd2[i] = __builtin_inff(); rid[i] = kEmptyId; }
     } else {
         int size = 1;
         while (size < nk) size <<= 1;
         for (int i = nk + tid; i < size; i += T) s_key[i] = ~0ull;
         __syncthreads();
         sort_keys(s_key, size);
-    }
-    const int have = nk < a.k ? nk : a.k;
-    for (int i = tid; i < kWave * E; i += T) {
-        rd2[i] = i < have ? __uint_as_float((uint32_t)(s_key[i] >> 32)) : __builtin_inff();
-        rid[i] = i < have ? (int32_t)((uint32_t)s_key[i] ^ 0x80000000u) : kEmptyId;
+        for (int i = tid; i < kWave * E; i += T) {
+            rd2[i] = i < have ? __uint_as_float((uint32_t)(s_key[i] >> 32)) : __builtin_inff();
+            rid[i] = i < have ? (int32_t)((uint32_t)s_key[i] ^ 0x80000000u) : kEmptyId;
+        }
     }
     __syncthreads();
     ResultRegs<E> R;
@@ -257,9 +296,38 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
     }
     __syncthreads();
     // ---- the rest ----
+    const float *least_of = a.least + (size_t)slot * ((a.stride + 63) / 64);
+    int looked = 0;                              // up to here s_ahead is known
+    uint32_t ahead = 0;
     for (int w0 = fb; w0 < total;) {
         const int V = a.nseg == 0 && w0 < 16384 ? 4 : 16, base = w0 & ~3;
         const int w1 = total - base < V * T ? total : base + V * T;
+        if (V == 16) {
+            // the next stretches, a wave each (thresholds only fall: who is above this one stays out)
+            if (w0 >= looked) {
+                __syncthreads();                 // (the last look has been read)
+                if (tid == 0) s_ahead = 0;
+                __syncthreads();
+                const float tau = __builtin_fmaxf(s_tau, s_tau_f);
+                const int64_t from = (int64_t)base + (int64_t)wave * 16 * T, to = from + 16 * T < total ? from + 16 * T : total;
+                constexpr int kLeast = 16 * T / 64 / kWave + 1;
+                const int g0 = (int)(from >> 6), g1 = (int)((to - 1) >> 6);
+                float v[kLeast];
+                bool any = false;
+#pragma unroll
+                for (int u = 0; u < kLeast; ++u) v[u] = least_of[from < to ? min(g0 + u * kWave + lane, g1) : 0];
+#pragma unroll
+                for (int u = 0; u < kLeast; ++u) any |= v[u] <= tau;
+                any &= from < to;
+                if (__any(any) && lane == 0) atomicOr(&s_ahead, 1u << wave);
+                __syncthreads();
+                ahead = s_ahead;
+                looked = base + 16 * T * (T / kWave) < total ? base + 16 * T * (T / kWave) : total;
+            }
+            const bool some = ahead & 1u;
+            ahead >>= 1;
+            if (!some) { w0 = w1; continue; }
+        }
         // (the batch that the last stretch ended in keeps the threshold that it began with)
         const float tau = s_tau, tau_b = __builtin_fmaxf(tau, s_tau_f);
         const int end_b = s_frozen >= 0 ? a.k + (s_frozen + 1) * a.batch : 0;

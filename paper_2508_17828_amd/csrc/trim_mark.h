@@ -1290,7 +1290,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                 measure(ns);
                 uint32_t most = 0;
                 for (int i = tid; i < ns; i += kReplayThreads) most = max(most, __float_as_uint(s_d2[i]));
-                if (most) atomicMax(&s_most, most);
+                wave_max(&s_most, most);
                 __syncthreads();
                 // (a distance that is no number is never in R: then R is not full yet)
                 const float tau1 = ns == a.k && s_most <= 0x7f800000u ? __uint_as_float(s_most) : __builtin_inff();
@@ -1305,7 +1305,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                             s_key[atomicAdd(&s_ntodo, 1)] = ((unsigned long long)__float_as_uint(s_d2[i]) << 32) | (uint32_t)i;
                     }
                 }
-                if (mine) atomicAdd(&s_count, mine);
+                wave_add(&s_count, mine);
                 __syncthreads();
                 int nc = s_ntodo;
                 if (tid == 0) survivors += s_count;
@@ -1321,7 +1321,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                 measure(first);
                 most = 0;
                 for (int i = tid; i < first; i += kReplayThreads) most = max(most, __float_as_uint(s_d2[s_todo[i]]));
-                if (most) atomicMax(&s_most, most);
+                wave_max(&s_most, most);
                 if (tid == 0) s_ntodo = 0;
                 __syncthreads();
                 // (a distance that is no number bounds nothing)
@@ -1331,7 +1331,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                     const bool need = __uint_as_float((uint32_t)(s_key[i] >> 32)) <= cut;
                     if (need) { s_todo[i - first] = (uint16_t)s_key[i]; ++more; }
                 }
-                if (more) atomicAdd(&s_ntodo, more);
+                wave_add(&s_ntodo, more);
                 __syncthreads();
                 const int n2 = s_ntodo;
                 measure(n2);

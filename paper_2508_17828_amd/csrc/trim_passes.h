@@ -201,6 +201,7 @@ struct FewArgs {
     int32_t *totals;          // candidates of the query
     float *g;                 // [stride] their bounds
     int64_t stride;           // (a multiple of 16)
+    float *least;             // [(stride + 63) / 64] the least bound of every 64
     float *d2;                // [k + batch] exact distances of the seed and the first batch, or null: settle measures
     int32_t *out_ids;
     float *out_d2;

@@ -68,6 +68,20 @@ __device__ __forceinline__ void segment_table_ready(const int32_t *seg, int nseg
     __syncthreads();
 }
 
+// Into a word of the LDS, one atomic a wave: lanes with a value each, the compiler would let take their turns (64 of them, some
+// 10,000 clocks where 16 waves do).  All lanes take part.
+__device__ __forceinline__ void wave_add(int *to, int v) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    if ((threadIdx.x & (kWave - 1)) == 0 && v) atomicAdd(to, v);
+}
+__device__ __forceinline__ void wave_max(uint32_t *to, uint32_t v) {
+    if (__ballot(v != 0) == 0) return;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, off));
+    if ((threadIdx.x & (kWave - 1)) == 0) atomicMax(to, v);
+}
+
 __device__ __forceinline__ int segment_position(int c, const int *segp, const int *segd, int nseg) {
     int lo = 0, hi = (nseg > 0 ? nseg : 1) - 1;
     while (lo < hi) {

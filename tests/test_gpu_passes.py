@@ -164,6 +164,31 @@ def test_few_queries_equal_the_single_kernel(T, case):
                 np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
 
 
+# survivors few and far between, at the ends of the stretches that are looked at together and of their groups of 64; result sets of
+# both block sizes (1024 and 512 threads: other stretches); after results that fill up late
+@pytest.mark.parametrize("k,batch", ((10, 64), (300, 100)))
+@pytest.mark.parametrize("near", ((16455, 16456, 278599, 278600, 599_999), (8592, 74127, 74128, 300_031, 300_032), ()))
+def test_few_survivors_among_many_candidates(T, k, batch, near):
+    import torch
+    n, d, nq, gamma = 600_000, 16, 2, 0.3
+    g = torch.Generator(device="cuda").manual_seed(len(near) + k)
+    base = torch.randn((n, d), device="cuda", generator=g) + 20
+    base[:k] -= 19
+    at = torch.tensor(near, device="cuda", dtype=torch.long)
+    base[at] = torch.randn((len(near), d), device="cuda", generator=g) * 0.1
+    q = torch.randn((nq, d), device="cuda", generator=g) * 0.1
+    cb = T.trim_train_pq(base[:4096].contiguous(), 4, 2, torch.randperm(4096, device="cuda", generator=g)[:256].to(torch.int32))
+    codes, dlx = T.trim_encode(base, cb)
+    ix = T.Index(base, codes, dlx, cb)
+    assert T.lib().trim_knn_workspace_bytes(C.byref(ix._view()), nq, None, k, batch) > 0
+    for count in (nq, 1):
+        want = single_kernel(T, ix, q[:count], k, gamma, batch, None, None)
+        got = T.trim_search_knn(ix, q[:count], k, gamma, batch, want_mask=True)
+        for name in ("ids", "d2", "n_scanned", "n_exact", "mask"):
+            np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
+        assert set(near) <= set(got["ids"][0].tolist())
+
+
 def single_range(T, ix, q, radius, gamma, probes, order, lut):
     import torch
     nq = q.shape[0]
