@@ -829,10 +829,8 @@ int knn_few(const trim_index_view *ix, const FewLayout &L, const SearchArgs &a, 
     f.d2 = L.measure_first ? reinterpret_cast<float *>(ws + L.off_d2) : nullptr;
     f.out_ids = a.out_ids; f.out_d2 = a.out_d2; f.n_scanned = a.n_scanned; f.n_exact = a.n_exact;
     f.mask = a.mask; f.mask_words = a.mask_words;
-    // two workgroups per CU over all queries, each with a candidate per thread at the least
-    const int64_t split = std::max<int64_t>(1, std::min<int64_t>((512 + a.nq - 1) / a.nq, (f.max_cand + kBoundThreads - 1) / kBoundThreads));
     int rc;
-    if ((rc = launch_bound(f, is_fs(ix), (int)split, st))) return rc;
+    if ((rc = launch_bound(f, is_fs(ix), st))) return rc;
     return launch_settle(f, st);
 }
 

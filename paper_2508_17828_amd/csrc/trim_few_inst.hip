@@ -44,8 +44,14 @@ bool few_fits(int d, int M, bool fs, int k, int nseg) {
     return bound_carve(a, fs) != 0 && settle_carve(a) + 2048 <= kLdsBytes;      // (and the static part)
 }
 
-int launch_bound(FewArgs a, bool fs, int nsplit, hipStream_t st) {
+int launch_bound(FewArgs a, bool fs, hipStream_t st) {
     const size_t lds = bound_carve(a, fs);
+    // As many workgroups as are resident at once (three per CU where their tables fit, else two), no more, over all
+    // queries, each with a candidate per thread at the least.  Searches, us, two per CU rounded up / this: 48 code bytes, 384 values: 20
+    // queries 73.7 / 72.8, 33 82.4 / 78.3, 48 91.4 / 88.7, 67 100.4 / 96.5; 32 code bytes: 20 89.7 / 85.1, 60 124.5 / 112.9; 96 code
+    // bytes, 768 values: 20 365.6 / 353.3, 67 518.8 / 504.2, 100 629.6 / 609.3.
+    const int64_t resident = 256 * (3 * lds <= kLdsBytes ? 3 : 2);
+    const int64_t nsplit = std::max<int64_t>(1, std::min<int64_t>(resident / a.nq, ((int64_t)a.max_cand + kBoundThreads - 1) / kBoundThreads));
     const int vec = (a.M % 16 == 0 && a.Mp % 16 == 0) ? 4 : (a.M % 8 == 0 && a.Mp % 8 == 0) ? 2 : 1;
     void (*fn)(const FewArgs) = nullptr;
     if (fs) {

@@ -55,7 +55,7 @@ int launch_range_exact(ReplayArgs a, int64_t nslots, int nchunk, hipStream_t st)
 size_t replay_lds(int d, int k, int nseg);      // LDS of one of their workgroups
 // The search of few queries (trim_few_inst.hip).
 bool few_fits(int d, int M, bool fs, int k, int nseg);
-int launch_bound(FewArgs a, bool fs, int nsplit, hipStream_t st);
+int launch_bound(FewArgs a, bool fs, hipStream_t st);
 int launch_settle(FewArgs a, hipStream_t st);
 int launch_replay(ReplayArgs a, int64_t nslots, hipStream_t st);
 
