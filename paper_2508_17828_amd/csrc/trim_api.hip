@@ -720,6 +720,24 @@ bool probe_in_two(int64_t nq, int d, int nlist, int nprobe) {
            (size_t)nq * nlist <= size_t(1) << 26;
 }
 
+// Queries per workgroup of ivf_probe_kernel: 8 (one per wave for the selection), fewer if their key arrays do not fit half of the
+// LDS (so that two workgroups share a CU).
+int probe_queries(int d, int nlist, int *npow2, size_t *lds) {
+    *npow2 = 1;
+    while (*npow2 < nlist && *npow2 < 1 << 30) *npow2 <<= 1;
+    int qt = 8;
+    while (qt > 1 && (size_t)qt * ((size_t)*npow2 * 8 + (size_t)d * 4) > kLdsBytes / 2) qt >>= 1;
+    *lds = (size_t)qt * ((size_t)*npow2 * 8 + (size_t)d * 4);
+    return qt;
+}
+// Sizes that a probe selection takes, whatever its work space.
+bool probe_takes(int64_t nq, int d, int nlist, int nprobe) {
+    int npow2;
+    size_t lds;
+    probe_queries(d, nlist, &npow2, &lds);
+    return nq <= 0x7fffffff && (lds <= kLdsBytes || probe_in_two(nq, d, nlist, nprobe));
+}
+
 // The work space of a probe selection through the matrix cores (trim_probe.h); total = 0: another one.
 struct ProbeLayout {
     int32_t dpad, lpad;
@@ -729,7 +747,7 @@ struct ProbeLayout {
 ProbeLayout probe_layout(int64_t nq, int d, int nlist, int nprobe) {
     ProbeLayout L{};
     if (!probe_ranked_pays(nq, d, nlist, nprobe) || nprobe < 2 || nprobe > 64 || nlist > 65536 || d % 4 || d > 4096 ||
-        (int64_t)nlist * d > int64_t(1) << 27) return L;
+        (int64_t)nlist * d > int64_t(1) << 27 || !probe_takes(nq, d, nlist, nprobe)) return L;
     L.dpad = (d + 15) / 16 * 16;
     L.lpad = (nlist + kPrbCols - 1) / kPrbCols * kPrbCols;
     L.slab = std::min<int64_t>((nq + 31) / 32 * 32, std::max<int64_t>(32, (int64_t(1) << 26) / (L.lpad + L.dpad / 2) / 32 * 32));
@@ -1552,13 +1570,9 @@ int trim_ivf_probe(const float *queries, int64_t nq, int32_t d, const float *cen
     if (nq < 0 || d <= 0 || nlist <= 0 || nprobe <= 0) return TRIM_INVALID_ARG;
     if (nprobe > nlist || nprobe > TRIM_MAX_NPROBE) return TRIM_INVALID_ARG;
     if (d % 4) return TRIM_UNSUPPORTED_SHAPE;
-    int npow2 = 1;
-    while (npow2 < nlist) npow2 <<= 1;
-    // queries per workgroup: 8 (one per wave for the selection), fewer if their key arrays do not
-    // fit half of the LDS (so that two workgroups share a CU)
-    int qt = 8;
-    while (qt > 1 && (size_t)qt * ((size_t)npow2 * 8 + (size_t)d * 4) > kLdsBytes / 2) qt >>= 1;
-    const size_t lds = (size_t)qt * ((size_t)npow2 * 8 + (size_t)d * 4);
+    int npow2;
+    size_t lds;
+    const int qt = probe_queries(d, nlist, &npow2, &lds);
     if (lds > kLdsBytes) return TRIM_UNSUPPORTED_SHAPE;
     if (nq == 0) return TRIM_OK;
     if (!queries || !centroids || !probes_out || !aligned16(centroids)) return TRIM_INVALID_ARG;

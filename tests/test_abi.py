@@ -146,6 +146,20 @@ def test_build_refuses_search_kernels_with_static_lds(L):
     assert len(search) >= 12 and all("static_lds=0" in r for r in search)
 
 
+@pytest.mark.parametrize("nq,d,nlist,nprobe,takes", [
+    (4097, 128, 16384, 32, True), (4097, 128, 16385, 32, False),         # ivf_probe_kernel's keys fill the LDS
+    (4096, 128, 16384, 32, True), (2000, 128, 20000, 32, True), (5000, 128, 65536, 64, False),
+    (1000, 2564, 17000, 32, False), (3000, 4096, 16384, 64, True),
+    (1 << 31, 128, 1024, 32, False)])
+def test_probe_selections_are_refused_whatever_their_work_space(L, nq, d, nlist, nprobe, takes):
+    """What trim_ivf_probe refuses and two kernels do not take either is not taken by the third way alone, which needs its
+    whole work space: nothing is asked for, and the call is trim_ivf_probe, which refuses on the host."""
+    need = L.trim_ivf_probe_workspace_bytes(nq, d, nlist, nprobe)
+    assert (need > 0) == takes
+    if not takes:        # (no work space is taken, so that nothing is launched on these addresses)
+        assert L.trim_ivf_probe_ws(4096, nq, d, 4096, nlist, nprobe, 4096, 4096, 1 << 40, None) in (-1, -2)
+
+
 def test_which_searches_of_few_queries_are_split(L):
     """More than one query is split over the chip up to a number of lookups that depends on the rows (csrc/trim_api.hip)."""
     def split(n, d, M, nq, k, nlist=0, nprobe=0):
