@@ -242,6 +242,22 @@ def test_probe_selection_of_equally_near_lists(T, oracle, nlist, same, nprobe):
     np.testing.assert_array_equal(got, oracle.ivf_probe(q, cent, nprobe))
 
 
+# queries so far away that all their distances agree in the leading bits that the selection looks at first; some of the lists are one
+@pytest.mark.parametrize("nlist,same,nprobe", ((1024, 0, 32), (1025, 300, 64), (3000, 500, 2), (300, 299, 33)))
+def test_probe_selection_of_queries_far_from_all_lists(T, oracle, nlist, same, nprobe):
+    import torch
+    rng = np.random.default_rng(nlist)
+    cent = rng.uniform(0, 255, (nlist, 128)).astype(np.float32)
+    cent[rng.permutation(nlist)[:same]] = 7.0
+    q = rng.uniform(0, 255, (3, 128)).astype(np.float32)
+    q[1:] += np.float32(1e5)
+    bits = ((q[1] - cent) ** 2).sum(axis=1).astype(np.float32).view(np.uint32) >> 12
+    assert np.unique(bits).size <= 4
+    assert T.lib().trim_ivf_probe_workspace_bytes(3, 128, nlist, nprobe) == 3 * nlist * 4
+    got = T.trim_ivf_probe(torch.from_numpy(q).cuda(), torch.from_numpy(cent).cuda(), nprobe).cpu().numpy()
+    np.testing.assert_array_equal(got, oracle.ivf_probe(q, cent, nprobe))
+
+
 # what the selection through the matrix cores takes: lists and values that leave its tiles unfilled, more queries than fit its
 # scores at a time, as many probes as it takes; ties, more lists in one place than a query's candidates can be (300 of 1501),
 # rows out of the scaled range, and what is no number: the same lists as the kernel that measures every pair
