@@ -742,7 +742,7 @@ bool probe_takes(int64_t nq, int d, int nlist, int nprobe) {
 struct ProbeLayout {
     int32_t dpad, lpad;
     int64_t slab;              // queries at a time: 256 MB of scores and operands
-    size_t off_c, off_q, off_cpar, off_cnm, off_qpar, off_t, total;
+    size_t off_c, off_q, off_cpar, off_cnm, off_qpar, off_left, off_t, total;
 };
 ProbeLayout probe_layout(int64_t nq, int d, int nlist, int nprobe) {
     ProbeLayout L{};
@@ -757,6 +757,7 @@ ProbeLayout probe_layout(int64_t nq, int d, int nlist, int nprobe) {
     L.off_cpar = off; off += up256((size_t)L.lpad * 16);
     L.off_cnm = off;  off += up256((size_t)L.lpad * 8);
     L.off_qpar = off; off += up256((size_t)L.slab * 16);
+    L.off_left = off; off += up256((size_t)kPrbLefts * (kPrbApart + (L.slab + kPrbLefts - 1) / kPrbLefts) * 4);
     L.off_t = off;    off += up256((size_t)L.slab * L.lpad * 4);
     L.total = off + 256;       // (the caller's memory need not be aligned)
     return L;
@@ -771,10 +772,13 @@ int launch_probe_ranked(const float *queries, int64_t nq, int d, const float *ce
     a.cpar = reinterpret_cast<float4 *>(ws + L.off_cpar);
     a.cnm = reinterpret_cast<float2 *>(ws + L.off_cnm);
     a.qpar = reinterpret_cast<float4 *>(ws + L.off_qpar);
+    a.left = reinterpret_cast<uint32_t *>(ws + L.off_left);
+    a.left_pitch = (L.slab + kPrbLefts - 1) / kPrbLefts;
     a.t = reinterpret_cast<float *>(ws + L.off_t);
     void (*nearest)(ProbeArgs) = d <= 128 ? probe_nearest_kernel<true> : probe_nearest_kernel<false>;
     HIP_TRY(allow_lds(reinterpret_cast<const void *>(probe_operands_kernel), (size_t)L.dpad * 4));
     HIP_TRY(allow_lds(reinterpret_cast<const void *>(nearest), (size_t)d * 4));
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(probe_rest_kernel), (size_t)8 * d * 4));
     for (int64_t q0 = 0; q0 < nq; q0 += L.slab) {
         a.nq = std::min<int64_t>(L.slab, nq - q0);
         a.queries = queries + (size_t)q0 * d;
@@ -784,6 +788,8 @@ int launch_probe_ranked(const float *queries, int64_t nq, int d, const float *ce
         hipLaunchKernelGGL(probe_operands_kernel, dim3((unsigned)a.list_groups + qblocks * (32 / kGrRows)), dim3(256), (size_t)L.dpad * 4, st, a);
         hipLaunchKernelGGL(probe_scores_kernel, dim3((unsigned)(L.lpad / kPrbCols), qblocks), dim3(256), 0, st, a);
         hipLaunchKernelGGL(nearest, dim3((unsigned)a.nq), dim3(kWave), (size_t)d * 4, st, a);
+        hipLaunchKernelGGL(probe_rest_kernel, dim3(kPrbRestGrid), dim3(kProbeThreads), (size_t)8 * d * 4, st, a);
+        hipLaunchKernelGGL(probe_rest_select_kernel, dim3((unsigned)std::min<int64_t>(a.nq, kPrbRestGrid)), dim3(kWave), 0, st, a);
         HIP_TRY(hipGetLastError());
     }
     return TRIM_OK;

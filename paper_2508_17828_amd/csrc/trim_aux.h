@@ -1570,22 +1570,14 @@ __global__ __launch_bounds__(256) void range_fill_kernel(const RangeFillArgs a) 
 // 128 values, 75 us for 67 over 1024 of 384, on one and nine of the CUs.  Here the lists are split over the grid as
 // well (grid.x, 8 kRows per workgroup) and the distances pass through memory: dist [nq][nlist], bit patterns.
 constexpr int kProbeThreads = 256;
-template <int QT>
-__global__ __launch_bounds__(kProbeThreads) void probe_distance_kernel(const float *__restrict__ queries, int64_t nq, int d,
-                                                                      const float *__restrict__ centroids, int nlist,
-                                                                      uint32_t *__restrict__ dist) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    float *q_lds = reinterpret_cast<float *>(smem);                            // [QT][d]
-    const int tid = threadIdx.x, lane32 = tid & 31, ng = d >> 2;
-    const int64_t q0 = (int64_t)blockIdx.y * QT;
-    const int nqt = (int)(nq - q0 < QT ? nq - q0 : QT);
-    for (int t = tid; t < QT * d; t += kProbeThreads) q_lds[t] = t < nqt * d ? queries[(size_t)q0 * d + t] : 0.0f;
-    __syncthreads();
-    // (the loop of ivf_probe_kernel: eight or four rows per half wave against the queries, sums reduced together)
+// Lists l0 .. (eight of them; four with eight queries) against the QT queries in the LDS, by a half wave (the loop of
+// ivf_probe_kernel): store(query, list, distance), each pair in one lane.
+template <int QT, typename F>
+__device__ __forceinline__ void probe_distances(const float *q_lds, int d, const float *__restrict__ centroids, int nlist, int l0,
+                                                int lane32, F &&store) {
     constexpr int kRows = QT == 8 ? 4 : 8, NP = kRows * QT;
     constexpr int kShift = NP == 32 ? 0 : NP == 16 ? 1 : 2;
-    const int l0 = ((int)blockIdx.x * (kProbeThreads / 32) + (tid >> 5)) * kRows;
-    if (l0 >= nlist) return;
+    const int ng = d >> 2;
     const float4 *row0 = reinterpret_cast<const float4 *>(centroids + (size_t)l0 * d);
     const int last = nlist - 1 - l0;     // (rows past the end: the last row again, never stored)
     float acc[NP];
@@ -1611,7 +1603,24 @@ __global__ __launch_bounds__(kProbeThreads) void probe_distance_kernel(const flo
     }
     const float v = reduce_pairs<NP>(acc, lane32);
     const int pair = lane32 >> kShift, l = l0 + pair / QT, qi = pair % QT;
-    if ((lane32 & ((1 << kShift) - 1)) == 0 && l < nlist && qi < nqt) dist[(size_t)(q0 + qi) * nlist + l] = __float_as_uint(v);
+    if ((lane32 & ((1 << kShift) - 1)) == 0 && l < nlist) store(qi, l, v);
+}
+template <int QT>
+__global__ __launch_bounds__(kProbeThreads) void probe_distance_kernel(const float *__restrict__ queries, int64_t nq, int d,
+                                                                      const float *__restrict__ centroids, int nlist,
+                                                                      uint32_t *__restrict__ dist) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    float *q_lds = reinterpret_cast<float *>(smem);                            // [QT][d]
+    const int tid = threadIdx.x, lane32 = tid & 31;
+    const int64_t q0 = (int64_t)blockIdx.y * QT;
+    const int nqt = (int)(nq - q0 < QT ? nq - q0 : QT);
+    for (int t = tid; t < QT * d; t += kProbeThreads) q_lds[t] = t < nqt * d ? queries[(size_t)q0 * d + t] : 0.0f;
+    __syncthreads();
+    const int l0 = ((int)blockIdx.x * (kProbeThreads / 32) + (tid >> 5)) * (QT == 8 ? 4 : 8);
+    if (l0 >= nlist) return;
+    probe_distances<QT>(q_lds, d, centroids, nlist, l0, lane32, [&](int qi, int l, float v) {
+        if (qi < nqt) dist[(size_t)(q0 + qi) * nlist + l] = __float_as_uint(v);
+    });
 }
 // The nprobe (at most 64) least (distance, list) of a query: one wave each.  The lists are 256 columns (lane, 0..3); the
 // nprobe-th least of the columns' minima, found bit by bit from above, bounds the nprobe-th least of all, so

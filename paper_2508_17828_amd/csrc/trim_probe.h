@@ -10,30 +10,37 @@
 //              least of the upper ends (of 256 columns' least ones) bounds who can be among the nearest; these, some nprobe
 //              and a few, are measured by the exact rule and ranked by (distance, number)
 //
-// 10000 queries x 1024 lists of 128 values, 32 probes: 128 -> 70 us, of which nearest 38 (latency: the candidates' rows, eight
-// at a time; a workgroup of 256 per query, with its barriers, took 110), scores 17.
+//   rest       who has more candidates than kPrbList (a query so far away that what rounding moved exceeds the spread of its
+//              distances; rows that are no numbers; many lists in one place): all lists measured, eight of these queries
+//              at a time, and selected as for few queries
+//
+// 10000 queries x 1024 lists of 128 values, 32 probes: 122 -> 71 us, of which nearest 38 (latency: the candidates' rows, eight
+// at a time; a workgroup of 256 per query, with its barriers, took 110), scores 17, the two launches of rest 2 where there
+// are none.  With 1 to 100 queries 10^5 away 80, with 1000 94, with all 223 (a wave that measured all lists of its query by itself and
+// picked them one after the other: 175 to 187, 226, 537); 2500 x 1024 of 768, 64 probes: 72, with one far away 90 (367).
 //
 // e = (5 d + 128) 2^-24 (|q'|^2 + |c'|^2) bounds the binary32 sums of S and the exact rule's own roundings.  Rows out of the scaled
-// range, and what is no number, have m = inf: always candidates, and nobody's bound.  More candidates than kPrbList (many lists in
-// one place): all are measured, and the nearest picked one after the other.
+// range, and what is no number, have m = inf: always candidates, and nobody's bound.
 #pragma once
 
 #include "trim_gamma.h"
 
 namespace trim {
 
-// From where on (both sides measured, us, two exact kernels (10000 queries: one) / these; 8, 32, 64 probes): 3000 x 1024 lists of 128
-// values 38 / 30, 34, 38, 10000 x 1024 128 / 70, 1000 x 4096 53 / 47, 50, 54; 10000 x 1024 of 768 453 / 102, 136, 179, of 1536 850 /
-// 172, 250, 350.  With less work the three launches and a wave's chain of candidates cost more: 1500 x 1024 of 128 24 / 24, 26, 31,
-// 1000 x 1024 of 768 51 / 37, 46, 61; and the fewer queries, the longer that chain shows: 300 x 4096 of 1536 180 / 73, 88, 123,
-// but 260 x 2048 88 / 59, 79, 110.  With more than an eighth of the lists probed most rows are measured anyway (10000 x 150 of
-// 1536, 64 probes: 165 / 231).
+// From where on (both sides measured, us, exact kernels / these; 8, 32, 64 probes): 4000 x 1024 lists of 128 values 45, 45, 48 / 38, 40,
+// 46, 10000 x 1024 121, 122, 138 / 64, 71, 82, 10000 x 512 75, 76, 94 / 45, 51, 61; 1400 x 1024 of 768 67, 68, 70 / 42, 50, 64, 10000 x 1024
+// of 768 457, 459, 470 / 109, 137, 186, 270 x 4096 of 1536 155, 154, 157 / 78, 101, 134.  Even at about 3,000,000 pairs: 3000 x 1024 of 128
+// 36, 37, 39 / 34, 35, 41 (2600 x 1024 32, 33, 35 / 33, 34, 39), and where fewer queries leave a wave's chain of candidates in the open, at
+// more: 1000 x 2600 35, 36, 38 / 41, 43, 47, 1000 x 4096 50, 51, 53 / 50, 52, 57, 1000 x 1024 of 1000 72, 73, 74 / 47, 59, 77.
+// With more than an eighth of the lists probed most rows are measured anyway (10000 x 150 of 1536, 64 probes: 165 / 231).
 inline bool probe_ranked_pays(int64_t nq, int d, int nlist, int nprobe) {
     const double pairs = (double)nq * nlist, values = pairs * d;
-    return nprobe <= nlist / 8 && ((nq >= 1000 && (pairs >= 2.5e6 || values >= 1e9)) || (nq >= 100 && values >= 1.6e9));
+    return nprobe <= nlist / 8 && ((nq >= 1500 && pairs >= 2.5e6) || (nq >= 1000 && (pairs >= 4.5e6 || values >= 1e9)) ||
+                                   (nq >= 100 && values >= 1.6e9));
 }
 
 constexpr int kPrbList = 256, kPrbCols = 256, kPrbRows = 32;
+constexpr int kPrbLefts = 32, kPrbApart = 32;       // (one counter took 15 ns a query; words from one to the next: a cache line)
 struct ProbeArgs {
     const float *queries, *cent;
     int64_t nq;                // queries of this launch
@@ -44,6 +51,8 @@ struct ProbeArgs {
     float4 *qpar, *cpar;       // 1 / scale, |.|^2, moved, unused
     float2 *cnm;               // of the lists once more: |.|^2, moved
     float *t;                  // [nq][lpad]
+    uint32_t *left;            // the queries with more candidates than kPrbList, kPrbLefts lists of them (by q % kPrbLefts): counts, then entries
+    int64_t left_pitch;
     int32_t *out;              // [nq][nprobe]
 };
 
@@ -54,6 +63,7 @@ __global__ __launch_bounds__(256) void probe_operands_kernel(const ProbeArgs a) 
     const int tid = threadIdx.x, part = tid & 31, d = a.d, np = a.dpad >> 3;
     const bool list = (int)blockIdx.x < a.list_groups;
     const int64_t row = (int64_t)(list ? blockIdx.x : blockIdx.x - a.list_groups) * kGrRows + (tid >> 5);
+    if (blockIdx.x == 0 && tid < kPrbLefts) a.left[tid * kPrbApart] = 0;
     for (int t = tid; t < a.dpad; t += 256) {
         float v[8], sum = 0.0f;
 #pragma unroll
@@ -176,7 +186,7 @@ __global__ __launch_bounds__(kWave) void probe_nearest_kernel(const ProbeArgs a)
     const int lane = threadIdx.x, lane32 = lane & 31;
     const int64_t q = blockIdx.x;
     const float *x = a.queries + (size_t)q * a.d;
-    float *row = a.t + (size_t)q * a.lpad;
+    const float *row = a.t + (size_t)q * a.lpad;
     const float4 qp = a.qpar[q];
     const float inf = __builtin_inff(), e2 = 2.0f * (5.0f * a.d + 128.0f) * (1.0f / 16777216.0f) * 1.0001f;
     for (int t = lane; t < a.d >> 2; t += kWave) reinterpret_cast<float4 *>(q_lds)[t] = reinterpret_cast<const float4 *>(x)[t];
@@ -221,44 +231,95 @@ __global__ __launch_bounds__(kWave) void probe_nearest_kernel(const ProbeArgs a)
         }
     }
     __syncthreads();
-    const bool few = n <= kPrbList;
-    const int all = few ? n : a.nlist;
-    // the exact distances, four rows to a half wave
-    for (int i0 = (lane >> 5) * 4; i0 < all; i0 += 8) {
-        int l[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { const int at = i0 + i < all ? i0 + i : i0; l[i] = few ? s_list[at] : at; }
-        const float dist = exact_d2_half_x4<!ONE_STEP, ONE_STEP>(a.cent + (size_t)l[0] * a.d, a.cent + (size_t)l[1] * a.d, a.cent + (size_t)l[2] * a.d,
-                                                                 a.cent + (size_t)l[3] * a.d, q_lds, a.d, lane32);
-        const int i = half_reduce_x4_row(lane32), mine = i == 0 ? l[0] : i == 1 ? l[1] : i == 2 ? l[2] : l[3];
-        if (half_reduce_x4_writer(lane32) && i0 + i < all) {
-            if (few) s_key[i0 + i] = ((unsigned long long)__float_as_uint(dist) << 32) | (uint32_t)mine;
-            else row[mine] = dist;                     // (the scores have been read)
-        }
-    }
-    __syncthreads();
-    int32_t *out = a.out + (size_t)q * a.nprobe;
-    if (few) {
-        for (int i = lane; i < n; i += kWave) {
-            const unsigned long long k = s_key[i];
-            int rank = 0;
-#pragma unroll 8
-            for (int j = 0; j < n; ++j) rank += s_key[j] < k;
-            if (rank < a.nprobe) out[rank] = (int32_t)(k & 0xffffffffu);
+    if (n > kPrbList) {                                // (probe_rest_kernel)
+        if (lane == 0) {
+            const int list = (int)(q % kPrbLefts);
+            a.left[kPrbLefts * kPrbApart + list * a.left_pitch + atomicAdd(&a.left[list * kPrbApart], 1u)] = (uint32_t)q;
         }
         return;
     }
-    unsigned long long last = 0;                       // keys below are taken
-    for (int p = 0; p < a.nprobe; ++p) {
-        unsigned long long k = ~0ull;
-        for (int l = lane; l < a.nlist; l += kWave) {
-            const unsigned long long v = ((unsigned long long)__float_as_uint(row[l]) << 32) | (uint32_t)l;
-            if (v >= last && v < k) k = v;
-        }
+    // the exact distances, four rows to a half wave
+    for (int i0 = (lane >> 5) * 4; i0 < n; i0 += 8) {
+        int l[4];
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) { const unsigned long long o = (unsigned long long)__shfl_xor((long long)k, off); k = o < k ? o : k; }
-        if (lane == 0) out[p] = (int32_t)(k & 0xffffffffu);
-        last = k + 1;
+        for (int i = 0; i < 4; ++i) l[i] = s_list[i0 + i < n ? i0 + i : i0];
+        const float dist = exact_d2_half_x4<!ONE_STEP, ONE_STEP>(a.cent + (size_t)l[0] * a.d, a.cent + (size_t)l[1] * a.d, a.cent + (size_t)l[2] * a.d,
+                                                                 a.cent + (size_t)l[3] * a.d, q_lds, a.d, lane32);
+        const int i = half_reduce_x4_row(lane32), mine = i == 0 ? l[0] : i == 1 ? l[1] : i == 2 ? l[2] : l[3];
+        if (half_reduce_x4_writer(lane32) && i0 + i < n) s_key[i0 + i] = ((unsigned long long)__float_as_uint(dist) << 32) | (uint32_t)mine;
+    }
+    __syncthreads();
+    int32_t *out = a.out + (size_t)q * a.nprobe;
+    for (int i = lane; i < n; i += kWave) {
+        const unsigned long long k = s_key[i];
+        int rank = 0;
+#pragma unroll 8
+        for (int j = 0; j < n; ++j) rank += s_key[j] < k;
+        if (rank < a.nprobe) out[rank] = (int32_t)(k & 0xffffffffu);
+    }
+}
+
+// The queries with more candidates than nearest takes: all lists measured, 32 lists by eight of these queries a workgroup and turn, the
+// distances kept where the scores were; then a wave each selects as probe_select_kernel does.  Both end with the list of them.
+constexpr int kPrbRestGrid = 1024;
+// How many there are; s_first: the lists' first numbers.  By the first wave and all threads that read it; ends with a barrier.
+__device__ __forceinline__ int rest_count(const ProbeArgs &a, uint32_t *s_first) {
+    if (threadIdx.x < kWave) {
+        const int lane = threadIdx.x;
+        uint32_t v = lane < kPrbLefts ? a.left[lane * kPrbApart] : 0u;
+#pragma unroll
+        for (int off = 1; off < kPrbLefts; off <<= 1) {
+            const uint32_t o = (uint32_t)__shfl_up((int)v, off);
+            if (lane >= off) v += o;
+        }
+        if (lane < kPrbLefts) s_first[lane + 1] = v;
+        if (lane == 0) s_first[0] = 0;
+    }
+    __syncthreads();
+    return (int)s_first[kPrbLefts];
+}
+__device__ __forceinline__ uint32_t rest_query(const ProbeArgs &a, const uint32_t *s_first, int i) {
+    int list = 0;
+#pragma unroll
+    for (int step = kPrbLefts / 2; step > 0; step >>= 1)
+        if (s_first[list + step] <= (uint32_t)i) list += step;
+    return a.left[kPrbLefts * kPrbApart + list * a.left_pitch + ((uint32_t)i - s_first[list])];
+}
+__global__ __launch_bounds__(kProbeThreads) void probe_rest_kernel(const ProbeArgs a) {
+    extern __shared__ __align__(16) float q_lds[];     // [8][d]
+    __shared__ uint32_t s_q[8], s_first[kPrbLefts + 1];
+    constexpr int kRows = kProbeThreads / 32 * 4;
+    const int tid = threadIdx.x, count = rest_count(a, s_first), groups = (count + 7) >> 3;
+    // lists per turn: 32; as many as leave every workgroup two turns where the queries are many (they are brought less often)
+    int per = kRows;
+    while (per < a.nlist && (int64_t)groups * ((a.nlist + 2 * per - 1) / (2 * per)) >= 2 * gridDim.x) per *= 2;
+    const int tiles = (a.nlist + per - 1) / per;
+    const int64_t units = (int64_t)groups * tiles;
+    for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
+        const int g0 = (int)(u / tiles) * 8, first = (int)(u % tiles) * per, nqt = count - g0 < 8 ? count - g0 : 8;
+        const int end = first + per < a.nlist ? first + per : a.nlist;
+        __syncthreads();                               // (the turn before is done with)
+        if (tid < 8) s_q[tid] = rest_query(a, s_first, g0 + (tid < nqt ? tid : 0));
+        __syncthreads();
+        for (int t = tid; t < 8 * a.d; t += kProbeThreads) {
+            const int qi = t / a.d;
+            q_lds[t] = a.queries[(size_t)s_q[qi] * a.d + (t - qi * a.d)];
+        }
+        __syncthreads();
+        for (int l0 = first + (tid >> 5) * 4; l0 < end; l0 += kRows)
+            probe_distances<8>(q_lds, a.d, a.cent, a.nlist, l0, tid & 31, [&](int qi, int l, float v) {
+                if (qi < nqt) a.t[(size_t)s_q[qi] * a.lpad + l] = v;
+            });
+    }
+}
+__global__ __launch_bounds__(kWave) void probe_rest_select_kernel(const ProbeArgs a) {
+    __shared__ unsigned long long s_key[kSelectList];
+    __shared__ uint32_t s_first[kPrbLefts + 1];
+    const int count = rest_count(a, s_first);
+    for (int i = blockIdx.x; i < count; i += gridDim.x) {
+        const uint32_t q = rest_query(a, s_first, i);
+        __syncthreads();                               // (the keys before these have been read)
+        select_least(reinterpret_cast<const uint32_t *>(a.t) + (size_t)q * a.lpad, a.nlist, a.nprobe, a.out + (size_t)q * a.nprobe, s_key, threadIdx.x);
     }
 }
 

@@ -294,6 +294,30 @@ def test_probe_of_many_queries(nq, nlist, d, nprobe):
         assert (got[-1].sort().values.diff() > 0).all()
 
 
+# of these, `far` are so far from all lists (or no numbers, or equally far) that nearly all lists are candidates: one query, a
+# workgroup's eight and one more, more than one turn of the whole grid, several slabs of scores
+@pytest.mark.parametrize("nq,nlist,d,nprobe,far", ((2500, 1024, 128, 32, 1), (2500, 1024, 128, 64, 9), (9001, 1030, 36, 3, 9000),
+                                                  (3000, 3001, 132, 50, 1025), (70001, 1030, 4, 8, 60000), (120, 8710, 1540, 50, 120),
+                                                  (110, 4000, 4096, 50, 55)))
+def test_probe_of_many_queries_far_from_all_lists(nq, nlist, d, nprobe, far):
+    import ctypes as C
+    import torch
+    from paper_2508_17828_amd import trim as T
+    L = T.lib()
+    assert L.trim_ivf_probe_workspace_bytes(nq, d, nlist, nprobe) > 4 * nlist * min(nq, 60000)
+    g = torch.Generator(device="cuda").manual_seed(nlist + d)
+    q, cent = torch.rand((nq, d), device="cuda", generator=g) * 255, torch.rand((nlist, d), device="cuda", generator=g) * 255
+    at = torch.randperm(nq, device="cuda", generator=g)[:far]
+    q[at] += 1e5
+    if far > 9:
+        q[at[::3]], q[at[1::100]] = 1e30, -3e12
+        cent[300:700] = cent[299]
+    want, got = torch.empty((nq, nprobe), dtype=torch.int32, device="cuda"), T.trim_ivf_probe(q, cent, nprobe)
+    assert L.trim_ivf_probe(C.c_void_p(q.data_ptr()), nq, d, C.c_void_p(cent.data_ptr()), nlist, nprobe, C.c_void_p(want.data_ptr()),
+                            C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    assert torch.equal(got, want)
+
+
 @pytest.mark.parametrize("n", (40, 3000, 200_000))
 @pytest.mark.parametrize("dsub,M", ((4, 8), (5, 8), (6, 8), (8, 8), (7, 4), (12, 4)))
 def test_encode_values_that_are_no_numbers(T, oracle, dsub, M, n):
