@@ -453,9 +453,11 @@ int scratch_for_current_device(void **out) {
 // ---- the scan in separate passes (trim_mark.h) ----
 
 // Table phases, block size and LDS layout of the finish pass: two workgroups of 512 threads per CU
-// where they fit, else one of 1024.  few: most candidates' sums are not wanted (range searches), and a workgroup spends
-// its time on the table and on getting ready; two per CU then pay for up to four phases (2,000 queries, 192 code bytes, 36 sums
-// each: 188 -> 159 us; with every sum wanted, 120 code bytes: 555 -> 691).
+// where they fit, else one of 1024.  few: most candidates' sums are not wanted (range searches, by the centroids' own tables), and a
+// workgroup spends its time on the table and on getting ready; two per CU then pay for up to four phases (2,000 queries, 192 code
+// bytes, 36 sums each: 188 -> 159 us; with every sum wanted, 120 code bytes: 555 -> 691).  Uneven variances and small radii leave more
+// sums, but few enough too: whole searches, 1,000 queries x 100,000 x 960, before / with certain bits and this plan: 600 / 533 us, gamma 0
+// and a small radius 501 / 470.
 struct FinishPlan {
     int threads, P, Mp, vec;
     size_t lds;
@@ -483,13 +485,17 @@ bool make_finish_plan(int d, int M, bool fs, int nseg, bool few, FinishPlan *pl)
     }
     return false;
 }
+void fill_plan(FinishArgs &m, const FinishPlan &pl) {
+    m.P = pl.P; m.Mp = pl.Mp;
+    m.off_q = pl.off_q; m.off_segp = pl.off_segp; m.off_segd = pl.off_segd; m.off_bits = pl.off_bits; m.off_ring = pl.off_ring;
+}
 void fill_finish(FinishArgs &m, const FinishPlan &pl, const SearchArgs &a) {
+    fill_plan(m, pl);
     m.codes = a.codes; m.dlx = a.dlx; m.codebooks = a.codebooks; m.n = a.n; m.d = a.d; m.M = a.M; m.dsub = a.dsub;
     m.queries = a.queries; m.nq = a.nq; m.order = a.order; m.lut = a.lut;
     m.list_offsets = a.list_offsets; m.probes = a.probes;
     m.nlist = a.nlist; m.nseg = a.nseg; m.max_cand = a.max_cand;
-    m.P = pl.P; m.Mp = pl.Mp; m.two_gamma = a.two_gamma; m.n_scanned = a.n_scanned;
-    m.off_q = pl.off_q; m.off_segp = pl.off_segp; m.off_segd = pl.off_segd; m.off_bits = pl.off_bits; m.off_ring = pl.off_ring;
+    m.two_gamma = a.two_gamma; m.n_scanned = a.n_scanned;
 }
 
 // Whether a search runs in passes.  They pay where rows are long (what the single kernel reads once per query and
@@ -988,7 +994,7 @@ int range_search(const trim_index_view *index, const float *queries, int64_t nq,
     if (a.max_cand > max_cand) a.max_cand = (int32_t)max_cand;
 
     a.nq = nq;
-    FinishPlan fpl;
+    FinishPlan fpl, whole;
     const size_t want = range_scratch_bytes(index, nq, cand, &fpl);
     if (scratch && want > 0 && scratch_bytes >= want && !a.work && (reinterpret_cast<uintptr_t>(scratch) & 255u) == 0 &&
         aligned16(queries) && (!lut || lut_tiled(a.dsub, is_fs(index)))) {
@@ -1003,7 +1009,11 @@ int range_search(const trim_index_view *index, const float *queries, int64_t nq,
         fa.by_query = v.by_query = 1;
         fa.range = 1; fa.radius2 = a.radius2; fa.lo = 0; fa.hi = a.max_cand;
         fa.totals = reinterpret_cast<int32_t *>(sc); fa.possible = rmask; fa.words = L.rmask_words; fa.d2 = rd2;
-        fa.certain = reinterpret_cast<uint32_t *>(sc + FL.end);
+        // (out of this range nobody passes for certain: see filter_kernel)
+        const bool some = a.radius2 > kCertainLow && a.radius2 < kCertainHigh;
+        make_finish_plan(index->d, code_bytes(index), is_fs(index), a.nseg, false, &whole);      // (it fits where the other one does)
+        if (!some) fpl = whole;
+        fa.certain = some ? reinterpret_cast<uint32_t *>(sc + FL.end) : nullptr;
         z.add(fa.certain, (size_t)nq * L.rmask_words);
         FinishArgs m{};
         fill_finish(m, fpl, a);
@@ -1023,7 +1033,19 @@ int range_search(const trim_index_view *index, const float *queries, int64_t nq,
         // candidates per query: the filter needs them before the finish pass writes them
         if ((rc = launch_totals(m, st))) return rc;
         if ((rc = launch_filter(fa, st))) return rc;
-        if ((rc = launch_finish(m, fpl.vec, is_fs(index), fpl.threads, fpl.lds, (nq + kXcds - 1) / kXcds * kXcds, st))) return rc;
+        // A caller's table that is not the centroids': every sum of that query is wanted, and the plan for few sums is the wrong one
+        // (1,000 queries x 100,000 x 1536, all of them so: 2177 us by it, 1851 by a launch with the other; 2,000 x 200,000 x 768 in 192
+        // subspaces 4504 / 3388).  The host does not see which: both launches, of which the second costs 2 to 9 us where there are none.
+        const int64_t slots = (nq + kXcds - 1) / kXcds * kXcds;
+        const bool both = m.bad && some && whole.P != fpl.P;
+        m.only = both ? kFinishGood : 0;
+        if ((rc = launch_finish(m, fpl.vec, is_fs(index), fpl.threads, fpl.lds, slots, st))) return rc;
+        if (both) {
+            fill_plan(m, whole);
+            m.certain = nullptr;
+            m.only = kFinishBad;
+            if ((rc = launch_finish(m, whole.vec, is_fs(index), whole.threads, whole.lds, slots, st))) return rc;
+        }
         if ((rc = launch_measure(fa, st))) return rc;
         if ((rc = launch_range_exact(y, nq, L.nsplit, st))) return rc;
     } else {

@@ -263,7 +263,7 @@ __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs
                 // distances by anything), s_room: by how much
                 const float c1 = 1.0f - 0.5f * a.two_gamma, tau = a.radius2, under = b * b * (1.0f - c1 * c1);
                 float hi = -__builtin_inff(), room = __builtin_inff();
-                if (tau > 1e-30f && tau < 1e30f) {
+                if (tau > kCertainLow && tau < kCertainHigh) {
                     const float end = __builtin_fabsf(c1 * b) + sqrt_rn(__builtin_fmaxf(tau - under, 0.0f)) + __builtin_fabsf(b);
                     const float root2 = tau - end * end * ((float)(a.nsub + a.dsub + 64) * (1.0f / 8388608.0f)) - under;
                     if (root2 > 0.0f) {
@@ -852,8 +852,8 @@ __global__ __launch_bounds__(256) void lut_tile_kernel(const LutArgs a) {
 // ---- finish: the bounds of the marked candidates, by the rule ----
 // One workgroup per query: its table in the LDS (rows of one phase at a time), its marked candidates
 // (or, all: every candidate of the pass) listed a few thousand at a time, one per thread; who does not
-// pass is unmarked.
-template <int VEC, bool FS>
+// pass is unmarked.  PICK: only the queries that a.only names.
+template <int VEC, bool FS, bool PICK>
 __global__ __launch_bounds__(1024)
 __attribute__((amdgpu_waves_per_eu(4)))
 void finish_kernel(const FinishArgs a) {
@@ -874,6 +874,7 @@ void finish_kernel(const FinishArgs a) {
         if (!a.by_query && a.totals && a.lo == 0 && tid == 0) a.totals[slot] = 0;
         return;
     }
+    if (PICK && (a.bad[q] != 0) != (a.only == kFinishBad)) return;
     const int64_t row = a.by_query ? q : slot;
     const int nseg = a.nseg > 0 ? a.nseg : 1;
     // the first rows of the table are on their way while the rest is made ready

@@ -17,17 +17,17 @@ int launch_invert(const InvertArgs &a, hipStream_t st) {
     return TRIM_OK;
 }
 
+template <bool PICK>
+static void (*finish_of(int vec, bool fs))(const FinishArgs) {
+    if (fs) return vec == 4 ? finish_kernel<4, true, PICK> : finish_kernel<2, true, PICK>;
+    return vec == 4 ? finish_kernel<4, false, PICK> : vec == 2 ? finish_kernel<2, false, PICK> : finish_kernel<1, false, PICK>;
+}
 int launch_finish(const FinishArgs &a, int vec, bool fs, int threads, size_t lds, int64_t slots, hipStream_t st) {
-    void (*fn)(const FinishArgs) = nullptr;
-    if (fs) {
-        if (vec == 1) return TRIM_UNSUPPORTED_SHAPE;
-        fn = vec == 4 ? finish_kernel<4, true> : finish_kernel<2, true>;
-    } else {
-        fn = vec == 4 ? finish_kernel<4, false> : vec == 2 ? finish_kernel<2, false> : finish_kernel<1, false>;
-    }
+    if (fs && vec == 1) return TRIM_UNSUPPORTED_SHAPE;
+    void (*fn)(const FinishArgs) = a.only ? finish_of<true>(vec, fs) : finish_of<false>(vec, fs);
     // (the table must start at LDS address 0: see launch_instance)
-    static std::atomic<int> lds_checked[6];
-    std::atomic<int> &seen = lds_checked[(fs ? 3 : 0) + (vec == 4 ? 2 : vec == 2 ? 1 : 0)];
+    static std::atomic<int> lds_checked[12];
+    std::atomic<int> &seen = lds_checked[(a.only ? 6 : 0) + (fs ? 3 : 0) + (vec == 4 ? 2 : vec == 2 ? 1 : 0)];
     if (seen.load(std::memory_order_acquire) == 0) {
         hipFuncAttributes fa;
         HIP_TRY(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(fn)));

@@ -8,6 +8,8 @@ namespace trim {
 
 constexpr int kFinishPiece = 32768, kFinishList = 8192;   // candidates, listed candidates at a time (finish)
 
+constexpr float kCertainLow = 1e-30f, kCertainHigh = 1e30f;      // squared radii of which filter_kernel tells who passes for certain
+constexpr int kFinishGood = 1, kFinishBad = 2;      // FinishArgs::only
 struct FinishArgs {
     // index, queries, candidate structure: as in SearchArgs
     const uint8_t *codes;
@@ -23,6 +25,7 @@ struct FinishArgs {
     const float *lut;         // tables by query number, or (lut_by_row) by row of the workspace; null: built here
     int32_t lut_by_row;
     const uint32_t *bad;      // by query number: the table is not the centroids' (or null)
+    int32_t only;             // 0: all queries; else those that are not bad, or those that are
     const int64_t *list_offsets;
     const int32_t *probes;
     const int32_t *seg;       // see InvertArgs (null: no lists)

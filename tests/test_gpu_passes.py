@@ -242,6 +242,21 @@ def test_range_in_passes_equals_the_single_kernel(T, case, percent):
                 np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
 
 
+@pytest.mark.parametrize("radius", (0.0, 1e-16, 2e15, float("inf")))
+def test_range_in_passes_with_radii_that_settle_nothing(T, radius):
+    """Squared radii out of the range in which the filter tells who passes for certain; tables made here, the centroids' and others."""
+    import torch
+    ix, q, probes = built(T, 5000, 1536, 192, 8, 12, 260, 6, 0.3, 0.0, 3)
+    q[:200] = ix.base[torch.randperm(5000, device="cuda")[:200]]
+    lut = T.trim_build_lut(q, ix.codebooks)
+    lut[4:90] *= 0.75
+    for table in (None, lut):
+        want = single_range(T, ix, q, radius, 0.7, probes, None, table)
+        got = T.trim_search_range(ix, q, radius, 0.7, probes=probes, lut=table, want_mask=True)
+        for name in ("n_scanned", "n_exact", "mask", "offsets", "ids", "d2"):
+            np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
+
+
 def host_index(ix):
     """The same stored data for the oracle."""
     from oracle import trim_oracle, trim_oracle_fs
