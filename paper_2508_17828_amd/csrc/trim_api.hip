@@ -301,7 +301,7 @@ int zero_areas(const ZeroAreas &z, hipStream_t st) {
 }
 
 // Clusters per workgroup of the k-means update: as many as 32 (every workgroup reads all the
-// assignments), fewer until there are two workgroups per CU or one cluster is left, and never
+// assignments), fewer until there is a workgroup per CU or one cluster is left, and never
 // more than 48 KB of float64 sums.
 template <int ABYTES>
 int launch_kmeans_update(const float *x, int64_t ns, int d, int dim, const void *assign, int64_t astride, int64_t ystride, int K,
@@ -309,15 +309,18 @@ int launch_kmeans_update(const float *x, int64_t ns, int d, int dim, const void 
     const int cols = dim < kUpdCols ? dim : kUpdCols, nz = (dim + kUpdCols - 1) / kUpdCols;
     int lg = kUpdMaxLog2;
     while (lg > 0 && ((int64_t)((K + (1 << lg) - 1) >> lg) * ny * nz < 256 || ((size_t)cols << lg) * 8 > 48 * 1024)) --lg;
-    const size_t lds = kmeans_update_lds(lg, cols);
     UpdateArgs a{};
+    a.vals = (int32_t)std::min<int64_t>(kUpdVals, (ns * cols + 63) / 64 * 64);
+    const bool few = ns <= kUpdFew;
+    const size_t lds = kmeans_update_lds(lg, cols, few ? kUpdFew : kUpdList, a.vals);
     a.x = x; a.assign = assign; a.ns = ns; a.stride = d; a.astride = astride; a.ystride = ystride;
     a.dim = dim; a.K = K; a.cg_log2 = lg; a.groups = (K + (1 << lg) - 1) >> lg; a.ny = ny; a.cent = cent;
     const int64_t total = (int64_t)a.groups * ny * nz;
     if (total > 0x7fffffff - kXcds) return TRIM_UNSUPPORTED_SHAPE;
     a.total = (int32_t)total;
-    HIP_TRY(allow_lds(reinterpret_cast<const void *>(kmeans_update_kernel<ABYTES>), lds));
-    hipLaunchKernelGGL(kmeans_update_kernel<ABYTES>, dim3((unsigned)((total + kXcds - 1) / kXcds * kXcds)), dim3(kUpdThreads), lds,
+    void (*fn)(UpdateArgs) = few ? kmeans_update_kernel<ABYTES, kUpdFew> : kmeans_update_kernel<ABYTES, kUpdList>;
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), lds));
+    hipLaunchKernelGGL(fn, dim3((unsigned)((total + kXcds - 1) / kXcds * kXcds)), dim3(kUpdThreads), lds,
                        st, a);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;

@@ -299,26 +299,30 @@ __global__ void kmeans_init_kernel(const float *__restrict__ x, int64_t ns, int6
 // else from LDS, where all threads bring the rows found together.
 // (Sorting the assignments chunk by chunk ranked all of them in every workgroup.)  65,536 rows, 32 x 256 x 4 coordinates: 59 us
 // an iteration (134), 1024 x 128 coordinates: 38 .. 65 us by the largest cluster (72).  Bound by short steps one after
-// the other, one workgroup per CU; about half of it is bringing the rows: 16 bytes of every cache line.
+// the other, one workgroup per CU by its list and what sorting it holds in registers; about half of it is bringing the rows: 16 bytes of
+// every cache line.  Up to kUpdFew rows leave room for two per CU: 96 x 256 x 8 coordinates, 4 iterations of training, 300
+// rows 183 -> 129 us, 4000 258 -> 198, 8000 401 -> 327.
 constexpr int kUpdThreads = 512, kUpdRows = 16, kUpdChunk = kUpdThreads * kUpdRows;
 constexpr int kUpdMaxLog2 = 5;
-constexpr int kUpdList = 16384;  // rows found
+constexpr int kUpdList = 16384, kUpdFew = 8192;   // rows found (there is room for kUpdFew where there are no more at all)
 constexpr int kUpdVals = 8192, kUpdPiece = 2048;   // row values, rows in LDS at a time
 constexpr int kUpdCols = 256;    // coordinates per workgroup at most (grid: slices of that many)
-static_assert(kUpdList >= kUpdChunk, "a chunk's rows fit the list");
+static_assert(kUpdList >= kUpdChunk && kUpdFew <= kUpdChunk, "a chunk's rows fit the list");
 __host__ __device__ inline bool kmeans_update_direct(int cg_log2, int cols) { return (cols << cg_log2) >= 256; }
-__host__ __device__ inline size_t kmeans_update_lds(int cg_log2, int cols) {
-    return ((size_t)cols << cg_log2) * 8 + (size_t)kUpdList * 4 + (kmeans_update_direct(cg_log2, cols) ? 0 : (size_t)kUpdVals * 4 + kUpdPiece * 2) + (((size_t)kUpdThreads / kWave + 2) * 4 << cg_log2) + 16 + kUpdThreads / kWave * 4;
+// list, vals: how many rows, values there is room for
+inline size_t kmeans_update_lds(int cg_log2, int cols, int list, int vals) {
+    return ((size_t)cols << cg_log2) * 8 + (size_t)list * 4 + (kmeans_update_direct(cg_log2, cols) ? 0 : (size_t)vals * 4 + kUpdPiece * 2) + (((size_t)kUpdThreads / kWave + 2) * 4 << cg_log2) + 16 + kUpdThreads / kWave * 4;
 }
 struct UpdateArgs {
     const float *x;            // [ns][stride]
     const void *assign;
     int64_t ns, stride, astride, ystride;
     int32_t dim, K, cg_log2, groups, ny, total;     // total: workgroups that have work
+    int32_t vals;              // kUpdVals, or what fewer rows can fill
     float *cent;
 };
-template <int ABYTES>
-__global__ __launch_bounds__(kUpdThreads) void kmeans_update_kernel(const UpdateArgs a) {
+template <int ABYTES, int LIST>
+__global__ __launch_bounds__(kUpdThreads, LIST < kUpdList ? 4 : 1) void kmeans_update_kernel(const UpdateArgs a) {
     constexpr int kWaves = kUpdThreads / kWave;
     extern __shared__ __align__(16) unsigned char smem[];
     const int CG = 1 << a.cg_log2, dim = a.dim;
@@ -330,9 +334,9 @@ __global__ __launch_bounds__(kUpdThreads) void kmeans_update_kernel(const Update
     float *vals = reinterpret_cast<float *>(smem);                         // [rows][cols]
     // (the last slice of columns may be narrower than the others: the launch's layout is that of the first)
     const bool direct = kmeans_update_direct(a.cg_log2, dim < kUpdCols ? dim : kUpdCols);
-    double *sums = reinterpret_cast<double *>(vals + (direct ? 0 : kUpdVals));   // [CG][cols]
-    uint32_t *list = reinterpret_cast<uint32_t *>(sums + (size_t)CG * cols);     // [kUpdList] row << 5 | cluster, direct: then rows by cluster
-    int *wcount = reinterpret_cast<int *>(list + kUpdList);                // [kWaves][CG]
+    double *sums = reinterpret_cast<double *>(vals + (direct ? 0 : a.vals));     // [CG][cols]
+    uint32_t *list = reinterpret_cast<uint32_t *>(sums + (size_t)CG * cols);     // [LIST] row << 5 | cluster, direct: then rows by cluster
+    int *wcount = reinterpret_cast<int *>(list + LIST);                    // [kWaves][CG]
     int *rows_of = wcount + kWaves * CG;                                   // [CG] rows per cluster so far
     int *start = rows_of + CG;                                             // [CG + 1] runs of list[]
     int *part = start + CG + 4;                                            // [kWaves]
@@ -411,7 +415,7 @@ __global__ __launch_bounds__(kUpdThreads) void kmeans_update_kernel(const Update
     auto add_rows = [&]() {
         const float *xi = x + (size_t)row0 * a.stride;
         if (direct) {
-            sort_rows(0, found, std::integral_constant<int, kUpdList / kUpdThreads>(), [&](int, uint32_t m, int at) { list[at] = m >> 5; });
+            sort_rows(0, found, std::integral_constant<int, LIST / kUpdThreads>(), [&](int, uint32_t m, int at) { list[at] = m >> 5; });
             for (int e = tid; e < CG * cols; e += kUpdThreads) {
                 const int c = e / cols;
                 const float *xt = xi + (e - c * cols);
@@ -419,7 +423,7 @@ __global__ __launch_bounds__(kUpdThreads) void kmeans_update_kernel(const Update
                 const int end = start[c + 1];
                 if (i >= end) continue;
                 double sum = sums[e];
-                constexpr int kFly = 32;       // loads in flight
+                constexpr int kFly = LIST < kUpdList ? 16 : 32;       // loads in flight
                 for (; i < end; i += kFly) {
                     float v[kFly];
 #pragma unroll
@@ -435,7 +439,7 @@ __global__ __launch_bounds__(kUpdThreads) void kmeans_update_kernel(const Update
         }
         // Short rows: read in row order, so that workgroups of neighbouring subspaces, whose columns share cache lines, read a
         // line at about the same time, and that all clusters have something to add in a piece; stored in cluster order.
-        const int piece = kUpdVals / cols < kUpdPiece ? kUpdVals / cols : kUpdPiece;
+        const int piece = a.vals / cols < kUpdPiece ? a.vals / cols : kUpdPiece;
         for (int p0 = 0; p0 < found; p0 += piece) {
             const int p1 = p0 + piece < found ? p0 + piece : found;
             sort_rows(p0, p1, std::integral_constant<int, kUpdPiece / kUpdThreads>(), [&](int i, uint32_t, int at) { place[i - p0] = (uint16_t)at; });
@@ -502,7 +506,7 @@ __global__ __launch_bounds__(kUpdThreads) void kmeans_update_kernel(const Update
     const uint32_t pattern = (uint32_t)c_first * 0x01010101u, group_bits = (uint32_t)(0xff & ~(CG - 1)) * 0x01010101u;
     load_chunk(0);
     __syncthreads();
-    for (int64_t i0 = 0;; i0 += kUpdChunk) {      // (past the last chunk once more: no rows, the list is added)
+    for (int64_t i0 = 0; i0 < a.ns; i0 += kUpdChunk) {
         uint32_t w[kWords], in = 0;               // this lane's rows: assignments, and a bit for each of the group's
 #pragma unroll
         for (int i = 0; i < kWords; ++i) {
@@ -536,30 +540,34 @@ __global__ __launch_bounds__(kUpdThreads) void kmeans_update_kernel(const Update
             if ((lane & (kWaves - 1)) >= off) incl += v;
         }
         const int before = __builtin_amdgcn_readlane(incl - n, wave_id), all = __builtin_amdgcn_readlane(incl, kWaves - 1);
-        if (i0 >= a.ns || found + all > kUpdList || i0 - row0 > (int64_t(1) << 26)) {      // (a row takes 27 bits of an entry)
-            if (found > 0) add_rows();
-            if (i0 >= a.ns) break;
-            found = 0;
-            row0 = i0;
-        }
-        int to = found + before + lower;
-        const uint32_t r = (uint32_t)(i0 - row0) + tid * kUpdRows;
-        while (in) {
-            const int i = __ffs((int)in) - 1;
-            in &= in - 1;
-            uint32_t c = 0;
-            if constexpr (ABYTES == 1) {
-                const uint32_t v = i & 8 ? (i & 4 ? w[3] : w[2]) : (i & 4 ? w[1] : w[0]);
-                c = v >> (8 * (i & 3));
-            } else {
+        for (bool fits = false; !fits;) {         // (once; twice where the rows before these have to be added first)
+            fits = found + all <= LIST && i0 - row0 <= (int64_t(1) << 26);      // (a row takes 27 bits of an entry)
+            if (fits) {
+                int to = found + before + lower;
+                const uint32_t r = (uint32_t)(i0 - row0) + tid * kUpdRows;
+                while (in) {
+                    const int i = __ffs((int)in) - 1;
+                    in &= in - 1;
+                    uint32_t c = 0;
+                    if constexpr (ABYTES == 1) {
+                        const uint32_t v = i & 8 ? (i & 4 ? w[3] : w[2]) : (i & 4 ? w[1] : w[0]);
+                        c = v >> (8 * (i & 3));
+                    } else {
 #pragma unroll
-                for (int k = 0; k < kWords; ++k) c = k == i ? w[k] : c;
-                c -= (uint32_t)c_first;
+                        for (int k = 0; k < kWords; ++k) c = k == i ? w[k] : c;
+                        c -= (uint32_t)c_first;
+                    }
+                    list[to++] = (r + i) << 5 | (c & (uint32_t)(CG - 1));
+                }
+                found += all;
+                __syncthreads();
             }
-            list[to++] = (r + i) << 5 | (c & (uint32_t)(CG - 1));
+            if (!fits || i0 + kUpdChunk >= a.ns) {
+                if (found > 0) add_rows();
+                found = 0;
+                row0 = i0;
+            }
         }
-        found += all;
-        __syncthreads();
     }
     for (int e = tid; e < CG * cols; e += kUpdThreads) {
         const int c = e / cols;

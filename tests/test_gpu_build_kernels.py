@@ -46,6 +46,30 @@ def test_update_of_codebooks(T, oracle, ns, d, M, bits):
     np.testing.assert_array_equal(got.view(np.uint32), want.view(np.uint32))
 
 
+# long rows, which are added straight from memory: the instance for up to 8192 rows and the other one; a cluster whose rows do not fit the
+# list, so that it is filled again after it has been put in order
+@pytest.mark.parametrize("ns,d,nlist", [(8192, 1028, 5), (8193, 260, 9), (300, 1028, 40), (40001, 260, 3)])
+def test_update_of_coarse_centroids_of_long_rows(T, oracle, ns, d, nlist):
+    test_update_of_coarse_centroids(T, oracle, ns, d, nlist)
+
+
+@pytest.mark.parametrize("ns,M,bits", [(8192, 32, 8), (300, 32, 8), (20001, 32, 8), (8192, 64, 4), (20001, 64, 4)])
+def test_update_of_codebooks_of_long_subvectors(T, oracle, ns, M, bits):
+    import torch
+    from oracle import index_build
+    rng = np.random.default_rng(ns)
+    x = rng.standard_normal((ns, 8 * M if bits == 8 else 16 * M)).astype(np.float32)
+    x[: ns * 9 // 10] = x[0]                     # (18,000 rows in one cluster; the list holds 16,384)
+    x[: ns * 9 // 10, ::8] += np.arange(ns * 9 // 10, dtype=np.float32)[:, None] * np.float32(1e-6)
+    K = 256 if bits == 8 else 16
+    init = np.concatenate([[0], ns - 1 - np.arange(K - 1)]).astype(np.int32) if ns > K else np.arange(K, dtype=np.int32)
+    fn = T.trim_train_pq if bits == 8 else T.trim_fs_train_pq
+    ref = index_build.train_pq_fixed if bits == 8 else index_build.train_pq_fs_fixed
+    want = ref(x, M, 2, init)
+    got = fn(torch.from_numpy(x).cuda(), M, 2, torch.from_numpy(init).cuda()).cpu().numpy()
+    np.testing.assert_array_equal(got.view(np.uint32), want.view(np.uint32))
+
+
 # every sub-vector length with the matrix-core filter and one without; rows around the workgroup's 128
 # and 256 vectors; unaligned rows; ties, all-zero centroids, magnitudes outside the filter's range
 @pytest.mark.parametrize("dsub,M,n", [(4, 4, 1), (4, 8, 129), (5, 4, 255), (6, 4, 700), (8, 8, 1000), (7, 4, 300),
