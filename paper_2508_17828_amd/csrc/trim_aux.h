@@ -167,43 +167,43 @@ __global__ __launch_bounds__(512) void lds_gather_wide_kernel(int iters, uint32_
 // the list's codes, then one wave per subspace writes the set codes in ascending order.
 // A thread takes four code bytes at a time, neighbouring threads neighbouring ones, and sets a bit only where it is not set yet: a
 // list holds some twenty codes per subspace, so that nearly always it is.  The longest list decides (lists of twenty
-// times the mean length are usual): 1024 threads, 16 looks at the bitmap under way together.
-// 1,000,000 x 32 in 1024 lists: 102 -> 39 us.
+// times the mean length are usual): 1024 threads, 16 looks at the bitmap under way together; 256 for many short lists (see
+// trim_pack_list_bounds).  1,000,000 x 32 in 1024 lists: 102 -> 39 us.
 constexpr int kBoundsPitch = 9;      // words per subspace, one of them spare (bank spread)
-constexpr int kBoundsThreads = 1024;
-__global__ __launch_bounds__(kBoundsThreads) void list_bounds_kernel(const uint8_t *__restrict__ codes,
+template <int T>
+__global__ __launch_bounds__(T) void list_bounds_kernel(const uint8_t *__restrict__ codes,
                                                           const float *__restrict__ dlx, int64_t n,
                                                           int M, const int64_t *__restrict__ list_offsets,
                                                           uint8_t *__restrict__ out) {
     extern __shared__ __align__(16) unsigned char smem[];
     uint32_t *bits = reinterpret_cast<uint32_t *>(smem);  // [M][kBoundsPitch]
-    __shared__ float red[kBoundsThreads / kWave];
+    __shared__ float red[T / kWave];
     const int l = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     uint8_t *rec = out + (size_t)l * list_record_bytes(M);
-    for (int i = tid; i < M * kBoundsPitch; i += kBoundsThreads) bits[i] = 0;
+    for (int i = tid; i < M * kBoundsPitch; i += T) bits[i] = 0;
     int64_t lo = list_offsets[l], hi = list_offsets[l + 1];
     lo = lo < 0 ? 0 : (lo > n ? n : lo);
     hi = hi < lo ? lo : (hi > n ? n : hi);
     float bmax = 0.0f;
-    for (int64_t x = lo + tid; x < hi; x += kBoundsThreads) bmax = fmaxf(bmax, dlx[x]);
+    for (int64_t x = lo + tid; x < hi; x += T) bmax = fmaxf(bmax, dlx[x]);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) bmax = fmaxf(bmax, __shfl_xor(bmax, off));
     if (lane == 0) red[tid >> 6] = bmax;
     __syncthreads();
     if (tid == 0) {
-        for (int w = 1; w < kBoundsThreads / kWave; ++w) bmax = fmaxf(bmax, red[w]);
+        for (int w = 1; w < T / kWave; ++w) bmax = fmaxf(bmax, red[w]);
         *reinterpret_cast<float *>(rec + list_record_bmax_offset(M)) = bmax;
     }
     const uint32_t *words = reinterpret_cast<const uint32_t *>(codes + (size_t)lo * M);     // (M % 4 == 0, the codes are aligned)
     const int per = M / 4;
     const int64_t all = (hi - lo) * per;
     constexpr int kFly = 4;
-    for (int64_t e = tid; e < all; e += kFly * kBoundsThreads) {
+    for (int64_t e = tid; e < all; e += kFly * T) {
         uint32_t w[kFly], have[4 * kFly];
         int j[kFly];
 #pragma unroll
         for (int u = 0; u < kFly; ++u) {
-            const int64_t at = e + u * kBoundsThreads < all ? e + u * kBoundsThreads : e;
+            const int64_t at = e + u * T < all ? e + u * T : e;
             w[u] = words[at];
             j[u] = 4 * (int)(at % per);
         }
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(kBoundsThreads) void list_bounds_kernel(const uint8
         }
     }
     __syncthreads();
-    for (int j = tid >> 6; j < M; j += kBoundsThreads >> 6) {   // one wave per subspace
+    for (int j = tid >> 6; j < M; j += T >> 6) {   // one wave per subspace
         const uint32_t nib = (bits[j * kBoundsPitch + (lane >> 3)] >> ((lane & 7) * 4)) & 15u;  // codes 4*lane..4*lane+3
         const int cnt = __popc(nib);
         int incl = cnt;                                  // inclusive prefix over the lanes

@@ -389,3 +389,29 @@ def test_training_rows_that_are_no_numbers(T, oracle, ns):
     # (one iteration: the oracle's lists take what is no number to the first, and stay there once its centroid is none)
     np.testing.assert_array_equal(T.trim_train_ivf(g(x), 70, 1, g(init[:70].copy())).cpu().numpy(),
                                   index_build.train_ivf_fixed(x, 70, 1, init[:70]))
+
+
+# many short lists and a few long ones (the instances with 256 and with 1024 threads a list); empty lists, one of all the codes
+@pytest.mark.parametrize("n,M,nlist", ((3000, 32, 700), (3000, 192, 500), (5000, 4, 90), (3000, 32, 16), (9000, 192, 30), (1, 8, 5)))
+def test_list_summaries(T, n, M, nlist):
+    import torch
+    rng = np.random.default_rng(n + M)
+    cuts = np.sort(rng.integers(0, n + 1, nlist - 1))
+    cuts[: nlist // 3] = cuts[nlist // 3]                # one long list, empty ones behind it
+    lo = np.concatenate([[0], np.sort(cuts), [n]]).astype(np.int64)
+    codes = rng.integers(0, 60, (n, M)).astype(np.uint8) * rng.integers(1, 5, M).astype(np.uint8)
+    codes[lo[-2]:, 1] = rng.integers(0, 256, n - lo[-2])
+    dlx = rng.random(n).astype(np.float32)
+    cuda = lambda a: torch.from_numpy(a).cuda()
+    ix = T.Index(torch.zeros((n, 4 * M), device="cuda"), cuda(codes), cuda(dlx), torch.zeros((M, 256, 4), device="cuda"), list_offsets=cuda(lo))
+    rec = T.trim_pack_list_bounds(ix).cpu().numpy().reshape(nlist, -1)
+    for l in range(nlist):
+        own, r = codes[lo[l]:lo[l + 1]], rec[l]
+        assert r[(M * 65 + 3) // 4 * 4:][:4].view(np.float32)[0] == (dlx[lo[l]:lo[l + 1]].max() if len(own) else 0)
+        for j in range(M):
+            want, count = np.unique(own[:, j]), r[M * 64 + j]
+            if 0 < len(want) <= 64:
+                assert count == len(want)
+                np.testing.assert_array_equal(r[j * 64:(j + 1) * 64], np.pad(want, (0, 64 - len(want)), constant_values=want[0]))
+            else:
+                assert count == (255 if len(want) else 0) and not r[j * 64:(j + 1) * 64].any()
