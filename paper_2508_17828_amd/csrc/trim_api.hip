@@ -1621,14 +1621,16 @@ int trim_ivf_probe(const float *queries, int64_t nq, int32_t d, const float *cen
         void (*assign)(const float *, int64_t, int, const float *, int, int32_t *) = assign_mfma_kernel;
         if (d <= kAsrCols) assign = d <= kAsrCols / 2 ? assign_rows_kernel<4> : assign_rows_kernel<8>;
         else HIP_TRY(allow_lds(reinterpret_cast<const void *>(assign_mfma_kernel), lds1));
-        HIP_TRY(allow_lds(reinterpret_cast<const void *>(assign_fix_kernel), lds2));
+        int span = kFixSpan;
+        while (span > 64 && nq / span < 512) span >>= 1;     // (two workgroups per CU, where there are so many vectors)
+        const int64_t blocks = (nq + span - 1) / span;
+        const bool one = d <= kAsrCols || blocks < 400;      // (see assign_fix_kernel)
+        void (*fix)(const float *, int64_t, int, const float *, int, int, int32_t *) = one ? assign_fix_kernel<1024> : assign_fix_kernel<512>;
+        HIP_TRY(allow_lds(reinterpret_cast<const void *>(fix), lds2));
         hipLaunchKernelGGL(assign, dim3((unsigned)((nq + kAsgTile - 1) / kAsgTile)), dim3(kAsgThreads), d <= kAsrCols ? 0 : lds1, st,
                            queries, nq, d, centroids, nlist, probes_out);
         HIP_TRY(hipGetLastError());
-        int span = kFixSpan;
-        while (span > 64 && nq / span < 512) span >>= 1;     // (two workgroups per CU, where there are so many vectors)
-        hipLaunchKernelGGL(assign_fix_kernel, dim3((unsigned)((nq + span - 1) / span)), dim3(kFixThreads), lds2, st,
-                           queries, nq, d, centroids, nlist, span, probes_out);
+        hipLaunchKernelGGL(fix, dim3((unsigned)blocks), dim3(one ? 1024 : 512), lds2, st, queries, nq, d, centroids, nlist, span, probes_out);
         HIP_TRY(hipGetLastError());
         return TRIM_OK;
     }

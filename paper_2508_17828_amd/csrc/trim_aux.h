@@ -1984,7 +1984,8 @@ __global__ __launch_bounds__(512) void ivf_probe_kernel(const float *__restrict_
 // Margin: twice E = (2^-16 + (3 d + 16) 2^-24) 2 |x||c|max     split, binary32 accumulation
 //                 + d 2^-24 |c|max^2 + d 2^-24 |x|^2             the norms
 //                 + (d / 32 + 8) 2^-24 (|x| + |c|max)^2          the exact rule's own roundings
-// 1,000,000 x 128 against 1024 lists: 1.33 ms with the marked vectors (9.3 ms measured exactly).  Rows of up to 128 values: assign_rows_kernel.
+// 1,000,000 x 128 against 1024 lists: 1.33 ms with the marked vectors (9.3 ms measured exactly).  Rows of up to 128 values:
+// assign_rows_kernel.  Longer ones, with the marked: 500,000 x 256 1.16 ms, x 384 1.63, 170,000 x 768 1.45.
 constexpr int kAsgThreads = 512, kAsgTile = 256, kAsgSlice = 32, kAsgMaxD = 4096;
 inline size_t assign_lds(int d) { return (size_t)2 * 4 * 4 * kAsgTile * 16 + (size_t)((d + kAsgSlice - 1) / kAsgSlice * kAsgSlice) * 4 + 2 * kAsgTile * 4 + 64; }
 
@@ -2528,11 +2529,17 @@ __global__ __launch_bounds__(kAsgThreads, 2) void assign_rows_kernel(const float
     if (tid < kAsgTile && x0 + tid < n && s_best[tid] != ~0ull) out[x0 + tid] = (int32_t)(s_best[tid] & 0xffffffffu);
 }
 
-// The vectors that assign_mfma_kernel marked: every centroid measured by the exact rule, eight
+// The vectors that assign_rows_kernel or assign_mfma_kernel marked: every centroid measured by the exact rule, eight
 // vectors at a time (ivf_probe_kernel's distance loop).  A workgroup looks after up to kFixSpan
 // vectors, so that even a mark in a hundred fills its groups.
-constexpr int kFixSpan = 1024, kFixThreads = 1024;   // (at most kFixSpan)
-__global__ __launch_bounds__(kFixThreads) void assign_fix_kernel(const float *__restrict__ xs, int64_t n, int d,
+// T: 1024 threads where there is at most a workgroup per CU and where few are marked (rows of up to 128 values), else 512 (us, 1024 / 512
+// threads: 16,384 x 768 36 / 45, x 1536 126 / 163, 8000 x 768, all marked, 2415 / 3189, whole assignments of 200,000 x 128 171 / 174, x 32
+// 114 / 129; 30,000 x 384 37 / 35, 500,000 x 384 172 / 154, 50,000 x 384, all marked, 1365 / 1270).  Norms over four decades mark three
+// quarters of 200,000 x 128 by assign_rows_kernel's one binary16 product (1745 us, 1875 in all), half by assign_mfma_kernel's three
+// of split values (1350, 1614).
+constexpr int kFixSpan = 1024;
+template <int T>
+__global__ __launch_bounds__(T) void assign_fix_kernel(const float *__restrict__ xs, int64_t n, int d,
                                                                  const float *__restrict__ cent, int nlist,
                                                                  int span, int32_t *__restrict__ out) {
     constexpr int QT = 8, kRows = 4, NP = QT * kRows;
@@ -2545,20 +2552,20 @@ __global__ __launch_bounds__(kFixThreads) void assign_fix_kernel(const float *__
     const int64_t x0 = (int64_t)blockIdx.x * span;
     if (tid == 0) count = 0;
     __syncthreads();
-    for (int i = tid; i < span; i += kFixThreads)
+    for (int i = tid; i < span; i += T)
         if (x0 + i < n && out[x0 + i] < 0) todo[atomicAdd(&count, 1)] = i;
     __syncthreads();
     const int total = count, ng = d >> 2;
     for (int g0 = 0; g0 < total; g0 += QT) {
         const int nqt = total - g0 < QT ? total - g0 : QT;
         if (tid < QT) best[tid] = ~0ull;
-        for (int t = tid; t < QT * d; t += kFixThreads) {
+        for (int t = tid; t < QT * d; t += T) {
             const int qi = t / d;
             q_lds[t] = xs[(size_t)(x0 + todo[g0 + (qi < nqt ? qi : 0)]) * d + (t - qi * d)];
         }
         __syncthreads();
         unsigned long long mine = ~0ull;
-        constexpr int kStep = (kFixThreads >> 5) * kRows;
+        constexpr int kStep = (T >> 5) * kRows;
         const int g1 = lane32 < ng ? lane32 : 0;         // the first group of the next rows is on its way while these are measured
         float4 x[kRows], next[kRows];
         auto load = [&](int l0, int g, float4 (&to)[kRows]) {

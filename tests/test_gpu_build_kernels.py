@@ -229,6 +229,23 @@ def test_nearest_list_with_centroids_that_are_no_numbers():
         assert torch.equal(many, few)
 
 
+@pytest.mark.parametrize("d", (36, 128, 132, 516))
+@pytest.mark.parametrize("nq", (25_500, 25_700))
+def test_nearest_list_of_vectors_that_the_scores_leave_open(nq, d):
+    """A workgroup per CU for these, and more than that; all vectors (a centroid is no number), and some of each workgroup's."""
+    import torch
+    from paper_2508_17828_amd import trim as T
+    g = torch.Generator(device="cuda").manual_seed(d)
+    x, cent = torch.randn((nq, d), device="cuda", generator=g), torch.randn((77, d), device="cuda", generator=g)
+    cent[60:70] = cent[59]
+    x[::37] = cent[63]
+    x[::101] *= 1e5
+    for bad in (0.0, float("nan")):
+        cent[5, 3] = bad
+        few = torch.cat([T.trim_ivf_probe(x[i:i + 4000].contiguous(), cent, 1) for i in range(0, nq, 4000)])
+        assert torch.equal(T.trim_ivf_probe(x, cent, 1), few)
+
+
 @pytest.mark.parametrize("nq", (1, 3, 20))
 def test_probe_of_few_queries_with_values_that_are_no_numbers(nq):
     """The two kernels for few queries and the one for many put NaN and infinite distances in the same places."""
