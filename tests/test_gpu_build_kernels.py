@@ -159,7 +159,8 @@ def test_gamma_rank(T, S, Q, d, M, p):
 @pytest.mark.parametrize("S,Q,d,M,p,kind", [
     (32, 256, 16, 4, 0.9, ""), (33, 1001, 100, 20, 0.7, ""), (1, 16384, 128, 16, 0.99, ""), (700, 300, 392, 56, 0.5, ""),
     (40, 5000, 128, 32, 0.0, ""), (5, 5000, 36, 12, 1.0, "same"), (4099, 16300, 4, 4, 0.8, ""), (65, 2000, 64, 16, 0.9, "odd"),
-    (65, 3000, 64, 16, 0.3, "tiny"), (65, 3000, 64, 16, 0.3, "huge"), (65, 3000, 64, 16, 0.6, "landmarks")])
+    (65, 3000, 64, 16, 0.3, "tiny"), (65, 3000, 64, 16, 0.3, "huge"), (65, 3000, 64, 16, 0.6, "landmarks"),
+    (300, 3000, 64, 16, 0.6, "all landmarks"), (65, 3000, 64, 16, 0.6, "spread")])
 def test_gamma_with_work_space(T, S, Q, d, M, p, kind):
     import ctypes
     import torch
@@ -176,7 +177,12 @@ def test_gamma_with_work_space(T, S, Q, d, M, p, kind):
     if kind in ("tiny", "huge"):
         scale = 1e-18 if kind == "tiny" else 1e16
         base, q, cb = base * scale, q * scale, cb * scale
+    if kind == "spread":                     # queries' lengths over four decades, sampled rows out of range
+        q *= torch.logspace(0, 4, Q, device="cuda")[:, None]
+        rows[:2] = torch.tensor([-5, 10**6], device="cuda")
     codes, dlx = T.trim_encode(base, cb)
+    if kind == "all landmarks":
+        base = torch.stack([cb[j][codes[:, j].long()] for j in range(M)], 1).reshape(-1, d).contiguous()
     if kind == "landmarks":                  # vectors, and queries, at a landmark
         land = torch.stack([cb[j][codes[:, j].long()] for j in range(M)], 1).reshape(-1, d)
         base[rows[:20].long()] = land[rows[:20].long()]
