@@ -3,7 +3,7 @@
 // gamma_x is ONE value of the Q that a sampled vector x has, the one of a given rank.  gamma_kernel (trim_aux.h) computes
 // all of them and is bound by the vector ALU; here
 //
-//   operands   landmarks l, differences u = x - l and queries as 16-bit operands (relative to the mean of a few sampled vectors,
+//   operands   landmarks l, differences u = x - l and queries as 16-bit operands (relative to the mean of a few queries,
 //              scaled row by row by a power of two), with their lengths and what rounding moved
 //   bins       q.l and q.u by v_mfma_f32_32x32x16_f16, and from them, per pair, two bins of 1 - cos(u, q - l) (2048
 //              bins over [0, 2]): the value lies in neither a lower nor a higher one.  16 bits per pair.
@@ -14,7 +14,7 @@
 // so that the result is gamma_kernel's bit for bit.  1000 vectors x 10,000 queries x 128: 67 us (258 with gamma_kernel): operands 13,
 // bins 22, rank 36, all of them latency; 100 x 1000 x 384: 33 us (34); 1000 x 10,000 x 768: 308 (837), the
 // values around the rank.  4096 bins leave fewer of those and cost more in the counting (76 us, 75 -> 81 for 1667 x 768).  Queries' lengths over four
-// decades: 70 us (256; relative to a mean of queries 304, the far ones' low bits being everybody's).  Vectors at their landmarks have one value
+// decades: 70 us (256; 304 where the mean is not kept within the vectors' range).  Vectors at their landmarks have one value
 // with all queries, known without them: 108 us (229; evaluated 482).  What cannot be told apart at all is evaluated, a vector
 // at a time where gamma_kernel takes two: 10,000 equal queries 486 us (228).
 //
@@ -63,20 +63,22 @@ __global__ __launch_bounds__(256) void gamma_operands_kernel(const GammaRankArgs
     const bool vec = (int)blockIdx.x < vector_groups;
     const int row = (vec ? blockIdx.x : blockIdx.x - vector_groups) * kGrRows + (tid >> 5);
     if (blockIdx.x == 0 && a.s0 == 0 && tid == 0) *a.g.gamma_bits = 0x7f800000u;      // +inf: the minimum comes later
-    // (not of queries: one far away would cost all the others their low bits)
-    __shared__ int64_t s_at[16];
-    if (tid < 16) {
-        const int64_t at = a.g.rows[(int64_t)tid * a.g.S >> 4];
-        s_at[tid] = at < 0 ? 0 : (at >= a.g.n ? a.g.n - 1 : at);
-    }
-    __syncthreads();
     for (int t = tid; t < a.dpad; t += 256) {
-        float v[16], sum = 0.0f;
+        // (within the range of a few stored vectors: a query far away would cost all of them their low bits)
+        float v[8], x[8], sum = 0.0f, least = __builtin_inff(), most = -__builtin_inff();
+        const int k = t < d ? t : 0;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = a.g.base[(size_t)s_at[i] * d + (t < d ? t : 0)];
+        for (int i = 0; i < 8; ++i) v[i] = a.g.queries[(size_t)((int64_t)i * a.g.Q >> 3) * d + k];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) sum += __builtin_fabsf(v[i]) < 1e18f ? v[i] : 0.0f;
-        s_mu[t] = t < d ? sum * (1.0f / 16.0f) : 0.0f;
+        for (int i = 0; i < 8; ++i) x[i] = a.g.base[(size_t)(i * a.g.n >> 3) * d + k];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) { least = __builtin_fminf(least, x[i]); most = __builtin_fmaxf(most, x[i]); }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float c = __builtin_fminf(__builtin_fmaxf(v[i], least), most);
+            sum += __builtin_fabsf(c) < 1e18f ? c : 0.0f;
+        }
+        s_mu[t] = t < d ? sum * 0.125f : 0.0f;
     }
     __syncthreads();
     const int dsub = d / a.g.M;
