@@ -365,6 +365,28 @@ def test_probe_of_many_queries_far_from_all_lists(nq, nlist, d, nprobe, far):
     assert torch.equal(got, want)
 
 
+def test_probe_of_many_queries_captured_and_replayed():
+    """One graph, other queries on every replay: none, some and all of them far from all lists."""
+    import torch
+    from paper_2508_17828_amd import trim as T
+    nq, nlist, d, nprobe = 3000, 1024, 64, 16
+    g = torch.Generator(device="cuda").manual_seed(5)
+    cent = torch.rand((nlist, d), device="cuda", generator=g) * 255
+    q = torch.rand((nq, d), device="cuda", generator=g) * 255
+    assert T.lib().trim_ivf_probe_workspace_bytes(nq, d, nlist, nprobe) > 4 * nq * nlist
+    T.trim_ivf_probe(q, cent, nprobe)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = T.trim_ivf_probe(q, cent, nprobe)
+    for far in (0, 7, nq, 1, 0):
+        new = torch.rand((nq, d), device="cuda", generator=g) * 255
+        new[torch.randperm(nq, device="cuda", generator=g)[:far]] += 2e5
+        q.copy_(new)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, T.trim_ivf_probe(new, cent, nprobe))
+
+
 @pytest.mark.parametrize("n", (40, 3000, 200_000))
 @pytest.mark.parametrize("dsub,M", ((4, 8), (5, 8), (6, 8), (8, 8), (7, 4), (12, 4)))
 def test_encode_values_that_are_no_numbers(T, oracle, dsub, M, n):

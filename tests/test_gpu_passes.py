@@ -600,6 +600,33 @@ def test_hardly_any_candidates(T, n, nlist):
                 np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
 
 
+# As many lists as are counted in the LDS, and more: one to several vectors each, empty ones, lists named twice and lists that are none.
+@pytest.mark.parametrize("nlist", (16384, 16385, 30000))
+def test_thousands_of_lists(T, nlist):
+    import torch
+    n, d, M, nq, nprobe, k, batch, gamma = 40000, 512, 64, 300, 1700, 10, 64, 0.4
+    g = torch.Generator(device="cuda").manual_seed(nlist)
+    base, q = torch.randn((n, d), device="cuda", generator=g), torch.randn((nq, d), device="cuda", generator=g)
+    cb = torch.randn((M, 256, d // M), device="cuda", generator=g)
+    codes, dlx = T.trim_encode(base, cb)
+    offsets = torch.cat([torch.zeros(1, device="cuda", dtype=torch.int64), torch.randint(0, n, (nlist - 1,), device="cuda", generator=g).sort().values,
+                         torch.full((1,), n, device="cuda", dtype=torch.int64)])
+    probes = torch.randint(-3, nlist + 3, (nq, nprobe), device="cuda", generator=g).to(torch.int32)
+    probes[:, :40] = nlist - 1 - torch.arange(40, device="cuda", dtype=torch.int32)        # (everybody's)
+    ix = T.Index(base, codes, dlx, cb, list_offsets=offsets, max_list_len=int((offsets[1:] - offsets[:-1]).max()))
+    order = torch.randperm(nq, device="cuda", generator=g).to(torch.int32)
+    assert T.trim_knn_workspace_bytes(ix, nq, k, batch, probes) > 0 and T.trim_range_scratch_bytes(ix, nq, probes) > 0
+    want = single_kernel(T, ix, q, k, gamma, batch, probes, order)
+    got = T.trim_search_knn(ix, q, k, gamma, batch, probes=probes, query_order=order, want_mask=True)
+    for name in ("ids", "d2", "n_scanned", "n_exact", "mask"):
+        np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
+    want = single_range(T, ix, q, 29.0, gamma, probes, order, None)
+    got = T.trim_search_range(ix, q, 29.0, gamma, probes=probes, query_order=order, want_mask=True)
+    assert 0 < want["ids"].shape[0] < want["n_scanned"].sum()
+    for name in ("offsets", "ids", "d2", "n_scanned", "n_exact", "mask"):
+        np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
+
+
 # A query with more candidates than max_candidates is cut there: inside a list, at its end, before the first batch ends.
 @pytest.mark.parametrize("nq", (300, 20))
 @pytest.mark.parametrize("cut", (5, 31, 500, 513, 2000, 2048))
