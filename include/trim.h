@@ -361,7 +361,8 @@ int trim_search_range(const trim_index_view *index, const float *queries, int64_
  * The same search (Section 4.2; same results, masks and counters) with scratch memory beside the
  * workspace: many queries over long vectors are then searched in passes (see trim_search_knn_ws).
  * trim_range_scratch_bytes: the bytes such a search wants, or 0 where trim_search_range is the better way.
- * (The 16-bit queries and their probe lists, about 2 d + 8 nprobe bytes a query, and up to 2 GiB of distance tables.)
+ * (The 16-bit queries and their probe lists, about 2 d + 16 nprobe bytes a query, a bit per (query, candidate) pair, and up to 2 GiB of
+ * distance tables.)
  * scratch: device, 256-byte aligned, contents on entry ignored; NULL or fewer bytes: exactly trim_search_range.
  *
  * trim_range_collect: the CSR arrays of a search that has been counted.  After a call of

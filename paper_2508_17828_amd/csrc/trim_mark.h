@@ -183,7 +183,10 @@ __device__ __forceinline__ int list_of_task(const int32_t *start, int nlist, int
 // 437.  Taken out of copies one at a time, the gathers' bank conflicts cost 8 % of what is left, staging 5 to 8, the norms 4, barriers
 // 10; half the products are 76 us of the last: the products themselves, at the clock they leave, and a tile's ends (18,000
 // of 60,000 clocks at 24 slices: finding it, its queries' lines, marking) are most of it.  Six buffers and a barrier
-// every two slices: 416, 571, 442.
+// every two slices: 416, 571, 442.  Those are sub-vectors of 8 values; 2,000 x 200,000 x 768 with sub-vectors of 4: 190 -> 182, of 16:
+// 179 -> 156, 4-bit codes: 188 -> 174 (range searches, with the certain bits and without: 220 / 186, 192 / 174, 194 / 185, for a finish
+// pass of 149 / 477, 26 / 105, 63 / 322).  What instances spill (2 to 18 registers, most with sub-vectors of 4) they spill outside of the loop
+// over slices, whose assembly has no scratch instruction.
 template <int PAD, bool FS, int AL, bool CERTAIN>
 __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs a) {
     typedef _Float16 h8 __attribute__((ext_vector_type(8)));
