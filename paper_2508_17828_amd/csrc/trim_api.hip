@@ -311,13 +311,15 @@ int launch_kmeans_update(const float *x, int64_t ns, int d, int dim, const void 
     while (lg > 0 && ((int64_t)((K + (1 << lg) - 1) >> lg) * ny * nz < 256 || ((size_t)cols << lg) * 8 > 48 * 1024)) --lg;
     UpdateArgs a{};
     a.vals = (int32_t)std::min<int64_t>(kUpdVals, (ns * cols + 63) / 64 * 64);
-    const bool few = ns <= kUpdFew;
-    const size_t lds = kmeans_update_lds(lg, cols, few ? kUpdFew : kUpdList, a.vals);
     a.x = x; a.assign = assign; a.ns = ns; a.stride = d; a.astride = astride; a.ystride = ystride;
     a.dim = dim; a.K = K; a.cg_log2 = lg; a.groups = (K + (1 << lg) - 1) >> lg; a.ny = ny; a.cent = cent;
     const int64_t total = (int64_t)a.groups * ny * nz;
     if (total > 0x7fffffff - kXcds) return TRIM_UNSUPPORTED_SHAPE;
     a.total = (int32_t)total;
+    // (no more workgroups than CUs: room beside them is none's, and the other instance has more loads in flight: 8192 x 128, 64 x 16 x 2
+    // coordinates, 4 iterations: 361 us, 388 with the few)
+    const bool few = ns <= kUpdFew && total > 256;
+    const size_t lds = kmeans_update_lds(lg, cols, few ? kUpdFew : kUpdList, a.vals);
     void (*fn)(UpdateArgs) = few ? kmeans_update_kernel<ABYTES, kUpdFew> : kmeans_update_kernel<ABYTES, kUpdList>;
     HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), lds));
     hipLaunchKernelGGL(fn, dim3((unsigned)((total + kXcds - 1) / kXcds * kXcds)), dim3(kUpdThreads), lds,
@@ -1624,7 +1626,7 @@ int trim_ivf_probe(const float *queries, int64_t nq, int32_t d, const float *cen
         int span = kFixSpan;
         while (span > 64 && nq / span < 512) span >>= 1;     // (two workgroups per CU, where there are so many vectors)
         const int64_t blocks = (nq + span - 1) / span;
-        const bool one = d <= kAsrCols || blocks < 400;      // (see assign_fix_kernel)
+        const bool one = d <= kAsrCols || d > 1024 || blocks < 400;      // (see assign_fix_kernel)
         void (*fix)(const float *, int64_t, int, const float *, int, int, int32_t *) = one ? assign_fix_kernel<1024> : assign_fix_kernel<512>;
         HIP_TRY(allow_lds(reinterpret_cast<const void *>(fix), lds2));
         hipLaunchKernelGGL(assign, dim3((unsigned)((nq + kAsgTile - 1) / kAsgTile)), dim3(kAsgThreads), d <= kAsrCols ? 0 : lds1, st,

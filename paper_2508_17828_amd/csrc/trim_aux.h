@@ -2532,7 +2532,8 @@ __global__ __launch_bounds__(kAsgThreads, 2) void assign_rows_kernel(const float
 // The vectors that assign_rows_kernel or assign_mfma_kernel marked: every centroid measured by the exact rule, eight
 // vectors at a time (ivf_probe_kernel's distance loop).  A workgroup looks after up to kFixSpan
 // vectors, so that even a mark in a hundred fills its groups.
-// T: 1024 threads where there is at most a workgroup per CU and where few are marked (rows of up to 128 values), else 512 (us, 1024 / 512
+// T: 1024 threads where there is at most a workgroup per CU, where few are marked (rows of up to 128 values) and for rows of more than 1024
+// (whole assignments, 40,000 x 1536 in 200 lists: 324 / 337 us), else 512 (us, 1024 / 512
 // threads: 16,384 x 768 36 / 45, x 1536 126 / 163, 8000 x 768, all marked, 2415 / 3189, whole assignments of 200,000 x 128 171 / 174, x 32
 // 114 / 129; 30,000 x 384 37 / 35, 500,000 x 384 172 / 154, 50,000 x 384, all marked, 1365 / 1270).  Norms over four decades mark three
 // quarters of 200,000 x 128 by assign_rows_kernel's one binary16 product (1745 us, 1875 in all), half by assign_mfma_kernel's three

@@ -260,7 +260,9 @@ __global__ __launch_bounds__(kWave) void probe_nearest_kernel(const ProbeArgs a)
 }
 
 // The queries with more candidates than nearest takes: all lists measured, 32 lists by eight of these queries a workgroup and turn, the
-// distances kept where the scores were; then a wave each selects as probe_select_kernel does.  Both end with the list of them.
+// distances kept where the scores were; then a wave each selects as probe_select_kernel does.  Both end with the list of them.  (One launch,
+// the workgroup with the last turn of eight queries selecting: 0.3 us less where there are none, but its fences: 548 us in place of 91 for
+// 3000 x 1024 x 128, all far.)
 constexpr int kPrbRestGrid = 1024;
 // How many there are; s_first: the lists' first numbers.  By the first wave and all threads that read it; ends with a barrier.
 __device__ __forceinline__ int rest_count(const ProbeArgs &a, uint32_t *s_first) {
