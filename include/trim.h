@@ -158,6 +158,11 @@ int trim_fs_build_lut(const float *queries, int64_t nq, int32_t d, const float *
                       float *lut_out, void *stream);
 int trim_fs_train_pq(const float *train, int64_t ns, int32_t d, int32_t M, int32_t iters,
                      const int32_t *init_rows, float *codebooks_out, uint8_t *assign_ws, void *stream);
+/* trim_fs_train_pq_ws: see trim_train_pq_ws. */
+size_t trim_fs_train_pq_workspace_bytes(int64_t ns, int32_t d, int32_t M);
+int trim_fs_train_pq_ws(const float *train, int64_t ns, int32_t d, int32_t M, int32_t iters,
+                        const int32_t *init_rows, float *codebooks_out, uint8_t *assign_ws,
+                        void *workspace, size_t workspace_bytes, void *stream);
 
 /*
  * Preprocessing step 1 of Section 3.3: codes_out[x][j] = index of the centroid of subspace j
@@ -188,6 +193,17 @@ int trim_train_pq(const float *train, int64_t ns, int32_t d, int32_t M, int32_t 
                   void *stream);
 int trim_train_ivf(const float *train, int64_t ns, int32_t d, int32_t nlist, int32_t iters,
                    const int32_t *init_rows, float *centroids_out, int32_t *assign_ws, void *stream);
+/* trim_train_pq_ws, trim_train_ivf_ws: the same centroids, codes, distances and assignments with a workspace of
+ * trim_train_*_workspace_bytes, device, contents on entry ignored; with it the rows are put in
+ * the order of their clusters once an iteration.  0 bytes, NULL or less than that: trim_train_pq, trim_train_ivf. */
+size_t trim_train_pq_workspace_bytes(int64_t ns, int32_t d, int32_t M);
+int trim_train_pq_ws(const float *train, int64_t ns, int32_t d, int32_t M, int32_t iters,
+                     const int32_t *init_rows, float *codebooks_out, uint8_t *codes_ws, float *dlx_ws,
+                     void *workspace, size_t workspace_bytes, void *stream);
+size_t trim_train_ivf_workspace_bytes(int64_t ns, int32_t d, int32_t nlist);
+int trim_train_ivf_ws(const float *train, int64_t ns, int32_t d, int32_t nlist, int32_t iters,
+                      const int32_t *init_rows, float *centroids_out, int32_t *assign_ws,
+                      void *workspace, size_t workspace_bytes, void *stream);
 
 /*
  * Relaxation parameter from a confidence level (Section 3.2, the sampling route for queries

@@ -14,6 +14,7 @@
 #include "trim_gamma.h"
 #include "trim_probe.h"
 #include "trim_launch.h"
+#include "trim_update.h"
 
 // Scratch area of trim_search_range_static (see below): device memory inside the library's code
 // object; every GPU the library runs on holds its own copy at its own address.
@@ -326,6 +327,87 @@ int launch_kmeans_update(const float *x, int64_t ns, int d, int dim, const void 
                        st, a);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
+}
+
+// Work space of the update step (trim_update.h): the clusters' first places, the rows' numbers in cluster order, and (short rows) the
+// sub-vectors clustering by clustering.
+struct UpdateLayout {
+    bool brief;                   // short rows
+    int loops, threads, rows, nchunk;
+    size_t off_list, off_columns, total;      // total: 0 where the update goes without
+};
+UpdateLayout update_layout(int64_t ns, int dim, int K, int ny) {
+    UpdateLayout L{};
+    if (ns <= 0 || dim <= 0 || K <= 0 || ny <= 0 || ny > 65535 || ns > 0x7fffffff - 65536) return L;
+    // Few rows, or few to a cluster: kmeans_update_kernel, one launch instead of two (4 iterations of training, us, without / with:
+    // codebooks, 300 x 128 76 / 90, 4096 x 128 98 / 106, 8192 x 128 109 / 118, 8192 x 1024 430 / 409, 65,536 x 128 513 / 418, 16 centroids:
+    // 16,384 x 512 1186 / 1223, 65,536 x 128 1080 / 1014; coarse lists, 8000 x 768 in 4096 5214 / 5354, 4096 x 128 in 64 168 / 133).
+    if (ny > 1 ? ns <= 4096 || ny * ns < (1 << 19) || (K < kC && ns < 32768) : ns < 8 * (int64_t)K) return L;
+    L.brief = dim <= kShortRow;
+    // 4096 rows a chunk; 1024 where a workgroup has one clustering's assignments only, and there are few chunks
+    L.loops = ny > 1 || ns > 256 * kSortThreads ? 4 : 1;
+    for (L.threads = kSortThreads; kmeans_sort_lds(L.threads, K) > (size_t)kSortCounters; L.threads >>= 1)
+        if (L.threads == kWave) return L;
+    if (L.threads < kSortThreads) L.loops = 4;
+    L.rows = L.loops * L.threads;
+    L.nchunk = (int)((ns + L.rows - 1) / L.rows);
+    if ((int64_t)K * ny * ((dim + kUpdCols - 1) / kUpdCols) > 0x7fffffff - kXcds) return L;
+    L.off_list = ((size_t)ny * L.nchunk * (K + 1) * 2 + 255) & ~size_t(255);
+    L.off_columns = (L.off_list + (size_t)ny * ns * 2 + 255) & ~size_t(255);
+    L.total = L.off_columns + (L.brief && ny > 1 ? (size_t)ny * ns * dim * 4 : 0);
+    return L;
+}
+// What is laid out once per training.
+int kmeans_columns(const float *x, int64_t ns, int d, int dim, int ny, const UpdateLayout &L, unsigned char *ws, hipStream_t st) {
+    if (!ws || !L.brief || ny == 1 || !aligned16(x)) return TRIM_OK;
+    hipLaunchKernelGGL(kmeans_columns_kernel, dim3((unsigned)((ns + kWave - 1) / kWave)), dim3(256), 0, st, x, ns, (int64_t)d, dim, ny,
+                       reinterpret_cast<float *>(ws + L.off_columns));
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+template <int ABYTES>
+int launch_kmeans_sorted(const float *x, int64_t ns, int d, int dim, const void *assign, int64_t astride, int64_t ystride, int K, int ny,
+                         float *cent, const UpdateLayout &L, unsigned char *ws, hipStream_t st) {
+    SortArgs a{};
+    a.x = x; a.assign = assign; a.ns = ns; a.stride = d; a.astride = astride; a.ystride = ystride;
+    a.xstep = dim;
+    if (L.brief && ny > 1 && aligned16(x)) { a.x = reinterpret_cast<const float *>(ws + L.off_columns); a.stride = dim; a.xstep = ns * dim; }
+    a.dim = dim; a.K = K; a.ny = ny; a.nchunk = L.nchunk; a.rows = L.rows; a.cent = cent;
+    while ((1 << a.kbits) < K) ++a.kbits;
+    a.starts = reinterpret_cast<uint16_t *>(ws);
+    a.list = reinterpret_cast<uint16_t *>(ws + L.off_list);
+    void (*sort)(SortArgs) = L.loops == 4 ? kmeans_sort_kernel<ABYTES, 4> : kmeans_sort_kernel<ABYTES, 1>;
+    const size_t lds = kmeans_sort_lds(L.threads, K);
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(sort), lds));
+    hipLaunchKernelGGL(sort, dim3((unsigned)L.nchunk, (unsigned)ny), dim3(L.threads), lds, st, a);
+    HIP_TRY(hipGetLastError());
+    if (L.brief) {
+        // clusters per workgroup: as many as there are threads to add for, fewer until there is a workgroup per CU
+        a.cg_log2 = kSumMaxLog2;
+        while (a.cg_log2 > 0 && ((dim << a.cg_log2) > kSumThreads || (int64_t)((K + (1 << a.cg_log2) - 1) >> a.cg_log2) * ny < 512)) --a.cg_log2;
+        const int64_t groups = (int64_t)((K + (1 << a.cg_log2) - 1) >> a.cg_log2) * ny;
+        const bool vec = dim % 4 == 0 && (a.stride | a.xstep) % 4 == 0 && aligned16(a.x);
+        void (*sums)(SortArgs) = vec ? (dim == 4 ? kmeans_sums_kernel<4, true> : dim == 8 ? kmeans_sums_kernel<8, true> : kmeans_sums_kernel<0, true>)
+                                     : dim == 2 ? kmeans_sums_kernel<2, false> : kmeans_sums_kernel<0, false>;
+        hipLaunchKernelGGL(sums, dim3((unsigned)((groups + kXcds - 1) / kXcds * kXcds)), dim3(kSumThreads), 0, st, a);
+    } else {
+        const int nz = (dim + kUpdCols - 1) / kUpdCols, cols = dim < kUpdCols ? dim : kUpdCols;
+        hipLaunchKernelGGL(kmeans_rows_kernel, dim3((unsigned)(K * nz), (unsigned)ny), dim3(cols <= 64 ? 64 : cols <= 128 ? 128 : kUpdCols), 0, st, a);
+    }
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+// The update with a work space (null: without) that update_layout's size was asked for.
+template <int ABYTES>
+int kmeans_update(const float *x, int64_t ns, int d, int dim, const void *assign, int64_t astride, int64_t ystride, int K, int ny,
+                  float *cent, unsigned char *ws, hipStream_t st) {
+    if (ws) return launch_kmeans_sorted<ABYTES>(x, ns, d, dim, assign, astride, ystride, K, ny, cent, update_layout(ns, dim, K, ny), ws, st);
+    return launch_kmeans_update<ABYTES>(x, ns, d, dim, assign, astride, ystride, K, ny, cent, st);
+}
+// A caller's work space from its first multiple of 256 on, or null where it is too small for that.
+unsigned char *update_space(void *ws, size_t bytes, size_t need) {
+    if (!ws || need == 0 || bytes < need + 256) return nullptr;
+    return reinterpret_cast<unsigned char *>((reinterpret_cast<uintptr_t>(ws) + 255) & ~uintptr_t(255));
 }
 
 // Encoding with the matrix-core filter: 256 vectors per workgroup, 128 where 256 would leave fewer
@@ -1255,34 +1337,61 @@ int trim_pack_scan_head(const uint8_t *codes, const float *dlx, int64_t n, int32
 int trim_train_pq(const float *train, int64_t ns, int32_t d, int32_t M, int32_t iters,
                   const int32_t *init_rows, float *codebooks_out, uint8_t *codes_ws, float *dlx_ws,
                   void *stream) {
+    return trim_train_pq_ws(train, ns, d, M, iters, init_rows, codebooks_out, codes_ws, dlx_ws, nullptr, 0, stream);
+}
+
+size_t trim_train_pq_workspace_bytes(int64_t ns, int32_t d, int32_t M) {
+    if (ns <= 0 || d <= 0 || M <= 0 || d % M) return 0;
+    const UpdateLayout L = update_layout(ns, d / M, kC, M);
+    return L.total > 0 ? L.total + 256 : 0;
+}
+
+int trim_train_pq_ws(const float *train, int64_t ns, int32_t d, int32_t M, int32_t iters,
+                     const int32_t *init_rows, float *codebooks_out, uint8_t *codes_ws, float *dlx_ws,
+                     void *workspace, size_t workspace_bytes, void *stream) {
     if (ns <= 0 || d <= 0 || M <= 0 || iters < 0) return TRIM_INVALID_ARG;
     if (d % M || M % 4 || M > 65535) return TRIM_UNSUPPORTED_SHAPE;
     if (!train || !init_rows || !codebooks_out || !codes_ws || !dlx_ws) return TRIM_INVALID_ARG;
     const int dsub = d / M;
     if (iters > 0 && (size_t)kC * dsub * 4 > 64 * 1024) return TRIM_UNSUPPORTED_SHAPE;
     if (iters > 0 && (reinterpret_cast<uintptr_t>(codes_ws) & 3u)) return TRIM_INVALID_ARG;
+    const UpdateLayout L = update_layout(ns, dsub, kC, M);
+    unsigned char *ws = update_space(workspace, workspace_bytes, L.total);
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int per = kC * dsub;  // centroid coordinates per subspace
     hipLaunchKernelGGL(kmeans_init_kernel, dim3((per + 255) / 256, M), dim3(256), 0, st, train, ns, (int64_t)d, dsub,
                        init_rows, kC, codebooks_out);
     HIP_TRY(hipGetLastError());
+    if (const int rc = iters > 0 ? kmeans_columns(train, ns, d, dsub, M, L, ws, st) : TRIM_OK) return rc;
     for (int it = 0; it < iters; ++it) {
         // The codes and landmark distances that the caller sees are the last iteration's; before that the codes are laid out for
         // the update, subspace by subspace (a workgroup reads 64 KB of 2 MB; row by row every one brings all of it in).
         const bool last = it + 1 == iters;
         int rc = encode_codes(train, ns, d, codebooks_out, M, codes_ws, last ? 0 : ns, last ? dlx_ws : nullptr, st);
         if (rc) return rc;
-        if ((rc = launch_kmeans_update<1>(train, ns, d, dsub, codes_ws, last ? M : 1, last ? 1 : ns, kC, M, codebooks_out, st))) return rc;
+        if ((rc = kmeans_update<1>(train, ns, d, dsub, codes_ws, last ? M : 1, last ? 1 : ns, kC, M, codebooks_out, ws, st))) return rc;
     }
     return TRIM_OK;
 }
 
 int trim_train_ivf(const float *train, int64_t ns, int32_t d, int32_t nlist, int32_t iters,
                    const int32_t *init_rows, float *centroids_out, int32_t *assign_ws, void *stream) {
+    return trim_train_ivf_ws(train, ns, d, nlist, iters, init_rows, centroids_out, assign_ws, nullptr, 0, stream);
+}
+
+size_t trim_train_ivf_workspace_bytes(int64_t ns, int32_t d, int32_t nlist) {
+    const UpdateLayout L = update_layout(ns, d, nlist, 1);
+    return L.total > 0 ? L.total + 256 : 0;
+}
+
+int trim_train_ivf_ws(const float *train, int64_t ns, int32_t d, int32_t nlist, int32_t iters,
+                      const int32_t *init_rows, float *centroids_out, int32_t *assign_ws, void *workspace, size_t workspace_bytes,
+                      void *stream) {
     if (ns <= 0 || d <= 0 || nlist <= 0 || iters < 0) return TRIM_INVALID_ARG;
     if (d % 4) return TRIM_UNSUPPORTED_SHAPE;
     if (!train || !init_rows || !centroids_out || !assign_ws) return TRIM_INVALID_ARG;
     if ((int64_t)nlist * d > 0x7fffffff) return TRIM_UNSUPPORTED_SHAPE;
+    unsigned char *ws = update_space(workspace, workspace_bytes, update_layout(ns, d, nlist, 1).total);
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int per = nlist * d;
     hipLaunchKernelGGL(kmeans_init_kernel, dim3((per + 255) / 256), dim3(256), 0, st, train, ns, (int64_t)d, d, init_rows,
@@ -1291,7 +1400,7 @@ int trim_train_ivf(const float *train, int64_t ns, int32_t d, int32_t nlist, int
     for (int it = 0; it < iters; ++it) {
         int rc = trim_ivf_probe(train, ns, d, centroids_out, nlist, 1, assign_ws, stream);
         if (rc) return rc;
-        if ((rc = launch_kmeans_update<4>(train, ns, d, d, assign_ws, 1, 0, nlist, 1, centroids_out, st))) return rc;
+        if ((rc = kmeans_update<4>(train, ns, d, d, assign_ws, 1, 0, nlist, 1, centroids_out, ws, st))) return rc;
     }
     return TRIM_OK;
 }
@@ -1405,20 +1514,35 @@ int trim_fs_encode(const float *base, int64_t n, int32_t d, const float *codeboo
 
 int trim_fs_train_pq(const float *train, int64_t ns, int32_t d, int32_t M, int32_t iters,
                      const int32_t *init_rows, float *codebooks_out, uint8_t *assign_ws, void *stream) {
+    return trim_fs_train_pq_ws(train, ns, d, M, iters, init_rows, codebooks_out, assign_ws, nullptr, 0, stream);
+}
+
+size_t trim_fs_train_pq_workspace_bytes(int64_t ns, int32_t d, int32_t M) {
+    if (ns <= 0 || d <= 0 || M <= 0 || d % M) return 0;
+    const UpdateLayout L = update_layout(ns, d / M, kC4, M);
+    return L.total > 0 ? L.total + 256 : 0;
+}
+
+int trim_fs_train_pq_ws(const float *train, int64_t ns, int32_t d, int32_t M, int32_t iters,
+                        const int32_t *init_rows, float *codebooks_out, uint8_t *assign_ws, void *workspace, size_t workspace_bytes,
+                        void *stream) {
     if (ns <= 0 || d <= 0 || M <= 0 || iters < 0) return TRIM_INVALID_ARG;
     if (d % M || M % 2 || M > 65535) return TRIM_UNSUPPORTED_SHAPE;
     if (!train || !init_rows || !codebooks_out || !assign_ws) return TRIM_INVALID_ARG;
     const int dsub = d / M;
     if ((size_t)2 * kC4 * dsub * 4 > 64 * 1024) return TRIM_UNSUPPORTED_SHAPE;
+    const UpdateLayout L = update_layout(ns, dsub, kC4, M);
+    unsigned char *ws = update_space(workspace, workspace_bytes, L.total);
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int per = kC4 * dsub;  // centroid coordinates per subspace
     hipLaunchKernelGGL(kmeans_init_kernel, dim3((per + 255) / 256, M), dim3(256), 0, st, train, ns, (int64_t)d, dsub,
                        init_rows, kC4, codebooks_out);
     HIP_TRY(hipGetLastError());
+    if (const int rc = iters > 0 ? kmeans_columns(train, ns, d, dsub, M, L, ws, st) : TRIM_OK) return rc;
     for (int it = 0; it < iters; ++it) {
         const bool last = it + 1 == iters;      // (see trim_train_pq)
         if (const int rc = launch_encode_fs<false>(train, ns, d, codebooks_out, M, assign_ws, last ? 0 : ns, nullptr, st)) return rc;
-        if (const int rc = launch_kmeans_update<1>(train, ns, d, dsub, assign_ws, last ? M : 1, last ? 1 : ns, kC4, M, codebooks_out, st))
+        if (const int rc = kmeans_update<1>(train, ns, d, dsub, assign_ws, last ? M : 1, last ? 1 : ns, kC4, M, codebooks_out, ws, st))
             return rc;
     }
     return TRIM_OK;

@@ -21,7 +21,8 @@ TRIM_MAX_BATCH = 4096
 TRIM_MAX_NPROBE = 4096
 
 EXPORTS = ("trim_shape_supported", "trim_fs_shape_supported", "trim_fs_encode", "trim_fs_build_lut",
-           "trim_fs_train_pq", "trim_train_pq", "trim_train_ivf", "trim_estimate_gamma", "trim_estimate_gamma_ws", "trim_estimate_gamma_workspace_bytes", "trim_estimate_gamma_normal", "trim_encode", "trim_pack_scan_head", "trim_codes_tiled_bytes", "trim_pack_codes_tiled",
+           "trim_fs_train_pq", "trim_fs_train_pq_ws", "trim_fs_train_pq_workspace_bytes", "trim_train_pq", "trim_train_pq_ws",
+           "trim_train_pq_workspace_bytes", "trim_train_ivf", "trim_train_ivf_ws", "trim_train_ivf_workspace_bytes", "trim_estimate_gamma", "trim_estimate_gamma_ws", "trim_estimate_gamma_workspace_bytes", "trim_estimate_gamma_normal", "trim_encode", "trim_pack_scan_head", "trim_codes_tiled_bytes", "trim_pack_codes_tiled",
            "trim_build_lut", "trim_search_knn", "trim_search_knn_ws", "trim_knn_workspace_bytes",
            "trim_search_range", "trim_search_range_static", "trim_search_range_ws", "trim_range_scratch_bytes", "trim_range_collect", "trim_static_scratch_bytes", "trim_range_workspace_bytes", "trim_ivf_probe", "trim_ivf_probe_ws",
            "trim_ivf_probe_workspace_bytes", "trim_query_order",
@@ -97,6 +98,10 @@ def lib() -> C.CDLL:
                                     C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]
         L.trim_train_ivf.argtypes = [C.c_void_p, C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.c_void_p,
                                      C.c_void_p, C.c_void_p, C.c_void_p]
+        for name in ("trim_train_pq", "trim_fs_train_pq", "trim_train_ivf"):
+            getattr(L, name + "_ws").argtypes = getattr(L, name).argtypes[:-1] + [C.c_void_p, C.c_size_t, C.c_void_p]
+            getattr(L, name + "_workspace_bytes").restype = C.c_size_t
+            getattr(L, name + "_workspace_bytes").argtypes = [C.c_int64, C.c_int32, C.c_int32]
         L.trim_estimate_gamma.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_int32, C.c_float,
                                           C.c_void_p, C.c_void_p, C.c_void_p]
         L.trim_estimate_gamma_ws.argtypes = L.trim_estimate_gamma.argtypes[:-1] + [C.c_void_p, C.c_size_t, C.c_void_p]
@@ -281,10 +286,12 @@ def trim_fs_train_pq(train: torch.Tensor, M: int, iters: int, init_rows: torch.T
                         f"{init_rows.numel()} rows")
     codebooks = torch.empty((M, 16, d // M), dtype=torch.float32, device=train.device)
     assign = torch.empty((ns, M), dtype=torch.uint8, device=train.device)
-    _check(lib().trim_fs_train_pq(_ptr(train, torch.float32, "train"), ns, d, M, iters,
-                                  _ptr(init_rows, torch.int32, "init_rows"),
-                                  _ptr(codebooks, torch.float32, "codebooks"),
-                                  _ptr(assign, torch.uint8, "assign_ws"), _stream()), "trim_fs_train_pq")
+    ws, need = _scratch(lib().trim_fs_train_pq_workspace_bytes(ns, d, M) if iters > 0 else 0, train.device)
+    _check(lib().trim_fs_train_pq_ws(_ptr(train, torch.float32, "train"), ns, d, M, iters,
+                                     _ptr(init_rows, torch.int32, "init_rows"),
+                                     _ptr(codebooks, torch.float32, "codebooks"),
+                                     _ptr(assign, torch.uint8, "assign_ws"), _ptr(ws, torch.uint8, "workspace"), need,
+                                     _stream()), "trim_fs_train_pq")
     return codebooks
 
 
@@ -296,10 +303,12 @@ def trim_train_pq(train: torch.Tensor, M: int, iters: int, init_rows: torch.Tens
     codebooks = torch.empty((M, 256, d // M), dtype=torch.float32, device=train.device)
     codes = torch.empty((ns, M), dtype=torch.uint8, device=train.device)
     dlx = torch.empty((ns,), dtype=torch.float32, device=train.device)
-    _check(lib().trim_train_pq(_ptr(train, torch.float32, "train"), ns, d, M, iters,
-                               _ptr(init_rows, torch.int32, "init_rows"),
-                               _ptr(codebooks, torch.float32, "codebooks"), _ptr(codes, torch.uint8, "codes_ws"),
-                               _ptr(dlx, torch.float32, "dlx_ws"), _stream()), "trim_train_pq")
+    ws, need = _scratch(lib().trim_train_pq_workspace_bytes(ns, d, M) if iters > 0 else 0, train.device)
+    _check(lib().trim_train_pq_ws(_ptr(train, torch.float32, "train"), ns, d, M, iters,
+                                  _ptr(init_rows, torch.int32, "init_rows"),
+                                  _ptr(codebooks, torch.float32, "codebooks"), _ptr(codes, torch.uint8, "codes_ws"),
+                                  _ptr(dlx, torch.float32, "dlx_ws"), _ptr(ws, torch.uint8, "workspace"), need,
+                                  _stream()), "trim_train_pq")
     return codebooks
 
 
@@ -309,10 +318,12 @@ def trim_train_ivf(train: torch.Tensor, nlist: int, iters: int, init_rows: torch
         raise TypeError(f"trim_train_ivf: need {nlist} initial rows, got {init_rows.numel()}")
     centroids = torch.empty((nlist, d), dtype=torch.float32, device=train.device)
     assign = torch.empty((ns,), dtype=torch.int32, device=train.device)
-    _check(lib().trim_train_ivf(_ptr(train, torch.float32, "train"), ns, d, nlist, iters,
-                                _ptr(init_rows, torch.int32, "init_rows"),
-                                _ptr(centroids, torch.float32, "centroids"),
-                                _ptr(assign, torch.int32, "assign_ws"), _stream()), "trim_train_ivf")
+    ws, need = _scratch(lib().trim_train_ivf_workspace_bytes(ns, d, nlist) if iters > 0 else 0, train.device)
+    _check(lib().trim_train_ivf_ws(_ptr(train, torch.float32, "train"), ns, d, nlist, iters,
+                                   _ptr(init_rows, torch.int32, "init_rows"),
+                                   _ptr(centroids, torch.float32, "centroids"),
+                                   _ptr(assign, torch.int32, "assign_ws"), _ptr(ws, torch.uint8, "workspace"), need,
+                                   _stream()), "trim_train_ivf")
     return centroids
 
 

@@ -53,6 +53,48 @@ def test_update_of_coarse_centroids_of_long_rows(T, oracle, ns, d, nlist):
     test_update_of_coarse_centroids(T, oracle, ns, d, nlist)
 
 
+# the update with work space: chunks of 4096 and 1024 rows that are full, one short and one over, more than 64 of them, rows of every
+# kind of sub-vector (four values at a time or one by one, in the LDS or straight from memory), fewer counters than 1024 threads
+# have room for, half of the rows in one cluster; and the same without it
+@pytest.mark.parametrize("ns,d,M,bits", [(32768, 64, 16, 8), (33001, 80, 16, 8), (36863, 128, 16, 8), (45057, 144, 12, 8), (131073, 8, 4, 8),
+                                         (26215, 340, 20, 8), (40001, 32, 16, 4), (270001, 16, 4, 8),
+                                         (1025, 12, 33, 0), (2047, 20, 100, 0), (3072, 24, 7, 0), (262145, 4, 50, 0), (40000, 4, 4990, 0), (70000, 300, 3, 0)])
+def test_update_with_work_space(T, oracle, ns, d, M, bits):
+    import ctypes as C
+    import torch
+    from oracle import index_build
+    L = T.lib()
+    size = L.trim_train_ivf_workspace_bytes if bits == 0 else L.trim_train_pq_workspace_bytes if bits == 8 else L.trim_fs_train_pq_workspace_bytes
+    need = size(ns, d, M)
+    assert need > 0
+    rng = np.random.default_rng(ns + d)
+    x = rng.standard_normal((ns, d)).astype(np.float32)
+    x[: ns // 2] = x[0]
+    K = M if bits == 0 else 256 if bits == 8 else 16
+    init = rng.choice(np.arange(ns // 2, ns), K, replace=False).astype(np.int32)
+    ref = index_build.train_ivf_fixed if bits == 0 else index_build.train_pq_fixed if bits == 8 else index_build.train_pq_fs_fixed
+    want = ref(x, M, 2, init)
+    g, gi = torch.from_numpy(x).cuda(), torch.from_numpy(init).cuda()
+    fn = T.trim_train_ivf if bits == 0 else T.trim_train_pq if bits == 8 else T.trim_fs_train_pq
+    np.testing.assert_array_equal(fn(g, M, 2, gi).cpu().numpy().view(np.uint32), want.view(np.uint32))
+    ws = torch.empty((need + 4,), dtype=torch.uint8, device="cuda")
+    p = lambda t: C.c_void_p(t.data_ptr())
+    stream = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    for shift, bytes_ in ((4, need), (0, need - 1)):                  # (the last: the kernel without)
+        ws.fill_(0xff)
+        out = torch.empty(want.shape, dtype=torch.float32, device="cuda")
+        codes, dlx = torch.empty((ns * max(M, 4),), dtype=torch.uint8, device="cuda"), torch.empty((ns,), device="cuda")
+        tail = [C.c_void_p(ws.data_ptr() + shift), bytes_, stream]
+        if bits == 0:
+            rc = L.trim_train_ivf_ws(p(g), ns, d, M, 2, p(gi), p(out), p(codes), *tail)
+        elif bits == 8:
+            rc = L.trim_train_pq_ws(p(g), ns, d, M, 2, p(gi), p(out), p(codes), p(dlx), *tail)
+        else:
+            rc = L.trim_fs_train_pq_ws(p(g), ns, d, M, 2, p(gi), p(out), p(codes), *tail)
+        assert rc == 0
+        np.testing.assert_array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
 @pytest.mark.parametrize("ns,M,bits", [(8192, 32, 8), (300, 32, 8), (20001, 32, 8), (8192, 64, 4), (20001, 64, 4)])
 def test_update_of_codebooks_of_long_subvectors(T, oracle, ns, M, bits):
     import torch
