@@ -2531,7 +2531,8 @@ __global__ __launch_bounds__(kAsgThreads, 2) void assign_rows_kernel(const float
 
 // The vectors that assign_rows_kernel or assign_mfma_kernel marked: every centroid measured by the exact rule, eight
 // vectors at a time (ivf_probe_kernel's distance loop).  A workgroup looks after up to kFixSpan
-// vectors, so that even a mark in a hundred fills its groups.
+// vectors, so that even a mark in a hundred fills its groups; the last one takes as many vectors' worth of work as it has, or nearly
+// (ten iterations of 65,536 x 128 against 1024, two or three marks a workgroup: 208 -> 110 us).
 // T: 1024 threads where there is at most a workgroup per CU, where few are marked (rows of up to 128 values) and for rows of more than 1024
 // (whole assignments, 40,000 x 1536 in 200 lists: 324 / 337 us), else 512 (us, 1024 / 512
 // threads: 16,384 x 768 36 / 45, x 1536 126 / 163, 8000 x 768, all marked, 2415 / 3189, whole assignments of 200,000 x 128 171 / 174, x 32
@@ -2543,13 +2544,13 @@ template <int T>
 __global__ __launch_bounds__(T) void assign_fix_kernel(const float *__restrict__ xs, int64_t n, int d,
                                                                  const float *__restrict__ cent, int nlist,
                                                                  int span, int32_t *__restrict__ out) {
-    constexpr int QT = 8, kRows = 4, NP = QT * kRows;
+    constexpr int QT = 8, kRows = 4;
     extern __shared__ __align__(16) unsigned char smem[];
     float *q_lds = reinterpret_cast<float *>(smem);                      // [QT][d]
     __shared__ int todo[kFixSpan];
     __shared__ int count;
     __shared__ unsigned long long best[QT];
-    const int tid = threadIdx.x, lane32 = tid & 31;
+    const int tid = threadIdx.x;
     const int64_t x0 = (int64_t)blockIdx.x * span;
     if (tid == 0) count = 0;
     __syncthreads();
@@ -2565,44 +2566,53 @@ __global__ __launch_bounds__(T) void assign_fix_kernel(const float *__restrict__
             q_lds[t] = xs[(size_t)(x0 + todo[g0 + (qi < nqt ? qi : 0)]) * d + (t - qi * d)];
         }
         __syncthreads();
-        unsigned long long mine = ~0ull;
-        constexpr int kStep = (T >> 5) * kRows;
-        const int g1 = lane32 < ng ? lane32 : 0;         // the first group of the next rows is on its way while these are measured
-        float4 x[kRows], next[kRows];
-        auto load = [&](int l0, int g, float4 (&to)[kRows]) {
+        auto measure = [&](auto wide) {              // against so many vectors
+            int tid = threadIdx.x;                   // (opaque: addresses are made anew, not kept for the other widths as well)
+            asm volatile("" : "+v"(tid));
+            const int lane32 = tid & 31;
+            constexpr int Q = decltype(wide)::value, NP = Q * kRows, kShift = NP == 32 ? 0 : NP == 16 ? 1 : 2;
+            unsigned long long mine = ~0ull;
+            constexpr int kStep = (T >> 5) * kRows;
+            const int g1 = lane32 < ng ? lane32 : 0;         // the first group of the next rows is on its way while these are measured
+            float4 x[kRows], next[kRows];
+            auto load = [&](int l0, int g, float4 (&to)[kRows]) {
 #pragma unroll
-            for (int r = 0; r < kRows; ++r) to[r] = reinterpret_cast<const float4 *>(cent)[(size_t)(l0 + r < nlist ? l0 + r : nlist - 1) * ng + g];
-        };
-        load((tid >> 5) * kRows, g1, next);
-        for (int l0 = (tid >> 5) * kRows; l0 < nlist; l0 += kStep) {
-            float acc[NP];
+                for (int r = 0; r < kRows; ++r) to[r] = reinterpret_cast<const float4 *>(cent)[(size_t)(l0 + r < nlist ? l0 + r : nlist - 1) * ng + g];
+            };
+            load((tid >> 5) * kRows, g1, next);
+            for (int l0 = (tid >> 5) * kRows; l0 < nlist; l0 += kStep) {
+                float acc[NP];
 #pragma unroll
-            for (int i = 0; i < NP; ++i) acc[i] = 0.0f;
+                for (int i = 0; i < NP; ++i) acc[i] = 0.0f;
 #pragma unroll
-            for (int r = 0; r < kRows; ++r) x[r] = next[r];
-            load(l0 + kStep, g1, next);
-            for (int g = lane32; g < ng; g += 32) {
-                if (g != lane32) load(l0, g, x);
+                for (int r = 0; r < kRows; ++r) x[r] = next[r];
+                load(l0 + kStep, g1, next);
+                for (int g = lane32; g < ng; g += 32) {
+                    if (g != lane32) load(l0, g, x);
 #pragma unroll
-                for (int qi = 0; qi < QT; ++qi) {
-                    const float4 qv = *reinterpret_cast<const float4 *>(q_lds + qi * d + 4 * g);
+                    for (int qi = 0; qi < Q; ++qi) {
+                        const float4 qv = *reinterpret_cast<const float4 *>(q_lds + qi * d + 4 * g);
 #pragma unroll
-                    for (int r = 0; r < kRows; ++r) {
-                        float e, a0 = acc[r * QT + qi];
-                        e = qv.x - x[r].x; a0 = __builtin_fmaf(e, e, a0);
-                        e = qv.y - x[r].y; a0 = __builtin_fmaf(e, e, a0);
-                        e = qv.z - x[r].z; a0 = __builtin_fmaf(e, e, a0);
-                        e = qv.w - x[r].w; a0 = __builtin_fmaf(e, e, a0);
-                        acc[r * QT + qi] = a0;
+                        for (int r = 0; r < kRows; ++r) {
+                            float e, a0 = acc[r * Q + qi];
+                            e = qv.x - x[r].x; a0 = __builtin_fmaf(e, e, a0);
+                            e = qv.y - x[r].y; a0 = __builtin_fmaf(e, e, a0);
+                            e = qv.z - x[r].z; a0 = __builtin_fmaf(e, e, a0);
+                            e = qv.w - x[r].w; a0 = __builtin_fmaf(e, e, a0);
+                            acc[r * Q + qi] = a0;
+                        }
                     }
                 }
+                const float dist = reduce_pairs<NP>(acc, lane32);
+                const int l = l0 + (lane32 >> kShift) / Q;
+                const unsigned long long key = ((unsigned long long)__float_as_uint(dist) << 32) | (uint32_t)l;
+                if (l < nlist && key < mine) mine = key;
             }
-            const float dist = reduce_pairs<NP>(acc, lane32);   // lane: row (bits 3..4), vector (bits 0..2)
-            const int l = l0 + (lane32 >> 3);
-            const unsigned long long key = ((unsigned long long)__float_as_uint(dist) << 32) | (uint32_t)l;
-            if (l < nlist && key < mine) mine = key;
-        }
-        atomicMin(&best[lane32 & 7], mine);
+            atomicMin(&best[(lane32 >> kShift) % Q], mine);
+        };
+        if (nqt <= 2) measure(std::integral_constant<int, 2>());
+        else if (nqt <= 4) measure(std::integral_constant<int, 4>());
+        else measure(std::integral_constant<int, 8>());
         __syncthreads();
         if (tid < nqt) out[x0 + todo[g0 + tid]] = (int32_t)(best[tid] & 0xffffffffu);
         __syncthreads();

@@ -46,6 +46,23 @@ def test_update_of_codebooks(T, oracle, ns, d, M, bits):
     np.testing.assert_array_equal(got.view(np.uint32), want.view(np.uint32))
 
 
+# vectors whose nearest list the matrix cores leave open (many lists in one place): as many of a workgroup's together as the exact
+# rule has widths for, one fewer and one more
+@pytest.mark.parametrize("d", (64, 128, 132))
+@pytest.mark.parametrize("marked", (1, 2, 3, 4, 5, 8, 9, 11))
+def test_nearest_list_of_vectors_left_open(T, oracle, d, marked):
+    import torch
+    rng = np.random.default_rng(d + marked)
+    cent = rng.integers(-40, 41, (150, d)).astype(np.float32)
+    cent[30:90:2] = cent[31]
+    x = (cent[rng.integers(90, 150, 4100)] + rng.integers(-2, 3, (4100, d))).astype(np.float32)
+    at = np.concatenate([7 + np.arange(marked), [300]])
+    x[at] = cent[31] + rng.integers(-2, 3, (marked + 1, d)).astype(np.float32)
+    got = T.trim_ivf_probe(torch.from_numpy(x).cuda(), torch.from_numpy(cent).cuda(), 1).cpu().numpy()
+    np.testing.assert_array_equal(got[:400], oracle.ivf_probe(x[:400], cent, 1))
+    assert (got[at] == 30).all()
+
+
 # long rows, which are added straight from memory: the instance for up to 8192 rows and the other one; a cluster whose rows do not fit the
 # list, so that it is filled again after it has been put in order
 @pytest.mark.parametrize("ns,d,nlist", [(8192, 1028, 5), (8193, 260, 9), (300, 1028, 40), (40001, 260, 3)])
