@@ -410,29 +410,37 @@ unsigned char *update_space(void *ws, size_t bytes, size_t need) {
     return reinterpret_cast<unsigned char *>((reinterpret_cast<uintptr_t>(ws) + 255) & ~uintptr_t(255));
 }
 
-// Encoding with the matrix-core filter: 256 vectors per workgroup, 128 where 256 would leave fewer
-// than two workgroups per CU (a workgroup splits the centroids for its own vectors, so fewer of
-// them cost more).
+// Encoding with the matrix-core filter: T vectors per workgroup, 512 or 256 (which prepare a subspace's centroids twice as often).
+template <int D, int T>
+int launch_encode_t(const float *base, int64_t n, int d, const float *codebooks, int M, int jper, uint8_t *codes, int64_t across,
+                    float *dlx, hipStream_t st) {
+    void (*fn)(const float *, int64_t, int, const float *, int, int, uint8_t *, int64_t, float *) =
+        across ? encode_mfma_kernel<D, T, true> : encode_mfma_kernel<D, T, false>;
+    const size_t lds = sizeof(EncodeLds<D, T>);
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), lds));
+    hipLaunchKernelGGL(fn, dim3((unsigned)((n + T - 1) / T), (unsigned)((M + jper - 1) / jper)), dim3(T), lds, st, base, n, d,
+                       codebooks, M, jper, codes, across, dlx);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
 template <int D>
 int launch_encode(const float *base, int64_t n, int d, const float *codebooks, int M, uint8_t *codes, int64_t across, float *dlx,
                   hipStream_t st) {
-    const bool wide = n >= 512 * kEncThreads;
-    const int per = wide ? kEncThreads : kEncThreads / 2;
-    void (*fn)(const float *, int64_t, int, const float *, int, int, uint8_t *, int64_t, float *) =
-        across ? (wide ? encode_mfma_kernel<D, 2, true> : encode_mfma_kernel<D, 1, true>)
-               : (wide ? encode_mfma_kernel<D, 2, false> : encode_mfma_kernel<D, 1, false>);
-    const size_t lds = wide ? encode_lds<D, 2>() : encode_lds<D, 1>();
-    const int64_t blocks = (n + per - 1) / per;
-    // subspaces per workgroup: all, or fewer until there are about three workgroups per CU; four where nobody wants the landmark
-    // distances, which take a pass of their own then (training, 65,536 x 128: 57 us an iteration, 76 with two)
+    // Subspaces per workgroup: all, or fewer until there are enough workgroups: two thirds again as many as are resident, or more where
+    // nobody wants the landmark distances, which take a pass of their own then (us, whole / split: 49,152 x 128 80 / 58, 40,000 x 1536
+    // 733 / 515, 65,536 x 128 82 / 72, 60,000 x 1536 762 / 780; training, 65,536 x 128, four iterations 480 / 354).
+    const int64_t many = (n + 511) / 512, few = (n + 255) / 256;
     int jper = M;
-    if (blocks < (dlx ? 384 : 768)) {
-        const int64_t split = std::min<int64_t>(M / 4, ((dlx ? 768 : 1024) + blocks - 1) / blocks);
+    if (many <= (dlx ? 112 : 512)) {
+        const int64_t split = std::min<int64_t>(M / 4, ((dlx ? 768 : 1024) + many - 1) / many);
         jper = (int)((M / 4 + split - 1) / split) * 4;
     }
-    HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), lds));
-    hipLaunchKernelGGL(fn, dim3((unsigned)blocks, (unsigned)((M + jper - 1) / jper)), dim3(kEncThreads), lds, st, base, n, d,
-                       codebooks, M, jper, codes, across, dlx);
+    // 512 vectors a workgroup, unless few are there (us, 256 / 512: 4096 x 128 18 / 20, 16,384 x 128 27 / 26) or 256 share the CUs out better:
+    // a step with 256 costs 9/8 of one with 512 (160,000 x 128 115 / 125, 200,000 x 128 142 / 125, 1,000,000 x 128 599 / 547).
+    const bool wide = jper < M ? many * (M / jper) > 128 : 9 * ((few + 255) / 256) >= 16 * ((many + 255) / 256);
+    const int rc = wide ? launch_encode_t<D, 512>(base, n, d, codebooks, M, jper, codes, across, dlx, st)
+                        : launch_encode_t<D, 256>(base, n, d, codebooks, M, jper, codes, across, dlx, st);
+    if (rc) return rc;
     if (jper < M && dlx)
         hipLaunchKernelGGL(encode_dlx_kernel, dim3((unsigned)((n + kDlxRows - 1) / kDlxRows)), dim3(256), 0, st, base, n, d,
                            codebooks, M, D, codes, dlx);

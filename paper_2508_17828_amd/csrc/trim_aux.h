@@ -890,158 +890,186 @@ __global__ __launch_bounds__(256) void gamma_normal_kernel(const GammaNormalArgs
 // ---- PQ encode (Section 3.3, preprocessing step 1) ----
 // The nearest centroid by the fixed binary32 rule (encode distance, smallest index on ties).
 // Evaluating the rule for all 256 centroids is bound by the vector ALU (2 d/M operations and the
-// comparison each).  For the usual sub-vector lengths the matrix cores leave 16 centroids to it:
+// comparison each).  For the usual sub-vector lengths the matrix cores leave eight centroids to it:
 //
 //   filter   S(c) = |x|^2 + m + |c|^2 - 2 x.c for all 256 centroids, 32 vectors x 32 centroids per
 //            v_mfma_f32_32x32x16_f16.  x and c are taken relative to the mean of a few centroids
 //            (their difference is what counts, and the margin below grows with their lengths), scaled by a power of two and split into a
 //            binary16 value and a binary16 remainder (22 bits); the depth of the instruction
-//            holds the three products x_hi c_hi, x_lo c_hi, x_hi c_lo of every coordinate and |c|^2 in three pieces
-//            (3 d/M + 3 slots), so the split costs no extra instruction up to d/M = 4, one more
-//            up to 9.  |x|^2 + m (m: the margin below) makes every score positive, so that
-//            scores order like their bits (integer minimum of three: half an instruction a score).
-//   groups   a lane holds the scores of 16 consecutive centroids per instruction; only the group
-//            minima are kept.  Groups whose minimum is within the margin of the best are evaluated
-//            by the exact rule, 8 centroids by each of the two lanes that share a vector; usually one group.
+//            holds the three products x_hi c_hi, x_lo c_hi, x_hi c_lo of every coordinate, |c|^2 in three pieces, and
+//            |x|^2 + m (m: the margin below) as 2^15 times one or two binary16 values that are rounded up (3 d/M + 4 slots or
+//            one more), so the split costs no extra instruction up to d/M = 4, one more up to 9.  |x|^2 + m makes every score positive,
+//            so that scores order like their bits (integer minimum of three: half an instruction a score).
+//   groups   only the minima of eight consecutive centroids are kept.  Groups whose minimum is within the margin of the best are
+//            evaluated by the exact rule; usually one.
+//
+// A wave takes 64 vectors: a lane prepares one and evaluates its groups; the operands go to the two blocks of 32 that the instruction
+// takes, and the groups found come back, by exchanging half waves (v_permlane32_swap).  (A block of 32 at a time, both half waves
+// preparing the same vectors and 16 centroids a group: 0.75 ms instead of 0.55 for 1,000,000 x 128.)
 //
 // The margin is twice a bound of |S - exact distance|: dropped products and remainders 3 * 2^-22 of 2 |x||c|, the
-// 16 or 32 binary32 additions of an element (2^-23 each of the sum of magnitudes, at most
-// (|x| + |c|)^2), the exact rule's own roundings (d/M + 2) * 2^-24: below 2^-18 (2^-17 with
+// 16 or 32 binary32 additions of an element (2^-23 each of the sum of magnitudes, at most (1 + 2^-8) (|x| + |c|)^2), the exact rule's own
+// roundings (d/M + 2) * 2^-24: below 2^-18 (2^-17 with
 // two instructions) of (|x| + |c|max)^2, with what binary16 subnormals lose (both sides are
 // scaled so that |c|max is 2^12 .. 2^13) inside the same bound.  Vectors or centroids out of the scaled range get an infinite
 // margin: every group is then evaluated exactly.
 //
-// 1,000,000 x 128, d/M = 4: 0.65 ms (1.75 ms on the vector ALU alone); 83,333 x 1536, d/M = 8: 0.84 ms.
+// Bound by the vector ALU (per 64 vectors and subspace at d/M = 4: 128 operations for the minima, 64 for the groups, 60 for the
+// operands, 100 for a round of groups, of which there are one or two, 70 or 140 for the centroids).  1,000,000 x 128, d/M = 4: 0.55 ms
+// (1.75 without the matrix cores); 83,333 x 1536, d/M = 8: 0.77 ms, 333,333 x 384 0.48.
 // across: 0, or (ACROSS) the codes are stored subspace by subspace, that many bytes apart (what training's update reads best).
-// BLK: blocks of 32 vectors per wave (2; 1 where that leaves fewer than two workgroups per CU).
-// Where there are still fewer, grid.y workgroups take jper subspaces each of the same vectors and
+// T: vectors per workgroup.  512: one half of the waves prepares the centroids of the even subspaces, the other those of the odd ones, a
+// step ahead of the others: a barrier per subspace; 256: all waves prepare them, between two barriers.
+// With grid.y > 1 a workgroup takes jper subspaces of its vectors and
 // encode_dlx_kernel adds the landmark distances up afterwards (their order of summation crosses
-// all subspaces): 9,000 x 768: 0.056 + 0.044 ms (0.285 ms with one workgroup per 128 vectors).
-template <int D> constexpr int kEncSteps = (3 * D + 3 + 15) / 16;
-constexpr int kEncThreads = 256;
-template <int D, int BLK>
-constexpr size_t encode_lds() {
-    return (size_t)kEncSteps<D> * 2 * kC * 16 + (size_t)(kC / 8) * (8 * D + 4) * 4 + (size_t)(kEncThreads / 2) * BLK * (4 * D + 4) * 4 + 16;
-}
-template <int D, int BLK, bool ACROSS>
-__global__ __launch_bounds__(kEncThreads) void encode_mfma_kernel(const float *__restrict__ base, int64_t n, int d,
-                                                                  const float *__restrict__ codebooks, int M, int jper,
-                                                                  uint8_t *__restrict__ codes, int64_t across,
-                                                                  float *__restrict__ dlx) {
+// all subspaces).
+template <int D> constexpr int kEncBias = D <= 4 ? 1 : 2;               // slots of |x|^2 + m
+template <int D> constexpr int kEncSteps = (3 * D + 3 + kEncBias<D> + 15) / 16;
+template <int D, int T>
+struct EncodeLds {
+    static constexpr int kBufs = T / kC;
+    _Float16 frag[kBufs][kEncSteps<D>][2][kC][8];   // 8 slots of one centroid
+    float cf[kBufs][kC / 8][8 * D + 4];                 // the centroids themselves, eight to a run: runs begin in different banks
+    float mean[4][D];                               // of a few centroids
+    float par[4][D + 4];                            // -mean * scale; scale; the longest centroid's length, scaled
+    float wmax[2][4];
+};
+template <int D, int T, bool ACROSS>
+__global__ __launch_bounds__(T, 4) void encode_mfma_kernel(const float *__restrict__ base, int64_t n, int d,
+                                                                      const float *__restrict__ codebooks, int M, int jper,
+                                                                      uint8_t *__restrict__ codes, int64_t across,
+                                                                      float *__restrict__ dlx) {
     typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
     typedef float v16f __attribute__((ext_vector_type(16)));
-    constexpr int KS = kEncSteps<D>, NX = kEncThreads / 2 * BLK, XS = 4 * D + 4;
-    static_assert(3 * D + 3 <= 16 * KS, "slots");
+    constexpr int KS = kEncSteps<D>, NB = kEncBias<D>, GROUPS = T / kC;       // of threads that prepare centroids
     extern __shared__ __align__(16) unsigned char smem[];
-    h8 *frag = reinterpret_cast<h8 *>(smem);                           // [KS][2][256]: 8 slots of one centroid
-    // the centroids themselves, eight to a run of 8 D + 4 values: the runs that lanes with different
-    // groups read begin in different banks
-    float *cf = reinterpret_cast<float *>(frag + KS * 2 * kC);         // [32][8 D + 4]
-    float *xt = cf + (kC / 8) * (8 * D + 4);                                           // [NX][XS] four sub-vectors of every vector
-    float *wmax = xt + NX * XS;                                        // [4]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int col = lane & 31, half = lane >> 5;
-    const int64_t x0 = (int64_t)blockIdx.x * NX;
+    EncodeLds<D, T> &s = *reinterpret_cast<EncodeLds<D, T> *>(smem);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, half = lane >> 5;
+    const int64_t xi = (int64_t)blockIdx.x * T + tid;
+    const float *row = base + (size_t)(xi < n ? xi : n - 1) * d;
     const bool vec_rows = (d & 3) == 0 && (reinterpret_cast<uintptr_t>(base) & 15u) == 0;
-    // where this thread's centroid sits in its 32-row tile: a lane of the result holds rows
-    // 8 q + 4 half + s, which are made the consecutive centroids 16 half + 4 q + s
-    const int my_row = (tid & ~31) | (((tid >> 2) & 3) << 3) | (((tid >> 4) & 1) << 2) | (tid & 3);
     const int jlo = blockIdx.y * jper, jhi = jlo + jper < M ? jlo + jper : M;    // (multiples of four)
+    // ---- centroids ----
+    const int ct = tid & (kC - 1), mine = wave >> 2;       // this thread's centroid, in the subspaces of this parity
+    // where it sits: a lane of the result holds rows 8 q + 4 half + i of a tile, which are made the consecutive centroids
+    // 128 half + 16 tile + 4 q + i
+    const int my_row = ((ct >> 4) & 7) << 5 | ((ct >> 2) & 3) << 3 | (ct >> 7) << 2 | (ct & 3);
     float c[D];
+    auto fetch = [&](int j) {
 #pragma unroll
-    for (int t = 0; t < D; ++t) c[t] = codebooks[((size_t)jlo * kC + tid) * D + t];
-    float tot[BLK];
-    uint32_t packed[BLK];
-#pragma unroll
-    for (int b = 0; b < BLK; ++b) { tot[b] = 0.0f; packed[b] = 0; }
-    for (int j = jlo; j < jhi; ++j) {
-        // (the same values in every lane: scalar loads)
-        float mu[D];
+        for (int t = 0; t < D; ++t) c[t] = codebooks[((size_t)j * kC + ct) * D + t];
+    };
+    auto measure = [&](int j) {        // mean and longest centroid of a subspace
+        float mu[D], n2 = 0.0f;        // (mu: the same values in every lane, scalar loads)
 #pragma unroll
         for (int t = 0; t < D; ++t) {
             float sum = 0.0f;
 #pragma unroll
             for (int i = 0; i < 8; ++i) sum = sum + codebooks[((size_t)j * kC + 32 * i) * D + t];
             mu[t] = sum * 0.125f;
+            const float cc = c[t] - mu[t];
+            n2 = __builtin_fmaf(cc, cc, n2);
         }
-        float n2 = 0.0f, cc[D];
-#pragma unroll
-        for (int t = 0; t < D; ++t) { cc[t] = c[t] - mu[t]; n2 = __builtin_fmaf(cc[t], cc[t], n2); }
         float m = n2;
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, off));
-        if (lane == 0) wmax[wave] = m;
-        __syncthreads();    // the previous subspace is done with; wmax is there
-        const float max2 = __builtin_fmaxf(__builtin_fmaxf(wmax[0], wmax[1]), __builtin_fmaxf(wmax[2], wmax[3]));
+        if (lane == 0) s.wmax[j & 1][wave & 3] = m;
+        if (ct == 0)
+#pragma unroll
+            for (int t = 0; t < D; ++t) s.mean[j & 3][t] = mu[t];
+    };
+    auto operands = [&](int j) {
+        const float max2 = __builtin_fmaxf(__builtin_fmaxf(s.wmax[j & 1][0], s.wmax[j & 1][1]), __builtin_fmaxf(s.wmax[j & 1][2], s.wmax[j & 1][3]));
         const bool usable = max2 > 1e-30f && max2 < 1e30f;
         // 2^k with 2^24 <= 2^2k max2 < 2^26
         const int k = usable ? (25 - (int)((__float_as_uint(max2) >> 23) - 127)) >> 1 : 0;
         const float sc = __uint_as_float((uint32_t)(k + 127) << 23);
-        {
-            _Float16 slot[KS * 16];
+        _Float16 slot[KS * 16];
 #pragma unroll
-            for (int i = 0; i < KS * 16; ++i) slot[i] = (_Float16)0.0f;
+        for (int i = 0; i < KS * 16; ++i) slot[i] = (_Float16)0.0f;
+        float n2 = 0.0f;
 #pragma unroll
-            for (int t = 0; t < D; ++t) {
-                const float v = -2.0f * (cc[t] * sc);
-                const _Float16 hi = (_Float16)v;
-                const _Float16 lo = (_Float16)(v - (float)hi);
-                slot[t] = hi;
-                slot[D + t] = hi;
-                slot[2 * D + t] = lo;
-            }
-            const float q2 = (n2 * sc) * sc * (1.0f / 4096.0f);       // (the vector's side of these slots is 4096)
-            const _Float16 p1 = (_Float16)q2;
-            const _Float16 p2 = (_Float16)(q2 - (float)p1);
-            const _Float16 p3 = (_Float16)((q2 - (float)p1) - (float)p2);
-            slot[3 * D] = p1;
-            slot[3 * D + 1] = p2;
-            slot[3 * D + 2] = p3;
-#pragma unroll
-            for (int i = 0; i < KS * 2; ++i) {
-                h8 f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) f[e] = slot[8 * i + e];
-                frag[i * kC + my_row] = f;
-            }
-#pragma unroll
-            for (int t = 0; t < D; ++t) cf[(tid >> 3) * (8 * D + 4) + (tid & 7) * D + t] = c[t];
+        for (int t = 0; t < D; ++t) {
+            const float cc = c[t] - s.mean[j & 3][t], v = -2.0f * (cc * sc);
+            n2 = __builtin_fmaf(cc, cc, n2);
+            const _Float16 hi = (_Float16)v;
+            slot[t] = hi;
+            slot[D + t] = hi;
+            slot[2 * D + t] = (_Float16)(v - (float)hi);
         }
-        if ((j & 3) == 0) {     // the next four sub-vectors of the workgroup's vectors
-            if (vec_rows) {
-                for (int e = tid; e < NX * D; e += kEncThreads) {
-                    const int r = e / D, g = e - r * D;
-                    const int64_t x = x0 + r < n ? x0 + r : n - 1;
-                    *reinterpret_cast<float4 *>(xt + r * XS + 4 * g) =
-                        *reinterpret_cast<const float4 *>(base + (size_t)x * d + (size_t)j * D + 4 * g);
-                }
-            } else {
-                for (int e = tid; e < NX * 4 * D; e += kEncThreads) {
-                    const int r = e / (4 * D), g = e - r * (4 * D);
-                    const int64_t x = x0 + r < n ? x0 + r : n - 1;
-                    xt[r * XS + g] = base[(size_t)x * d + (size_t)j * D + g];
-                }
+        const float q2 = (n2 * sc) * sc * (1.0f / 4096.0f);       // (the vector's side of these slots is 4096)
+        const _Float16 p1 = (_Float16)q2;
+        const _Float16 p2 = (_Float16)(q2 - (float)p1);
+        slot[3 * D] = p1;
+        slot[3 * D + 1] = p2;
+        slot[3 * D + 2] = (_Float16)((q2 - (float)p1) - (float)p2);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) slot[3 * D + 3 + i] = (_Float16)32768.0f;
+#pragma unroll
+        for (int i = 0; i < KS * 2; ++i) {
+            h8 f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) f[e] = slot[8 * i + e];
+            *reinterpret_cast<h8 *>(s.frag[j % GROUPS][i >> 1][i & 1][my_row]) = f;
+        }
+#pragma unroll
+        for (int t = 0; t < D; ++t) s.cf[j % GROUPS][ct >> 3][(ct & 7) * D + t] = c[t];
+        if (ct == 0) {
+#pragma unroll
+            for (int t = 0; t < D; ++t) s.par[j & 3][t] = -(s.mean[j & 3][t] * sc);
+            s.par[j & 3][D] = sc;
+            s.par[j & 3][D + 1] = usable ? trim::sqrt_rn(max2) * sc : __builtin_inff();
+        }
+    };
+    // ---- vectors ----
+    float xs[4 * D];                   // four sub-vectors
+    auto read_rows = [&](int j) {
+        if (vec_rows) {
+#pragma unroll
+            for (int g = 0; g < D; ++g) *reinterpret_cast<float4 *>(xs + 4 * g) = *reinterpret_cast<const float4 *>(row + (size_t)j * D + 4 * g);
+        } else {
+#pragma unroll
+            for (int t = 0; t < 4 * D; ++t) xs[t] = row[(size_t)j * D + t];
+        }
+    };
+    read_rows(jlo);
+    if (jlo + mine < jhi) {
+        fetch(jlo + mine);
+        measure(jlo + mine);
+    }
+    __syncthreads();
+    if (mine == 0) {
+        operands(jlo);
+        if (jlo + GROUPS < jhi) fetch(jlo + GROUPS);
+    }
+    __syncthreads();
+    float tot = 0.0f;
+    for (int j0 = jlo; j0 < jhi; j0 += 4) {
+        uint32_t packed = 0;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+            const int j = j0 + jj;
+            if constexpr (GROUPS == 1) {
+                if (j + 1 < jhi) measure(j + 1);
+            } else if (mine != (jj & 1)) {
+                if (j + 1 < jhi) operands(j + 1);
+                if (j + 3 < jhi) fetch(j + 3);
+            } else if (j + 2 < jhi) {
+                measure(j + 2);
             }
-        }
-        __syncthreads();
-        if (j + 1 < jhi) {
-#pragma unroll
-            for (int t = 0; t < D; ++t) c[t] = codebooks[((size_t)(j + 1) * kC + tid) * D + t];
-        }
-        const float cmax = trim::sqrt_rn(max2) * sc;
-#pragma unroll
-        for (int b = 0; b < BLK; ++b) {
-            const float *xr = xt + ((wave * BLK + b) * 32 + col) * XS + (j & 3) * D;
             float x[D];
 #pragma unroll
-            for (int t = 0; t < D; ++t) x[t] = xr[t];
+            for (int t = 0; t < D; ++t) x[t] = xs[jj * D + t];
+            if (jj == 3 && j0 + 4 < jhi) read_rows(j0 + 4);
+            const float sc = s.par[jj][D], cmax = s.par[jj][D + 1];
             float xn2 = 0.0f, xmax = 0.0f;
             _Float16 slot[KS * 16];
 #pragma unroll
             for (int i = 0; i < KS * 16; ++i) slot[i] = (_Float16)0.0f;
 #pragma unroll
             for (int t = 0; t < D; ++t) {
-                const float v = (x[t] - mu[t]) * sc;
+                const float v = __builtin_fmaf(x[t], sc, s.par[jj][t]);      // (x - mean) * scale, rounded once
                 const _Float16 hi = (_Float16)v;
                 slot[t] = hi;
                 slot[D + t] = (_Float16)(v - (float)hi);
@@ -1050,63 +1078,73 @@ __global__ __launch_bounds__(kEncThreads) void encode_mfma_kernel(const float *_
                 xmax = __builtin_fmaxf(xmax, __builtin_fabsf(v));
             }
             slot[3 * D] = slot[3 * D + 1] = slot[3 * D + 2] = (_Float16)4096.0f;
-            const float reach = trim::sqrt_rn(xn2) + cmax;
+            const float reach = __builtin_amdgcn_sqrtf(xn2) + cmax;
             float margin = reach * reach * (KS == 1 ? 1.25f / 131072.0f : 1.0f / 65536.0f);
-            if (!usable || !(xmax < 32768.0f)) margin = __builtin_inff();
-            const float bias = margin < __builtin_inff() ? xn2 + margin : 0.0f;
-            v16f start;
+            if (!(xmax < 16384.0f)) margin = __builtin_inff();
+            const float bias = margin < __builtin_inff() ? (xn2 + margin) * ((1.0f + 1.0f / 512.0f) / 32768.0f / NB) : 0.0f;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) start[i] = bias;
-            h8 xf[KS];
+            for (int i = 0; i < NB; ++i) slot[3 * D + 3 + i] = (_Float16)bias;
+            h8 xf[2][KS];
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
                 h8 f0, f1;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) { f0[e] = slot[16 * ks + e]; f1[e] = slot[16 * ks + 8 + e]; }
-                typedef uint32_t u4 __attribute__((ext_vector_type(4)));
                 const u4 w0 = __builtin_bit_cast(u4, f0), w1 = __builtin_bit_cast(u4, f1);
-                u4 w;
+                u4 r0, r1;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = half ? w1[e] : w0[e];
-                xf[ks] = __builtin_bit_cast(h8, w);
+                for (int e = 0; e < 4; ++e) {
+                    const auto p = __builtin_amdgcn_permlane32_swap(w0[e], w1[e], false, false);
+                    r0[e] = p[0];
+                    r1[e] = p[1];
+                }
+                xf[0][ks] = __builtin_bit_cast(h8, r0);
+                xf[1][ks] = __builtin_bit_cast(h8, r1);
             }
-            int gmin[8];
+            const auto margins = __builtin_amdgcn_permlane32_swap(__float_as_uint(margin), __float_as_uint(margin), false, false);
+            float thr[2];
+            uint32_t past[2] = {0, 0};       // groups beyond the threshold
 #pragma unroll
-            for (int t = 0; t < 8; t += 2) {
-                v16f acc[2] = {start, start};
+            for (int b = 0; b < 2; ++b) {
+                int gmin[16];
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
+                for (int t = 0; t < 8; t += 2) {
+                    v16f acc[2] = {};
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                        for (int u = 0; u < 2; ++u)
+                            acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+                                *reinterpret_cast<const h8 *>(s.frag[jj % GROUPS][ks][half][(t + u) * 32 + col]), xf[b][ks], acc[u], 0, 0, 0);
 #pragma unroll
                     for (int u = 0; u < 2; ++u)
-                        acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(frag[(ks * 2 + half) * kC + (t + u) * 32 + col], xf[ks], acc[u], 0, 0, 0);
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    int g = __float_as_int(acc[u][0]);
+                        for (int h = 0; h < 2; ++h) {
+                            int g = __float_as_int(acc[u][8 * h]);
 #pragma unroll
-                    for (int i = 1; i < 16; ++i) g = g < __float_as_int(acc[u][i]) ? g : __float_as_int(acc[u][i]);
-                    gmin[t + u] = g;
+                            for (int i = 1; i < 8; ++i) g = g < __float_as_int(acc[u][8 * h + i]) ? g : __float_as_int(acc[u][8 * h + i]);
+                            gmin[2 * (t + u) + h] = g;
+                        }
                 }
+                int least = gmin[0];
+#pragma unroll
+                for (int g = 1; g < 16; ++g) least = least < gmin[g] ? least : gmin[g];
+                const auto both = __builtin_amdgcn_permlane32_swap((uint32_t)least, (uint32_t)least, false, false);
+                thr[b] = __int_as_float((int)both[0] < (int)both[1] ? (int)both[0] : (int)both[1]) + __uint_as_float(margins[b]);
+                // by the sign of a difference (scores are positive: they order like their bits)
+#pragma unroll
+                for (int g = 15; g >= 0; --g) past[b] = __builtin_amdgcn_alignbit(past[b], __float_as_uint(thr[b]) - (uint32_t)gmin[g], 31);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            int bi = gmin[0];
-#pragma unroll
-            for (int t = 1; t < 8; ++t) bi = bi < gmin[t] ? bi : gmin[t];
-            const int ob = __shfl_xor(bi, 32);
-            bi = bi < ob ? bi : ob;
-            const float thr = __int_as_float(bi) + margin;
-            uint32_t todo = 0;      // bit 2 t + half: group t of a half
-#pragma unroll
-            for (int t = 0; t < 8; ++t)
-                if (!(__int_as_float(gmin[t]) > thr)) todo |= 1u << (2 * t);
-            todo <<= half;
-            todo |= (uint32_t)__shfl_xor((int)todo, 32);
+            const auto mp = __builtin_amdgcn_permlane32_swap(past[0], past[1], false, false);
+            uint32_t todo = (half ? thr[1] : thr[0]) < __builtin_inff() ? ~(mp[0] | mp[1] << 16) : ~0u;
             float best = __builtin_inff();
             int arg = 0;
-            while (__any(todo != 0)) {
+            do {
                 if (todo != 0) {
                     const int g = __ffs((int)todo) - 1;
                     todo &= todo - 1;
-                    const int c0 = g * 16 + 8 * half;
-                    const float *run = cf + (2 * g + half) * (8 * D + 4);     // ascending from group to group: strict < keeps the smallest index
+                    const float *run = s.cf[jj % GROUPS][g];     // ascending from group to group: strict < keeps the smallest index
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
                         float acc = 0.0f;
@@ -1115,35 +1153,27 @@ __global__ __launch_bounds__(kEncThreads) void encode_mfma_kernel(const float *_
                             const float e = x[t] - run[i * D + t];
                             acc = __builtin_fmaf(e, e, acc);
                         }
-                        if (acc < best) { best = acc; arg = c0 + i; }
+                        if (acc < best) { best = acc; arg = g * 8 + i; }
                     }
                 }
+            } while (__any(todo != 0));
+            tot = tot + best;
+            if constexpr (ACROSS) {
+                if (xi < n) codes[(size_t)j * across + xi] = (uint8_t)arg;
+            } else {
+                packed |= (uint32_t)arg << (8 * jj);
             }
-            const float od = __shfl_xor(best, 32);
-            const int oa = __shfl_xor(arg, 32);
-            if (od < best || (od == best && oa < arg)) { best = od; arg = oa; }
-            tot[b] = tot[b] + best;
-            packed[b] |= (uint32_t)arg << (8 * (j & 3));
-            if ((j & 3) == 3) {
-                const int64_t xi = x0 + (wave * BLK + b) * 32 + col;
-                if (half == 0 && xi < n) {
-                    if constexpr (ACROSS) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) codes[(size_t)(j - 3 + i) * across + xi] = (uint8_t)(packed[b] >> (8 * i));
-                    } else {
-                        *reinterpret_cast<uint32_t *>(codes + (size_t)xi * M + (j - 3)) = packed[b];
-                    }
-                }
-                packed[b] = 0;
+            __syncthreads();
+            if constexpr (GROUPS == 1) {
+                if (j + 1 < jhi) operands(j + 1);
+                if (j + 2 < jhi) fetch(j + 2);
+                __syncthreads();
             }
         }
+        if constexpr (!ACROSS)
+            if (xi < n) *reinterpret_cast<uint32_t *>(codes + (size_t)xi * M + j0) = packed;
     }
-    if (jper < M || !dlx) return;
-#pragma unroll
-    for (int b = 0; b < BLK; ++b) {
-        const int64_t xi = x0 + (wave * BLK + b) * 32 + col;
-        if (half == 0 && xi < n) dlx[xi] = trim::sqrt_rn(tot[b]);
-    }
+    if (jper >= M && dlx && xi < n) dlx[xi] = trim::sqrt_rn(tot);
 }
 
 // Landmark distances from finished codes: the same sub-distances, added in subspace order.  A

@@ -129,11 +129,10 @@ def test_update_of_codebooks_of_long_subvectors(T, oracle, ns, M, bits):
     np.testing.assert_array_equal(got.view(np.uint32), want.view(np.uint32))
 
 
-# every sub-vector length with the matrix-core filter and one without; rows around the workgroup's 128
-# and 256 vectors; unaligned rows; ties, all-zero centroids, magnitudes outside the filter's range
+# every sub-vector length with the matrix-core filter and one without; few vectors, with their subspaces dealt out; ties, all-zero centroids, magnitudes outside the filter's range
 @pytest.mark.parametrize("dsub,M,n", [(4, 4, 1), (4, 8, 129), (5, 4, 255), (6, 4, 700), (8, 8, 1000), (7, 4, 300),
                                       (4, 4, 131073), (8, 4, 131100)])
-def test_encode_filter(T, oracle, dsub, M, n):
+def test_encode_filter(T, oracle, dsub, M, n, skew=0):
     import torch
     rng = np.random.default_rng(dsub * 1000 + n)
     d = dsub * M
@@ -146,9 +145,19 @@ def test_encode_filter(T, oracle, dsub, M, n):
     cb[3] *= np.float32(1e-20) if n % 3 else np.float32(1e17)
     x[n // 3, :dsub] = 3e6                         # a vector far beyond the centroids
     rc, rd = oracle.encode(x, cb)
-    codes, dlx = T.trim_encode(torch.from_numpy(x).cuda(), torch.from_numpy(cb).cuda())
+    rows = torch.zeros((n * d + skew,), device="cuda")[skew:].view(n, d).copy_(torch.from_numpy(x))
+    codes, dlx = T.trim_encode(rows, torch.from_numpy(cb).cuda())
     np.testing.assert_array_equal(codes.cpu().numpy(), rc)
     np.testing.assert_array_equal(dlx.cpu().numpy().view(np.uint32), rd.view(np.uint32))
+
+
+# workgroups of 256 and of 512 vectors, whole and with the subspaces dealt out: full, one vector short and one over; more than one round
+# of the row reader; rows that begin off a 16-byte boundary
+@pytest.mark.parametrize("skew", (0, 1))
+@pytest.mark.parametrize("dsub,M,n", [(4, 4, 255), (5, 12, 257), (4, 16, 16385), (8, 16, 19968), (6, 16, 20001), (5, 16, 20479),
+                                      (4, 8, 57345), (8, 4, 58111), (4, 8, 65537), (5, 8, 66049), (6, 4, 66048), (8, 8, 66047)])
+def test_encode_filter_by_workgroup(T, oracle, dsub, M, n, skew):
+    test_encode_filter(T, oracle, dsub, M, n, skew)
 
 
 # the nearest list of many vectors: ragged vector, list and column counts, ties between lists, vectors
