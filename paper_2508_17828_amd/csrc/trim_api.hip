@@ -15,6 +15,7 @@
 #include "trim_probe.h"
 #include "trim_launch.h"
 #include "trim_update.h"
+#include "trim_assign.h"
 
 // Scratch area of trim_search_range_static (see below): device memory inside the library's code
 // object; every GPU the library runs on holds its own copy at its own address.
@@ -831,6 +832,87 @@ int probe_queries(int d, int nlist, int *npow2, size_t *lds) {
     *lds = (size_t)qt * ((size_t)*npow2 * 8 + (size_t)d * 4);
     return qt;
 }
+
+// The nearest list of many vectors: scored on the matrix cores.  Below 4096 vectors fewer than 16
+// workgroups would do it, and below 64 lists a 256-wide tile is mostly padding.
+bool nearest_pays(int64_t nq, int d, int nlist) { return nq >= 4096 && nlist >= 64 && d <= kAsgMaxD; }
+// Bytes of work space for it, 256-byte aligned, or 0 where it goes without.
+size_t nearest_bytes(int64_t nq, int d, int nlist) {
+    return nq > 0 && d > 0 && d % 4 == 0 && nlist > 0 && d <= kAsrCols && nearest_pays(nq, d, nlist) ? ast_layout(d, nlist).total : 0;
+}
+// Of the training of coarse lists: the update's, then the assignment's.
+size_t train_ivf_bytes(int64_t ns, int d, int nlist) {
+    const size_t near = nearest_bytes(ns, d, nlist), sorted = update_layout(ns, d, nlist, 1).total;
+    return near > 0 ? up256(sorted) + near : sorted;
+}
+template <int KS>
+int launch_tiles(const float *x, int64_t n, int d, const float *cent, int nlist, int32_t *out, unsigned char *ws, hipStream_t st) {
+    const AstLayout L = ast_layout(d, nlist);
+    AstHead *head = reinterpret_cast<AstHead *>(ws);
+    uint32_t *most = reinterpret_cast<uint32_t *>(ws + L.off_most);
+    uint4 *ops = reinterpret_cast<uint4 *>(ws + L.off_ops);
+    hipLaunchKernelGGL(assign_operands_kernel<KS>, dim3((unsigned)L.nst), dim3(512), 0, st, cent, nlist, d, head, most, ops);
+    HIP_TRY(hipGetLastError());
+    hipLaunchKernelGGL(assign_tiles_kernel<KS>, dim3((unsigned)((n + kAstVecs - 1) / kAstVecs)), dim3(kAstThreads), 0, st, x, n, d, cent,
+                       nlist, L.nst, head, most, ops, out);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+int launch_nearest(const float *x, int64_t n, int d, const float *cent, int nlist, int32_t *out, unsigned char *ws, hipStream_t st) {
+    if (ws) {
+        if (const int rc = d <= kAsrCols / 2 ? launch_tiles<4>(x, n, d, cent, nlist, out, ws, st) : launch_tiles<8>(x, n, d, cent, nlist, out, ws, st))
+            return rc;
+    } else {
+        const size_t lds = assign_lds(d);
+        void (*assign)(const float *, int64_t, int, const float *, int, int32_t *) = assign_mfma_kernel;
+        if (d <= kAsrCols) assign = d <= kAsrCols / 2 ? assign_rows_kernel<4> : assign_rows_kernel<8>;
+        else HIP_TRY(allow_lds(reinterpret_cast<const void *>(assign_mfma_kernel), lds));
+        hipLaunchKernelGGL(assign, dim3((unsigned)((n + kAsgTile - 1) / kAsgTile)), dim3(kAsgThreads), d <= kAsrCols ? 0 : lds, st, x, n, d,
+                           cent, nlist, out);
+        HIP_TRY(hipGetLastError());
+    }
+    // the marked vectors
+    const size_t lds = (size_t)8 * d * 4;
+    int span = kFixSpan;
+    while (span > 64 && n / span < 512) span >>= 1;     // (two workgroups per CU, where there are so many vectors)
+    const int64_t blocks = (n + span - 1) / span;
+    const bool one = d <= kAsrCols || d > 1024 || blocks < 400;      // (see assign_fix_kernel)
+    void (*fix)(const float *, int64_t, int, const float *, int, int, int32_t *) = one ? assign_fix_kernel<1024> : assign_fix_kernel<512>;
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(fix), lds));
+    hipLaunchKernelGGL(fix, dim3((unsigned)blocks), dim3(one ? 1024 : 512), lds, st, x, n, d, cent, nlist, span, out);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+
+// trim_ivf_probe; ws: null, or where nearest_bytes bytes are, for one probe.
+int ivf_probe(const float *queries, int64_t nq, int d, const float *centroids, int nlist, int nprobe, int32_t *probes_out, unsigned char *ws,
+              hipStream_t st) {
+    if (nq < 0 || d <= 0 || nlist <= 0 || nprobe <= 0) return TRIM_INVALID_ARG;
+    if (nprobe > nlist || nprobe > TRIM_MAX_NPROBE) return TRIM_INVALID_ARG;
+    if (d % 4) return TRIM_UNSUPPORTED_SHAPE;
+    int npow2;
+    size_t lds;
+    const int qt = probe_queries(d, nlist, &npow2, &lds);
+    if (lds > kLdsBytes) return TRIM_UNSUPPORTED_SHAPE;
+    if (nq == 0) return TRIM_OK;
+    if (!queries || !centroids || !probes_out || !aligned16(centroids)) return TRIM_INVALID_ARG;
+    if (nq > 0x7fffffff) return TRIM_INVALID_ARG;
+    if (nprobe == 1 && nearest_pays(nq, d, nlist) && aligned16(queries)) return launch_nearest(queries, nq, d, centroids, nlist, probes_out, ws, st);
+    void (*fn)(const float *, int64_t, int, const float *, int, int, int, int32_t *) =
+        qt == 8 ? ivf_probe_kernel<8> : qt == 4 ? ivf_probe_kernel<4> : qt == 2 ? ivf_probe_kernel<2> : ivf_probe_kernel<1>;
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), lds));
+    // a launch holds fewer than 2^32 threads: walk the queries in slabs
+    const int64_t slab = (int64_t)qt * (1 << 22);
+    for (int64_t q0 = 0; q0 < nq; q0 += slab) {
+        const int64_t cnt = nq - q0 < slab ? nq - q0 : slab;
+        hipLaunchKernelGGL(fn, dim3((unsigned)((cnt + qt - 1) / qt)), dim3(512), lds, st,
+                           queries + (size_t)q0 * d, cnt, d, centroids, nlist, npow2, nprobe,
+                           probes_out + (size_t)q0 * nprobe);
+        HIP_TRY(hipGetLastError());
+    }
+    return TRIM_OK;
+}
+
 // Sizes that a probe selection takes, whatever its work space.
 bool probe_takes(int64_t nq, int d, int nlist, int nprobe) {
     int npow2;
@@ -1388,8 +1470,8 @@ int trim_train_ivf(const float *train, int64_t ns, int32_t d, int32_t nlist, int
 }
 
 size_t trim_train_ivf_workspace_bytes(int64_t ns, int32_t d, int32_t nlist) {
-    const UpdateLayout L = update_layout(ns, d, nlist, 1);
-    return L.total > 0 ? L.total + 256 : 0;
+    const size_t need = train_ivf_bytes(ns, d, nlist);
+    return need > 0 ? need + 256 : 0;
 }
 
 int trim_train_ivf_ws(const float *train, int64_t ns, int32_t d, int32_t nlist, int32_t iters,
@@ -1399,16 +1481,18 @@ int trim_train_ivf_ws(const float *train, int64_t ns, int32_t d, int32_t nlist, 
     if (d % 4) return TRIM_UNSUPPORTED_SHAPE;
     if (!train || !init_rows || !centroids_out || !assign_ws) return TRIM_INVALID_ARG;
     if ((int64_t)nlist * d > 0x7fffffff) return TRIM_UNSUPPORTED_SHAPE;
-    unsigned char *ws = update_space(workspace, workspace_bytes, update_layout(ns, d, nlist, 1).total);
+    const UpdateLayout L = update_layout(ns, d, nlist, 1);
+    unsigned char *ws = update_space(workspace, workspace_bytes, train_ivf_bytes(ns, d, nlist));
+    unsigned char *sorted = L.total > 0 ? ws : nullptr, *near = ws && nearest_bytes(ns, d, nlist) > 0 ? ws + up256(L.total) : nullptr;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int per = nlist * d;
     hipLaunchKernelGGL(kmeans_init_kernel, dim3((per + 255) / 256), dim3(256), 0, st, train, ns, (int64_t)d, d, init_rows,
                        nlist, centroids_out);
     HIP_TRY(hipGetLastError());
     for (int it = 0; it < iters; ++it) {
-        int rc = trim_ivf_probe(train, ns, d, centroids_out, nlist, 1, assign_ws, stream);
+        int rc = ivf_probe(train, ns, d, centroids_out, nlist, 1, assign_ws, near, st);
         if (rc) return rc;
-        if ((rc = kmeans_update<4>(train, ns, d, d, assign_ws, 1, 0, nlist, 1, centroids_out, ws, st))) return rc;
+        if ((rc = kmeans_update<4>(train, ns, d, d, assign_ws, 1, 0, nlist, 1, centroids_out, sorted, st))) return rc;
     }
     return TRIM_OK;
 }
@@ -1704,12 +1788,19 @@ size_t trim_static_scratch_bytes(void) { return kScratchBytes; }
 
 size_t trim_ivf_probe_workspace_bytes(int64_t nq, int32_t d, int32_t nlist, int32_t nprobe) {
     if (nq <= 0 || d <= 0 || nlist <= 0 || nprobe <= 0) return 0;
+    if (nprobe == 1) {
+        const size_t need = nearest_bytes(nq, d, nlist);
+        return need > 0 ? need + 256 : 0;
+    }
     const ProbeLayout L = probe_layout(nq, d, nlist, nprobe);
     return L.total > 0 ? L.total : probe_in_two(nq, d, nlist, nprobe) ? (size_t)nq * nlist * 4 : 0;
 }
 
 int trim_ivf_probe_ws(const float *queries, int64_t nq, int32_t d, const float *centroids, int32_t nlist, int32_t nprobe,
                       int32_t *probes_out, void *workspace, size_t workspace_bytes, void *stream) {
+    if (nprobe == 1)
+        return ivf_probe(queries, nq, d, centroids, nlist, 1, probes_out, update_space(workspace, workspace_bytes, nearest_bytes(nq, d, nlist)),
+                         static_cast<hipStream_t>(stream));
     const ProbeLayout L = nq > 0 && d > 0 && nlist > 0 ? probe_layout(nq, d, nlist, nprobe) : ProbeLayout{};
     if (L.total > 0 && workspace && workspace_bytes >= L.total && queries && centroids && probes_out && aligned16(centroids) &&
         aligned16(queries))
@@ -1737,50 +1828,7 @@ int trim_ivf_probe_ws(const float *queries, int64_t nq, int32_t d, const float *
 
 int trim_ivf_probe(const float *queries, int64_t nq, int32_t d, const float *centroids,
                    int32_t nlist, int32_t nprobe, int32_t *probes_out, void *stream) {
-    if (nq < 0 || d <= 0 || nlist <= 0 || nprobe <= 0) return TRIM_INVALID_ARG;
-    if (nprobe > nlist || nprobe > TRIM_MAX_NPROBE) return TRIM_INVALID_ARG;
-    if (d % 4) return TRIM_UNSUPPORTED_SHAPE;
-    int npow2;
-    size_t lds;
-    const int qt = probe_queries(d, nlist, &npow2, &lds);
-    if (lds > kLdsBytes) return TRIM_UNSUPPORTED_SHAPE;
-    if (nq == 0) return TRIM_OK;
-    if (!queries || !centroids || !probes_out || !aligned16(centroids)) return TRIM_INVALID_ARG;
-    if (nq > 0x7fffffff) return TRIM_INVALID_ARG;
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    // The nearest list of many vectors: scored on the matrix cores.  Below 4096 vectors fewer than 16
-    // workgroups would do it, and below 64 lists a 256-wide tile is mostly padding.
-    if (nprobe == 1 && nq >= 4096 && nlist >= 64 && d <= kAsgMaxD && aligned16(queries)) {
-        const size_t lds1 = assign_lds(d), lds2 = (size_t)8 * d * 4;
-        void (*assign)(const float *, int64_t, int, const float *, int, int32_t *) = assign_mfma_kernel;
-        if (d <= kAsrCols) assign = d <= kAsrCols / 2 ? assign_rows_kernel<4> : assign_rows_kernel<8>;
-        else HIP_TRY(allow_lds(reinterpret_cast<const void *>(assign_mfma_kernel), lds1));
-        int span = kFixSpan;
-        while (span > 64 && nq / span < 512) span >>= 1;     // (two workgroups per CU, where there are so many vectors)
-        const int64_t blocks = (nq + span - 1) / span;
-        const bool one = d <= kAsrCols || d > 1024 || blocks < 400;      // (see assign_fix_kernel)
-        void (*fix)(const float *, int64_t, int, const float *, int, int, int32_t *) = one ? assign_fix_kernel<1024> : assign_fix_kernel<512>;
-        HIP_TRY(allow_lds(reinterpret_cast<const void *>(fix), lds2));
-        hipLaunchKernelGGL(assign, dim3((unsigned)((nq + kAsgTile - 1) / kAsgTile)), dim3(kAsgThreads), d <= kAsrCols ? 0 : lds1, st,
-                           queries, nq, d, centroids, nlist, probes_out);
-        HIP_TRY(hipGetLastError());
-        hipLaunchKernelGGL(fix, dim3((unsigned)blocks), dim3(one ? 1024 : 512), lds2, st, queries, nq, d, centroids, nlist, span, probes_out);
-        HIP_TRY(hipGetLastError());
-        return TRIM_OK;
-    }
-    void (*fn)(const float *, int64_t, int, const float *, int, int, int, int32_t *) =
-        qt == 8 ? ivf_probe_kernel<8> : qt == 4 ? ivf_probe_kernel<4> : qt == 2 ? ivf_probe_kernel<2> : ivf_probe_kernel<1>;
-    HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), lds));
-    // a launch holds fewer than 2^32 threads: walk the queries in slabs
-    const int64_t slab = (int64_t)qt * (1 << 22);
-    for (int64_t q0 = 0; q0 < nq; q0 += slab) {
-        const int64_t cnt = nq - q0 < slab ? nq - q0 : slab;
-        hipLaunchKernelGGL(fn, dim3((unsigned)((cnt + qt - 1) / qt)), dim3(512), lds, st,
-                           queries + (size_t)q0 * d, cnt, d, centroids, nlist, npow2, nprobe,
-                           probes_out + (size_t)q0 * nprobe);
-        HIP_TRY(hipGetLastError());
-    }
-    return TRIM_OK;
+    return ivf_probe(queries, nq, d, centroids, nlist, nprobe, probes_out, nullptr, static_cast<hipStream_t>(stream));
 }
 
 int trim_query_order(const int32_t *probes, int64_t nq, int32_t nprobe, int32_t nlist,

@@ -182,6 +182,37 @@ def test_assignment(T, oracle, n, d, nlist, scale):
     np.testing.assert_array_equal(got, want)
 
 
+# the nearest list with work space and without: vectors one short of a workgroup, full and one over, lists around a stage of them (128 of up to
+# 64 values, 64 of longer ones), equal lists at one place of as many tiles as are told apart and one more, and at as many places as are
+# measured and more
+@pytest.mark.parametrize("n,d,nlist", [(4097, 4, 64), (4351, 64, 129), (4352, 60, 128), (4353, 68, 127), (4100, 128, 64), (4120, 128, 65),
+                                       (4200, 124, 250), (6000, 128, 1025), (5000, 32, 2050)])
+def test_nearest_list_by_work_space(T, oracle, n, d, nlist):
+    import ctypes as C
+    import torch
+    rng = np.random.default_rng(n + d)
+    cent = rng.integers(-40, 41, (nlist, d)).astype(np.float32)
+    for k, tiles in ((3, 2), (9, 3), (17, 4), (30, 5)):
+        cent[k: 32 * tiles + k: 32] = cent[k]
+    for k, places in ((5, 2), (40, 12), (64, 20)):
+        cent[k: k + places] = cent[min(k, nlist - 1)]
+    x = (cent[rng.integers(0, nlist, n)] + rng.integers(-2, 3, (n, d))).astype(np.float32)
+    x[50], x[51] = np.nan, 1e30
+    xg, cg = torch.from_numpy(x).cuda(), torch.from_numpy(cent).cuda()
+    want = oracle.ivf_probe(x, cent, 1)
+    np.testing.assert_array_equal(T.trim_ivf_probe(xg, cg, 1).cpu().numpy(), want)
+    out = torch.full((n, 1), -7, dtype=torch.int32, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    need = T.lib().trim_ivf_probe_workspace_bytes(n, d, nlist, 1)
+    assert need > 0
+    space = torch.empty((need + 4,), dtype=torch.uint8, device="cuda")
+    for ws, size in ((None, 0), (space.data_ptr(), need - 1), (space.data_ptr() + 4, need)):
+        out.fill_(-7)
+        assert T.lib().trim_ivf_probe_ws(C.c_void_p(xg.data_ptr()), n, d, C.c_void_p(cg.data_ptr()), nlist, 1, C.c_void_p(out.data_ptr()),
+                                         C.c_void_p(ws), size, C.c_void_p(stream)) == 0
+        np.testing.assert_array_equal(out.cpu().numpy(), want)
+
+
 # 4-bit codes: sub-vectors of two values (whole and ragged 32-column slices, odd row counts) and of four
 @pytest.mark.parametrize("d,m,n", [(128, 64, 257), (36, 18, 100), (24, 12, 1), (100, 50, 513), (64, 16, 300)])
 def test_encode_four_bit(T, d, m, n):
