@@ -436,10 +436,13 @@ size_t trim_range_workspace_bytes(int64_t nq, int64_t max_candidates);
 int trim_ivf_probe(const float *queries, int64_t nq, int32_t d, const float *centroids,
                    int32_t nlist, int32_t nprobe, int32_t *probes_out, void *stream);
 /* trim_ivf_probe_ws: the same lists (Section 6.1) with a workspace of trim_ivf_probe_workspace_bytes, device, 4-byte aligned,
- * contents on entry ignored; with it a few queries are spread over the whole chip, for many the matrix cores
- * leave few lists to measure, and the nearest list of many short vectors (one probe) takes half the time.  0 bytes, NULL or less than that: trim_ivf_probe, which takes at most 16384 lists (of up to 8192
+ * contents on entry ignored; with it a few queries are spread over the whole chip, and for many the matrix cores
+ * leave few lists to measure.  0 bytes, NULL or less than that: trim_ivf_probe, which takes at most 16384 lists (of up to 8192
  * values); up to 4096 queries of 2 to 64 probes also find more, with nq nlist 4 bytes and nq nlist <= 2^26. */
 size_t trim_ivf_probe_workspace_bytes(int64_t nq, int32_t d, int32_t nlist, int32_t nprobe);
+/* One probe (Section 3.3's assignment): the workspace with which trim_ivf_probe_ws takes about half the time for 4096 vectors or more of
+ * up to 128 values (0: it has no use for one); with less, or NULL, as without. */
+size_t trim_ivf_nearest_workspace_bytes(int64_t nq, int32_t d, int32_t nlist);
 int trim_ivf_probe_ws(const float *queries, int64_t nq, int32_t d, const float *centroids, int32_t nlist, int32_t nprobe,
                       int32_t *probes_out, void *workspace, size_t workspace_bytes, void *stream);
 

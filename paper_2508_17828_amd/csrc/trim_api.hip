@@ -1786,12 +1786,13 @@ int trim_range_collect(const trim_index_view *index, int64_t nq, const trim_cand
 
 size_t trim_static_scratch_bytes(void) { return kScratchBytes; }
 
+size_t trim_ivf_nearest_workspace_bytes(int64_t nq, int32_t d, int32_t nlist) {
+    const size_t need = nearest_bytes(nq, d, nlist);
+    return need > 0 ? need + 256 : 0;
+}
+
 size_t trim_ivf_probe_workspace_bytes(int64_t nq, int32_t d, int32_t nlist, int32_t nprobe) {
     if (nq <= 0 || d <= 0 || nlist <= 0 || nprobe <= 0) return 0;
-    if (nprobe == 1) {
-        const size_t need = nearest_bytes(nq, d, nlist);
-        return need > 0 ? need + 256 : 0;
-    }
     const ProbeLayout L = probe_layout(nq, d, nlist, nprobe);
     return L.total > 0 ? L.total : probe_in_two(nq, d, nlist, nprobe) ? (size_t)nq * nlist * 4 : 0;
 }

@@ -25,7 +25,7 @@ EXPORTS = ("trim_shape_supported", "trim_fs_shape_supported", "trim_fs_encode", 
            "trim_train_pq_workspace_bytes", "trim_train_ivf", "trim_train_ivf_ws", "trim_train_ivf_workspace_bytes", "trim_estimate_gamma", "trim_estimate_gamma_ws", "trim_estimate_gamma_workspace_bytes", "trim_estimate_gamma_normal", "trim_encode", "trim_pack_scan_head", "trim_codes_tiled_bytes", "trim_pack_codes_tiled",
            "trim_build_lut", "trim_search_knn", "trim_search_knn_ws", "trim_knn_workspace_bytes",
            "trim_search_range", "trim_search_range_static", "trim_search_range_ws", "trim_range_scratch_bytes", "trim_range_collect", "trim_static_scratch_bytes", "trim_range_workspace_bytes", "trim_ivf_probe", "trim_ivf_probe_ws",
-           "trim_ivf_probe_workspace_bytes", "trim_query_order",
+           "trim_ivf_probe_workspace_bytes", "trim_ivf_nearest_workspace_bytes", "trim_query_order",
            "trim_list_bounds_bytes", "trim_pack_list_bounds",
            "trim_ceiling_stream_read", "trim_ceiling_lds_gather",
            "trim_strerror", "trim_last_hip_error", "trim_version")
@@ -140,6 +140,8 @@ def lib() -> C.CDLL:
         L.trim_static_scratch_bytes.restype = C.c_size_t
         L.trim_ivf_probe_workspace_bytes.restype = C.c_size_t
         L.trim_ivf_probe_workspace_bytes.argtypes = [C.c_int64, C.c_int32, C.c_int32, C.c_int32]
+        L.trim_ivf_nearest_workspace_bytes.restype = C.c_size_t
+        L.trim_ivf_nearest_workspace_bytes.argtypes = [C.c_int64, C.c_int32, C.c_int32]
         L.trim_ivf_probe_ws.argtypes = [C.c_void_p, C.c_int64, C.c_int32, C.c_void_p, C.c_int32, C.c_int32, C.c_void_p,
                                         C.c_void_p, C.c_size_t, C.c_void_p]
         L.trim_ivf_probe.argtypes = [C.c_void_p, C.c_int64, C.c_int32, C.c_void_p, C.c_int32,
@@ -550,7 +552,8 @@ def trim_ivf_probe(queries: torch.Tensor, centroids: torch.Tensor, nprobe: int) 
     nq, d = queries.shape
     nlist = centroids.shape[0]
     probes = torch.empty((nq, nprobe), dtype=torch.int32, device=queries.device)
-    ws, need = _scratch(lib().trim_ivf_probe_workspace_bytes(nq, d, nlist, nprobe), queries.device)
+    ws, need = _scratch(lib().trim_ivf_nearest_workspace_bytes(nq, d, nlist) if nprobe == 1 else
+                        lib().trim_ivf_probe_workspace_bytes(nq, d, nlist, nprobe), queries.device)
     _check(lib().trim_ivf_probe_ws(_ptr(queries, torch.float32, "queries"), nq, d,
                                    _ptr(centroids, torch.float32, "centroids"), nlist,
                                    nprobe, _ptr(probes, torch.int32, "probes"), _ptr(ws, torch.uint8, "workspace"), need,

@@ -203,7 +203,7 @@ def test_nearest_list_by_work_space(T, oracle, n, d, nlist):
     np.testing.assert_array_equal(T.trim_ivf_probe(xg, cg, 1).cpu().numpy(), want)
     out = torch.full((n, 1), -7, dtype=torch.int32, device="cuda")
     stream = torch.cuda.current_stream().cuda_stream
-    need = T.lib().trim_ivf_probe_workspace_bytes(n, d, nlist, 1)
+    need = T.lib().trim_ivf_nearest_workspace_bytes(n, d, nlist)
     assert need > 0
     space = torch.empty((need + 4,), dtype=torch.uint8, device="cuda")
     for ws, size in ((None, 0), (space.data_ptr(), need - 1), (space.data_ptr() + 4, need)):
