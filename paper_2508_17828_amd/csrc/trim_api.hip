@@ -631,7 +631,7 @@ bool counts_fit(const trim_index_view *ix, int64_t rows, const trim_candidates *
 bool passes_fit(const trim_index_view *ix, const trim_candidates *cand, int k, bool few, FinishPlan *fp) {
     const int nseg = cand ? cand->nprobe : 0;
     return ix->codebooks && make_finish_plan(ix->d, code_bytes(ix), is_fs(ix), nseg, few, fp) &&
-           replay_lds(ix->d, k, nseg) <= kLdsBytes && measure_lds(ix->d, 2) <= kLdsBytes;
+           replay_lds(ix->d, k, nseg) <= kLdsBytes && measure_lds(ix->d, 2, 4) <= kLdsBytes;
 }
 
 inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }

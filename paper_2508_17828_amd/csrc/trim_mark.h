@@ -558,25 +558,31 @@ __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs
 // Only where that does not exceed the threshold is the exact distance taken (replay_kernel,
 // range_exact_kernel).  A row is read once for all its queries, and the contraction takes the place of 2 d
 // vector operations per survivor: of 3,940 survivors per query (2,500 queries x 500,000 x 768) some forty
-// can still matter.  Bound by reading the rows; one or two slices of 32 values are on their way while one is used: 440 -> 405 us,
-// 500 queries x 300,000 x 960: 906 -> 547 us (WQ = 4: 256 queries at a time, so that rows are read half as often).
+// can still matter.  WR waves of 64 rows by WQ waves of 64 queries; NS slices of 32 values are on their way in registers while one is
+// used; WAVES: per SIMD.  Lists are cut at kMsrRows rows: WR = 4 there.
+//   <2, 4, 1, 4>  two workgroups per CU, bound by reading the rows (4.2 TB/s): 2,500 queries x 500,000 x 768, 440 -> 405 us
+//   <4, 4, 2, 4>  256 queries at a time, rows are read half as often: 500 queries x 300,000 x 960 906 -> 547 us
+//   <8, 2, 1, 4>  512 queries, half as many rows: the same bytes through the LDS, rows read once: there 555 -> 404 us (NS = 2 spills: 426;
+//                 waves of 64 x 128 at two per SIMD: 474).  Bound by the chain of barriers over slices, one workgroup per CU
+//   <2, 2, 4, 2>  too few tiles for the chip: bound by a tile's own chain; half as long a tile, rows asked for further ahead: 52 -> 35 us
 // Queries go to workgroups in blocks of 512, so that a list that many want is not one workgroup's tail.
-template <int WQ>
-__global__ __launch_bounds__(256 * WQ, 4) void measure_kernel(const FilterArgs a) {
+template <int WQ, int WR, int NS, int WAVES>
+__global__ __launch_bounds__(64 * WQ * WR, WAVES) void measure_kernel(const FilterArgs a) {
     typedef _Float16 h8 __attribute__((ext_vector_type(8)));
     typedef _Float16 h4 __attribute__((ext_vector_type(4)));
     typedef _Float16 h2 __attribute__((ext_vector_type(2)));
     typedef float v16f __attribute__((ext_vector_type(16)));
     typedef float f4 __attribute__((ext_vector_type(4)));
     typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-    constexpr int kMsrThreads = 256 * WQ, kMsrQ = 64 * WQ;
-    constexpr int kPer = 8 / WQ, kApart = kMsrThreads / 8;        // rows staged by a thread
-    constexpr int kSets = WQ / 2;                                 // slices ahead in registers
-    constexpr int kXRows = kMsrRows + 2;                          // rows per 8 columns (two spare: bank spread)
+    constexpr int kMsrThreads = 64 * WQ * WR, kMsrQ = 64 * WQ, kRows = 64 * WR;
+    constexpr int kApart = kMsrThreads / 8, kPer = kRows / kApart;        // rows staged by a thread
+    constexpr int kQApart = kMsrThreads / 4, kQPer = kMsrQ / kQApart;     // queries staged by a thread
+    constexpr int kStep = NS > 2 ? NS : 2;                        // slices a turn of the loop
+    constexpr int kXRows = kRows + 2;                          // rows per 8 columns (two spare: bank spread)
     constexpr int kQStride = kMsrQ + 4;                           // (bank spread)
     __shared__ __align__(16) unsigned char s_x[2][4 * kXRows * 16];
     __shared__ __align__(16) h8 s_q[2][4 * kQStride];             // [8 columns][query]
-    __shared__ __align__(16) float s_nx[kMsrRows], s_mx[kMsrRows];
+    __shared__ __align__(16) float s_nx[kRows], s_mx[kRows];
     __shared__ float s_mq[2 * kMsrQ], s_nq[2 * kMsrQ];
     __shared__ int s_row[2 * kMsrQ], s_c0[2 * kMsrQ], s_end[2 * kMsrQ];
     __shared__ int s_n;
@@ -590,7 +596,7 @@ __global__ __launch_bounds__(256 * WQ, 4) void measure_kernel(const FilterArgs a
     const float lost = sqrt_rn((float)a.d) * (1.0f / 16384.0f);
     for (int t = threadIdx.x; t < a.d; t += kMsrThreads) s_mu[t] = a.mu[t];      // (barriers follow)
     const int total_tasks = a.list_offsets ? a.row_tasks[a.nlist]
-                            : (int)((rows_all + kMsrRows - 1) / kMsrRows * ((qall + a.msr_block - 1) / a.msr_block));
+                            : (int)((rows_all + kRows - 1) / kRows * ((qall + a.msr_block - 1) / a.msr_block));
     for (int task = blockIdx.x; task < total_tasks; task += gridDim.x) {
         int tid = threadIdx.x;            // (opaque: see filter_kernel)
         asm volatile("" : "+v"(tid));
@@ -607,15 +613,15 @@ __global__ __launch_bounds__(256 * WQ, 4) void measure_kernel(const FilterArgs a
             const int nqb = (q1 - qb + a.msr_block - 1) / a.msr_block, t = task - a.row_tasks[x], rt = t / nqb;
             qb += (t - rt * nqb) * a.msr_block;
             q1 = qb + a.msr_block < q1 ? qb + a.msr_block : q1;
-            r0 = ls + (int64_t)rt * kMsrRows;
+            r0 = ls + (int64_t)rt * kRows;
         } else {
             const int nqb = (int)((qall + a.msr_block - 1) / a.msr_block);
             const int rt = task / nqb;
             qb = (task - rt * nqb) * a.msr_block;
             q1 = qb + a.msr_block < (int)qall ? qb + a.msr_block : (int)qall;
-            r0 = (int64_t)rt * kMsrRows;
+            r0 = (int64_t)rt * kRows;
         }
-        const int nrows = le - r0 < kMsrRows ? (int)(le - r0) : kMsrRows;
+        const int nrows = le - r0 < kRows ? (int)(le - r0) : kRows;
         int have = 0;                     // queries waiting in the arrays (the same for all threads)
         __syncthreads();                  // (the previous tile is done with)
         while (qb < q1 || have > 0) {
@@ -656,16 +662,21 @@ __global__ __launch_bounds__(256 * WQ, 4) void measure_kernel(const FilterArgs a
             }
             if (have == 0) break;
             asm volatile("" : "+v"(tid));
-            const int lane = tid & 63, wave = (tid >> 6) & 3, wq = tid >> 8, col = lane & 31, half = lane >> 5;
+            const int lane = tid & 63, wave = (tid >> 6) % WR, wq = (tid >> 6) / WR, col = lane & 31, half = lane >> 5;
             const int nqs = have < kMsrQ ? have : kMsrQ, nq32 = (nqs + 31) >> 5;
             const int nv = nq32 - 2 * wq < 2 ? nq32 - 2 * wq : 2;        // query tiles of this wave
-            // staging: eight threads per row (a whole cache line together), kPer rows each, kApart apart; four per query
+            // staging: eight threads per row (a whole cache line together), kPer rows each, kApart apart; four per query, kQPer each
             const int xr = tid >> 3, xc = tid & 7, sq = tid >> 2, sp = tid & 3;
             float nx[kPer] = {};
             const u4 *q_src = reinterpret_cast<const u4 *>(a.q16_rows);
-            const uint32_t q_at = (uint32_t)s_row[sq < nqs ? sq : 0] * (uint32_t)(a.kpad_rows / 8) + sp;     // (16 bytes)
+            uint32_t q_at[kQPer];              // (16 bytes)
+#pragma unroll
+            for (int i = 0; i < kQPer; ++i) {
+                const int w = sq + kQApart * i;
+                q_at[i] = (uint32_t)s_row[w < nqs ? w : 0] * (uint32_t)(a.kpad_rows / 8) + sp;
+            }
             const unsigned char *x_src = reinterpret_cast<const unsigned char *>(a.base + (size_t)r0 * a.d);
-            struct Ahead { f4 x[kPer]; u4 q; };
+            struct Ahead { f4 x[kPer]; u4 q[kQPer]; };
             auto load = [&](int sl, Ahead &r) {
                 sl = sl < nslice ? sl : nslice - 1;
                 const int k = sl * kFltSlice + 4 * xc;
@@ -675,7 +686,8 @@ __global__ __launch_bounds__(256 * WQ, 4) void measure_kernel(const FilterArgs a
                     const int w = xr + kApart * i;
                     r.x[i] = *reinterpret_cast<const f4 *>(x_src + (uint32_t)((w < nrows ? w : 0) * a.d + (in ? k : 0)) * 4u);
                 }
-                r.q = q_src[q_at + (uint32_t)sl * (kFltSlice / 8)];
+#pragma unroll
+                for (int i = 0; i < kQPer; ++i) r.q[i] = q_src[q_at[i] + (uint32_t)sl * (kFltSlice / 8)];
             };
             auto stage = [&](int sl, const Ahead &r) {
                 const bool in = sl * kFltSlice + 4 * xc < a.d;     // (nothing past the end)
@@ -692,7 +704,8 @@ __global__ __launch_bounds__(256 * WQ, 4) void measure_kernel(const FilterArgs a
                     }
                     *reinterpret_cast<h4 *>(s_x[sl & 1] + ((xc >> 1) * kXRows + xr + kApart * i) * 16 + (xc & 1) * 8) = h;
                 }
-                reinterpret_cast<u4 *>(s_q[sl & 1])[sp * kQStride + sq] = r.q;
+#pragma unroll
+                for (int i = 0; i < kQPer; ++i) reinterpret_cast<u4 *>(s_q[sl & 1])[sp * kQStride + sq + kQApart * i] = r.q[i];
             };
             v16f acc[2][2];
 #pragma unroll
@@ -702,15 +715,15 @@ __global__ __launch_bounds__(256 * WQ, 4) void measure_kernel(const FilterArgs a
 #pragma unroll
                     for (int i = 0; i < 16; ++i) acc[u][v][i] = 0.0f;
             const bool busy = wave * 64 < nrows && nv > 0;
-            Ahead ra, rb;
-            load(0, ra);
-            if constexpr (kSets > 1) load(1, rb);
-            stage(0, ra);
-            load(kSets, ra);
+            Ahead ahead[NS];
+#pragma unroll
+            for (int i = 0; i < NS; ++i) load(i, ahead[i]);
+            stage(0, ahead[0]);
+            load(NS, ahead[0]);
             __syncthreads();
             auto slice = [&](int sl, Ahead &r) {     // r: slice sl + 1
                 stage(sl + 1, r);
-                load(sl + 1 + kSets, r);
+                load(sl + 1 + NS, r);
                 if (busy) {
                     const unsigned char *bb = s_x[sl & 1];
                     const h8 *qq = s_q[sl & 1];
@@ -733,9 +746,12 @@ __global__ __launch_bounds__(256 * WQ, 4) void measure_kernel(const FilterArgs a
                 __syncthreads();
             };
 #pragma unroll 1
-            for (int sl = 0; sl < nslice; sl += 2) {
-                if constexpr (kSets > 1) slice(sl, rb); else slice(sl, ra);
-                slice(sl + 1, ra);
+            for (int sl = 0; sl < nslice; sl += kStep) {
+#pragma unroll
+                for (int u = 0; u < kStep; ++u) {
+                    if (u >= 2 && sl + u >= nslice) break;         // (an even number of slices)
+                    slice(sl + u, ahead[(u + 1) % NS]);
+                }
             }
 #pragma unroll
             for (int i = 0; i < kPer; ++i) {

@@ -101,17 +101,25 @@ int launch_filter(const FilterArgs &a, hipStream_t st) {
 int launch_measure(const FilterArgs &a, hipStream_t st) {
     // 256 queries at a time where a row tile meets that many (rows are then read half as often: 500 queries x 300,000 x
     // 960: 906 -> 547 us), else 128 and two workgroups per CU (2500 queries in 1024 lists, 768: 414 -> 405, 332 -> 285 us).
-    // Without lists the queries are cut finer while there are fewer row tiles than CUs.
-    const int64_t row_tiles = (std::min<int64_t>(a.n, a.hi) + kMsrRows - 1) / kMsrRows;
-    const bool few_rows = !a.list_offsets && row_tiles < 256;
+    // Without lists:
+    //   - 512 queries by 128 rows from 320 queries on, where that makes three tiles for four CUs: 300,000 x 960, 260 queries
+    //     308 -> 338 us, 320 441 -> 353, 400 537 -> 373, 500 555 -> 404, 1000 872 -> 684; 28,672 rows x 500 108 -> 87, 3,584 rows 53 -> 75;
+    //   - otherwise the queries are cut finer while there are fewer row tiles than CUs, and the rows too while all tiles are resident at
+    //     once (500 queries: 612 rows 52 -> 35 us, 3,584 rows 53 -> 36; 11,700 rows, 368 tiles, 43 -> 49).
+    const int64_t hi = std::min<int64_t>(a.n, a.hi), row_tiles = (hi + kMsrRows - 1) / kMsrRows;
+    const int64_t half_tiles = (std::max<int64_t>(hi - a.lo, 0) + kMsrRows / 2 - 1) / (kMsrRows / 2);
     const double share = a.list_offsets ? (double)a.nslots * a.nseg / a.nlist : (double)a.nslots;
+    const bool few_rows = !a.list_offsets && row_tiles < 256;
+    const bool wide = !a.list_offsets && a.nslots >= 320 && half_tiles >= 192 && measure_lds(a.d, 8, 2) <= kLdsBytes;
+    const bool few = few_rows && !wide && half_tiles * ((a.nslots + 127) / 128) <= 256;
     // (the means of more than 21,000 values leave the LDS no room for 256)
-    const int wq = share >= 192.0 && !few_rows && measure_lds(a.d, 4) <= kLdsBytes ? 4 : 2;
+    const int wr = wide || few ? 2 : 4, wq = wide ? 8 : share >= 192.0 && !few_rows && measure_lds(a.d, 4, 4) <= kLdsBytes ? 4 : 2;
     FilterArgs b = a;
-    b.msr_block = few_rows ? 64 * wq : kMsrBlock;
-    void (*fn)(const FilterArgs) = wq == 4 ? measure_kernel<4> : measure_kernel<2>;
+    b.msr_block = few_rows && !wide ? 64 * wq : kMsrBlock;
+    void (*fn)(const FilterArgs) = wide ? measure_kernel<8, 2, 1, 4> : few ? measure_kernel<2, 2, 4, 2> :
+                                   wq == 4 ? measure_kernel<4, 4, 2, 4> : measure_kernel<2, 4, 1, 4>;
     HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, a.d * 4));
-    hipLaunchKernelGGL(fn, dim3(256 * 4), dim3(256 * wq), (size_t)a.d * 4, st, b);
+    hipLaunchKernelGGL(fn, dim3(256 * 4), dim3(64 * wq * wr), (size_t)a.d * 4, st, b);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
 }

@@ -93,10 +93,10 @@ struct InvertArgs {
 // ---- filter: who can pass, on the matrix cores (see filter_kernel) ----
 constexpr int kFltRows = 512, kFltQ = 128, kFltThreads = 512, kFltSlice = 32;
 constexpr int kMsrRows = 256, kMsrBlock = 512;        // measure: rows at a time, queries per task
-// LDS of measure_kernel<wq>: two buffers of rows and of queries (two and four spare per 8 columns), the rows' norms, the
+// LDS of measure_kernel<wq, wr>: two buffers of rows and of queries (two and four spare per 8 columns), the rows' norms, the
 // waiting queries, and the centroids' means.
-constexpr size_t measure_lds(int d, int wq) {
-    return 2 * 4 * ((size_t)(kMsrRows + 2) + 64 * wq + 4) * 16 + 2 * kMsrRows * 4 + 5 * (size_t)(2 * 64 * wq) * 4 + 64 + (size_t)d * 4;
+constexpr size_t measure_lds(int d, int wq, int wr) {
+    return 2 * 4 * ((size_t)(64 * wr + 2) + 64 * wq + 4) * 16 + 2 * 64 * wr * 4 + 5 * (size_t)(2 * 64 * wq) * 4 + 64 + (size_t)d * 4;
 }
 // Values per sub-vector after padding: what a 16-byte operand holds, a part or a multiple of it.
 __host__ __device__ inline int filter_padded(int dsub, bool fs) {

@@ -112,6 +112,13 @@ def test_passes_equal_the_single_kernel(T, case):
         np.testing.assert_array_equal(got["ids"].cpu().numpy(), want["ids"].cpu().numpy())
 
 
+# no lists and rows enough for 512 queries by 128 rows at a time (measure_kernel): queries that fill a block, leave one idle and begin a
+# second, a last tile of a few rows, an uneven number of pairs of slices; the short stretches before take 128 by 128
+@pytest.mark.parametrize("n,d,M,nq,batch", ((30000, 528, 44, 320, 64), (30103, 544, 68, 515, 64), (50000, 600, 120, 512, 1024), (28100, 1024, 32, 319, 64)))
+def test_many_queries_without_lists(T, n, d, M, nq, batch):
+    test_passes_equal_the_single_kernel(T, (n, d, M, 8, 0, nq, 0, 10, batch, 0.3, 0.3, 0.0))
+
+
 # a last tile of one to four blocks of 32 queries (the filter has a loop for each), rows that leave waves of the last row tile idle,
 # an uneven number of code words, sub-vectors of every padded length
 @pytest.mark.parametrize("nq", (288, 320, 350, 384))
