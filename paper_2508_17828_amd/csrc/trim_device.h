@@ -39,10 +39,6 @@ struct Hit {
 // is expanded by the compiler into the approximation plus a correction step.)
 __device__ __forceinline__ float sqrt_rn(float x) { return __builtin_sqrtf(x); }
 
-__device__ __forceinline__ bool hit_less(float d2a, int32_t ida, float d2b, int32_t idb) {
-    return d2a < d2b || (d2a == d2b && ida < idb);
-}
-
 // Squared distance between a query sub-vector held in LDS and a centroid in global memory.
 __device__ __forceinline__ float subvec_sqdist(const float *__restrict__ x,
                                                const float *__restrict__ c, int dsub) {

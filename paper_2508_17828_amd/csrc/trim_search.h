@@ -172,43 +172,45 @@ constexpr int32_t kEmptyId = 0x7fffffff;  // id of an unused slot of R (its d2 i
 // Entries per lane that hold a result set of size k in one wave's registers.
 __host__ __device__ inline int result_slots(int k) { return k <= 64 ? 1 : k <= 128 ? 2 : k <= 256 ? 4 : 16; }
 
-// Merge the refined survivors of a batch into R and publish tau (the "result queue update"
-// of Section 4.2).  Executed by ONE whole wave.  R lives in LDS between calls (64*E
-// entries, ascending by (d2,id), unused slots = (+inf, kEmptyId)); during the call lane l
-// keeps entries l*E .. l*E+E-1 in registers, so an insertion is a ballot (rank), one
-// cross-lane shift and a few selects, with no LDS round trip.
 // The result set R in one wave's registers: 64*E entries ascending by (d2,id), lane l holding
-// entries l*E .. l*E+E-1, unused slots = (+inf, kEmptyId).  R lives in LDS between uses.
+// entries l*E .. l*E+E-1, unused slots = (+inf, kEmptyId).  R lives in LDS between uses.  An entry is one
+// number that orders by (d2, id) (d2 >= 0; what is no number comes last and never enters).
 template <int E>
 struct ResultRegs {
-    float r_d2[E];
-    int32_t r_id[E];
-    float t_d2;      // the k-th entry (tau): +inf while R holds fewer than k entries
-    int32_t t_id;
+    static constexpr unsigned long long kEmptyKey = 0x7f800000ffffffffull;       // key_of(+inf, kEmptyId)
+    unsigned long long r[E];
+    unsigned long long t;      // the k-th entry: kEmptyKey while R holds fewer than k entries
+    float t_d2;                // its distance (tau)
     int k, lane, kl, ks;
 
+    static __device__ __forceinline__ unsigned long long key_of(float d2, int32_t id) {
+        return ((unsigned long long)__float_as_uint(d2) << 32) | ((uint32_t)id ^ 0x80000000u);
+    }
+    __device__ __forceinline__ bool enters(float d2, int32_t id) const { return key_of(d2, id) < t; }
     __device__ __forceinline__ void load(const float *rd2, const int32_t *rid, int k_, int lane_) {
         k = k_; lane = lane_;
         kl = (k - 1) / E; ks = (k - 1) % E;  // lane and slot of the k-th entry
 #pragma unroll
-        for (int s = 0; s < E; ++s) { r_d2[s] = rd2[lane * E + s]; r_id[s] = rid[lane * E + s]; }
+        for (int s = 0; s < E; ++s) r[s] = key_of(rd2[lane * E + s], rid[lane * E + s]);
         load_kth();
     }
     __device__ __forceinline__ void store(float *rd2, int32_t *rid) const {
 #pragma unroll
-        for (int s = 0; s < E; ++s) { rd2[lane * E + s] = r_d2[s]; rid[lane * E + s] = r_id[s]; }
+        for (int s = 0; s < E; ++s) {
+            rd2[lane * E + s] = __uint_as_float((uint32_t)(r[s] >> 32));
+            rid[lane * E + s] = (int32_t)((uint32_t)r[s] ^ 0x80000000u);
+        }
+    }
+    static __device__ __forceinline__ unsigned long long key_at(unsigned long long v, int from) {      // from: the same in all lanes
+        return ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), from) << 32) |
+               (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, from);
     }
     __device__ __forceinline__ void load_kth() {
-        float vd = r_d2[0];
-        int32_t vi = r_id[0];
+        unsigned long long v = r[0];
 #pragma unroll
-        for (int s = 1; s < E; ++s) if (s == ks) { vd = r_d2[s]; vi = r_id[s]; }
-        t_d2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(vd), kl));  // kl is uniform
-        t_id = __builtin_amdgcn_readlane(vi, kl);
-    }
-    // An entry as one number that orders like hit_less (d2 >= 0; empty entries last).
-    static __device__ __forceinline__ unsigned long long key_of(float d2, int32_t id) {
-        return ((unsigned long long)__float_as_uint(d2) << 32) | ((uint32_t)id ^ 0x80000000u);
+        for (int s = 1; s < E; ++s) if (s == ks) v = r[s];
+        t = key_at(v, kl);  // kl is uniform
+        t_d2 = __uint_as_float((uint32_t)(t >> 32));
     }
     template <int BIT>
     static __device__ __forceinline__ unsigned long long key_xor(unsigned long long v) {
@@ -241,8 +243,8 @@ struct ResultRegs {
     }
     // Many items at once: sorted across the lanes, set against the end of R in reverse, and what is
     // the smaller of each pair put back in order (a bitonic merge): 21 + 6 steps whatever their number.
-    __device__ __forceinline__ void merge_items(bool on, float d2, int32_t id) {
-        unsigned long long x = on ? key_of(d2, id) : ~0ull;
+    __device__ __forceinline__ void merge_items(bool on, unsigned long long x) {
+        if (!on) x = ~0ull;
         order_run<2, 1>(x, lane);
         order_run<4, 2>(x, lane);
         order_run<8, 4>(x, lane);
@@ -252,7 +254,7 @@ struct ResultRegs {
         unsigned long long v[E];
 #pragma unroll
         for (int s = 0; s < E; ++s) {
-            v[s] = key_of(r_d2[s], r_id[s]);
+            v[s] = r[s];
             const int j = kWave * E - 1 - (lane * E + s);         // item set against entry lane E + s
             const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)x, j & 63), hi = (uint32_t)__shfl((int)(uint32_t)(x >> 32), j & 63);
             const unsigned long long o = ((unsigned long long)hi << 32) | lo;
@@ -269,70 +271,43 @@ struct ResultRegs {
                     v[s | h] = p < q ? q : p;
                 }
 #pragma unroll
-        for (int s = 0; s < E; ++s) {
-            const bool in = lane * E + s < k;
-            r_d2[s] = in ? __uint_as_float((uint32_t)(v[s] >> 32)) : __builtin_inff();
-            r_id[s] = in ? (int32_t)((uint32_t)v[s] ^ 0x80000000u) : kEmptyId;
-        }
+        for (int s = 0; s < E; ++s) r[s] = lane * E + s < k ? v[s] : kEmptyKey;
         load_kth();
     }
-    // One item that beats the k-th entry, the same in all lanes.  (What is shifted beyond the k-th place stays there: nobody
-    // looks at it, and it is not below the k-th.)
-    __device__ __forceinline__ void insert(float xd2, int32_t xid) {
-        int rank = 0;
-#pragma unroll
-        for (int s = 0; s < E; ++s) rank += __popcll(__ballot(!hit_less(xd2, xid, r_d2[s], r_id[s])));
-        const float c_d2 = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(r_d2[E - 1]), 0x138, 0xf, 0xf, false));
-        const int32_t c_id = __builtin_amdgcn_update_dpp(0, r_id[E - 1], 0x138, 0xf, 0xf, false);
+    // One item that beats the k-th entry, the same in all lanes: an entry becomes the lesser of itself and the greater of the item and the
+    // entry before it.  No ranks, whose ballots go through the scalar unit: 10,000 queries over 1M x 128 1253 -> 1231 us, 4-bit codes
+    // 488 -> 476, 500 queries x 300,000 x 960, k = 100, 2141 -> 2111.  (What is shifted beyond the k-th place stays there: nobody looks at it, and it is not below the k-th.)
+    __device__ __forceinline__ void insert(unsigned long long x) {
+        // last slot of the lane below (whole-wave shift right by one lane; lane 0: below every item)
+        const unsigned long long c = ((unsigned long long)(uint32_t)__builtin_amdgcn_update_dpp(0, (int)(r[E - 1] >> 32), 0x138, 0xf, 0xf, false) << 32) |
+                                     (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)r[E - 1], 0x138, 0xf, 0xf, false);
 #pragma unroll
         for (int s = E - 1; s >= 0; --s) {
-            const int g = lane * E + s;
-            const float p_d2 = s > 0 ? r_d2[s > 0 ? s - 1 : 0] : c_d2;
-            const int32_t p_id = s > 0 ? r_id[s > 0 ? s - 1 : 0] : c_id;
-            r_d2[s] = g == rank ? xd2 : g > rank ? p_d2 : r_d2[s];
-            r_id[s] = g == rank ? xid : g > rank ? p_id : r_id[s];
+            const unsigned long long before = s > 0 ? r[s > 0 ? s - 1 : 0] : c, m = before < x ? x : before;
+            r[s] = m < r[s] ? m : r[s];
         }
         load_kth();
     }
     // Insert the lanes' items (one per lane with `pending` set) that beat the k-th entry, one at
-    // a time: an insertion is a ballot (rank), one cross-lane shift and a few selects.  Many of them
+    // a time: an insertion is a cross-lane shift, two compares and two selects per entry.  Many of them
     // (kMergeFrom, where a merge costs what that many insertions do) are merged instead.  One entry per
     // lane: few enough come at a time, and the kernels with 80 registers were 4% slower with the code in
     // them; result sets beyond 256: registers.
     static constexpr int kMergeFrom = 8;
     __device__ __forceinline__ void insert_pending(bool pending, float d2, int32_t id) {
+        const unsigned long long key = key_of(d2, id);
         for (;;) {
-            const unsigned long long m = __ballot(pending && hit_less(d2, id, t_d2, t_id));
+            const unsigned long long m = __ballot(pending && key < t);
             if (m == 0) break;
             if constexpr (E == 2 || E == 4) {
                 if (__popcll(m) >= kMergeFrom) {
-                    merge_items(pending && hit_less(d2, id, t_d2, t_id), d2, id);
+                    merge_items(pending && key < t, key);
                     break;
                 }
             }
-            const int src = __ffsll((long long)m) - 1;
-            const float xd2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d2), src));
-            const int32_t xid = __builtin_amdgcn_readlane(id, src);  // src is the same in all lanes
+            const int src = __ffsll((long long)m) - 1;  // the same in all lanes
             if (lane == src) pending = false;
-            // rank = number of entries that are not greater than the item (a prefix of R)
-            int rank = 0;
-#pragma unroll
-            for (int s = 0; s < E; ++s)
-                rank += __popcll(__ballot(!hit_less(xd2, xid, r_d2[s], r_id[s])));
-            // last slot of the lane below (whole-wave shift right by one lane; lane 0 unused)
-            const float c_d2 = __int_as_float(
-                __builtin_amdgcn_update_dpp(0, __float_as_int(r_d2[E - 1]), 0x138, 0xf, 0xf, false));
-            const int32_t c_id = __builtin_amdgcn_update_dpp(0, r_id[E - 1], 0x138, 0xf, 0xf, false);
-#pragma unroll
-            for (int s = E - 1; s >= 0; --s) {
-                const int g = lane * E + s;
-                const float p_d2 = s > 0 ? r_d2[s > 0 ? s - 1 : 0] : c_d2;
-                const int32_t p_id = s > 0 ? r_id[s > 0 ? s - 1 : 0] : c_id;
-                if (g == rank) { r_d2[s] = xd2; r_id[s] = xid; }
-                else if (g > rank) { r_d2[s] = p_d2; r_id[s] = p_id; }
-                if (g >= k) { r_d2[s] = __builtin_inff(); r_id[s] = kEmptyId; }
-            }
-            load_kth();
+            insert(key_at(key, src));
         }
     }
 };
@@ -464,7 +439,7 @@ __device__ __forceinline__ int replay_batches(const int32_t *s_cl, const float *
             // Only an entry that also beats the k-th distance changes anything.  Up to the first
             // such entry (in batch order) every pending entry is a survivor of a batch whose
             // threshold is the current k-th distance: counted and marked in one go.
-            const unsigned long long mi = __ballot(pending && hit_less(d2, id, R.t_d2, R.t_id));
+            const unsigned long long mi = __ballot(pending && R.enters(d2, id));
             int fb = 0x7fffffff;
             if (mi != 0) fb = __builtin_amdgcn_readlane(b, __ffsll((long long)mi) - 1);
             const bool plain = pending && b < fb;

@@ -147,7 +147,7 @@ __device__ __forceinline__ int replay_entries(ResultRegs<E> &R, int &frozen_b, f
         for (;;) {
             // (see replay_batches: survivors that do not beat the k-th distance are taken all at once)
             pending = pending && g <= (b == frozen_b ? tau_f : R.t_d2);
-            const unsigned long long mi = __ballot(pending && hit_less(d2, id, R.t_d2, R.t_id));
+            const unsigned long long mi = __ballot(pending && R.enters(d2, id));
             int fb = 0x7fffffff;
             if (mi != 0) fb = __builtin_amdgcn_readlane(b, __ffsll((long long)mi) - 1);
             const bool plain = pending && b < fb;
@@ -184,26 +184,25 @@ __device__ __forceinline__ void replay_measured(ResultRegs<E> &R, int &frozen_b,
         bool pending = i0 + R.lane < n;
         const int i = pending ? order[i0 + R.lane] : 0;
         int b = 0x7fffffff;
-        float g = __builtin_inff(), d2 = __builtin_inff();
-        int32_t id = 0;
+        float g = __builtin_inff();
+        unsigned long long key = ~0ull;
         if (pending) {
             const int cl = s_cl[i];
-            g = s_g[i]; d2 = s_d2[i]; id = s_id[i];
+            g = s_g[i]; key = R.key_of(s_d2[i], s_id[i]);
             b = cl < R.k ? -1 : (cl - R.k) / batch;
             if (b < 0) g = -__builtin_inff();
         }
         // (who does not beat the k-th distance now never will: it only falls)
-        unsigned long long left = __ballot(pending && g <= (b == frozen_b ? tau_f : R.t_d2) && hit_less(d2, id, R.t_d2, R.t_id));
+        unsigned long long left = __ballot(pending && g <= (b == frozen_b ? tau_f : R.t_d2) && key < R.t);
         while (left) {
             const int src = __ffsll((long long)left) - 1;
             left &= left - 1;
             const int xb = __builtin_amdgcn_readlane(b, src);
-            const int32_t xid = __builtin_amdgcn_readlane(id, src);
             const float xg = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g), src));
-            const float xd2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d2), src));
             if (xb != frozen_b) { frozen_b = xb; tau_f = R.t_d2; }
-            if (!(xg <= tau_f) || !hit_less(xd2, xid, R.t_d2, R.t_id)) continue;
-            R.insert(xd2, xid);
+            if (!(xg <= tau_f)) continue;
+            R.insert(R.key_at(key, src));
+            left &= __ballot(key < R.t);
             if (xb != last_b) { last_b = xb; ++out.count; }
             if (R.lane == 0) steps[out.count - 1] = ((unsigned long long)(uint32_t)xb << 32) | __float_as_uint(R.t_d2);
         }
