@@ -58,11 +58,12 @@ constexpr int kSpanLong = 4096;   // kNN span target when the table leaves one w
 constexpr int kMaxBatchesPerSpan = 1024;
 constexpr int kPossMin = 512;    // smallest possibles list worth cruising with
 constexpr int kPossMax = 2048;
+constexpr int64_t kCus = 256;
 
 // Block size and LDS bytes per workgroup for 4, 3, 2 and 1 workgroups per CU (LDS is handed
 // out in 1280-byte granules).  Three 512-thread workgroups, or two of 768 threads, are 6 waves
-// per SIMD: only the kernel instances built for that register budget (result_slots == 1) can use
-// those tiers.  The second is for tables too long for three workgroups (M = 40..60): with 24
+// per SIMD: only the kernel instances built for that register budget (result_slots <= 2) can use
+// those tiers (k = 100, 8000 queries, 32 of 1024 lists: 1M x 128, M = 32, 1745 -> 1244 us; 500,000 x 384, M = 48, 64 lists, 2032 -> 1760).  The second is for tables too long for three workgroups (M = 40..60): with 24
 // instead of 16 waves per CU more rows and code blocks are in flight (5M x 384, M = 48: the
 // scan went 5.06 -> 4.70 ms); it is kept to codes under 64 bytes, which the 80-register
 // instance is the better one for anyway.
@@ -157,7 +158,7 @@ bool fit_plan(int d, int M, int row_bytes, int nsegs, int cap, int batch, int k,
 }
 
 // M counts code bytes; fs: 4-bit codes (two subspaces of 16 centroids per byte), else 8-bit.
-bool make_plan(int d, int M, bool fs, int nseg, int cap, int batch, int k, bool range, Plan *pl) {
+bool make_plan(int d, int M, bool fs, int nseg, int cap, int batch, int k, bool range, int64_t nq, Plan *pl) {
     if (d <= 0 || M <= 0 || d % 4 || M % 4) return false;
     if (fs ? (d % (2 * M) || M % 8 || d / (2 * M) > 64) : (d % M || d / M > 64)) return false;
     const int row_bytes = fs ? (int)kByteRow<true> : (int)kByteRow<false>;
@@ -172,11 +173,17 @@ bool make_plan(int d, int M, bool fs, int nseg, int cap, int batch, int k, bool 
         if (M % P || (M / P) % 4) continue;
         for (int t = 0; t < nt; ++t) {
             const Tier &tier = kTiers[t];
-            if (tier.needs_6_waves && (range || result_slots(k) != 1)) continue;
+            if (tier.needs_6_waves && (range || result_slots(k) > 2)) continue;
             if (tier.short_codes_only && M >= 64) continue;
-            // a short table would fit four small workgroups per CU (16 waves); the instance built
-            // for six waves per SIMD does better as three 512-thread ones (24 waves)
-            if (t == 0 && !range && result_slots(k) == 1 && fs) continue;
+            // A short table would fit four small workgroups per CU (16 waves); the instance built
+            // for six waves per SIMD does better as three 512-thread ones (24 waves), which also have twice the threads for
+            // a query where all are resident at once.  1.18M x 100, M = 20, 32 of 1024 lists, k = 10: 600 queries 333 -> 230 us, 1500
+            // 609 -> 425, 8000 2266 -> 1841; k = 100: 300 366 -> 260, 8000 2554 -> 2137; M = 16, k = 10: 167 -> 122, 8000 771 -> 740.
+            // Not between 768 and 1024 queries, which four a CU take in one go (M = 16, batches of 256, 1000 queries: 169 / 211, k = 100
+            // 282 / 303), and not for two result entries per lane and 4-bit codes beyond that (8000 queries 1040 / 1082).
+            const bool one_go = nq > 3 * kCus && nq <= 4 * kCus;
+            if (t == 0 && !range && result_slots(k) <= 2 &&
+                (nq <= 3 * kCus || (fs ? result_slots(k) == 1 : !one_go))) continue;
             if (t + 1 < nt) {
                 // below the last tier a layout must leave room for a cruise when one is possible
                 // at all (else the next tier is tried first)
@@ -211,7 +218,10 @@ int launch_search(bool range, bool fs, const SearchArgs &a, const Plan &pl, dim3
             if (pl.lean == kLeanLongRows) return fs ? launch_search_knnleanlong_e1_c4(a, pl, grid, st) : launch_search_knnleanlong_e1_c8(a, pl, grid, st);
             if (pl.lean) return fs ? launch_search_knnlean_e1_c4(a, pl, grid, st) : launch_search_knnlean_e1_c8(a, pl, grid, st);
             return fs ? launch_search_knn_e1_c4(a, pl, grid, st) : launch_search_knn_e1_c8(a, pl, grid, st);
-        case 2: return fs ? launch_search_knn_e2_c4(a, pl, grid, st) : launch_search_knn_e2_c8(a, pl, grid, st);
+        case 2:
+            if (pl.lean == kLeanLongRows) return fs ? launch_search_knnleanlong_e2_c4(a, pl, grid, st) : launch_search_knnleanlong_e2_c8(a, pl, grid, st);
+            if (pl.lean) return fs ? launch_search_knnlean_e2_c4(a, pl, grid, st) : launch_search_knnlean_e2_c8(a, pl, grid, st);
+            return fs ? launch_search_knn_e2_c4(a, pl, grid, st) : launch_search_knn_e2_c8(a, pl, grid, st);
         case 4: return fs ? launch_search_knn_e4_c4(a, pl, grid, st) : launch_search_knn_e4_c8(a, pl, grid, st);
         default: return fs ? launch_search_knn_e16_c4(a, pl, grid, st) : launch_search_knn_e16_c8(a, pl, grid, st);
     }
@@ -1058,7 +1068,7 @@ int search_knn(const trim_index_view *index, const float *queries, int64_t nq, c
     if (survivor_mask && mask_words <= 0) return TRIM_INVALID_ARG;
     Plan pl;
     const int cap = batch > k ? batch : k;
-    if (!make_plan(index->d, code_bytes(index), is_fs(index), cand ? cand->nprobe : 0, cap, batch, k, false, &pl))
+    if (!make_plan(index->d, code_bytes(index), is_fs(index), cand ? cand->nprobe : 0, cap, batch, k, false, nq, &pl))
         return TRIM_UNSUPPORTED_SHAPE;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (survivor_mask && (rc = fill_u32(survivor_mask, (size_t)nq * mask_words, 0u, st))) return rc;
@@ -1143,7 +1153,7 @@ int range_search(const trim_index_view *index, const float *queries, int64_t nq,
     if (!workspace || workspace_bytes < L.total || (reinterpret_cast<uintptr_t>(workspace) & 255u))
         return TRIM_WORKSPACE;
     Plan pl;
-    if (!make_plan(index->d, code_bytes(index), is_fs(index), cand ? cand->nprobe : 0, kRangeRound, kRangeRound, 1, true, &pl))
+    if (!make_plan(index->d, code_bytes(index), is_fs(index), cand ? cand->nprobe : 0, kRangeRound, kRangeRound, 1, true, nq, &pl))
         return TRIM_UNSUPPORTED_SHAPE;
 
     unsigned char *ws = static_cast<unsigned char *>(workspace);
@@ -1326,13 +1336,13 @@ extern "C" {
 int trim_shape_supported(int32_t d, int32_t M) {
     Plan pl;
     if (d <= 0 || M <= 0 || d % M) return 0;
-    return make_plan(d, M, false, 64, 2048, 2048, 10, true, &pl) ? 1 : 0;
+    return make_plan(d, M, false, 64, 2048, 2048, 10, true, 1, &pl) ? 1 : 0;
 }
 
 int trim_fs_shape_supported(int32_t d, int32_t M) {
     Plan pl;
     if (d <= 0 || M <= 0 || M % 2 || d % M) return 0;
-    return make_plan(d, M / 2, true, 64, 2048, 2048, 10, true, &pl) ? 1 : 0;
+    return make_plan(d, M / 2, true, 64, 2048, 2048, 10, true, 1, &pl) ? 1 : 0;
 }
 
 int trim_encode(const float *base, int64_t n, int32_t d, const float *codebooks, int32_t M,

@@ -706,3 +706,23 @@ def test_captured_and_replayed(T, nq):
         want += [offsets, rids[:total], rd2[:total]]
         for a, b in zip(got, want):
             assert torch.equal(a, b), rep
+
+
+# one and two result entries per lane at their edges, codes with and without a scan head, query counts at which another block size is taken
+# (make_plan): who asks beside them changes nobody's answer, and the first are the oracle's
+@pytest.mark.parametrize("d,M,bits", ((100, 20, 8), (128, 16, 8), (128, 32, 8), (384, 48, 8), (128, 64, 4)))
+@pytest.mark.parametrize("k,batch", ((64, 256), (65, 100), (128, 512)))
+def test_answers_do_not_depend_on_the_number_of_queries(T, d, M, bits, k, batch):
+    ix, q, probes = built(T, 20000, d, M, bits, 40, 1100, 9, 1.0, 2.0, d + M + k)
+    want = single_kernel(T, ix, q, k, 0.3, batch, probes, None)
+    for nq in (20, 256, 257, 512, 513, 768, 769, 1024, 1025):
+        got = single_kernel(T, ix, q[:nq], k, 0.3, batch, probes[:nq].contiguous(), None)
+        for name in ("ids", "d2", "n_scanned", "n_exact", "mask"):
+            np.testing.assert_array_equal(got[name].cpu().numpy(), want[name][:nq].cpu().numpy(), err_msg=f"{name} {nq}")
+    c = lambda t: t.cpu().numpy()
+    from oracle import trim_oracle, trim_oracle_fs
+    o = trim_oracle if bits == 8 else trim_oracle_fs
+    oix = o.Index(c(ix.base), c(ix.codes), c(ix.dlx), c(ix.codebooks), ids=c(ix.ids), list_offsets=c(ix.list_offsets))
+    ref = o.search_knn(oix, c(q[:20]), k, 0.3, batch, c(probes[:20]))
+    np.testing.assert_array_equal(c(want["ids"][:20]), ref["ids"])
+    np.testing.assert_array_equal(c(want["n_exact"][:20]), ref["n_exact"])
