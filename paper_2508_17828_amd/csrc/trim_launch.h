@@ -60,10 +60,6 @@ int launch_settle(FewArgs a, hipStream_t st);
 int launch_replay(ReplayArgs a, int64_t nslots, hipStream_t st);
 
 TRIM_DECLARE_LAUNCH(launch_search_knnlean_e1_c8);
-TRIM_DECLARE_LAUNCH(launch_search_knnlean_e2_c8);
-TRIM_DECLARE_LAUNCH(launch_search_knnlean_e2_c4);
-TRIM_DECLARE_LAUNCH(launch_search_knnleanlong_e2_c8);
-TRIM_DECLARE_LAUNCH(launch_search_knnleanlong_e2_c4);
 TRIM_DECLARE_LAUNCH(launch_search_knnlean_e1_c4);
 TRIM_DECLARE_LAUNCH(launch_search_knnleanlong_e1_c8);
 TRIM_DECLARE_LAUNCH(launch_search_knnleanlong_e1_c4);
