@@ -224,11 +224,14 @@ struct ResultRegs {
         }
         return ((unsigned long long)hi << 32) | lo;
     }
-    // One compare-exchange of a bitonic network with lane ^ BIT.
+    // One compare-exchange of a bitonic network with lane ^ BIT: one compare, its mask against the lanes that keep the lesser, two selects
+    // (of equal ones it does not matter which).  Said with two compares it became a branch a step: 1000 queries over 1.18M x 100,
+    // k = 100, 484 -> 458 us.
     template <int BIT>
     static __device__ __forceinline__ void order_step(unsigned long long &v, bool up, int lane) {
         const unsigned long long o = key_xor<BIT>(v);
-        if (((lane & BIT) == 0) == up ? o < v : o > v) v = o;
+        const bool lesser = ((lane & BIT) == 0) == up;
+        v = (o < v) == lesser ? o : v;
     }
     template <int SIZE, int BIT>
     static __device__ __forceinline__ void order_run(unsigned long long &v, int lane) {
