@@ -71,7 +71,7 @@ __global__ __launch_bounds__(512) void assign_operands_kernel(const float *__res
         if (lane == 0) s_top[tid >> 6] = top;
     }
     if (tid == 0) s_cmax = s_mmax = 0;
-    __syncthreads();
+    sync_block();
     const uint32_t top = max(s_top[0], s_top[1]);
     const bool usable = __uint_as_float(top) > 1e-30f && __uint_as_float(top) < 1e30f;
     const float sc = __uint_as_float((uint32_t)((usable ? 6 - ((int)(top >> 23) - 127) : 0) + 127) << 23);     // (the spread: 2^6 .. 2^7)
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(512) void assign_operands_kernel(const float *__res
         }
         *reinterpret_cast<h8 *>(to + 2 * KS * Shape::kRows + s_row) = f;
     }
-    __syncthreads();
+    sync_block();
     if (tid == 0) { most_of[2 * st] = s_cmax; most_of[2 * st + 1] = s_mmax; }
 }
 
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(kAstThreads, 4) void assign_tiles_kernel(const floa
     fetch(0);
     if (lane == 0) s_np[wave] = 0;
     if (half == 0) s_best[wave * 32 + col] = ~0ull;
-    __syncthreads();
+    sync_block();
     place(0);
     fetch(nst > 1 ? 1 : 0);
     // a vector per column from here on, in both half waves
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(kAstThreads, 4) void assign_tiles_kernel(const floa
     const uint32_t number = (1u << bits) - 1u;
 #pragma unroll 1
     for (int st = 0; st < nst; ++st) {
-        __syncthreads();
+        sync_block();
         if (st + 1 < nst) {
             place((st + 1) & 1);
             fetch(st + 2 < nst ? st + 2 : nst - 1);

@@ -54,7 +54,7 @@ __global__ __launch_bounds__(512) void stream_read_kernel(const uint4 *__restric
     for (int off = 32; off > 0; off >>= 1) acc ^= __shfl_xor(acc, off);
     __shared__ uint32_t part[8];
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
-    __syncthreads();
+    sync_block();
     if (threadIdx.x == 0) {
         uint32_t r = 0;
         for (int w = 0; w < (int)(blockDim.x >> 6); ++w) r ^= part[w];
@@ -71,7 +71,7 @@ __global__ __launch_bounds__(512) void lds_gather_kernel(int iters, uint32_t see
     extern __shared__ __align__(16) unsigned char smem[];
     float *tab = reinterpret_cast<float *>(smem);  // [32][256]
     for (int i = threadIdx.x; i < 32 * kC; i += blockDim.x) tab[i] = (float)((i * 2654435761u) >> 20);
-    __syncthreads();
+    sync_block();
     const uint32_t tab_base = lds_addr(tab);
     uint32_t w[8];
     uint32_t h = seed ^ ((blockIdx.x * 512u + threadIdx.x) * 0x9e3779b9u);
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(512) void lds_gather_fs_kernel(int iters, uint32_t 
     extern __shared__ __align__(16) unsigned char smem[];
     float *tab = reinterpret_cast<float *>(smem);  // [64][16]
     for (int i = threadIdx.x; i < 64 * kC4; i += blockDim.x) tab[i] = (float)((i * 2654435761u) >> 20);
-    __syncthreads();
+    sync_block();
     const uint32_t tab_base = lds_addr(tab);
     uint32_t w[8];
     uint32_t h = seed ^ ((blockIdx.x * 512u + threadIdx.x) * 0x9e3779b9u);
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(512) void lds_gather_wide_kernel(int iters, uint32_
     extern __shared__ __align__(16) unsigned char smem[];
     float *tab = reinterpret_cast<float *>(smem);  // [8][256][W]
     for (int i = threadIdx.x; i < 8 * kC * W; i += blockDim.x) tab[i] = (float)(i & 1023);
-    __syncthreads();
+    sync_block();
     uint32_t h = seed ^ ((blockIdx.x * 512u + threadIdx.x) * 0x9e3779b9u);
     h ^= h << 13; h ^= h >> 17; h ^= h << 5;
     uint32_t w0 = h;
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(T) void list_bounds_kernel(const uint8_t *__restric
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) bmax = fmaxf(bmax, __shfl_xor(bmax, off));
     if (lane == 0) red[tid >> 6] = bmax;
-    __syncthreads();
+    sync_block();
     if (tid == 0) {
         for (int w = 1; w < T / kWave; ++w) bmax = fmaxf(bmax, red[w]);
         *reinterpret_cast<float *>(rec + list_record_bmax_offset(M)) = bmax;
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(T) void list_bounds_kernel(const uint8_t *__restric
             if (!(have[i] >> (c & 31) & 1u)) atomicOr(&bits[(j[i >> 2] + (i & 3)) * kBoundsPitch + (c >> 5)], 1u << (c & 31));
         }
     }
-    __syncthreads();
+    sync_block();
     for (int j = tid >> 6; j < M; j += T >> 6) {   // one wave per subspace
         const uint32_t nib = (bits[j * kBoundsPitch + (lane >> 3)] >> ((lane & 7) * 4)) & 15u;  // codes 4*lane..4*lane+3
         const int cnt = __popc(nib);
@@ -384,7 +384,7 @@ __global__ __launch_bounds__(kUpdThreads, LIST < kUpdList ? 4 : 1) void kmeans_u
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }
-        __syncthreads();
+        sync_block();
         if (wave == 0) {                                 // counts -> first slots
             int n[kWaves], run = 0;
 #pragma unroll
@@ -405,11 +405,11 @@ __global__ __launch_bounds__(kUpdThreads, LIST < kUpdList ? 4 : 1) void kmeans_u
                 for (int v = 0; v < kWaves; ++v) wcount[v * CG + lane] = n[v] + incl - run;
             }
         }
-        __syncthreads();
+        sync_block();
 #pragma unroll
         for (int s = 0; s < kLoops; ++s)
             if (rank[s] >= 0) f(s0 + s * kWave + lane, mem[s], mine[mem[s] & 31u] + rank[s]);
-        __syncthreads();
+        sync_block();
     };
     // the rows in list[0 .. found) are added
     auto add_rows = [&]() {
@@ -434,7 +434,7 @@ __global__ __launch_bounds__(kUpdThreads, LIST < kUpdList ? 4 : 1) void kmeans_u
                 }
                 sums[e] = sum;
             }
-            __syncthreads();
+            sync_block();
             return;
         }
         // Short rows: read in row order, so that workgroups of neighbouring subspaces, whose columns share cache lines, read a
@@ -462,7 +462,7 @@ __global__ __launch_bounds__(kUpdThreads, LIST < kUpdList ? 4 : 1) void kmeans_u
                     else to[e - i * g4] = v[u].x;
                 }
             }
-            __syncthreads();
+            sync_block();
             for (int e = tid; e < CG * cols; e += kUpdThreads) {
                 const int c = e / cols, t = e - c * cols;
                 int i = start[c];
@@ -482,7 +482,7 @@ __global__ __launch_bounds__(kUpdThreads, LIST < kUpdList ? 4 : 1) void kmeans_u
                 for (; i < hi; ++i, v += cols) sum += (double)*v;
                 sums[e] = sum;
             }
-            __syncthreads();
+            sync_block();
         }
     };
     constexpr int kWords = 4 * ABYTES;
@@ -505,7 +505,7 @@ __global__ __launch_bounds__(kUpdThreads, LIST < kUpdList ? 4 : 1) void kmeans_u
     };
     const uint32_t pattern = (uint32_t)c_first * 0x01010101u, group_bits = (uint32_t)(0xff & ~(CG - 1)) * 0x01010101u;
     load_chunk(0);
-    __syncthreads();
+    sync_block();
     for (int64_t i0 = 0; i0 < a.ns; i0 += kUpdChunk) {
         uint32_t w[kWords], in = 0;               // this lane's rows: assignments, and a bit for each of the group's
 #pragma unroll
@@ -531,7 +531,7 @@ __global__ __launch_bounds__(kUpdThreads, LIST < kUpdList ? 4 : 1) void kmeans_u
             total += __popcll(m) << b;
         }
         if (lane == 0) part[wave] = total;
-        __syncthreads();
+        sync_block();
         int n = part[lane & (kWaves - 1)];        // the waves' prefix, in every wave
         int incl = n;
 #pragma unroll
@@ -560,7 +560,7 @@ __global__ __launch_bounds__(kUpdThreads, LIST < kUpdList ? 4 : 1) void kmeans_u
                     list[to++] = (r + i) << 5 | (c & (uint32_t)(CG - 1));
                 }
                 found += all;
-                __syncthreads();
+                sync_block();
             }
             if (!fits || i0 + kUpdChunk >= a.ns) {
                 if (found > 0) add_rows();
@@ -645,23 +645,23 @@ __device__ uint32_t key_of_rank(const uint32_t *keys, int count, int rank, int *
     __shared__ int part[T / kWave];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
     if (tid == 0) { s_lo = 0xffffffffu; s_hi = 0u; s_rank = rank; }
-    __syncthreads();
+    sync_block();
     uint32_t mn = 0xffffffffu, mx = 0u;
     for (int i = tid; i < count; i += T) { const uint32_t k = keys[i]; mn = k < mn ? k : mn; mx = k > mx ? k : mx; }
     atomicMin(&s_lo, mn);
     atomicMax(&s_hi, mx);
-    __syncthreads();
+    sync_block();
     uint32_t lo = s_lo, hi = s_hi;
     while (lo < hi) {
         const int bits = 32 - __builtin_clz(hi - lo);
         const int sh = bits > 11 ? bits - 11 : 0;      // (hi - lo) >> sh < 2048
         for (int b = tid; b < kGammaBins; b += T) hist[b] = 0;
-        __syncthreads();
+        sync_block();
         for (int i = tid; i < count; i += T) {
             const uint32_t k = keys[i];
             if (k >= lo && k <= hi) atomicAdd(&hist[(k - lo) >> sh], 1);
         }
-        __syncthreads();
+        sync_block();
         // the bin of the rank: a few bins per thread, prefix over the lanes, then over the waves
         int h[kPer], sum = 0;
 #pragma unroll
@@ -674,7 +674,7 @@ __device__ uint32_t key_of_rank(const uint32_t *keys, int count, int rank, int *
         }
         if (lane == kWave - 1) part[wave] = incl;
         const int want = s_rank;
-        __syncthreads();
+        sync_block();
         int before = incl - sum;
         for (int w = 0; w < wave; ++w) before += part[w];
 #pragma unroll
@@ -682,17 +682,17 @@ __device__ uint32_t key_of_rank(const uint32_t *keys, int count, int rank, int *
             if (want >= before && want < before + h[i]) { s_bin = kPer * tid + i; s_rank = want - before; s_lo = 0xffffffffu; s_hi = 0u; }
             before += h[i];
         }
-        __syncthreads();
+        sync_block();
         const uint32_t bin = s_bin;
         for (int i = tid; i < count; i += T) {
             const uint32_t k = keys[i];
             if (k >= lo && k <= hi && (k - lo) >> sh == bin) { atomicMin(&s_lo, k); atomicMax(&s_hi, k); }
         }
-        __syncthreads();
+        sync_block();
         lo = s_lo;
         hi = s_hi;
     }
-    __syncthreads();
+    sync_block();
     return lo;
 }
 
@@ -708,7 +708,7 @@ __global__ __launch_bounds__(kGammaThreads) void gamma_kernel(const GammaArgs a)
     const int s0 = blockIdx.x * kGammaRows;
     const int dsub = a.d / a.M;
     if (tid < kGammaRows) norm2[tid] = 0.0f;
-    __syncthreads();
+    sync_block();
 #pragma unroll
     for (int x = 0; x < kGammaRows; ++x) {
         int64_t r = a.rows[s0 + x < a.S ? s0 + x : s0];
@@ -725,13 +725,13 @@ __global__ __launch_bounds__(kGammaThreads) void gamma_kernel(const GammaArgs a)
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) p += __shfl_xor(p, off);
         if (lane == 0) part[wave] = __float_as_int(p);
-        __syncthreads();
+        sync_block();
         if (tid == 0) {
             float sum = 0.0f;
             for (int w = 0; w < kGammaThreads / kWave; ++w) sum += __int_as_float(part[w]);
             norm2[x] = sum;
         }
-        __syncthreads();
+        sync_block();
     }
     const int lane32 = tid & 31;
     const int ng = a.d >> 2;
@@ -765,7 +765,7 @@ __global__ __launch_bounds__(kGammaThreads) void gamma_kernel(const GammaArgs a)
         const int qi = q0 + (mine & 7);
         if (!(mine & 8) && qi < a.Q) keys[(size_t)(mine >> 4) * a.Q + qi] = gamma_key(sum, nn, nu);
     }
-    __syncthreads();
+    sync_block();
     for (int x = 0; x < kGammaRows && s0 + x < a.S; ++x) {
         const uint32_t k = key_of_rank<kGammaThreads>(keys + (size_t)x * a.Q, a.Q, a.rank, hist);
         if (tid == 0) gamma_store(a, s0 + x, k);
@@ -825,10 +825,10 @@ __global__ __launch_bounds__(256) void gamma_normal_kernel(const GammaNormalArgs
         ul += ut * lt; uu += ut * ut; ll += lt * lt;
     }
     red[0][tid] = ul; red[1][tid] = uu; red[2][tid] = ll;
-    __syncthreads();
+    sync_block();
     for (int h = 128; h > 0; h >>= 1) {
         if (tid < h) { red[0][tid] += red[0][tid + h]; red[1][tid] += red[1][tid + h]; red[2][tid] += red[2][tid + h]; }
-        __syncthreads();
+        sync_block();
     }
     // a vector equal to its landmark has no angle: 1 - Z counts as 1 for every query (cos = 0)
     const bool no_angle = !(red[1][0] > 0.0);
@@ -844,7 +844,7 @@ __global__ __launch_bounds__(256) void gamma_normal_kernel(const GammaNormalArgs
         }
         z2[i] = v;
     }
-    __syncthreads();
+    sync_block();
     for (int k = 2; k <= a.npow2; k <<= 1) {
         for (int j = k >> 1; j > 0; j >>= 1) {
             for (int i = tid; i < a.npow2; i += blockDim.x) {
@@ -855,7 +855,7 @@ __global__ __launch_bounds__(256) void gamma_normal_kernel(const GammaNormalArgs
                     if ((x > y) == up) { z2[i] = y; z2[p] = x; }
                 }
             }
-            __syncthreads();
+            sync_block();
         }
     }
     if (tid == 0) {
@@ -1038,12 +1038,12 @@ __global__ __launch_bounds__(T, 4) void encode_mfma_kernel(const float *__restri
         fetch(jlo + mine);
         measure(jlo + mine);
     }
-    __syncthreads();
+    sync_block();
     if (mine == 0) {
         operands(jlo);
         if (jlo + GROUPS < jhi) fetch(jlo + GROUPS);
     }
-    __syncthreads();
+    sync_block();
     float tot = 0.0f;
     for (int j0 = jlo; j0 < jhi; j0 += 4) {
         uint32_t packed = 0;
@@ -1163,11 +1163,11 @@ __global__ __launch_bounds__(T, 4) void encode_mfma_kernel(const float *__restri
             } else {
                 packed |= (uint32_t)arg << (8 * jj);
             }
-            __syncthreads();
+            sync_block();
             if constexpr (GROUPS == 1) {
                 if (j + 1 < jhi) operands(j + 1);
                 if (j + 2 < jhi) fetch(j + 2);
-                __syncthreads();
+                sync_block();
             }
         }
         if constexpr (!ACROSS)
@@ -1199,10 +1199,10 @@ __global__ __launch_bounds__(256) void encode_dlx_kernel(const float *__restrict
             }
             part[r * (kDlxSub + 1) + j] = acc < __builtin_inff() ? acc : __builtin_inff();     // (the least distance begins at infinity: no NaN)
         }
-        __syncthreads();
+        sync_block();
         if (threadIdx.x < kDlxRows)
             for (int j = 0; j < nj; ++j) tot = tot + part[threadIdx.x * (kDlxSub + 1) + j];
-        __syncthreads();
+        sync_block();
     }
     if (threadIdx.x < kDlxRows && x0 + threadIdx.x < n) dlx[x0 + threadIdx.x] = trim::sqrt_rn(tot);
 }
@@ -1222,10 +1222,10 @@ __global__ __launch_bounds__(256) void encode_kernel(const float *__restrict__ b
     float tot = 0.0f;
     uint32_t packed = 0;
     for (int j = 0; j < M; ++j) {
-        __syncthreads();
+        sync_block();
         for (int e = threadIdx.x; e < kC * dsub; e += blockDim.x)
             cb[e] = codebooks[(size_t)j * kC * dsub + e];
-        __syncthreads();
+        sync_block();
         float best = __builtin_inff();
         int arg = 0;
         for (int c = 0; c < kC; ++c) {
@@ -1271,7 +1271,7 @@ __global__ __launch_bounds__(kFsRows) void encode_fs2_kernel(const float *__rest
     float tot = 0.0f;
     for (int c0 = 0; c0 < d; c0 += kFsCols) {
         const int cols = d - c0 < kFsCols ? d - c0 : kFsCols;
-        __syncthreads();
+        sync_block();
         if (vec_rows) {
             for (int e = threadIdx.x; e < kFsRows * (kFsCols / 4); e += kFsRows) {
                 const int r = e / (kFsCols / 4), g = e % (kFsCols / 4);
@@ -1287,7 +1287,7 @@ __global__ __launch_bounds__(kFsRows) void encode_fs2_kernel(const float *__rest
                 if (g < cols) xt[r * kFsStride + g] = base[(size_t)x * d + c0 + g];
             }
         }
-        __syncthreads();
+        sync_block();
         uint32_t out[PACKED ? 2 : 4] = {};
         const float *xr = xt + threadIdx.x * kFsStride;
 #pragma clang loop unroll(disable)
@@ -1345,10 +1345,10 @@ __global__ __launch_bounds__(256) void encode_fs_kernel(const float *__restrict_
     const float *x = base + (size_t)(valid ? i : 0) * d;
     float tot = 0.0f;
     for (int jb = 0; jb < m / 2; ++jb) {
-        __syncthreads();
+        sync_block();
         for (int e = threadIdx.x; e < 2 * kC4 * dsub; e += blockDim.x)
             cb[e] = codebooks[(size_t)jb * 2 * kC4 * dsub + e];
-        __syncthreads();
+        sync_block();
         uint32_t byte = 0;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -1383,7 +1383,7 @@ __global__ __launch_bounds__(256) void lut_fs_kernel(const float *__restrict__ q
     const int b0 = blockIdx.x * bper;
     const int nb = b0 + bper <= m / 2 ? bper : m / 2 - b0;
     for (int t = threadIdx.x; t < d; t += blockDim.x) q_lds[t] = queries[(size_t)q * d + t];
-    __syncthreads();
+    sync_block();
     build_table_rows<true>(lut + ((size_t)q * m + 2 * b0) * kC4, q_lds, codebooks, dsub, b0, nb);
 }
 
@@ -1398,7 +1398,7 @@ __global__ __launch_bounds__(256) void lut_kernel(const float *__restrict__ quer
     const int j0 = blockIdx.x * jper;
     const int nj = j0 + jper <= M ? jper : M - j0;
     for (int t = threadIdx.x; t < d; t += blockDim.x) q_lds[t] = queries[(size_t)q * d + t];
-    __syncthreads();
+    sync_block();
     build_table_rows(lut + ((size_t)q * M + j0) * kC, q_lds, codebooks, dsub, j0, nj);
 }
 
@@ -1479,7 +1479,7 @@ __global__ __launch_bounds__(1024) void range_offsets_kernel(const int32_t *__re
         if (lane >= off) incl += v;
     }
     if (lane == 63) part[wave] = incl;
-    __syncthreads();
+    sync_block();
     int64_t run = incl - s;
     for (int w = 0; w < wave; ++w) run += part[w];
     if (threadIdx.x == 1023) {
@@ -1541,7 +1541,7 @@ __global__ __launch_bounds__(256) void range_fill_kernel(const RangeFillArgs a) 
         segd[p] = (int)s;
         segp[p + 1] = (int)(e - s);
     }
-    __syncthreads();
+    sync_block();
     if (tid == 0) {
         int64_t run = 0;
         segp[0] = 0;
@@ -1554,7 +1554,7 @@ __global__ __launch_bounds__(256) void range_fill_kernel(const RangeFillArgs a) 
         }
         s_total = (int)run;
     }
-    __syncthreads();
+    sync_block();
     const int total = s_total;
     const int c_begin = split * a.chunk;
     if (c_begin >= total) return;
@@ -1583,7 +1583,7 @@ __global__ __launch_bounds__(256) void range_fill_kernel(const RangeFillArgs a) 
             }
             if (lane == kWave - 1) s_cnt = incl;
         }
-        __syncthreads();
+        sync_block();
         const int cnt = s_cnt;
         for (int i = tid; i < cnt; i += T) {
             if (out + i >= a.capacity) break;
@@ -1599,7 +1599,7 @@ __global__ __launch_bounds__(256) void range_fill_kernel(const RangeFillArgs a) 
             a.out_d2[out + i] = a.result_d2[(size_t)q * a.rmask_words * 32 + c];   // as the search computed it
         }
         out += cnt;
-        __syncthreads();
+        sync_block();
     }
 }
 
@@ -1653,7 +1653,7 @@ __global__ __launch_bounds__(kProbeThreads) void probe_distance_kernel(const flo
     const int64_t q0 = (int64_t)blockIdx.y * QT;
     const int nqt = (int)(nq - q0 < QT ? nq - q0 : QT);
     for (int t = tid; t < QT * d; t += kProbeThreads) q_lds[t] = t < nqt * d ? queries[(size_t)q0 * d + t] : 0.0f;
-    __syncthreads();
+    sync_block();
     const int l0 = ((int)blockIdx.x * (kProbeThreads / 32) + (tid >> 5)) * (QT == 8 ? 4 : 8);
     if (l0 >= nlist) return;
     probe_distances<QT>(q_lds, d, centroids, nlist, l0, lane32, [&](int qi, int l, float v) {
@@ -1793,7 +1793,7 @@ __global__ __launch_bounds__(512) void ivf_probe_kernel(const float *__restrict_
         q_lds[t] = qi < nqt ? queries[(size_t)q0 * d + t] : 0.0f;
     }
     for (int i = tid; i < QT * npow2; i += T) keys[i] = ~0ull;
-    __syncthreads();
+    sync_block();
     const int lane32 = tid & 31;
     const int ng = d >> 2;
     const int nh = T >> 5;
@@ -1846,7 +1846,7 @@ __global__ __launch_bounds__(512) void ivf_probe_kernel(const float *__restrict_
         if ((lane32 & ((1 << kShift) - 1)) == 0 && l < nlist)
             keys[(size_t)qi * npow2 + l] = ((unsigned long long)__float_as_uint(dist) << 32) | (uint32_t)l;
     }
-    __syncthreads();
+    sync_block();
     // Short probe lists (nprobe <= 64, at least 256 lists): one wave per query.  The keys are seen
     // as 64 S interleaved columns (S = 1 for nprobe <= 32, else 2; lane l, slot s holds column
     // 64 s + l); the nprobe-th smallest of the column minima (sorted across lanes and slots) is
@@ -1857,7 +1857,7 @@ __global__ __launch_bounds__(512) void ivf_probe_kernel(const float *__restrict_
     __shared__ int general_path;
     if (nprobe <= 64 && npow2 >= 256) {
         if (tid == 0) general_path = 0;
-        __syncthreads();
+        sync_block();
         const int wave = tid >> 6, lane = tid & 63;
         const int S = nprobe <= 32 ? 1 : 2;
         // ascending bitonic sort of the 64 S elements (element e = 64 slot + lane)
@@ -1910,7 +1910,7 @@ __global__ __launch_bounds__(512) void ivf_probe_kernel(const float *__restrict_
             for (int i0 = 0; i0 < npow2; i0 += 64) c += __popcll(__ballot(kq[i0 + lane] <= cut));
             if (c > 64 * S) atomicOr(&general_path, 1);
         }
-        __syncthreads();   // nothing has been moved yet: the general path finds every key in place
+        sync_block();   // nothing has been moved yet: the general path finds every key in place
         if (!general_path) {
             if (wave < nqt) {
                 // move the qualifying keys to the front (in place: none moves backwards)
@@ -1956,7 +1956,7 @@ __global__ __launch_bounds__(512) void ivf_probe_kernel(const float *__restrict_
                 const unsigned long long x = kq[lo], y = kq[hi];
                 if ((x > y) == up) { kq[lo] = y; kq[hi] = x; }
             }
-            __syncthreads();
+            sync_block();
         }
     }
     const int R = 1 << lg_r;
@@ -1971,7 +1971,7 @@ __global__ __launch_bounds__(512) void ivf_probe_kernel(const float *__restrict_
             const unsigned long long x = kq[i], y = kq[(1 << lg_gap) + i];
             if (y < x) kq[i] = y;
         }
-        __syncthreads();
+        sync_block();
         // sort the bitonic survivors: ascending for even pairs, descending for odd ones
         for (int lg_stride = lg_r - 1; lg_stride >= 0; --lg_stride) {
             const int stride = 1 << lg_stride;
@@ -1986,7 +1986,7 @@ __global__ __launch_bounds__(512) void ivf_probe_kernel(const float *__restrict_
                 const unsigned long long x = kq[lo], y = kq[lo + stride];
                 if ((x > y) == up) { kq[lo] = y; kq[lo + stride] = x; }
             }
-            __syncthreads();
+            sync_block();
         }
     }
     for (int w = tid; w < nqt * nprobe; w += T) {
@@ -2043,7 +2043,7 @@ __global__ __launch_bounds__(kAsgThreads) void assign_mfma_kernel(const float *_
         mu[t] = sum * (1.0f / 16.0f);
     }
     if (tid == 0) { *cmax_bits = 0; *namb = 0; }
-    __syncthreads();
+    sync_block();
     // staging: two threads per row, 16 columns of a slice each
     const int srow = tid >> 1, sstep = tid & 1;
     const int64_t xr = x0 + srow < n ? x0 + srow : n - 1;
@@ -2112,7 +2112,7 @@ __global__ __launch_bounds__(kAsgThreads) void assign_mfma_kernel(const float *_
                 for (int i = 0; i < 16; ++i) acc[u][t][i] = 0.0f;
         load(crow, 0);
         stage(0, 0);
-        __syncthreads();
+        sync_block();
         for (int kc = 0; kc < nk; ++kc) {
             if (kc + 1 < nk) load(crow, (kc + 1) * kAsgSlice);
             const b8 *b = buf + (kc & 1) * kBuf + half * kAsgTile + col;
@@ -2137,7 +2137,7 @@ __global__ __launch_bounds__(kAsgThreads) void assign_mfma_kernel(const float *_
                 }
             }
             if (kc + 1 < nk) stage((kc + 1) & 1, (kc + 1) * kAsgSlice);
-            __syncthreads();
+            sync_block();
         }
         xsum += __shfl_xor(xsum, 1);
         csum += __shfl_xor(csum, 1);
@@ -2146,7 +2146,7 @@ __global__ __launch_bounds__(kAsgThreads) void assign_mfma_kernel(const float *_
             cn2[srow] = cr < nlist ? csum : __builtin_inff();     // (rows past the end never win)
             if (cr < nlist) cmax2 = max(cmax2, __float_as_uint(csum));
         }
-        __syncthreads();
+        sync_block();
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const float xb = xn2[xg * 64 + u * 32 + col];
@@ -2186,7 +2186,7 @@ __global__ __launch_bounds__(kAsgThreads) void assign_mfma_kernel(const float *_
             t2[at] = m2[u][t];
             tc[at] = (i >> 4) * kAsgTile + cg * 128 + t * 32 + 8 * ((i & 15) >> 2) + 4 * half + (i & 3);
         }
-    __syncthreads();
+    sync_block();
     if (tid < kAsgTile && x0 + tid < n) {
         const float c2 = __uint_as_float(*cmax_bits), x2 = xn2[tid];
         const float xl = trim::sqrt_rn(x2), cl = trim::sqrt_rn(c2);
@@ -2208,7 +2208,7 @@ __global__ __launch_bounds__(kAsgThreads) void assign_mfma_kernel(const float *_
         else if ((close & (close - 1)) == 0) out[x0 + tid] = one;
         else amb[atomicAdd(namb, 1)] = (close << 8) | (uint32_t)tid;
     }
-    __syncthreads();
+    sync_block();
     const int na = *namb;
     for (int i = tid >> 5; i < na; i += kAsgThreads >> 5) {        // a half wave per undecided vector
         const int x = (int)(amb[i] & 255u);
@@ -2307,7 +2307,7 @@ __global__ __launch_bounds__(kAsgThreads, 2) void assign_rows_kernel(const float
     }
     if (tid == 0) { s_cmax = s_mmax = 0; s_np = 0; }
     if (tid < kAsgTile) s_best[tid] = ~0ull;
-    __syncthreads();
+    sync_block();
     const uint32_t top = max(s_top[0], s_top[1]);
     const bool usable = __uint_as_float(top) > 1e-30f && __uint_as_float(top) < 1e30f;
     const float sc = __uint_as_float((uint32_t)((usable ? 6 - ((int)(top >> 23) - 127) : 0) + 127) << 23);     // (the spread: 2^6 .. 2^7)
@@ -2389,7 +2389,7 @@ __global__ __launch_bounds__(kAsgThreads, 2) void assign_rows_kernel(const float
             pieces(f, 3, fits ? norm : 0.0f);
             *reinterpret_cast<h8 *>(s_buf + (i & 1) * Shape::kStage + (KS * 2 * P + s_row) * 16) = f;
         }
-        __syncthreads();
+        sync_block();
         if (xg * 64 / R == i) {
             const h8 *b = reinterpret_cast<const h8 *>(s_buf + (i & 1) * Shape::kStage) + xg * 64 % R + col;
 #pragma unroll
@@ -2401,7 +2401,7 @@ __global__ __launch_bounds__(kAsgThreads, 2) void assign_rows_kernel(const float
             }
         }
     }
-    __syncthreads();
+    sync_block();
     stage(0);
     const int nst = (nlist + R - 1) / R;
     load(nst > 1 ? 1 : 0);
@@ -2446,7 +2446,7 @@ __global__ __launch_bounds__(kAsgThreads, 2) void assign_rows_kernel(const float
             }
         }
     };
-    __syncthreads();
+    sync_block();
 #pragma unroll 1
     for (int st = 0; st < nst; ++st) {
         if (cg == 0) {
@@ -2470,7 +2470,7 @@ __global__ __launch_bounds__(kAsgThreads, 2) void assign_rows_kernel(const float
                 multiply(st, tt);
             }
         }
-        __syncthreads();
+        sync_block();
     }
     if (cg != 0) track(nst * TT - 1);
     // the trackers of every vector side by side (over the stages, which are done with)
@@ -2486,7 +2486,7 @@ __global__ __launch_bounds__(kAsgThreads, 2) void assign_rows_kernel(const float
             at[kTrk * kAsgTile] = m2[u][k];
             at[2 * kTrk * kAsgTile] = m3[u][k];
         }
-    __syncthreads();
+    sync_block();
     if (tid < kAsgTile && x0 + tid < n) {
         int key[2 * kTrk], third = 0x7fffffff;
 #pragma unroll
@@ -2530,7 +2530,7 @@ __global__ __launch_bounds__(kAsgThreads, 2) void assign_rows_kernel(const float
                 if (key[k] >= 0) s_pair[at++] = (uint32_t)tid | (uint32_t)key[k] << 8;
         }
     }
-    __syncthreads();
+    sync_block();
     const int np = s_np, lane32 = tid & 31, at4 = 4 * lane32 < d ? 4 * lane32 : 0;      // (at most 32 groups of four)
     for (int i0 = (tid >> 5) * 4; i0 < np; i0 += (kAsgThreads >> 5) * 4) {
         uint32_t pair[4];
@@ -2555,7 +2555,7 @@ __global__ __launch_bounds__(kAsgThreads, 2) void assign_rows_kernel(const float
         if (half_reduce_x4_writer(lane32) && i0 + i < np)
             atomicMin(&s_best[p & 255u], ((unsigned long long)__float_as_uint(dist) << 32) | (p >> 8));
     }
-    __syncthreads();
+    sync_block();
     if (tid < kAsgTile && x0 + tid < n && s_best[tid] != ~0ull) out[x0 + tid] = (int32_t)(s_best[tid] & 0xffffffffu);
 }
 
@@ -2583,10 +2583,10 @@ __global__ __launch_bounds__(T) void assign_fix_kernel(const float *__restrict__
     const int tid = threadIdx.x;
     const int64_t x0 = (int64_t)blockIdx.x * span;
     if (tid == 0) count = 0;
-    __syncthreads();
+    sync_block();
     for (int i = tid; i < span; i += T)
         if (x0 + i < n && out[x0 + i] < 0) todo[atomicAdd(&count, 1)] = i;
-    __syncthreads();
+    sync_block();
     const int total = count, ng = d >> 2;
     for (int g0 = 0; g0 < total; g0 += QT) {
         const int nqt = total - g0 < QT ? total - g0 : QT;
@@ -2595,7 +2595,7 @@ __global__ __launch_bounds__(T) void assign_fix_kernel(const float *__restrict__
             const int qi = t / d;
             q_lds[t] = xs[(size_t)(x0 + todo[g0 + (qi < nqt ? qi : 0)]) * d + (t - qi * d)];
         }
-        __syncthreads();
+        sync_block();
         auto measure = [&](auto wide) {              // against so many vectors
             int tid = threadIdx.x;                   // (opaque: addresses are made anew, not kept for the other widths as well)
             asm volatile("" : "+v"(tid));
@@ -2643,9 +2643,9 @@ __global__ __launch_bounds__(T) void assign_fix_kernel(const float *__restrict__
         if (nqt <= 2) measure(std::integral_constant<int, 2>());
         else if (nqt <= 4) measure(std::integral_constant<int, 4>());
         else measure(std::integral_constant<int, 8>());
-        __syncthreads();
+        sync_block();
         if (tid < nqt) out[x0 + todo[g0 + tid]] = (int32_t)(best[tid] & 0xffffffffu);
-        __syncthreads();
+        sync_block();
     }
 }
 
@@ -2669,7 +2669,7 @@ __global__ __launch_bounds__(1024) void query_order_kernel(const int32_t *__rest
         const int64_t q = tid + (int64_t)i * T;
         mine[i] = q < nq ? (uint32_t)probes[(size_t)q * nprobe] % (uint32_t)nbucket : 0xffffffffu;
     }
-    __syncthreads();
+    sync_block();
 #pragma unroll
     for (int i = 0; i < kKeep; ++i)
         if (mine[i] != 0xffffffffu) atomicAdd(&hist[mine[i]], 1);
@@ -2677,7 +2677,7 @@ __global__ __launch_bounds__(1024) void query_order_kernel(const int32_t *__rest
         const uint32_t l = (uint32_t)probes[(size_t)q * nprobe];
         atomicAdd(&hist[l % (uint32_t)nbucket], 1);
     }
-    __syncthreads();
+    sync_block();
     // exclusive prefix over the buckets: each thread owns a contiguous run; the runs' sums are
     // scanned inside each wave, then across the (at most 16) waves
     const int per = (nbucket + T - 1) / T;
@@ -2693,12 +2693,12 @@ __global__ __launch_bounds__(1024) void query_order_kernel(const int32_t *__rest
         if (lane >= off) incl += v;
     }
     if (lane == 63) part[wave] = incl;
-    __syncthreads();
+    sync_block();
     int before = 0;
     for (int w = 0; w < wave; ++w) before += part[w];
     int run = before + incl - sum;
     for (int b = lo; b < hi; ++b) { const int c = hist[b]; hist[b] = run; run += c; }
-    __syncthreads();
+    sync_block();
 #pragma unroll
     for (int i = 0; i < kKeep; ++i)
         if (mine[i] != 0xffffffffu) order[atomicAdd(&hist[mine[i]], 1)] = (int32_t)(tid + i * T);

@@ -29,6 +29,17 @@ template <bool FS> constexpr int kByteEntries = FS ? 2 * kC4 : kC;      // table
 template <bool FS> constexpr uint32_t kByteRow = kByteEntries<FS> * 4;  // their bytes
 template <bool FS> constexpr int kByteLookups = FS ? 2 : 1;             // lookups per code byte
 
+// The workgroup's barrier: every wave has waited for its own LDS accesses.  __syncthreads() asks the compiler for that wait, which its last
+// pass drops again where nothing is outstanding on the way into a loop, although a store is on the way round it (hipcc of ROCm 7.2;
+// search_kernel's loop over stretches).  Other waves then read what the store replaces now and then: the threshold of the stretch
+// before, say, so that counts and places of a workgroup did not match.  A wait that is written down stays.
+__device__ __forceinline__ void sync_block() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0xc07f);        // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
 struct Hit {
     float d2;
     int32_t id;

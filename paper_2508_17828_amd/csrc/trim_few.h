@@ -59,7 +59,7 @@ __global__ __launch_bounds__(kBoundThreads) __attribute__((amdgpu_waves_per_eu(6
     const int c0 = (int)cb, c1 = c0 + chunk < total ? c0 + chunk : total;
     float *row_g = a.g + (size_t)slot * a.stride;
     for (int ph = 0; ph < a.P; ++ph) {
-        if (ph > 0) __syncthreads();
+        if (ph > 0) sync_block();
         if (a.lut) {
             const float4 *src = reinterpret_cast<const float4 *>(a.lut + ((size_t)q * a.M + ph * a.Mp) * kByteEntries<FS>);
             float4 *dst = reinterpret_cast<float4 *>(tab);
@@ -67,7 +67,7 @@ __global__ __launch_bounds__(kBoundThreads) __attribute__((amdgpu_waves_per_eu(6
         } else {
             build_table_rows<FS>(tab, q_lds, a.codebooks, a.dsub, ph * a.Mp, a.Mp);
         }
-        __syncthreads();
+        sync_block();
         const bool last = ph == a.P - 1;
         // (a wave has 64 candidates that begin at a multiple of 64)
         for (int cw = c0 + (tid & ~63); cw < c1; cw += kBoundThreads) {
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
             const int p = r == 0 ? pos[0] : r == 1 ? pos[1] : r == 2 ? pos[2] : pos[3];
             if (half_reduce_x4_writer(lane32) && i + r < n) put(i + r, v, p);
         }
-        __syncthreads();
+        sync_block();
     };
     // ---- the seed: its largest distance is the first batch's threshold ----
     if (a.d2) {
@@ -171,14 +171,14 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
         for (int u = 0; u < kPre; ++u)
             if (tid + u * T < fb) f_d2[tid + u * T] = pre_d2[u];
         for (int i = tid + kPre * T; i < fb; i += T) f_d2[i] = a.d2[(size_t)slot * (a.k + a.batch) + i];
-        __syncthreads();
+        sync_block();
     } else {
         measure(ns, [&](int i) { return i; }, [&](int i, float v, int) { f_d2[i] = v; });
     }
     uint32_t most = 0;
     for (int i = tid; i < ns; i += T) most = max(most, __float_as_uint(f_d2[i]));
     wave_max(&s_most, most);
-    __syncthreads();
+    sync_block();
     // (a distance that is no number is never in R: then R is not full yet)
     const bool full = ns == a.k && s_most <= 0x7f800000u;
     const float tau1 = full ? __uint_as_float(s_most) : __builtin_inff();
@@ -202,13 +202,13 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
         for (int i0 = kPre * T; i0 < fb; i0 += T) first(i0 + tid, row_g[i0 + tid < fb ? i0 + tid : 0]);
         wave_add(&s_count, mine);
     }
-    __syncthreads();
+    sync_block();
     int n = s_n;
     if (!a.d2) {
         measure(n, [&](int i) { return (int)s_todo[i]; }, [&](int i, float v, int) { f_d2[s_todo[i]] = v; });
         for (int i = tid; i < ns; i += T) s_todo[n + i] = (uint16_t)i;
         n += ns;
-        __syncthreads();
+        sync_block();
     }
     // the k least distances by (distance, id)
     const uint32_t top = full ? __float_as_uint(tau1) : 0x7f800000u;    // (nothing above it can be among them)
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) least = min(least, (uint32_t)__shfl_xor((int)least, off));
     if (lane == 0) atomicMin(&s_least, least);
-    __syncthreads();
+    sync_block();
     least = s_least;
     if (full) {                                  // (else all of them are wanted, as far as they go)
         const uint32_t span = top - least;       // least <= top: the seed is among them
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
             const uint32_t key = __float_as_uint(f_d2[s_todo[i]]);
             if (key <= top) atomicAdd(&hist[(key - least) >> shift], 1);
         }
-        __syncthreads();
+        sync_block();
         if (wave == 0) {
             int h[4], sum = 0;
 #pragma unroll
@@ -245,7 +245,7 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
                 before += h[u];
             }
         }
-        __syncthreads();
+        sync_block();
         cut = s_least < top ? s_least : top;
     }
     for (int i = tid; i < n; i += T) {
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
             s_key[atomicAdd(&s_nk, 1)] = ((unsigned long long)key << 32) | ((uint32_t)id ^ 0x80000000u);   // (ids order as signed)
         }
     }
-    __syncthreads();
+    sync_block();
     nk = s_nk;
     const int have = nk < a.k ? nk : a.k;
     if (nk <= 256) {                             // (a rank each; two entries may be one and the same)
@@ -279,14 +279,14 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
         int size = 1;
         while (size < nk) size <<= 1;
         for (int i = nk + tid; i < size; i += T) s_key[i] = ~0ull;
-        __syncthreads();
+        sync_block();
         sort_keys(s_key, size);
         for (int i = tid; i < kWave * E; i += T) {
             rd2[i] = i < have ? __uint_as_float((uint32_t)(s_key[i] >> 32)) : __builtin_inff();
             rid[i] = i < have ? (int32_t)((uint32_t)s_key[i] ^ 0x80000000u) : kEmptyId;
         }
     }
-    __syncthreads();
+    sync_block();
     ResultRegs<E> R;
     int frozen_b = -2, survivors = s_count;
     float tau_f = 0.0f;
@@ -294,7 +294,7 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
         R.load(rd2, rid, a.k, lane);
         if (lane == 0) { s_tau = R.t_d2; s_frozen = -2; s_tau_f = 0.0f; }
     }
-    __syncthreads();
+    sync_block();
     // ---- the rest ----
     const float *least_of = a.least + (size_t)slot * ((a.stride + 63) / 64);
     int looked = 0;                              // up to here s_ahead is known
@@ -305,9 +305,9 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
         if (V == 16) {
             // the next stretches, a wave each (thresholds only fall: who is above this one stays out)
             if (w0 >= looked) {
-                __syncthreads();                 // (the last look has been read)
+                sync_block();                 // (the last look has been read)
                 if (tid == 0) s_ahead = 0;
-                __syncthreads();
+                sync_block();
                 const float tau = __builtin_fmaxf(s_tau, s_tau_f);
                 const int64_t from = (int64_t)base + (int64_t)wave * 16 * T, to = from + 16 * T < total ? from + 16 * T : total;
                 constexpr int kLeast = 16 * T / 64 / kWave + 1;
@@ -320,7 +320,7 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
                 for (int u = 0; u < kLeast; ++u) any |= v[u] <= tau;
                 any &= from < to;
                 if (__any(any) && lane == 0) atomicOr(&s_ahead, 1u << wave);
-                __syncthreads();
+                sync_block();
                 ahead = s_ahead;
                 looked = base + 16 * T * (T / kWave) < total ? base + 16 * T * (T / kWave) : total;
             }
@@ -353,7 +353,7 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
             if (lane >= off) incl += v;
         }
         if (lane == 63) part[wave] = incl;
-        __syncthreads();
+        sync_block();
         int before = incl - cnt, all = 0;
 #pragma unroll
         for (int v = 0; v < T / kWave; ++v) {
@@ -371,7 +371,7 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
                     ++at;
                 }
             if (tid == 0) s_n = 0;
-            __syncthreads();
+            sync_block();
             // who is a survivor by now (a batch keeps the threshold that it began with) is measured
             const float now = s_tau, tf = s_tau_f;
             const int fz = s_frozen;
@@ -381,23 +381,23 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
                 s_id[i] = kEmptyId;
                 if (s_g[i] <= (b == fz ? tf : now)) s_todo[atomicAdd(&s_n, 1)] = (uint16_t)i;
             }
-            __syncthreads();
+            sync_block();
             measure(s_n, [&](int i) { return s_cl[s_todo[i]]; },
                     [&](int i, float v, int pos) { s_d2[s_todo[i]] = v; s_id[s_todo[i]] = a.ids ? a.ids[pos] : pos; });
             if (wave == 0) {
                 survivors += replay_entries<E>(R, frozen_b, tau_f, s_cl, s_g, s_d2, s_id, np, a.batch, mask_row, a.mask_words);
                 if (lane == 0) { s_tau = R.t_d2; s_frozen = frozen_b; s_tau_f = tau_f; }
             }
-            __syncthreads();
+            sync_block();
         }
-        __syncthreads();
+        sync_block();
         w0 = w1;
     }
     if (wave == 0) {
         R.store(rd2, rid);
         if (lane == 0 && a.n_exact) a.n_exact[q] = survivors;
     }
-    __syncthreads();
+    sync_block();
     for (int i = tid; i < a.k; i += T) {
         const int32_t id = rid[i];
         a.out_ids[(size_t)q * a.k + i] = id == kEmptyId ? -1 : id;

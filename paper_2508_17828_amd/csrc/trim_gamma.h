@@ -80,7 +80,7 @@ __global__ __launch_bounds__(256) void gamma_operands_kernel(const GammaRankArgs
         }
         s_mu[t] = t < d ? sum * 0.125f : 0.0f;
     }
-    __syncthreads();
+    sync_block();
     const int dsub = d / a.g.M;
     const float *x;                   // a vector, or a query
     const uint8_t *code = nullptr;
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(256) void gamma_bins_kernel(const GammaRankArgs a) 
             }
         }
     }
-    __syncthreads();
+    sync_block();
     constexpr float kUlp = 1.0f / 16777216.0f;
     const float d = (float)a.g.d;
     const float *vp = a.vpar + (size_t)(vb * 32 + col) * 8;
@@ -270,7 +270,7 @@ __global__ __launch_bounds__(T, 4) void gamma_rank_kernel(const GammaRankArgs a)
     const int dsub = d / a.g.M;
     for (int b = tid; b < kGrBins; b += T) hist[b] = 0;
     if (tid == 0) s_n = 0;
-    __syncthreads();
+    sync_block();
     const uint4 *src = reinterpret_cast<const uint4 *>(a.keys + (size_t)blockIdx.x * a.qpad);
     auto each = [&](auto &&f) {                      // f(query, lower bin, upper bin)
         for (int i = tid; i * 8 < Q; i += T) {
@@ -303,7 +303,7 @@ __global__ __launch_bounds__(T, 4) void gamma_rank_kernel(const GammaRankArgs a)
         for (int off = 32; off > 0; off >>= 1) p += __shfl_xor(p, off);
         if (lane == 0) norm_part[v >> 6] = p;
     }
-    __syncthreads();
+    sync_block();
     float norm2 = 0.0f;
     for (int w = 0; w < kGammaThreads / kWave; ++w) norm2 += norm_part[w];
     const float nu = sqrt_rn(norm2);
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(T, 4) void gamma_rank_kernel(const GammaRankArgs a)
         if (lane >= off) incl += v;
     }
     if (lane == kWave - 1) part[wave] = incl;
-    __syncthreads();
+    sync_block();
     uint32_t before = incl - sum;
     for (int w = 0; w < wave; ++w) before += part[w];
     const uint32_t rank = (uint32_t)a.g.rank;
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(T, 4) void gamma_rank_kernel(const GammaRankArgs a)
     }
 #pragma unroll
     for (int i = 0; i < kPer; i += 4) mine[i / 4] = make_uint4(h[i], h[i + 1], h[i + 2], h[i + 3]);
-    __syncthreads();
+    sync_block();
     const int lo = s_lo, hi = s_hi, below = (int)(hist[lo] >> 16), n = (int)(hist[hi] & 0xffffu) - below;
     const int want = a.g.rank - below;
     const int lane32 = tid & 31, ng = d >> 2;
@@ -349,7 +349,7 @@ __global__ __launch_bounds__(T, 4) void gamma_rank_kernel(const GammaRankArgs a)
         each([&](int q, int l0, int h0) {
             if (h0 >= lo && l0 <= hi) keys[atomicAdd(&s_n, 1)] = (uint32_t)q;
         });
-        __syncthreads();
+        sync_block();
         constexpr int QB = 4;
         for (int i0 = (tid >> 5) * QB; i0 < n; i0 += (T / 32) * QB) {
             const float4 *row[QB];
@@ -373,7 +373,7 @@ __global__ __launch_bounds__(T, 4) void gamma_rank_kernel(const GammaRankArgs a)
             // (numbers of this half wave's own: read above, before they are replaced)
             if (!(lane32 & 19) && i < n) keys[i] = gamma_key(v, nn, nu);
         }
-        __syncthreads();
+        sync_block();
     };
     if (n > kGrList) {
         uint32_t *keys = a.lists + (size_t)blockIdx.x * a.qpad;

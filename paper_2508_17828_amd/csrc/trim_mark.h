@@ -55,9 +55,9 @@ __global__ __launch_bounds__(256) void filter_means_kernel(const FilterArgs a) {
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
         if ((c & 63) == 0) part[wave] = sum;
-        __syncthreads();
+        sync_block();
         const float mu = (part[0] + part[1] + part[2] + part[3]) / (float)a.ncent;
-        __syncthreads();
+        sync_block();
         if (c == 0) a.mu[j * a.dsub + t] = mu;
         if (c < a.ncent) most = __builtin_fmaxf(most, __builtin_fabsf(v - mu));
     }
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(256) void filter_operands_kernel(const FilterArgs a
     }
     const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) { part[0][wave] = n2; part[1][wave] = moved; part[2][wave] = most; }
-    __syncthreads();
+    sync_block();
     if (threadIdx.x == 0) {
         n2 = part[0][0] + part[0][1] + part[0][2] + part[0][3];
         moved = part[1][0] + part[1][1] + part[1][2] + part[1][3];
@@ -238,10 +238,10 @@ __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs
         const int64_t r0 = ls + (int64_t)rt * kFltRows;
         const int nrows = le - r0 < kFltRows ? (int)(le - r0) : kFltRows;
         const int q0 = i0 + qt * kFltQ, nqs = i1 - q0 < kFltQ ? i1 - q0 : kFltQ;
-        __syncthreads();     // the previous tile is done with
+        sync_block();     // the previous tile is done with
         if constexpr (CERTAIN) {
             if (tid == 0) s_room = 0x7f800000u;
-            __syncthreads();
+            sync_block();
         }
         // the queries' rows of the workspace; landmark distances of the rows, their mean (the tangent point)
         int row = 0, c0q = 0, endq = 0;
@@ -364,7 +364,7 @@ __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs
         const int nv = (nqs + 31) >> 5;               // query tiles of this one in use
         stage(0, first[0]);
         stage(1, first[1]);
-        __syncthreads();
+        sync_block();
         // (the number of query tiles is fixed inside: a branch around each leaves its operands' latency open four times a step)
         auto slices = [&](auto tiles) {
             constexpr int NV = decltype(tiles)::value;
@@ -443,7 +443,7 @@ __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs
                     __builtin_amdgcn_sched_group_barrier(0x8, NV - 2, 1);
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                __syncthreads();
+                sync_block();
             };
             Operands o;
             operands(0, std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{}, cw, o);
@@ -464,7 +464,7 @@ __global__ __launch_bounds__(kFltThreads, 1) void filter_kernel(const FilterArgs
             for (int sl = 0; sl < nslice; ++sl) {
                 stage(sl + 2, ahead);
                 load(sl + 3, ahead);
-                __syncthreads();
+                sync_block();
             }
         } else switch (nv) {
             case 1: slices(std::integral_constant<int, 1>{}); break;
@@ -623,12 +623,12 @@ __global__ __launch_bounds__(64 * WQ * WR, WAVES) void measure_kernel(const Filt
         }
         const int nrows = le - r0 < kRows ? (int)(le - r0) : kRows;
         int have = 0;                     // queries waiting in the arrays (the same for all threads)
-        __syncthreads();                  // (the previous tile is done with)
+        sync_block();                  // (the previous tile is done with)
         while (qb < q1 || have > 0) {
             // gather queries with a mark in these rows until there are 64 WQ, or no more
             while (qb < q1 && have < kMsrQ) {
                 if (tid == 0) s_n = have;
-                __syncthreads();
+                sync_block();
                 if (tid < kMsrQ && qb + tid < q1) {
                     int row = qb + tid;
                     int64_t c = 0;
@@ -656,9 +656,9 @@ __global__ __launch_bounds__(64 * WQ * WR, WAVES) void measure_kernel(const Filt
                     }
                 }
                 qb += kMsrQ;
-                __syncthreads();
+                sync_block();
                 have = s_n;
-                __syncthreads();
+                sync_block();
             }
             if (have == 0) break;
             asm volatile("" : "+v"(tid));
@@ -720,7 +720,7 @@ __global__ __launch_bounds__(64 * WQ * WR, WAVES) void measure_kernel(const Filt
             for (int i = 0; i < NS; ++i) load(i, ahead[i]);
             stage(0, ahead[0]);
             load(NS, ahead[0]);
-            __syncthreads();
+            sync_block();
             auto slice = [&](int sl, Ahead &r) {     // r: slice sl + 1
                 stage(sl + 1, r);
                 load(sl + 1 + NS, r);
@@ -743,7 +743,7 @@ __global__ __launch_bounds__(64 * WQ * WR, WAVES) void measure_kernel(const Filt
                             }
                     }
                 }
-                __syncthreads();
+                sync_block();
             };
 #pragma unroll 1
             for (int sl = 0; sl < nslice; sl += kStep) {
@@ -764,7 +764,7 @@ __global__ __launch_bounds__(64 * WQ * WR, WAVES) void measure_kernel(const Filt
                     s_mx[xr + kApart * i] = sqrt_rn(v) * (1.0f / 2048.0f + 1.0f / 4194304.0f) * 1.001f + lost;
                 }
             }
-            __syncthreads();
+            sync_block();
             if (busy) {
 #pragma unroll
                 for (int v = 0; v < 2; ++v) {
@@ -803,7 +803,7 @@ __global__ __launch_bounds__(64 * WQ * WR, WAVES) void measure_kernel(const Filt
                     }
                 }
             }
-            __syncthreads();
+            sync_block();
             // who did not fit comes to the front
             const int rest = have - nqs;
             int r_row = 0, r_c0 = 0, r_end = 0;
@@ -812,10 +812,10 @@ __global__ __launch_bounds__(64 * WQ * WR, WAVES) void measure_kernel(const Filt
                 r_row = s_row[nqs + tid]; r_c0 = s_c0[nqs + tid]; r_end = s_end[nqs + tid];
                 r_nq = s_nq[nqs + tid]; r_mq = s_mq[nqs + tid];
             }
-            __syncthreads();
+            sync_block();
             if (tid < rest) { s_row[tid] = r_row; s_c0[tid] = r_c0; s_end[tid] = r_end; s_nq[tid] = r_nq; s_mq[tid] = r_mq; }
             have = rest;
-            __syncthreads();
+            sync_block();
         }
     }
 }
@@ -969,16 +969,16 @@ void finish_kernel(const FinishArgs a) {
         if (row_in) {           // (nobody's sum wanted in this piece: no table either)
             const bool here = __any(some);
             if (lane == 0) part[wave] = here ? 1 : 0;
-            __syncthreads();
+            sync_block();
             some = false;
             for (int v = 0; v < T / kWave; ++v) some = some || part[v] != 0;
         } else {
             some = true;
         }
-        __syncthreads();
+        sync_block();
         for (int ph = 0; some && ph < a.P; ++ph) {
             const bool last = ph == a.P - 1;
-            if (in_place != ph) { fill(ph * a.Mp, a.Mp); in_place = ph; __syncthreads(); }
+            if (in_place != ph) { fill(ph * a.Mp, a.Mp); in_place = ph; sync_block(); }
             for (int w0 = 0; w0 < nwords; w0 += T) {
                 uint32_t b = w0 + tid < nwords ? bits[w0 + tid] : 0u;
                 if (row_in && w0 + tid < nwords) b &= ~row_in[(p0 >> 5) + w0 + tid];      // (these keep their mark)
@@ -990,7 +990,7 @@ void finish_kernel(const FinishArgs a) {
                     if (lane >= off) incl += v;
                 }
                 if (lane == kWave - 1) part[wave] = incl;
-                __syncthreads();
+                sync_block();
                 int before = incl - cnt;
                 all = 0;
                 for (int v = 0; v < T / kWave; ++v) {
@@ -1007,7 +1007,7 @@ void finish_kernel(const FinishArgs a) {
                         rem &= rem - 1;
                         ++at;
                     }
-                    __syncthreads();
+                    sync_block();
                     for (int i = tid; i < np; i += T) {
                         const int cl = list[i];
                         const int pos = segment_position(p0 + cl, segp, segd, nseg);
@@ -1033,9 +1033,9 @@ void finish_kernel(const FinishArgs a) {
                         }
                         row_g[p0 + cl] = keep;
                     }
-                    __syncthreads();
+                    sync_block();
                 }
-                __syncthreads();     // part[] is read (where nothing is marked no barrier has come since)
+                sync_block();     // part[] is read (where nothing is marked no barrier has come since)
             }
         }
         for (int w = tid; w < nwords; w += T) {
@@ -1049,7 +1049,7 @@ void finish_kernel(const FinishArgs a) {
             }
             row_bits[(p0 >> 5) + w] = b;
         }
-        __syncthreads();
+        sync_block();
     }
     if (a.range && a.n_exact) {
 #pragma unroll
@@ -1068,7 +1068,7 @@ __global__ __launch_bounds__(1024) void invert_count_kernel(const InvertArgs a) 
     const bool lds = a.nlist <= kInvLists;
     if (lds) {
         for (int l = threadIdx.x; l < a.nlist; l += blockDim.x) s_cnt[l] = 0;
-        __syncthreads();
+        sync_block();
     }
     for (int64_t i = (int64_t)blockIdx.x * kInvPer + threadIdx.x; i < ((int64_t)blockIdx.x + 1) * kInvPer && i < a.nslots * a.nseg; i += blockDim.x) {
         const int64_t slot = i / a.nseg, q = a.query(slot);
@@ -1077,7 +1077,7 @@ __global__ __launch_bounds__(1024) void invert_count_kernel(const InvertArgs a) 
         if (l >= 0 && l < a.nlist) atomicAdd(lds ? &s_cnt[l] : &a.cnt[l], 1);
     }
     if (!lds) return;
-    __syncthreads();
+    sync_block();
     for (int l = threadIdx.x; l < a.nlist; l += blockDim.x)
         if (s_cnt[l]) atomicAdd(&a.cnt[l], s_cnt[l]);
 }
@@ -1089,7 +1089,7 @@ __global__ __launch_bounds__(1024) void invert_scan_kernel(const InvertArgs a) {
     __shared__ int carry, tcarry, rcarry;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (tid == 0) carry = tcarry = rcarry = 0;
-    __syncthreads();
+    sync_block();
     for (int l0 = 0; l0 < nlist; l0 += 1024) {
         const int l = l0 + tid, v = l < nlist ? cnt[l] : 0;
         int t = 0, rt = 0;
@@ -1108,7 +1108,7 @@ __global__ __launch_bounds__(1024) void invert_scan_kernel(const InvertArgs a) {
             if (lane >= off) { incl += o; tincl += to; rincl += ro; }
         }
         if (lane == 63) { part[wave] = incl; tpart[wave] = tincl; rpart[wave] = rincl; }
-        __syncthreads();
+        sync_block();
         int before = carry, tbefore = tcarry, rbefore = rcarry;
         for (int w = 0; w < wave; ++w) { before += part[w]; tbefore += tpart[w]; rbefore += rpart[w]; }
         if (l < nlist) {
@@ -1117,9 +1117,9 @@ __global__ __launch_bounds__(1024) void invert_scan_kernel(const InvertArgs a) {
             a.tasks[l] = tbefore + tincl - t;
             a.row_tasks[l] = rbefore + rincl - rt;
         }
-        __syncthreads();
+        sync_block();
         if (tid == 1023) { carry = before + incl; tcarry = tbefore + tincl; rcarry = rbefore + rincl; }
-        __syncthreads();
+        sync_block();
     }
     if (tid == 0) {
         start[nlist] = carry;
@@ -1137,7 +1137,7 @@ __global__ __launch_bounds__(1024) void invert_place_kernel(const InvertArgs a) 
     constexpr int kWaves = 1024 / kWave;
     if (lds) {
         for (int l = threadIdx.x; l < a.nlist; l += 1024) s_cnt[l] = 0;
-        __syncthreads();
+        sync_block();
     }
     // twice over the pairs: numbers and segment tables, then places
     for (int round = lds ? 0 : 1; round < 2; ++round) {
@@ -1183,10 +1183,10 @@ __global__ __launch_bounds__(1024) void invert_place_kernel(const InvertArgs a) 
             }
         }
         if (round == 0) {
-            __syncthreads();
+            sync_block();
             for (int l = threadIdx.x; l < a.nlist; l += 1024)
                 if (s_cnt[l]) s_cnt[l] = atomicAdd(&a.cnt[l], s_cnt[l]);
-            __syncthreads();
+            sync_block();
         }
     }
 }
@@ -1233,7 +1233,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
         rd2[i] = have ? a.out_d2[(size_t)q * a.k + i] : __builtin_inff();
         rid[i] = id < 0 ? kEmptyId : id;
     }
-    __syncthreads();
+    sync_block();
     ResultRegs<E> R;
     int frozen_b = -2, survivors = 0;          // (survivors: this thread's)
     float tau_f = 0.0f;
@@ -1259,7 +1259,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                 s_d2[e1] = d2[1]; s_id[e1] = id1;
             }
         }
-        __syncthreads();
+        sync_block();
     };
     const int w_end = (hi + 31) >> 5;
     for (int w0 = lo >> 5; w0 < w_end; w0 += kReplayThreads) {
@@ -1275,7 +1275,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
             if (lane >= off) incl += v;
         }
         if (lane == 63) part[wave] = incl;
-        __syncthreads();
+        sync_block();
         int before = incl - cnt, all = 0;
         for (int v = 0; v < kReplayThreads / kWave; ++v) {
             const int p = part[v];
@@ -1294,7 +1294,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
             }
             if (tid == 0) s_ntodo = 0;
             if (tid < kReplayCap / 32) s_bit[tid] = 0;
-            __syncthreads();
+            sync_block();
             const float tau = s_tau;
             // the seed and the first batch, whole (the candidates of this pass are all marked)
             if (a.lo == 0 && hi <= (int64_t)a.k + a.batch && all == np && np == hi) {
@@ -1306,12 +1306,12 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                     if (i < ns) s_todo[i] = (uint16_t)i;
                 }
                 if (tid == 0) { s_most = 0; s_count = 0; }
-                __syncthreads();
+                sync_block();
                 measure(ns);
                 uint32_t most = 0;
                 for (int i = tid; i < ns; i += kReplayThreads) most = max(most, __float_as_uint(s_d2[i]));
                 wave_max(&s_most, most);
-                __syncthreads();
+                sync_block();
                 // (a distance that is no number is never in R: then R is not full yet)
                 const float tau1 = ns == a.k && s_most <= 0x7f800000u ? __uint_as_float(s_most) : __builtin_inff();
                 int mine = 0;
@@ -1326,24 +1326,24 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                     }
                 }
                 wave_add(&s_count, mine);
-                __syncthreads();
+                sync_block();
                 int nc = s_ntodo;
                 if (tid == 0) survivors += s_count;
                 int size = 1;
                 while (size < nc) size <<= 1;
                 for (int i = nc + tid; i < size; i += kReplayThreads) s_key[i] = ~0ull;
-                __syncthreads();
+                sync_block();
                 sort_keys(s_key, size);
                 const int first = nc < a.k ? nc : a.k;
                 for (int i = tid; i < first; i += kReplayThreads) s_todo[i] = (uint16_t)s_key[i];
                 if (tid == 0) s_most = 0;
-                __syncthreads();
+                sync_block();
                 measure(first);
                 most = 0;
                 for (int i = tid; i < first; i += kReplayThreads) most = max(most, __float_as_uint(s_d2[s_todo[i]]));
                 wave_max(&s_most, most);
                 if (tid == 0) s_ntodo = 0;
-                __syncthreads();
+                sync_block();
                 // (a distance that is no number bounds nothing)
                 const float cut = first == a.k && s_most <= 0x7f800000u ? __uint_as_float(s_most) : __builtin_inff();
                 int more = 0;                         // bounds are ascending: a prefix
@@ -1352,7 +1352,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                     if (need) { s_todo[i - first] = (uint16_t)s_key[i]; ++more; }
                 }
                 wave_add(&s_ntodo, more);
-                __syncthreads();
+                sync_block();
                 const int n2 = s_ntodo;
                 measure(n2);
                 nc = first + n2;
@@ -1366,7 +1366,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                 for (int i = tid; i < ns; i += kReplayThreads)
                     s_key[nc + i] = ((unsigned long long)__float_as_uint(s_d2[i]) << 32) | ((uint32_t)s_id[i] ^ 0x80000000u);
                 for (int i = nc + ns + tid; i < size; i += kReplayThreads) s_key[i] = ~0ull;
-                __syncthreads();
+                sync_block();
                 sort_keys(s_key, size);
                 const int have = nc + ns < a.k ? nc + ns : a.k;
                 for (int i = tid; i < kWave * E; i += kReplayThreads) {
@@ -1374,7 +1374,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                     rd2[i] = in ? __uint_as_float((uint32_t)(s_key[i] >> 32)) : __builtin_inff();
                     rid[i] = in ? (int32_t)((uint32_t)s_key[i] ^ 0x80000000u) : kEmptyId;
                 }
-                __syncthreads();
+                sync_block();
                 if (wave == 0) R.load(rd2, rid, a.k, lane);
                 continue;
             }
@@ -1388,7 +1388,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                     atomicOr(&s_bit[i >> 5], 1u << (i & 31));
                 }
             }
-            __syncthreads();
+            sync_block();
             const int nt = s_ntodo;
             measure(nt);
             if (wave == 0) {
@@ -1411,7 +1411,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                 replay_measured<E>(R, frozen_b, tau_f, s_cl, s_g, s_d2, s_id, s_todo, nt, a.batch, &s_steps, s_key);
                 if (lane == 0) s_tau = R.t_d2;
             }
-            __syncthreads();
+            sync_block();
             const TauSteps steps = s_steps;
             for (int i = tid; i < np; i += kReplayThreads) {
                 const int c = s_cl[i], b4 = c < a.k ? -1 : (c - a.k) / a.batch;
@@ -1420,21 +1420,21 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                     if (mask_row && (c >> 5) < a.mask_words) atomicOr(&mask_row[c >> 5], 1u << (c & 31));
                 }
             }
-            __syncthreads();
+            sync_block();
         }
-        __syncthreads();
+        sync_block();
     }
     if (a.n_exact) {
         if (tid == 0) s_count = 0;
-        __syncthreads();
+        sync_block();
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) survivors += __shfl_xor(survivors, off);
         if (lane == 0 && survivors) atomicAdd(&s_count, survivors);
-        __syncthreads();
+        sync_block();
         if (tid == 0) a.n_exact[q] = s_count + (a.lo > 0 ? a.n_exact[q] : 0);
     }
     if (wave == 0) R.store(rd2, rid);
-    __syncthreads();
+    sync_block();
     for (int i = tid; i < a.k; i += kReplayThreads) {
         const int32_t id = rid[i];
         a.out_ids[(size_t)q * a.k + i] = id == kEmptyId ? -1 : id;
@@ -1478,7 +1478,7 @@ __global__ __launch_bounds__(kReplayThreads) void range_exact_kernel(const Repla
         }
         if (lane == 63) part[wave] = incl;
         s_word[tid] = b;
-        __syncthreads();
+        sync_block();
         int before = incl - cnt, all = 0;
         for (int v = 0; v < kReplayThreads / kWave; ++v) {
             const int p = part[v];
@@ -1495,7 +1495,7 @@ __global__ __launch_bounds__(kReplayThreads) void range_exact_kernel(const Repla
                 ++at;
             }
             if (tid == 0) s_n = 0;
-            __syncthreads();
+            sync_block();
             // bounds beyond the radius leave at once; the others are listed in place of the candidates
             int keep[kReplayCap / kReplayThreads];
 #pragma unroll
@@ -1508,11 +1508,11 @@ __global__ __launch_bounds__(kReplayThreads) void range_exact_kernel(const Repla
                     else atomicAnd(&s_word[(c >> 5) - w0], ~(1u << (c & 31)));
                 }
             }
-            __syncthreads();
+            sync_block();
 #pragma unroll
             for (int v = 0; v < kReplayCap / kReplayThreads; ++v)
                 if (keep[v] >= 0) s_cl[atomicAdd(&s_n, 1)] = keep[v];
-            __syncthreads();
+            sync_block();
             const int n = s_n;
             constexpr int kHalves = kReplayThreads / 32;
             for (int i = half; i < n; i += 2 * kHalves) {
@@ -1529,14 +1529,14 @@ __global__ __launch_bounds__(kReplayThreads) void range_exact_kernel(const Repla
                     }
                 }
             }
-            __syncthreads();
+            sync_block();
         }
         out = s_word[tid];
         if (w < w_end) {
             if (out != b) bits[w] = out;
             results += __popc(out);
         }
-        __syncthreads();
+        sync_block();
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) results += __shfl_xor(results, off);

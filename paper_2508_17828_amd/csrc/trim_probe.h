@@ -72,7 +72,7 @@ __global__ __launch_bounds__(256) void probe_operands_kernel(const ProbeArgs a) 
         for (int i = 0; i < 8; ++i) sum += __builtin_fabsf(v[i]) < 1e18f ? v[i] : 0.0f;
         s_mu[t] = t < d ? sum * 0.125f : 0.0f;
     }
-    __syncthreads();
+    sync_block();
     const int64_t rows = list ? a.nlist : a.nq;
     const float *x = (list ? a.cent : a.queries) + (size_t)(row < rows ? row : rows - 1) * d;
     auto values = [&](int p, float (&v)[8]) {          // (d is a multiple of four)
@@ -159,7 +159,7 @@ __global__ __launch_bounds__(256) void probe_scores_kernel(const ProbeArgs a) {
             }
         }
     }
-    __syncthreads();
+    sync_block();
     const float e2 = (5.0f * a.d + 128.0f) * (1.0f / 16777216.0f);
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -230,7 +230,7 @@ __global__ __launch_bounds__(kWave) void probe_nearest_kernel(const ProbeArgs a)
             n += __popcll(m);
         }
     }
-    __syncthreads();
+    sync_block();
     if (n > kPrbList) {                                // (probe_rest_kernel)
         if (lane == 0) {
             const int list = (int)(q % kPrbLefts);
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(kWave) void probe_nearest_kernel(const ProbeArgs a)
         const int i = half_reduce_x4_row(lane32), mine = i == 0 ? l[0] : i == 1 ? l[1] : i == 2 ? l[2] : l[3];
         if (half_reduce_x4_writer(lane32) && i0 + i < n) s_key[i0 + i] = ((unsigned long long)__float_as_uint(dist) << 32) | (uint32_t)mine;
     }
-    __syncthreads();
+    sync_block();
     int32_t *out = a.out + (size_t)q * a.nprobe;
     for (int i = lane; i < n; i += kWave) {
         const unsigned long long k = s_key[i];
@@ -277,7 +277,7 @@ __device__ __forceinline__ int rest_count(const ProbeArgs &a, uint32_t *s_first)
         if (lane < kPrbLefts) s_first[lane + 1] = v;
         if (lane == 0) s_first[0] = 0;
     }
-    __syncthreads();
+    sync_block();
     return (int)s_first[kPrbLefts];
 }
 __device__ __forceinline__ uint32_t rest_query(const ProbeArgs &a, const uint32_t *s_first, int i) {
@@ -300,14 +300,14 @@ __global__ __launch_bounds__(kProbeThreads) void probe_rest_kernel(const ProbeAr
     for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
         const int g0 = (int)(u / tiles) * 8, first = (int)(u % tiles) * per, nqt = count - g0 < 8 ? count - g0 : 8;
         const int end = first + per < a.nlist ? first + per : a.nlist;
-        __syncthreads();                               // (the turn before is done with)
+        sync_block();                               // (the turn before is done with)
         if (tid < 8) s_q[tid] = rest_query(a, s_first, g0 + (tid < nqt ? tid : 0));
-        __syncthreads();
+        sync_block();
         for (int t = tid; t < 8 * a.d; t += kProbeThreads) {
             const int qi = t / a.d;
             q_lds[t] = a.queries[(size_t)s_q[qi] * a.d + (t - qi * a.d)];
         }
-        __syncthreads();
+        sync_block();
         for (int l0 = first + (tid >> 5) * 4; l0 < end; l0 += kRows)
             probe_distances<8>(q_lds, a.d, a.cent, a.nlist, l0, tid & 31, [&](int qi, int l, float v) {
                 if (qi < nqt) a.t[(size_t)s_q[qi] * a.lpad + l] = v;
@@ -320,7 +320,7 @@ __global__ __launch_bounds__(kWave) void probe_rest_select_kernel(const ProbeArg
     const int count = rest_count(a, s_first);
     for (int i = blockIdx.x; i < count; i += gridDim.x) {
         const uint32_t q = rest_query(a, s_first, i);
-        __syncthreads();                               // (the keys before these have been read)
+        sync_block();                               // (the keys before these have been read)
         select_least(reinterpret_cast<const uint32_t *>(a.t) + (size_t)q * a.lpad, a.nlist, a.nprobe, a.out + (size_t)q * a.nprobe, s_key, threadIdx.x);
     }
 }

@@ -568,7 +568,7 @@ void search_kernel(const SearchArgs a) {
         segp[p + 1] = (int)(e - s);  // length for now
         if (segl_fits) segl[p] = e > s ? lp : -1;
     }
-    __syncthreads();
+    sync_block();
     if (tid == 0) {
         int64_t run = 0;
         segp[0] = 0;
@@ -594,7 +594,7 @@ void search_kernel(const SearchArgs a) {
         for (int i = 0; i < kWorkCounters; ++i) ctl->work[i] = 0;
     }
     if (nphase == 1) fill_table<FS>(tab, a, q_lds, q, 0, a.M);
-    __syncthreads();
+    sync_block();
     if constexpr (FS) {   // the pair table of the first 8 code bytes (read after later barriers)
         for (int e = tid; e < 8 * kC; e += T) {
             const float *row = tab + (size_t)(e >> 8) * kByteEntries<true>;
@@ -629,7 +629,7 @@ void search_kernel(const SearchArgs a) {
             if (lane == 0) restv[i] = gsum;
         }
     }
-    __syncthreads();
+    sync_block();
     if (tid == 0) {
         float acc = 0.0f;
         restv[Mp / 4] = 0.0f;
@@ -835,14 +835,14 @@ void search_kernel(const SearchArgs a) {
                             atomicAdd(&ctl->nresult, 1);
                         }
                     });
-        __syncthreads();
+        sync_block();
         if (MODE == kKnn && tid < kWave) merge_batch<E>(sd2, spos, ns, rd2, rid, ctl, a.k, lane);
         if (tid == 0) {
             ctl->nexact += ns;
             ctl->nsurv = 0;
             if (acct) tally(kWorkRows, (uint32_t)ns);
         }
-        __syncthreads();
+        sync_block();
     };
 
     // ---- stage B by replay (k <= 64): the possibles of a stretch or span, already laid out in
@@ -879,7 +879,7 @@ void search_kernel(const SearchArgs a) {
         int32_t *s_id = reinterpret_cast<int32_t *>(smem + a.off_plb);  // ids (that area is dead by now)
         refine_rows(np, [&](int i) { return locate(c0 + spos[i]); },
                     [&](int i, float d2, int32_t id) { sd2[i] = d2; s_id[i] = id; });
-        __syncthreads();
+        sync_block();
         if (tid < kWave) {
             uint32_t *mrow = a.mask ? a.mask + (size_t)q * a.mask_words : nullptr;
             int n;
@@ -911,7 +911,7 @@ void search_kernel(const SearchArgs a) {
     // ---- seed: the first k candidates populate R, all with exact distances ----
     if (kseed > 0) {
         for (int i0 = 0; i0 < kseed; i0 += T) append(i0 + tid < kseed, i0 + tid);
-        __syncthreads();
+        sync_block();
         refine_and_select(kseed);
     }
 
@@ -958,7 +958,7 @@ void search_kernel(const SearchArgs a) {
     // next span length while the spans of a small-batch search still grow (a multiple of batch)
     int small_span = (MODE == kKnn && a.batch < kSmallBatch) ? (64 + a.batch - 1) / a.batch * a.batch : a.span;
     for (int c0 = c_begin + kseed; c0 < c_end;) {
-        __syncthreads();  // every thread is done with the previous stretch
+        sync_block();  // every thread is done with the previous stretch
         const float tau0 = ctl->tau;
         const AbandonLine line0 = abandon_line(tau0, a.two_gamma, ctl->b0);
 
@@ -988,7 +988,7 @@ void search_kernel(const SearchArgs a) {
             const int nb = (S + a.bucket - 1) / a.bucket;   // buckets (= batches unless they are very small)
             for (int b = tid; b < nb; b += T) cnt0[b] = 0;
             if (tid == 0) { ctl->nposs = 0; ctl->npassed = 0; }
-            __syncthreads();
+            sync_block();
             {
                 uint32_t *ring = reinterpret_cast<uint32_t *>(wq) + (size_t)wave * kRing;  // (segment << 16) | number
                 int head = 0, count = 0;  // same in every lane of the wave
@@ -1227,7 +1227,7 @@ void search_kernel(const SearchArgs a) {
                     drain_issue();
                 }
             }
-            __syncthreads();
+            sync_block();
             // A first pass that abandons less than half of the candidates only adds work (its
             // lookups are redone when the survivor's whole code is summed, piece after piece): the
             // query then goes on span by span, where a round takes a long piece of every code at
@@ -1245,7 +1245,7 @@ void search_kernel(const SearchArgs a) {
                 advance = S;
                 if (np > 0) {
                     counts_to_offsets(nb);
-                    __syncthreads();
+                    sync_block();
                     float *s_g = sd2 + a.scap;
                     for (int i = tid; i < np; i += T) {
                         const int cl = poss_cl[i];
@@ -1255,7 +1255,7 @@ void search_kernel(const SearchArgs a) {
                     }
                     if (a.bucket > a.batch) {
                         // a bucket holds several batches: put its few entries in scan order
-                        __syncthreads();
+                        sync_block();
                         for (int t = tid; t < nb; t += T) {
                             const int lo = t > 0 ? cnt0[t - 1] : 0, hi = cnt0[t];  // ends after the scatter
                             for (int x = lo + 1; x < hi; ++x) {
@@ -1275,7 +1275,7 @@ void search_kernel(const SearchArgs a) {
                 // would have fitted: the stretch just failed)
                 failed = true;
                 cur.init(segp, segd);
-                __syncthreads();
+                sync_block();
             }
             if (tid == 0) {   // (read again only after the barrier at the top of the loop)
                 // (long codes: a first pass that fails once rarely pays later; short codes: the
@@ -1298,7 +1298,7 @@ void search_kernel(const SearchArgs a) {
         const int span = c0 + span_len < c_end ? span_len : c_end - c0;
         const int nb = (span + a.batch - 1) / a.batch;
         for (int b = tid; b < nb; b += T) cnt0[b] = 0;
-        __syncthreads();
+        sync_block();
         // Rounds, wave by wave.  Each wave owns a contiguous slice of the span.  Round 0
         // bounds ALL its candidates over the first H0 subspaces, branch-free, U x 64
         // candidates in flight.  Whoever is not abandoned yet goes on the wave's own work
@@ -1367,9 +1367,9 @@ void search_kernel(const SearchArgs a) {
         int rnd = 0;  // rounds taken so far (the second one reads the rest of a code for the first time)
         for (int ph = 0; ph < (direct ? 0 : nphase); ++ph) {
             if (nphase > 1) {
-                __syncthreads();
+                sync_block();
                 fill_table<FS>(tab, a, q_lds, q, ph * Mp, Mp);
-                __syncthreads();
+                sync_block();
             }
             const bool last_ph = ph == nphase - 1;
             for (int h0 = 0; h0 < Mp;) {
@@ -1519,13 +1519,13 @@ void search_kernel(const SearchArgs a) {
                 if (qn == 0) break;  // this wave has nobody left in this phase
             }
         }
-        __syncthreads();
+        sync_block();
         // Several batches in the span and a result set of at most 64: replay (see above), unless
         // the possibles do not fit its arrays (a loose threshold: then batch by batch as below).
         int np_span = -1;
         if (MODE == kKnn && nb > 1) {
             counts_to_offsets(nb);
-            __syncthreads();
+            sync_block();
             np_span = ctl->nposs;
             if (np_span <= a.scap && np_span <= a.rcap) {
                 replay_np = np_span;
@@ -1557,16 +1557,16 @@ void search_kernel(const SearchArgs a) {
                 const bool live = i < blen && plbs[l0 + i] <= tau;
                 append(live, c0 + l0 + i);
             }
-            __syncthreads();
+            sync_block();
             const int ns = ctl->nsurv;
-            __syncthreads();  // nobody appends for the next batch before everyone has read ns
+            sync_block();  // nobody appends for the next batch before everyone has read ns
             if (ns > 0) refine_and_select(ns);
         }
         if (replay_np < 0) advance = span;
         if (tid == 0) ctl->hold -= advance;   // (several barriers after everybody read it)
         }  // span path
         if (replay_np > 0) {
-            __syncthreads();   // the possibles are in place
+            sync_block();   // the possibles are in place
             refine_and_replay(replay_np, c0);
         }
         c0 += advance;
@@ -1575,7 +1575,7 @@ void search_kernel(const SearchArgs a) {
     // ---- epilogue ----
     // (the last stretch may have ended in a replay by the first wave alone: every thread that
     // writes results must see its R)
-    __syncthreads();
+    sync_block();
     if (MODE == kKnn) {
         for (int i = tid; i < a.k; i += T) {
             const int32_t id = rid[i];

@@ -27,7 +27,7 @@ __device__ __forceinline__ void segment_table(const int64_t *list_offsets, const
         segd[p] = (int)s;
         segp[p + 1] = (int)(e - s);
     }
-    __syncthreads();
+    sync_block();
     if (threadIdx.x < kWave) {
         const int lane = threadIdx.x;
         uint32_t carry = 0;
@@ -50,7 +50,7 @@ __device__ __forceinline__ void segment_table(const int64_t *list_offsets, const
         }
         if (lane == 0) segp[0] = 0;
     }
-    __syncthreads();
+    sync_block();
 }
 
 // The same where it has been made already (invert_place_kernel): one look at memory instead of three, one after the other.
@@ -65,7 +65,7 @@ __device__ __forceinline__ void segment_table_ready(const int32_t *seg, int nseg
         segd[0] = 0;
     }
     if (threadIdx.x == 0) segp[0] = 0;
-    __syncthreads();
+    sync_block();
 }
 
 // Into a word of the LDS, one atomic a wave: lanes with a value each, the compiler would let take their turns (64 of them, some
@@ -228,7 +228,7 @@ __device__ __forceinline__ void sort_keys(unsigned long long *key, int n) {
                 const unsigned long long p = key[x], q = key[y];
                 if ((p > q) == ((x & size) == 0)) { key[x] = q; key[y] = p; }
             }
-            __syncthreads();
+            sync_block();
         }
 }
 

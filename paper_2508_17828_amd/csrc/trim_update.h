@@ -56,7 +56,7 @@ __global__ __launch_bounds__(kSortThreads) void kmeans_sort_kernel(const SortArg
     }
     for (int i = tid; i < waves * pitch / 2; i += T) reinterpret_cast<uint32_t *>(cnt)[i] = 0u;
     if (tid == 0) s_carry = 0;
-    __syncthreads();
+    sync_block();
     const unsigned long long below = (1ull << lane) - 1ull;
     int rank[LOOPS];
 #pragma unroll
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kSortThreads) void kmeans_sort_kernel(const SortArg
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }
-    __syncthreads();
+    sync_block();
     // counts -> first places
     uint16_t *starts = a.starts + ((size_t)y * a.nchunk + chunk) * (K + 1);
     for (int c0 = 0; c0 < K; c0 += T) {
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kSortThreads) void kmeans_sort_kernel(const SortArg
             if (lane >= off) incl += o;
         }
         if (lane == kWave - 1) s_part[wave] = incl;
-        __syncthreads();
+        sync_block();
         int at = s_carry + incl - run;
         for (int v = 0; v < wave; ++v) at += s_part[v];
         if (k < K) {
@@ -102,12 +102,12 @@ __global__ __launch_bounds__(kSortThreads) void kmeans_sort_kernel(const SortArg
                 to += n;
             }
         }
-        __syncthreads();
+        sync_block();
         if (tid == T - 1) {
             s_carry = at + run;
             if (c0 + T >= K) starts[K] = (uint16_t)(at + run);
         }
-        __syncthreads();
+        sync_block();
     }
     uint16_t *list = a.list + (size_t)y * a.ns + r0;
 #pragma unroll
@@ -142,12 +142,12 @@ __global__ __launch_bounds__(kSumThreads) void kmeans_sums_kernel(const SortArgs
     int64_t count = 0;
     for (int i0 = 0; i0 < a.nchunk; i0 += kSumChunks) {
         const int nc = a.nchunk - i0 < kSumChunks ? a.nchunk - i0 : kSumChunks;
-        __syncthreads();
+        sync_block();
         for (int e = tid; e < nc * (ncl + 1); e += kSumThreads) {
             const int i = e / (ncl + 1), c = e - i * (ncl + 1);
             s_run[i * P + c] = starts[(size_t)(i0 + i) * (K + 1) + c];
         }
-        __syncthreads();
+        sync_block();
         const int first = lane < nc ? s_run[lane * P] : 0, n = lane < nc ? s_run[lane * P + ncl] - first : 0;
         int incl = n;
 #pragma unroll
@@ -161,12 +161,12 @@ __global__ __launch_bounds__(kSumThreads) void kmeans_sums_kernel(const SortArgs
             s_adj[lane] = incl - n - first;
             s_end[lane] = lane < nc ? incl : 0x7fffffff;
         }
-        __syncthreads();
+        sync_block();
         for (int e = tid; e < nc * (ncl + 1); e += kSumThreads) {
             const int i = e / (ncl + 1), c = e - i * (ncl + 1);
             s_run[i * P + c] += s_adj[i];
         }
-        __syncthreads();
+        sync_block();
         float f[kPer];
         int row[kPieces];                  // a piece's rows are known before its values are asked for: in their chunk,
         int from[kPieces];                 // and the chunk's first (added up later: nothing waits for one before the next is asked for)
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(kSumThreads) void kmeans_sums_kernel(const SortArgs
         int i = 0, buf = 0;                // i: the first chunk with rows in the piece or after it
         for (int p0 = 0; p0 < total; p0 += cap, buf ^= 1) {
             store(s_vals[buf]);
-            __syncthreads();
+            sync_block();
             const int p1 = p0 + cap < total ? p0 + cap : total;
             if (p1 < total) load(p1);
             if (p1 + cap < total) look_up(p1 + cap);
@@ -307,7 +307,7 @@ __global__ __launch_bounds__(kUpdCols) void kmeans_rows_kernel(const SortArgs a)
             if (lane >= off) incl += o;
         }
         if (lane == kWave - 1) s_part[wave] = incl;
-        __syncthreads();
+        sync_block();
         int before = incl - n, total = 0;
         for (int v = 0; v < T >> 6; ++v) {
             if (v < wave) before += s_part[v];
@@ -316,7 +316,7 @@ __global__ __launch_bounds__(kUpdCols) void kmeans_rows_kernel(const SortArgs a)
         count += total;
         s_end[tid] = before + n;
         s_off[tid] = i * a.rows + s - before;
-        __syncthreads();
+        sync_block();
         for (int p0 = 0; p0 < total; p0 += kRowsCap) {
             const int np = total - p0 < kRowsCap ? total - p0 : kRowsCap;
             for (int k = tid; k < np; k += T) {
@@ -324,7 +324,7 @@ __global__ __launch_bounds__(kUpdCols) void kmeans_rows_kernel(const SortArgs a)
                 for (int half = T >> 1; half > 0; half >>= 1) at += s_end[at + half - 1] <= p0 + k ? half : 0;
                 s_rows[k] = (i0 + at) * a.rows + list[p0 + k + s_off[at]];
             }
-            __syncthreads();
+            sync_block();
             float f[kRowsFly], h[kRowsFly];
             auto load = [&](int k, float (&to)[kRowsFly]) {
 #pragma unroll
@@ -348,9 +348,9 @@ __global__ __launch_bounds__(kUpdCols) void kmeans_rows_kernel(const SortArgs a)
                 if (k + 2 * kRowsFly < np) load(k + 2 * kRowsFly, f);
                 add(k + kRowsFly, h);
             }
-            __syncthreads();
+            sync_block();
         }
-        __syncthreads();       // s_part is read
+        sync_block();       // s_part is read
     }
     if (on && count > 0) a.cent[((size_t)y * K + c) * a.dim + t] = (float)(sum / (double)count);
 }

@@ -708,10 +708,10 @@ def test_captured_and_replayed(T, nq):
             assert torch.equal(a, b), rep
 
 
-# one result entry per lane, codes with and without a scan head, query counts at which another block size is taken
-# (make_plan): who asks beside them changes nobody's answer, and the first are the oracle's
+# one and two result entries per lane at their edges, codes with and without a scan head, query counts at which another block size is
+# taken (make_plan): who asks beside them changes nobody's answer, and the first are the oracle's
 @pytest.mark.parametrize("d,M,bits", ((100, 20, 8), (128, 16, 8), (128, 32, 8), (384, 48, 8), (128, 64, 4)))
-@pytest.mark.parametrize("k,batch", ((1, 512), (10, 100), (64, 256)))
+@pytest.mark.parametrize("k,batch", ((1, 512), (10, 100), (64, 256), (65, 100), (128, 512)))
 def test_answers_do_not_depend_on_the_number_of_queries(T, d, M, bits, k, batch):
     ix, q, probes = built(T, 20000, d, M, bits, 40, 1100, 9, 1.0, 2.0, d + M + k)
     want = single_kernel(T, ix, q, k, 0.3, batch, probes, None)
