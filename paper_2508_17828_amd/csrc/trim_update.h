@@ -156,6 +156,7 @@ __global__ __launch_bounds__(kSumThreads) void kmeans_sums_kernel(const SortArgs
             if (lane >= off) incl += o;
         }
         const int total = __builtin_amdgcn_readlane(incl, kWave - 1);      // (the same in every wave)
+        if (total == 0) continue;          // (no row to look up: the search below would end behind the last chunk)
         if (tid < kWave) {
             s_off[lane] = (i0 + lane) * a.rows + first - (incl - n);
             s_adj[lane] = incl - n - first;

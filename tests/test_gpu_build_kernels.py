@@ -72,10 +72,10 @@ def test_update_of_coarse_centroids_of_long_rows(T, oracle, ns, d, nlist):
 
 # the update with work space: chunks of 4096 and 1024 rows that are full, one short and one over, more than 64 of them, rows of every
 # kind of sub-vector (four values at a time or one by one, in the LDS or straight from memory), fewer counters than 1024 threads
-# have room for, half of the rows in one cluster; and the same without it
+# have room for, half of the rows in one cluster and none in two; and the same without it
 @pytest.mark.parametrize("ns,d,M,bits", [(32768, 64, 16, 8), (33001, 80, 16, 8), (36863, 128, 16, 8), (45057, 144, 12, 8), (131073, 8, 4, 8),
                                          (26215, 340, 20, 8), (40001, 32, 16, 4), (270001, 16, 4, 8),
-                                         (1025, 12, 33, 0), (2047, 20, 100, 0), (3072, 24, 7, 0), (262145, 4, 50, 0), (40000, 4, 4990, 0), (70000, 300, 3, 0)])
+                                         (1025, 12, 33, 0), (9300, 8, 20, 0), (5000, 16, 30, 0), (2047, 20, 100, 0), (3072, 24, 7, 0), (262145, 4, 50, 0), (40000, 4, 4990, 0), (70000, 300, 3, 0)])
 def test_update_with_work_space(T, oracle, ns, d, M, bits):
     import ctypes as C
     import torch
@@ -89,6 +89,7 @@ def test_update_with_work_space(T, oracle, ns, d, M, bits):
     x[: ns // 2] = x[0]
     K = M if bits == 0 else 256 if bits == 8 else 16
     init = rng.choice(np.arange(ns // 2, ns), K, replace=False).astype(np.int32)
+    init[K // 2] = init[K - 1] = init[0]             # (the first of equal centroids takes the rows)
     ref = index_build.train_ivf_fixed if bits == 0 else index_build.train_pq_fixed if bits == 8 else index_build.train_pq_fs_fixed
     want = ref(x, M, 2, init)
     g, gi = torch.from_numpy(x).cuda(), torch.from_numpy(init).cuda()
