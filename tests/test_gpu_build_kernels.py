@@ -72,7 +72,8 @@ def test_update_of_coarse_centroids_of_long_rows(T, oracle, ns, d, nlist):
 
 # the update with work space: chunks of 4096 and 1024 rows that are full, one short and one over, more than 64 of them, rows of every
 # kind of sub-vector (four values at a time or one by one, in the LDS or straight from memory), fewer counters than 1024 threads
-# have room for, half of the rows in one cluster and none in two; and the same without it
+# have room for, half of the rows in one cluster and none in two; and the same without it, codes, distances and assignments too.  Around the
+# work space nothing is written
 @pytest.mark.parametrize("ns,d,M,bits", [(32768, 64, 16, 8), (33001, 80, 16, 8), (36863, 128, 16, 8), (45057, 144, 12, 8), (131073, 8, 4, 8),
                                          (26215, 340, 20, 8), (40001, 32, 16, 4), (270001, 16, 4, 8),
                                          (1025, 12, 33, 0), (9300, 8, 20, 0), (5000, 16, 30, 0), (2047, 20, 100, 0), (3072, 24, 7, 0), (262145, 4, 50, 0), (40000, 4, 4990, 0), (70000, 300, 3, 0)])
@@ -95,13 +96,14 @@ def test_update_with_work_space(T, oracle, ns, d, M, bits):
     g, gi = torch.from_numpy(x).cuda(), torch.from_numpy(init).cuda()
     fn = T.trim_train_ivf if bits == 0 else T.trim_train_pq if bits == 8 else T.trim_fs_train_pq
     np.testing.assert_array_equal(fn(g, M, 2, gi).cpu().numpy().view(np.uint32), want.view(np.uint32))
-    ws = torch.empty((need + 4,), dtype=torch.uint8, device="cuda")
+    ws = torch.empty((4 + need + 65536,), dtype=torch.uint8, device="cuda")
     p = lambda t: C.c_void_p(t.data_ptr())
     stream = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    used = []
     for shift, bytes_ in ((4, need), (0, need - 1)):                  # (the last: the kernel without)
-        ws.fill_(0xff)
+        ws.fill_(0xa5)
         out = torch.empty(want.shape, dtype=torch.float32, device="cuda")
-        codes, dlx = torch.empty((ns * max(M, 4),), dtype=torch.uint8, device="cuda"), torch.empty((ns,), device="cuda")
+        codes, dlx = torch.zeros((ns * max(M, 4),), dtype=torch.uint8, device="cuda"), torch.zeros((ns,), device="cuda")
         tail = [C.c_void_p(ws.data_ptr() + shift), bytes_, stream]
         if bits == 0:
             rc = L.trim_train_ivf_ws(p(g), ns, d, M, 2, p(gi), p(out), p(codes), *tail)
@@ -111,6 +113,11 @@ def test_update_with_work_space(T, oracle, ns, d, M, bits):
             rc = L.trim_fs_train_pq_ws(p(g), ns, d, M, 2, p(gi), p(out), p(codes), *tail)
         assert rc == 0
         np.testing.assert_array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32))
+        used.append((codes, dlx.view(torch.int32)))
+        assert (ws[:4] == 0xa5).all() and (ws[4 + need:] == 0xa5).all()
+    assert (ws == 0xa5).all()
+    for with_it, without in zip(*used):
+        assert torch.equal(with_it, without)
 
 
 @pytest.mark.parametrize("ns,M,bits", [(8192, 32, 8), (300, 32, 8), (20001, 32, 8), (8192, 64, 4), (20001, 64, 4)])
@@ -206,12 +213,13 @@ def test_nearest_list_by_work_space(T, oracle, n, d, nlist):
     stream = torch.cuda.current_stream().cuda_stream
     need = T.lib().trim_ivf_nearest_workspace_bytes(n, d, nlist)
     assert need > 0
-    space = torch.empty((need + 4,), dtype=torch.uint8, device="cuda")
+    space = torch.full((4 + need + 65536,), 0xa5, dtype=torch.uint8, device="cuda")
     for ws, size in ((None, 0), (space.data_ptr(), need - 1), (space.data_ptr() + 4, need)):
         out.fill_(-7)
         assert T.lib().trim_ivf_probe_ws(C.c_void_p(xg.data_ptr()), n, d, C.c_void_p(cg.data_ptr()), nlist, 1, C.c_void_p(out.data_ptr()),
                                          C.c_void_p(ws), size, C.c_void_p(stream)) == 0
         np.testing.assert_array_equal(out.cpu().numpy(), want)
+    assert (space[:4] == 0xa5).all() and (space[4 + need:] == 0xa5).all()
 
 
 # 4-bit codes: sub-vectors of two values (whole and ragged 32-column slices, odd row counts) and of four
