@@ -195,7 +195,8 @@ int trim_train_ivf(const float *train, int64_t ns, int32_t d, int32_t nlist, int
                    const int32_t *init_rows, float *centroids_out, int32_t *assign_ws, void *stream);
 /* trim_train_pq_ws, trim_train_ivf_ws: the same centroids, codes, distances and assignments with a workspace of
  * trim_train_*_workspace_bytes, device, contents on entry ignored; with it the rows are put in
- * the order of their clusters once an iteration.  0 bytes, NULL or less than that: trim_train_pq, trim_train_ivf. */
+ * the order of their clusters once an iteration.  Codebooks: about ns (4 d + 2 M) bytes (sub-vectors of up to 16 values, else
+ * 2 ns M); lists: about 2 ns.  0 bytes, NULL or less than that: trim_train_pq, trim_train_ivf. */
 size_t trim_train_pq_workspace_bytes(int64_t ns, int32_t d, int32_t M);
 int trim_train_pq_ws(const float *train, int64_t ns, int32_t d, int32_t M, int32_t iters,
                      const int32_t *init_rows, float *codebooks_out, uint8_t *codes_ws, float *dlx_ws,

@@ -1,5 +1,5 @@
 // The nearest list of many vectors of at most 128 values (trim_ivf_probe with one probe, trim_train_ivf) with work space: the lists'
-// operands are made once (assign_operands_kernel), and a wave keeps 64 vectors' operands in registers while the lists pass by
+// operands are made once (assign_operands_kernel), and a wave keeps 32 vectors' operands in registers while the lists pass by
 // (assign_tiles_kernel).  Scores, their bounds and what is measured exactly: as in assign_rows_kernel (trim_aux.h), which goes without.
 #pragma once
 

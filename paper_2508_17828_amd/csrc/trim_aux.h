@@ -2562,7 +2562,7 @@ __global__ __launch_bounds__(kAsgThreads, 2) void assign_rows_kernel(const float
 // The vectors that assign_rows_kernel or assign_mfma_kernel marked: every centroid measured by the exact rule, eight
 // vectors at a time (ivf_probe_kernel's distance loop).  A workgroup looks after up to kFixSpan
 // vectors, so that even a mark in a hundred fills its groups; the last one takes as many vectors' worth of work as it has, or nearly
-// (ten iterations of 65,536 x 128 against 1024, two or three marks a workgroup: 208 -> 110 us).
+// (ten iterations of 65,536 x 128 against 1024, two or three marks a workgroup: 208 -> 101 us, 96 to 110 by machine).
 // T: 1024 threads where there is at most a workgroup per CU, where few are marked (rows of up to 128 values) and for rows of more than 1024
 // (whole assignments, 40,000 x 1536 in 200 lists: 324 / 337 us), else 512 (us, 1024 / 512
 // threads: 16,384 x 768 36 / 45, x 1536 126 / 163, 8000 x 768, all marked, 2415 / 3189, whole assignments of 200,000 x 128 171 / 174, x 32

@@ -40,11 +40,6 @@ __device__ __forceinline__ void sync_block() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-struct Hit {
-    float d2;
-    int32_t id;
-};
-
 // Correctly rounded binary32 square root.  (The __fsqrt_rn intrinsic maps to the bare
 // hardware approximation, which is within 1 ulp but not always the nearest value; sqrtf
 // is expanded by the compiler into the approximation plus a correction step.)

@@ -278,8 +278,9 @@ struct ResultRegs {
         load_kth();
     }
     // One item that beats the k-th entry, the same in all lanes: an entry becomes the lesser of itself and the greater of the item and the
-    // entry before it.  No ranks, whose ballots go through the scalar unit: 10,000 queries over 1M x 128 1253 -> 1231 us, 4-bit codes
-    // 488 -> 476, 500 queries x 300,000 x 960, k = 100, 2141 -> 2111.  (What is shifted beyond the k-th place stays there: nobody looks at it, and it is not below the k-th.)
+    // entry before it.  No ranks, whose ballots go through the scalar unit: one or two per cent of a search, as much as runs differ by (10,000
+    // queries over 1M x 128 1253 -> 1231 us, elsewhere 1288 -> 1270; 4-bit codes 488 -> 476, 500 -> 489; 500 queries x 300,000 x 960, k = 100,
+    // 2141 -> 2111).  (What is shifted beyond the k-th place stays there: nobody looks at it, and it is not below the k-th.)
     __device__ __forceinline__ void insert(unsigned long long x) {
         // last slot of the lane below (whole-wave shift right by one lane; lane 0: below every item)
         const unsigned long long c = ((unsigned long long)(uint32_t)__builtin_amdgcn_update_dpp(0, (int)(r[E - 1] >> 32), 0x138, 0xf, 0xf, false) << 32) |

@@ -10,7 +10,7 @@
 // Rows are ascending inside a chunk's run of a cluster and from chunk to chunk, so every sum is added in row order.
 //
 // 65,536 rows: 32 x 256 x 4 coordinates 62 -> 43 us an iteration (sort 13.6, sums 29) and 13 us once for the columns; 1024 x 128 coordinates
-// 41 -> 25 us (sort 5.4, rows 19.6).  Bound by latency: a workgroup's first places, then its rows' numbers, then its rows come one after
+// 41 -> 21 to 25 us by machine (sort 5.3, rows 15.4 to 19.6).  Bound by latency: a workgroup's first places, then its rows' numbers, then its rows come one after
 // the other from beyond the L2, 4000 clocks each, and a clusters' longest run in a chunk takes 20 clocks a value; the sort by its
 // ballots.  (Values stored in cluster order instead of numbers: sort 23 us, and as much again to read them.)
 #pragma once
@@ -266,8 +266,8 @@ __global__ __launch_bounds__(kSumThreads) void kmeans_sums_kernel(const SortArgs
     if (on && count > 0) a.cent[((size_t)y * K + c0 + cl) * dim + t] = (float)(sum / (double)count);
 }
 
-// The rows' sub-vectors side by side, clustering by clustering: [ny][ns][dim].  Once per training: read out of whole rows, the sort
-// kernel brings a cache line for every 16 or 32 bytes, in every iteration.  64 rows per workgroup.
+// The rows' sub-vectors side by side, clustering by clustering: [ny][ns][dim].  Once per training: read out of whole rows,
+// kmeans_sums_kernel would bring a cache line for every 16 or 32 bytes, in every iteration.  64 rows per workgroup.
 __global__ __launch_bounds__(256) void kmeans_columns_kernel(const float *__restrict__ x, int64_t ns, int64_t stride, int dim, int ny,
                                                              float *__restrict__ out) {
     const int64_t r = (int64_t)blockIdx.x * kWave + (threadIdx.x & (kWave - 1));
