@@ -62,8 +62,9 @@ constexpr int64_t kCus = 256;
 
 // Block size and LDS bytes per workgroup for 4, 3, 2 and 1 workgroups per CU (LDS is handed
 // out in 1280-byte granules).  Three 512-thread workgroups, or two of 768 threads, are 6 waves
-// per SIMD: only the kernel instances built for that register budget (result_slots == 1) can use
-// those tiers.  The second is for tables too long for three workgroups (M = 40..60): with 24
+// per SIMD: only the kernel instances built for that register budget (result_slots <= 2) can use
+// those tiers (two entries per lane: k = 100, 8000 queries, 1M x 128, M = 32, 1652 -> 1182 us; 4000 x 500,000 x 384, M = 48, 970 ->
+// 839).  The second is for tables too long for three workgroups (M = 40..60): with 24
 // instead of 16 waves per CU more rows and code blocks are in flight (5M x 384, M = 48: the
 // scan went 5.06 -> 4.70 ms); it is kept to codes under 64 bytes, which the 80-register
 // instance is the better one for anyway.
@@ -143,8 +144,11 @@ bool fit_plan(int d, int M, int row_bytes, int nsegs, int cap, int batch, int k,
         pl->lds = off;
         pl->threads = tier.threads;
         // the 80-register instance: needed for three workgroups per CU, and the better one for short
-        // codes in any case (the other's bulk rounds and deeper refine pipelines pay from 64 code bytes on)
-        pl->lean = !(P == 1 && M <= 256 && (tier.needs_6_waves || M < 64)) ? kFullInstance
+        // codes in any case (the other's bulk rounds and deeper refine pipelines pay from 64 code bytes on), but with two result
+        // entries per lane not where four small workgroups share a CU, whose 16 waves get 128 registers anyway (k = 100: 1000 queries x
+        // 1.18M x 100, M = 20: 459 / 467 us; 4-bit codes, 900 x 1M x 128: 286 / 290)
+        const bool four = tier.lds < kLdsBytes / 3;
+        pl->lean = !(P == 1 && M <= 256 && (tier.needs_6_waves || (M < 64 && !(four && result_slots(k) == 2)))) ? kFullInstance
                    : d <= 128 ? kLeanShortRows : kLeanLongRows;
         pl->wqcap = wqcap;
         pl->cruise = p > 0 ? cruise : 0;
@@ -173,18 +177,20 @@ bool make_plan(int d, int M, bool fs, int nseg, int cap, int batch, int k, bool 
         if (M % P || (M / P) % 4) continue;
         for (int t = 0; t < nt; ++t) {
             const Tier &tier = kTiers[t];
-            if (tier.needs_6_waves && (range || result_slots(k) != 1)) continue;
+            if (tier.needs_6_waves && (range || result_slots(k) > 2)) continue;
             if (tier.short_codes_only && M >= 64) continue;
             // Fewer queries than workgroups that fit side by side: more threads a query, one or two workgroups per CU (32 lists of 1024, k = 10,
             // M = 32: 256 queries 125 -> 109 us, 512 142 -> 128; 4-bit codes 94 -> 82, 102 -> 98; 350 queries one per CU: 126 -> 150; 700
-            // two per CU: 150 -> 187).
-            if (!range && result_slots(k) == 1 && (nq <= kCus ? t + 1 < nt : nq <= 2 * kCus && tier.lds < kLdsBytes / 2)) continue;
+            // two per CU: 150 -> 187; k = 100, 200 queries: M = 32 159 -> 128, M = 20 351 -> 159, 4-bit codes 224 -> 139).
+            if (!range && result_slots(k) <= 2 && (nq <= kCus ? t + 1 < nt : nq <= 2 * kCus && tier.lds < kLdsBytes / 2)) continue;
             // A short table would fit four small workgroups per CU (16 waves); the instance built
             // for six waves per SIMD does better as three 512-thread ones (24 waves), which also have twice the threads for
             // a query where all are resident at once.  1.18M x 100, M = 20, 32 of 1024 lists, k = 10: 600 queries 333 -> 230 us, 1500
-            // 609 -> 425, 8000 2266 -> 1841; M = 16: 167 -> 122, 8000 771 -> 740.  With 8-bit codes not between 768 and 1024 queries,
-            // which four a CU take in one go (M = 16, batches of 256, 1000 queries: 169 / 211).
-            if (t == 0 && !range && result_slots(k) == 1 && (fs || nq <= 3 * kCus || nq > 4 * kCus)) continue;
+            // 609 -> 425, 8000 2266 -> 1841; M = 16: 167 -> 122, 8000 771 -> 740; k = 100: 700 queries 404 -> 276, 2000 789 -> 652, 8000 2588 ->
+            // 2058; M = 16 4000 510 -> 462.  With 8-bit codes not between 768 and 1024 queries, which four a CU take in one go (M = 16,
+            // batches of 256, 1000 queries: 169 / 211), and not with 4-bit codes and two result entries per lane beyond that (8000
+            // queries 1040 / 1082; 700 in one go 260 -> 210).
+            if (t == 0 && !range && (nq <= 3 * kCus ? result_slots(k) <= 2 : fs ? result_slots(k) == 1 : result_slots(k) <= 2 && nq > 4 * kCus)) continue;
             if (t + 1 < nt) {
                 // below the last tier a layout must leave room for a cruise when one is possible
                 // at all (else the next tier is tried first)
@@ -219,7 +225,10 @@ int launch_search(bool range, bool fs, const SearchArgs &a, const Plan &pl, dim3
             if (pl.lean == kLeanLongRows) return fs ? launch_search_knnleanlong_e1_c4(a, pl, grid, st) : launch_search_knnleanlong_e1_c8(a, pl, grid, st);
             if (pl.lean) return fs ? launch_search_knnlean_e1_c4(a, pl, grid, st) : launch_search_knnlean_e1_c8(a, pl, grid, st);
             return fs ? launch_search_knn_e1_c4(a, pl, grid, st) : launch_search_knn_e1_c8(a, pl, grid, st);
-        case 2: return fs ? launch_search_knn_e2_c4(a, pl, grid, st) : launch_search_knn_e2_c8(a, pl, grid, st);
+        case 2:
+            if (pl.lean == kLeanLongRows) return fs ? launch_search_knnleanlong_e2_c4(a, pl, grid, st) : launch_search_knnleanlong_e2_c8(a, pl, grid, st);
+            if (pl.lean) return fs ? launch_search_knnlean_e2_c4(a, pl, grid, st) : launch_search_knnlean_e2_c8(a, pl, grid, st);
+            return fs ? launch_search_knn_e2_c4(a, pl, grid, st) : launch_search_knn_e2_c8(a, pl, grid, st);
         case 4: return fs ? launch_search_knn_e4_c4(a, pl, grid, st) : launch_search_knn_e4_c8(a, pl, grid, st);
         default: return fs ? launch_search_knn_e16_c4(a, pl, grid, st) : launch_search_knn_e16_c8(a, pl, grid, st);
     }

@@ -20,7 +20,7 @@ struct Plan {
     uint32_t off_q, off_segp, off_segd, off_rest, off_seglb, off_spos, off_sd2, off_sidx, off_rd2, off_rid, off_ctl;
     uint32_t off_plb, off_cnt, off_wq;
     int span, wqcap, cruise, poss_cap, scap, rcap, bucket;
-    int lean;    // a LeanKind; small-k kNN: launch an 80-register instance (six waves per SIMD, or short codes)
+    int lean;    // a LeanKind; kNN, up to 128 results: launch an 80-register instance (six waves per SIMD, or short codes)
 };
 
 // Records a failed HIP call for trim_last_hip_error and returns TRIM_HIP_ERROR.
@@ -60,6 +60,10 @@ int launch_settle(FewArgs a, hipStream_t st);
 int launch_replay(ReplayArgs a, int64_t nslots, hipStream_t st);
 
 TRIM_DECLARE_LAUNCH(launch_search_knnlean_e1_c8);
+TRIM_DECLARE_LAUNCH(launch_search_knnlean_e2_c8);
+TRIM_DECLARE_LAUNCH(launch_search_knnlean_e2_c4);
+TRIM_DECLARE_LAUNCH(launch_search_knnleanlong_e2_c8);
+TRIM_DECLARE_LAUNCH(launch_search_knnleanlong_e2_c4);
 TRIM_DECLARE_LAUNCH(launch_search_knnlean_e1_c4);
 TRIM_DECLARE_LAUNCH(launch_search_knnleanlong_e1_c8);
 TRIM_DECLARE_LAUNCH(launch_search_knnleanlong_e1_c4);

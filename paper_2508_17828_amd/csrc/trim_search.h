@@ -478,7 +478,7 @@ __device__ __forceinline__ int replay_batches(const int32_t *s_cl, const float *
 
 // E = result_slots(k) is a template parameter of the kernel, so that the common small-k case
 // does not carry the registers of the wide result sets.
-// LEAN_KIND (kNN, E = 1 only; see LeanKind): the instances held to 80 registers (6 waves per SIMD), so that three
+// LEAN_KIND (kNN, E = 1 and 2 only; see LeanKind): the instances held to 80 registers (6 waves per SIMD), so that three
 // 512-thread workgroups share a CU when the table is short enough for that; it goes without
 // the bulk rounds over long codes, the tiled code copy and the deeper refine pipelines, which
 // the other instances (128 registers, at most 4 waves per SIMD) use.
@@ -496,7 +496,7 @@ __global__ __launch_bounds__(1024)
 __attribute__((amdgpu_waves_per_eu(LEAN_KIND != kFullInstance ? kLeanWavesPerSimd : 4)))
 void search_kernel(const SearchArgs a) {
     constexpr bool LEAN = LEAN_KIND != kFullInstance;
-    static_assert(!LEAN || (MODE == kKnn && E == 1), "the lean instances are the small-k kNN ones");
+    static_assert(!LEAN || (MODE == kKnn && E <= 2), "the lean instances are kNN ones for up to 128 results");
     // The tiled copy of the codes is read by the instances with 16-byte code loads, except the
     // lean ones, whose codes are short (they read the row-major array).
     constexpr bool kTiledOk = VEC == 4 && !LEAN;

@@ -1,6 +1,6 @@
 // One group of instances of the fused scan kernel and its launcher.  Compiled once per
 // (TRIM_INST_MODE: 0 kNN / 1 range, TRIM_INST_E: result entries per lane of the merging wave,
-// TRIM_INST_BITS: 8- or 4-bit codes, TRIM_INST_LEAN: an 80-register small-k kNN instance), each
+// TRIM_INST_BITS: 8- or 4-bit codes, TRIM_INST_LEAN: an 80-register kNN instance), each
 // time into an object of its own.
 #include <atomic>
 
@@ -10,7 +10,7 @@
 #error "define TRIM_INST_MODE, TRIM_INST_E and TRIM_INST_BITS"
 #endif
 #ifndef TRIM_INST_LEAN
-#define TRIM_INST_LEAN 0   // 1, 2: the 80-register instances of small-k kNN (see LeanKind)
+#define TRIM_INST_LEAN 0   // 1, 2: the 80-register instances of kNN with up to 128 results (see LeanKind)
 #endif
 
 #define TRIM_CAT_(a, b, c, d, e, f) a##b##c##d##e##f
