@@ -124,7 +124,9 @@ bool fit_plan(int d, int M, int row_bytes, int nsegs, int cap, int batch, int k,
         if (total > tier.lds) continue;
         pl->P = P;
         pl->Mp = Mp;
-        pl->vec = (M % 16 == 0 && Mp % 16 == 0) ? 4 : (M % 8 == 0 && Mp % 8 == 0) ? 2 : 1;
+        pl->vec = (M % 16 == 0 && Mp % 16 == 0) ? 4 : (M % 8 == 0 && Mp % 8 == 0) ? 2 : (!range && M % 8 != 0 && Mp >= 16) ? kDwordRows : 1;
+        // (kDwordRows: 32 of 1024 lists, 1.18M x 100, M = 20, k = 100: 200 queries 159 -> 136 us, 1000 459 -> 336, 8000 2058 -> 1345;
+        // k = 10, 1000 382 -> 241; 100 queries, no lists, 8226 -> 3684.  Range searches, which abandon little early, lose 2 %: 1629 / 1675)
         size_t off = tab;
         pl->off_q = (uint32_t)off;    off += up16((size_t)d * 4);
         pl->off_segp = (uint32_t)off; off += up16((size_t)(nsegs + 1) * 4);
@@ -144,11 +146,8 @@ bool fit_plan(int d, int M, int row_bytes, int nsegs, int cap, int batch, int k,
         pl->lds = off;
         pl->threads = tier.threads;
         // the 80-register instance: needed for three workgroups per CU, and the better one for short
-        // codes in any case (the other's bulk rounds and deeper refine pipelines pay from 64 code bytes on), but with two result
-        // entries per lane not where four small workgroups share a CU, whose 16 waves get 128 registers anyway (k = 100: 1000 queries x
-        // 1.18M x 100, M = 20: 459 / 467 us; 4-bit codes, 900 x 1M x 128: 286 / 290)
-        const bool four = tier.lds < kLdsBytes / 3;
-        pl->lean = !(P == 1 && M <= 256 && (tier.needs_6_waves || (M < 64 && !(four && result_slots(k) == 2)))) ? kFullInstance
+        // codes in any case (the other's bulk rounds and deeper refine pipelines pay from 64 code bytes on)
+        pl->lean = !(P == 1 && M <= 256 && (tier.needs_6_waves || M < 64)) ? kFullInstance
                    : d <= 128 ? kLeanShortRows : kLeanLongRows;
         pl->wqcap = wqcap;
         pl->cruise = p > 0 ? cruise : 0;
@@ -183,14 +182,14 @@ bool make_plan(int d, int M, bool fs, int nseg, int cap, int batch, int k, bool 
             // M = 32: 256 queries 125 -> 109 us, 512 142 -> 128; 4-bit codes 94 -> 82, 102 -> 98; 350 queries one per CU: 126 -> 150; 700
             // two per CU: 150 -> 187; k = 100, 200 queries: M = 32 159 -> 128, M = 20 351 -> 159, 4-bit codes 224 -> 139).
             if (!range && result_slots(k) <= 2 && (nq <= kCus ? t + 1 < nt : nq <= 2 * kCus && tier.lds < kLdsBytes / 2)) continue;
-            // A short table would fit four small workgroups per CU (16 waves); the instance built
-            // for six waves per SIMD does better as three 512-thread ones (24 waves), which also have twice the threads for
-            // a query where all are resident at once.  1.18M x 100, M = 20, 32 of 1024 lists, k = 10: 600 queries 333 -> 230 us, 1500
-            // 609 -> 425, 8000 2266 -> 1841; M = 16: 167 -> 122, 8000 771 -> 740; k = 100: 700 queries 404 -> 276, 2000 789 -> 652, 8000 2588 ->
-            // 2058; M = 16 4000 510 -> 462.  With 8-bit codes not between 768 and 1024 queries, which four a CU take in one go (M = 16,
-            // batches of 256, 1000 queries: 169 / 211), and not with 4-bit codes and two result entries per lane beyond that (8000
-            // queries 1040 / 1082; 700 in one go 260 -> 210).
-            if (t == 0 && !range && (nq <= 3 * kCus ? result_slots(k) <= 2 : fs ? result_slots(k) == 1 : result_slots(k) <= 2 && nq > 4 * kCus)) continue;
+            // A short table would fit four small workgroups per CU (16 waves); the instances built
+            // for six waves per SIMD do better as three 512-thread ones (24 waves), which also have twice the threads for
+            // a query where all are resident at once.  32 of 1024 lists: 1.18M x 100, M = 20, k = 10: 600 queries 333 -> 230 us, 1000 230 ->
+            // 229, 8000 2266 -> 1841, k = 100: 200 351 -> 159, 700 404 -> 276, 1000 336 -> 293; M = 16, k = 100, 1000 228 -> 196, 4000 510 ->
+            // 462; 4-bit codes, k = 100, 700 260 -> 210, 3000 650 -> 586, 8000 1363 -> 1279.  But not for shorter 8-bit codes and k up to 64
+            // between 768 and 1024 queries, which four a CU take in one go (M = 8, 900 queries 104 / 121; M = 16, 800 124 / 127).
+            const bool one_go = !fs && M <= 16 && result_slots(k) == 1 && nq > 3 * kCus && nq <= 4 * kCus;
+            if (t == 0 && !range && result_slots(k) <= 2 && !one_go) continue;
             if (t + 1 < nt) {
                 // below the last tier a layout must leave room for a cruise when one is possible
                 // at all (else the next tier is tried first)

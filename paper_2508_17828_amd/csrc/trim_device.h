@@ -491,9 +491,18 @@ template <> struct CodeVec<4> { using type = uint4; };
 template <> struct CodeVec<2> { using type = uint2; };
 template <> struct CodeVec<1> { using type = uint32_t; };
 
-template <int VEC>
+// DWORD: p is a multiple of 4 bytes only (the hardware asks no more of a load of several words).
+struct __attribute__((packed, aligned(4))) Words2 { uint32_t x, y; };
+struct __attribute__((packed, aligned(4))) Words4 { uint32_t x, y, z, w; };
+template <int VEC, bool DWORD = false>
 __device__ __forceinline__ void load_codes(uint32_t (&w)[VEC], const uint8_t *__restrict__ p) {
-    if constexpr (VEC == 4) {
+    if constexpr (DWORD && VEC == 4) {
+        const Words4 v = *reinterpret_cast<const Words4 *>(p);
+        w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+    } else if constexpr (DWORD && VEC == 2) {
+        const Words2 v = *reinterpret_cast<const Words2 *>(p);
+        w[0] = v.x; w[1] = v.y;
+    } else if constexpr (VEC == 4) {
         const uint4 v = *reinterpret_cast<const uint4 *>(p);
         w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
     } else if constexpr (VEC == 2) {

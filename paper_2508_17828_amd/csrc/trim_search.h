@@ -491,6 +491,12 @@ enum LeanKind { kFullInstance = 0, kLeanShortRows = 1, kLeanLongRows = 2 };
 // of that code.
 // FS: 4-bit codes, two per code byte, with rows of 16 table entries (see kByteRow); SearchArgs::M
 // counts code bytes in either case.
+// VEC: the widest code loads.  4, 2, 1: as many words, codes aligned to them (16, 8, 4 code bytes); kDwordRows: 16 bytes at a
+// multiple of 4, for codes of 16 bytes and more that are no multiple of 8 (and have no scan head).  With loads of 4 bytes such a code
+// took a memory latency per 4 subspaces, four of them decided who is abandoned, and no list was passed over (those blocks wanted the
+// scan head).  Multiples of 8 keep their head and loads of 8 bytes (300,000 x 960,
+// M = 120, no lists, 100 queries: 1632 us, 1731 this way).
+constexpr int kDwordRows = 3;
 template <int MODE, int VEC, int E, bool ACCT, bool FS, int LEAN_KIND>
 __global__ __launch_bounds__(1024)
 __attribute__((amdgpu_waves_per_eu(LEAN_KIND != kFullInstance ? kLeanWavesPerSimd : 4)))
@@ -500,6 +506,8 @@ void search_kernel(const SearchArgs a) {
     // The tiled copy of the codes is read by the instances with 16-byte code loads, except the
     // lean ones, whose codes are short (they read the row-major array).
     constexpr bool kTiledOk = VEC == 4 && !LEAN;
+    constexpr int W = VEC == kDwordRows ? 4 : VEC;     // words of the widest load
+    constexpr bool kDword = VEC == kDwordRows;
     extern __shared__ __align__(16) unsigned char smem[];
     float *tab = reinterpret_cast<float *>(smem + kTabAt<FS>);
     float *pair_tab = reinterpret_cast<float *>(smem);   // 4-bit codes only: see kTabAt
@@ -946,7 +954,7 @@ void search_kernel(const SearchArgs a) {
             if (cl < hi) {
                 const int pos = cur.pos(c0n + cl, segp, segd);
                 sg[u] = cur.seg;
-                load_codes<H0 / 4>(w[u], code_row<kTiledOk>(a, pos).at(0));
+                load_codes<H0 / 4, kDword>(w[u], code_row<kTiledOk>(a, pos).at(0));
                 bq[u] = a.dlx[pos];
             }
         }
@@ -1000,7 +1008,7 @@ void search_kernel(const SearchArgs a) {
                 // the entries and starts the loads of the landmark distance and the first code
                 // chunk; drain_finish redoes the table sum from the start (now with a test every
                 // 8 subspaces), evaluates Equation 3 and records the candidate if it passes tau0.
-                constexpr int DV = VEC;            // dwords per code chunk
+                constexpr int DV = W;              // dwords per code chunk
                 const bool two_chunks = a.M >= 8 * DV;  // the first two chunks are loaded ahead
                 int d_n = 0, d_cl = 0, d_pos = 0;
                 float d_b = 0.0f;
@@ -1015,8 +1023,8 @@ void search_kernel(const SearchArgs a) {
                         d_pos = c0 + d_cl + segd[e >> 16];
                         const CodeRow cr = code_row<kTiledOk>(a, d_pos);
                         d_b = a.dlx[d_pos];
-                        load_codes<DV>(d_w0, cr.at(0));
-                        if (two_chunks) load_codes<DV>(d_w1, cr.at(4 * DV));
+                        load_codes<DV, kDword>(d_w0, cr.at(0));
+                        if (two_chunks) load_codes<DV, kDword>(d_w1, cr.at(4 * DV));
                     }
                     head = (head + d_n) & (kRing - 1);
                     count -= d_n;
@@ -1036,14 +1044,14 @@ void search_kernel(const SearchArgs a) {
                             j = 8 * DV;
                         }
                         while (j < a.M && !(sum > thr - restv[j >> 2])) {  // widest aligned load that fits
-                            if (VEC == 4 && (j & 15) == 0 && j + 16 <= a.M) {
+                            if (W == 4 && (j & 15) == 0 && j + 16 <= a.M) {
                                 uint32_t w[4];
-                                load_codes<4>(w, cr.at(j));
+                                load_codes<4, kDword>(w, cr.at(j));
                                 sum = gather_add<4, true, FS>(sum, kTabAt<FS> + j * kByteRow<FS>, w, thr - restv[(j >> 2) + 2]);
                                 j += 16;
                             } else if (VEC >= 2 && (j & 7) == 0 && j + 8 <= a.M) {
                                 uint32_t w[2];
-                                load_codes<2>(w, cr.at(j));
+                                load_codes<2, kDword>(w, cr.at(j));
                                 sum = gather_add<2, false, FS>(sum, kTabAt<FS> + j * kByteRow<FS>, w, thr);
                                 j += 8;
                             } else {
@@ -1097,7 +1105,7 @@ void search_kernel(const SearchArgs a) {
                     int sg[U];
                     const int cb = blk * U * kWave;
                     // same for the whole wave
-                    const bool full = H0 == 8 && a.head && a.small_addr && cb + U * kWave <= S;
+                    const bool full = H0 == 8 && (kDword || a.head) && a.small_addr && cb + U * kWave <= S;
                     // A block that lies inside one list takes that list's remaining minimum, or is
                     // passed over with the list; any other block takes the global minimum.
                     float blk_rest = rest_h0;
@@ -1155,11 +1163,16 @@ void search_kernel(const SearchArgs a) {
                                 pos = (uint32_t)(c + delta);
                                 sg[u] = seg << 16;
                             }
-                            const HeadRecord r = *reinterpret_cast<const HeadRecord *>(
-                                reinterpret_cast<const char *>(a.head) + (size_t)(uint32_t)__umul24(pos, 12u));
-                            w[u][0] = r.w0;
-                            w[u][H0 / 4 - 1] = r.w1;  // H0 == 8 here
-                            bq[u] = r.b;
+                            if constexpr (kDword) {
+                                load_codes<H0 / 4, true>(w[u], a.codes + (size_t)(uint32_t)__umul24(pos, (uint32_t)a.M));
+                                bq[u] = a.dlx[pos];
+                            } else {
+                                const HeadRecord r = *reinterpret_cast<const HeadRecord *>(
+                                    reinterpret_cast<const char *>(a.head) + (size_t)(uint32_t)__umul24(pos, 12u));
+                                w[u][0] = r.w0;
+                                w[u][H0 / 4 - 1] = r.w1;  // H0 == 8 here
+                                bq[u] = r.b;
+                            }
                         }
                     } else {
                         issue_loads(c0, cb, S, w, bq, sg);
@@ -1316,13 +1329,13 @@ void search_kernel(const SearchArgs a) {
         // A batch that runs against a loose threshold (the first ones after the seed) abandons
         // nobody, so the rounds would only add dependent memory latencies: its candidates are
         // bounded in one go instead, two per lane, with all their loads issued together.
-        constexpr int kDirectChunks = 2;  // code chunks of 4*VEC bytes a lane keeps per candidate
-        const bool direct = MODE == kKnn && VEC == 4 && nphase == 1 && a.M <= 4 * VEC * kDirectChunks &&
-                            a.M % (4 * VEC) == 0 && c0 == c_begin + kseed;
+        constexpr int kDirectChunks = 2;  // code chunks of 4*W bytes a lane keeps per candidate
+        const bool direct = MODE == kKnn && W == 4 && nphase == 1 && a.M <= 4 * W * kDirectChunks &&
+                            (kDword || a.M % (4 * W) == 0) && c0 == c_begin + kseed;
         if (direct) {
             constexpr int UD = 2;
             for (int base = wlo; base < whi; base += UD * kWave) {
-                uint32_t w[UD][kDirectChunks][VEC];
+                uint32_t w[UD][kDirectChunks][W];
                 float b[UD];
 #pragma unroll
                 for (int u = 0; u < UD; ++u) {
@@ -1331,14 +1344,21 @@ void search_kernel(const SearchArgs a) {
 #pragma unroll
                     for (int c = 0; c < kDirectChunks; ++c)
 #pragma unroll
-                        for (int v = 0; v < VEC; ++v) w[u][c][v] = 0;
+                        for (int v = 0; v < W; ++v) w[u][c][v] = 0;
                     if (cl < whi) {
                         const int pos = cur.pos(c0 + cl, segp, segd);
                         const CodeRow cr = code_row<kTiledOk>(a, pos);
                         b[u] = a.dlx[pos];
 #pragma unroll
-                        for (int c = 0; c < kDirectChunks; ++c)
-                            if (c * 4 * VEC < a.M) load_codes<VEC>(w[u][c], cr.at(c * 4 * VEC));
+                        for (int c = 0; c < kDirectChunks; ++c) {
+                            if (c * 4 * W + (kDword ? 4 * W - 1 : 0) < a.M) {
+                                load_codes<W, kDword>(w[u][c], cr.at(c * 4 * W));
+                            } else if constexpr (kDword) {          // what is left of a code
+#pragma unroll
+                                for (int v = 0; v < W - 1; ++v)
+                                    if (c * 4 * W + 4 * v < a.M) w[u][c][v] = *reinterpret_cast<const uint32_t *>(cr.at(c * 4 * W + 4 * v));
+                            }
+                        }
                     }
                 }
 #pragma unroll
@@ -1347,9 +1367,15 @@ void search_kernel(const SearchArgs a) {
                     float sum = 0.0f;
 #pragma unroll
                     for (int c = 0; c < kDirectChunks; ++c)
-                        if (c * 4 * VEC < a.M)
-                            sum = gather_add<VEC, false, FS>(sum, kTabAt<FS> + c * 4 * VEC * kByteRow<FS>, w[u][c],
+                        if (c * 4 * W + (kDword ? 4 * W - 1 : 0) < a.M) {
+                            sum = gather_add<W, false, FS>(sum, kTabAt<FS> + c * 4 * W * kByteRow<FS>, w[u][c],
                                                   __builtin_inff());
+                        } else if constexpr (kDword) {
+#pragma unroll
+                            for (int v = 0; v < W - 1; ++v)
+                                if (c * 4 * W + 4 * v < a.M)
+                                    sum = gather_add<1>(sum, kTabAt<FS> + (c * 4 * W + 4 * v) * kByteRow<FS>, {w[u][c][v]}, __builtin_inff());
+                        }
                     if (cl < whi) {
                         const float g = plb_from_s(sum, b[u], a.two_gamma);
                         plbs[cl] = g;
@@ -1380,7 +1406,7 @@ void search_kernel(const SearchArgs a) {
                 // nobody, so the first round of phase 0 is a bulk round over the whole slice.
                 const bool slice_round = ph == 0 && h0 == 0;
                 constexpr int kPieces = LEAN ? 0 : 6;
-                const bool bulk_first = kPieces > 0 && VEC == 4 && a.M >= 64;
+                const bool bulk_first = kPieces > 0 && W == 4 && a.M >= 64;
                 if (slice_round && !bulk_first) {
                     // ---- round 0 ----
                     h1 = H0 < Mp ? H0 : Mp;
@@ -1422,9 +1448,11 @@ void search_kernel(const SearchArgs a) {
                     // all its loads together with the landmark distance: one memory latency per
                     // queue entry instead of one per piece.  Otherwise: 32 subspaces, piece by piece.
                     // (not in the lean instance, which meets later rounds only on fallback)
-                    const bool lead8 = kPieces > 0 && VEC == 4 && (h0 & 15) == 8 && h0 + 8 <= Mp;
+                    constexpr bool kBulk = kPieces > 0 && W == 4;
+                    const bool long_rows = !kDword || a.M >= 64;      // (shorter ones: one round more)
+                    const bool lead8 = kBulk && long_rows && (h0 & 15) == 8 && h0 + 8 <= Mp;
                     const int ja = h0 + (lead8 ? 8 : 0);
-                    int n16 = kPieces > 0 && VEC == 4 && (ja & 15) == 0 ? (Mp - ja) / 16 : 0;
+                    int n16 = kBulk && long_rows && (ja & 15) == 0 ? (Mp - ja) / 16 : 0;
                     if (n16 > kPieces) n16 = kPieces;
                     const bool bulk = lead8 || n16 > 0;
                     h1 = bulk ? ja + 16 * n16 : (h0 + 32 < Mp ? h0 + 32 : Mp);
@@ -1443,10 +1471,10 @@ void search_kernel(const SearchArgs a) {
                             uint32_t w8[2] = {0, 0};
                             uint32_t w16[kPieces > 0 ? kPieces : 1][4];
                             if (bulk) {
-                                if (lead8) load_codes<2>(w8, cr.at(jp + h0));
+                                if (lead8) load_codes<2, kDword>(w8, cr.at(jp + h0));
 #pragma unroll
                                 for (int c = 0; c < kPieces; ++c)
-                                    if (c < n16) load_codes<4>(w16[c], cr.at(jp + ja + 16 * c));
+                                    if (c < n16) load_codes<4, kDword>(w16[c], cr.at(jp + ja + 16 * c));
                             }
                             const float b = a.dlx[pos];
                             const float thr = abandon_threshold(b, line0);
@@ -1467,14 +1495,14 @@ void search_kernel(const SearchArgs a) {
                                 j = h1;
                             }
                             while (j < h1) {  // widest aligned load that fits, test after each
-                                if (VEC == 4 && (j & 15) == 0 && j + 16 <= h1) {
+                                if (W == 4 && (j & 15) == 0 && j + 16 <= h1) {
                                     uint32_t w[4];
-                                    load_codes<4>(w, cr.at(jp + j));
+                                    load_codes<4, kDword>(w, cr.at(jp + j));
                                     sum = gather_add<4, true, FS>(sum, kTabAt<FS> + j * kByteRow<FS>, w, thr);
                                     j += 16;
                                 } else if (VEC >= 2 && (j & 7) == 0 && j + 8 <= h1) {
                                     uint32_t w[2];
-                                    load_codes<2>(w, cr.at(jp + j));
+                                    load_codes<2, kDword>(w, cr.at(jp + j));
                                     sum = gather_add<2, false, FS>(sum, kTabAt<FS> + j * kByteRow<FS>, w, thr);
                                     j += 8;
                                 } else {
@@ -1488,7 +1516,7 @@ void search_kernel(const SearchArgs a) {
                             if (acct) {
                                 const int bytes = bulk ? (lead8 ? 8 : 0) + 16 * n16 : j - h0;
                                 const int looks = (bulk ? (lead8 ? 8 : 0) + 16 * used16 : j - h0) -
-                                                  (VEC == 4 && sum == __builtin_inff() ? 8 : 0);
+                                                  (W == 4 && sum == __builtin_inff() ? 8 : 0);
                                 tally(kWorkCodeBytes, (uint32_t)(bytes + 4));
                                 tally(kWorkLookups, (uint32_t)looks * kByteLookups<FS>);
                                 if (slice_round) tally(kWorkFirstPass, 1u);

@@ -39,6 +39,10 @@ int launch_instance(const SearchArgs &a, const Plan &pl, dim3 grid, hipStream_t 
     void (*fn)(const SearchArgs) = nullptr;
     switch (pl.vec) {
         case 4: fn = search_kernel<kMode, 4, kE, ACCT, kFs, kLean>; break;
+        case kDwordRows:
+            if constexpr (kFs) return TRIM_UNSUPPORTED_SHAPE;
+            else fn = search_kernel<kMode, kDwordRows, kE, ACCT, kFs, kLean>;
+            break;
         case 2: fn = search_kernel<kMode, 2, kE, ACCT, kFs, kLean>; break;
         default:
             // 4-bit codes come in rows of a multiple of 8 bytes: no 4-byte code loads there
@@ -49,8 +53,8 @@ int launch_instance(const SearchArgs &a, const Plan &pl, dim3 grid, hipStream_t 
     // The kernel addresses its distance table with immediate offsets from LDS address 0, so it
     // must own the workgroup's LDS from the first byte: an instance that was built with static
     // LDS in front of the dynamic area is refused here instead of being launched.
-    static std::atomic<int> lds_checked[3];   // per instance (ACCT) and code-load width
-    std::atomic<int> &seen = lds_checked[pl.vec == 4 ? 2 : pl.vec == 2 ? 1 : 0];
+    static std::atomic<int> lds_checked[5];   // per instance (ACCT) and code-load width
+    std::atomic<int> &seen = lds_checked[pl.vec];
     if (seen.load(std::memory_order_acquire) == 0) {
         hipFuncAttributes fa;
         HIP_TRY(hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(fn)));

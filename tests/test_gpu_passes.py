@@ -726,3 +726,19 @@ def test_answers_do_not_depend_on_the_number_of_queries(T, d, M, bits, k, batch)
     ref = o.search_knn(oix, c(q[8:28]), k, 0.3, batch, c(probes[8:28]))      # (those before it probe lists that are not there)
     np.testing.assert_array_equal(c(want["ids"][8:28]), ref["ids"])
     np.testing.assert_array_equal(c(want["n_exact"][8:28]), ref["n_exact"])
+
+
+# codes of 16 bytes and more that are no multiple of 8: 16-byte pieces at multiples of 4, what is left of a code (4, 8, 12 bytes), table
+# phases, the list summaries without a scan head; one to sixteen result entries per lane
+@pytest.mark.parametrize("d,M", ((80, 20), (112, 28), (132, 44), (240, 60), (720, 180)))
+@pytest.mark.parametrize("k,batch,nlist", ((10, 1024, 60), (10, 3, 0), (100, 512, 60), (200, 256, 0), (300, 100, 25)))
+def test_codes_that_are_no_multiple_of_eight(T, d, M, k, batch, nlist):
+    from oracle import trim_oracle
+    ix, q, probes = built(T, 30000, d, M, 8, nlist, 12, min(nlist, 20), 1.0, 2.0, d + k)
+    got = single_kernel(T, ix, q, k, 0.3, batch, probes, None)
+    c = lambda t: None if t is None else t.cpu().numpy()
+    oix = trim_oracle.Index(c(ix.base), c(ix.codes), c(ix.dlx), c(ix.codebooks), ids=c(ix.ids), list_offsets=c(ix.list_offsets))
+    rows = slice(8, 12)                      # (those before it probe lists that are not there)
+    ref = trim_oracle.search_knn(oix, c(q[rows]), k, 0.3, batch, c(probes[rows]) if nlist else None)
+    for name in ("ids", "d2", "n_scanned", "n_exact"):
+        np.testing.assert_array_equal(c(got[name])[rows], ref[name], err_msg=name)
