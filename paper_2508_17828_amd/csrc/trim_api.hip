@@ -291,6 +291,7 @@ void fill_common(SearchArgs &a, const trim_index_view *ix, const float *queries,
     a.off_rd2 = pl.off_rd2; a.off_rid = pl.off_rid; a.off_ctl = pl.off_ctl;
     a.off_plb = pl.off_plb; a.off_cnt = pl.off_cnt; a.span = pl.span;
     a.off_wq = pl.off_wq; a.wqcap = pl.wqcap; a.cruise = pl.cruise; a.poss_cap = pl.poss_cap; a.scap = pl.scap; a.rcap = pl.rcap; a.bucket = pl.bucket;
+    a.bucket_inv = pl.bucket > 1 ? (uint32_t)(((uint64_t(1) << 32) + pl.bucket - 1) / pl.bucket) : 0;      // (stretches have buckets of 60 and more)
     a.small_addr = ix->n < (int64_t(1) << 24) && ix->n * (int64_t)ix->M < (int64_t(1) << 32) &&
                    ix->M < (1 << 24);
     // Thresholds that count on the remaining table minima (and list summaries) rest on an error

@@ -256,6 +256,63 @@ __device__ __forceinline__ float reduce_pairs(float (&v)[N], int lane32) {
     return v[0];
 }
 
+// Least value of a wave and sum over the lanes l, l + 4, l + 8, .. (all lanes get it), by the vector ALU alone.
+__device__ __forceinline__ float swap_rows16(float a, bool upper) {      // (rows of 16 lanes: 0, 0, 2, 2 or 1, 1, 3, 3)
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(a), false, false);
+    return __uint_as_float(upper ? r[1] : r[0]);
+}
+__device__ __forceinline__ float swap_halves(float a, bool upper) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(a), false, false);
+    return __uint_as_float(upper ? r[1] : r[0]);
+}
+template <int CTRL>
+__device__ __forceinline__ float lane_move(float a) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(a), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float quad_min(float v) {
+    v = __builtin_fminf(v, lane_xor<1>(v));
+    return __builtin_fminf(v, lane_xor<2>(v));
+}
+__device__ __forceinline__ float wave_least(float v) {
+    v = quad_min(v);
+    v = __builtin_fminf(v, lane_move<0x124>(v));      // row rotations by 4 and 8
+    v = __builtin_fminf(v, lane_move<0x128>(v));
+    v = __builtin_fminf(swap_rows16(v, false), swap_rows16(v, true));
+    return __builtin_fminf(swap_halves(v, false), swap_halves(v, true));
+}
+__device__ __forceinline__ float sum_of_quads(float v) {
+    v = v + lane_move<0x124>(v);
+    v = v + lane_move<0x128>(v);
+    v = swap_rows16(v, false) + swap_rows16(v, true);
+    return swap_halves(v, false) + swap_halves(v, true);
+}
+
+// The segment table of a query (see SearchArgs) from the segments' starts segd[p] and lengths segp[p + 1], by the first wave: segp becomes
+// the prefix of the lengths, cut at cap < 2^31 (sums saturate there, so 32 bits do), segd start less prefix.  Returns their total.
+// (One thread, a list after the other, took 130 clocks a list in search_kernel.)
+__device__ __forceinline__ uint32_t segment_prefix(int *segp, int *segd, int ns, uint32_t cap) {
+    const int lane = threadIdx.x;
+    uint32_t carry = 0;
+    for (int p0 = 0; p0 < ns; p0 += kWave) {
+        const int p = p0 + lane;
+        uint32_t incl = p < ns ? (uint32_t)segp[p + 1] : 0u;
+        incl = incl < cap ? incl : cap;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const uint32_t v = (uint32_t)__shfl_up((int)incl, off);
+            if (lane >= off) { incl += v; incl = incl < cap ? incl : cap; }
+        }
+        incl += carry;
+        incl = incl < cap ? incl : cap;
+        uint32_t before = (uint32_t)__shfl_up((int)incl, 1);
+        if (lane == 0) before = carry;
+        if (p < ns) { segp[p + 1] = (int)incl; segd[p] -= (int)before; }
+        carry = (uint32_t)__shfl((int)incl, kWave - 1);
+    }
+    if (lane == 0) segp[0] = 0;
+    return carry;
+}
+
 // Four rows at once (same arithmetic per row as exact_d2_half; the four loads of each step
 // are in flight together).  PIPE: the next step's four loads are issued before the current
 // step is reduced (twice the registers; for long rows).  ONE_STEP: the caller guarantees rows of

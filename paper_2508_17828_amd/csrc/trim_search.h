@@ -80,7 +80,22 @@ struct SearchArgs {
     int32_t scap;      // entries of spos[] and of sd2[] (>= survivor capacity and >= poss_cap)
     int32_t rcap;      // entries behind sd2[scap] (bounds of a replay; >= poss_cap)
     int32_t bucket;    // cruise: possibles are counted per bucket of this many candidates (a multiple of batch)
+    uint32_t bucket_inv;   // 2^32 / bucket, rounded up: a number of a stretch (16 bits) times this, over 2^32, is its bucket
 };
+
+// The kernel's arguments, read again from memory by whoever asks (the compiler cannot know that they are the same): kept from the
+// prologue to where they are used they do not fit the scalar registers, and what the loops want is spilled instead.
+typedef const SearchArgs __attribute__((address_space(4))) ConstantArgs;
+__device__ __forceinline__ ConstantArgs *fresh_args() {
+    auto p = (ConstantArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+// (a pointer that was read from memory: into device memory)
+template <typename T>
+__device__ __forceinline__ T *in_memory(T *p) {
+    return (T *)(__attribute__((address_space(1))) T *)p;
+}
 
 // One record of the optional scan head.
 struct __attribute__((packed, aligned(4))) HeadRecord {
@@ -316,6 +331,24 @@ struct ResultRegs {
     }
 };
 
+// The lanes' values (no NaN), ascending by lane: a bitonic network.
+template <int SIZE, int BIT>
+__device__ __forceinline__ float sort_lanes_run(float v, int lane) {
+    const float o = BIT == 32 ? __shfl_xor(v, 32) : lane_xor<(BIT < 32 ? BIT : 1)>(v);
+    const bool lesser = ((lane & BIT) == 0) == ((lane & SIZE) == 0);
+    v = (o < v) == lesser ? o : v;
+    if constexpr (BIT > 1) return sort_lanes_run<SIZE, BIT / 2>(v, lane);
+    return v;
+}
+__device__ __forceinline__ float sort_lanes(float v, int lane) {
+    v = sort_lanes_run<2, 1>(v, lane);
+    v = sort_lanes_run<4, 2>(v, lane);
+    v = sort_lanes_run<8, 4>(v, lane);
+    v = sort_lanes_run<16, 8>(v, lane);
+    v = sort_lanes_run<32, 16>(v, lane);
+    return sort_lanes_run<64, 32>(v, lane);
+}
+
 // Merge the refined survivors of a batch into R and publish tau (the "result queue update"
 // of Section 4.2).  Executed by ONE whole wave.
 template <int E>
@@ -323,27 +356,50 @@ __device__ __forceinline__ void merge_batch(float *sd2, int32_t *sid, int ns,
                                             float *rd2, int32_t *rid, Ctl *ctl, int k, int lane) {
     ResultRegs<E> R;
     R.load(rd2, rid, k, lane);
-    // A long list (the first batch after the seed) is pre-filtered: lane l takes the minimum of
-    // entries l, l+64, ...; the k-th smallest of these 64 minima (distinct entries) is an upper
+    // A long list (the first batch after the seed) is pre-filtered: a lane takes the minimum of the
+    // entries it reads; the k-th smallest of these 64 minima (distinct entries) is an upper
     // bound on the k-th distance after the merge, so entries above it never enter R and skip
-    // the insertion below.  Larger result sets: the same over 64 E columns, E per lane, their
+    // the insertion below.  (A lane keeps 16 entries in registers: one look at the LDS, and the ids of few.)  Larger result sets: the same
+    // over 64 E columns, E per lane, their
     // k-th least minimum found bit by bit, and whoever is left is moved together so that R takes 64 at a time.
     // (R of 100 entries after a first batch of 1024: 60 us of single insertions before.)
     float cut = __builtin_inff();
     if constexpr (E == 1) {
         if (ns > 2 * kWave) {
+            constexpr int kHeld = 16, kPiece = kHeld * kWave;
+            float v[kHeld];
+            auto at = [&](int p0, int e) { return p0 + (e >> 2) * 4 * kWave + 4 * lane + (e & 3); };
+            auto read = [&](int p0) {
+#pragma unroll
+                for (int e = 0; e < kHeld; e += 4) {
+                    const int i = at(p0, e);
+                    float4 x = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    if (i < ns) x = *reinterpret_cast<const float4 *>(sd2 + i);      // (up to three past the end: inside the area)
+                    v[e] = i < ns ? x.x : __builtin_inff();
+                    v[e + 1] = i + 1 < ns ? x.y : __builtin_inff();
+                    v[e + 2] = i + 2 < ns ? x.z : __builtin_inff();
+                    v[e + 3] = i + 3 < ns ? x.w : __builtin_inff();
+                }
+            };
             float cmin = __builtin_inff();
-            for (int i = lane; i < ns; i += kWave) cmin = __builtin_fminf(cmin, sd2[i]);
+            for (int p0 = 0; p0 < ns; p0 += kPiece) {
+                read(p0);
 #pragma unroll
-            for (int size = 2; size <= kWave; size <<= 1) {
+                for (int e = 0; e < kHeld; ++e) cmin = __builtin_fminf(cmin, v[e]);
+            }
+            cut = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sort_lanes(cmin, lane)), k - 1));
+            for (int p0 = 0; p0 < ns; p0 += kPiece) {
+                if (ns > kPiece) read(p0);
 #pragma unroll
-                for (int j = size >> 1; j > 0; j >>= 1) {   // bitonic network across the lanes
-                    const float other = __shfl_xor(cmin, j);
-                    const bool keep_min = ((lane & j) == 0) == ((lane & size) == 0);
-                    cmin = keep_min ? __builtin_fminf(cmin, other) : __builtin_fmaxf(cmin, other);
+                for (int e0 = 0; e0 < kHeld; e0 += 8) {
+                    int32_t id[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) id[e] = v[e0 + e] <= cut && at(p0, e0 + e) < ns ? sid[at(p0, e0 + e)] : 0;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) R.insert_pending(v[e0 + e] <= cut && at(p0, e0 + e) < ns, v[e0 + e], id[e]);
                 }
             }
-            cut = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cmin), k - 1));
+            ns = 0;
         }
     } else if (ns > 2 * kWave * E) {
         uint32_t cmin[E];
@@ -482,6 +538,13 @@ __device__ __forceinline__ int replay_batches(const int32_t *s_cl, const float *
 // 512-thread workgroups share a CU when the table is short enough for that; it goes without
 // the bulk rounds over long codes, the tiled code copy and the deeper refine pipelines, which
 // the other instances (128 registers, at most 4 waves per SIMD) use.
+// Bound by the length of a query's chain of phases, which six waves per SIMD hide from each other in part, and by the vector ALU (0.7
+// busy).  10,000 queries over 1M x 128, a workgroup's share of time by its own clock: stretches 38 %, exact distances of the first batch 17,
+// list-level bounds 10, merges 10, bounds of the first batch 8, segment table 5.  What shortened the chain (whole search 1230 -> 1096 us):
+// a merging wave goes first on its SIMD (-2 %), list-level bounds in whole steps and sums by DPP (-2.5), a merge that reads
+// its list once (-2), one id a lane instead of four (-1.5), positions of a replay searched once (-2; batches of 100, k = 100: -10),
+// arguments read where they are used instead of spilled scalars (-1.5), divisions by a bucket as products (-2).  Vector registers spilled
+// in these loops cost more than all that: next rows loaded ahead into 16 more registers 1230 -> 1475.
 constexpr int kLeanWavesPerSimd = 6;
 // The lean instance comes in two kinds, one per shape of the refine step, so that neither carries
 // the other's code: rows of at most 128 values (four rows per half wave, one 16-byte group per
@@ -517,8 +580,7 @@ void search_kernel(const SearchArgs a) {
     float *restv = reinterpret_cast<float *>(smem + a.off_rest);  // [M/4+1] remaining minima (cruise)
     float *rowmin = reinterpret_cast<float *>(smem + a.off_plb);     // [M] smallest entry of each table row (prologue only)
     float2 *seglist = reinterpret_cast<float2 *>(smem + a.off_seglb); // [nseg] list-level pruning {threshold, rest}: see the prologue
-    int32_t *spos = reinterpret_cast<int32_t *>(smem + a.off_spos);  // survivor position -> id
-    float *sd2 = reinterpret_cast<float *>(smem + a.off_sd2);        // exact d2 (shares the queue area)
+    // (off_spos: survivor position -> id; off_sd2: exact d2, shares the queue area)
     int32_t *sidx = reinterpret_cast<int32_t *>(smem + a.off_sidx);  // range: scan-order number
     float *plbs = reinterpret_cast<float *>(smem + a.off_plb);       // [span] partial s, then bound
     int *cnt0 = reinterpret_cast<int *>(smem + a.off_cnt);           // per-batch counts
@@ -578,17 +640,11 @@ void search_kernel(const SearchArgs a) {
         if (segl_fits) segl[p] = e > s ? lp : -1;
     }
     sync_block();
+    if (tid < kWave) {
+        const uint32_t all = segment_prefix(segp, segd, nseg, (uint32_t)a.max_cand);
+        if (lane == 0) ctl->total = (int)all;
+    }
     if (tid == 0) {
-        int64_t run = 0;
-        segp[0] = 0;
-        for (int p = 0; p < nseg; ++p) {
-            int64_t len = segp[p + 1];
-            if (run + len > a.max_cand) len = a.max_cand - run;
-            segd[p] = segd[p] - (int)run;
-            run += len;
-            segp[p + 1] = (int)run;
-        }
-        ctl->total = (int)run;
         ctl->nsurv = 0;
         ctl->tau = MODE == kRange ? a.radius2 : __builtin_inff();
         ctl->nresult = 0;
@@ -629,8 +685,7 @@ void search_kernel(const SearchArgs a) {
                 } else {
                     const float4 v = *reinterpret_cast<const float4 *>(tab + (size_t)(4 * i + r) * kC + 4 * lane);
                     m = __builtin_fminf(__builtin_fminf(v.x, v.y), __builtin_fminf(v.z, v.w));
-#pragma unroll
-                    for (int off = 32; off > 0; off >>= 1) m = __builtin_fminf(m, __shfl_xor(m, off));
+                    m = wave_least(m);
                 }
                 gsum = gsum + m;
                 if (lane == 0) rowmin[4 * i + r] = m;
@@ -653,8 +708,7 @@ void search_kernel(const SearchArgs a) {
     // over the subspaces from H0 on; bm = the list's largest landmark distance.  Equation 3 is at
     // least list_threshold(lb, bm) for every vector of the list: while that exceeds the threshold
     // in force, nothing in the list can survive.
-    // Two segments per wave and round; a lane takes 16 recorded codes of one subspace (4 lanes
-    // per subspace, 32 subspaces of either list per step, all loads of a step issued together).
+    // Two segments per wave and round; four lanes per subspace, 32 subspaces of either list per step, all loads of a step issued together.
     if (MODE == kKnn && use_rest && a.nseg > 0 && a.list_bounds != nullptr) {
         constexpr int kH0 = VEC >= 2 ? 8 : 4;
         const size_t rec_bytes = list_record_bytes(a.M);
@@ -673,17 +727,22 @@ void search_kernel(const SearchArgs a) {
                                : __builtin_inff();
             }
             for (int j0 = 0; j0 < a.M; j0 += 32) {
-                uint4 cw[2][2];
+                // (lane k of a subspace's four takes the words k, k + 4, ..: codes are recorded in front, so whole steps fall away where few
+                // are.  A lane's 16 codes side by side: three quarters of the lanes idle in every step at 20 codes a subspace)
+                uint32_t cw[2][2][4];
                 int cnt[2][2];
 #pragma unroll
                 for (int t = 0; t < 2; ++t)
 #pragma unroll
                     for (int g = 0; g < 2; ++g) {
                         const int j = j0 + 16 * g + (lane >> 2);
-                        cw[t][g] = make_uint4(0, 0, 0, 0);
                         cnt[t][g] = 0;
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) cw[t][g][v] = 0;
                         if (rec[t] && j < a.M) {
-                            cw[t][g] = *reinterpret_cast<const uint4 *>(rec[t] + (size_t)j * kSetCap + (lane & 3) * 16);
+                            const uint32_t *words = reinterpret_cast<const uint32_t *>(rec[t] + (size_t)j * kSetCap) + (lane & 3);
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) cw[t][g][v] = words[4 * v];
                             cnt[t][g] = rec[t][(size_t)a.M * kSetCap + j];
                         }
                     }
@@ -694,24 +753,22 @@ void search_kernel(const SearchArgs a) {
                         const int j = j0 + 16 * g + (lane >> 2);
                         const bool on = rec[t] && j < a.M;
                         const float *row = tab + (size_t)(on ? j : 0) * kByteEntries<FS>;
-                        const uint32_t w4[4] = {cw[t][g].x, cw[t][g].y, cw[t][g].z, cw[t][g].w};
                         float m = __builtin_inff();
                         // (words past the recorded count repeat the first code: skipped)
                         const int nrec = cnt[t][g] == kSetAny ? 0 : cnt[t][g];
 #pragma unroll
                         for (int v = 0; v < 4; ++v)
-                            if (16 * (lane & 3) + 4 * v < nrec) {
+                            if (16 * v + 4 * (lane & 3) < nrec) {
 #pragma unroll
                                 for (int b = 0; b < 4; ++b) {
-                                    const uint32_t c = (w4[v] >> (8 * b)) & 255u;
+                                    const uint32_t c = (cw[t][g][v] >> (8 * b)) & 255u;
                                     // what a vector with this code byte adds (4-bit codes: both halves)
                                     m = __builtin_fminf(m, FS ? row[c & 15u] + row[kC4 + (c >> 4)] : row[c]);
                                 }
                             }
-                        m = __builtin_fminf(m, __shfl_xor(m, 1));
-                        m = __builtin_fminf(m, __shfl_xor(m, 2));
+                        m = quad_min(m);
                         if (on && (cnt[t][g] == 0 || cnt[t][g] == kSetAny)) m = rowmin[j];
-                        if (on && (lane & 3) == 0) {
+                        if (on) {
                             lb[t] = lb[t] + m;
                             if (j >= kH0) rest[t] = rest[t] + m;
                         }
@@ -719,11 +776,8 @@ void search_kernel(const SearchArgs a) {
             }
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
-#pragma unroll
-                for (int off = 32; off >= 4; off >>= 1) {
-                    lb[t] = lb[t] + __shfl_xor(lb[t], off);
-                    rest[t] = rest[t] + __shfl_xor(rest[t], off);
-                }
+                lb[t] = sum_of_quads(lb[t]);
+                rest[t] = sum_of_quads(rest[t]);
                 // the list is passed over while the threshold in force is below this
                 const float slack = list_threshold(lb[t], bm[t], a.two_gamma);
                 if (lane == 0 && p0 + t < nseg) seglist[p0 + t] = make_float2(slack, rest[t]);
@@ -768,12 +822,13 @@ void search_kernel(const SearchArgs a) {
         basei = __shfl(basei, 0);
         if (live) {
             const int slot = basei + __popcll(m & ((1ull << lane) - 1ull));
-            spos[slot] = locate(c);
+            const auto f = fresh_args();
+            reinterpret_cast<int32_t *>(smem + f->off_spos)[slot] = locate(c);
             if (MODE == kRange) sidx[slot] = c;
-            if (a.mask) {
+            if (f->mask) {
                 const int64_t wi = c >> 5;
-                if (wi < a.mask_words)
-                    atomicOr(&a.mask[(size_t)q * a.mask_words + wi], 1u << (c & 31));
+                if (wi < f->mask_words)
+                    atomicOr(&in_memory(f->mask)[(size_t)q * f->mask_words + wi], 1u << (c & 31));
             }
         }
     };
@@ -782,19 +837,24 @@ void search_kernel(const SearchArgs a) {
     // per half wave.  pos_of(i) gives the storage position of entry i; put(i, d2, id or
     // position) stores the result (called by the lane that holds the row's distance).
     auto refine_rows = [&](int ns, auto pos_of, auto put) {
+        const auto f = fresh_args();
+        const float *base = in_memory(f->base);
+        const int32_t *ids = in_memory(f->ids);
+        const float *q_lds = reinterpret_cast<const float *>(smem + f->off_q);
+        const int d = f->d;
         // Two rows per half wave with several 16-byte groups of each in flight, instead of four
         // rows step by step: the lean instance for long rows always (three groups: its register
         // budget), the full instance for the few long rows that survive a short span (eight).
-        if (LEAN_KIND == kLeanLongRows || (!LEAN && a.d >= 512 && ns <= 8 * nhalf)) {
+        if (LEAN_KIND == kLeanLongRows || (!LEAN && d >= 512 && ns <= 8 * nhalf)) {
             for (int i = half; i < ns; i += 2 * nhalf) {
                 const int i1 = i + nhalf;
                 const bool ok1 = i1 < ns;               // uniform within the half wave
                 const int p0 = pos_of(i), p1 = pos_of(ok1 ? i1 : i);
-                const int32_t id0 = (MODE == kKnn && a.ids) ? a.ids[p0] : p0;
-                const int32_t id1 = (MODE == kKnn && a.ids) ? a.ids[p1] : p1;
+                const int32_t id0 = (MODE == kKnn && ids) ? ids[p0] : p0;
+                const int32_t id1 = (MODE == kKnn && ids) ? ids[p1] : p1;
                 float d2[2];
-                exact_d2_half_x2_deep<LEAN ? 3 : 8>(a.base + (size_t)p0 * a.d, a.base + (size_t)p1 * a.d, q_lds,
-                                                    a.d, lane32, d2);
+                exact_d2_half_x2_deep<LEAN ? 3 : 8>(base + (size_t)p0 * d, base + (size_t)p1 * d, q_lds,
+                                                    d, lane32, d2);
                 if (lane32 == 0) {
                     put(i, d2[0], id0);
                     if (ok1) put(i1, d2[1], id1);
@@ -802,29 +862,26 @@ void search_kernel(const SearchArgs a) {
             }
             return;
         }
-        if constexpr (LEAN_KIND != kLeanLongRows)   // (that instance goes without this loop)
-        for (int i = half; i < ns; i += 4 * nhalf) {
-            int idx[4], pos[4];
-            bool ok[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                idx[u] = i + u * nhalf;
-                ok[u] = idx[u] < ns;              // uniform within the half wave
-                pos[u] = pos_of(ok[u] ? idx[u] : i);
-            }
-            int32_t rid4[4];  // ids are fetched together with the rows, not after them
-#pragma unroll
-            for (int u = 0; u < 4; ++u) rid4[u] = (MODE == kKnn && a.ids) ? a.ids[pos[u]] : pos[u];
-            const float d2 = exact_d2_half_x4<!LEAN, LEAN_KIND == kLeanShortRows>(
-                a.base + (size_t)pos[0] * a.d, a.base + (size_t)pos[1] * a.d, a.base + (size_t)pos[2] * a.d,
-                a.base + (size_t)pos[3] * a.d, q_lds, a.d, lane32);
-            // four lanes of the half wave hold one row's distance each and store it
+        if constexpr (LEAN_KIND != kLeanLongRows) {   // (that instance goes without this loop)
+            // four lanes of the half wave hold one row's distance each, and store it with its id
             const int mine = half_reduce_x4_row(lane32);
             const bool hi2 = (mine & 2) != 0, lo1 = (mine & 1) != 0;
-            const bool my_ok = hi2 ? (lo1 ? ok[3] : ok[2]) : (lo1 ? ok[1] : ok[0]);
-            const int my_idx = hi2 ? (lo1 ? idx[3] : idx[2]) : (lo1 ? idx[1] : idx[0]);
-            const int32_t my_id = hi2 ? (lo1 ? rid4[3] : rid4[2]) : (lo1 ? rid4[1] : rid4[0]);
-            if (half_reduce_x4_writer(lane32) && my_ok) put(my_idx, d2, my_id);
+            for (int i = half; i < ns; i += 4 * nhalf) {
+                int pos[4];                       // (past the end: the first one's; entries of other half waves may hold an id by now)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int at = i + u * nhalf;
+                    pos[u] = pos_of(at < ns ? at : i);
+                }
+                // the id is fetched together with the rows, not after them
+                const int my_pos = hi2 ? (lo1 ? pos[3] : pos[2]) : (lo1 ? pos[1] : pos[0]);
+                const int32_t my_id = (MODE == kKnn && ids) ? ids[my_pos] : my_pos;
+                const float d2 = exact_d2_half_x4<!LEAN, LEAN_KIND == kLeanShortRows>(
+                    base + (size_t)pos[0] * d, base + (size_t)pos[1] * d, base + (size_t)pos[2] * d,
+                    base + (size_t)pos[3] * d, q_lds, d, lane32);
+                const int my_idx = i + mine * nhalf;
+                if (half_reduce_x4_writer(lane32) && my_idx < ns) put(my_idx, d2, my_id);
+            }
         }
     };
 
@@ -832,6 +889,9 @@ void search_kernel(const SearchArgs a) {
     // by the whole block after a barrier that made the survivor list visible; ends with a
     // barrier.
     auto refine_and_select = [&](int ns) {
+        const auto f = fresh_args();
+        int32_t *spos = reinterpret_cast<int32_t *>(smem + f->off_spos);
+        float *sd2 = reinterpret_cast<float *>(smem + f->off_sd2);
         refine_rows(ns, [&](int i) { return spos[i]; },
                     [&](int i, float d2, int32_t id) {
                         if (MODE == kKnn) {
@@ -845,7 +905,11 @@ void search_kernel(const SearchArgs a) {
                         }
                     });
         sync_block();
-        if (MODE == kKnn && tid < kWave) merge_batch<E>(sd2, spos, ns, rd2, rid, ctl, a.k, lane);
+        if (MODE == kKnn && tid < kWave) {
+            __builtin_amdgcn_s_setprio(3);       // (the workgroup waits for this wave, which shares its SIMD with five of other workgroups)
+            merge_batch<E>(sd2, spos, ns, reinterpret_cast<float *>(smem + f->off_rd2), reinterpret_cast<int32_t *>(smem + f->off_rid), ctl, f->k, lane);
+            __builtin_amdgcn_s_setprio(0);
+        }
         if (tid == 0) {
             ctl->nexact += ns;
             ctl->nsurv = 0;
@@ -884,28 +948,39 @@ void search_kernel(const SearchArgs a) {
         }
     };
     auto refine_and_replay = [&](int np, int c0) {
-        float *s_g = sd2 + a.scap;                                 // bounds, in batch order
+        const auto f = fresh_args();
+        int32_t *spos = reinterpret_cast<int32_t *>(smem + f->off_spos);
+        float *sd2 = reinterpret_cast<float *>(smem + f->off_sd2), *s_g = sd2 + f->scap;     // (s_g: bounds, in batch order)
         int32_t *s_id = reinterpret_cast<int32_t *>(smem + a.off_plb);  // ids (that area is dead by now)
-        refine_rows(np, [&](int i) { return locate(c0 + spos[i]); },
+        // (positions: one search of the segment table per entry, not one by each of the 32 lanes that share a row)
+        for (int i = tid; i < np; i += T) s_id[i] = locate(c0 + spos[i]);
+        sync_block();
+        refine_rows(np, [&](int i) { return s_id[i]; },
                     [&](int i, float d2, int32_t id) { sd2[i] = d2; s_id[i] = id; });
         sync_block();
         if (tid < kWave) {
-            uint32_t *mrow = a.mask ? a.mask + (size_t)q * a.mask_words : nullptr;
+            __builtin_amdgcn_s_setprio(3);
+            const int64_t mask_words = f->mask_words;
+            const int batch = f->batch, k = f->k;
+            float *rd2 = reinterpret_cast<float *>(smem + f->off_rd2);
+            int32_t *rid = reinterpret_cast<int32_t *>(smem + f->off_rid);
+            uint32_t *mrow = f->mask ? in_memory(f->mask) + (size_t)q * mask_words : nullptr;
             int n;
             if constexpr (E > 1) {
-                n = replay_batches<E, true>(spos, s_g, sd2, s_id, np, a.batch, c0, mrow, a.mask_words,
-                                            rd2, rid, ctl, a.k, lane);
+                n = replay_batches<E, true>(spos, s_g, sd2, s_id, np, batch, c0, mrow, mask_words,
+                                            rd2, rid, ctl, k, lane);
             } else {
-                n = a.batch < kSmallBatch
-                    ? replay_batches<E, true>(spos, s_g, sd2, s_id, np, a.batch, c0, mrow, a.mask_words,
-                                              rd2, rid, ctl, a.k, lane)
-                    : replay_batches<E, false>(spos, s_g, sd2, s_id, np, a.batch, c0, mrow, a.mask_words,
-                                               rd2, rid, ctl, a.k, lane);
+                n = batch < kSmallBatch
+                    ? replay_batches<E, true>(spos, s_g, sd2, s_id, np, batch, c0, mrow, mask_words,
+                                              rd2, rid, ctl, k, lane)
+                    : replay_batches<E, false>(spos, s_g, sd2, s_id, np, batch, c0, mrow, mask_words,
+                                               rd2, rid, ctl, k, lane);
             }
             if (lane == 0) {
                 ctl->nexact += n;
                 if (acct) tally(kWorkRows, (uint32_t)np);
             }
+            __builtin_amdgcn_s_setprio(0);
         }
     };
 
@@ -1076,7 +1151,7 @@ void search_kernel(const SearchArgs a) {
                                 const int at = atomicAdd(&ctl->nposs, 1);
                                 if (at < a.poss_cap) { poss_cl[at] = d_cl; poss_g[at] = g; }
 
-                                atomicAdd(&cnt0[d_cl / a.bucket], 1);
+                                atomicAdd(&cnt0[__umulhi((uint32_t)d_cl, a.bucket_inv)], 1);
                             }
                         }
                     }
@@ -1260,10 +1335,12 @@ void search_kernel(const SearchArgs a) {
                 if (np > 0) {
                     counts_to_offsets(nb);
                     sync_block();
-                    float *s_g = sd2 + a.scap;
+                    const auto f = fresh_args();
+                    int32_t *spos = reinterpret_cast<int32_t *>(smem + f->off_spos);
+                    float *s_g = reinterpret_cast<float *>(smem + f->off_sd2) + f->scap;
                     for (int i = tid; i < np; i += T) {
                         const int cl = poss_cl[i];
-                        const int slot = atomicAdd(&cnt0[cl / a.bucket], 1);
+                        const int slot = atomicAdd(&cnt0[__umulhi((uint32_t)cl, a.bucket_inv)], 1);
                         spos[slot] = cl;
                         s_g[slot] = poss_g[i];
                     }
@@ -1376,10 +1453,14 @@ void search_kernel(const SearchArgs a) {
                                 if (c * 4 * W + 4 * v < a.M)
                                     sum = gather_add<1>(sum, kTabAt<FS> + (c * 4 * W + 4 * v) * kByteRow<FS>, {w[u][c][v]}, __builtin_inff());
                         }
-                    if (cl < whi) {
-                        const float g = plb_from_s(sum, b[u], a.two_gamma);
-                        plbs[cl] = g;
-                        if (g <= tau0) atomicAdd(&cnt0[cl / a.batch], 1);
+                    const float g = plb_from_s(sum, b[u], a.two_gamma);
+                    const bool in = cl < whi && g <= tau0;
+                    if (cl < whi) plbs[cl] = g;
+                    if (nb == 1) {          // (one counter: lanes would take their turns)
+                        const unsigned long long m = __ballot(in);
+                        if (lane == 0 && m) atomicAdd(&cnt0[0], __popcll(m));
+                    } else if (in) {
+                        atomicAdd(&cnt0[cl / a.batch], 1);
                     }
                 }
             }
@@ -1560,7 +1641,9 @@ void search_kernel(const SearchArgs a) {
                 replay_np = np_span;
                 advance = span;
                 if (np_span > 0) {
-                    float *s_g = sd2 + a.scap;
+                    const auto f = fresh_args();
+                    int32_t *spos = reinterpret_cast<int32_t *>(smem + f->off_spos);
+                    float *s_g = reinterpret_cast<float *>(smem + f->off_sd2) + f->scap;
                     for (int i = tid; i < span; i += T) {
                         const float g = plbs[i];
                         if (g <= tau0) {
@@ -1605,26 +1688,29 @@ void search_kernel(const SearchArgs a) {
     // (the last stretch may have ended in a replay by the first wave alone: every thread that
     // writes results must see its R)
     sync_block();
+    const auto f = fresh_args();
     if (MODE == kKnn) {
-        for (int i = tid; i < a.k; i += T) {
+        const float *rd2 = reinterpret_cast<const float *>(smem + f->off_rd2);
+        const int32_t *rid = reinterpret_cast<const int32_t *>(smem + f->off_rid);
+        for (int i = tid; i < f->k; i += T) {
             const int32_t id = rid[i];
-            a.out_ids[(size_t)q * a.k + i] = id == kEmptyId ? -1 : id;
-            a.out_d2[(size_t)q * a.k + i] = rd2[i];
+            in_memory(f->out_ids)[(size_t)q * f->k + i] = id == kEmptyId ? -1 : id;
+            in_memory(f->out_d2)[(size_t)q * f->k + i] = rd2[i];
         }
         if (tid == 0) {
-            if (a.n_scanned) a.n_scanned[q] = total;
-            if (a.n_exact) a.n_exact[q] = ctl->nexact;
+            if (f->n_scanned) in_memory(f->n_scanned)[q] = total;
+            if (f->n_exact) in_memory(f->n_exact)[q] = ctl->nexact;
         }
-        if (acct && tid < kWorkCounters) a.work[(size_t)q * kWorkCounters + tid] = ctl->work[tid];
+        if (acct && tid < kWorkCounters) in_memory(f->work)[(size_t)q * kWorkCounters + tid] = ctl->work[tid];
     } else {
         if (tid == 0) {
-            a.chunk_counts[(size_t)q * a.nsplit + split] = ctl->nresult;
-            if (a.n_scanned && split == 0) a.n_scanned[q] = total;
-            if (a.n_exact && ctl->nexact) atomicAdd(&a.n_exact[q], ctl->nexact);
+            in_memory(f->chunk_counts)[(size_t)q * f->nsplit + split] = ctl->nresult;
+            if (f->n_scanned && split == 0) in_memory(f->n_scanned)[q] = total;
+            if (f->n_exact && ctl->nexact) atomicAdd(&in_memory(f->n_exact)[q], ctl->nexact);
         }
         // (the host zeroed the array: a query's chunks add up)
         if (acct && tid < kWorkCounters && ctl->work[tid])
-            atomicAdd(&a.work[(size_t)q * kWorkCounters + tid], ctl->work[tid]);
+            atomicAdd(&in_memory(f->work)[(size_t)q * kWorkCounters + tid], ctl->work[tid]);
     }
 }
 

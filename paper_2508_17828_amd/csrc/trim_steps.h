@@ -28,28 +28,7 @@ __device__ __forceinline__ void segment_table(const int64_t *list_offsets, const
         segp[p + 1] = (int)(e - s);
     }
     sync_block();
-    if (threadIdx.x < kWave) {
-        const int lane = threadIdx.x;
-        uint32_t carry = 0;
-        const uint32_t cap = (uint32_t)max_cand;
-        for (int p0 = 0; p0 < ns; p0 += kWave) {
-            const int p = p0 + lane;
-            uint32_t incl = p < ns ? (uint32_t)segp[p + 1] : 0u;
-            incl = incl < cap ? incl : cap;
-#pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) {
-                const uint32_t v = (uint32_t)__shfl_up((int)incl, off);
-                if (lane >= off) { incl += v; incl = incl < cap ? incl : cap; }
-            }
-            incl += carry;
-            incl = incl < cap ? incl : cap;
-            uint32_t before = (uint32_t)__shfl_up((int)incl, 1);
-            if (lane == 0) before = carry;
-            if (p < ns) { segp[p + 1] = (int)incl; segd[p] -= (int)before; }
-            carry = (uint32_t)__shfl((int)incl, kWave - 1);
-        }
-        if (lane == 0) segp[0] = 0;
-    }
+    if (threadIdx.x < kWave) segment_prefix(segp, segd, ns, (uint32_t)max_cand);
     sync_block();
 }
 
