@@ -798,7 +798,7 @@ int knn_in_passes(const trim_index_view *ix, const KnnLayout &L, const SearchArg
     for (int64_t s0 = 0; s0 < a.nq; s0 += L.slab) {
         const int64_t ns = a.nq - s0 < L.slab ? a.nq - s0 : L.slab;
         m.slot0 = y.slot0 = s0;
-        m.nslots = ns;
+        m.nslots = y.nslots = ns;
         int rc;
         ZeroAreas z;
         z.add(m.possible, (size_t)ns * L.words);
@@ -809,6 +809,7 @@ int knn_in_passes(const trim_index_view *ix, const KnnLayout &L, const SearchArg
         // threshold that they leave.  Where that is no threshold to speak of yet (short first batches;
         // candidates in no particular order), eight times as many candidates from pass to pass.
         int64_t lo = 0, hi = (int64_t)a.k + a.batch;
+        int first = 0;                  // the first batch's end, while it is not measured yet
         for (;;) {
             if (hi > most) hi = most;
             m.lo = y.lo = f.lo = (int)lo;
@@ -817,8 +818,22 @@ int knn_in_passes(const trim_index_view *ix, const KnnLayout &L, const SearchArg
             m.all = lo == 0;            // (all of the first pass's candidates are bounded; after that the filter goes first)
             if (lo > 0 && (rc = launch_filter(f, st))) return rc;
             if ((rc = launch_finish(m, pl.vec, is_fs(ix), pl.threads, pl.lds, (ns + kXcds - 1) / kXcds * kXcds, st))) return rc;
-            if ((rc = launch_measure(f, st))) return rc;
-            if ((rc = launch_replay(y, ns, st))) return rc;
+            // With lists, the first batch is measured with the pass after it: other queries have that pass's rows in their first batch, so that
+            // most rows were read twice (start / now, us: 2,500 queries, 200,000 x 768, batches of 1024: 1475 / 1345, of 256: 1914 / 1818;
+            // 300 queries 571 / 466, x 960 616 / 470).  More results take more picks from fewer vectors each: k = 128, batches of
+            // 512, 1,500 queries 1697 / 1627, groups far apart 1190 / 1142; k = 250, 1024: 1843 / 1816, but far apart 1199 / 1306.  Without lists
+            // the passes have no rows in common: 500 x 100,000 x 960, k = 10: 755 / 806, k = 100: 1432 / 1406.
+            if (lo == 0 && hi < most && a.nseg > 0 && a.k <= kPickMost && a.batch >= kPickGroup * a.k) {
+                first = (int)hi;
+                y.mid = first;
+                if ((rc = launch_pick(y, st))) return rc;
+            } else {
+                y.mid = first;
+                if (first > 0) y.lo = f.lo = 0;
+                first = 0;
+                if ((rc = launch_measure(f, st))) return rc;
+                if ((rc = launch_replay(y, st))) return rc;
+            }
             if (hi >= most) break;
             lo = hi;
             if (a.nseg == 0 || hi < 1024) {

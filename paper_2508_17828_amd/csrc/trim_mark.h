@@ -6,6 +6,7 @@
 //   finish  the bounds of the marked candidates, by the rule; who does not pass is unmarked
 //   measure a lower bound of the distance of everyone still marked, on the matrix cores: a raw row is read once for
 //           all the queries that want it, and few exact distances are left to take
+//   pick    (kNN) a threshold from the bounds of the first batch, so that it is measured with what comes after it
 //   replay  (kNN) walks a query's marked candidates in scan order, batch by batch, with the threshold
 //           rule of Section 4.2, and merges the survivors into R
 //   range_exact  (range) the exact distances of those that the lower bound leaves
@@ -1047,7 +1048,9 @@ void finish_kernel(const FinishArgs a) {
                     if (wi < a.mask_words) atomicOr(&a.mask[(size_t)q * a.mask_words + wi], b);
                 }
             }
-            row_bits[(p0 >> 5) + w] = b;
+            // (the marks of the pass before stay: they may not be read yet)
+            const uint32_t before = p0 + w * 32 < lo ? row_bits[(p0 >> 5) + w] & ((1u << (lo - p0 - w * 32)) - 1u) : 0u;
+            row_bits[(p0 >> 5) + w] = b | before;
         }
         sync_block();
     }
@@ -1191,6 +1194,54 @@ __global__ __launch_bounds__(1024) void invert_place_kernel(const InvertArgs a) 
     }
 }
 
+// ---- a threshold for the rest before the first batch is measured (kNN) ----
+// The first batch is dealt into k groups; the least bound of each and its exact distance: the larger of the two, over all groups, is no
+// less than the k-th distance tau that the first batch will leave.  (Either all of these k survive the seed's threshold and are in the
+// running, or one does not, and its bound exceeds that threshold, which exceeds tau.)  What is marked against it contains what
+// tau would mark, so that the rows of the first batch and of the next pass are measured together and read once: 2,500 queries x
+// 500,000 x 768, measure 690 us in two launches -> 419, this kernel 33, replay 342 -> 309 (one launch), the search 2058 -> 1770.
+// One workgroup per query, a half wave per group.  A distance or bound that is no number makes it infinite.
+__global__ __launch_bounds__(kReplayThreads) void pick_kernel(const ReplayArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    int *segp = reinterpret_cast<int *>(smem + a.off_segp), *segd = reinterpret_cast<int *>(smem + a.off_segd);
+    float *q_lds = reinterpret_cast<float *>(smem + a.off_q);
+    __shared__ uint32_t s_most;
+    const int tid = threadIdx.x, lane32 = tid & 31;
+    const int64_t per_xcd = gridDim.x / kXcds, row = (int64_t)(blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+    if (row >= a.nslots) return;
+    const int64_t q = a.order ? a.order[a.slot0 + row] : a.slot0 + row;
+    if (q < 0 || q >= a.nq) return;
+    const int total = a.totals[row], end = total < a.mid ? total : a.mid;
+    if (tid == 0) s_most = end - a.k < a.k ? 0x7f800000u : 0u;      // (fewer than k: infinite)
+    for (int t = tid; t < a.d; t += kReplayThreads) q_lds[t] = a.queries[(size_t)q * a.d + t];
+    segment_table_ready(a.seg, a.nseg, a.n, a.max_cand, row, segp, segd);
+    const float *g = a.g + (size_t)row * a.words * 32;
+    if (end - a.k >= a.k)
+        for (int j = tid >> 5; j < a.k; j += kReplayThreads / 32) {
+            float least = __builtin_inff();
+            int at = 0x7fffffff;
+            for (int i = a.k + j + lane32 * a.k; i < end; i += 32 * a.k) {
+                const float v = g[i];
+                if (v < least) { least = v; at = i; }
+            }
+#pragma unroll
+            for (int off = 16; off > 0; off >>= 1) {
+                const float v = __shfl_xor(least, off);
+                const int o = __shfl_xor(at, off);
+                if (v < least || (v == least && o < at)) { least = v; at = o; }
+            }
+            float d2 = __builtin_inff();
+            if (at < end) {
+                const int pos = segment_position(at, segp, segd, a.nseg);
+                d2 = exact_d2_half(a.base + (size_t)pos * a.d, q_lds, a.d, lane32);
+                d2 = d2 <= __builtin_inff() ? __builtin_fmaxf(d2, least) : __builtin_inff();
+            }
+            if (lane32 == 0) atomicMax(&s_most, __float_as_uint(d2));
+        }
+    sync_block();
+    if (tid == 0) a.out_d2[(size_t)q * a.k + a.k - 1] = __uint_as_float(s_most);
+}
+
 // ---- replay (kNN) ----
 // One workgroup per query.  The entries of a stretch are listed in scan order; the exact distance is taken
 // here of those whose lower bound (a.d2) does not exceed the threshold at the start, the first wave
@@ -1261,168 +1312,176 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
         }
         sync_block();
     };
-    const int w_end = (hi + 31) >> 5;
-    for (int w0 = lo >> 5; w0 < w_end; w0 += kReplayThreads) {
-        const int w = w0 + tid;
-        uint32_t b = w < w_end ? bits[w] : 0u;
-        if (w == lo >> 5) b &= ~0u << (lo & 31);
-        if (w == hi >> 5) b &= (1u << (hi & 31)) - 1u;
-        const int cnt = __popc(b);
-        int incl = cnt;
+    // (with the first batch, the pass after it: see pick_kernel)
+    const int mid = a.mid > lo && a.mid < hi ? a.mid : hi;
+    for (int turn = 0; turn < 2; ++turn) {
+        const int part_lo = turn ? mid : lo, part_hi = turn ? hi : mid;
+        const int w_end = part_lo < part_hi ? (part_hi + 31) >> 5 : 0;
+        for (int w0 = part_lo >> 5; w0 < w_end; w0 += kReplayThreads) {
+            const int w = w0 + tid;
+            uint32_t b = w < w_end ? bits[w] : 0u;
+            if (w == part_lo >> 5) b &= ~0u << (part_lo & 31);
+            if (w == part_hi >> 5) b &= (1u << (part_hi & 31)) - 1u;
+            const int cnt = __popc(b);
+            int incl = cnt;
 #pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const int v = __shfl_up(incl, off);
-            if (lane >= off) incl += v;
-        }
-        if (lane == 63) part[wave] = incl;
-        sync_block();
-        int before = incl - cnt, all = 0;
-        for (int v = 0; v < kReplayThreads / kWave; ++v) {
-            const int p = part[v];
-            if (v < wave) before += p;
-            all += p;
-        }
-        for (int e0 = 0; e0 < all; e0 += kReplayCap) {
-            const int np = all - e0 < kReplayCap ? all - e0 : kReplayCap;
-            uint32_t rem = b;
-            int at = before - e0;
-            while (rem) {
-                const int c = w * 32 + (__ffs((int)rem) - 1);
-                rem &= rem - 1;
-                if (at >= 0 && at < np) s_cl[at] = c;
-                ++at;
+            for (int off = 1; off < kWave; off <<= 1) {
+                const int v = __shfl_up(incl, off);
+                if (lane >= off) incl += v;
             }
-            if (tid == 0) s_ntodo = 0;
-            if (tid < kReplayCap / 32) s_bit[tid] = 0;
+            if (lane == 63) part[wave] = incl;
             sync_block();
-            const float tau = s_tau;
-            // the seed and the first batch, whole (the candidates of this pass are all marked)
-            if (a.lo == 0 && hi <= (int64_t)a.k + a.batch && all == np && np == hi) {
-                const int ns = np < a.k ? np : a.k;
+            int before = incl - cnt, all = 0;
+            for (int v = 0; v < kReplayThreads / kWave; ++v) {
+                const int p = part[v];
+                if (v < wave) before += p;
+                all += p;
+            }
+            for (int e0 = 0; e0 < all; e0 += kReplayCap) {
+                const int np = all - e0 < kReplayCap ? all - e0 : kReplayCap;
+                uint32_t rem = b;
+                int at = before - e0;
+                while (rem) {
+                    const int c = w * 32 + (__ffs((int)rem) - 1);
+                    rem &= rem - 1;
+                    if (at >= 0 && at < np) s_cl[at] = c;
+                    ++at;
+                }
+                if (tid == 0) s_ntodo = 0;
+                if (tid < kReplayCap / 32) s_bit[tid] = 0;
+                sync_block();
+                const float tau = s_tau;
+                // the seed and the first batch, whole (the candidates of this pass are all marked)
+                if (part_lo == 0 && part_hi <= (int64_t)a.k + a.batch && all == np && np == part_hi) {
+                    const int ns = np < a.k ? np : a.k;
+                    for (int i = tid; i < np; i += kReplayThreads) {
+                        const int c = s_cl[i];
+                        s_g[i] = row_g[c];
+                        s_d2[i] = row_d2[c];
+                        if (i < ns) s_todo[i] = (uint16_t)i;
+                    }
+                    if (tid == 0) { s_most = 0; s_count = 0; }
+                    sync_block();
+                    measure(ns);
+                    uint32_t most = 0;
+                    for (int i = tid; i < ns; i += kReplayThreads) most = max(most, __float_as_uint(s_d2[i]));
+                    wave_max(&s_most, most);
+                    sync_block();
+                    // (a distance that is no number is never in R: then R is not full yet)
+                    const float tau1 = ns == a.k && s_most <= 0x7f800000u ? __uint_as_float(s_most) : __builtin_inff();
+                    int mine = 0;
+                    for (int i = tid; i < np; i += kReplayThreads) {
+                        const bool on = i < ns || s_g[i] <= tau1;
+                        if (on) {
+                            ++mine;
+                            if (mask_row && (i >> 5) < a.mask_words) atomicOr(&mask_row[i >> 5], 1u << (i & 31));
+                            // who could enter R at all, by lower bound (seeds: measured already)
+                            if (i >= ns && s_d2[i] <= tau1)
+                                s_key[atomicAdd(&s_ntodo, 1)] = ((unsigned long long)__float_as_uint(s_d2[i]) << 32) | (uint32_t)i;
+                        }
+                    }
+                    wave_add(&s_count, mine);
+                    sync_block();
+                    int nc = s_ntodo;
+                    if (tid == 0) survivors += s_count;
+                    int size = 1;
+                    while (size < nc) size <<= 1;
+                    for (int i = nc + tid; i < size; i += kReplayThreads) s_key[i] = ~0ull;
+                    sync_block();
+                    sort_keys(s_key, size);
+                    const int first = nc < a.k ? nc : a.k;
+                    for (int i = tid; i < first; i += kReplayThreads) s_todo[i] = (uint16_t)s_key[i];
+                    if (tid == 0) s_most = 0;
+                    sync_block();
+                    measure(first);
+                    most = 0;
+                    for (int i = tid; i < first; i += kReplayThreads) most = max(most, __float_as_uint(s_d2[s_todo[i]]));
+                    wave_max(&s_most, most);
+                    if (tid == 0) s_ntodo = 0;
+                    sync_block();
+                    // (a distance that is no number bounds nothing)
+                    const float cut = first == a.k && s_most <= 0x7f800000u ? __uint_as_float(s_most) : __builtin_inff();
+                    int more = 0;                         // bounds are ascending: a prefix
+                    for (int i = first + tid; i < nc; i += kReplayThreads) {
+                        const bool need = __uint_as_float((uint32_t)(s_key[i] >> 32)) <= cut;
+                        if (need) { s_todo[i - first] = (uint16_t)s_key[i]; ++more; }
+                    }
+                    wave_add(&s_ntodo, more);
+                    sync_block();
+                    const int n2 = s_ntodo;
+                    measure(n2);
+                    nc = first + n2;
+                    // R: the k least of the seed and the measured ones, by (distance, id)
+                    for (int i = tid; i < nc; i += kReplayThreads) {
+                        const int e = (int)(uint32_t)s_key[i];
+                        s_key[i] = ((unsigned long long)__float_as_uint(s_d2[e]) << 32) | ((uint32_t)s_id[e] ^ 0x80000000u);   // (ids order as signed)
+                    }
+                    size = 1;
+                    while (size < nc + ns) size <<= 1;
+                    for (int i = tid; i < ns; i += kReplayThreads)
+                        s_key[nc + i] = ((unsigned long long)__float_as_uint(s_d2[i]) << 32) | ((uint32_t)s_id[i] ^ 0x80000000u);
+                    for (int i = nc + ns + tid; i < size; i += kReplayThreads) s_key[i] = ~0ull;
+                    sync_block();
+                    sort_keys(s_key, size);
+                    const int have = nc + ns < a.k ? nc + ns : a.k;
+                    for (int i = tid; i < kWave * E; i += kReplayThreads) {
+                        const bool in = i < have && (uint32_t)(s_key[i] >> 32) <= 0x7f800000u;      // (what is no number sorts last)
+                        rd2[i] = in ? __uint_as_float((uint32_t)(s_key[i] >> 32)) : __builtin_inff();
+                        rid[i] = in ? (int32_t)((uint32_t)s_key[i] ^ 0x80000000u) : kEmptyId;
+                    }
+                    sync_block();
+                    if (wave == 0) {
+                        R.load(rd2, rid, a.k, lane);
+                        if (lane == 0) s_tau = R.t_d2;
+                    }
+                    continue;
+                }
                 for (int i = tid; i < np; i += kReplayThreads) {
                     const int c = s_cl[i];
-                    s_g[i] = row_g[c];
-                    s_d2[i] = row_d2[c];
-                    if (i < ns) s_todo[i] = (uint16_t)i;
-                }
-                if (tid == 0) { s_most = 0; s_count = 0; }
-                sync_block();
-                measure(ns);
-                uint32_t most = 0;
-                for (int i = tid; i < ns; i += kReplayThreads) most = max(most, __float_as_uint(s_d2[i]));
-                wave_max(&s_most, most);
-                sync_block();
-                // (a distance that is no number is never in R: then R is not full yet)
-                const float tau1 = ns == a.k && s_most <= 0x7f800000u ? __uint_as_float(s_most) : __builtin_inff();
-                int mine = 0;
-                for (int i = tid; i < np; i += kReplayThreads) {
-                    const bool on = i < ns || s_g[i] <= tau1;
-                    if (on) {
-                        ++mine;
-                        if (mask_row && (i >> 5) < a.mask_words) atomicOr(&mask_row[i >> 5], 1u << (i & 31));
-                        // who could enter R at all, by lower bound (seeds: measured already)
-                        if (i >= ns && s_d2[i] <= tau1)
-                            s_key[atomicAdd(&s_ntodo, 1)] = ((unsigned long long)__float_as_uint(s_d2[i]) << 32) | (uint32_t)i;
+                    const float d2 = row_d2[c], g = row_g[c];
+                    s_g[i] = g;
+                    // (its bound is held against the threshold of its own batch, later)
+                    if (d2 <= tau) {
+                        s_todo[atomicAdd(&s_ntodo, 1)] = (uint16_t)i;
+                        atomicOr(&s_bit[i >> 5], 1u << (i & 31));
                     }
                 }
-                wave_add(&s_count, mine);
                 sync_block();
-                int nc = s_ntodo;
-                if (tid == 0) survivors += s_count;
-                int size = 1;
-                while (size < nc) size <<= 1;
-                for (int i = nc + tid; i < size; i += kReplayThreads) s_key[i] = ~0ull;
-                sync_block();
-                sort_keys(s_key, size);
-                const int first = nc < a.k ? nc : a.k;
-                for (int i = tid; i < first; i += kReplayThreads) s_todo[i] = (uint16_t)s_key[i];
-                if (tid == 0) s_most = 0;
-                sync_block();
-                measure(first);
-                most = 0;
-                for (int i = tid; i < first; i += kReplayThreads) most = max(most, __float_as_uint(s_d2[s_todo[i]]));
-                wave_max(&s_most, most);
-                if (tid == 0) s_ntodo = 0;
-                sync_block();
-                // (a distance that is no number bounds nothing)
-                const float cut = first == a.k && s_most <= 0x7f800000u ? __uint_as_float(s_most) : __builtin_inff();
-                int more = 0;                         // bounds are ascending: a prefix
-                for (int i = first + tid; i < nc; i += kReplayThreads) {
-                    const bool need = __uint_as_float((uint32_t)(s_key[i] >> 32)) <= cut;
-                    if (need) { s_todo[i - first] = (uint16_t)s_key[i]; ++more; }
-                }
-                wave_add(&s_ntodo, more);
-                sync_block();
-                const int n2 = s_ntodo;
-                measure(n2);
-                nc = first + n2;
-                // R: the k least of the seed and the measured ones, by (distance, id)
-                for (int i = tid; i < nc; i += kReplayThreads) {
-                    const int e = (int)(uint32_t)s_key[i];
-                    s_key[i] = ((unsigned long long)__float_as_uint(s_d2[e]) << 32) | ((uint32_t)s_id[e] ^ 0x80000000u);   // (ids order as signed)
-                }
-                size = 1;
-                while (size < nc + ns) size <<= 1;
-                for (int i = tid; i < ns; i += kReplayThreads)
-                    s_key[nc + i] = ((unsigned long long)__float_as_uint(s_d2[i]) << 32) | ((uint32_t)s_id[i] ^ 0x80000000u);
-                for (int i = nc + ns + tid; i < size; i += kReplayThreads) s_key[i] = ~0ull;
-                sync_block();
-                sort_keys(s_key, size);
-                const int have = nc + ns < a.k ? nc + ns : a.k;
-                for (int i = tid; i < kWave * E; i += kReplayThreads) {
-                    const bool in = i < have && (uint32_t)(s_key[i] >> 32) <= 0x7f800000u;      // (what is no number sorts last)
-                    rd2[i] = in ? __uint_as_float((uint32_t)(s_key[i] >> 32)) : __builtin_inff();
-                    rid[i] = in ? (int32_t)((uint32_t)s_key[i] ^ 0x80000000u) : kEmptyId;
-                }
-                sync_block();
-                if (wave == 0) R.load(rd2, rid, a.k, lane);
-                continue;
-            }
-            for (int i = tid; i < np; i += kReplayThreads) {
-                const int c = s_cl[i];
-                const float d2 = row_d2[c], g = row_g[c];
-                s_g[i] = g;
-                // (its bound is held against the threshold of its own batch, later)
-                if (d2 <= tau) {
-                    s_todo[atomicAdd(&s_ntodo, 1)] = (uint16_t)i;
-                    atomicOr(&s_bit[i >> 5], 1u << (i & 31));
-                }
-            }
-            sync_block();
-            const int nt = s_ntodo;
-            measure(nt);
-            if (wave == 0) {
-                // the measured ones in scan order
-                uint32_t word = s_bit[lane];
-                const int ones = __popc(word);
-                int place = ones;
+                const int nt = s_ntodo;
+                measure(nt);
+                if (wave == 0) {
+                    // the measured ones in scan order
+                    uint32_t word = s_bit[lane];
+                    const int ones = __popc(word);
+                    int place = ones;
 #pragma unroll
-                for (int off = 1; off < kWave; off <<= 1) {
-                    const int v = __shfl_up(place, off);
-                    if (lane >= off) place += v;
+                    for (int off = 1; off < kWave; off <<= 1) {
+                        const int v = __shfl_up(place, off);
+                        if (lane >= off) place += v;
+                    }
+                    place -= ones;
+                    while (word) {
+                        s_todo[place++] = (uint16_t)(lane * 32 + (__ffs((int)word) - 1));
+                        word &= word - 1;
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    replay_measured<E>(R, frozen_b, tau_f, s_cl, s_g, s_d2, s_id, s_todo, nt, a.batch, &s_steps, s_key);
+                    if (lane == 0) s_tau = R.t_d2;
                 }
-                place -= ones;
-                while (word) {
-                    s_todo[place++] = (uint16_t)(lane * 32 + (__ffs((int)word) - 1));
-                    word &= word - 1;
+                sync_block();
+                const TauSteps steps = s_steps;
+                for (int i = tid; i < np; i += kReplayThreads) {
+                    const int c = s_cl[i], b4 = c < a.k ? -1 : (c - a.k) / a.batch;
+                    if (b4 < 0 || s_g[i] <= threshold_of(b4, steps, s_key)) {
+                        ++survivors;
+                        if (mask_row && (c >> 5) < a.mask_words) atomicOr(&mask_row[c >> 5], 1u << (c & 31));
+                    }
                 }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                replay_measured<E>(R, frozen_b, tau_f, s_cl, s_g, s_d2, s_id, s_todo, nt, a.batch, &s_steps, s_key);
-                if (lane == 0) s_tau = R.t_d2;
-            }
-            sync_block();
-            const TauSteps steps = s_steps;
-            for (int i = tid; i < np; i += kReplayThreads) {
-                const int c = s_cl[i], b4 = c < a.k ? -1 : (c - a.k) / a.batch;
-                if (b4 < 0 || s_g[i] <= threshold_of(b4, steps, s_key)) {
-                    ++survivors;
-                    if (mask_row && (c >> 5) < a.mask_words) atomicOr(&mask_row[c >> 5], 1u << (c & 31));
-                }
+                sync_block();
             }
             sync_block();
         }
-        sync_block();
     }
     if (a.n_exact) {
         if (tid == 0) s_count = 0;

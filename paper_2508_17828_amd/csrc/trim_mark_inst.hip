@@ -161,12 +161,21 @@ int launch_range_exact(ReplayArgs a, int64_t nslots, int nchunk, hipStream_t st)
     return TRIM_OK;
 }
 
-int launch_replay(ReplayArgs a, int64_t nslots, hipStream_t st) {
+int launch_pick(ReplayArgs a, hipStream_t st) {
+    replay_carve(a);
+    const size_t off = a.off_cl;          // (what follows is the replay's)
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(pick_kernel), off));
+    hipLaunchKernelGGL(pick_kernel, dim3((unsigned)((a.nslots + kXcds - 1) / kXcds * kXcds)), dim3(kReplayThreads), off, st, a);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+
+int launch_replay(ReplayArgs a, hipStream_t st) {
     const int E = result_slots(a.k);
     const size_t off = replay_carve(a);
     void (*fn)(const ReplayArgs) = E == 1 ? replay_kernel<1> : E == 2 ? replay_kernel<2> : E == 4 ? replay_kernel<4> : replay_kernel<16>;
     HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), off));
-    hipLaunchKernelGGL(fn, dim3((unsigned)nslots), dim3(kReplayThreads), off, st, a);
+    hipLaunchKernelGGL(fn, dim3((unsigned)a.nslots), dim3(kReplayThreads), off, st, a);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
 }

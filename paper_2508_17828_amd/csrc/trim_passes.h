@@ -156,8 +156,9 @@ struct ReplayArgs {
     int32_t nlist, nseg, max_cand;
     int32_t k, batch;
     int32_t lo, hi;             // candidates of this pass; lo == 0: R is empty
+    int32_t mid;                // the first batch's end, where it is taken with the pass after it; else 0
     const int32_t *order;       // queries that it does not name are left alone
-    int64_t slot0;
+    int64_t slot0, nslots;
     const int32_t *totals;
     const uint32_t *possible;
     const float *g, *d2;        // d2: lower bounds of the exact distances
@@ -175,6 +176,7 @@ struct ReplayArgs {
     int32_t *counts;
     uint32_t off_segp, off_segd, off_cl, off_g, off_d2, off_id, off_rd2, off_rid, off_q, off_key, off_todo;
 };
+constexpr int kPickMost = 128, kPickGroup = 4;    // pick_kernel: most results, least vectors of the first batch per result
 constexpr int kReplayThreads = 512, kReplayCap = 2048;   // (a power of two)
 
 // ---- few queries (trim_few.h) ----

@@ -112,6 +112,13 @@ def test_passes_equal_the_single_kernel(T, case):
         np.testing.assert_array_equal(got["ids"].cpu().numpy(), want["ids"].cpu().numpy())
 
 
+# the first batch measured with the pass after it, from the least batch per result and up to the most results where it is, on both sides
+# of either; batches whose end lies inside a word of marks and at its edge; more passes after it
+@pytest.mark.parametrize("k,batch", ((1, 4), (1, 3), (10, 40), (10, 39), (8, 1016), (10, 1030), (64, 300), (128, 512), (129, 516), (3, 4096)))
+def test_first_batch_with_the_next_pass(T, k, batch):
+    test_passes_equal_the_single_kernel(T, (16000, 768, 96, 8, 20, 280, 9, k, batch, 0.4, 0.3, 0.0))
+
+
 # no lists and rows enough for 512 queries by 128 rows at a time (measure_kernel): queries that fill a block, leave one idle and begin a
 # second, a last tile of a few rows, an uneven number of pairs of slices; the short stretches before take 128 by 128
 @pytest.mark.parametrize("n,d,M,nq,batch", ((30000, 528, 44, 320, 64), (30103, 544, 68, 515, 64), (50000, 600, 120, 512, 1024), (28100, 1024, 32, 319, 64)))
