@@ -1247,8 +1247,8 @@ __global__ __launch_bounds__(kReplayThreads) void pick_kernel(const ReplayArgs a
 // here of those whose lower bound (a.d2) does not exceed the threshold at the start, the first wave
 // goes through the batch rule with these, and all threads count the others by the thresholds it leaves.  (When the first
 // wave went through all of them, the other seven waited: 2,500 queries x 500,000 x 768 472 -> 365 us, 500 x 300,000 x 960, k = 100,
-// 963 -> 575.  Of a later pass's 340,000 clocks there, 144,000 are the first wave's, some 200 insertions one after the
-// other, 80,000 the rows, 31,000 the bounds read.)
+// 963 -> 575.  Of a later pass's 340,000 clocks there, 144,000 were the first wave's, some 200 insertions one after the
+// other, 80,000 the rows, 31,000 the bounds read.  A batch's entries inserted together, and that wave first on its SIMD: 537 -> 510 us.)
 // The first pass (seed and first batch, lo == 0) is done by all threads: the seed's distances give the
 // batch its threshold; of its survivors the k with the least lower bounds are measured, the largest of those
 // distances bounds the k-th, so that only bounds up to it need measuring; a sort gives R.
@@ -1450,6 +1450,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                 const int nt = s_ntodo;
                 measure(nt);
                 if (wave == 0) {
+                    __builtin_amdgcn_s_setprio(3);       // (the workgroup waits for this wave)
                     // the measured ones in scan order
                     uint32_t word = s_bit[lane];
                     const int ones = __popc(word);
@@ -1468,6 +1469,7 @@ __global__ __launch_bounds__(kReplayThreads) void replay_kernel(const ReplayArgs
                     __builtin_amdgcn_wave_barrier();
                     replay_measured<E>(R, frozen_b, tau_f, s_cl, s_g, s_d2, s_id, s_todo, nt, a.batch, &s_steps, s_key);
                     if (lane == 0) s_tau = R.t_d2;
+                    __builtin_amdgcn_s_setprio(0);
                 }
                 sync_block();
                 const TauSteps steps = s_steps;

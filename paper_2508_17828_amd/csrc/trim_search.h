@@ -329,6 +329,24 @@ struct ResultRegs {
             insert(key_at(key, src));
         }
     }
+    // The same with keys and the lanes left in a mask; whether any item beat the k-th entry.
+    __device__ __forceinline__ bool insert_keys(bool pending, unsigned long long key) {
+        unsigned long long m = __ballot(pending && key < t);
+        if (m == 0) return false;
+        if constexpr (E == 2 || E == 4) {
+            if (__popcll(m) >= kMergeFrom) {
+                merge_items(pending && key < t, key);
+                return true;
+            }
+        }
+        do {
+            const int src = __ffsll((long long)m) - 1;
+            m &= m - 1;
+            insert(key_at(key, src));
+            m &= __ballot(key < t);
+        } while (m);
+        return true;
+    }
 };
 
 // The lanes' values (no NaN), ascending by lane: a bitonic network.

@@ -174,16 +174,15 @@ __device__ __forceinline__ void replay_measured(ResultRegs<E> &R, int &frozen_b,
         // (who does not beat the k-th distance now never will: it only falls)
         unsigned long long left = __ballot(pending && g <= (b == frozen_b ? tau_f : R.t_d2) && key < R.t);
         while (left) {
-            const int src = __ffsll((long long)left) - 1;
-            left &= left - 1;
-            const int xb = __builtin_amdgcn_readlane(b, src);
-            const float xg = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g), src));
+            const int xb = __builtin_amdgcn_readlane(b, __ffsll((long long)left) - 1);
             if (xb != frozen_b) { frozen_b = xb; tau_f = R.t_d2; }
-            if (!(xg <= tau_f)) continue;
-            R.insert(R.key_at(key, src));
-            left &= __ballot(key < R.t);
-            if (xb != last_b) { last_b = xb; ++out.count; }
-            if (R.lane == 0) steps[out.count - 1] = ((unsigned long long)(uint32_t)xb << 32) | __float_as_uint(R.t_d2);
+            // (a batch's entries together: they have one threshold, and only what it leaves counts)
+            const bool here = b == xb;
+            if (R.insert_keys(here && g <= tau_f, key)) {
+                if (xb != last_b) { last_b = xb; ++out.count; }
+                if (R.lane == 0) steps[out.count - 1] = ((unsigned long long)(uint32_t)xb << 32) | __float_as_uint(R.t_d2);
+            }
+            left &= __ballot(!here && key < R.t);
         }
     }
     if (R.lane == 0) *info = out;
