@@ -1026,13 +1026,36 @@ int launch_probe_ranked(const float *queries, int64_t nq, int d, const float *ce
 //   30,000 x 960, no lists, 64 / 80 / 128                         357 / 311  355 / 403  357 / 457
 // What is left on the wrong side: 800,000 x 384 and 256 at gamma 0.5, 30 to 55 queries, up to 1.4 times the single kernel's time
 // (it abandons nearly everything early there, which depends on the data), 30,000 x 768 and 1536 from 96 queries on, up to 1.14.
+//
+// Over rows of 512 values and more settle_kernel stops at the first batch, and what its threshold leaves is measured by many workgroups and
+// then replayed (few_rows_kernel): two launches more, 4 to 5 us.  Without / with, us (k = 10, gamma 0.3 where nothing is said):
+//   200,000 x 768 (unit vectors), 30 of 450 lists, 1 / 33 / 100 queries     195 / 85    373 / 216   638 / 476;  k = 100, 33: 695 / 321
+//   500,000 x 768, 20 of 700, gamma 0.1, 1 / 16 / 128 queries               978 / 166   1548 / 381  2345 / 1736
+//   100,000 x 1536, 30 of 300, 1 / 33, gamma 0.1; gamma 0.5                 1850 / 213  2705 / 939;   283 / 109   615 / 392
+//   200,000 x 960, no lists, 1 / 4 queries                                  251 / 161   389 / 237
+//   60,000 x 768, 16 of 256 lists that separate the data, 1 / 33 queries    33 / 38     80 / 88     (hardly anyone is left: two launches more)
+// With fewer values it costs more than it gives: 500,000 x 384, 64 of 1024, 1 / 67 queries 30.7 / 34.7  74.5 / 83.1.
+// With them the lookups may be more, single kernel / this, us:
+//   lists: 300,000 x 1536, 4-bit codes, 60 of 500, 33 / 128 queries 2376 / 595  2477 / 1547; 400,000 x 768, 32 of 256, 90 / 128, gamma 0.5
+//   785 / 553  793 / 694 (gamma 0.1: 6538 / 3913  6800 / 5238): all that 128 queries came to, 3.5e9;
+//   none, x 960: about as the square root of the vectors, where one workgroup per query takes longer.  40,000 vectors, 48 / 67 queries 330 / 303
+//   330 / 391; 200,000, 16 / 22 541 / 412  547 / 576; 500,000, 10 / 16 840 / 775  858 / 827.  With more than 64 results, which hold the
+//   single kernel up more: 40,000, 67 / 90 521 / 545  527 / 681; 200,000, 48 / 67 1750 / 1382  1782 / 2031; 500,000, 22 / 33 2183 / 1859  2184 / 2376.
 constexpr int64_t kFewQueries = 128, kFewQueriesWide = 256;
 constexpr double kFewLookups = 500000.0, kFewShortRows = 1.05e8, kFewNoLists = 2.5e8;
 constexpr size_t kFewBytes = size_t(1) << 30;
+double few_pass_lookups(int64_t n, int k, bool lists) {
+    if (lists) return 4e9;
+    const double root = std::sqrt((double)n);
+    return k <= kWave ? 1.05e6 * root : std::min(7000.0 * (double)n, 2.6e6 * root);
+}
 struct FewLayout {
     int64_t stride;           // bounds per query (0: not this way)
     size_t off_g, off_least, off_d2, total;      // totals at 0
     bool measure_first;
+    // passes over long rows (r_stride 0: none); a work space that holds only the `least` bytes goes without
+    int64_t r_stride;
+    size_t off_all, off_rd2, off_rid, least;
 };
 FewLayout few_layout(const trim_index_view *ix, int64_t nq, const trim_candidates *cand, int k, int batch) {
     FewLayout L{};
@@ -1041,7 +1064,9 @@ FewLayout few_layout(const trim_index_view *ix, int64_t nq, const trim_candidate
     // (a query's share of the base set, lists as long as each other)
     const double scanned = cand ? (double)ix->n * std::min(1.0, (double)cand->nprobe / cand->nlist) : (double)ix->n;
     const double lookups = (double)nq * scanned * ix->M;
-    if (nq > 1 && (lookups > kFewLookups * ix->d || (ix->d < kLongRow && lookups > kFewShortRows) || (!cand && lookups > kFewNoLists))) return L;
+    const bool fits = nq == 1 || !(lookups > kFewLookups * ix->d || (ix->d < kLongRow && lookups > kFewShortRows) || (!cand && lookups > kFewNoLists));
+    const bool passes = ix->d >= kLongRow && mc > (int64_t)k + batch;
+    if (!fits && !(passes && lookups <= few_pass_lookups(ix->n, k, cand != nullptr))) return L;
     const int64_t stride = (mc + 15) / 16 * 16;
     const size_t g_bytes = (size_t)nq * stride * 4;
     if ((size_t)stride > kFewBytes || g_bytes > kFewBytes || mc > 0x40000000 || !few_fits(ix->d, code_bytes(ix), is_fs(ix), k, cand ? cand->nprobe : 0)) return L;
@@ -1052,9 +1077,18 @@ FewLayout few_layout(const trim_index_view *ix, int64_t nq, const trim_candidate
     L.off_least = L.off_g + up256(g_bytes);
     L.off_d2 = L.off_least + up256((size_t)nq * ((stride + 63) / 64) * 4);
     L.total = L.off_d2 + (L.measure_first ? up256((size_t)nq * (k + batch) * 4) : 0);
+    L.least = fits ? L.total : 0;
+    if (passes) {
+        L.r_stride = kWave * result_slots(k);
+        L.off_all = L.total;
+        L.off_rd2 = L.off_all + up256(g_bytes);
+        L.off_rid = L.off_rd2 + up256((size_t)nq * L.r_stride * 4);
+        L.total = L.off_rid + up256((size_t)nq * L.r_stride * 4);
+        if (!fits) L.least = L.total;
+    }
     return L;
 }
-int knn_few(const trim_index_view *ix, const FewLayout &L, const SearchArgs &a, unsigned char *ws, hipStream_t st) {
+int knn_few(const trim_index_view *ix, const FewLayout &L, const SearchArgs &a, unsigned char *ws, size_t ws_bytes, hipStream_t st) {
     FewArgs f{};
     f.base = a.base; f.codes = a.codes; f.dlx = a.dlx; f.codebooks = a.codebooks; f.ids = a.ids; f.n = a.n;
     f.d = a.d; f.M = a.M; f.dsub = a.dsub; f.queries = a.queries; f.nq = a.nq; f.order = a.order; f.lut = a.lut;
@@ -1070,7 +1104,26 @@ int knn_few(const trim_index_view *ix, const FewLayout &L, const SearchArgs &a, 
     f.mask = a.mask; f.mask_words = a.mask_words;
     int rc;
     if ((rc = launch_bound(f, is_fs(ix), st))) return rc;
-    return launch_settle(f, st);
+    if (L.r_stride == 0 || ws_bytes < L.total) return launch_settle(f, st);
+    f.d2_all = reinterpret_cast<float *>(ws + L.off_all);
+    f.r_d2 = reinterpret_cast<float *>(ws + L.off_rd2);
+    f.r_id = reinterpret_cast<int32_t *>(ws + L.off_rid);
+    f.r_stride = (int32_t)L.r_stride;
+    if ((rc = launch_settle(f, st))) return rc;
+    // (passes begin where batches do)
+    const int64_t most = f.max_cand;
+    for (int64_t lo = (int64_t)a.k + a.batch, hi; lo < most; lo = hi) {
+        hi = most;
+        if (a.nseg == 0 || lo < 1024) {
+            hi = (int64_t)a.k + (lo - a.k) * 8;
+            if (hi > most / 2) hi = most;
+        }
+        f.lo = (int32_t)lo;
+        f.hi = (int32_t)hi;
+        if ((rc = launch_few_rows(f, st))) return rc;
+        if ((rc = launch_settle(f, st))) return rc;
+    }
+    return TRIM_OK;
 }
 
 int search_knn(const trim_index_view *index, const float *queries, int64_t nq, const float *lut, const trim_candidates *cand,
@@ -1102,7 +1155,7 @@ int search_knn(const trim_index_view *index, const float *queries, int64_t nq, c
     a.nq = nq; a.order = query_order;
     if (workspace && !a.work && (reinterpret_cast<uintptr_t>(workspace) & 255u) == 0 && aligned16(queries)) {
         const FewLayout F = few_layout(index, nq, cand, k, batch);
-        if (F.stride > 0 && workspace_bytes >= F.total) return knn_few(index, F, a, static_cast<unsigned char *>(workspace), st);
+        if (F.stride > 0 && workspace_bytes >= F.least) return knn_few(index, F, a, static_cast<unsigned char *>(workspace), workspace_bytes, st);
         FinishPlan fp;
         const KnnLayout L = knn_layout(index, nq, cand, k, &fp);
         if (L.slab > 0 && workspace_bytes >= L.total && (!lut || lut_tiled(a.dsub, is_fs(index))))

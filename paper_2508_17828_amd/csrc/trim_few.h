@@ -9,6 +9,12 @@
 //   settle_kernel  one workgroup per query: the seed, the first batch, then whoever is not above the
 //                  threshold, measured and replayed batch by batch
 //
+// Over long rows, whose bounds leave thousands to be measured, that is a workgroup's work no longer: settle_kernel ends with the first
+// batch, and then, pass by pass,
+//
+//   few_rows_kernel  many workgroups per query: the exact distances of those that the threshold leaves
+//   settle_kernel    replays them
+//
 // No candidate is abandoned early and no list is passed over: with CUs to spare the lookups cost less than the chain
 // of thresholds they would have to wait for.  Bound by latency: launches, the table, the measured rows.
 #pragma once
@@ -110,7 +116,8 @@ __global__ __launch_bounds__(kBoundThreads) __attribute__((amdgpu_waves_per_eu(6
 // by the first wave; a stretch whose bounds' least (one of every 64, from bound_kernel) is above the threshold is not looked
 // at.  Bound by latency: bounds of 84,000 candidates read stretch by stretch, first-batch bounds read one after the other and a
 // sort across the lanes took 46,000 of a single query's 59,000 clocks (25.2 us; now 10.6).
-template <int E>
+// PART: 0 all of it; 1 the seed and the first batch; 2 a pass after that, measured already.
+template <int E, int PART>
 __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs a) {
     constexpr int T = settle_threads(E);
     extern __shared__ __align__(16) unsigned char smem[];
@@ -135,21 +142,13 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
     const int64_t q = a.order ? a.order[slot] : slot;
     if (q < 0 || q >= a.nq) return;
     const float *row_g = a.g + (size_t)slot * a.stride;
-    // the first batch's bounds and distances on their way (what lies beyond it is not used)
-    constexpr int kPre = 2;
-    float pre_g[kPre], pre_d2[kPre] = {};
-#pragma unroll
-    for (int u = 0; u < kPre; ++u) {
-        pre_g[u] = row_g[tid + u * T < a.stride ? tid + u * T : 0];
-        if (a.d2) pre_d2[u] = a.d2[(size_t)slot * (a.k + a.batch) + (tid + u * T < a.k + a.batch ? tid + u * T : 0)];
-    }
-    for (int t = tid; t < a.d; t += T) q_lds[t] = a.queries[(size_t)q * a.d + t];
-    if (tid < 256) hist[tid] = 0;
-    if (tid == 0) { s_most = 0; s_least = ~0u; s_n = 0; s_nk = 0; s_count = 0; }
-    segment_table(a.list_offsets, a.probes, a.nlist, a.nseg, a.n, a.max_cand, q, segp, segd);
+    float *const r_d2 = PART ? a.r_d2 + (size_t)slot * a.r_stride : nullptr;
+    int32_t *const r_id = PART ? a.r_id + (size_t)slot * a.r_stride : nullptr;
+    uint32_t *mask_row = a.mask ? a.mask + (size_t)q * a.mask_words : nullptr;
     const int total = a.totals[slot];
     const int ns = total < a.k ? total : a.k, fb = total < a.k + a.batch ? total : a.k + a.batch;
-    uint32_t *mask_row = a.mask ? a.mask + (size_t)q * a.mask_words : nullptr;
+    const int from = PART == 2 ? a.lo : fb, until = PART == 2 && a.hi < total ? a.hi : total;      // (of the rest)
+    if (PART == 2 && from >= until) return;
     // exact distances of n candidates at(i), four rows per half wave; put(i, d2, storage position)
     auto measure = [&](int n, auto at, auto put) {
         const int half = tid >> 5, lane32 = tid & 31;
@@ -165,6 +164,23 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
         }
         sync_block();
     };
+    if constexpr (PART == 2) {
+        for (int i = tid; i < kWave * E; i += T) { rd2[i] = r_d2[i]; rid[i] = r_id[i]; }
+        if (tid == 0) s_count = a.n_exact ? a.n_exact[q] : 0;
+        segment_table(a.list_offsets, a.probes, a.nlist, a.nseg, a.n, a.max_cand, q, segp, segd);
+    } else {
+    // the first batch's bounds and distances on their way (what lies beyond it is not used)
+    constexpr int kPre = 2;
+    float pre_g[kPre], pre_d2[kPre] = {};
+#pragma unroll
+    for (int u = 0; u < kPre; ++u) {
+        pre_g[u] = row_g[tid + u * T < a.stride ? tid + u * T : 0];
+        if (a.d2) pre_d2[u] = a.d2[(size_t)slot * (a.k + a.batch) + (tid + u * T < a.k + a.batch ? tid + u * T : 0)];
+    }
+    for (int t = tid; t < a.d; t += T) q_lds[t] = a.queries[(size_t)q * a.d + t];
+    if (tid < 256) hist[tid] = 0;
+    if (tid == 0) { s_most = 0; s_least = ~0u; s_n = 0; s_nk = 0; s_count = 0; }
+    segment_table(a.list_offsets, a.probes, a.nlist, a.nseg, a.n, a.max_cand, q, segp, segd);
     // ---- the seed: its largest distance is the first batch's threshold ----
     if (a.d2) {
 #pragma unroll
@@ -287,6 +303,7 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
         }
     }
     sync_block();
+    }
     ResultRegs<E> R;
     int frozen_b = -2, survivors = s_count;
     float tau_f = 0.0f;
@@ -296,12 +313,13 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
     }
     sync_block();
     // ---- the rest ----
+    if constexpr (PART != 1) {
     const float *least_of = a.least + (size_t)slot * ((a.stride + 63) / 64);
     int looked = 0;                              // up to here s_ahead is known
     uint32_t ahead = 0;
-    for (int w0 = fb; w0 < total;) {
+    for (int w0 = from; w0 < until;) {
         const int V = a.nseg == 0 && w0 < 16384 ? 4 : 16, base = w0 & ~3;
-        const int w1 = total - base < V * T ? total : base + V * T;
+        const int w1 = until - base < V * T ? until : base + V * T;
         if (V == 16) {
             // the next stretches, a wave each (thresholds only fall: who is above this one stays out)
             if (w0 >= looked) {
@@ -309,20 +327,20 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
                 if (tid == 0) s_ahead = 0;
                 sync_block();
                 const float tau = __builtin_fmaxf(s_tau, s_tau_f);
-                const int64_t from = (int64_t)base + (int64_t)wave * 16 * T, to = from + 16 * T < total ? from + 16 * T : total;
+                const int64_t first = (int64_t)base + (int64_t)wave * 16 * T, to = first + 16 * T < until ? first + 16 * T : until;
                 constexpr int kLeast = 16 * T / 64 / kWave + 1;
-                const int g0 = (int)(from >> 6), g1 = (int)((to - 1) >> 6);
+                const int g0 = (int)(first >> 6), g1 = (int)((to - 1) >> 6);
                 float v[kLeast];
                 bool any = false;
 #pragma unroll
-                for (int u = 0; u < kLeast; ++u) v[u] = least_of[from < to ? min(g0 + u * kWave + lane, g1) : 0];
+                for (int u = 0; u < kLeast; ++u) v[u] = least_of[first < to ? min(g0 + u * kWave + lane, g1) : 0];
 #pragma unroll
                 for (int u = 0; u < kLeast; ++u) any |= v[u] <= tau;
-                any &= from < to;
+                any &= first < to;
                 if (__any(any) && lane == 0) atomicOr(&s_ahead, 1u << wave);
                 sync_block();
                 ahead = s_ahead;
-                looked = base + 16 * T * (T / kWave) < total ? base + 16 * T * (T / kWave) : total;
+                looked = base + 16 * T * (T / kWave) < until ? base + 16 * T * (T / kWave) : until;
             }
             const bool some = ahead & 1u;
             ahead >>= 1;
@@ -372,18 +390,27 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
                 }
             if (tid == 0) s_n = 0;
             sync_block();
-            // who is a survivor by now (a batch keeps the threshold that it began with) is measured
-            const float now = s_tau, tf = s_tau_f;
-            const int fz = s_frozen;
-            for (int i = tid; i < np; i += T) {
-                const int c = s_cl[i], b = (c - a.k) / a.batch;
-                s_d2[i] = __builtin_inff();
-                s_id[i] = kEmptyId;
-                if (s_g[i] <= (b == fz ? tf : now)) s_todo[atomicAdd(&s_n, 1)] = (uint16_t)i;
+            if constexpr (PART == 2) {           // (all that the pass's first threshold leaves have been measured)
+                for (int i = tid; i < np; i += T) {
+                    const int c = s_cl[i], pos = segment_position(c, segp, segd, a.nseg);
+                    s_d2[i] = a.d2_all[(size_t)slot * a.stride + c];
+                    s_id[i] = a.ids ? a.ids[pos] : pos;
+                }
+                sync_block();
+            } else {
+                // who is a survivor by now (a batch keeps the threshold that it began with) is measured
+                const float now = s_tau, tf = s_tau_f;
+                const int fz = s_frozen;
+                for (int i = tid; i < np; i += T) {
+                    const int c = s_cl[i], b = (c - a.k) / a.batch;
+                    s_d2[i] = __builtin_inff();
+                    s_id[i] = kEmptyId;
+                    if (s_g[i] <= (b == fz ? tf : now)) s_todo[atomicAdd(&s_n, 1)] = (uint16_t)i;
+                }
+                sync_block();
+                measure(s_n, [&](int i) { return s_cl[s_todo[i]]; },
+                        [&](int i, float v, int pos) { s_d2[s_todo[i]] = v; s_id[s_todo[i]] = a.ids ? a.ids[pos] : pos; });
             }
-            sync_block();
-            measure(s_n, [&](int i) { return s_cl[s_todo[i]]; },
-                    [&](int i, float v, int pos) { s_d2[s_todo[i]] = v; s_id[s_todo[i]] = a.ids ? a.ids[pos] : pos; });
             if (wave == 0) {
                 survivors += replay_entries<E>(R, frozen_b, tau_f, s_cl, s_g, s_d2, s_id, np, a.batch, mask_row, a.mask_words);
                 if (lane == 0) { s_tau = R.t_d2; s_frozen = frozen_b; s_tau_f = tau_f; }
@@ -393,15 +420,81 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
         sync_block();
         w0 = w1;
     }
+    }
     if (wave == 0) {
         R.store(rd2, rid);
         if (lane == 0 && a.n_exact) a.n_exact[q] = survivors;
     }
     sync_block();
+    if constexpr (PART != 0)
+        for (int i = tid; i < kWave * E; i += T) { r_d2[i] = rd2[i]; r_id[i] = rid[i]; }
     for (int i = tid; i < a.k; i += T) {
         const int32_t id = rid[i];
         a.out_ids[(size_t)q * a.k + i] = id == kEmptyId ? -1 : id;
         a.out_d2[(size_t)q * a.k + i] = rd2[i];
+    }
+}
+
+// The exact distances of the candidates [lo, hi) whose bound does not exceed the k-th distance so far: all that can be survivors among them
+// (the threshold only falls), and some more.  The candidates of a query are dealt out 64 at a time, since the near ones lie together; a
+// wave lists its 64, all half waves measure.  Bound by the rows, which one workgroup reads at 0.15 TB/s: one query over 14,000 unit vectors of 768
+// values, nearly all of them wanted, 978 us with settle_kernel alone, 166 so; 128 queries 2345, 1736.
+constexpr int kFewRowsThreads = 256;
+__global__ __launch_bounds__(kFewRowsThreads) void few_rows_kernel(const FewArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    float *q_lds = reinterpret_cast<float *>(smem + a.off_q);
+    int *segp = reinterpret_cast<int *>(smem + a.off_segp), *segd = reinterpret_cast<int *>(smem + a.off_segd);
+    constexpr int kWaves = kFewRowsThreads / kWave, kHalves = 2 * kWaves;
+    __shared__ int s_c[kWaves * kWave], s_n;
+    const int tid = threadIdx.x, lane = tid & 63, half = tid >> 5, lane32 = tid & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t slot = blockIdx.y;
+    const int64_t q = a.order ? a.order[slot] : slot;
+    if (q < 0 || q >= a.nq) return;
+    const int total = a.totals[slot], hi = a.hi < total ? a.hi : total;
+    if (a.lo >= hi) return;
+    const float tau = a.r_d2[(size_t)slot * a.r_stride + a.k - 1];
+    const float *row_g = a.g + (size_t)slot * a.stride, *least = a.least + (size_t)slot * ((a.stride + 63) / 64);
+    float *out = a.d2_all + (size_t)slot * a.stride;
+    const int g0 = a.lo >> 6, g1 = ((hi - 1) >> 6) + 1, step = (int)gridDim.x;
+    bool ready = false;
+    for (int64_t b0 = g0 + (int)blockIdx.x; b0 < g1; b0 += (int64_t)kWave * step) {
+        const int64_t mine = b0 + (int64_t)lane * step;
+        unsigned long long left = __ballot(mine < g1 && least[mine < g1 ? mine : g0] <= tau);     // (the same in all waves)
+        while (left) {
+            if (!ready) {
+                ready = true;
+                for (int t = tid; t < a.d; t += kFewRowsThreads) q_lds[t] = a.queries[(size_t)q * a.d + t];
+                segment_table(a.list_offsets, a.probes, a.nlist, a.nseg, a.n, a.max_cand, q, segp, segd);
+            }
+            int group = -1;                 // a wave each
+            for (int w = 0; w < kWaves && left; ++w) {
+                const int at = __ffsll((long long)left) - 1;
+                left &= left - 1;
+                if (w == wave) group = (int)(b0 + (int64_t)at * step);
+            }
+            if (tid == 0) s_n = 0;
+            sync_block();
+            if (group >= 0) {
+                const int c = group * 64 + lane;
+                const bool on = c >= a.lo && c < hi && row_g[c < hi ? c : a.lo] <= tau;
+                const unsigned long long m = __ballot(on);
+                int to = 0;
+                if (lane == 0) to = atomicAdd(&s_n, __popcll(m));
+                to = __builtin_amdgcn_readfirstlane(to);
+                if (on) s_c[to + __popcll(m & ((1ull << lane) - 1ull))] = c;
+            }
+            sync_block();
+            const int n = s_n;
+            for (int i = half; i < n; i += 2 * kHalves) {
+                const int c0 = s_c[i], c1 = s_c[i + kHalves < n ? i + kHalves : i];
+                float d2[2];
+                exact_d2_half_x2_deep<4>(a.base + (size_t)segment_position(c0, segp, segd, a.nseg) * a.d,
+                                         a.base + (size_t)segment_position(c1, segp, segd, a.nseg) * a.d, q_lds, a.d, lane32, d2);
+                if (lane32 == 0) { out[c0] = d2[0]; out[c1] = d2[1]; }
+            }
+            sync_block();
+        }
     }
 }
 

@@ -1,5 +1,6 @@
 // The instances of the few-queries kernels and their launchers (see trim_few.h).
 #include <atomic>
+#include <type_traits>
 
 #include "trim_few.h"
 #include "trim_launch.h"
@@ -78,9 +79,25 @@ int launch_bound(FewArgs a, bool fs, hipStream_t st) {
 int launch_settle(FewArgs a, hipStream_t st) {
     const size_t lds = settle_carve(a);
     const int E = result_slots(a.k);
-    void (*fn)(const FewArgs) = E == 1 ? settle_kernel<1> : E == 2 ? settle_kernel<2> : E == 4 ? settle_kernel<4> : settle_kernel<16>;
+    auto of = [&](auto part) {
+        constexpr int P = decltype(part)::value;
+        return E == 1 ? settle_kernel<1, P> : E == 2 ? settle_kernel<2, P> : E == 4 ? settle_kernel<4, P> : settle_kernel<16, P>;
+    };
+    void (*fn)(const FewArgs) = !a.d2_all ? of(std::integral_constant<int, 0>{}) : a.lo == 0 ? of(std::integral_constant<int, 1>{})
+                                                                                             : of(std::integral_constant<int, 2>{});
     HIP_TRY(allow_lds(reinterpret_cast<const void *>(fn), lds));
     hipLaunchKernelGGL(fn, dim3((unsigned)a.nq), dim3(settle_threads(E)), lds, st, a);
+    HIP_TRY(hipGetLastError());
+    return TRIM_OK;
+}
+
+int launch_few_rows(FewArgs a, hipStream_t st) {
+    settle_carve(a);
+    const size_t lds = a.off_rd2;         // (what follows is settle's)
+    // as many workgroups as are resident at once, no more than there are groups of 64
+    const int64_t groups = ((int64_t)a.hi - a.lo + 63) / 64 + 1, nsplit = std::max<int64_t>(1, std::min<int64_t>(256 * 6 / a.nq, groups));
+    HIP_TRY(allow_lds(reinterpret_cast<const void *>(few_rows_kernel), lds));
+    hipLaunchKernelGGL(few_rows_kernel, dim3((unsigned)nsplit, (unsigned)a.nq), dim3(kFewRowsThreads), lds, st, a);
     HIP_TRY(hipGetLastError());
     return TRIM_OK;
 }

@@ -57,6 +57,7 @@ size_t replay_lds(int d, int k, int nseg);      // LDS of one of their workgroup
 bool few_fits(int d, int M, bool fs, int k, int nseg);
 int launch_bound(FewArgs a, bool fs, hipStream_t st);
 int launch_settle(FewArgs a, hipStream_t st);
+int launch_few_rows(FewArgs a, hipStream_t st);
 int launch_replay(ReplayArgs a, hipStream_t st);
 int launch_pick(ReplayArgs a, hipStream_t st);
 

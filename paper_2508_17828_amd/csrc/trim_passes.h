@@ -208,6 +208,10 @@ struct FewArgs {
     int64_t stride;           // (a multiple of 16)
     float *least;             // [(stride + 63) / 64] the least bound of every 64
     float *d2;                // [k + batch] exact distances of the seed and the first batch, or null: settle measures
+    float *d2_all;            // [stride] exact distances of those that may be survivors (few_rows_kernel), or null: settle measures
+    float *r_d2;              // [r_stride] R between launches
+    int32_t *r_id;
+    int32_t r_stride, lo, hi; // candidates of this pass
     int32_t *out_ids;
     float *out_d2;
     int32_t *n_scanned, *n_exact;

@@ -178,6 +178,42 @@ def test_few_queries_equal_the_single_kernel(T, case):
                 np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
 
 
+# few queries over long rows, measured by many workgroups pass by pass: results of every width, passes that begin after 2 and after 4096
+# candidates, inside a group of 64 and at its edge, one candidate after the first batch and none; more lookups than without passes; with the
+# work space that a search without passes takes, and a byte less than either
+@pytest.mark.parametrize("case", [
+    (3000, 512, 128, 8, 0, 20, 0, 1, 1, 0.3, 0.3, 0.0),
+    (3000, 512, 128, 8, 20, 20, 7, 10, 54, 0.0, 0.3, 0.0),
+    (9000, 528, 44, 8, 12, 33, 6, 100, 7, 0.5, 0.3, 3.0),
+    (20000, 768, 96, 8, 33, 128, 33, 65, 447, 0.2, 0.2, 0.0),
+    (20000, 1536, 192, 8, 0, 9, 0, 300, 1000, 0.1, 0.2, 0.0),
+    (9000, 640, 320, 4, 16, 12, 9, 1000, 3096, 0.4, 0.5, 0.0),
+    (1035, 512, 32, 8, 0, 7, 0, 10, 1024, 0.2, 0.5, 0.0),
+    (1034, 512, 32, 8, 0, 7, 0, 10, 1024, 0.2, 0.5, 0.0),
+    (40000, 1024, 256, 8, 0, 27, 0, 128, 512, 0.3, 0.2, 0.0),
+    (20000, 768, 384, 4, 33, 128, 33, 10, 300, 0.2, 0.2, 0.0),
+], ids=lambda c: "-".join(map(str, c)))
+def test_few_queries_over_long_rows(T, case):
+    import torch
+    test_few_queries_equal_the_single_kernel(T, case)
+    n, d, M, bits, nlist, nq, nprobe, k, batch, gamma, spread, offset = case
+    ix, q, probes = built(T, n, d, M, bits, nlist, nq, nprobe, spread, offset, n + d)
+    cand, _ = ix._cand(probes)
+    view = ix._view()
+    p = lambda t: None if t is None else C.c_void_p(t.data_ptr())
+    pc = C.byref(cand) if cand is not None else None
+    need = T.lib().trim_knn_workspace_bytes(C.byref(view), nq, pc, k, batch)
+    want = single_kernel(T, ix, q, k, gamma, batch, probes, None)
+    for size in (need, need - 1, need // 2, 0):
+        ws = torch.full((need + 256,), 0xa5, dtype=torch.uint8, device="cuda")
+        ids, d2 = torch.full((nq, k), -7, dtype=torch.int32, device="cuda"), torch.full((nq, k), -7.0, device="cuda")
+        rc = T.lib().trim_search_knn_ws(C.byref(view), p(q), nq, None, pc, k, gamma, batch, None, p(ids), p(d2), None, None, 0, p(ws), size,
+                                        C.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert rc == 0
+        assert torch.equal(ids, want["ids"]) and torch.equal(d2, want["d2"]), size
+        assert (ws[size:] == 0xa5).all()
+
+
 # survivors few and far between, at the ends of the stretches that are looked at together and of their groups of 64; result sets of
 # both block sizes (1024 and 512 threads: other stretches); after results that fill up late
 @pytest.mark.parametrize("k,batch", ((10, 64), (300, 100)))
