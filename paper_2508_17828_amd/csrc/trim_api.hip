@@ -1055,7 +1055,7 @@ struct FewLayout {
     bool measure_first;
     // passes over long rows (r_stride 0: none); a work space that holds only the `least` bytes goes without
     int64_t r_stride;
-    size_t off_all, off_rd2, off_rid, least;
+    size_t off_all, off_rd2, off_rid, off_n, least;
 };
 FewLayout few_layout(const trim_index_view *ix, int64_t nq, const trim_candidates *cand, int k, int batch) {
     FewLayout L{};
@@ -1083,7 +1083,8 @@ FewLayout few_layout(const trim_index_view *ix, int64_t nq, const trim_candidate
         L.off_all = L.total;
         L.off_rd2 = L.off_all + up256(g_bytes);
         L.off_rid = L.off_rd2 + up256((size_t)nq * L.r_stride * 4);
-        L.total = L.off_rid + up256((size_t)nq * L.r_stride * 4);
+        L.off_n = L.off_rid + up256((size_t)nq * L.r_stride * 4);
+        L.total = L.off_n + up256((size_t)nq * 4);
         if (!fits) L.least = L.total;
     }
     return L;
@@ -1108,6 +1109,7 @@ int knn_few(const trim_index_view *ix, const FewLayout &L, const SearchArgs &a, 
     f.d2_all = reinterpret_cast<float *>(ws + L.off_all);
     f.r_d2 = reinterpret_cast<float *>(ws + L.off_rd2);
     f.r_id = reinterpret_cast<int32_t *>(ws + L.off_rid);
+    f.r_n = reinterpret_cast<int32_t *>(ws + L.off_n);
     f.r_stride = (int32_t)L.r_stride;
     if ((rc = launch_settle(f, st))) return rc;
     // (passes begin where batches do)

@@ -166,7 +166,7 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
     };
     if constexpr (PART == 2) {
         for (int i = tid; i < kWave * E; i += T) { rd2[i] = r_d2[i]; rid[i] = r_id[i]; }
-        if (tid == 0) s_count = a.n_exact ? a.n_exact[q] : 0;
+        if (tid == 0) s_count = a.r_n[slot];
         segment_table(a.list_offsets, a.probes, a.nlist, a.nseg, a.n, a.max_cand, q, segp, segd);
     } else {
     // the first batch's bounds and distances on their way (what lies beyond it is not used)
@@ -424,6 +424,7 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
     if (wave == 0) {
         R.store(rd2, rid);
         if (lane == 0 && a.n_exact) a.n_exact[q] = survivors;
+        if (PART && lane == 0) a.r_n[slot] = survivors;
     }
     sync_block();
     if constexpr (PART != 0)

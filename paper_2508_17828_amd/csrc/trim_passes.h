@@ -211,6 +211,7 @@ struct FewArgs {
     float *d2_all;            // [stride] exact distances of those that may be survivors (few_rows_kernel), or null: settle measures
     float *r_d2;              // [r_stride] R between launches
     int32_t *r_id;
+    int32_t *r_n;             // survivors so far (by place: the order may name a query twice)
     int32_t r_stride, lo, hi; // candidates of this pass
     int32_t *out_ids;
     float *out_d2;

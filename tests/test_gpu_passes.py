@@ -212,6 +212,12 @@ def test_few_queries_over_long_rows(T, case):
         assert rc == 0
         assert torch.equal(ids, want["ids"]) and torch.equal(d2, want["d2"]), size
         assert (ws[size:] == 0xa5).all()
+    order = torch.arange(nq, dtype=torch.int32, device="cuda")
+    order[nq - 1] = 0                                    # a query twice
+    want = single_kernel(T, ix, q, k, gamma, batch, probes, order)
+    got = T.trim_search_knn(ix, q, k, gamma, batch, probes=probes, want_mask=True, query_order=order)
+    for name in ("ids", "d2", "n_scanned", "n_exact", "mask"):
+        assert torch.equal(got[name][:-1], want[name][:-1]), name
 
 
 # survivors few and far between, at the ends of the stretches that are looked at together and of their groups of 64; result sets of
