@@ -1029,17 +1029,17 @@ int launch_probe_ranked(const float *queries, int64_t nq, int d, const float *ce
 //
 // Over rows of 512 values and more settle_kernel stops at the first batch, and what its threshold leaves is measured by many workgroups and
 // then replayed (few_rows_kernel): two launches more, 4 to 5 us.  Without / with, us (k = 10, gamma 0.3 where nothing is said):
-//   200,000 x 768 (unit vectors), 30 of 450 lists, 1 / 33 / 100 queries     195 / 85    373 / 216   638 / 476;  k = 100, 33: 695 / 321
-//   500,000 x 768, 20 of 700, gamma 0.1, 1 / 16 / 128 queries               978 / 166   1548 / 381  2345 / 1736
-//   100,000 x 1536, 30 of 300, 1 / 33, gamma 0.1; gamma 0.5                 1850 / 213  2705 / 939;   283 / 109   615 / 392
-//   200,000 x 960, no lists, 1 / 4 queries                                  251 / 161   389 / 237
-//   60,000 x 768, 16 of 256 lists that separate the data, 1 / 33 queries    33 / 38     80 / 88     (hardly anyone is left: two launches more)
+//   200,000 x 768 (unit vectors), 30 of 450 lists, 1 / 33 / 128 queries     195 / 68    373 / 190   658 / 524;  k = 100, 33: 695 / 252
+//   500,000 x 768, 20 of 700, gamma 0.1, 1 / 16 / 33 queries                978 / 103   1548 / 311  1703 / 483
+//   100,000 x 1536, 30 of 300, 1 / 33, gamma 0.1; gamma 0.5                 1850 / 136  2705 / 863;   283 / 87   615 / 363
+//   200,000 x 960, no lists, 1 / 4 queries                                  251 / 164   389 / 220
+//   60,000 x 768, 16 of 256 lists that separate the data, 1 / 33 queries    33 / 39     80 / 89     (hardly anyone is left: two launches more)
 // With fewer values it costs more than it gives: 500,000 x 384, 64 of 1024, 1 / 67 queries 30.7 / 34.7  74.5 / 83.1.
 // With them the lookups may be more, single kernel / this, us:
-//   lists: 300,000 x 1536, 4-bit codes, 60 of 500, 33 / 128 queries 2376 / 595  2477 / 1547; 400,000 x 768, 32 of 256, 90 / 128, gamma 0.5
+//   lists: 300,000 x 1536, 4-bit codes, 60 of 500, 33 / 128 queries 2376 / 569  2477 / 1547; 400,000 x 768, 32 of 256, 90 / 128, gamma 0.5
 //   785 / 553  793 / 694 (gamma 0.1: 6538 / 3913  6800 / 5238): all that 128 queries came to, 3.5e9;
 //   none, x 960: about as the square root of the vectors, where one workgroup per query takes longer.  40,000 vectors, 48 / 67 queries 330 / 303
-//   330 / 391; 200,000, 16 / 22 541 / 412  547 / 576; 500,000, 10 / 16 840 / 775  858 / 827.  With more than 64 results, which hold the
+//   330 / 391; 200,000, 16 / 22 541 / 385  547 / 576; 500,000, 10 / 16 840 / 775  858 / 827.  With more than 64 results, which hold the
 //   single kernel up more: 40,000, 67 / 90 521 / 545  527 / 681; 200,000, 48 / 67 1750 / 1382  1782 / 2031; 500,000, 22 / 33 2183 / 1859  2184 / 2376.
 constexpr int64_t kFewQueries = 128, kFewQueriesWide = 256;
 constexpr double kFewLookups = 500000.0, kFewShortRows = 1.05e8, kFewNoLists = 2.5e8;

@@ -131,6 +131,10 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
     // (stretches; over the keys)
     int32_t *s_cl = reinterpret_cast<int32_t *>(smem + a.off_key), *s_id = s_cl + kSettleList;
     float *s_g = reinterpret_cast<float *>(s_id + kSettleList), *s_d2 = s_g + kSettleList;
+    __shared__ TauSteps s_steps;
+    __shared__ uint32_t s_bit[kSettleList / 32];
+    unsigned long long *s_step = reinterpret_cast<unsigned long long *>(smem + a.off_fd2);  // [kSettleList] (passes; over the distances)
+    static_assert(kSettleList / 32 == kWave && kSettleList * 8 <= kSettleFirst * 4, "a word of the measured ones per lane; room for the steps");
     __shared__ int hist[256], part[T / kWave];
     __shared__ uint32_t s_most, s_least;
     __shared__ int s_n, s_count, s_frozen;
@@ -305,7 +309,7 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
     sync_block();
     }
     ResultRegs<E> R;
-    int frozen_b = -2, survivors = s_count;
+    int frozen_b = -2, survivors = s_count, counted = 0;       // (counted: this thread's)
     float tau_f = 0.0f;
     if (wave == 0) {
         R.load(rd2, rid, a.k, lane);
@@ -390,13 +394,52 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
                 }
             if (tid == 0) s_n = 0;
             sync_block();
-            if constexpr (PART == 2) {           // (all that the pass's first threshold leaves have been measured)
+            if constexpr (PART == 2) {
+                // All that the pass's first threshold leaves have been measured: the first wave goes through those that can enter R and
+                // leaves the thresholds by batch, all threads count the others by these (as in replay_kernel).  (All by the first wave: one
+                // query over 500,000 x 768, 20 of 700 lists, 166 -> 103 us, 16 381 -> 311; k = 100 244 -> 145, 457 -> 347.)
+                if (tid < kSettleList / 32) s_bit[tid] = 0;
+                sync_block();
+                const float now = s_tau;
                 for (int i = tid; i < np; i += T) {
-                    const int c = s_cl[i], pos = segment_position(c, segp, segd, a.nseg);
-                    s_d2[i] = a.d2_all[(size_t)slot * a.stride + c];
+                    const int c = s_cl[i];
+                    const float d2 = a.d2_all[(size_t)slot * a.stride + c];
+                    if (!(d2 <= now)) continue;
+                    const int pos = segment_position(c, segp, segd, a.nseg);
+                    s_d2[i] = d2;
                     s_id[i] = a.ids ? a.ids[pos] : pos;
+                    atomicOr(&s_bit[i >> 5], 1u << (i & 31));
                 }
                 sync_block();
+                if (wave == 0) {
+                    __builtin_amdgcn_s_setprio(3);       // (the workgroup waits for this wave)
+                    uint32_t word = s_bit[lane];
+                    const int ones = __popc(word);
+                    int place = ones;
+#pragma unroll
+                    for (int off = 1; off < kWave; off <<= 1) {
+                        const int v = __shfl_up(place, off);
+                        if (lane >= off) place += v;
+                    }
+                    const int nt = __builtin_amdgcn_readlane(place, kWave - 1);
+                    for (place -= ones; word; word &= word - 1) s_todo[place++] = (uint16_t)(lane * 32 + (__ffs((int)word) - 1));
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    replay_measured<E>(R, frozen_b, tau_f, s_cl, s_g, s_d2, s_id, s_todo, nt, a.batch, &s_steps, s_step);
+                    if (lane == 0) { s_tau = R.t_d2; s_frozen = frozen_b; s_tau_f = tau_f; }
+                    __builtin_amdgcn_s_setprio(0);
+                }
+                sync_block();
+                const TauSteps steps = s_steps;
+                for (int i = tid; i < np; i += T) {
+                    const int c = s_cl[i];
+                    if (s_g[i] <= threshold_of((c - a.k) / a.batch, steps, s_step)) {
+                        ++counted;
+                        if (mask_row && (c >> 5) < a.mask_words) atomicOr(&mask_row[c >> 5], 1u << (c & 31));
+                    }
+                }
+                sync_block();
+                continue;
             } else {
                 // who is a survivor by now (a batch keeps the threshold that it began with) is measured
                 const float now = s_tau, tf = s_tau_f;
@@ -421,6 +464,11 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
         w0 = w1;
     }
     }
+    if constexpr (PART == 2) {
+        wave_add(&s_count, counted);
+        sync_block();
+        survivors = s_count;
+    }
     if (wave == 0) {
         R.store(rd2, rid);
         if (lane == 0 && a.n_exact) a.n_exact[q] = survivors;
@@ -439,7 +487,7 @@ __global__ __launch_bounds__(settle_threads(E)) void settle_kernel(const FewArgs
 // The exact distances of the candidates [lo, hi) whose bound does not exceed the k-th distance so far: all that can be survivors among them
 // (the threshold only falls), and some more.  The candidates of a query are dealt out 64 at a time, since the near ones lie together; a
 // wave lists its 64, all half waves measure.  Bound by the rows, which one workgroup reads at 0.15 TB/s: one query over 14,000 unit vectors of 768
-// values, nearly all of them wanted, 978 us with settle_kernel alone, 166 so; 128 queries 2345, 1736.
+// values, nearly all of them wanted, 978 us with settle_kernel alone, 103 so; 33 queries 1703, 483.
 constexpr int kFewRowsThreads = 256;
 __global__ __launch_bounds__(kFewRowsThreads) void few_rows_kernel(const FewArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
