@@ -72,6 +72,12 @@ struct Tier { int threads; size_t lds; bool needs_6_waves; bool short_codes_only
 constexpr Tier kTiers[] = {{256, 40960, false, false}, {512, 53760, true, false}, {768, 81920, true, true},
                            {512, 81920, false, false}, {1024, kLdsBytes, false, false}};
 
+// Thresholds that count on the remaining table minima (and list summaries) rest on an error
+// bound of 2 * (table additions) * 2^-24 <= 3.1e-5 (see abandon_threshold): at most 256
+// additions per table sum (4-bit codes: two a byte), and the whole table resident.  The 80-register
+// instances have them compiled in.
+bool rest_holds(int P, int M, int row_bytes) { return P == 1 && M * (row_bytes == (int)kByteRow<true> ? 2 : 1) <= 256; }
+
 // One attempt: table phases P, a footprint tier, a span; need_poss: only layouts with a possibles
 // list (a cruise) count.
 bool fit_plan(int d, int M, int row_bytes, int nsegs, int cap, int batch, int k, bool range, int P,
@@ -89,6 +95,8 @@ bool fit_plan(int d, int M, int row_bytes, int nsegs, int cap, int batch, int k,
     const int ncnt = nbucket > nbatch ? nbucket : nbatch;
     // (4-bit codes: 8 KB in front of the table for the pair table of the first filter pass)
     const size_t tab = (size_t)Mp * row_bytes + (row_bytes == (int)kByteRow<true> ? 8 * kC * 4 : 0);
+    const bool rest_ok = rest_holds(P, M, row_bytes);
+    if (tier.needs_6_waves && !rest_ok) return false;
     const bool can_cruise = cruise > 0 && P == 1;  // table phases need block-wide barriers
     if (need_poss && !can_cruise) return false;
     const int nwaves = tier.threads / 64;
@@ -147,7 +155,8 @@ bool fit_plan(int d, int M, int row_bytes, int nsegs, int cap, int batch, int k,
         pl->threads = tier.threads;
         // the 80-register instance: needed for three workgroups per CU, and the better one for short
         // codes in any case (the other's bulk rounds and deeper refine pipelines pay from 64 code bytes on)
-        pl->lean = !(P == 1 && M <= 256 && (tier.needs_6_waves || M < 64)) ? kFullInstance
+        pl->use_rest = rest_ok;
+        pl->lean = !(rest_ok && (tier.needs_6_waves || M < 64)) ? kFullInstance
                    : d <= 128 ? kLeanShortRows : kLeanLongRows;
         pl->wqcap = wqcap;
         pl->cruise = p > 0 ? cruise : 0;
@@ -294,10 +303,7 @@ void fill_common(SearchArgs &a, const trim_index_view *ix, const float *queries,
     a.bucket_inv = pl.bucket > 1 ? (uint32_t)(((uint64_t(1) << 32) + pl.bucket - 1) / pl.bucket) : 0;      // (stretches have buckets of 60 and more)
     a.small_addr = ix->n < (int64_t(1) << 24) && ix->n * (int64_t)ix->M < (int64_t(1) << 32) &&
                    ix->M < (1 << 24);
-    // Thresholds that count on the remaining table minima (and list summaries) rest on an error
-    // bound of 2 * (table additions) * 2^-24 <= 3.1e-5 (see abandon_threshold): at most 256
-    // additions per table sum, and the whole table resident.
-    a.use_rest = pl.P == 1 && ix->M <= 256;
+    a.use_rest = pl.use_rest;
 }
 
 int fill_u32(uint32_t *p, size_t count, uint32_t v, hipStream_t st) {

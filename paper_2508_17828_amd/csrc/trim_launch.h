@@ -20,6 +20,7 @@ struct Plan {
     uint32_t off_q, off_segp, off_segd, off_rest, off_seglb, off_spos, off_sd2, off_sidx, off_rd2, off_rid, off_ctl;
     uint32_t off_plb, off_cnt, off_wq;
     int span, wqcap, cruise, poss_cap, scap, rcap, bucket;
+    int use_rest;    // see rest_holds
     int lean;    // a LeanKind; kNN, up to 128 results: launch an 80-register instance (six waves per SIMD, or short codes)
 };
 

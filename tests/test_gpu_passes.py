@@ -791,3 +791,21 @@ def test_codes_that_are_no_multiple_of_eight(T, d, M, k, batch, nlist):
     ref = trim_oracle.search_knn(oix, c(q[rows]), k, 0.3, batch, c(probes[rows]) if nlist else None)
     for name in ("ids", "d2", "n_scanned", "n_exact"):
         np.testing.assert_array_equal(c(got[name])[rows], ref[name], err_msg=name)
+
+
+# The thresholds that count on remaining table minima, and the list summaries, hold for up to 256 additions per table sum: searches over
+# longer 4-bit codes go without (nothing is passed over), also where three workgroups would fit a CU; 128 code bytes are the most with them.
+@pytest.mark.parametrize("d,M,with_them", ((256, 256, True), (272, 272, False), (320, 320, False), (672, 336, False)))
+@pytest.mark.parametrize("k,batch", ((10, 256), (100, 256)))
+def test_thresholds_of_long_4_bit_codes(T, d, M, with_them, k, batch):
+    from oracle import trim_oracle_fs
+    ix, q, probes = built(T, 30000, d, M, 4, 40, 600, 32, 3.0, 0.0, d + k)
+    got = T.trim_search_knn(ix, q, k, 0.3, batch, probes=probes, want_work=True)
+    skipped = got["work"][:, T.WORK_NAMES.index("skipped")].cpu().numpy()
+    assert (skipped.max() > 0) == with_them
+    c = lambda t: t.cpu().numpy()
+    oix = trim_oracle_fs.Index(c(ix.base), c(ix.codes), c(ix.dlx), c(ix.codebooks), ids=c(ix.ids), list_offsets=c(ix.list_offsets))
+    rows = slice(8, 24)                      # (those before it probe lists that are not there)
+    ref = trim_oracle_fs.search_knn(oix, c(q[rows]), k, 0.3, batch, c(probes[rows]))
+    for name in ("ids", "d2", "n_scanned", "n_exact"):
+        np.testing.assert_array_equal(c(got[name])[rows], ref[name], err_msg=name)
