@@ -1195,51 +1195,62 @@ __global__ __launch_bounds__(1024) void invert_place_kernel(const InvertArgs a) 
 }
 
 // ---- a threshold for the rest before the first batch is measured (kNN) ----
-// The first batch is dealt into k groups; the least bound of each and its exact distance: the larger of the two, over all groups, is no
-// less than the k-th distance tau that the first batch will leave.  (Either all of these k survive the seed's threshold and are in the
-// running, or one does not, and its bound exceeds that threshold, which exceeds tau.)  What is marked against it contains what
-// tau would mark, so that the rows of the first batch and of the next pass are measured together and read once: 2,500 queries x
-// 500,000 x 768, measure 690 us in two launches -> 419, this kernel 33, replay 342 -> 309 (one launch), the search 2058 -> 1770.
-// One workgroup per query, a half wave per group.  A distance or bound that is no number makes it infinite.
+// The first batch is dealt into kPicks groups; the vector of least bound of each has its exact distance taken, and of the larger of the
+// two, over the groups, the k-th least is no less than the k-th distance tau that the first batch will leave.  (Either all of these k survive the
+// seed's threshold and are in the running, or the bound of one exceeds that threshold, which is no less than tau.)
+// What is marked against it contains what tau would mark, so that the rows of the first batch and of the next pass are measured
+// together and read once.  128 groups, k = 10: a bound of the rest lies below it for 0.365 of them where tau has 0.317 (unit vectors of 768 values,
+// gamma 0.27, first batches of 1024; 10 groups 0.825, 64 0.405, 256 0.334), and elsewhere as often as below tau.  Bound by the rows, which
+// neighbouring queries share: 2,000 queries over 100,000 x 1536, 80 us for the 118 groups beyond the first ten.
+// One workgroup per query, half waves take the groups two at a time.  A candidate whose bound is no number never passes a threshold and is
+// left out; a group without a finite bound, and a pick whose distance is no number, count as infinite.
 __global__ __launch_bounds__(kReplayThreads) void pick_kernel(const ReplayArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     int *segp = reinterpret_cast<int *>(smem + a.off_segp), *segd = reinterpret_cast<int *>(smem + a.off_segd);
     float *q_lds = reinterpret_cast<float *>(smem + a.off_q);
-    __shared__ uint32_t s_most;
-    const int tid = threadIdx.x, lane32 = tid & 31;
+    __shared__ unsigned long long s_pick[kPicks];      // {bound, place}, least of its group
+    __shared__ float s_val[kPicks];
+    const int tid = threadIdx.x, half = tid >> 5, lane32 = tid & 31;
     const int64_t per_xcd = gridDim.x / kXcds, row = (int64_t)(blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
     if (row >= a.nslots) return;
     const int64_t q = a.order ? a.order[a.slot0 + row] : a.slot0 + row;
     if (q < 0 || q >= a.nq) return;
     const int total = a.totals[row], end = total < a.mid ? total : a.mid;
-    if (tid == 0) s_most = end - a.k < a.k ? 0x7f800000u : 0u;      // (fewer than k: infinite)
+    for (int j = tid; j < kPicks; j += kReplayThreads) s_pick[j] = ~0ull;
     for (int t = tid; t < a.d; t += kReplayThreads) q_lds[t] = a.queries[(size_t)q * a.d + t];
     segment_table_ready(a.seg, a.nseg, a.n, a.max_cand, row, segp, segd);
     const float *g = a.g + (size_t)row * a.words * 32;
-    if (end - a.k >= a.k)
-        for (int j = tid >> 5; j < a.k; j += kReplayThreads / 32) {
-            float least = __builtin_inff();
-            int at = 0x7fffffff;
-            for (int i = a.k + j + lane32 * a.k; i < end; i += 32 * a.k) {
-                const float v = g[i];
-                if (v < least) { least = v; at = i; }
-            }
-#pragma unroll
-            for (int off = 16; off > 0; off >>= 1) {
-                const float v = __shfl_xor(least, off);
-                const int o = __shfl_xor(at, off);
-                if (v < least || (v == least && o < at)) { least = v; at = o; }
-            }
-            float d2 = __builtin_inff();
-            if (at < end) {
-                const int pos = segment_position(at, segp, segd, a.nseg);
-                d2 = exact_d2_half(a.base + (size_t)pos * a.d, q_lds, a.d, lane32);
-                d2 = d2 <= __builtin_inff() ? __builtin_fmaxf(d2, least) : __builtin_inff();
-            }
-            if (lane32 == 0) atomicMax(&s_most, __float_as_uint(d2));
-        }
+    static_assert(kReplayThreads % kPicks == 0, "a thread's candidates are of one group");
+    unsigned long long best = ~0ull;
+    for (int i = a.k + tid; i < end; i += kReplayThreads) {
+        const float v = g[i];
+        const unsigned long long key = ((unsigned long long)__float_as_uint(v) << 32) | (uint32_t)i;
+        if (v < __builtin_inff() && key < best) best = key;
+    }
+    if (best != ~0ull) atomicMin(&s_pick[tid % kPicks], best);
     sync_block();
-    if (tid == 0) a.out_d2[(size_t)q * a.k + a.k - 1] = __uint_as_float(s_most);
+    for (int j = 2 * half; j < kPicks; j += kReplayThreads / 32 * 2) {
+        const unsigned long long p0 = s_pick[j], p1 = s_pick[j + 1];
+        const int c0 = p0 != ~0ull ? (int)(uint32_t)p0 : 0, c1 = p1 != ~0ull ? (int)(uint32_t)p1 : c0;
+        float d2[2] = {__builtin_inff(), __builtin_inff()};
+        if (p0 != ~0ull || p1 != ~0ull)
+            exact_d2_half_x2_deep<4>(a.base + (size_t)segment_position(p0 != ~0ull ? c0 : c1, segp, segd, a.nseg) * a.d,
+                                     a.base + (size_t)segment_position(c1, segp, segd, a.nseg) * a.d, q_lds, a.d, lane32, d2);
+        if (lane32 == 0) {
+            auto larger = [](unsigned long long p, float d) {
+                return p != ~0ull && d <= __builtin_inff() ? __builtin_fmaxf(d, __uint_as_float((uint32_t)(p >> 32))) : __builtin_inff();
+            };
+            s_val[j] = larger(p0, d2[0]);
+            s_val[j + 1] = larger(p1, d2[1]);
+        }
+    }
+    sync_block();
+    if (tid < kPicks) {
+        const float v = s_val[tid];
+        int before = 0;
+        for (int j = 0; j < kPicks; ++j) before += s_val[j] < v || (s_val[j] == v && j < tid);
+        if (before == a.k - 1) a.out_d2[(size_t)q * a.k + a.k - 1] = v;
+    }
 }
 
 // ---- replay (kNN) ----

@@ -176,7 +176,7 @@ struct ReplayArgs {
     int32_t *counts;
     uint32_t off_segp, off_segd, off_cl, off_g, off_d2, off_id, off_rd2, off_rid, off_q, off_key, off_todo;
 };
-constexpr int kPickMost = 128, kPickGroup = 4;    // pick_kernel: most results, least vectors of the first batch per result
+constexpr int kPicks = 128, kPickMost = 12, kPickBatch = 1024;    // pick_kernel: vectors taken, most results, largest batch
 constexpr int kReplayThreads = 512, kReplayCap = 2048;   // (a power of two)
 
 // ---- few queries (trim_few.h) ----
