@@ -1195,53 +1195,99 @@ __global__ __launch_bounds__(1024) void invert_place_kernel(const InvertArgs a) 
 }
 
 // ---- a threshold for the rest before the first batch is measured (kNN) ----
-// The first batch is dealt into kPicks groups; the vector of least bound of each has its exact distance taken, and of the larger of the
-// two, over the groups, the k-th least is no less than the k-th distance tau that the first batch will leave.  (Either all of these k survive the
-// seed's threshold and are in the running, or the bound of one exceeds that threshold, which is no less than tau.)
+// The kPicks vectors of the first batch with the least bounds have their exact distances taken, and of the larger of the
+// two, over the picks, the k-th least is no less than the k-th distance tau that the first batch will leave.  (Either all of these k survive the
+// seed's threshold and are in the running, or the bound of one exceeds that threshold, which is no less than tau.)  Any choice of picks will do
+// for that: which of the same bin of the histogram are taken is left to chance.
 // What is marked against it contains what tau would mark, so that the rows of the first batch and of the next pass are measured
-// together and read once.  128 groups, k = 10: a bound of the rest lies below it for 0.365 of them where tau has 0.317 (unit vectors of 768 values,
-// gamma 0.27, first batches of 1024; 10 groups 0.825, 64 0.405, 256 0.334), and elsewhere as often as below tau.  Bound by the rows, which
-// neighbouring queries share: 2,000 queries over 100,000 x 1536, 80 us for the 118 groups beyond the first ten.
-// One workgroup per query, half waves take the groups two at a time.  A candidate whose bound is no number never passes a threshold and is
-// left out; a group without a finite bound, and a pick whose distance is no number, count as infinite.
+// together and read once.  64 picks, k = 10: a bound of the rest lies below it for 0.372 of them where tau has 0.317 (unit vectors of 768 values,
+// gamma 0.27, first batches of 1024; 10 picks 0.79, 128 0.337, 64 and 128 groups' least 0.405 and 0.365), and elsewhere as often as below tau.
+// Bound by the rows, which neighbouring queries share: 2,500 queries over 500,000 x 768, 118 more of them cost 90 us.
+// One workgroup per query.  A candidate whose bound is no number never passes a threshold and is left out, like an infinite one; a pick whose
+// distance is no number counts as infinite, and so does what is missing where there are fewer than kPicks.
 __global__ __launch_bounds__(kReplayThreads) void pick_kernel(const ReplayArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     int *segp = reinterpret_cast<int *>(smem + a.off_segp), *segd = reinterpret_cast<int *>(smem + a.off_segd);
     float *q_lds = reinterpret_cast<float *>(smem + a.off_q);
-    __shared__ unsigned long long s_pick[kPicks];      // {bound, place}, least of its group
-    __shared__ float s_val[kPicks];
+    __shared__ int hist[256], s_at[kPicks], s_n, s_bin;
+    __shared__ uint32_t s_low, s_high;
+    __shared__ float s_bound[kPicks], s_val[kPicks];
     const int tid = threadIdx.x, half = tid >> 5, lane32 = tid & 31;
     const int64_t per_xcd = gridDim.x / kXcds, row = (int64_t)(blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
     if (row >= a.nslots) return;
     const int64_t q = a.order ? a.order[a.slot0 + row] : a.slot0 + row;
     if (q < 0 || q >= a.nq) return;
     const int total = a.totals[row], end = total < a.mid ? total : a.mid;
-    for (int j = tid; j < kPicks; j += kReplayThreads) s_pick[j] = ~0ull;
-    for (int t = tid; t < a.d; t += kReplayThreads) q_lds[t] = a.queries[(size_t)q * a.d + t];
-    segment_table_ready(a.seg, a.nseg, a.n, a.max_cand, row, segp, segd);
+    constexpr int kHeld = kPickBatch / kReplayThreads;
+    static_assert(kPickBatch % kReplayThreads == 0 && kPicks <= kReplayThreads, "the first batch in registers");
+    uint32_t key[kHeld];                 // (bounds are not negative: they order as their bits)
     const float *g = a.g + (size_t)row * a.words * 32;
-    static_assert(kReplayThreads % kPicks == 0, "a thread's candidates are of one group");
-    unsigned long long best = ~0ull;
-    for (int i = a.k + tid; i < end; i += kReplayThreads) {
-        const float v = g[i];
-        const unsigned long long key = ((unsigned long long)__float_as_uint(v) << 32) | (uint32_t)i;
-        if (v < __builtin_inff() && key < best) best = key;
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u) {
+        const int i = a.k + u * kReplayThreads + tid;
+        const float v = i < end ? g[i] : __builtin_inff();
+        key[u] = v < __builtin_inff() ? __float_as_uint(v) : ~0u;
     }
-    if (best != ~0ull) atomicMin(&s_pick[tid % kPicks], best);
+    for (int t = tid; t < a.d; t += kReplayThreads) q_lds[t] = a.queries[(size_t)q * a.d + t];
+    if (tid < 256) hist[tid] = 0;
+    if (tid < kPicks) { s_at[tid] = -1; s_val[tid] = __builtin_inff(); }
+    if (tid == 0) { s_low = ~0u; s_high = 0; s_n = 0; }
+    segment_table_ready(a.seg, a.nseg, a.n, a.max_cand, row, segp, segd);
+    uint32_t low = ~0u, high = 0;
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u)
+        if (key[u] != ~0u) { low = min(low, key[u]); high = max(high, key[u]); }
+    wave_max(&s_high, high);
+    if (low != ~0u) atomicMin(&s_low, low);
     sync_block();
-    for (int j = 2 * half; j < kPicks; j += kReplayThreads / 32 * 2) {
-        const unsigned long long p0 = s_pick[j], p1 = s_pick[j + 1];
-        const int c0 = p0 != ~0ull ? (int)(uint32_t)p0 : 0, c1 = p1 != ~0ull ? (int)(uint32_t)p1 : c0;
-        float d2[2] = {__builtin_inff(), __builtin_inff()};
-        if (p0 != ~0ull || p1 != ~0ull)
-            exact_d2_half_x2_deep<4>(a.base + (size_t)segment_position(p0 != ~0ull ? c0 : c1, segp, segd, a.nseg) * a.d,
-                                     a.base + (size_t)segment_position(c1, segp, segd, a.nseg) * a.d, q_lds, a.d, lane32, d2);
+    const uint32_t base = s_low, width = s_high > base ? s_high - base : 1u;
+    const int shift = max(0, 24 - (int)__clz(width));       // 256 bins
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u)
+        if (key[u] != ~0u) atomicAdd(&hist[(key[u] - base) >> shift], 1);
+    sync_block();
+    if (tid < kWave) {                   // the bin that the kPicks-th least is in
+        int c[4], sum = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { c[e] = hist[4 * tid + e]; sum += c[e]; }
+        int incl = sum;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int v = __shfl_up(incl, off);
+            if (tid >= off) incl += v;
+        }
+        int run = incl - sum;
+        if (tid == kWave - 1 && incl < kPicks) s_bin = 255;          // (all of them)
+        if (run < kPicks && incl >= kPicks) {
+            int b = 4 * tid;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { run += c[e]; if (run < kPicks) ++b; }
+            s_bin = b;
+        }
+    }
+    sync_block();
+    const int bin = s_bin;
+#pragma unroll
+    for (int turn = 0; turn < 2; ++turn) {
+#pragma unroll
+        for (int u = 0; u < kHeld; ++u) {
+            if (key[u] == ~0u) continue;
+            const int mine = (int)((key[u] - base) >> shift);
+            if (turn == 0 ? mine >= bin : mine != bin) continue;
+            const int at = atomicAdd(&s_n, 1);
+            if (at < kPicks) { s_at[at] = a.k + u * kReplayThreads + tid; s_bound[at] = __uint_as_float(key[u]); }
+        }
+        sync_block();
+    }
+    const int n = min(s_n, kPicks);
+    for (int j = half; j < n; j += kReplayThreads / 32 * 2) {
+        const int j1 = j + kReplayThreads / 32;
+        float d2[2];
+        exact_d2_half_x2_deep<4>(a.base + (size_t)segment_position(s_at[j], segp, segd, a.nseg) * a.d,
+                                 a.base + (size_t)segment_position(s_at[j1 < n ? j1 : j], segp, segd, a.nseg) * a.d, q_lds, a.d, lane32, d2);
         if (lane32 == 0) {
-            auto larger = [](unsigned long long p, float d) {
-                return p != ~0ull && d <= __builtin_inff() ? __builtin_fmaxf(d, __uint_as_float((uint32_t)(p >> 32))) : __builtin_inff();
-            };
-            s_val[j] = larger(p0, d2[0]);
-            s_val[j + 1] = larger(p1, d2[1]);
+            s_val[j] = d2[0] <= __builtin_inff() ? __builtin_fmaxf(d2[0], s_bound[j]) : __builtin_inff();
+            if (j1 < n) s_val[j1] = d2[1] <= __builtin_inff() ? __builtin_fmaxf(d2[1], s_bound[j1]) : __builtin_inff();
         }
     }
     sync_block();

@@ -176,7 +176,8 @@ struct ReplayArgs {
     int32_t *counts;
     uint32_t off_segp, off_segd, off_cl, off_g, off_d2, off_id, off_rd2, off_rid, off_q, off_key, off_todo;
 };
-constexpr int kPicks = 128, kPickMost = 12, kPickBatch = 1024;    // pick_kernel: vectors taken, most results, largest batch
+constexpr int kPicks = 64, kPickMost = 10, kPickBatch = 1024, kPickVectors = 96;    // pick_kernel: vectors taken, most results, largest batch, least
+                                                                                     // vectors of the index per query
 constexpr int kReplayThreads = 512, kReplayCap = 2048;   // (a power of two)
 
 // ---- few queries (trim_few.h) ----

@@ -118,35 +118,35 @@ def test_first_batch_with_the_next_pass(T, k, batch):
     test_passes_equal_the_single_kernel(T, (16000, 768, 96, 8, 20, 280, 9, k, batch, 0.4, 0.3, 0.0))
 
 
-# pick_kernel at the edges of its rule: results, largest batch, picks in all no more than vectors (33,280 = 260 * 128) and one query
-# more; batches of fewer vectors than groups and than results; candidates cut before every group has one, and inside the first batch
-@pytest.mark.parametrize("k,batch,nq,cut", ((1, 1, 260, 0), (12, 5, 260, 0), (12, 512, 260, 0), (13, 512, 260, 0), (3, 127, 260, 0), (10, 1024, 260, 0),
-                                            (10, 1025, 260, 0), (10, 1024, 261, 0), (10, 600, 260, 1034), (10, 600, 260, 611), (12, 1024, 260, 90),
-                                            (12, 512, 260, 23)))
+# pick_kernel at the edges of its rule: results, largest batch, 96 vectors a query (24,960 = 260 * 96) and one query more; batches of fewer
+# vectors than picks and than results; candidates cut before there are as many as picks, and inside the first batch
+@pytest.mark.parametrize("k,batch,nq,cut", ((1, 1, 260, 0), (10, 5, 260, 0), (10, 512, 260, 0), (11, 512, 260, 0), (3, 63, 260, 0), (3, 64, 260, 0),
+                                            (10, 1024, 260, 0), (10, 1025, 260, 0), (10, 1024, 261, 0), (10, 600, 260, 1034), (10, 600, 260, 611),
+                                            (10, 1024, 260, 70), (9, 512, 260, 23)))
 def test_picked_threshold(T, k, batch, nq, cut, monkeypatch):
     if cut:
         plain = T.Index._cand
         monkeypatch.setattr(T.Index, "_cand", lambda self, p, max_candidates=0: plain(self, p, cut))
     for spread, gamma in ((0.3, 0.3), (0.05, 0.1)):
-        test_passes_equal_the_single_kernel(T, (33280, 512, 64, 8, 20, nq, 9, k, batch, gamma, spread, 0.0))
+        test_passes_equal_the_single_kernel(T, (24960, 512, 64, 8, 20, nq, 9, k, batch, gamma, spread, 0.0))
 
 
 @pytest.mark.parametrize("what", ("landmark distances", "rows", "queries", "centroids", "table"))
 def test_picked_threshold_with_values_that_are_no_numbers(T, what):
-    ix, q, probes = built(T, 33280, 512, 128, 8, 12, 260, 7, 0.5, 0.0, 11)
+    ix, q, probes = built(T, 24960, 512, 128, 8, 12, 260, 7, 0.5, 0.0, 11)
     ix.list_bounds = None
     table = T.trim_build_lut(q, ix.codebooks) if what == "table" else None
     plant(what, ix, q, table)
     for l in range(12):                       # in the first candidates of every list, whichever comes first
         at = int(ix.list_offsets[l])
-        if what == "rows" and at + 400 < 33280:
+        if what == "rows" and at + 400 < 24960:
             ix.base[at + 20:at + 400:37, 3] = float("nan")
             ix.base[at + 25:at + 400:41, 3] = float("inf")
-        if what == "landmark distances" and at + 400 < 33280:
+        if what == "landmark distances" and at + 400 < 24960:
             ix.dlx[at + 20:at + 400:37] = float("nan")
             ix.dlx[at + 25:at + 400:41] = float("inf")
     ix.scan_head = T.trim_pack_scan_head(ix.codes, ix.dlx)
-    for k, batch in ((1, 20), (1, 512), (12, 1024)):
+    for k, batch in ((1, 20), (1, 512), (10, 1024)):
         want = single_kernel(T, ix, q, k, 0.4, batch, probes, None, table)
         got = T.trim_search_knn(ix, q, k, 0.4, batch, probes=probes, lut=table, want_mask=True)
         for name in ("ids", "d2", "n_scanned", "n_exact", "mask"):
