@@ -59,6 +59,8 @@ constexpr int kMaxBatchesPerSpan = 1024;
 constexpr int kPossMin = 512;    // smallest possibles list worth cruising with
 constexpr int kPossMax = 2048;
 constexpr int64_t kCus = 256;
+constexpr double kOneGoScan = 16384.0;
+constexpr int kOneGoBatch = 128;
 
 // Block size and LDS bytes per workgroup for 4, 3, 2 and 1 workgroups per CU (LDS is handed
 // out in 1280-byte granules).  Three 512-thread workgroups, or two of 768 threads, are 6 waves
@@ -169,8 +171,9 @@ bool fit_plan(int d, int M, int row_bytes, int nsegs, int cap, int batch, int k,
     return false;
 }
 
-// M counts code bytes; fs: 4-bit codes (two subspaces of 16 centroids per byte), else 8-bit.
-bool make_plan(int d, int M, bool fs, int nseg, int cap, int batch, int k, bool range, int64_t nq, Plan *pl) {
+// M counts code bytes; fs: 4-bit codes (two subspaces of 16 centroids per byte), else 8-bit.  scanned: candidates of a query, lists as long
+// as each other.
+bool make_plan(int d, int M, bool fs, int nseg, int cap, int batch, int k, bool range, int64_t nq, double scanned, Plan *pl) {
     if (d <= 0 || M <= 0 || d % 4 || M % 4) return false;
     if (fs ? (d % (2 * M) || M % 8 || d / (2 * M) > 64) : (d % M || d / M > 64)) return false;
     const int row_bytes = fs ? (int)kByteRow<true> : (int)kByteRow<false>;
@@ -195,9 +198,14 @@ bool make_plan(int d, int M, bool fs, int nseg, int cap, int batch, int k, bool 
             // for six waves per SIMD do better as three 512-thread ones (24 waves), which also have twice the threads for
             // a query where all are resident at once.  32 of 1024 lists: 1.18M x 100, M = 20, k = 10: 600 queries 333 -> 230 us, 1000 230 ->
             // 229, 8000 2266 -> 1841, k = 100: 200 351 -> 159, 700 404 -> 276, 1000 336 -> 293; M = 16, k = 100, 1000 228 -> 196, 4000 510 ->
-            // 462; 4-bit codes, k = 100, 700 260 -> 210, 3000 650 -> 586, 8000 1363 -> 1279.  But not for shorter 8-bit codes and k up to 64
-            // between 768 and 1024 queries, which four a CU take in one go (M = 8, 900 queries 104 / 121; M = 16, 800 124 / 127).
-            const bool one_go = !fs && M <= 16 && result_slots(k) == 1 && nq > 3 * kCus && nq <= 4 * kCus;
+            // 462; 4-bit codes, k = 100, 700 260 -> 210, 3000 650 -> 586, 8000 1363 -> 1279.  But not with 8-bit codes
+            // between 768 and 1024 queries, which four a CU take in one go, where there is little to scan (three a CU / four, M = 20, 900
+            // queries, 7 of 275 lists of 47,000: k = 1 124 / 98, 10 103 / 83, 50 126 / 95, 100 112 / 89; 20 of 640 of 400,000, gamma 0.5, 1024: k = 10 131 /
+            // 119, 64 202 / 157, 100 152 / 158; 20 of 900 of 800,000, 775, gamma 0.1: k = 10 157 / 183, 100 180 / 197), batches are short (of 128, k = 64:
+            // those 800,000 238 / 216, 30,000 without lists 505 / 403) or codes are shorter and k up to 64 (M = 8, 900 queries 121 / 104; M = 16, 800
+            // 127 / 124).
+            const bool one_go = !fs && nq > 3 * kCus && nq <= 4 * kCus &&
+                                (scanned <= kOneGoScan || batch <= kOneGoBatch || (M <= 16 && result_slots(k) == 1));
             if (t == 0 && !range && result_slots(k) <= 2 && !one_go) continue;
             if (t + 1 < nt) {
                 // below the last tier a layout must leave room for a cruise when one is possible
@@ -245,6 +253,11 @@ int launch_search(bool range, bool fs, const SearchArgs &a, const Plan &pl, dim3
 // 4-bit codes (two per byte, 16 centroids per subspace)?  Bytes of one stored code.
 inline bool is_fs(const trim_index_view *ix) { return ix->code_bits == 4; }
 inline int code_bytes(const trim_index_view *ix) { return is_fs(ix) ? ix->M / 2 : ix->M; }
+
+// A query's share of the base set, lists as long as each other.
+inline double scanned_per_query(const trim_index_view *ix, const trim_candidates *cand) {
+    return cand ? (double)ix->n * std::min(1.0, (double)cand->nprobe / cand->nlist) : (double)ix->n;
+}
 
 int check_index(const trim_index_view *ix) {
     if (!ix) return TRIM_INVALID_ARG;
@@ -1072,9 +1085,7 @@ FewLayout few_layout(const trim_index_view *ix, int64_t nq, const trim_candidate
     FewLayout L{};
     const int64_t mc = cand ? std::min<int64_t>(cand->max_candidates, (int64_t)cand->nprobe * ix->n) : ix->n;
     if (nq <= 0 || nq > (k > kWave && ix->d < kLongRow ? kFewQueriesWide : kFewQueries) || mc <= 0 || k + batch > kSettleFirst || k < 1 || batch < 1) return L;
-    // (a query's share of the base set, lists as long as each other)
-    const double scanned = cand ? (double)ix->n * std::min(1.0, (double)cand->nprobe / cand->nlist) : (double)ix->n;
-    const double lookups = (double)nq * scanned * ix->M;
+    const double lookups = (double)nq * scanned_per_query(ix, cand) * ix->M;
     const bool fits = nq == 1 || !(lookups > kFewLookups * ix->d || (ix->d < kLongRow && lookups > kFewShortRows) || (!cand && lookups > kFewNoLists));
     const bool passes = ix->d >= kLongRow && mc > (int64_t)k + batch;
     if (!fits && !(passes && lookups <= few_pass_lookups(ix->n, k, cand != nullptr))) return L;
@@ -1156,7 +1167,7 @@ int search_knn(const trim_index_view *index, const float *queries, int64_t nq, c
     if (survivor_mask && mask_words <= 0) return TRIM_INVALID_ARG;
     Plan pl;
     const int cap = batch > k ? batch : k;
-    if (!make_plan(index->d, code_bytes(index), is_fs(index), cand ? cand->nprobe : 0, cap, batch, k, false, nq, &pl))
+    if (!make_plan(index->d, code_bytes(index), is_fs(index), cand ? cand->nprobe : 0, cap, batch, k, false, nq, scanned_per_query(index, cand), &pl))
         return TRIM_UNSUPPORTED_SHAPE;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (survivor_mask && (rc = fill_u32(survivor_mask, (size_t)nq * mask_words, 0u, st))) return rc;
@@ -1241,7 +1252,7 @@ int range_search(const trim_index_view *index, const float *queries, int64_t nq,
     if (!workspace || workspace_bytes < L.total || (reinterpret_cast<uintptr_t>(workspace) & 255u))
         return TRIM_WORKSPACE;
     Plan pl;
-    if (!make_plan(index->d, code_bytes(index), is_fs(index), cand ? cand->nprobe : 0, kRangeRound, kRangeRound, 1, true, nq, &pl))
+    if (!make_plan(index->d, code_bytes(index), is_fs(index), cand ? cand->nprobe : 0, kRangeRound, kRangeRound, 1, true, nq, 0.0, &pl))
         return TRIM_UNSUPPORTED_SHAPE;
 
     unsigned char *ws = static_cast<unsigned char *>(workspace);
@@ -1424,13 +1435,13 @@ extern "C" {
 int trim_shape_supported(int32_t d, int32_t M) {
     Plan pl;
     if (d <= 0 || M <= 0 || d % M) return 0;
-    return make_plan(d, M, false, 64, 2048, 2048, 10, true, 1, &pl) ? 1 : 0;
+    return make_plan(d, M, false, 64, 2048, 2048, 10, true, 1, 0.0, &pl) ? 1 : 0;
 }
 
 int trim_fs_shape_supported(int32_t d, int32_t M) {
     Plan pl;
     if (d <= 0 || M <= 0 || M % 2 || d % M) return 0;
-    return make_plan(d, M / 2, true, 64, 2048, 2048, 10, true, 1, &pl) ? 1 : 0;
+    return make_plan(d, M / 2, true, 64, 2048, 2048, 10, true, 1, 0.0, &pl) ? 1 : 0;
 }
 
 int trim_encode(const float *base, int64_t n, int32_t d, const float *codebooks, int32_t M,

@@ -811,6 +811,18 @@ def test_answers_do_not_depend_on_the_number_of_queries(T, d, M, bits, k, batch)
     np.testing.assert_array_equal(c(want["n_exact"][8:28]), ref["n_exact"])
 
 
+# 769 to 1024 queries over short codes: four workgroups a CU up to 16,384 candidates or batches of 128, three beyond
+@pytest.mark.parametrize("n", (16384, 16385))
+@pytest.mark.parametrize("k,batch", ((10, 128), (10, 129), (100, 128), (100, 512)))
+def test_queries_that_fit_in_one_go(T, n, k, batch):
+    ix, q, _ = built(T, n, 100, 20, 8, 0, 1024, 0, 1.0, 2.0, k)
+    want = single_kernel(T, ix, q[:20].contiguous(), k, 0.3, batch, None, None)
+    for nq in (769, 1024):
+        got = single_kernel(T, ix, q[:nq].contiguous(), k, 0.3, batch, None, None)
+        for name in ("ids", "d2", "n_scanned", "n_exact", "mask"):
+            np.testing.assert_array_equal(got[name].cpu().numpy()[:20], want[name].cpu().numpy(), err_msg=f"{name} {nq}")
+
+
 # codes of 16 bytes and more that are no multiple of 8: 16-byte pieces at multiples of 4, what is left of a code (4, 8, 12 bytes), table
 # phases, the list summaries without a scan head; one to sixteen result entries per lane
 @pytest.mark.parametrize("d,M", ((80, 20), (112, 28), (132, 44), (240, 60), (720, 180)))
