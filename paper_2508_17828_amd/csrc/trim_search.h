@@ -5,6 +5,8 @@
 // survivors, and the results.
 #pragma once
 
+#include <type_traits>
+
 #include "trim_device.h"
 
 namespace trim {
@@ -85,6 +87,9 @@ struct SearchArgs {
 
 // The kernel's arguments, read again from memory by whoever asks (the compiler cannot know that they are the same): kept from the
 // prologue to where they are used they do not fit the scalar registers, and what the loops want is spilled instead.
+// Not where it costs more vector registers than it saves scalars: the rows' loop of the instances of 128 registers with up to four result
+// entries per lane (spilled 31 -> 18 with 8-bit codes and one entry; 480,000 x 256, M = 64, 320 queries, k = 100: 277 -> 254 us, k = 200 315 ->
+// 292; 400,000 x 512, M = 64, k = 100 2735 -> 2442), the survivors' list of those with sixteen (1,600 searches for 500 results 1 % faster).
 typedef const SearchArgs __attribute__((address_space(4))) ConstantArgs;
 __device__ __forceinline__ ConstantArgs *fresh_args() {
     auto p = (ConstantArgs *)__builtin_amdgcn_kernarg_segment_ptr();
@@ -587,6 +592,11 @@ void search_kernel(const SearchArgs a) {
     // The tiled copy of the codes is read by the instances with 16-byte code loads, except the
     // lean ones, whose codes are short (they read the row-major array).
     constexpr bool kTiledOk = VEC == 4 && !LEAN;
+    constexpr bool kFreshRows = LEAN || MODE == kRange || E > 4, kFreshAppend = E <= 4;    // see fresh_args
+    auto args = [&](auto again) {
+        if constexpr (decltype(again)::value) return fresh_args();
+        else return &a;
+    };
     constexpr int W = VEC == kDwordRows ? 4 : VEC;     // words of the widest load
     constexpr bool kDword = VEC == kDwordRows;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -840,7 +850,7 @@ void search_kernel(const SearchArgs a) {
         basei = __shfl(basei, 0);
         if (live) {
             const int slot = basei + __popcll(m & ((1ull << lane) - 1ull));
-            const auto f = fresh_args();
+            const auto f = args(std::bool_constant<kFreshAppend>{});
             reinterpret_cast<int32_t *>(smem + f->off_spos)[slot] = locate(c);
             if (MODE == kRange) sidx[slot] = c;
             if (f->mask) {
@@ -855,7 +865,7 @@ void search_kernel(const SearchArgs a) {
     // per half wave.  pos_of(i) gives the storage position of entry i; put(i, d2, id or
     // position) stores the result (called by the lane that holds the row's distance).
     auto refine_rows = [&](int ns, auto pos_of, auto put) {
-        const auto f = fresh_args();
+        const auto f = args(std::bool_constant<kFreshRows>{});
         const float *base = in_memory(f->base);
         const int32_t *ids = in_memory(f->ids);
         const float *q_lds = reinterpret_cast<const float *>(smem + f->off_q);
