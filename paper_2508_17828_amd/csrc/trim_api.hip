@@ -1059,19 +1059,21 @@ int launch_probe_ranked(const float *queries, int64_t nq, int d, const float *ce
 //   200,000 x 960, no lists, 1 / 4 queries                                  251 / 164   389 / 220
 //   60,000 x 768, 16 of 256 lists that separate the data, 1 / 33 queries    33 / 39     80 / 89     (hardly anyone is left: two launches more)
 // With fewer values it costs more than it gives: 500,000 x 384, 64 of 1024, 1 / 67 queries 30.7 / 34.7  74.5 / 83.1.
-// With them the lookups may be more, single kernel / this, us:
-//   lists: 300,000 x 1536, 4-bit codes, 60 of 500, 33 / 128 queries 2376 / 569  2477 / 1547; 400,000 x 768, 32 of 256, 90 / 128, gamma 0.5
-//   785 / 553  793 / 694 (gamma 0.1: 6538 / 3913  6800 / 5238): all that 128 queries came to, 3.5e9;
-//   none, x 960: about as the square root of the vectors, where one workgroup per query takes longer.  40,000 vectors, 48 / 67 queries 330 / 303
-//   330 / 391; 200,000, 16 / 22 541 / 385  547 / 576; 500,000, 10 / 16 840 / 775  858 / 827.  With more than 64 results, which hold the
-//   single kernel up more: 40,000, 67 / 90 521 / 545  527 / 681; 200,000, 48 / 67 1750 / 1382  1782 / 2031; 500,000, 22 / 33 2183 / 1859  2184 / 2376.
+// Without lists the lookups may be more then, about as a root of the vectors (one workgroup per query takes longer and longer), and with
+// more than 64 results, which hold the single kernel up more.  Single kernel / this, us, x 960: 40,000 vectors, 48 / 67 queries 330 / 303
+// 330 / 391; 100,000, 22 290 / 311; 200,000, 16 / 22 541 / 385  547 / 576; 500,000, 10 / 16 840 / 775  858 / 827; k = 100: 40,000, 67 / 90
+// 521 / 545  527 / 681; 200,000, 40 1022 / 1750, k = 128, gamma 0.1, 22 / 26 1171 / 1177  1163 / 1340; 400,000 x 768, k = 200, 20 2872 / 3205;
+// k = 300, 200,000, 40 3547 / 2683.  200,000 x 768, k = 10, 20 queries, unit vectors 9143 / 2004, groups far apart 1115 / 286.
+// With lists they may not: the single kernel passes over most of them where they separate the data, whatever their number (400,000 x 768, 150 of 256
+// lists, gamma 0.5, 33 / 128 queries 257 / 425  305 / 1357; 200,000 x 960, 4-bit codes, 64 of 256: 209 / 271  263 / 902), and only vectors that no list
+// separates gain (500,000 x 768, unit vectors, 150 of 256: 1867 / 567  2000 / 1916).
 constexpr int64_t kFewQueries = 128, kFewQueriesWide = 256;
 constexpr double kFewLookups = 500000.0, kFewShortRows = 1.05e8, kFewNoLists = 2.5e8;
 constexpr size_t kFewBytes = size_t(1) << 30;
-double few_pass_lookups(int64_t n, int k, bool lists) {
-    if (lists) return 4e9;
+double few_pass_lookups(int64_t n, int k) {
     const double root = std::sqrt((double)n);
-    return k <= kWave ? 1.05e6 * root : std::min(7000.0 * (double)n, 2.6e6 * root);
+    if (k <= kWave) return std::min(2600.0 * (double)n, 1.05e6 * root);
+    return std::min(7000.0 * (double)n, k <= 2 * kWave ? 8.2e6 * std::cbrt((double)n) : (k <= 4 * kWave ? 1.2e6 : 2.6e6) * root);
 }
 struct FewLayout {
     int64_t stride;           // bounds per query (0: not this way)
@@ -1088,7 +1090,7 @@ FewLayout few_layout(const trim_index_view *ix, int64_t nq, const trim_candidate
     const double lookups = (double)nq * scanned_per_query(ix, cand) * ix->M;
     const bool fits = nq == 1 || !(lookups > kFewLookups * ix->d || (ix->d < kLongRow && lookups > kFewShortRows) || (!cand && lookups > kFewNoLists));
     const bool passes = ix->d >= kLongRow && mc > (int64_t)k + batch;
-    if (!fits && !(passes && lookups <= few_pass_lookups(ix->n, k, cand != nullptr))) return L;
+    if (!fits && !(passes && !cand && lookups <= few_pass_lookups(ix->n, k))) return L;
     const int64_t stride = (mc + 15) / 16 * 16;
     const size_t g_bytes = (size_t)nq * stride * 4;
     if ((size_t)stride > kFewBytes || g_bytes > kFewBytes || mc > 0x40000000 || !few_fits(ix->d, code_bytes(ix), is_fs(ix), k, cand ? cand->nprobe : 0)) return L;
