@@ -39,8 +39,8 @@ int launch_instance(const SearchArgs &a, const Plan &pl, dim3 grid, hipStream_t 
     void (*fn)(const SearchArgs) = nullptr;
     switch (pl.vec) {
         case 4: fn = search_kernel<kMode, 4, kE, ACCT, kFs, kLean>; break;
-        case kDwordRows:
-            if constexpr (kFs) return TRIM_UNSUPPORTED_SHAPE;
+        case kDwordRows:          // (kNN over 8-bit codes: see fit_plan)
+            if constexpr (kFs || kMode == kRange) return TRIM_UNSUPPORTED_SHAPE;
             else fn = search_kernel<kMode, kDwordRows, kE, ACCT, kFs, kLean>;
             break;
         case 2: fn = search_kernel<kMode, 2, kE, ACCT, kFs, kLean>; break;
