@@ -247,11 +247,15 @@ def test_few_queries_over_long_rows(T, case):
         assert torch.equal(ids, want["ids"]) and torch.equal(d2, want["d2"]), size
         assert (ws[size:] == 0xa5).all()
     order = torch.arange(nq, dtype=torch.int32, device="cuda")
-    order[nq - 1] = 0                                    # a query twice
-    want = single_kernel(T, ix, q, k, gamma, batch, probes, order)
-    got = T.trim_search_knn(ix, q, k, gamma, batch, probes=probes, want_mask=True, query_order=order)
+    order[nq - 1], order[nq // 2] = 0, 1                 # queries twice, at other places than their own; two that are not named
+    named = [i for i in range(nq) if i not in (nq - 1, nq // 2)]
+    want = single_kernel(T, ix, q, k, gamma, batch, probes, None)
+    out = (torch.full((nq, k), -7, dtype=torch.int32, device="cuda"), torch.full((nq, k), -7.0, device="cuda"))
+    got = T.trim_search_knn(ix, q, k, gamma, batch, probes=probes, want_mask=True, out=out, query_order=order)
     for name in ("ids", "d2", "n_scanned", "n_exact", "mask"):
-        assert torch.equal(got[name][:-1], want[name][:-1]), name
+        assert torch.equal(got[name][named], want[name][named]), name
+    for t in out:
+        assert (t[nq - 1] == -7).all() and (t[nq // 2] == -7).all()
 
 
 # survivors few and far between, at the ends of the stretches that are looked at together and of their groups of 64; result sets of
