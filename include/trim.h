@@ -334,13 +334,15 @@ int trim_search_knn(const trim_index_view *index, const float *queries, int64_t 
  * passes: the bounds of a stretch of candidates, the exact distances of those that pass (a
  * stored vector is read once for all the queries that want it), the batch rule over them.  The
  * passes keep a bit and two binary32 values per (query, candidate) pair in the work space,
- * query sets being split so that it stays below about 8 GiB.
+ * query sets being split so that it stays below about 8 GiB.  Few queries: one binary32 value per pair, two over vectors of 512 values
+ * and more, of at most 1 GiB each.
  * trim_knn_workspace_bytes: the bytes such a search wants, or 0 where the single kernel of
  * trim_search_knn is the better way (a host function of the sizes in its arguments; of the pointers only whether
  * index->codebooks is given, which many queries in passes need).  A caller's table (lut) of sub-vectors of other than 4, 8 or 16
  * values (2 with 4-bit codes) keeps many queries on the single kernel: ask without codebooks to learn what is used then.
- * workspace: device, 256-byte aligned, contents on entry ignored; NULL or fewer bytes than that:
- * exactly trim_search_knn.  A search that keeps the work counters (trim_stats.work) runs as the
+ * workspace: device, 256-byte aligned, contents on entry ignored; NULL or too few bytes for any of these ways:
+ * exactly trim_search_knn.  (Fewer bytes than wanted serve for few queries over long vectors where one value per pair fits: the same
+ * results, with one workgroup per query for the exact distances.)  A search that keeps the work counters (trim_stats.work) runs as the
  * single kernel.
  */
 size_t trim_knn_workspace_bytes(const trim_index_view *index, int64_t nq, const trim_candidates *cand,
