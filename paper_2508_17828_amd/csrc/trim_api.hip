@@ -1070,6 +1070,7 @@ int launch_probe_ranked(const float *queries, int64_t nq, int d, const float *ce
 constexpr int64_t kFewQueries = 128, kFewQueriesWide = 256;
 constexpr double kFewLookups = 500000.0, kFewShortRows = 1.05e8, kFewNoLists = 2.5e8;
 constexpr size_t kFewBytes = size_t(1) << 30;
+constexpr int64_t kFewOnePass = 4;
 double few_pass_lookups(int64_t n, int k) {
     const double root = std::sqrt((double)n);
     if (k <= kWave) return std::min(2600.0 * (double)n, 1.05e6 * root);
@@ -1136,11 +1137,14 @@ int knn_few(const trim_index_view *ix, const FewLayout &L, const SearchArgs &a, 
     f.r_n = reinterpret_cast<int32_t *>(ws + L.off_n);
     f.r_stride = (int32_t)L.r_stride;
     if ((rc = launch_settle(f, st))) return rc;
-    // (passes begin where batches do)
+    // (passes begin where batches do)  After a short first batch, or without lists, the next eight times as far against its threshold,
+    // the rest against a better one.  With lists and up to 4 queries that saves less than two launches more: passes / one, us: 200,000 x 960, 4-bit codes, 20 of 450
+    // lists, gamma 0.5, batches of 256, 1 / 4 queries 60 / 52  76 / 70; 200,000 x 768, unit vectors, gamma 0.3 87 / 74  119 / 103; 8 at gamma 0.27, where
+    // many bounds lie about the threshold: 145 / 151, 16 180 / 208.
     const int64_t most = f.max_cand;
     for (int64_t lo = (int64_t)a.k + a.batch, hi; lo < most; lo = hi) {
         hi = most;
-        if (a.nseg == 0 || lo < 1024) {
+        if (a.nseg == 0 || (lo < 1024 && a.nq > kFewOnePass)) {
             hi = (int64_t)a.k + (lo - a.k) * 8;
             if (hi > most / 2) hi = most;
         }
