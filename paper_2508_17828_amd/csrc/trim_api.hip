@@ -839,15 +839,21 @@ int knn_in_passes(const trim_index_view *ix, const KnnLayout &L, const SearchArg
             if ((rc = launch_finish(m, pl.vec, is_fs(ix), pl.threads, pl.lds, (ns + kXcds - 1) / kXcds * kXcds, st))) return rc;
             // With lists, the first batch is measured with the pass after it: other queries have that pass's rows in their first batch, so that
             // most rows were read twice.  In passes of its own / with the next, us: 500,000 x 768 (unit vectors, 64 of 1024 lists), 2,500
-            // queries, k = 10, batches of 1024, gamma 0.6: 2063 / 1818, of 256 2679 / 2549; 211,000 x 768, 300 queries, gamma
-            // 0.35: 608 / 506, 1,600 of batches of 64 1959 / 1894; 200,000 x 960, 4-bit codes, 300: 603 / 494.
-            // The picked threshold exceeds the first batch's a little, which lets more be measured where many bounds lie just there: the same
-            // with gamma 0.3 3458 / 3493; 1,600 over 211,000 x 768, gamma 0.27: 2011 / 1997.  (With one pick per result it exceeded it by 6 to 10 %:
+            // queries, k = 10, batches of 1024, gamma 0.6: 2063 / 1818; 211,000 x 768, 300 queries, gamma 0.35: 608 / 506; 200,000 x 960, 4-bit
+            // codes, 300: 603 / 494.
+            // The picked threshold exceeds the first batch's a little, which lets more be measured where many bounds lie just there: 64
+            // picks, the same with gamma 0.3 3458 / 3493; 1,600 over 211,000 x 768, gamma 0.27: 2011 / 1997.  (One pick per result, 6 to 10 % more:
             // 3458 / 5330.)  More results take more picks than that: k = 12 3538 / 3602; with 128 picks, k = 16 2106 / 2131, 100 2783 / 3042.
             // Picks are work per query, what they save is rows read: 96 vectors a query (3,200 over 211,000 x 768 3148 / 3225; 2,300 over
             // 150,000 x 1536 1332 / 1333; with 128 picks, 2,581 over 25,664 x 960 864 / 894).  Longer batches have more to measure than to share (with 128, 4000 over
-            // 150,000 x 1536, 1,100 queries: 2586 / 2663).  Without lists the passes have no rows in common: 500 x 100,000 x 960, k = 10: 755 / 806.
-            if (lo == 0 && hi < most && a.nseg > 0 && a.k <= kPickMost && a.batch <= kPickBatch && a.nq * kPickVectors <= a.n) {
+            // 150,000 x 1536, 1,100 queries: 2586 / 2663).
+            // After a shorter batch the next pass is short too, and one pick per result will do whatever the number of queries: batches of 512, 600 over 211,000 x
+            // 768, gamma 0.27 1315 / 1207, 2,000 of 1536 over 100,000, gamma 0.25 2689 / 2585; of 256, k = 50, 400 over 100,000 x 512 424 / 396.
+            // Without lists the passes have no rows in common: 500 x 100,000 x 960, k = 10: 755 / 806.
+            const bool brief = hi < 1024;
+            if (lo == 0 && hi < most && a.nseg > 0 && a.batch <= kPickBatch &&
+                (brief ? a.k <= kPickMost || (a.k <= kPicks && a.batch >= kPickGroup * a.k) : a.k <= kPickMost && a.nq * kPickVectors <= a.n)) {
+                y.picks = brief ? a.k : kPickLong;
                 first = (int)hi;
                 y.mid = first;
                 if ((rc = launch_pick(y, st))) return rc;

@@ -1195,7 +1195,7 @@ __global__ __launch_bounds__(1024) void invert_place_kernel(const InvertArgs a) 
 }
 
 // ---- a threshold for the rest before the first batch is measured (kNN) ----
-// The kPicks vectors of the first batch with the least bounds have their exact distances taken, and of the larger of the
+// The a.picks vectors of the first batch with the least bounds have their exact distances taken, and of the larger of the
 // two, over the picks, the k-th least is no less than the k-th distance tau that the first batch will leave.  (Either all of these k survive the
 // seed's threshold and are in the running, or the bound of one exceeds that threshold, which is no less than tau.)  Any choice of picks will do
 // for that: which of the same bin of the histogram are taken is left to chance.
@@ -1204,7 +1204,7 @@ __global__ __launch_bounds__(1024) void invert_place_kernel(const InvertArgs a) 
 // gamma 0.27, first batches of 1024; 10 picks 0.79, 128 0.337, 64 and 128 groups' least 0.405 and 0.365), and elsewhere as often as below tau.
 // Bound by the rows, which neighbouring queries share: 2,500 queries over 500,000 x 768, 118 more of them cost 90 us.
 // One workgroup per query.  A candidate whose bound is no number never passes a threshold and is left out, like an infinite one; a pick whose
-// distance is no number counts as infinite, and so does what is missing where there are fewer than kPicks.
+// distance is no number counts as infinite, and so does what is missing where there are fewer.
 __global__ __launch_bounds__(kReplayThreads) void pick_kernel(const ReplayArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     int *segp = reinterpret_cast<int *>(smem + a.off_segp), *segd = reinterpret_cast<int *>(smem + a.off_segd);
@@ -1217,6 +1217,7 @@ __global__ __launch_bounds__(kReplayThreads) void pick_kernel(const ReplayArgs a
     if (row >= a.nslots) return;
     const int64_t q = a.order ? a.order[a.slot0 + row] : a.slot0 + row;
     if (q < 0 || q >= a.nq) return;
+    const int picks = a.picks;
     const int total = a.totals[row], end = total < a.mid ? total : a.mid;
     constexpr int kHeld = kPickBatch / kReplayThreads;
     static_assert(kPickBatch % kReplayThreads == 0 && kPicks <= kReplayThreads, "the first batch in registers");
@@ -1230,7 +1231,7 @@ __global__ __launch_bounds__(kReplayThreads) void pick_kernel(const ReplayArgs a
     }
     for (int t = tid; t < a.d; t += kReplayThreads) q_lds[t] = a.queries[(size_t)q * a.d + t];
     if (tid < 256) hist[tid] = 0;
-    if (tid < kPicks) { s_at[tid] = -1; s_val[tid] = __builtin_inff(); }
+    if (tid < kPicks) s_val[tid] = __builtin_inff();
     if (tid == 0) { s_low = ~0u; s_high = 0; s_n = 0; }
     segment_table_ready(a.seg, a.nseg, a.n, a.max_cand, row, segp, segd);
     uint32_t low = ~0u, high = 0;
@@ -1246,7 +1247,7 @@ __global__ __launch_bounds__(kReplayThreads) void pick_kernel(const ReplayArgs a
     for (int u = 0; u < kHeld; ++u)
         if (key[u] != ~0u) atomicAdd(&hist[(key[u] - base) >> shift], 1);
     sync_block();
-    if (tid < kWave) {                   // the bin that the kPicks-th least is in
+    if (tid < kWave) {                   // the bin that the last pick is in
         int c[4], sum = 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e) { c[e] = hist[4 * tid + e]; sum += c[e]; }
@@ -1257,11 +1258,11 @@ __global__ __launch_bounds__(kReplayThreads) void pick_kernel(const ReplayArgs a
             if (tid >= off) incl += v;
         }
         int run = incl - sum;
-        if (tid == kWave - 1 && incl < kPicks) s_bin = 255;          // (all of them)
-        if (run < kPicks && incl >= kPicks) {
+        if (tid == kWave - 1 && incl < picks) s_bin = 255;          // (all of them)
+        if (run < picks && incl >= picks) {
             int b = 4 * tid;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) { run += c[e]; if (run < kPicks) ++b; }
+            for (int e = 0; e < 4; ++e) { run += c[e]; if (run < picks) ++b; }
             s_bin = b;
         }
     }
@@ -1275,11 +1276,11 @@ __global__ __launch_bounds__(kReplayThreads) void pick_kernel(const ReplayArgs a
             const int mine = (int)((key[u] - base) >> shift);
             if (turn == 0 ? mine >= bin : mine != bin) continue;
             const int at = atomicAdd(&s_n, 1);
-            if (at < kPicks) { s_at[at] = a.k + u * kReplayThreads + tid; s_bound[at] = __uint_as_float(key[u]); }
+            if (at < picks) { s_at[at] = a.k + u * kReplayThreads + tid; s_bound[at] = __uint_as_float(key[u]); }
         }
         sync_block();
     }
-    const int n = min(s_n, kPicks);
+    const int n = min(s_n, picks);
     for (int j = half; j < n; j += kReplayThreads / 32 * 2) {
         const int j1 = j + kReplayThreads / 32;
         float d2[2];
@@ -1291,10 +1292,10 @@ __global__ __launch_bounds__(kReplayThreads) void pick_kernel(const ReplayArgs a
         }
     }
     sync_block();
-    if (tid < kPicks) {
+    if (tid < picks) {
         const float v = s_val[tid];
         int before = 0;
-        for (int j = 0; j < kPicks; ++j) before += s_val[j] < v || (s_val[j] == v && j < tid);
+        for (int j = 0; j < picks; ++j) before += s_val[j] < v || (s_val[j] == v && j < tid);
         if (before == a.k - 1) a.out_d2[(size_t)q * a.k + a.k - 1] = v;
     }
 }

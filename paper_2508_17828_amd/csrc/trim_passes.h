@@ -157,6 +157,7 @@ struct ReplayArgs {
     int32_t k, batch;
     int32_t lo, hi;             // candidates of this pass; lo == 0: R is empty
     int32_t mid;                // the first batch's end, where it is taken with the pass after it; else 0
+    int32_t picks;              // pick_kernel: vectors taken (k .. kPicks)
     const int32_t *order;       // queries that it does not name are left alone
     int64_t slot0, nslots;
     const int32_t *totals;
@@ -176,8 +177,9 @@ struct ReplayArgs {
     int32_t *counts;
     uint32_t off_segp, off_segd, off_cl, off_g, off_d2, off_id, off_rd2, off_rid, off_q, off_key, off_todo;
 };
-constexpr int kPicks = 64, kPickMost = 10, kPickBatch = 1024, kPickVectors = 96;    // pick_kernel: vectors taken, most results, largest batch, least
-                                                                                     // vectors of the index per query
+// pick_kernel: most vectors taken; those taken, most results and least vectors of the index per query where the next pass is long; largest batch; least
+// vectors of the batch per result beyond kPickMost.
+constexpr int kPicks = 128, kPickLong = 64, kPickMost = 10, kPickVectors = 96, kPickBatch = 1024, kPickGroup = 4;
 constexpr int kReplayThreads = 512, kReplayCap = 2048;   // (a power of two)
 
 // ---- few queries (trim_few.h) ----

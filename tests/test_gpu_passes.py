@@ -118,11 +118,13 @@ def test_first_batch_with_the_next_pass(T, k, batch):
     test_passes_equal_the_single_kernel(T, (16000, 768, 96, 8, 20, 280, 9, k, batch, 0.4, 0.3, 0.0))
 
 
-# pick_kernel at the edges of its rule: results, largest batch, 96 vectors a query (24,960 = 260 * 96) and one query more; batches of fewer
-# vectors than picks and than results; candidates cut before there are as many as picks, and inside the first batch
-@pytest.mark.parametrize("k,batch,nq,cut", ((1, 1, 260, 0), (10, 5, 260, 0), (10, 512, 260, 0), (11, 512, 260, 0), (3, 63, 260, 0), (3, 64, 260, 0),
+# pick_kernel at the edges of its rule: results and vectors of the batch per result; batches with which the next pass is short and not, largest
+# batch, 96 vectors a query (24,960 = 260 * 96) and one query more; batches of fewer vectors than picks and than results; candidates cut
+# before there are as many as picks, and inside the first batch
+@pytest.mark.parametrize("k,batch,nq,cut", ((1, 1, 260, 0), (10, 5, 260, 0), (10, 512, 300, 0), (11, 44, 260, 0), (11, 43, 260, 0), (128, 512, 260, 0),
+                                            (129, 516, 260, 0), (10, 1013, 260, 0), (10, 1014, 260, 0), (11, 1013, 260, 0),
                                             (10, 1024, 260, 0), (10, 1025, 260, 0), (10, 1024, 261, 0), (10, 600, 260, 1034), (10, 600, 260, 611),
-                                            (10, 1024, 260, 70), (9, 512, 260, 23)))
+                                            (10, 1024, 260, 70), (100, 400, 260, 170), (9, 512, 260, 23)))
 def test_picked_threshold(T, k, batch, nq, cut, monkeypatch):
     if cut:
         plain = T.Index._cand
@@ -222,6 +224,7 @@ def test_few_queries_equal_the_single_kernel(T, case):
     (20000, 768, 96, 8, 33, 128, 33, 65, 447, 0.2, 0.2, 0.0),
     (20000, 1536, 192, 8, 0, 9, 0, 300, 1000, 0.1, 0.2, 0.0),
     (9000, 640, 320, 4, 16, 12, 9, 1000, 3096, 0.4, 0.5, 0.0),
+    (9000, 640, 320, 4, 16, 12, 14, 1000, 3096, 0.4, 0.5, 0.0),
     (1035, 512, 32, 8, 0, 7, 0, 10, 1024, 0.2, 0.5, 0.0),
     (1034, 512, 32, 8, 0, 7, 0, 10, 1024, 0.2, 0.5, 0.0),
     (40000, 1024, 256, 8, 0, 27, 0, 128, 512, 0.3, 0.2, 0.0),
@@ -721,9 +724,9 @@ def test_thousands_of_lists(T, nlist):
         np.testing.assert_array_equal(got[name].cpu().numpy(), want[name].cpu().numpy(), err_msg=name)
 
 
-# A query with more candidates than max_candidates is cut there: inside a list, at its end, before the first batch ends.
+# A query with more candidates than max_candidates is cut there: inside a list, at its end, before the first batch ends, one candidate after it.
 @pytest.mark.parametrize("nq", (300, 20))
-@pytest.mark.parametrize("cut", (5, 31, 500, 513, 2000, 2048))
+@pytest.mark.parametrize("cut", (5, 31, 267, 500, 513, 2000, 2048))
 def test_candidates_are_cut(T, cut, nq, monkeypatch):
     import torch
     ix, q, probes = built(T, 9000, 512, 128, 8, 6, nq, 4, 0.5, 0.0, 3)
