@@ -413,13 +413,18 @@ __device__ __forceinline__ void merge_batch(float *sd2, int32_t *sid, int ns,
             cut = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sort_lanes(cmin, lane)), k - 1));
             for (int p0 = 0; p0 < ns; p0 += kPiece) {
                 if (ns > kPiece) read(p0);
+                // (256 entries are 4 a lane: a short list's merge, one of 1600 in a search of 411,000 vectors in batches of 256, stops there)
 #pragma unroll
                 for (int e0 = 0; e0 < kHeld; e0 += 8) {
+                    if (p0 + e0 * kWave >= ns) break;
                     int32_t id[8];
 #pragma unroll
                     for (int e = 0; e < 8; ++e) id[e] = v[e0 + e] <= cut && at(p0, e0 + e) < ns ? sid[at(p0, e0 + e)] : 0;
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) R.insert_pending(v[e0 + e] <= cut && at(p0, e0 + e) < ns, v[e0 + e], id[e]);
+                    for (int e = 0; e < 8; ++e) {
+                        if (e == 4 && p0 + (e0 + 4) * kWave >= ns) break;
+                        R.insert_pending(v[e0 + e] <= cut && at(p0, e0 + e) < ns, v[e0 + e], id[e]);
+                    }
                 }
             }
             ns = 0;
