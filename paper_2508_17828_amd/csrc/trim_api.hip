@@ -844,9 +844,10 @@ int knn_in_passes(const trim_index_view *ix, const KnnLayout &L, const SearchArg
             // The picked threshold exceeds the first batch's a little, which lets more be measured where many bounds lie just there: 64
             // picks, the same with gamma 0.3 3458 / 3493; 1,600 over 211,000 x 768, gamma 0.27: 2011 / 1997.  (One pick per result, 6 to 10 % more:
             // 3458 / 5330.)  More results take more picks than that: k = 12 3538 / 3602; with 128 picks, k = 16 2106 / 2131, 100 2783 / 3042.
-            // Picks are work per query, what they save is rows read: 96 vectors a query (3,200 over 211,000 x 768 3148 / 3225; 2,300 over
-            // 150,000 x 1536 1332 / 1333; with 128 picks, 2,581 over 25,664 x 960 864 / 894).  Longer batches have more to measure than to share (with 128, 4000 over
-            // 150,000 x 1536, 1,100 queries: 2586 / 2663).
+            // Picks are work per query, what they save is rows read: 32 vectors a query (665 queries over 20,232 x 1536, 30 a query, 502 / 475; 2,000 over
+            // 100,000, groups far apart, 50 a query, 1113 / 1124, 4,000 1704 / 1760; 6,000 over 211,000 x 768 gamma 0.5 3689 / 3438, gamma 0.25 7252 / 7431;
+            // 2,581 over 25,664 x 960 820 / 824). Longer batches have more to measure than to share (with 128 picks, 4000 over 150,000 x 1536, 1,100
+            // queries: 2586 / 2663).
             // After a shorter batch the next pass is short too, and one pick per result will do whatever the number of queries: batches of 512, 600 over 211,000 x
             // 768, gamma 0.27 1315 / 1207, 2,000 of 1536 over 100,000, gamma 0.25 2689 / 2585; of 256, k = 50, 400 over 100,000 x 512 424 / 396.
             // Without lists the passes have no rows in common: 500 x 100,000 x 960, k = 10: 755 / 806.
