@@ -844,17 +844,18 @@ int knn_in_passes(const trim_index_view *ix, const KnnLayout &L, const SearchArg
             // The picked threshold exceeds the first batch's a little, which lets more be measured where many bounds lie just there: 64
             // picks, the same with gamma 0.3 3458 / 3493; 1,600 over 211,000 x 768, gamma 0.27: 2011 / 1997.  (One pick per result, 6 to 10 % more:
             // 3458 / 5330.)  More results take more picks than that: k = 12 3538 / 3602; with 128 picks, k = 16 2106 / 2131, 100 2783 / 3042.
-            // Picks are work per query, what they save is rows read: 32 vectors a query (665 queries over 20,232 x 1536, 30 a query, 502 / 475; 2,000 over
-            // 100,000, groups far apart, 50 a query, 1113 / 1124, 4,000 1704 / 1760; 6,000 over 211,000 x 768 gamma 0.5 3689 / 3438, gamma 0.25 7252 / 7431;
-            // 2,581 over 25,664 x 960 820 / 824). Longer batches have more to measure than to share (with 128 picks, 4000 over 150,000 x 1536, 1,100
-            // queries: 2586 / 2663).
+            // Fewer results take fewer picks (k = 1, 32 / 64: 2,931 over 68,440 x 768 1183 / 1198).  Picks are work per query, what they save is rows read: 16
+            // vectors a query (665 queries over 20,232 x 1536, 30 a query, 502 / 475; 2,931 over 68,440 x 768, 23, 1332 / 1272; 3,255 over
+            // 61,802, 4-bit codes, 19, 1419 / 1331; 100,000 x 1536, groups far apart, 50 a query 1113 / 1124, 25 1710 / 1770, 12 3000 / 3119; 25,664 x 960, 10,
+            // 822 / 823; at gamma 0.24, where many bounds lie about the threshold, 3,548 over 188,000 x 768 3928 / 4004).  Longer batches have more to measure
+            // than to share (with 128 picks, 4000 over 150,000 x 1536, 1,100 queries: 2586 / 2663).
             // After a shorter batch the next pass is short too, and one pick per result will do whatever the number of queries: batches of 512, 600 over 211,000 x
             // 768, gamma 0.27 1315 / 1207, 2,000 of 1536 over 100,000, gamma 0.25 2689 / 2585; of 256, k = 50, 400 over 100,000 x 512 424 / 396.
             // Without lists the passes have no rows in common: 500 x 100,000 x 960, k = 10: 755 / 806.
             const bool brief = hi < 1024;
             if (lo == 0 && hi < most && a.nseg > 0 && a.batch <= kPickBatch &&
                 (brief ? a.k <= kPickMost || (a.k <= kPicks && a.batch >= kPickGroup * a.k) : a.k <= kPickMost && a.nq * kPickVectors <= a.n)) {
-                y.picks = brief ? a.k : kPickLong;
+                y.picks = brief ? a.k : std::min(kPickLong, 32 + 4 * a.k);
                 first = (int)hi;
                 y.mid = first;
                 if ((rc = launch_pick(y, st))) return rc;

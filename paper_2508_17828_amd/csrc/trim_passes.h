@@ -179,7 +179,7 @@ struct ReplayArgs {
 };
 // pick_kernel: most vectors taken; those taken, most results and least vectors of the index per query where the next pass is long; largest batch; least
 // vectors of the batch per result beyond kPickMost.
-constexpr int kPicks = 128, kPickLong = 64, kPickMost = 10, kPickVectors = 32, kPickBatch = 1024, kPickGroup = 4;
+constexpr int kPicks = 128, kPickLong = 64, kPickMost = 10, kPickVectors = 16, kPickBatch = 1024, kPickGroup = 4;
 constexpr int kReplayThreads = 512, kReplayCap = 2048;   // (a power of two)
 
 // ---- few queries (trim_few.h) ----

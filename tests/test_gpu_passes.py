@@ -119,11 +119,11 @@ def test_first_batch_with_the_next_pass(T, k, batch):
 
 
 # pick_kernel at the edges of its rule: results and vectors of the batch per result; batches with which the next pass is short and not, largest
-# batch, 32 vectors a query (24,960 = 780 * 32) and one query more; batches of fewer vectors than picks and than results; candidates cut
+# batch, 16 vectors a query (24,960 = 1560 * 16) and one query more; batches of fewer vectors than picks and than results; candidates cut
 # before there are as many as picks, and inside the first batch
 @pytest.mark.parametrize("k,batch,nq,cut", ((1, 1, 260, 0), (10, 5, 260, 0), (10, 512, 300, 0), (11, 44, 260, 0), (11, 43, 260, 0), (128, 512, 260, 0),
                                             (129, 516, 260, 0), (10, 1013, 260, 0), (10, 1014, 260, 0), (11, 1013, 260, 0),
-                                            (10, 1024, 780, 0), (10, 1025, 260, 0), (10, 1024, 781, 0), (10, 600, 260, 1034), (10, 600, 260, 611),
+                                            (10, 1024, 1560, 0), (2, 1024, 260, 0), (10, 1025, 260, 0), (10, 1024, 1561, 0), (10, 600, 260, 1034), (10, 600, 260, 611),
                                             (10, 1024, 260, 70), (100, 400, 260, 170), (9, 512, 260, 23)))
 def test_picked_threshold(T, k, batch, nq, cut, monkeypatch):
     if cut:
